@@ -75,6 +75,7 @@ struct Plan {
   int64_t max_tiles = 1;    // largest look-back tile count of a segment
   int64_t total_tiles = 1;
   int64_t max_cap = 1;      // largest list capacity of a segment
+  int32_t hist_copies = 0;  // histogram copies the segments use in h_all's memory
   int32_t total_chunks = 0; // chunks of all segments together (entries of the device chunk map), 0: no map
 };
 
@@ -309,8 +310,15 @@ int64_t seg_list_cap(int64_t n_s, int64_t k_s) {
   return cap < n_s ? cap : n_s;
 }
 
-// One segment covering the whole vector.
-Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool whole_pass_tiles = false) {
+// k_hist0's blocks add their occupied bins to a histogram of the range at about 0.1 us for each
+// same-address atomic: a range of many chunks spreads them over kHistReps copies, which cost the pick
+// about 4 us more to add up (eight selections on 25.6 M elements, 780 chunks: 0.88 ms with copies, 1.14
+// without; one on 138 M, 845 chunks: no difference.  Segments of up to 128 chunks: 5 us slower with them).
+constexpr int32_t kManyChunks = 128;
+
+// One segment covering the whole vector.  own_hist: no fused pass has built its histograms.
+Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool whole_pass_tiles = false,
+               bool own_hist = false) {
   Plan pl;
   pl.nseg = 1;
   SegDesc d{};
@@ -324,6 +332,8 @@ Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool
   d.k = (uint32_t)k;
   d.cap = c->s.cap < (uint64_t)n ? c->s.cap : (uint32_t)n;
   d.vec = vec;
+  d.hreps = own_hist && d.geom.nchunks > kManyChunks ? kHistReps : 1;
+  pl.hist_copies = d.hreps > 1 ? d.hreps : 0;
   pl.desc.push_back(d);
   pl.max_chunks = d.geom.nchunks;
   pl.max_tiles = pl.total_tiles = tiles_of_range(0, n);
@@ -364,6 +374,7 @@ int segmented_plan(artopk_ctx* c, int64_t n, int32_t nseg, const int64_t* seg_of
       d.k = (uint32_t)seg_k[sgi];
       d.cap = (uint32_t)seg_list_cap(ns, seg_k[sgi]);
       d.vec = -1;
+      d.hreps = 1;
       koff += seg_k[sgi];
       list_base += ((int64_t)d.cap + 3) / 4 * 4;
       const int64_t tiles = tiles_of_range(d.e_lo, d.e_hi);
@@ -404,6 +415,7 @@ SelParams make_params(const artopk_ctx* c, const Plan& pl, const PtrTable& tab, 
   p.tab = tab;
   p.leader_dev = s.leader_dev;
   p.n = n;
+  p.hcopies = s.h_all;
   p.h_all = hist_from_pass ? s.h_all : nullptr;
   p.mask = nullptr;
   p.mask_stride = s.mask_stride;
@@ -436,7 +448,8 @@ int enqueue_clear(artopk_ctx* c, const Plan& pl, int hist_slots, int32_t leader 
   Scratch& s = c->s;
   const size_t words1 = (size_t)pl.nseg * kSegWords;
   const size_t words2 = (size_t)pl.total_tiles * kNumLookback * 2;
-  const size_t words3 = (size_t)hist_slots * kSlotWords;
+  // (a plan with histograms of its own uses h_all's memory for their copies; no pass fills slots then)
+  const size_t words3 = hist_slots > 0 ? (size_t)hist_slots * kSlotWords : (size_t)pl.hist_copies * kHistBins;
   const size_t total = words1 + words2 + words3;
   int blocks = (int)((total + 256 * 8 - 1) / (256 * 8));
   if (blocks < 1) blocks = 1;
@@ -837,7 +850,7 @@ int enqueue_topk_workers(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t 
                          bool guessed = false) {
   Scratch& s = c->s;
   for (int32_t r = 0; r < w; ++r) {
-    const Plan pl = flat_plan(c, n, k, r, guessed);
+    const Plan pl = flat_plan(c, n, k, r, guessed, !hist_ready);
     int rc = enqueue_clear(c, pl, 0);
     if (rc) return rc;
     if ((rc = enqueue_select(c, pl, tab, n, idx_rows + (size_t)r * (size_t)k, hist_ready, 1,
@@ -1253,7 +1266,7 @@ int artopk_select_topk(artopk_ctx* ctx, const float* acc, int64_t n, int32_t nse
   if (seg_off && nseg > 1) {
     if ((rc = segmented_plan(ctx, n, nseg, seg_off, seg_k, &pl))) return rc;
   } else {
-    flat = flat_plan(ctx, n, k);
+    flat = flat_plan(ctx, n, k, -1, false, true);
   }
   if ((rc = enqueue_clear(ctx, *pl, 0, 0, nullptr))) return rc;  // the single vector is "leader 0"
   rc = enqueue_select(ctx, *pl, tab, n, idx_out, false, 0);

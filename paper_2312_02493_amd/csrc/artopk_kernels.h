@@ -144,6 +144,8 @@ struct SegDesc {
   uint32_t k;          // entries wanted
   uint32_t cap;        // survivor-list capacity of this segment
   int32_t vec;         // which vector of the pointer table to select on; -1 = the leader's
+  int32_t hreps;  // k_hist0 adds the blocks' histograms to this many copies in SelParams::hcopies (1: to the
+                  // one in the segment's scratch block)
 };
 
 // Everything the selection kernels need; blockIdx.y
@@ -152,6 +154,7 @@ struct SelParams {
   PtrTable tab;
   const int32_t* leader_dev;
   int64_t n;               // length of the vector
+  uint32_t* hcopies;       // copies of top-digit histograms that k_hist0 fills (h_all's memory, when no pass fills that)
   const uint32_t* h_all;   // [workers][kSlotWords] whole-vector histograms from the fused pass, or nullptr
   const uint64_t* mask;    // [workers][mask_stride] survivor bit masks from the fused pass, or nullptr
   int64_t mask_stride;     // 64-bit words per worker
@@ -526,8 +529,9 @@ __device__ __forceinline__ SegView seg_view(const SelParams& p, int seg, int lea
   const int vec = v.d.vec >= 0 ? v.d.vec : (leader >= 0 ? leader : *p.leader_dev);
   v.x = p.tab.p[vec];
   const size_t slot = p.slot_by_leader ? (size_t)vec : 0;  // histogram slot: per vector, or the only one
-  v.htop = p.h_all ? const_cast<uint32_t*>(p.h_all) + slot * kSlotWords : zb + kSegHtop;
-  v.htop_reps = p.h_all ? kHistReps : 1;
+  v.htop = p.h_all ? const_cast<uint32_t*>(p.h_all) + slot * kSlotWords
+                   : (v.d.hreps > 1 ? p.hcopies : zb + kSegHtop);
+  v.htop_reps = p.h_all ? kHistReps : v.d.hreps;
   v.hseg = zb + kSegHtop;
   v.ctrl = p.h_all ? p.h_all + slot * kSlotWords + kSlotCtrl : nullptr;
   v.mask = p.mask ? p.mask + slot * (size_t)p.mask_stride : nullptr;
@@ -1297,9 +1301,11 @@ k_guess_refine(uint32_t* __restrict__ slots, const uint32_t* __restrict__ sample
 // ---------------------------------------------------------------------------
 // k_hist0 : per-chunk top-digit suffix histograms of |x[e_lo .. e_hi)| for the
 // leader's vector.  grid = (max chunks of a segment, segments), block = T (1024:
-// there are at most about a thousand blocks, so a block must keep many loads in flight).
-// Whole aligned float4 groups are read where they lie inside the array, single
-// elements at its ragged end; elements outside the chunk are masked out.
+// there are at most about a thousand blocks, so a block must keep many loads in flight:
+// eight float4 groups a thread, unconditional; four behind conditions took 137 us on
+// 138 M elements, these 116).  Whole float4 groups of the chunk are read as such, the at
+// most three elements before and behind them one by one.  Bound by the chip's memory and
+// then by the on-chip atomics (more copies of the block's histogram changed nothing).
 // ---------------------------------------------------------------------------
 // The guess did not hold after a fused pass that handed marked elements on per tile and stored
 // +0.0 in their place: the block that owns chunk c puts the values of its tiles' pieces back into
@@ -1324,6 +1330,7 @@ __device__ __forceinline__ void restore_pieces(const SelParams& p, const SegView
 
 template <int T>
 __device__ __forceinline__ void hist0_body(const SelParams& p) {
+  constexpr int U = 8;  // float4 groups a thread has in flight
   __shared__ __attribute__((aligned(16))) uint32_t lh[kHistBins];
   __shared__ uint32_t red_u[T];
   int seg, c;
@@ -1340,38 +1347,47 @@ __device__ __forceinline__ void hist0_body(const SelParams& p) {
   int64_t ce = cs + sv.d.geom.chunk_elems;
   if (cs < sv.d.e_lo) cs = sv.d.e_lo;
   if (ce > sv.d.e_hi) ce = sv.d.e_hi;
-  const int64_t n_vec = p.n & ~(int64_t)3;
-  const int64_t q_lo = cs >> 2;
-  const int64_t q_hi = (ce + 3) >> 2;  // exclusive
-  for (int64_t q0 = q_lo + tid; q0 < q_hi; q0 += T * 4) {
-    uint4 v[4];
+  auto count = [&](uint32_t raw) { atomicAdd(&lh[(raw & kKeyMask) >> 19], 1u); };
+  const int64_t q_lo = (cs + 3) >> 2, q_hi = ce >> 2;  // whole float4 groups of the chunk
+  if (q_lo < q_hi) {
+    int64_t q0 = q_lo;
+    for (; q0 + T * U <= q_hi; q0 += T * U) {
+      uint4 v[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {  // whole groups inside the array are read as one vector
-      const int64_t j = (q0 + u * T) << 2;
-      v[u] = make_uint4(0u, 0u, 0u, 0u);
-      if (q0 + u * T < q_hi) {
-        if (j + 4 <= n_vec) {
-          v[u] = *reinterpret_cast<const uint4*>(xp + j);
-        } else {
-          v[u].x = (j + 0 < p.n) ? __float_as_uint(xp[j + 0]) : 0u;
-          v[u].y = (j + 1 < p.n) ? __float_as_uint(xp[j + 1]) : 0u;
-          v[u].z = (j + 2 < p.n) ? __float_as_uint(xp[j + 2]) : 0u;
-          v[u].w = (j + 3 < p.n) ? __float_as_uint(xp[j + 3]) : 0u;
+      for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4*>(xp + 4 * (q0 + tid + u * T));
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        count(v[u].x);
+        count(v[u].y);
+        count(v[u].z);
+        count(v[u].w);
+      }
+    }
+    if (q0 < q_hi) {
+      uint4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {  // (no branch around the loads: behind the chunk they re-read its last group)
+        const int64_t q = q0 + tid + u * T;
+        v[u] = *reinterpret_cast<const uint4*>(xp + 4 * (q < q_hi ? q : q_hi - 1));
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (q0 + tid + u * T < q_hi) {
+          count(v[u].x);
+          count(v[u].y);
+          count(v[u].z);
+          count(v[u].w);
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t j = (q0 + u * T) << 2;
-      if (q0 + u * T < q_hi) {
-        const uint32_t kk[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (j + e >= cs && j + e < ce) atomicAdd(&lh[(kk[e] & kKeyMask) >> 19], 1u);
-      }
-    }
+    // the chunk's first and last elements outside whole groups (at most three each)
+    const int64_t j = tid < 4 ? cs + tid : 4 * q_hi + (tid - 4);
+    if (tid < 8 && j < (tid < 4 ? 4 * q_lo : ce)) count(__float_as_uint(xp[j]));
+  } else if (cs + tid < ce) {  // not one whole group: at most six elements
+    count(__float_as_uint(xp[cs + tid]));
   }
-  flush_suffix_hist<T>(lh, red_u, sv.S + (size_t)c * kHistBins, sv.htop);
+  flush_suffix_hist<T>(lh, red_u, sv.S + (size_t)c * kHistBins,
+                       sv.htop + (size_t)(c % sv.htop_reps) * kHistBins);
 }
 
 template <int T>
@@ -1557,11 +1573,13 @@ k_pick0(SelParams p, LeaderArgs la) {
       }
     }
   } else {
-    const uint4 q = reinterpret_cast<const uint4*>(htop)[t];
-    h[0] = q.x;
-    h[1] = q.y;
-    h[2] = q.z;
-    h[3] = q.w;
+    for (int r = 0; r < htop_reps; ++r) {
+      const uint4 q = reinterpret_cast<const uint4*>(htop + (size_t)r * kHistBins)[t];
+      h[0] += q.x;
+      h[1] += q.y;
+      h[2] += q.z;
+      h[3] += q.w;
+    }
   }
   const uint32_t hsum = h[0] + h[1] + h[2] + h[3];
   uint32_t sx[5];

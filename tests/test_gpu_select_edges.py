@@ -1,0 +1,58 @@
+"""The selection at the sizes where its kernels' tiles, chunks and copies meet: against the oracle, bit for bit."""
+
+import numpy as np
+import pytest
+
+from oracle import artopk_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _values(rng, n, kind):
+    x = (rng.standard_normal(n) * 0.01).astype(np.float32)
+    if kind == "ties":
+        x[rng.integers(0, n, n // 3)] = np.float32(-0.0125)
+    elif kind == "special":  # infinities, NaN, zeros and the smallest denormal
+        x[rng.integers(0, n, 40)] = np.inf
+        x[rng.integers(0, n, 40)] = -np.nan
+        x[rng.integers(0, n, n // 4)] = 0.0
+        x[rng.integers(0, n, n // 4)] = np.float32(1e-45)
+    return x
+
+
+# one chunk more than a single copy of the whole-range histogram serves, one less, a ragged last group, the
+# largest vector whose list holds everything and one element more, one tile of the fused pass and its neighbours
+@pytest.mark.parametrize("n", [32767, 32769, 128 * 8192, 128 * 8192 + 1, 129 * 8192 + 3, (1 << 22), (1 << 22) + 5])
+@pytest.mark.parametrize("kind", ["normal", "ties", "special"])
+def test_stand_alone_selection(n, kind):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    rng = np.random.default_rng(n)
+    x = _values(rng, n, kind)
+    xd = torch.from_numpy(x).cuda()
+    ctx = lib.Context(1, n, n // 2)
+    for k in (1, n // 700 + 1, n // 9, n // 2):
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        ctx.artopk_select_topk(xd, k, idx)
+        ctx.status()
+        assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x, k)), (n, k)
+
+
+@pytest.mark.parametrize("start", [0, 1, 2, 3, 5, 8191])
+def test_segments_that_begin_and_end_inside_a_group(start):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    rng = np.random.default_rng(start)
+    sizes = ([start] if start else []) + [1, 2, 3, 4, 5, 6, 7, 8, 9, 8190, 8193, 2, 32766, 32771, 1, 300_001, 3]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(off[-1])
+    x = _values(rng, n, "ties")
+    ks = [max(1, s // 3) for s in sizes]
+    xd = torch.from_numpy(x).cuda()
+    ctx = lib.Context(1, n, sum(ks), max_segments=len(sizes))
+    idx = torch.full((sum(ks),), -1, dtype=torch.int32, device="cuda")
+    ctx.artopk_select_topk(xd, sum(ks), idx, seg_off=[int(o) for o in off], seg_k=ks)
+    ctx.status()
+    assert np.array_equal(idx.cpu().numpy(), orc.topk_indices_segmented(x, [int(o) for o in off], ks))
