@@ -1684,25 +1684,34 @@ k_pick_mask(SelParams p, LeaderArgs la) {
 // row-coalesced ones here), so a survivor's rank is the lane's exclusive prefix
 // plus its position among the lane's own survivors: five or six ballots per
 // tile instead of one per element.
+//   Bound by instructions issued, not by memory: with the survivors handled where
+// they are found (sixteen predicated blocks a lane, run by every wave as soon as one of
+// its lanes has any) the kernel took 152 us on 138 M elements and 42 on 25.6 M in 54
+// segments.  Now a lane only lists its survivors' places on chip and the wave then
+// takes them one per lane, values from the tile's on-chip copy: 141 and 34.5 us.
+// Shapes (138 M select, whole call): 8 waves x 16 elements 303 us, 8 x 8 325, 4 x 16
+// 333, 16 x 16 310, 16 x 8 328.
 // ---------------------------------------------------------------------------
 constexpr int kC1Waves = 4, kC1R = 4;  // (flat vectors on the histogram route take 8 waves)
 
 template <int WAVES, int R>
 __device__ __forceinline__ void compact1_body(const SelParams& p) {
   constexpr int T = 64 * WAVES;
-  constexpr int E = 4 * R;             // consecutive elements one lane owns in a tile
+  constexpr int E = 4 * R;             // consecutive elements one lane owns in a tile (a power of two)
   constexpr int WSPAN = 64 * E;        // consecutive elements one wave owns in a tile
   constexpr int TILE = WAVES * WSPAN;  // elements per block iteration
   static_assert(E <= 32, "one 32-bit mask per lane");
   __shared__ uint32_t lh[kHistBins];
   __shared__ uint32_t wtot[2][WAVES];
+  __shared__ __attribute__((aligned(16))) uint32_t tile_raw[WAVES][WSPAN];  // a wave's tile, group r of lane l at 256 r + 4 l
+  __shared__ uint16_t tile_pos[WAVES][WSPAN];                               // its survivors' places in the wave's tile
 
   int seg, c;
   block_chunk(p, seg, c);
   const SegView sv = seg_view(p, seg);
   if (c >= sv.d.geom.nchunks) return;
   const int tid = threadIdx.x;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t lane = lane_id();
   const int64_t n = p.n, e_lo = sv.d.e_lo, e_hi = sv.d.e_hi;
   const ChunkGeom geom = sv.d.geom;
@@ -1805,44 +1814,40 @@ __device__ __forceinline__ void compact1_body(const SelParams& p) {
       }
       buf ^= 1;
     }
-    if (own != 0u) {  // few lanes get here
-      uint32_t pos = base + before;
+    if (wsum != 0u) {
+      uint32_t* __restrict__ traw = tile_raw[wave];
+      uint16_t* __restrict__ tpos = tile_pos[wave];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if ((own >> e) & 1u) {
-          const uint32_t kk = raw[e] & kKeyMask;
-          if (kk <= khi) atomicAdd(&lh[(kk >> 7) & 0xfffu], 1u);  // candidate: feeds the next digit
-          // (index, raw bits): the sign travels with the survivor
-          if (write_out && pos < cap) list[pos] = make_uint2((uint32_t)(j0 + e), raw[e]);
-          ++pos;
-        }
+      for (int r = 0; r < R; ++r)
+        reinterpret_cast<uint4*>(traw)[r * 64 + lane] =
+            make_uint4(raw[4 * r + 0], raw[4 * r + 1], raw[4 * r + 2], raw[4 * r + 3]);
+      // every lane lists its survivors; few lanes have more than one or two
+      uint32_t pos = before;
+      for (uint32_t left = own; left != 0u; left &= left - 1u) {
+        tpos[pos] = (uint16_t)(lane * E + (uint32_t)__builtin_ctz(left));
+        ++pos;
       }
-      // Keys above the threshold digit are kept whatever the later digits say: if asked to, put
-      // +0.0 there now, while the group is in registers (the list carries the values on).  Only
-      // when the list is written here, because the deeper array passes would re-read the vector.
-      if (zero_out) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          uint32_t z[4];
-          uint32_t hit = 0u;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bool a = ((own >> (4 * r + e)) & 1u) && (raw[4 * r + e] & kKeyMask) > khi;
-            z[e] = a ? 0u : raw[4 * r + e];
-            hit |= a ? (1u << e) : 0u;
-          }
-          if (hit) {  // (rewriting the lane's whole 64 bytes instead was measured slower)
-            const int64_t j = j0 + 4 * r;
-            if (clean && j + 4 <= n_vec) {
-              *reinterpret_cast<uint4*>(p.zero_vec + j) = make_uint4(z[0], z[1], z[2], z[3]);
-            } else {  // at a chunk's edge a group may hold a neighbour's elements
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if ((hit >> e) & 1u) p.zero_vec[j + e] = 0.0f;
-            }
-          }
-        }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      // then the wave takes them one per lane: list entries go out side by side
+      for (uint32_t i = lane; i < wsum; i += 64u) {
+        const uint32_t q = tpos[i];  // element q of the wave's tile: lane q / E, group (q / 4) mod R
+        const uint32_t w = traw[((q >> 2) & (uint32_t)(R - 1)) * 256u + (q / E) * 4u + (q & 3u)];
+        const uint32_t kk = w & kKeyMask;
+        const uint32_t j = (uint32_t)(tb + (int64_t)wave * WSPAN) + q;
+        // (index, raw bits): the sign travels with the survivor
+        if (write_out && base + i < cap) list[base + i] = make_uint2(j, w);
+        if (kk <= khi)
+          atomicAdd(&lh[(kk >> 7) & 0xfffu], 1u);  // candidate: feeds the next digit
+        else if (zero_out)
+          // Keys above the threshold digit are kept whatever the later digits say: if asked to, put
+          // +0.0 there now (the list carries the values on).  Only when the list is written here,
+          // because the deeper array passes would re-read the vector.
+          p.zero_vec[j] = 0.0f;
       }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();  // (the next tile overwrites the wave's stage)
     }
     if (more) {
 #pragma unroll
