@@ -764,21 +764,31 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   if (always_fits) {
     hipLaunchKernelGGL(k_list_hist, dim3((unsigned)lblocks, nseg), dim3(256), 0, st, p, 2);
   } else if (long_list) {
-    hipLaunchKernelGGL(k_compact<false>, dim3(cblocks, nseg), dim3(kCompactThreads), 0, st, p, 2, 0);
+    hipLaunchKernelGGL(k_compact, dim3(cblocks, nseg), dim3(kCompactThreads), 0, st, p);
     hipLaunchKernelGGL(k_list_hist, dim3((unsigned)lblocks, nseg), dim3(256), 0, st, p, 2);
   } else {  // the same launch is the level-2 array pass where the level-1 survivors did not fit the list
     const int64_t b2 = lblocks > cblocks ? lblocks : cblocks;
     hipLaunchKernelGGL(k_level2, dim3((unsigned)b2, nseg), dim3(kCompactThreads), 0, st, p);
   }
-  int64_t ltiles = (pl.max_cap + kCompactTile - 1) / kCompactTile;
+  int64_t k_all = 0;
+  for (const SegDesc& d : pl.desc) k_all += d.k;
+  const bool many = k_all > ((int64_t)1 << 19);
+  const int64_t ltile = kCompactThreads * (many ? 16 : 8);
+  int64_t ltiles = (pl.max_cap + ltile - 1) / ltile;
   int fblocks = (int)(ltiles < per_seg ? ltiles : per_seg);
   if (fblocks < 1) fblocks = 1;
-  if (always_fits) {
-    hipLaunchKernelGGL(k_compact<true>, dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p, 3, 2);
-  } else {  // the same launch is the level-3 array pass where no list could be written
-    if (fblocks < cblocks) fblocks = cblocks;
-    hipLaunchKernelGGL(k_final, dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
-  }
+  // (the same launch is the level-3 array pass where no list could be written)
+  if (!always_fits && fblocks < cblocks) fblocks = cblocks;
+  // entries a lane takes of the list: 8 up to half a million kept, 16 beyond (measured on both sides, see
+  // list_final_body: 255 k entries 11 against 13 us, 1.4 million 26 against 19)
+  if (always_fits && !many)
+    hipLaunchKernelGGL((k_final<true, 8>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
+  else if (always_fits)
+    hipLaunchKernelGGL((k_final<true, 16>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
+  else if (!many)
+    hipLaunchKernelGGL((k_final<false, 8>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
+  else
+    hipLaunchKernelGGL((k_final<false, 16>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
   HIP_TRY(c, hipGetLastError());
   return ARTOPK_OK;
 }

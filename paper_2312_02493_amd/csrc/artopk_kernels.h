@@ -22,8 +22,7 @@
 //   k_mask_or_hist   the survivor list written from the mask instead; or, after
 //                    a guess that did not hold, k_hist0's work in the same launch
 //   k_compact        ordered compaction with a decoupled look-back scan: the
-//                    rarely needed deeper array passes and the final pass over
-//                    the survivor list
+//                    rarely needed deeper array pass
 //   k_list_hist      digit histograms over the survivor list
 //   k_level1 / k_level2 / k_final   the launches behind the first pick where
 //                    alternatives exist: each does whichever of two jobs the state
@@ -125,7 +124,9 @@ constexpr int kSegHist1 = 32;                      // next-digit histogram, digi
 constexpr int kSegHist2 = kSegHist1 + kHistBins;   // next-digit histogram, digit 2
 constexpr int kSegHtop = kSegHist2 + kHistBins;    // top-digit histogram (when built by k_hist0)
 constexpr int kSegWords = kSegHtop + kHistBins;
-constexpr int kNumLookback = 4;                    // flag words per tile: array level 2, 3, list pass, spare
+// Look-back flag words per 16384 elements: one of the array passes at level 2 and at level 3, four of the
+// final list pass (whose tiles are 4096 entries).
+constexpr int kNumLookback = 6;
 
 struct ChunkGeom {
   int64_t chunk0;       // first element of chunk 0 (a multiple of kTile, <= range start)
@@ -1419,11 +1420,16 @@ __device__ void block_pick(SelState& st, const uint32_t* __restrict__ hist, int 
   const int nbins = (int)digit_mask(digit) + 1;
   uint32_t h[BPT];
   uint32_t tot = 0u;
+  static_assert(BPT % 4 == 0, "whole uint4 groups per thread");
 #pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    const int b = BPT * t + j;
-    h[j] = (b < nbins) ? hist[b] : 0u;
-    tot += h[j];
+  for (int j = 0; j < BPT / 4; ++j) {
+    uint4 q = make_uint4(0u, 0u, 0u, 0u);
+    if (BPT * t < nbins) q = reinterpret_cast<const uint4*>(hist)[(BPT / 4) * t + j];  // (nbins is a multiple of BPT)
+    h[4 * j + 0] = q.x;
+    h[4 * j + 1] = q.y;
+    h[4 * j + 2] = q.z;
+    h[4 * j + 3] = q.w;
+    tot += (q.x + q.y) + (q.z + q.w);
   }
   __syncthreads();  // st is stable and `part` is free
   uint32_t total;
@@ -2213,14 +2219,21 @@ __device__ __forceinline__ void flag_store(uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ uint64_t lookback_exclusive(uint64_t* __restrict__ flags, int flag_stride, int64_t tile,
-                                       uint64_t agg, uint32_t* __restrict__ err) {
+// Flag word of a tile: `flags` + 0 or 1 for the array passes, the words behind those for the list pass.
+template <bool LIST>
+__device__ __forceinline__ uint64_t* flag_word(uint64_t* flags, int64_t tile) {
+  return LIST ? flags + (tile >> 2) * kNumLookback + 2 + (tile & 3) : flags + tile * kNumLookback;
+}
+
+template <bool LIST>
+__device__ uint64_t lookback_exclusive(uint64_t* __restrict__ flags, int64_t tile, uint64_t agg,
+                                       uint32_t* __restrict__ err) {
   const uint32_t lane = lane_id();
   if (tile == 0) {
-    if (lane == 0) flag_store(&flags[0], kFlagIncl | agg);
+    if (lane == 0) flag_store(flag_word<LIST>(flags, 0), kFlagIncl | agg);
     return 0ull;
   }
-  if (lane == 0) flag_store(&flags[tile * flag_stride], kFlagAgg | agg);
+  if (lane == 0) flag_store(flag_word<LIST>(flags, tile), kFlagAgg | agg);
   uint64_t excl = 0ull;     // wave-uniform running total
   int64_t base = tile - 1;  // lane L inspects tile base - L
   while (true) {
@@ -2228,7 +2241,7 @@ __device__ uint64_t lookback_exclusive(uint64_t* __restrict__ flags, int flag_st
     uint64_t word = kFlagIncl;  // tiles before the first act as an inclusive prefix of zero
     if (my >= 0) {
       int spins = 0;
-      word = flag_load(&flags[my * flag_stride]);
+      word = flag_load(flag_word<LIST>(flags, my));
       while ((word >> 62) == 0ull) {
         if (++spins > kSpinLimit) {
           atomicOr(err, kErrWait);
@@ -2236,7 +2249,7 @@ __device__ uint64_t lookback_exclusive(uint64_t* __restrict__ flags, int flag_st
           break;
         }
         __builtin_amdgcn_s_sleep(2);
-        word = flag_load(&flags[my * flag_stride]);
+        word = flag_load(flag_word<LIST>(flags, my));
       }
     }
     const uint64_t incl_mask = __ballot((word >> 62) == 2ull);
@@ -2250,7 +2263,7 @@ __device__ uint64_t lookback_exclusive(uint64_t* __restrict__ flags, int flag_st
     excl += wave_allsum_u64(contrib);
     base -= 64;
   }
-  if (lane == 0) flag_store(&flags[tile * flag_stride], kFlagIncl | ((excl + agg) & kFlagValMask));
+  if (lane == 0) flag_store(flag_word<LIST>(flags, tile), kFlagIncl | ((excl + agg) & kFlagValMask));
   return excl;
 }
 
@@ -2262,15 +2275,11 @@ __device__ uint64_t lookback_exclusive(uint64_t* __restrict__ flags, int flag_st
 //        (#A before it) + min(#B before it, quota)
 //   which is ascending in element order.  quota = infinity below level 3.
 //
-//   SRC_ARRAY (LIST = false): elements are x[e_lo .. e_hi) of the selected
-//     vector, kept entries go to the survivor list as (index, bits).  Level 2
-//     runs when the level-1 survivors did not fit the list, level 3 when the
-//     level-2 ones did not either; a pass writes the list only if it fits
-//     (otherwise it only feeds the next digit histogram).
-//   SRC_LIST (LIST = true): elements are the survivor list, kept entries'
-//     indices go to idx_out[0 .. k) and, if vals_row is given, their values
-//     (the list carries the raw float bits) to vals_row[0 .. k).  Requires
-//     level 3.
+//   Elements are x[e_lo .. e_hi) of the selected vector, kept entries go to the
+//   survivor list as (index, bits).  Level 2 runs when the level-1 survivors did
+//   not fit the list, level 3 when the level-2 ones did not either; a pass writes
+//   the list only if it fits (otherwise it only feeds the next digit histogram).
+//   The pass over the list itself is list_final_body.
 //
 //   block = 512 threads = 8 waves; a tile is 8 waves x 8 rows x 64 lanes x 4
 //   consecutive elements, each wave owning a contiguous 2048-element piece.
@@ -2283,20 +2292,18 @@ constexpr int kWaveSpan = 64 * 4 * kCompactRows;                  // 2048 elemen
 // The pass itself; st is the state derived for it (in shared memory, the same in every thread).
 // DIRECT (array source, level 3): the kept entries go straight to idx_out / vals_row (and are put
 // to +0.0 in zero_vec) instead of into the list, so no pass over the list has to follow.
-template <bool LIST, bool DIRECT>
+template <bool DIRECT>
 __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& sv, const SelState& st, int level,
                                              int launch_id, uint32_t zero_below) {
-  static_assert(!(LIST && DIRECT), "DIRECT is a form of the array pass");
-  __shared__ uint32_t lh[(!LIST && !DIRECT) ? kHistBins : 4];
+  __shared__ uint32_t lh[!DIRECT ? kHistBins : 4];
   __shared__ uint64_t wave_tot[8];
   __shared__ uint64_t tile_excl;
   __shared__ int64_t tile_sh;
 
-  int64_t n = p.n, e_lo = sv.d.e_lo, e_hi = sv.d.e_hi;
+  const int64_t n = p.n, e_lo = sv.d.e_lo, e_hi = sv.d.e_hi;
   const uint32_t cap = sv.d.cap;
   uint32_t* __restrict__ hist_next = sv.hist2;
   uint64_t* __restrict__ flags = sv.flags + launch_id;
-  constexpr int flag_stride = kNumLookback;
   uint32_t* __restrict__ tile_counter = sv.counters + launch_id;
   uint2* __restrict__ list = sv.list;
   int32_t* __restrict__ idx_out = sv.idx_out;
@@ -2311,38 +2318,19 @@ __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& 
   // With zeroing on the way: the level-1 pass zeroed the keys above its range if it wrote the
   // list (zero_below = the top of that range); the pass that writes idx_out zeroes the kept rest,
   // or all of them otherwise (zero_below = every key).
-  float* __restrict__ zero_vec = (LIST || DIRECT) ? p.zero_vec : nullptr;
-  bool write_out;
-  bool do_hist;
-  uint32_t quota;
-  int64_t first_tile, ntiles;
-  if (!LIST) {
-    // level 2 runs whenever level 1 did not fit; level 3 only if level 2 did not fit either
-    if (level == 3 && st.compact_level != 3u) return;
-    quota = (level == 3) ? st.need : kQuotaInf;
-    write_out = st.compact_level == (uint32_t)level;
-    do_hist = level < 3 && !DIRECT;
-    first_tile = e_lo / kCompactTile;
-    ntiles = (e_hi + kCompactTile - 1) / kCompactTile - first_tile;
-  } else {
-    if (st.level != 3u) {
-      if (tid == 0 && blockIdx.x == 0) atomicOr(err, kErrSequence);
-      return;
-    }
-    quota = st.need;
-    write_out = true;
-    do_hist = false;
-    e_lo = 0;
-    e_hi = (int64_t)st.list_count;
-    n = (int64_t)cap;  // list arrays are allocated with cap rounded up to a whole tile
-    first_tile = 0;
-    ntiles = (e_hi + kCompactTile - 1) / kCompactTile;
-  }
+  float* __restrict__ zero_vec = DIRECT ? p.zero_vec : nullptr;
+  // level 2 runs whenever level 1 did not fit; level 3 only if level 2 did not fit either
+  if (level == 3 && st.compact_level != 3u) return;
+  const uint32_t quota = (level == 3) ? st.need : kQuotaInf;
+  const bool write_out = st.compact_level == (uint32_t)level;
+  const bool do_hist = level < 3 && !DIRECT;
+  const int64_t first_tile = e_lo / kCompactTile;
+  const int64_t ntiles = (e_hi + kCompactTile - 1) / kCompactTile - first_tile;
   const uint32_t klo = st.lo, khi = st.hi;
   const int dshift = digit_shift(level < 3 ? level : 2);
   const uint32_t dmask = digit_mask(level < 3 ? level : 2);
 
-  const float* __restrict__ xp = LIST ? nullptr : sv.x;
+  const float* __restrict__ xp = sv.x;
 
   if (do_hist) {
     for (int b = tid; b < kHistBins; b += kCompactThreads) lh[b] = 0u;
@@ -2356,27 +2344,15 @@ __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& 
     if (trel >= ntiles) break;
     const int64_t tbase = (first_tile + trel) * kCompactTile + (int64_t)wave * kWaveSpan;
 
-    // ---- load keys (and list payloads) --------------------------------
+    // ---- load keys ------------------------------------------------------
     uint32_t key[kCompactRows][4];
-    int32_t pay[LIST ? kCompactRows : 1][4];
     uint32_t valid = 0u;  // bit (r*4+e)
     const bool full = (tbase >= e_lo) && (tbase + kWaveSpan <= e_hi) && (tbase + kWaveSpan <= (n & ~(int64_t)3));
     if (full) {
 #pragma unroll
       for (int r = 0; r < kCompactRows; ++r) {
         const int64_t j = tbase + (int64_t)r * 256 + (int64_t)lane * 4;
-        uint4 v;
-        if (!LIST) {
-          v = *reinterpret_cast<const uint4*>(xp + j);
-        } else {
-          const uint4 e01 = reinterpret_cast<const uint4*>(list + j)[0];  // (idx, bits) x 2
-          const uint4 e23 = reinterpret_cast<const uint4*>(list + j)[1];
-          v = make_uint4(e01.y, e01.w, e23.y, e23.w);
-          pay[LIST ? r : 0][0] = (int32_t)e01.x;
-          pay[LIST ? r : 0][1] = (int32_t)e01.z;
-          pay[LIST ? r : 0][2] = (int32_t)e23.x;
-          pay[LIST ? r : 0][3] = (int32_t)e23.z;
-        }
+        const uint4 v = *reinterpret_cast<const uint4*>(xp + j);
         key[r][0] = v.x;  // raw bits; comparisons mask the sign off
         key[r][1] = v.y;
         key[r][2] = v.z;
@@ -2390,16 +2366,9 @@ __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& 
         for (int e = 0; e < 4; ++e) {
           const int64_t j = tbase + (int64_t)r * 256 + (int64_t)lane * 4 + e;
           key[r][e] = 0u;
-          if (LIST) pay[LIST ? r : 0][e] = 0;
           if (j >= e_lo && j < e_hi) {
             valid |= 1u << (r * 4 + e);
-            if (!LIST) {
-              key[r][e] = __float_as_uint(xp[j]);
-            } else {
-              const uint2 ent = list[j];
-              key[r][e] = ent.y;
-              pay[LIST ? r : 0][e] = (int32_t)ent.x;
-            }
+            key[r][e] = __float_as_uint(xp[j]);
           }
         }
       }
@@ -2431,7 +2400,7 @@ __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& 
         uint64_t agg = 0ull;
 #pragma unroll
         for (int i = 0; i < 8; ++i) agg += wave_tot[i];
-        const uint64_t ex = lookback_exclusive(flags, flag_stride, trel, agg, err);
+        const uint64_t ex = lookback_exclusive<false>(flags, trel, agg, err);
         if (lane == 0) tile_excl = ex;
       }
       __syncthreads();
@@ -2466,24 +2435,14 @@ __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& 
               if (a || (b && befB < quota)) {
                 const uint32_t pos = befA + (befB < quota ? befB : quota);
                 const int64_t j = tbase + (int64_t)r * 256 + (int64_t)lane * 4 + e;
-                if (!LIST && DIRECT) {
+                if (DIRECT) {
                   if (pos < k_out) {
                     idx_out[pos] = (int32_t)j;
                     if (vals_row) vals_row[pos] = __uint_as_float(key[r][e]);
                     if (zero_vec && ((key[r][e] & kKeyMask) <= zero_below) && j < p.n) zero_vec[j] = 0.0f;
                   }
-                } else if (!LIST) {
-                  if (pos < cap) list[pos] = make_uint2((uint32_t)j, key[r][e]);
-                } else {
-                  if (pos < k_out) {
-                    idx_out[pos] = pay[LIST ? r : 0][e];
-                    if (vals_row) vals_row[pos] = __uint_as_float(key[r][e]);
-                    // kept entries that nothing has put to +0.0 yet
-                    if (zero_vec && ((key[r][e] & kKeyMask) <= zero_below)) {
-                      const int32_t zi = pay[LIST ? r : 0][e];
-                      if (zi >= 0 && (int64_t)zi < p.n) zero_vec[zi] = 0.0f;
-                    }
-                  }
+                } else if (pos < cap) {
+                  list[pos] = make_uint2((uint32_t)j, key[r][e]);
                 }
               }
               befA += a ? 1u : 0u;
@@ -2507,6 +2466,134 @@ __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& 
   }
 }
 
+// ---------------------------------------------------------------------------
+// list_final_body : the final pass over the survivor list.  Kept entries (the two classes
+// above, with the tie quota) go to idx_out[0 .. k) in list order, their values (the list
+// carries the raw bits) to vals_row, and +0.0 to zero_vec where the key is <= zero_below.
+//   Bound by its chain of dependent steps, not by bytes: lists are short (k entries and some),
+// so tiles are small (512 threads of PER consecutive entries) to spread them over the chip; ranks
+// come from the bit planes of the lanes' counts (eight or ten ballots a tile); the kept entries are
+// collected on chip and stored side by side.  The form before it (16384 entries a tile, 128
+// ballots, entries stored from where they are found) took 20 us on 12 thousand entries, 20 on
+// 120 thousand, 22.5 on 1.4 million, 95 on 14.5 million; this one 9 / 11 / 26 / 105 with PER = 8
+// and 12 / 13 / 19 / 92 with 16: the more tiles, the longer the walk back over their flags takes
+// (more tiles per step of that walk, or more blocks at once, made it slower, not faster).
+// Tiles come from a counter, so that a block never waits for one that has not started.
+// ---------------------------------------------------------------------------
+constexpr int kListTile = kCompactThreads * 8;  // the smallest tile: 4096 entries
+static_assert(kCompactTile == 4 * kListTile, "four flag words of the list pass per array tile");
+
+template <int PER>
+__device__ __forceinline__ void list_final_body(const SelParams& p, const SegView& sv, const SelState& st,
+                                                uint32_t zero_below, int64_t tile) {
+  constexpr int T = kCompactThreads, WAVES = T / 64, TILE = T * PER;
+  __shared__ uint2 stage[TILE];
+  __shared__ uint64_t wave_tot[WAVES];
+  __shared__ uint64_t tile_excl;
+  __shared__ int64_t tile_sh;
+
+  const int tid = threadIdx.x;
+  const int wave = tid >> 6;
+  const uint32_t lane = lane_id();
+  uint64_t* __restrict__ flags = sv.flags;
+  uint32_t* __restrict__ tile_counter = sv.counters + 2;
+  const uint2* __restrict__ list = sv.list;
+  int32_t* __restrict__ idx_out = sv.idx_out;
+  float* __restrict__ vals_row = sv.vals_row;
+  float* __restrict__ zero_vec = p.zero_vec;
+  const uint32_t k_out = sv.d.k;
+  uint32_t* __restrict__ err = p.err;
+  if (st.level != 3u) {
+    if (tid == 0 && blockIdx.x == 0) atomicOr(err, kErrSequence);
+    return;
+  }
+  const uint32_t quota = st.need, klo = st.lo, khi = st.hi, count = st.list_count;
+  const int64_t ntiles = ((int64_t)count + TILE - 1) / TILE;
+
+  while (tile < ntiles) {
+    const uint32_t q0 = (uint32_t)(tile * TILE) + (uint32_t)tid * PER;
+    // (the list's memory goes on for a whole tile behind its last entry)
+    uint32_t raw[PER], ind[PER];
+#pragma unroll
+    for (int i = 0; i < PER / 2; ++i) {
+      const uint4 v = reinterpret_cast<const uint4*>(list + q0)[i];
+      ind[2 * i] = v.x;
+      raw[2 * i] = v.y;
+      ind[2 * i + 1] = v.z;
+      raw[2 * i + 1] = v.w;
+    }
+    uint32_t isA = 0u, isB = 0u;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const uint32_t kk = raw[e] & kKeyMask;
+      const bool ok = q0 + (uint32_t)e < count;
+      isA |= (ok && kk > khi) ? 1u << e : 0u;
+      isB |= (ok && kk >= klo && kk <= khi) ? 1u << e : 0u;
+    }
+    const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
+    uint32_t befA = 0u, befB = 0u, totA = 0u, totB = 0u;
+#pragma unroll
+    for (int b = 0; (1 << b) <= PER; ++b) {
+      const uint64_t pa = __ballot((cA >> b) & 1u), pb = __ballot((cB >> b) & 1u);
+      befA += popc_lt(pa) << b;
+      befB += popc_lt(pb) << b;
+      totA += (uint32_t)__popcll(pa) << b;
+      totB += (uint32_t)__popcll(pb) << b;
+    }
+    if (lane == 0) wave_tot[wave] = ((uint64_t)totA << 31) | (uint64_t)totB;
+    __syncthreads();
+    if (wave == 0) {
+      uint64_t agg = 0ull;
+#pragma unroll
+      for (int i = 0; i < WAVES; ++i) agg += wave_tot[i];
+      const uint64_t ex = lookback_exclusive<true>(flags, tile, agg, err);
+      if (lane == 0) {
+        tile_excl = ex;
+        tile_sh = (int64_t)atomicAdd(tile_counter, 1u);  // this block's next tile
+      }
+    }
+    __syncthreads();
+    const uint64_t before_tile = tile_excl;
+    uint64_t mine = before_tile, total = before_tile;
+#pragma unroll
+    for (int i = 0; i < WAVES; ++i) {
+      const uint64_t wt = wave_tot[i];
+      if (i < wave) mine += wt;
+      total += wt;
+    }
+    // first output position of the tile, and behind its last
+    auto place = [&](uint64_t ab) {
+      const uint32_t a = (uint32_t)(ab >> 31), b = (uint32_t)(ab & 0x7fffffffu);
+      return a + (b < quota ? b : quota);
+    };
+    const uint32_t p0 = place(before_tile), p1 = place(total);
+    befA += (uint32_t)(mine >> 31);
+    befB += (uint32_t)(mine & 0x7fffffffu);
+    if ((isA | isB) != 0u) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const bool a = (isA >> e) & 1u, b = (isB >> e) & 1u;
+        if (a || (b && befB < quota)) stage[befA + (befB < quota ? befB : quota) - p0] = make_uint2(ind[e], raw[e]);
+        befA += a ? 1u : 0u;
+        befB += b ? 1u : 0u;
+      }
+    }
+    const int64_t next = tile_sh;
+    __syncthreads();
+    for (uint32_t i = (uint32_t)tid; i < p1 - p0; i += T) {
+      const uint2 ent = stage[i];
+      if (p0 + i < k_out) {
+        idx_out[p0 + i] = (int32_t)ent.x;
+        if (vals_row) vals_row[p0 + i] = __uint_as_float(ent.y);
+        // kept entries that nothing has put to +0.0 yet
+        if (zero_vec && (ent.y & kKeyMask) <= zero_below && (int64_t)ent.x < p.n) zero_vec[ent.x] = 0.0f;
+      }
+    }
+    tile = next;  // (the next tile writes wave_tot before its first barrier and the stage behind its second:
+                  //  every thread has left both by then)
+  }
+}
+
 // The survivor list was copied from pieces staged by a fused pass that stored +0.0 in place of
 // every element it handed on (k_pass_mark with STAGE).  The pass that counts the last digit over the
 // list (list_hist_body, digit 2) knows the threshold key up to its last seven bits, [lo, hi]: it gives
@@ -2523,43 +2610,50 @@ __device__ __forceinline__ uint32_t zeroed_above(const SelState* stp) {
   return (stp->compact_level == 1u && stp->use_mask == 0u) ? stp->hi : kKeyMask;
 }
 
-template <bool LIST>
+// The level-2 pass over the array (where the level-1 survivors did not fit the list).
 __global__ void __launch_bounds__(kCompactThreads)
-k_compact(SelParams p, int level, int launch_id) {
+k_compact(SelParams p) {
   __shared__ SelState st;
   __shared__ uint32_t pick_part[kCompactThreads];
   const SegView sv = seg_view(p, blockIdx.y);
-  const SelState* __restrict__ stp = sv.st;
-  const uint32_t zero_below = zeroed_above(stp);
-  // the level-1 survivors fitted the list: the deeper array passes have nothing to do
-  if (!LIST && (stp->compact_level == 1u || *p.err)) return;
-  if (LIST && *p.err) return;
-  // tiles are handed out by a counter, so blocks beyond the number of list tiles are not needed
-  if (LIST && stp->compact_level == 1u && (uint64_t)blockIdx.x * kCompactTile >= (uint64_t)stp->list_count) return;
-  derive_state<kCompactThreads>(sv, st, LIST ? 3 : level, pick_part, p.err);
-  compact_body<LIST, false>(p, sv, st, level, launch_id, (LIST && from_pieces(p, sv)) ? (st.hi | 0x7fu) : zero_below);
+  // the level-1 survivors fitted the list: nothing to do
+  if (sv.st->compact_level == 1u || *p.err) return;
+  derive_state<kCompactThreads>(sv, st, 2, pick_part, p.err);
+  compact_body<false>(p, sv, st, 2, 0, kKeyMask);
 }
 
 // ---------------------------------------------------------------------------
-// k_final : the last selection kernel where the deeper array passes exist.  If a list
-// was written (at level 1, from the mask, or by the level-2 pass) it is the final
-// pass over the list; if not even the level-2 survivors fitted one (e.g. an all-equal
-// vector) it is the level-3 pass over the array, which then writes the outputs itself.
+// k_final : the last selection kernel.  If a list was written (at level 1, from the mask,
+// or by the level-2 pass) it is the final pass over the list; if not even the level-2
+// survivors fitted one (e.g. an all-equal vector) it is the level-3 pass over the array,
+// which then writes the outputs itself.  ALWAYS_LIST: the list takes the whole vector, so
+// the array passes do not exist.  PER: entries a lane takes of the list.
 // ---------------------------------------------------------------------------
+template <bool ALWAYS_LIST, int PER>
 __global__ void __launch_bounds__(kCompactThreads)
 k_final(SelParams p) {
   __shared__ SelState st;
   __shared__ uint32_t pick_part[kCompactThreads];
+  __shared__ int64_t first_tile;
   const SegView sv = seg_view(p, blockIdx.y);
   const SelState* __restrict__ stp = sv.st;
   const uint32_t zero_below = zeroed_above(stp);
   if (*p.err) return;
-  if (stp->compact_level == 1u && (uint64_t)blockIdx.x * kCompactTile >= (uint64_t)stp->list_count) return;
+  const bool list_known = ALWAYS_LIST || stp->compact_level == 1u;
+  // tiles are handed out by a counter, so blocks beyond the number of list tiles are not needed
+  if (list_known && (uint64_t)blockIdx.x * (kCompactThreads * PER) >= (uint64_t)stp->list_count) return;
+  // (the first tile's number comes while the digits are replayed)
+  if (list_known && threadIdx.x == 0) first_tile = (int64_t)atomicAdd(sv.counters + 2, 1u);
   derive_state<kCompactThreads>(sv, st, 3, pick_part, p.err);
-  if (st.compact_level == 3u)
-    compact_body<false, true>(p, sv, st, 3, 1, zero_below);
-  else
-    compact_body<true, false>(p, sv, st, 3, 2, from_pieces(p, sv) ? (st.hi | 0x7fu) : zero_below);
+  if (!ALWAYS_LIST && st.compact_level == 3u) {
+    compact_body<true>(p, sv, st, 3, 1, zero_below);
+    return;
+  }
+  if (!list_known) {
+    if (threadIdx.x == 0) first_tile = (int64_t)atomicAdd(sv.counters + 2, 1u);
+    __syncthreads();
+  }
+  list_final_body<PER>(p, sv, st, from_pieces(p, sv) ? (st.hi | 0x7fu) : zero_below, first_tile);
 }
 
 // ---------------------------------------------------------------------------
@@ -2684,7 +2778,7 @@ k_level2(SelParams p) {
     __shared__ SelState st;
     __shared__ uint32_t pick_part[kCompactThreads];
     derive_state<kCompactThreads>(sv, st, 2, pick_part, p.err);
-    compact_body<false, false>(p, sv, st, 2, 0, kKeyMask);
+    compact_body<false>(p, sv, st, 2, 0, kKeyMask);
   }
 }
 

@@ -56,3 +56,24 @@ def test_segments_that_begin_and_end_inside_a_group(start):
     ctx.artopk_select_topk(xd, sum(ks), idx, seg_off=[int(o) for o in off], seg_k=ks)
     ctx.status()
     assert np.array_equal(idx.cpu().numpy(), orc.topk_indices_segmented(x, [int(o) for o in off], ks))
+
+
+# kept entries around one tile of the final list pass (4096 entries, 8192 for long lists), and enough of them
+# for the longer tile; a plateau of equal values at the threshold is cut by the tie quota inside a tile
+@pytest.mark.parametrize("k", [1, 7, 8, 4095, 4096, 4097, 8192 * 3 + 1, (1 << 19), (1 << 19) + 1, 1_300_001])
+def test_final_list_pass_tiles_and_quota(k):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    n = 2_000_003
+    rng = np.random.default_rng(k)
+    x = (rng.standard_normal(n) * 1e-3).astype(np.float32)
+    x[rng.permutation(n)[:k // 2]] += np.float32(1.0)                    # above the plateau
+    free = np.flatnonzero(x < 0.5)
+    x[rng.permutation(free)[:k]] = np.float32(-0.25)                     # twice as many as are still needed
+    xd = torch.from_numpy(x).cuda()
+    ctx = lib.Context(1, n, k)
+    idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+    ctx.artopk_select_topk(xd, k, idx)
+    ctx.status()
+    assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x, k))
