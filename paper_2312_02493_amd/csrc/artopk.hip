@@ -277,6 +277,16 @@ int stats_blocks(int num_cu, int32_t w, int64_t n) {
   return (int)nblk;
 }
 
+// Launches the statistics of w vectors of n elements (k_stats; rows 16-byte aligned).
+template <bool SHIFT>
+void launch_stats(hipStream_t st, const PtrTable& x, int nblk, int32_t w, int64_t n, double* partials) {
+  // beyond twice the last-level cache (256 MiB) the loads are non-temporal (see the kernel)
+  if ((int64_t)w * n * 4 > ((int64_t)1 << 29))
+    hipLaunchKernelGGL((k_stats<SHIFT, true, true>), dim3(nblk, w), dim3(256), 0, st, x, n, partials);
+  else
+    hipLaunchKernelGGL((k_stats<SHIFT, true, false>), dim3(nblk, w), dim3(256), 0, st, x, n, partials);
+}
+
 // A stage boundary (level 2 only).
 void prof_mark(artopk_ctx* c, int mark) {
   if (!c->profile || c->profile_level < 2) return;
@@ -872,7 +882,7 @@ int enqueue_topk_workers(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t 
   int nblk = (int)((k + 256 * 16 - 1) / (256 * 16));
   if (nblk < 1) nblk = 1;
   if (nblk > kMaxChunks) nblk = kMaxChunks;
-  hipLaunchKernelGGL((k_stats<false, false>), dim3(nblk, w), dim3(256), 0, c->stream, vtab, k, s.partials);
+  hipLaunchKernelGGL((k_stats<false, false, false>), dim3(nblk, w), dim3(256), 0, c->stream, vtab, k, s.partials);
   hipLaunchKernelGGL(k_sqnorm, dim3(1), dim3(1024), 0, c->stream, s.partials, nblk, (int)w, s.var_scratch,
                      sqnorm_out, s.leader_dev, argmax_out);
   HIP_TRY(c, hipGetLastError());
@@ -1175,7 +1185,7 @@ int artopk_variance(artopk_ctx* ctx, const float* const* x, int32_t w, int64_t n
   const PtrTable tab = make_table(x, w);
   const int nblk = stats_blocks(ctx->num_cu, w, n);
   Scratch& s = ctx->s;
-  hipLaunchKernelGGL((k_stats<true, true>), dim3(nblk, w), dim3(256), 0, ctx->stream, tab, n, s.partials);
+  launch_stats<true>(ctx->stream, tab, nblk, w, n, s.partials);
   hipLaunchKernelGGL(k_leader, dim3(1), dim3(1024), 0, ctx->stream, s.partials, (int)w, nblk, n, s.var_scratch,
                      var_out, s.leader_dev, argmax_out);
   HIP_TRY(ctx, hipGetLastError());
@@ -1246,7 +1256,7 @@ int artopk_variance_static(const float* const* x, int32_t w, int64_t n, double* 
   double* var_scratch = sd->ptr + kStaticPartials;
   int32_t* leader_word = reinterpret_cast<int32_t*>(sd->ptr + kStaticPartials + kMaxW);
   // every word of the scratch that is read is written first by these two launches: nothing to clear
-  hipLaunchKernelGGL((k_stats<true, true>), dim3(nblk, w), dim3(256), 0, st, tab, n, partials);
+  launch_stats<true>(st, tab, nblk, w, n, partials);
   hipLaunchKernelGGL(k_leader, dim3(1), dim3(1024), 0, st, partials, (int)w, nblk, n, var_scratch, var_out,
                      leader_word, argmax_out);
   const hipError_t e = hipGetLastError();
@@ -1369,8 +1379,8 @@ int artopk_compression_gain(artopk_ctx* ctx, const float* const* residual, int32
   double* part_res = s.partials;
   double* part_vals = s.partials + (size_t)ctx->max_w * (kMaxChunks / 2) * 2;
   const int nblk_res_c = nblk_res > kMaxChunks / 2 ? kMaxChunks / 2 : nblk_res;
-  hipLaunchKernelGGL((k_stats<false, true>), dim3(nblk_res_c, w), dim3(256), 0, ctx->stream, rtab, n, part_res);
-  hipLaunchKernelGGL((k_stats<false, false>), dim3(nblk_vals, w), dim3(256), 0, ctx->stream, vtab, k, part_vals);
+  launch_stats<false>(ctx->stream, rtab, nblk_res_c, w, n, part_res);
+  hipLaunchKernelGGL((k_stats<false, false, false>), dim3(nblk_vals, w), dim3(256), 0, ctx->stream, vtab, k, part_vals);
   hipLaunchKernelGGL(k_gain, dim3(1), dim3(1024), 0, ctx->stream, part_vals, nblk_vals, part_res, nblk_res_c, (int)w,
                      gain_out);
   HIP_TRY(ctx, hipGetLastError());

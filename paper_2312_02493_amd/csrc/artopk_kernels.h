@@ -938,8 +938,14 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
 //   SHIFT (variance): the block's (count, mean, sum of squared deviations), see VarAcc.
 //   !SHIFT (sum of squares): the block's sum of x and of x^2 to partials[w][b][0..1].
 // VEC reads float4 groups (rows must be 16-byte aligned).
+//   NT: non-temporal loads, for vectors that together are larger than twice the last-level
+// cache: what earlier kernels left there (written and half-written lines) slowed ordinary
+// loads to 4.4 TB/s on 2 x 138 M elements behind a residual rewrite, non-temporal ones
+// run at 5.6 (253 against 200 us; 4 x 138 M alone 383 against 343).  Where the vectors
+// partly lie in the cache ordinary loads are the better ones (1 x 60 M behind a rewrite:
+// 54 against 92 us, 8 x 11.7 M 86 against 99, 1 x 138 M the same).
 // ---------------------------------------------------------------------------
-template <bool SHIFT, bool VEC>
+template <bool SHIFT, bool VEC, bool NT>
 __global__ void __launch_bounds__(256)
 k_stats(PtrTable x, int64_t n, double* __restrict__ partials) {
   __shared__ double red[3 * 4];
@@ -949,7 +955,6 @@ k_stats(PtrTable x, int64_t n, double* __restrict__ partials) {
   VarAcc va;                 // SHIFT
   double s = 0.0, ss = 0.0;  // !SHIFT
   if (VEC) {
-    const v4f* __restrict__ x4 = reinterpret_cast<const v4f*>(xp);
     const int64_t tile = 256 * kPassAUnroll;
     const int64_t ntile = (n4 + tile - 1) / tile;
     for (int64_t t = bx; t < ntile; t += nblk) {
@@ -958,7 +963,7 @@ k_stats(PtrTable x, int64_t n, double* __restrict__ partials) {
 #pragma unroll
       for (int u = 0; u < kPassAUnroll; ++u) {
         const int64_t q = q0 + u * 256;
-        if (q < n4) a[u] = x4[q];
+        if (q < n4) a[u] = load4<NT>(xp + 4 * q);
       }
 #pragma unroll
       for (int u = 0; u < kPassAUnroll; ++u) {

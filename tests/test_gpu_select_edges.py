@@ -77,3 +77,24 @@ def test_final_list_pass_tiles_and_quota(k):
     ctx.artopk_select_topk(xd, k, idx)
     ctx.status()
     assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x, k))
+
+
+@pytest.mark.parametrize("w,n", [(1, 134_217_728), (1, 134_217_732), (3, 44_739_245), (2, 1023)])
+def test_gain_and_variance_on_both_sides_of_the_cache_limit(w, n):
+    """float64 sums in another order: relative difference below n rounding errors of 2^-53, 1e-9 at these sizes."""
+    import torch
+    import paper_2312_02493_amd as lib
+
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = [torch.randn(n, generator=gen, device="cuda") for _ in range(w)]
+    vals = torch.randn(w, 500, generator=gen, device="cuda")
+    ctx = lib.Context(w, n, 500)
+    out, gain = (torch.zeros(w, dtype=torch.float64, device="cuda") for _ in range(2))
+    ctx.artopk_variance(x, out)
+    ctx.artopk_compression_gain(x, vals, 500, gain)
+    ctx.status()
+    for r in range(w):
+        d = x[r].double()
+        v = float(vals[r].double().square().sum())
+        np.testing.assert_allclose(float(out[r]), float(d.var(correction=0)), rtol=1e-9)
+        np.testing.assert_allclose(float(gain[r]), v / (v + float(d.square().sum())), rtol=1e-9)
