@@ -103,7 +103,8 @@ enum {
  * 64 KiB per segment plus
  * 8 (max_k + max(max_n / 8, 2^22)) bytes of survivor list plus 8 max_w max_k bytes plus
  * max_n / 8 bytes per worker of survivor bit masks plus 1.5 max_n bytes in which a
- * leader's fused pass stages list entries tile by tile.  The library reads no environment
+ * leader's fused pass stages list entries tile by tile plus, for selections on several vectors
+ * at a time, max_n / 341 bytes of scan flags for each of up to 16 workers.  The library reads no environment
  * variable and keeps no state outside its contexts (artopk_variance_static's fixed
  * scratch excepted, see there).
  */

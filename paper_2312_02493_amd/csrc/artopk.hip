@@ -35,6 +35,14 @@ namespace {
 constexpr int kPassAThreads = 1024, kPassAU = 8;        // 128 KiB of each array per block iteration
 constexpr int kPassRestThreads = 1024, kPassRestU = 8;
 
+constexpr int32_t kMaxBatch = 16;  // vectors selected on in one launch set
+// Default of ARTOPK_OPT_GUESS_MIN_N, and what stands in its place for vectors that are only read: elements of
+// the vectors selected on together.  Measured (us, one in a thousand / one in a hundred kept; histogram route
+// against read-only marking): 1 x 11.7 M 58/60 against 63/65, 1 x 16.8 M 63/65 against 67/75, 1 x 25.6 M 85/88.5
+// against 79/88, 8 x 4 M 113/117 against 105/117, 1 x 138 M 268/294 against 162/184, 8 x 25.6 M 393/441 against
+// 234/287.  (One in ten kept: 25.6 M 116 against 137, 138 M 390 against 389, so denser than one in 32 never.)
+constexpr int64_t kGuessMinN = (int64_t)1 << 25, kReadGuessMinN = (int64_t)3 << 23;
+
 struct Scratch {
   // zeroed before every select: one kSegWords block per segment, then the look-back flags
   uint32_t* h_all = nullptr;      // [max_w][kSlotWords] whole-vector histograms of the fused pass, guess sample
@@ -45,7 +53,7 @@ struct Scratch {
   int64_t max_tiles = 0;
   // not zeroed
   uint32_t* S = nullptr;          // [max_w * kMaxChunks + max_seg][4096] per-chunk suffix histograms
-  uint32_t* chunk_off = nullptr;  // [kMaxChunks + max_seg]
+  uint32_t* chunk_off = nullptr;  // [16 kMaxChunks + max_seg]
   double* partials = nullptr;     // [max_w][kMaxPassBlocks][3] per-block moments (or [2] sums)
   double* var_scratch = nullptr;  // [max_w]
   int32_t* leader_dev = nullptr;
@@ -75,7 +83,9 @@ struct Plan {
   int64_t max_tiles = 1;    // largest look-back tile count of a segment
   int64_t total_tiles = 1;
   int64_t max_cap = 1;      // largest list capacity of a segment
-  int32_t hist_copies = 0;  // histogram copies the segments use in h_all's memory
+  size_t hist_words = 0;    // words of h_all's memory used for copies of histograms
+  bool batch = false;       // nseg whole vectors with one descriptor (SelParams::batch)
+  int64_t list_stride = 0;  // list entries per vector of a batch
   int32_t total_chunks = 0; // chunks of all segments together (entries of the device chunk map), 0: no map
 };
 
@@ -92,7 +102,7 @@ struct artopk_ctx {
   bool leader_first = true;  // STAR / FIXED: leader pass + select first, then one fused pass over the rest
   // vectors of at least this many elements get a sampled threshold guess before the fused pass, which
   // then counts and marks only the keys that reach it (the selection no longer re-reads the vector)
-  int64_t guess_min_n = (int64_t)1 << 25;
+  int64_t guess_min_n = kGuessMinN;
   // vectors of at least this many elements get their dense update from k_update_tiles
   int64_t update_tiles_min_n = (int64_t)1 << 22;
   int stage_tiles = 1;  // guess route, one marking worker: the fused pass hands the marked elements on per tile
@@ -326,15 +336,18 @@ int64_t seg_list_cap(int64_t n_s, int64_t k_s) {
 // without; one on 138 M, 845 chunks: no difference.  Segments of up to 128 chunks: 5 us slower with them).
 constexpr int32_t kManyChunks = 128;
 
+// List capacity of a flat selection whose list has `room` entries of memory.
+int64_t vec_cap(const artopk_ctx* c, int64_t room) { return room < (int64_t)c->s.cap ? room : (int64_t)c->s.cap; }
+
 // One segment covering the whole vector.  own_hist: no fused pass has built its histograms.
 Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool whole_pass_tiles = false,
-               bool own_hist = false) {
+               bool own_hist = false, int64_t max_chunks = kMaxChunks) {
   Plan pl;
   pl.nseg = 1;
   SegDesc d{};
   d.e_lo = 0;
   d.e_hi = n;
-  d.geom = make_geom(0, n, kMaxChunks, whole_pass_tiles);
+  d.geom = make_geom(0, n, max_chunks, whole_pass_tiles);
   d.koff = 0;
   d.list_base = 0;
   d.flag_base = 0;
@@ -343,7 +356,7 @@ Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool
   d.cap = c->s.cap < (uint64_t)n ? c->s.cap : (uint32_t)n;
   d.vec = vec;
   d.hreps = own_hist && d.geom.nchunks > kManyChunks ? kHistReps : 1;
-  pl.hist_copies = d.hreps > 1 ? d.hreps : 0;
+  pl.hist_words = d.hreps > 1 ? (size_t)d.hreps * kHistBins : 0;
   pl.desc.push_back(d);
   pl.max_chunks = d.geom.nchunks;
   pl.max_tiles = pl.total_tiles = tiles_of_range(0, n);
@@ -443,6 +456,9 @@ SelParams make_params(const artopk_ctx* c, const Plan& pl, const PtrTable& tab, 
   p.vals_row = vals_row;
   p.zero_vec = nullptr;
   p.err = s.err_dev;
+  p.batch = pl.batch ? 1 : 0;
+  p.list_stride = pl.list_stride;
+  p.flag_stride = pl.batch ? pl.max_tiles : 0;
   p.table = pl.use_table ? s.table_dev : nullptr;
   p.chunk_map = (pl.use_table && pl.total_chunks > 0) ? s.chunk_map : nullptr;
   p.slot_by_leader = slot_by_leader;
@@ -459,7 +475,7 @@ int enqueue_clear(artopk_ctx* c, const Plan& pl, int hist_slots, int32_t leader 
   const size_t words1 = (size_t)pl.nseg * kSegWords;
   const size_t words2 = (size_t)pl.total_tiles * kNumLookback * 2;
   // (a plan with histograms of its own uses h_all's memory for their copies; no pass fills slots then)
-  const size_t words3 = hist_slots > 0 ? (size_t)hist_slots * kSlotWords : (size_t)pl.hist_copies * kHistBins;
+  const size_t words3 = hist_slots > 0 ? (size_t)hist_slots * kSlotWords : pl.hist_words;
   const size_t total = words1 + words2 + words3;
   int blocks = (int)((total + 256 * 8 - 1) / (256 * 8));
   if (blocks < 1) blocks = 1;
@@ -639,6 +655,8 @@ struct GuessPlan {
   int runs = 0;
   int64_t stride = 0;
   uint32_t m_hi = 0;
+  int32_t span = 0;      // elements per piece of the read-only marking pass (tile_cap entries each)
+  uint32_t m_max = 0xffffffffu;  // more sample keys at or above a bound than this: no bound
   int32_t tile_cap = 0;  // > 0: one marking worker, whose fused pass stages up to this many list entries per tile
 };
 
@@ -677,25 +695,87 @@ GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, int marking) {
   return gp;
 }
 
+// The guess of a selection on `vectors` vectors as they are (no pass writes them): a smaller sample, since a
+// longer list costs little here (nothing has to be given back from it), and pieces wherever they fit.
+GuessPlan plan_guess_read(const artopk_ctx* c, int64_t n, int64_t k, int vectors, int64_t list_cap) {
+  GuessPlan gp;
+  const bool by_default = c->guess_min_n == kGuessMinN;  // (the option's own value holds for every vector)
+  if (c->s.mask == nullptr || (by_default ? n * vectors < kReadGuessMinN : n < c->guess_min_n)) return gp;
+  if (k * 32 > n) return gp;
+  int64_t runs = n / (4 * kGuessRun);
+  if (runs > 4096) runs = 4096;
+  if (runs < 256) return gp;
+  gp.runs = (int)runs;
+  gp.stride = n / runs;
+  const double sample = (double)(runs * kGuessRun);
+  const double expect = (double)k * sample / (double)n;
+  gp.m_hi = (uint32_t)std::ceil(expect + 6.0 * std::sqrt(expect) + 8.0);
+  if ((double)gp.m_hi > sample) return gp;
+  // what k_pick_mask accepts: at most k + n/8 keys, and no more than the list takes
+  int64_t limit = k + (n >> 3);
+  if (limit > list_cap) limit = list_cap;
+  gp.m_max = (uint32_t)((double)limit * sample / (double)n);
+  if (gp.m_max <= gp.m_hi) return gp;
+  // entries a span hands on: the bound is the lower edge of a top-digit bin (up to about 15 % more keys than
+  // the sample's m_hi-th largest), plus four standard deviations of a span's count (a span with more is marked
+  // a second time)
+  gp.span = n * vectors < ((int64_t)1 << 23) ? kSpanStep : 4 * kSpanStep;  // (short vectors need the spans to fill the chip)
+  const double per_span = 1.15 * (double)gp.m_hi / sample * (double)gp.span;
+  const int64_t want = ((int64_t)std::ceil(per_span + 4.0 * std::sqrt(per_span) + 8.0) + 15) / 16 * 16;
+  const int64_t nspans = (n + gp.span - 1) / gp.span;
+  if (nspans * want * vectors > c->s.tilebuf_entries) return gp;
+  gp.tile_cap = (int32_t)want;
+  gp.on = true;
+  return gp;
+}
+
+// The spans' pieces of the marking pass on vectors that are only read (slots 0, 1, ...); their counts lie in
+// the memory of the vectors' masks, which this route does not use.
+TileBuf span_buf(const artopk_ctx* c, const GuessPlan& gp, int64_t n) {
+  const int64_t nspans = (n + gp.span - 1) / gp.span;
+  TileBuf t{c->s.tilebuf, reinterpret_cast<uint32_t*>(c->s.mask), nspans * gp.tile_cap, 2 * c->s.mask_stride,
+            gp.tile_cap};
+  t.span = gp.span;
+  return t;
+}
+
+// The marking pass over the first nv vectors of the table.
+void launch_mark_spans(artopk_ctx* c, const GuessPlan& gp, int nv, const PtrTable& x, int64_t n, int64_t chunk_elems) {
+  const int64_t nspans = (n + gp.span - 1) / gp.span;
+  int64_t blocks = (nspans + 3) / 4;
+  if (blocks > (int64_t)c->num_cu * 8) blocks = (int64_t)c->num_cu * 8;
+  const dim3 grid((unsigned)blocks, (unsigned)nv);
+  const TileBuf tb = span_buf(c, gp, n);
+  if (c->pass_a_nt)
+    hipLaunchKernelGGL(k_mark_spans<true>, grid, dim3(256), 0, c->stream, x, n, chunk_elems, c->s.h_all, tb);
+  else
+    hipLaunchKernelGGL(k_mark_spans<false>, grid, dim3(256), 0, c->stream, x, n, chunk_elems, c->s.h_all, tb);
+}
+
 // Samples the first nvec vectors of (g + residual) into slots 0 .. nvec-1 (cleared beforehand).
-void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const PtrTable& res, int nvec) {
+void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const PtrTable& res, int nvec,
+                   bool read_only = false) {
   // one vector whose marked elements are handed on per tile: a finer bound keeps the list (and the
   // number of values to give back afterwards) close to k
-  uint32_t* sample = (nvec == 1 && gp.tile_cap > 0) ? c->s.sample_keys : nullptr;
+  uint32_t* sample = (!read_only && nvec == 1 && gp.tile_cap > 0) ? c->s.sample_keys : nullptr;
   // about 128 blocks over all vectors (measured: 8 vectors take 70 us with 64 blocks each, 32 us
   // with 16; one vector 15 us with 64 blocks, 19 us with 16)
   int gblocks = 128 / nvec;
   if (gblocks > 64) gblocks = 64;
   if (gblocks < 8) gblocks = 8;
-  if (c->g_type == ARTOPK_G_BF16)
+  if (read_only) {
+    gblocks = (gp.runs + 255) / 256;  // one run a thread
+    hipLaunchKernelGGL(k_guess<kGNone>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
+                       gp.stride, gp.m_hi, gp.m_max, sample);
+  } else if (c->g_type == ARTOPK_G_BF16)
     hipLaunchKernelGGL(k_guess<kGBF16>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
-                       gp.stride, gp.m_hi, sample);
+                       gp.stride, gp.m_hi, gp.m_max, sample);
   else if (c->g_type == ARTOPK_G_F16)
     hipLaunchKernelGGL(k_guess<kGF16>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
-                       gp.stride, gp.m_hi, sample);
+                       gp.stride, gp.m_hi, gp.m_max, sample);
   else
     hipLaunchKernelGGL(k_guess<kGF32>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
-                       gp.stride, gp.m_hi, sample);
+                       gp.stride, gp.m_hi, gp.m_max, sample);
   if (sample != nullptr)
     hipLaunchKernelGGL(k_guess_refine, dim3(64), dim3(256), 0, c->stream, c->s.h_all, sample, gp.runs * kGuessRun,
                        gp.m_hi);
@@ -709,10 +789,13 @@ void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const 
 int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n, int32_t* idx_out,
                    bool hist_ready, int slot_by_leader, float* vals_row = nullptr,
                    const LeaderArgs* leader_args = nullptr, bool guessed = false, float* zero_vec = nullptr,
-                   int32_t tile_cap = 0) {
+                   int32_t tile_cap = 0, int32_t first_slot = 0, const GuessPlan* spans = nullptr) {
   hipStream_t st = c->stream;
   const unsigned nseg = (unsigned)pl.nseg;
-  SelParams p = make_params(c, pl, tab, n, idx_out, vals_row, hist_ready ? slot_by_leader : 0, hist_ready);
+  SelParams p = make_params(c, pl, tab, n, idx_out, vals_row, (hist_ready || pl.batch) ? slot_by_leader : 0,
+                            hist_ready);
+  if (hist_ready) p.h_all += (size_t)first_slot * kSlotWords;  // (slots of a later group of a batch)
+  p.S += (size_t)first_slot * kMaxChunks * kHistBins;
   p.zero_vec = zero_vec;
   LeaderArgs la{};
   if (leader_args) la = *leader_args;
@@ -724,14 +807,17 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
     // the list is written from the mask and the threshold digit taken from the list; otherwise the
     // state says need_full, and the same two launches build the histogram of every key and pick
     // from that, after which the selection goes on as without a guess.
-    p.mask = c->s.mask;
-    p.tiles = tile_buf(c, tile_cap);
+    p.mask = spans ? nullptr : c->s.mask + (size_t)first_slot * (size_t)c->s.mask_stride;
+    p.tiles = spans ? span_buf(c, *spans, n) : tile_buf(c, tile_cap);
     p.use_mcount = 1;
     hipLaunchKernelGGL(k_pick_mask, dim3(1, nseg), dim3(1024), 0, st, p, la);
     SelParams pf = p;
     pf.h_all = nullptr;
     pf.only_if_need_full = 1;
-    hipLaunchKernelGGL((k_mask_or_hist<4>), dim3(pl.max_chunks, nseg), dim3(1024), 0, st, p, pf);
+    if (spans)
+      hipLaunchKernelGGL(k_spans_or_hist, dim3(pl.max_chunks, nseg), dim3(1024), 0, st, p, pf);
+    else
+      hipLaunchKernelGGL((k_mask_or_hist<4>), dim3(pl.max_chunks, nseg), dim3(1024), 0, st, p, pf);
     SelParams pa = p;
     pa.after_mask = 1;
     hipLaunchKernelGGL(k_pick0, dim3(1, nseg), dim3(1024), 0, st, pa, LeaderArgs{});
@@ -745,7 +831,8 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   const int64_t per_seg = ((int64_t)c->num_cu * 2 + nseg - 1) / nseg;
   // deeper array passes: they run only for segments whose level-1 survivors did not fit the list,
   // which cannot happen if the list takes the whole range
-  const bool always_fits = nseg == 1 && (int64_t)pl.desc[0].cap >= pl.desc[0].e_hi - pl.desc[0].e_lo;
+  const bool one_range = nseg == 1 || pl.batch;
+  const bool always_fits = one_range && (int64_t)pl.desc[0].cap >= pl.desc[0].e_hi - pl.desc[0].e_lo;
   int cblocks = (int)(pl.max_tiles < per_seg ? pl.max_tiles : per_seg);
   if (cblocks < 1) cblocks = 1;
 
@@ -755,7 +842,7 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   // level 1: ordered compaction of the array (4 waves, 16 consecutive elements per lane: best of the
   // shapes measured on the 138 M and 1 G workloads); on the guess route the same launch counts
   // the second digit over a list that was written from the mask
-  const bool long_list = nseg == 1 && (int64_t)pl.desc[0].k * 32 > n;
+  const bool long_list = one_range && (int64_t)pl.desc[0].k * 32 > n;
   if (guessed && hist_ready && long_list) {
     // a list of many millions of entries written from the staged pieces: the lean list kernel
     // counts its second digit; the array pass stands by for a guess that did not hold
@@ -781,7 +868,7 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
     hipLaunchKernelGGL(k_level2, dim3((unsigned)b2, nseg), dim3(kCompactThreads), 0, st, p);
   }
   int64_t k_all = 0;
-  for (const SegDesc& d : pl.desc) k_all += d.k;
+  for (const SegDesc& d : pl.desc) k_all += pl.batch ? (int64_t)d.k * pl.nseg : d.k;
   const bool many = k_all > ((int64_t)1 << 19);
   const int64_t ltile = kCompactThreads * (many ? 16 : 8);
   int64_t ltiles = (pl.max_cap + ltile - 1) / ltile;
@@ -862,6 +949,72 @@ int enqueue_update_fill(artopk_ctx* c, float* update, int64_t n, const int32_t* 
 }
 
 
+// Top-k of each of w whole vectors (row r of idx_rows, and of val_rows if given), several at a time in one
+// launch set (8 x 25.6 M on the histogram route: 768 us one after the other, 438 together).  A context's list is sized for one selection, so a batch shares it out: as many vectors at a
+// time as leave each room for 1.25 k + n/128 entries (what a list usually holds, with some ties).
+//   hist_ready: the fused pass has left vector r's histograms (or, if guessed, its mask) in slot r.
+//   Otherwise a sampled bound and a read-only marking pass (k_mark_spans) take the place of the
+//   two passes over the vector, histograms and compaction, that the histogram route needs.
+int enqueue_topk_rows(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t n, int64_t k, int32_t* idx_rows,
+                      float* val_rows, bool hist_ready, bool guessed) {
+  Scratch& s = c->s;
+  const int64_t room = s.list_entries - kCompactTile;  // (the final pass reads up to a tile behind a list's end)
+  int64_t need = k + k / 4 + (n / 128 > 4096 ? n / 128 : 4096);
+  if (need > n) need = n;
+  auto group_size = [&](int64_t most) {
+    if (most > w) most = w;
+    if (most > kMaxBatch) most = kMaxBatch;
+    if (most < 1) most = 1;
+    const int64_t groups = (w + most - 1) / most;
+    return (int32_t)((w + groups - 1) / groups);
+  };
+  int32_t per = group_size(room / ((need + 3) / 4 * 4));
+  auto cap_of = [&](int32_t vectors) {
+    const int64_t stride = vectors == 1 ? room : room / vectors / 4 * 4;
+    return stride < n ? stride : n;
+  };
+  GuessPlan gp;
+  if (!hist_ready) {
+    gp = plan_guess_read(c, n, k, per, vec_cap(c, cap_of(per)));
+    for (int32_t fewer = per - 1; !gp.on && fewer >= 1; --fewer) {  // fewer at a time may leave room for the pieces
+      gp = plan_guess_read(c, n, k, fewer, vec_cap(c, cap_of(fewer)));
+      if (gp.on) {
+        per = group_size(fewer);
+        gp = plan_guess_read(c, n, k, per, vec_cap(c, cap_of(per)));
+      }
+    }
+  }
+  const bool marks = guessed || gp.on;
+  for (int32_t r0 = 0; r0 < w; r0 += per) {
+    const int32_t nv = w - r0 < per ? w - r0 : per;
+    // the fused pass counted per chunk of its own layout; otherwise about two thousand chunks over all vectors
+    int64_t max_chunks = kMaxChunks;
+    if (!hist_ready && nv > 1) max_chunks = 2 * kMaxChunks / nv > 128 ? 2 * kMaxChunks / nv : 128;
+    if (max_chunks > kMaxChunks) max_chunks = kMaxChunks;
+    Plan pl = flat_plan(c, n, k, -1, marks, !hist_ready && !gp.on, max_chunks);
+    pl.nseg = nv;
+    pl.batch = true;
+    pl.list_stride = nv == 1 ? 0 : room / nv / 4 * 4;
+    pl.desc[0].cap = (uint32_t)vec_cap(c, cap_of(nv));
+    pl.max_cap = pl.desc[0].cap;
+    pl.total_tiles = pl.max_tiles * nv;
+    if (pl.hist_words) pl.hist_words = (size_t)nv * kSlotWords;
+    int rc = enqueue_clear(c, pl, gp.on ? nv : 0);
+    if (rc) return rc;
+    PtrTable t;
+    for (int i = 0; i < kMaxW; ++i) t.p[i] = i < nv ? tab.p[r0 + i] : nullptr;
+    if (gp.on) {
+      enqueue_guess(c, gp, t, t, nv, true);
+      launch_mark_spans(c, gp, nv, t, n, pl.desc[0].geom.chunk_elems);
+    }
+    if ((rc = enqueue_select(c, pl, t, n, idx_rows + (size_t)r0 * (size_t)k, hist_ready || gp.on, 1,
+                             val_rows ? val_rows + (size_t)r0 * (size_t)k : nullptr, nullptr, marks, nullptr,
+                             0, hist_ready ? r0 : 0, gp.on ? &gp : nullptr)))
+      return rc;
+  }
+  return ARTOPK_OK;
+}
+
 // Every worker's own Top-k (indices ascending, values) and the squared norm of its k values;
 // argmax (first maximum) goes to leader_dev and, if given, argmax_out.  With hist_ready the
 // per-chunk histograms of all workers are already in S (pass A with histograms for every worker).
@@ -869,14 +1022,8 @@ int enqueue_topk_workers(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t 
                          float* val_rows, double* sqnorm_out, int32_t* argmax_out, bool hist_ready,
                          bool guessed = false) {
   Scratch& s = c->s;
-  for (int32_t r = 0; r < w; ++r) {
-    const Plan pl = flat_plan(c, n, k, r, guessed, !hist_ready);
-    int rc = enqueue_clear(c, pl, 0);
-    if (rc) return rc;
-    if ((rc = enqueue_select(c, pl, tab, n, idx_rows + (size_t)r * (size_t)k, hist_ready, 1,
-                             val_rows + (size_t)r * (size_t)k, nullptr, guessed)))
-      return rc;
-  }
+  const int rc = enqueue_topk_rows(c, tab, w, n, k, idx_rows, val_rows, hist_ready, guessed);
+  if (rc) return rc;
   PtrTable vtab;
   for (int i = 0; i < kMaxW; ++i) vtab.p[i] = (i < w) ? val_rows + (size_t)i * (size_t)k : nullptr;
   int nblk = (int)((k + 256 * 16 - 1) / (256 * 16));
@@ -897,6 +1044,7 @@ namespace {
 struct Layout {
   uint32_t cap = 0;
   int64_t list_entries = 0, max_tiles = 0, mask_stride = 0, tilebuf_entries = 0;
+  int32_t blocks = 0;  // scratch blocks: one per segment, or per vector of a batch
   size_t o_hall = 0, o_mask = 0, o_zero = 0, o_S = 0, o_coff = 0, o_part = 0, o_var = 0, o_leader = 0, o_err = 0, o_counter = 0, o_list = 0, o_vals = 0, o_rows = 0, o_table = 0, o_cmap = 0, o_tstart = 0, o_tbuf = 0, o_tcnt = 0, o_sample = 0;
   size_t total = 0;
 };
@@ -919,7 +1067,12 @@ Layout scratch_layout(int32_t max_w, int64_t max_n, int64_t max_k, int32_t max_s
   // segmented layouts add per-segment rounding: n_s/8 may be raised to 4096 and bases are aligned
   L.list_entries = (int64_t)align_up((size_t)cap + (size_t)max_segments * 4100, kCompactTile) + kCompactTile;
   // a range [lo, hi) touches at most ceil(len / tile) + 1 look-back tiles
-  L.max_tiles = (max_n + kCompactTile - 1) / kCompactTile + 2 * (int64_t)max_segments + 1;
+  // (or a batch of whole vectors)
+  const int64_t batch = max_w < kMaxBatch ? max_w : kMaxBatch;
+  const int64_t vec_tiles = (max_n + kCompactTile - 1) / kCompactTile;
+  L.max_tiles = vec_tiles + 2 * (int64_t)max_segments + 1;
+  if (L.max_tiles < vec_tiles * batch) L.max_tiles = vec_tiles * batch;
+  L.blocks = max_segments > batch ? max_segments : (int32_t)batch;
 
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -932,10 +1085,10 @@ Layout scratch_layout(int32_t max_w, int64_t max_n, int64_t max_k, int32_t max_s
   // one bit per element and worker, in rows of 256 elements (whole tiles of the fused pass)
   L.mask_stride = (max_n + kPassTile - 1) / kPassTile * (kPassTile / 64);
   L.o_mask = take((size_t)max_w * (size_t)L.mask_stride * sizeof(uint64_t));
-  L.o_zero = take((size_t)max_segments * kSegWords * sizeof(uint32_t) +
+  L.o_zero = take((size_t)L.blocks * kSegWords * sizeof(uint32_t) +
                              (size_t)L.max_tiles * kNumLookback * sizeof(uint64_t));
   L.o_S = take(((size_t)max_w * kMaxChunks + (size_t)max_segments) * kHistBins * sizeof(uint32_t));
-  L.o_coff = take(((size_t)kMaxChunks + (size_t)max_segments) * sizeof(uint32_t));
+  L.o_coff = take(((size_t)kMaxChunks * (size_t)batch + (size_t)max_segments) * sizeof(uint32_t));
   L.o_part = take((size_t)max_w * kMaxPassBlocks * 3 * sizeof(double));
   L.o_var = take((size_t)max_w * sizeof(double));
   L.o_leader = take(sizeof(int32_t));
@@ -1005,7 +1158,7 @@ int artopk_create(artopk_ctx** out, int32_t max_w, int64_t max_n, int64_t max_k,
   s.mask = reinterpret_cast<uint64_t*>(base + L.o_mask);
   s.zero_base = reinterpret_cast<uint32_t*>(base + L.o_zero);
   // kSegWords is even, so the flags stay 8-byte aligned
-  s.flags = reinterpret_cast<uint64_t*>(s.zero_base + (size_t)max_segments * kSegWords);
+  s.flags = reinterpret_cast<uint64_t*>(s.zero_base + (size_t)L.blocks * kSegWords);
   s.S = reinterpret_cast<uint32_t*>(base + L.o_S);
   s.chunk_off = reinterpret_cast<uint32_t*>(base + L.o_coff);
   s.partials = reinterpret_cast<double*>(base + L.o_part);
@@ -1281,15 +1434,14 @@ int artopk_select_topk(artopk_ctx* ctx, const float* acc, int64_t n, int32_t nse
   const PtrTable tab = make_table(one, 1);
   prof_begin(ctx);
   prof_mark(ctx, 1);
-  Plan flat;
-  const Plan* pl = &flat;
   if (seg_off && nseg > 1) {
+    const Plan* pl = nullptr;
     if ((rc = segmented_plan(ctx, n, nseg, seg_off, seg_k, &pl))) return rc;
+    if ((rc = enqueue_clear(ctx, *pl, 0, 0, nullptr))) return rc;  // the single vector is "leader 0"
+    rc = enqueue_select(ctx, *pl, tab, n, idx_out, false, 0);
   } else {
-    flat = flat_plan(ctx, n, k, -1, false, true);
+    rc = enqueue_topk_rows(ctx, tab, 1, n, k, idx_out, nullptr, false, false);
   }
-  if ((rc = enqueue_clear(ctx, *pl, 0, 0, nullptr))) return rc;  // the single vector is "leader 0"
-  rc = enqueue_select(ctx, *pl, tab, n, idx_out, false, 0);
   prof_mark(ctx, 2);
   return rc;
 }

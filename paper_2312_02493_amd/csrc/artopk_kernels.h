@@ -9,6 +9,8 @@
 //   k_pass_mark      the same pass behind k_guess: instead of histograms a bit
 //                    mask of the keys reaching the guessed bound; its blocks
 //                    stride over the tiles of the vector
+//   k_mark_spans     the marking alone, on vectors that are only read: their marked
+//                    elements per span of a wave (k_spans_or_hist then writes the list)
 //   k_hist0          the same histograms alone (stand-alone select, segments,
 //                    after a guess that did not hold)
 //   k_stats          variance partials alone (stand-alone variance)
@@ -90,6 +92,7 @@ struct TileBuf {
   int64_t buf_stride;  // entries per slot
   int64_t cnt_stride;  // tiles per slot
   int32_t cap;         // entries per tile (<= kStageMax)
+  int32_t span = 0;    // > 0: pieces of k_mark_spans, one per `span` elements (no mask stands behind them)
 };
 
 struct PtrTable {
@@ -173,6 +176,11 @@ struct SelParams {
   float* vals_row;         // leader's row of gathered values, or nullptr
   float* zero_vec;         // the selected vector itself if its kept entries are to become +0.0 on the way, or nullptr
   uint32_t* err;
+  // Several whole vectors at once: segment s is vector s of the table with `one` for a descriptor, its own
+  // list, look-back flags, chunk offsets and output row.
+  int32_t batch;
+  int64_t list_stride;     // list entries per vector
+  int64_t flag_stride;     // look-back tiles per vector
   const SegDesc* table;
   // per-chunk kernels of a segmented selection run one block per chunk of the whole layout:
   // entry b = (segment << 16) | chunk within the segment; nullptr: grid = (chunks, segments)
@@ -402,6 +410,7 @@ __device__ __forceinline__ void store4(float* p, v4f v) {
 // Gradient element types: float32, or 16 bits widened exactly to float32 before use
 // (bfloat16: the bits become the upper half of the float32; float16: hardware conversion).
 constexpr int kGF32 = 0, kGBF16 = 1, kGF16 = 2;
+constexpr int kGNone = 3;  // no gradient: the vector is only read
 
 template <int GT>
 __device__ __forceinline__ float widen16(uint32_t h) {  // h: the 16 bits in the low half
@@ -521,6 +530,12 @@ __device__ __forceinline__ void flush_suffix_hist(uint32_t* lh, uint32_t* red, u
 __device__ __forceinline__ SegView seg_view(const SelParams& p, int seg, int leader = -1) {
   SegView v;
   v.d = p.table ? p.table[seg] : p.one;
+  if (p.batch) {
+    v.d.vec = seg;
+    v.d.koff = (int64_t)seg * (int64_t)v.d.k;
+    v.d.list_base = (int64_t)seg * p.list_stride;
+    v.d.flag_base = (int64_t)seg * p.flag_stride;
+  }
   uint32_t* zb = p.zero_base + (size_t)seg * kSegWords;
   v.st = reinterpret_cast<SelState*>(zb + kSegState);
   v.counters = zb + kSegCounters;
@@ -531,17 +546,17 @@ __device__ __forceinline__ SegView seg_view(const SelParams& p, int seg, int lea
   v.x = p.tab.p[vec];
   const size_t slot = p.slot_by_leader ? (size_t)vec : 0;  // histogram slot: per vector, or the only one
   v.htop = p.h_all ? const_cast<uint32_t*>(p.h_all) + slot * kSlotWords
-                   : (v.d.hreps > 1 ? p.hcopies : zb + kSegHtop);
+                   : (v.d.hreps > 1 ? p.hcopies + slot * kSlotWords : zb + kSegHtop);
   v.htop_reps = p.h_all ? kHistReps : v.d.hreps;
   v.hseg = zb + kSegHtop;
   v.ctrl = p.h_all ? p.h_all + slot * kSlotWords + kSlotCtrl : nullptr;
   v.mask = p.mask ? p.mask + slot * (size_t)p.mask_stride : nullptr;
-  v.tbuf = (p.mask && p.tiles.buf) ? p.tiles.buf + slot * (size_t)p.tiles.buf_stride : nullptr;
-  v.tcnt = (p.mask && p.tiles.buf) ? p.tiles.cnt + slot * (size_t)p.tiles.cnt_stride : nullptr;
+  v.tbuf = p.tiles.buf ? p.tiles.buf + slot * (size_t)p.tiles.buf_stride : nullptr;
+  v.tcnt = p.tiles.buf ? p.tiles.cnt + slot * (size_t)p.tiles.cnt_stride : nullptr;
   v.tcap = p.tiles.cap;
   v.mcount = (p.h_all && p.use_mcount) ? p.h_all + slot * kSlotWords + kSlotMcount : nullptr;
   v.S = p.S + (slot * kMaxChunks + (size_t)v.d.chunk_begin) * kHistBins;
-  v.chunk_off = p.chunk_off + v.d.chunk_begin;
+  v.chunk_off = p.chunk_off + (p.batch ? (size_t)seg * kMaxChunks : (size_t)v.d.chunk_begin);
   v.list = p.list + v.d.list_base;
   v.idx_out = p.idx_out + v.d.koff;
   v.vals_row = p.vals_row ? p.vals_row + v.d.koff : nullptr;
@@ -1141,7 +1156,8 @@ __global__ void k_set_counter(uint64_t* __restrict__ counter, uint64_t value) {
 // consecutive elements, run r starting at (r stride) rounded down to a multiple
 // of kGuessRun.  The last block to finish takes the top digit d of the sample's
 // m_hi-th largest key and publishes d << 19 (kNoGuess if the sample is smaller
-// than m_hi).  The bound is only a guess: whoever uses it checks that at least
+// than m_hi, or more than m_max of its keys reach that bound).  GT = kGNone samples
+// the residuals alone.  The bound is only a guess: whoever uses it checks that at least
 // k keys of the whole vector reach it.
 //   With sample_keys (vector 0 only: room for runs kGuessRun keys) every block
 //   also stores its sample's keys there, for k_guess_refine.
@@ -1149,7 +1165,7 @@ __global__ void k_set_counter(uint64_t* __restrict__ counter, uint64_t value) {
 template <int GT>
 __global__ void __launch_bounds__(256)
 k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_t stride, uint32_t m_hi,
-        uint32_t* __restrict__ sample_keys) {
+        uint32_t m_max, uint32_t* __restrict__ sample_keys) {
   __shared__ uint32_t lh[kHistBins];
   __shared__ uint32_t wsum[4];
   __shared__ int last_sh, hit_sh;
@@ -1167,16 +1183,16 @@ k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_
     v4f a[kGuessRun / 4], b[kGuessRun / 4];
 #pragma unroll
     for (int i = 0; i < kGuessRun / 4; ++i) {
-      a[i] = load4g<false, GT>(gp, e0 + 4 * i);
+      if (GT != kGNone) a[i] = load4g<false, GT>(gp, e0 + 4 * i);
       b[i] = load4<false>(rp + e0 + 4 * i);
     }
 #pragma unroll
     for (int i = 0; i < kGuessRun / 4; ++i) {
       uint4 kq;
-      kq.x = __float_as_uint(a[i].x + b[i].x) & kKeyMask;
-      kq.y = __float_as_uint(a[i].y + b[i].y) & kKeyMask;
-      kq.z = __float_as_uint(a[i].z + b[i].z) & kKeyMask;
-      kq.w = __float_as_uint(a[i].w + b[i].w) & kKeyMask;
+      kq.x = __float_as_uint(GT != kGNone ? a[i].x + b[i].x : b[i].x) & kKeyMask;
+      kq.y = __float_as_uint(GT != kGNone ? a[i].y + b[i].y : b[i].y) & kKeyMask;
+      kq.z = __float_as_uint(GT != kGNone ? a[i].z + b[i].z : b[i].z) & kKeyMask;
+      kq.w = __float_as_uint(GT != kGNone ? a[i].w + b[i].w : b[i].w) & kKeyMask;
       atomicAdd(&lh[kq.x >> 19], 1u);
       atomicAdd(&lh[kq.y >> 19], 1u);
       atomicAdd(&lh[kq.z >> 19], 1u);
@@ -1220,7 +1236,8 @@ k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_
 #pragma unroll
   for (int j = 15; j >= 0; --j) {
     if (above < m_hi && above + h[j] >= m_hi) {  // one thread, one bin
-      hit_sh = 16 * tid + j;
+      // (a bound that so many keys reach that the list could not take them is none)
+      if (above + h[j] <= m_max) hit_sh = 16 * tid + j;
       hit_above_sh = above;
     }
     above += h[j];
@@ -2182,6 +2199,228 @@ __device__ __forceinline__ void compact_tiles_body(const SelParams& p) {
     const uint32_t v = lh[b];
     if (v) atomicAdd(&htop[b], v);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Marking on vectors that are only read (k_mark_spans): a wave works alone on spans of
+// 2048 or 8192 consecutive elements.  Per row of 64 float4 groups it needs the largest
+// magnitude of each group, one comparison with the bound and, where a group reaches it,
+// the group's place in a queue on chip; 64 queued groups at a time are then taken one per
+// lane, their marked elements ranked (three ballots) and stored.  About 200 instructions a
+// wave and 2048 elements, so that the stream of loads is what bounds it: 102 us on 138 M
+// elements (5.4 TB/s), one in a hundred kept; a form of k_pass_mark that only read, about
+// 1700 instructions, took 191, and the two passes of the histogram route take 116 + 141.
+// ---------------------------------------------------------------------------
+constexpr int kSpanStep = 2048;  // elements a wave loads at a time: 8 rows of 64 float4 groups
+struct SpanQueue {
+  uint4 val[128];      // the queued groups' raw bits
+  uint32_t group[128]; // their numbers (element / 4)
+};
+
+// The elements of x[e0, min(e0 + span, n)) whose key reaches the bound, as (index, raw bits) in
+// ascending order to dst[0 .. cap); returns their number, which may be larger than cap.  With lh their
+// top digits are counted there.  The 64 lanes of a wave call it; gf is the bound as a float (an element
+// is marked if not |x| < gf, so a NaN is).
+template <bool NT>
+__device__ __forceinline__ uint32_t wave_span(const float* __restrict__ x, int64_t n, int64_t e0, int span, float gf,
+                                              SpanQueue& qu, uint2* __restrict__ dst, uint32_t cap,
+                                              uint32_t* __restrict__ lh) {
+  const uint32_t lane = lane_id();
+  uint32_t count = 0u, head = 0u, queued = 0u;
+  // takes the first m queued groups, one per lane
+  auto take = [&](uint32_t m) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint32_t p = (head + lane) & 127u;
+    const uint4 v = qu.val[p];
+    const uint32_t g = qu.group[p];
+    const uint32_t raw[4] = {v.x, v.y, v.z, v.w};
+    uint32_t own = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      own |= (!(__builtin_fabsf(__uint_as_float(raw[e])) < gf) && (int64_t)4 * g + e < n) ? 1u << e : 0u;
+    if (lane >= m) own = 0u;
+    const uint32_t c = (uint32_t)__popc(own);
+    uint32_t before = 0u, total = 0u;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const uint64_t plane = __ballot((c >> b) & 1u);
+      before += popc_lt(plane) << b;
+      total += (uint32_t)__popcll(plane) << b;
+    }
+    uint32_t pos = count + before;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if ((own >> e) & 1u) {
+        if (pos < cap) dst[pos] = make_uint2(4u * g + (uint32_t)e, raw[e]);
+        if (lh != nullptr) atomicAdd(&lh[(raw[e] & kKeyMask) >> 19], 1u);
+        ++pos;
+      }
+    }
+    count += total;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();  // (what is queued next may overwrite these)
+  };
+  for (int64_t base = e0; base < e0 + span && base < n; base += kSpanStep) {
+    const uint32_t g0 = (uint32_t)(base >> 2) + lane;
+    v4f v[8];
+    if (base + kSpanStep <= n) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = load4<NT>(x + 4 * (int64_t)(g0 + 64u * u));
+    } else {  // the vector's end: absent elements as 0, which only a bound of 0 marks (take() looks again)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t j = 4 * (int64_t)(g0 + 64u * u);
+        v[u] = v4f{0.f, 0.f, 0.f, 0.f};
+        if (j + 4 <= n) {
+          v[u] = load4<false>(x + j);
+        } else {
+          if (j + 0 < n) v[u].x = x[j + 0];
+          if (j + 1 < n) v[u].y = x[j + 1];
+          if (j + 2 < n) v[u].z = x[j + 2];
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float top = __builtin_elementwise_maximum(
+          __builtin_elementwise_maximum(__builtin_fabsf(v[u].x), __builtin_fabsf(v[u].y)),
+          __builtin_elementwise_maximum(__builtin_fabsf(v[u].z), __builtin_fabsf(v[u].w)));  // NaN if any is
+      const bool hit = !(top < gf);
+      const uint64_t hits = __ballot(hit);
+      if (hits != 0ull) {
+        if (hit) {
+          const uint32_t p = (head + queued + popc_lt(hits)) & 127u;
+          qu.val[p] = make_uint4(__float_as_uint(v[u].x), __float_as_uint(v[u].y), __float_as_uint(v[u].z),
+                                 __float_as_uint(v[u].w));
+          qu.group[p] = g0 + 64u * u;
+        }
+        queued += (uint32_t)__popcll(hits);
+        if (queued >= 64u) {
+          take(64u);
+          head += 64u;
+          queued -= 64u;
+        }
+      }
+    }
+  }
+  if (queued != 0u) take(queued);
+  return count;
+}
+
+// grid = (blocks, vectors), block = 256; vector y uses slot y and piece row y.  Every span's entries go to
+// its piece, the first tiles.cap of them, and their number to tiles.cnt; a vector without a bound is left alone.
+template <bool NT>
+__global__ void __launch_bounds__(256)
+k_mark_spans(PtrTable x, int64_t n, int64_t chunk_elems, uint32_t* __restrict__ h_all, TileBuf tiles) {
+  __shared__ SpanQueue qu[4];
+  const int v = blockIdx.y;
+  uint32_t* __restrict__ slot = h_all + (size_t)v * kSlotWords;
+  const uint32_t gkey = slot[kSlotCtrl + 1];
+  if (gkey == kNoGuess) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t nspans = (n + tiles.span - 1) / tiles.span;
+  uint2* __restrict__ buf = tiles.buf + (size_t)v * (size_t)tiles.buf_stride;
+  uint32_t* __restrict__ cnt = tiles.cnt + (size_t)v * (size_t)tiles.cnt_stride;
+  for (int64_t sp = (int64_t)blockIdx.x * 4 + wave; sp < nspans; sp += (int64_t)gridDim.x * 4) {
+    const uint32_t c = wave_span<NT>(x.p[v], n, sp * tiles.span, tiles.span, __uint_as_float(gkey), qu[wave],
+                                     buf + (size_t)sp * (size_t)tiles.cap, (uint32_t)tiles.cap, nullptr);
+    if (lane_id() == 0) {
+      cnt[sp] = c;
+      if (c != 0u) atomicAdd(&slot[kSlotMcount + (sp * tiles.span) / chunk_elems], c);
+    }
+  }
+}
+
+// The survivor list from the spans' pieces: one block of 1024 threads per chunk copies them, in order, to
+// the list from chunk_off[c] on and counts the entries' top digits.  A span with more entries than its piece
+// holds is marked again, into the list.
+__device__ __forceinline__ void compact_spans_body(const SelParams& p) {
+  constexpr int T = 1024, WAVES = T / 64;
+  __shared__ uint32_t lh[kHistBins];
+  __shared__ uint32_t pre[65];  // entries before each of 64 spans, and of all of them
+  __shared__ SpanQueue qu[WAVES];
+
+  const SegView sv = seg_view(p, blockIdx.y);
+  const int c = blockIdx.x;
+  if (c >= sv.d.geom.nchunks) return;
+  const SelState st = *sv.st;
+  if (st.use_mask == 0u || *p.err) return;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int64_t n = p.n;
+  const uint32_t cap = sv.d.cap, piece = (uint32_t)sv.tcap;
+  const int64_t span = p.tiles.span;
+  uint2* __restrict__ list = sv.list;
+
+  for (int b = tid; b < kHistBins; b += T) lh[b] = 0u;
+  const int64_t c_begin = sv.d.geom.chunk0 + (int64_t)c * sv.d.geom.chunk_elems;  // a whole number of spans
+  int64_t c_end = c_begin + sv.d.geom.chunk_elems;
+  if (c_end > n) c_end = n;
+  const int64_t s_hi = (c_end + span - 1) / span;
+  uint32_t run = sv.chunk_off[c];  // list position of the next entry of this chunk
+  for (int64_t s0 = c_begin / span; s0 < s_hi; s0 += 64) {
+    const int ns = (int)(s_hi - s0 < 64 ? s_hi - s0 : 64);
+    const uint32_t mine = lane < ns ? sv.tcnt[s0 + lane] : 0u;  // (every wave scans the counts itself)
+    const uint32_t incl = wave_incl_scan(mine);
+    const uint32_t total = __shfl(incl, 63, 64);
+    const uint64_t over = __ballot(mine > piece);
+    __syncthreads();  // pre is free, and the histogram cleared
+    if (wave == 0) {
+      pre[lane] = incl - mine;
+      if (lane == 63) pre[64] = total;
+    }
+    __syncthreads();
+    for (uint32_t f0 = (uint32_t)tid; f0 < total; f0 += 2 * T) {
+      uint2 ent[2];
+      bool ok[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t f = f0 + (uint32_t)u * T;
+        const uint32_t fc = f < total ? f : total - 1u;
+        int i = 0;  // the span this entry belongs to: the last whose first entry is not behind it
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) i += pre[i + w] <= fc ? w : 0;
+        const uint32_t r = fc - pre[i];
+        ok[u] = f < total && r < piece && pre[i + 1] - pre[i] <= piece;
+        ent[u] = sv.tbuf[(size_t)(s0 + i) * piece + (r < piece ? r : 0u)];
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t f = f0 + (uint32_t)u * T;
+        if (ok[u]) {
+          if (run + f < cap) list[run + f] = ent[u];
+          atomicAdd(&lh[(ent[u].y & kKeyMask) >> 19], 1u);
+        }
+      }
+    }
+    for (int i = wave; i < ns; i += WAVES) {
+      if ((over >> i) & 1ull) {
+        const uint32_t at = run + pre[i];
+        wave_span<false>(sv.x, n, (s0 + i) * span, (int)span, __uint_as_float(st.list_lo), qu[wave], list + at,
+                         at < cap ? cap - at : 0u, lh);
+      }
+    }
+    run += total;
+  }
+  __syncthreads();
+  uint32_t* __restrict__ htop = sv.htop + (size_t)(c % sv.htop_reps) * kHistBins;
+  for (int b = tid; b < kHistBins; b += T) {
+    const uint32_t v = lh[b];
+    if (v) atomicAdd(&htop[b], v);
+  }
+}
+
+// The kernel behind k_pick_mask where k_mark_spans left pieces: the list from them, or k_hist0's work.
+__global__ void __launch_bounds__(1024)
+k_spans_or_hist(SelParams p, SelParams p_full) {
+  const SelState* st = seg_view(p, blockIdx.y).st;
+  if (st->use_mask != 0u)
+    compact_spans_body(p);
+  else if (st->need_full != 0u)
+    hist0_body<1024>(p_full);
 }
 
 // k_mask_or_hist : the kernel behind k_pick_mask.  Per segment it does whichever of the two

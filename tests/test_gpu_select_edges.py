@@ -98,3 +98,59 @@ def test_gain_and_variance_on_both_sides_of_the_cache_limit(w, n):
         v = float(vals[r].double().square().sum())
         np.testing.assert_allclose(float(out[r]), float(d.var(correction=0)), rtol=1e-9)
         np.testing.assert_allclose(float(gain[r]), v / (v + float(d.square().sum())), rtol=1e-9)
+
+
+# Selections on several whole vectors at once, on the route that marks in one read (the option sends short
+# vectors there too): spans' and groups' edges, ragged ends, spans with more marks than their piece holds, a
+# sample that gives no bound, and a bound that the list could not serve.
+@pytest.mark.parametrize("n", [16384, 16387, 32767, 40961, 3 * 32768 + 2, 500_003])
+@pytest.mark.parametrize("kind", ["normal", "ties", "special", "clustered", "equal", "zeros"])
+def test_selection_marked_in_one_read(n, kind, monkeypatch):
+    import torch
+    import gpu_util
+
+    monkeypatch.setitem(gpu_util.OPTIONS, "guess_min_n", 4096)
+    rng = np.random.default_rng(n)
+    w = 5
+    xs = [_values(rng, n, kind) for _ in range(w)]
+    if kind == "clustered":
+        for r, x in enumerate(xs):
+            x[(r * n) // w:(r * n) // w + n // 50] *= np.float32(1000.0)
+    elif kind == "equal":
+        xs = [np.full(n, np.float32(0.5 if r % 2 else -2.0)) for r in range(w)]
+    elif kind == "zeros":
+        for x in xs:
+            x[rng.permutation(n)[: n - 20]] = 0.0
+    xd = [torch.from_numpy(x).cuda() for x in xs]
+    ctx = gpu_util.make_context(w, n, n // 8)
+    for k in (1, n // 1000 + 1, n // 100, n // 33, n // 8):
+        idx = torch.full((w, k), -1, dtype=torch.int32, device="cuda")
+        vals = torch.full((w, k), float("nan"), device="cuda")
+        sq = torch.zeros(w, dtype=torch.float64, device="cuda")
+        ctx.artopk_topk_workers(xd, k, idx, vals, sq)
+        one = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        ctx.artopk_select_topk(xd[w - 1], k, one)
+        ctx.status()
+        for r in range(w):
+            want = orc.topk_indices(xs[r], k)
+            assert np.array_equal(idx[r].cpu().numpy(), want), (n, kind, k, r)
+            assert np.array_equal(vals[r].cpu().numpy().view(np.uint32), xs[r][want].view(np.uint32))
+            assert np.array_equal(xd[r].cpu().numpy().view(np.uint32), xs[r].view(np.uint32))
+        assert np.array_equal(one.cpu().numpy(), orc.topk_indices(xs[w - 1], k))
+
+
+# more vectors than a batch holds, and batches whose shares of the list are small (one in eight kept)
+@pytest.mark.parametrize("w,n,k", [(17, 20_001, 2500), (33, 9001, 40), (3, 4_300_000, 600_000), (9, 4_300_001, 43_000)])
+def test_batches_of_whole_vectors(w, n, k):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    rng = np.random.default_rng(w)
+    xs = [_values(rng, n, "ties" if r % 2 else "normal") for r in range(w)]
+    xd = [torch.from_numpy(x).cuda() for x in xs]
+    ctx = lib.Context(w, n, k)
+    idx = torch.full((w, k), -1, dtype=torch.int32, device="cuda")
+    ctx.artopk_topk_workers(xd, k, idx)
+    ctx.status()
+    for r in range(w):
+        assert np.array_equal(idx[r].cpu().numpy(), orc.topk_indices(xs[r], k)), r
