@@ -148,13 +148,19 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 element in 256 or denser (beyond one in 32
  *                                 the alternative is the histogram route);
  *                                 2: for every selection; 0: never
+ *   ARTOPK_OPT_SHORT_MAX_N        longest flat vector whose step runs in three
+ *                                 launches (with at most 16384 elements kept;
+ *                                 three quarters of it under the variance rules
+ *                                 with fewer than eight workers);
+ *                                 0 .. 2^21 (0 = never), default 1048576
  */
 enum {
   ARTOPK_OPT_GUESS_MIN_N = 0,
   ARTOPK_OPT_UPDATE_TILES_MIN_N = 1,
   ARTOPK_OPT_LEADER_FIRST = 2,
   ARTOPK_OPT_NONTEMPORAL = 3,
-  ARTOPK_OPT_STAGE_TILES = 4
+  ARTOPK_OPT_STAGE_TILES = 4,
+  ARTOPK_OPT_SHORT_MAX_N = 5
 };
 int artopk_set_option(artopk_ctx* ctx, int32_t key, int64_t value);
 int artopk_get_option(const artopk_ctx* ctx, int32_t key, int64_t* value_out);

@@ -16,7 +16,7 @@ ARTOPK_STAR, ARTOPK_VAR, ARTOPK_FIXED, ARTOPK_VAR_TOPK, ARTOPK_VAR_G = 0, 1, 2, 
 ARTOPK_STAR_COUNTER = 5
 ARTOPK_G_F32, ARTOPK_G_BF16, ARTOPK_G_F16 = 0, 1, 2
 ARTOPK_OPT_GUESS_MIN_N, ARTOPK_OPT_UPDATE_TILES_MIN_N, ARTOPK_OPT_LEADER_FIRST, ARTOPK_OPT_NONTEMPORAL = 0, 1, 2, 3
-ARTOPK_OPT_STAGE_TILES = 4
+ARTOPK_OPT_STAGE_TILES, ARTOPK_OPT_SHORT_MAX_N = 4, 5
 PROF_NAMES = ("pass_a", "select", "gather", "update", "total")
 
 _SYMBOLS = (

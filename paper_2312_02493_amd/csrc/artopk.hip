@@ -43,6 +43,14 @@ constexpr int32_t kMaxBatch = 16;  // vectors selected on in one launch set
 // 234/287.  (One in ten kept: 25.6 M 116 against 137, 138 M 390 against 389, so denser than one in 32 never.)
 constexpr int64_t kGuessMinN = (int64_t)1 << 25, kReadGuessMinN = (int64_t)3 << 23;
 
+// Flat steps on short vectors run in three launches (small_step) up to ARTOPK_OPT_SHORT_MAX_N elements, or three
+// quarters of that where the leader comes from the data and fewer than eight workers share the cost of it, and up
+// to 16384 kept (a single block takes the last digits).  Measured, us, ten or eight launches against three, one in
+// a hundred kept: leader known, 2 workers: 65537 elements 58/31, 262144 58/36, 1 M 64/55, 1.6 M 66/70; 16 workers:
+// 58/36, 62/40, 89/73, 107/95.  Variance rule, 2 workers: 49/36, 50/40, 524288 52/46, 1 M 56/61; 8 workers: 53/38,
+// 55/44, 67/56, 88/84, 1.6 M 107/110; 16 workers: 60/43, 73/55, 94/76, 134/117.
+constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSmallMaxChunks * kTile, kSmallMaxK = 16384;
+
 struct Scratch {
   // zeroed before every select: one kSegWords block per segment, then the look-back flags
   uint32_t* h_all = nullptr;      // [max_w][kSlotWords] whole-vector histograms of the fused pass, guess sample
@@ -68,6 +76,7 @@ struct Scratch {
   int64_t tilebuf_entries = 0;
   uint32_t* tile_cnt = nullptr;   // [max_n / kPassTile + 1] entries staged per tile
   uint32_t* sample_keys = nullptr;  // [16384 kGuessRun] keys of one vector's guess sample
+  SmallScratch small{};           // short vectors' steps: zero whenever no step is running
   SegDesc* table_dev = nullptr;   // [max_seg] segment descriptors
   uint32_t* chunk_map = nullptr;  // [kMaxChunks + max_seg] (segment << 16) | chunk, one entry per chunk of the layout
   uint32_t cap = 0;               // list capacity of a flat (one-segment) select
@@ -107,6 +116,8 @@ struct artopk_ctx {
   int64_t update_tiles_min_n = (int64_t)1 << 22;
   int stage_tiles = 1;  // guess route, one marking worker: the fused pass hands the marked elements on per tile
                         // (0 never, 1 for selections of one element in 256 or denser, 2 whenever a piece can hold a tile's share)
+  int64_t small_max_n = kSmallMaxN;  // flat steps of up to about this many elements run in three launches
+  bool small_off = false;  // a launch of such a step failed: its scratch may not be zero any more
   void* slab = nullptr;
   Scratch s;
   // how the last step ran (artopk_select_info)
@@ -439,6 +450,8 @@ SelParams make_params(const artopk_ctx* c, const Plan& pl, const PtrTable& tab, 
   p.leader_dev = s.leader_dev;
   p.n = n;
   p.hcopies = s.h_all;
+  p.hcopy_stride = kSlotWords;
+  p.cand_off = nullptr;
   p.h_all = hist_from_pass ? s.h_all : nullptr;
   p.mask = nullptr;
   p.mask_stride = s.mask_stride;
@@ -1036,6 +1049,94 @@ int enqueue_topk_workers(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t 
   return ARTOPK_OK;
 }
 
+template <int STATS, int GT>
+void launch_small_pass_g(artopk_ctx* c, dim3 grid, const PtrTable& g, const PtrTable& r, int64_t n, const SelParams& p,
+                         const LeaderArgs& la, int leader, int32_t* leader_out) {
+  hipLaunchKernelGGL((k_small_pass<STATS, GT>), grid, dim3(1024), 0, c->stream, g, r, n, c->s.small, c->s.partials, p, la,
+                     (int32_t)leader, c->s.leader_dev, leader_out);
+}
+
+template <int STATS>
+void launch_small_pass(artopk_ctx* c, dim3 grid, const PtrTable& g, const PtrTable& r, int64_t n, const SelParams& p,
+                       const LeaderArgs& la, int leader, int32_t* leader_out) {
+  if (c->g_type == ARTOPK_G_BF16)
+    launch_small_pass_g<STATS, kGBF16>(c, grid, g, r, n, p, la, leader, leader_out);
+  else if (c->g_type == ARTOPK_G_F16)
+    launch_small_pass_g<STATS, kGF16>(c, grid, g, r, n, p, la, leader, leader_out);
+  else
+    launch_small_pass_g<STATS, kGF32>(c, grid, g, r, n, p, la, leader, leader_out);
+}
+
+// A flat step on a short vector in three launches.  leader >= 0: known up front; else it comes from the
+// statistics (stats 1 or 2) or is in leader_dev already (stats 0).
+int small_step(artopk_ctx* ctx, const PtrTable& gt, const PtrTable& rt, int32_t w, int64_t n, int64_t k, int stats,
+               int leader, int32_t* leader_out, double* var_out, int32_t* idx_out, float* vals_out, float* sum_out,
+               float* update_out) {
+  Scratch& s = ctx->s;
+  hipStream_t st = ctx->stream;
+  const bool known = leader >= 0;
+  const int32_t workers = known ? 1 : w;
+  Plan pl = flat_plan(ctx, n, k, known ? leader : -1);
+  pl.desc[0].geom.chunk0 = 0;
+  pl.desc[0].geom.chunk_elems = kTile;
+  pl.desc[0].geom.nchunks = (int32_t)((n + kTile - 1) / kTile);
+  pl.desc[0].hreps = kSmallReps;
+  SmallScratch ss = s.small;
+  ss.workers = workers;
+  SelParams p = make_params(ctx, pl, rt, n, idx_out, nullptr, known ? 0 : 1, false);
+  p.hcopies = ss.hist;
+  p.hcopy_stride = (int64_t)kSmallReps * kHistBins;
+  p.cand_off = ss.cand_off;
+  LeaderArgs la{};
+  if (stats != 0) {
+    la.partials = s.partials;
+    la.w_count = (int)w;
+    la.nblk = pl.desc[0].geom.nchunks;
+    la.n = n;
+    la.var_scratch = s.var_scratch;
+    la.var_out = var_out;
+    la.leader_dev = s.leader_dev;
+    la.leader_out = leader_out;
+  }
+  PtrTable g1 = gt, r1 = rt;
+  if (known) {
+    g1.p[0] = gt.p[leader];
+    r1.p[0] = rt.p[leader];
+  }
+  ctx->small_off = true;  // (until the kernel that leaves the scratch zero is enqueued)
+  const dim3 grid((unsigned)pl.desc[0].geom.nchunks, (unsigned)workers);
+  prof_dom(ctx, false);
+  if (stats == 0)
+    launch_small_pass<0>(ctx, grid, g1, r1, n, p, la, leader, leader_out);
+  else if (stats == 1)
+    launch_small_pass<1>(ctx, grid, g1, r1, n, p, la, -1, nullptr);
+  else
+    launch_small_pass<2>(ctx, grid, g1, r1, n, p, la, -1, nullptr);
+  HIP_TRY(ctx, hipGetLastError());
+  prof_dom(ctx, true);
+  prof_mark(ctx, 1);
+  hipLaunchKernelGGL(k_small_select, dim3((unsigned)pl.desc[0].geom.nchunks), dim3(1024), 0, st, p, ss);
+  HIP_TRY(ctx, hipGetLastError());
+  ctx->small_off = false;
+  prof_mark(ctx, 2);
+  const dim3 tiles((unsigned)((n + kSmallTile - 1) / kSmallTile));
+  if (!known)
+    hipLaunchKernelGGL(k_small_gather, tiles, dim3(256), 0, st, p, ss, rt, (int)w, k, vals_out, sum_out, update_out);
+  else if (ctx->g_type == ARTOPK_G_BF16)
+    hipLaunchKernelGGL(k_small_rest<kGBF16>, tiles, dim3(256), 0, st, p, ss, gt, rt, (int)w, leader, k, vals_out, sum_out,
+                       update_out);
+  else if (ctx->g_type == ARTOPK_G_F16)
+    hipLaunchKernelGGL(k_small_rest<kGF16>, tiles, dim3(256), 0, st, p, ss, gt, rt, (int)w, leader, k, vals_out, sum_out,
+                       update_out);
+  else
+    hipLaunchKernelGGL(k_small_rest<kGF32>, tiles, dim3(256), 0, st, p, ss, gt, rt, (int)w, leader, k, vals_out, sum_out,
+                       update_out);
+  HIP_TRY(ctx, hipGetLastError());
+  prof_mark(ctx, 3);
+  prof_mark(ctx, 4);
+  return ARTOPK_OK;
+}
+
 }  // namespace
 
 namespace {
@@ -1045,7 +1146,8 @@ struct Layout {
   uint32_t cap = 0;
   int64_t list_entries = 0, max_tiles = 0, mask_stride = 0, tilebuf_entries = 0;
   int32_t blocks = 0;  // scratch blocks: one per segment, or per vector of a batch
-  size_t o_hall = 0, o_mask = 0, o_zero = 0, o_S = 0, o_coff = 0, o_part = 0, o_var = 0, o_leader = 0, o_err = 0, o_counter = 0, o_list = 0, o_vals = 0, o_rows = 0, o_table = 0, o_cmap = 0, o_tstart = 0, o_tbuf = 0, o_tcnt = 0, o_sample = 0;
+  size_t o_hall = 0, o_mask = 0, o_zero = 0, o_S = 0, o_coff = 0, o_part = 0, o_var = 0, o_leader = 0, o_err = 0, o_counter = 0, o_list = 0, o_vals = 0, o_rows = 0, o_table = 0, o_cmap = 0, o_tstart = 0, o_tbuf = 0, o_tcnt = 0, o_sample = 0, o_small = 0;
+  size_t small_words = 0;  // words of the short vectors' scratch that have to be zero between steps
   size_t total = 0;
 };
 
@@ -1107,6 +1209,9 @@ Layout scratch_layout(int32_t max_w, int64_t max_n, int64_t max_k, int32_t max_s
   L.o_tbuf = take((size_t)L.tilebuf_entries * sizeof(uint2));
   L.o_tcnt = take((size_t)(max_tiles_pass + 1) * sizeof(uint32_t));
   L.o_sample = take((size_t)16384 * kGuessRun * sizeof(uint32_t));
+  L.small_words = (size_t)max_w * kSmallReps * kHistBins + 16;
+  const int64_t small_n = max_n < kSmallMaxNLimit ? max_n : kSmallMaxNLimit;
+  L.o_small = take((L.small_words + (2 * 16 + 2 + 2) * kSmallMaxChunks + (size_t)small_n) * sizeof(uint32_t));
   L.total = off;
   return L;
 }
@@ -1176,11 +1281,22 @@ int artopk_create(artopk_ctx** out, int32_t max_w, int64_t max_n, int64_t max_k,
   s.tile_cnt = reinterpret_cast<uint32_t*>(base + L.o_tcnt);
   s.sample_keys = reinterpret_cast<uint32_t*>(base + L.o_sample);
 
+  uint32_t* small = reinterpret_cast<uint32_t*>(base + L.o_small);
+  s.small.hist = small;
+  s.small.ctr = small + (size_t)max_w * kSmallReps * kHistBins;
+  s.small.low_bits = reinterpret_cast<uint64_t*>(small + L.small_words);
+  s.small.before = reinterpret_cast<uint2*>(s.small.low_bits + 16 * kSmallMaxChunks);
+  s.small.cand_off = reinterpret_cast<uint32_t*>(s.small.before + kSmallMaxChunks);
+  s.small.sure = s.small.cand_off + kSmallMaxChunks;
+  s.small.cand = s.small.sure + kSmallMaxChunks;
+
   // leader, error word and step counter start at zero (stream-ordered before any later call)
   hipLaunchKernelGGL(k_fill_zero, dim3(1), dim3(256), 0, c->stream,
                      reinterpret_cast<uint32_t*>(s.leader_dev), (size_t)1, s.err_dev, (size_t)1,
                      reinterpret_cast<uint32_t*>(s.counter_dev), (size_t)2, 0, (int32_t*)nullptr,
                      (int32_t*)nullptr);
+  hipLaunchKernelGGL(k_fill_zero, dim3(64), dim3(256), 0, c->stream, small, L.small_words, (uint32_t*)nullptr, (size_t)0,
+                     (uint32_t*)nullptr, (size_t)0, 0, (int32_t*)nullptr, (int32_t*)nullptr);
   if (hipGetLastError() != hipSuccess) {
     (void)hipFree(c->slab);
     delete c;
@@ -1258,6 +1374,10 @@ int artopk_set_option(artopk_ctx* ctx, int32_t key, int64_t value) {
       if (value < 0 || value > 2) return fail(ctx, ARTOPK_EINVAL, "ARTOPK_OPT_STAGE_TILES takes 0, 1 or 2");
       ctx->stage_tiles = (int)value;
       return ARTOPK_OK;
+    case ARTOPK_OPT_SHORT_MAX_N:
+      if (value < 0 || value > kSmallMaxNLimit) return fail(ctx, ARTOPK_EINVAL, "ARTOPK_OPT_SHORT_MAX_N outside [0, 2^21]");
+      ctx->small_max_n = value;
+      return ARTOPK_OK;
     default:
       return fail(ctx, ARTOPK_EINVAL, "unknown option %d", key);
   }
@@ -1271,6 +1391,7 @@ int artopk_get_option(const artopk_ctx* ctx, int32_t key, int64_t* value_out) {
     case ARTOPK_OPT_LEADER_FIRST: *value_out = ctx->leader_first ? 1 : 0; return ARTOPK_OK;
     case ARTOPK_OPT_NONTEMPORAL: *value_out = ctx->pass_a_nt ? 1 : 0; return ARTOPK_OK;
     case ARTOPK_OPT_STAGE_TILES: *value_out = ctx->stage_tiles; return ARTOPK_OK;
+    case ARTOPK_OPT_SHORT_MAX_N: *value_out = ctx->small_max_n; return ARTOPK_OK;
     default: return ARTOPK_EINVAL;
   }
 }
@@ -1658,6 +1779,21 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
     if (update_out && (rc = enqueue_update_fill(ctx, update_out, n, idx_out, sum_out, k))) return rc;
     prof_mark(ctx, 4);
     return ARTOPK_OK;
+  }
+
+  const int64_t short_n = (device_leader && w < 8) ? ctx->small_max_n / 4 * 3 : ctx->small_max_n;
+  if (!segmented && !gp.on && n <= short_n && k <= kSmallMaxK && !ctx->small_off && (leader_first || device_leader)) {
+    ctx->lvl1_a = 0;
+    ctx->lvl1_b = 1;
+    prof_begin(ctx);
+    prof_mark(ctx, 0);
+    if (mode == ARTOPK_STAR_COUNTER) {
+      hipLaunchKernelGGL(k_counter_leader, dim3(1), dim3(64), 0, st, s.counter_dev, (int32_t)w, s.leader_dev, leader_out);
+      HIP_TRY(ctx, hipGetLastError());
+    }
+    if (leader_first) ctx->last_dom_workers = 1;
+    return small_step(ctx, gt, rt, w, n, k, mode == ARTOPK_VAR ? 1 : mode == ARTOPK_VAR_G ? 2 : 0,
+                      leader_first ? leader_host : -1, leader_out, var_out, idx_out, vals_out, sum_out, update_out);
   }
 
   if (leader_first) {

@@ -40,6 +40,7 @@
 //   k_gather         vals / ordered sum / residual zeroing at the k indices
 //   k_zero_at        residual zeroing alone
 //   k_update_fill    dense update = zeros + k scattered sums, written once
+//   k_small_pass, k_small_select, k_small_rest / k_small_gather   a whole step on a short vector
 //   k_update_tiles   the same for long, sparsely kept vectors: zeros streamed tile
 //                    by tile, the sums stored behind them
 //
@@ -159,6 +160,8 @@ struct SelParams {
   const int32_t* leader_dev;
   int64_t n;               // length of the vector
   uint32_t* hcopies;       // copies of top-digit histograms that k_hist0 fills (h_all's memory, when no pass fills that)
+  int64_t hcopy_stride;    // their words per vector
+  uint32_t* cand_off;      // k_pick0's body leaves the number of candidates in front of every chunk here, or nullptr
   const uint32_t* h_all;   // [workers][kSlotWords] whole-vector histograms from the fused pass, or nullptr
   const uint64_t* mask;    // [workers][mask_stride] survivor bit masks from the fused pass, or nullptr
   int64_t mask_stride;     // 64-bit words per worker
@@ -234,6 +237,12 @@ __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
 __device__ __forceinline__ uint32_t popc_lt(uint64_t mask) {
   // number of set bits of `mask` in lanes below the calling lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Stores that go through the XCD's own cache to where every XCD sees them.
+template <typename V>
+__device__ __forceinline__ void store_through(V* p, V v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -314,7 +323,8 @@ __device__ __forceinline__ double wave_allsum(double v) {
 // Adds up the threads' sums of a block of T threads (all of them call it) and thread 0 writes
 // the block's (n, mean, M2) to partials[w][.][b] (nblk blocks per worker).  Thread 0 must be a
 // thread that saw a value whenever any thread of the block did (it owns the block's first group).
-template <int T>
+// THROUGH: for a reader in the same launch (see last_block).
+template <int T, bool THROUGH = false>
 __device__ __forceinline__ void block_moments(const VarAcc& acc, double* __restrict__ partials, int w, int nblk,
                                               int b) {
   constexpr int NW = T / 64;
@@ -348,9 +358,15 @@ __device__ __forceinline__ void block_moments(const VarAcc& acc, double* __restr
       if (m2 < 0.0) m2 = 0.0;  // rounding only (NaN stays NaN)
     }
     double* __restrict__ out = partials + (size_t)w * 3 * nblk + b;
-    out[0] = N;
-    out[nblk] = mean;
-    out[2 * (size_t)nblk] = m2;
+    if (THROUGH) {
+      store_through(out, N);
+      store_through(out + nblk, mean);
+      store_through(out + 2 * (size_t)nblk, m2);
+    } else {
+      out[0] = N;
+      out[nblk] = mean;
+      out[2 * (size_t)nblk] = m2;
+    }
   }
 }
 
@@ -492,7 +508,8 @@ __device__ __forceinline__ uint32_t block_prefix_incl(uint32_t v, uint32_t* wtot
 // Adds the 4096-bin LDS histogram `lh` of a T-thread block to total[0..4096)
 // and writes its suffix sums to dst[0..4096).  `red` is T words of LDS.  All
 // threads of the block must call it after their last histogram update.
-template <int T>
+// THROUGH: for a reader in the same launch (see last_block).
+template <int T, bool THROUGH = false>
 __device__ __forceinline__ void flush_suffix_hist(uint32_t* lh, uint32_t* red, uint32_t* __restrict__ dst,
                                                   uint32_t* __restrict__ total) {
   constexpr int BPT = kHistBins / T;  // consecutive bins per thread (a multiple of 4)
@@ -522,7 +539,13 @@ __device__ __forceinline__ void flush_suffix_hist(uint32_t* lh, uint32_t* red, u
     q.y = v[4 * j + 1] + carry;
     q.z = v[4 * j + 2] + carry;
     q.w = v[4 * j + 3] + carry;
-    reinterpret_cast<uint4*>(dst)[(BPT / 4) * t + j] = q;
+    if (THROUGH) {
+      uint64_t* d2 = reinterpret_cast<uint64_t*>(dst) + 2 * ((BPT / 4) * t + j);
+      store_through(d2, ((uint64_t)q.y << 32) | q.x);
+      store_through(d2 + 1, ((uint64_t)q.w << 32) | q.z);
+    } else {
+      reinterpret_cast<uint4*>(dst)[(BPT / 4) * t + j] = q;
+    }
   }
 }
 
@@ -546,7 +569,7 @@ __device__ __forceinline__ SegView seg_view(const SelParams& p, int seg, int lea
   v.x = p.tab.p[vec];
   const size_t slot = p.slot_by_leader ? (size_t)vec : 0;  // histogram slot: per vector, or the only one
   v.htop = p.h_all ? const_cast<uint32_t*>(p.h_all) + slot * kSlotWords
-                   : (v.d.hreps > 1 ? p.hcopies + slot * kSlotWords : zb + kSegHtop);
+                   : (v.d.hreps > 1 ? p.hcopies + slot * (size_t)p.hcopy_stride : zb + kSegHtop);
   v.htop_reps = p.h_all ? kHistReps : v.d.hreps;
   v.hseg = zb + kSegHtop;
   v.ctrl = p.h_all ? p.h_all + slot * kSlotWords + kSlotCtrl : nullptr;
@@ -1431,28 +1454,16 @@ __device__ __forceinline__ bool fits_list(const SelState& st, uint32_t cap) {
   return (uint64_t)st.n_gt + (uint64_t)st.cand <= (uint64_t)cap;
 }
 
-// Narrows st (in shared memory) by digit `digit` (1 or 2) using the histogram of
-// that digit over the current candidates.  All T threads of the block call it;
-// `part` is T words of shared memory.
+// Narrows st (in shared memory) by digit `digit` (1 or 2); thread t holds the counts of the bins BPT t .. of
+// that digit over the current candidates.  All T threads call it; `part` is T words of shared memory.
 template <int T>
-__device__ void block_pick(SelState& st, const uint32_t* __restrict__ hist, int digit, uint32_t* part,
-                           uint32_t* __restrict__ err) {
+__device__ void block_pick_bins(SelState& st, const uint32_t (&h)[kHistBins / T], int digit, uint32_t* part,
+                                uint32_t* __restrict__ err) {
   constexpr int BPT = kHistBins / T;
   const int t = threadIdx.x;
-  const int nbins = (int)digit_mask(digit) + 1;
-  uint32_t h[BPT];
   uint32_t tot = 0u;
-  static_assert(BPT % 4 == 0, "whole uint4 groups per thread");
 #pragma unroll
-  for (int j = 0; j < BPT / 4; ++j) {
-    uint4 q = make_uint4(0u, 0u, 0u, 0u);
-    if (BPT * t < nbins) q = reinterpret_cast<const uint4*>(hist)[(BPT / 4) * t + j];  // (nbins is a multiple of BPT)
-    h[4 * j + 0] = q.x;
-    h[4 * j + 1] = q.y;
-    h[4 * j + 2] = q.z;
-    h[4 * j + 3] = q.w;
-    tot += (q.x + q.y) + (q.z + q.w);
-  }
+  for (int j = 0; j < BPT; ++j) tot += h[j];
   __syncthreads();  // st is stable and `part` is free
   uint32_t total;
   uint32_t above = block_suffix_incl<T>(tot, part, &total) - tot;
@@ -1480,6 +1491,27 @@ __device__ void block_pick(SelState& st, const uint32_t* __restrict__ hist, int 
   }
   if (t == 0 && total < need) atomicOr(err, kErrPick);  // histogram does not cover `need`
   __syncthreads();
+}
+
+// The same with the digit's histogram in memory.
+template <int T>
+__device__ void block_pick(SelState& st, const uint32_t* __restrict__ hist, int digit, uint32_t* part,
+                           uint32_t* __restrict__ err) {
+  constexpr int BPT = kHistBins / T;
+  const int t = threadIdx.x;
+  const int nbins = (int)digit_mask(digit) + 1;
+  uint32_t h[BPT];
+  static_assert(BPT % 4 == 0, "whole uint4 groups per thread");
+#pragma unroll
+  for (int j = 0; j < BPT / 4; ++j) {
+    uint4 q = make_uint4(0u, 0u, 0u, 0u);
+    if (BPT * t < nbins) q = reinterpret_cast<const uint4*>(hist)[(BPT / 4) * t + j];  // (nbins is a multiple of BPT)
+    h[4 * j + 0] = q.x;
+    h[4 * j + 1] = q.y;
+    h[4 * j + 2] = q.z;
+    h[4 * j + 3] = q.w;
+  }
+  block_pick_bins<T>(st, h, digit, part, err);
 }
 
 // State at `want_level` (2 or 3) in st (shared).  st.compact_level = the level
@@ -1548,9 +1580,7 @@ __device__ int block_take_leader(const LeaderArgs& la) {
   return best;
 }
 
-__global__ void __launch_bounds__(1024)
-k_pick0(SelParams p, LeaderArgs la) {
-  __shared__ uint32_t part[1024];
+__device__ __forceinline__ void pick0_body(const SelParams& p, const LeaderArgs& la, int seg, uint32_t* part) {
   __shared__ int b0_sh;
   __shared__ int lead_sh;
   const int t = threadIdx.x;
@@ -1563,7 +1593,7 @@ k_pick0(SelParams p, LeaderArgs la) {
     if (t == 0) lead_sh = best;
   }
   __syncthreads();
-  const SegView sv = seg_view(p, blockIdx.y, lead_sh);
+  const SegView sv = seg_view(p, seg, lead_sh);
   if (p.only_if_need_full && sv.st->need_full == 0u) return;
   if (p.from_list && sv.st->use_mask == 0u) return;
   const SelState prev = *sv.st;  // from_list: says how long the list is
@@ -1587,26 +1617,19 @@ k_pick0(SelParams p, LeaderArgs la) {
   uint32_t h[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) h[j] = 0u;
-  if (htop_reps == kHistReps) {  // sixteen loads in flight together
-    for (int r0 = 0; r0 < kHistReps; r0 += 16) {
-      uint4 q[16];
+  for (int r0 = 0; r0 < htop_reps; r0 += 8) {  // eight loads in flight together (one copy: the same one, used once)
+    uint4 q[8];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) q[r] = reinterpret_cast<const uint4*>(htop + (size_t)(r0 + r) * kHistBins)[t];
+    for (int r = 0; r < 8; ++r)
+      q[r] = reinterpret_cast<const uint4*>(htop + (size_t)(r0 + r < htop_reps ? r0 + r : r0) * kHistBins)[t];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < 8; ++r) {
+      if (r0 + r < htop_reps) {
         h[0] += q[r].x;
         h[1] += q[r].y;
         h[2] += q[r].z;
         h[3] += q[r].w;
       }
-    }
-  } else {
-    for (int r = 0; r < htop_reps; ++r) {
-      const uint4 q = reinterpret_cast<const uint4*>(htop + (size_t)r * kHistBins)[t];
-      h[0] += q.x;
-      h[1] += q.y;
-      h[2] += q.z;
-      h[3] += q.w;
     }
   }
   const uint32_t hsum = h[0] + h[1] + h[2] + h[3];
@@ -1648,6 +1671,17 @@ k_pick0(SelParams p, LeaderArgs la) {
   const uint32_t mine = (t < nchunks) ? sv.S[(size_t)t * kHistBins + b0] : 0u;
   const uint32_t upto = block_prefix_incl<1024>(mine, part);
   if (t < nchunks) sv.chunk_off[t] = upto - mine;
+  if (p.cand_off != nullptr) {
+    const uint32_t above = (t < nchunks && b0 + 1 < kHistBins) ? sv.S[(size_t)t * kHistBins + b0 + 1] : 0u;
+    const uint32_t cand_upto = block_prefix_incl<1024>(mine - above, part);
+    if (t < nchunks) p.cand_off[t] = cand_upto - (mine - above);
+  }
+}
+
+__global__ void __launch_bounds__(1024)
+k_pick0(SelParams p, LeaderArgs la) {
+  __shared__ uint32_t part[1024];
+  pick0_body(p, la, blockIdx.y, part);
 }
 
 // ---------------------------------------------------------------------------
@@ -3624,6 +3658,502 @@ k_sum_update(const float* __restrict__ vals, int w_count, int64_t n, const int32
       }
       update[j] = upd;
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Short vectors: a whole step in three launches (k_small_pass, k_small_select and k_small_rest or
+// k_small_gather).  Ten launches, each a few microseconds of latency, were all that such a step took: 65537
+// elements x 2 workers 52 us, now 31; 1 M x 4 61 us, now 52 (18 and 22 us of them in k_small_select and its
+// last block; see small_step's rule for other sizes).  What a single block did in a launch of its own is done by the last block to finish of
+// the launch before it, and nothing has to be cleared first: the scratch of this route (SmallScratch) is
+// zero whenever no step is running, because k_small_select leaves it so.
+// ---------------------------------------------------------------------------
+constexpr int kSmallReps = 8;     // copies of a worker's top-digit histogram
+constexpr int kSmallMaxChunks = 256;  // chunks of kTile elements
+constexpr int kSmallTile = 1024;  // elements per block of the last launch: 256 threads x one float4 group
+
+struct SmallScratch {
+  uint32_t* hist;        // [workers][kSmallReps][kHistBins]
+  uint32_t* ctr;         // blocks done with the first and the second launch
+  // (these are written before they are read in every step)
+  uint32_t* cand_off;    // [kSmallMaxChunks] SelParams::cand_off
+  uint32_t* sure;        // [kSmallMaxChunks] keys above the threshold digit in every chunk
+  uint64_t* low_bits;    // [kSmallMaxChunks * 16] every wave's largest low bits of a candidate, and of their complement
+  uint32_t* cand;        // [2^21] the candidates: low 19 bits, chunk << 19
+  uint2* before;         // [kSmallMaxChunks] list entries above the threshold, and at it, in front of every chunk
+  int32_t workers;       // slots of hist in use
+};
+
+// Whether the calling block is the last of `total` to get here; all its threads call it.  What the other blocks
+// wrote before with store_through or atomics is then visible to it.  (Ordinary stores would need a release fence
+// in every block, which writes the XCD's whole cache back: 54 instead of 14 us for k_small_pass on 1 M elements.)
+__device__ __forceinline__ bool last_block(uint32_t* ctr, uint32_t total) {
+  __shared__ int last_sh;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores and atomics have reached memory
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last_sh = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1u ? 1 : 0;
+  __syncthreads();
+  const bool last = last_sh != 0;
+  if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return last;
+}
+
+// acc = g + residual (in place), per-chunk suffix histograms and whole-vector histograms of every worker of the
+// tables, variance partials (STATS as in k_pass_a); the last block takes the leader (la) and the threshold digit.
+// grid = (chunks of kTile elements, workers), block = 1024.  leader >= 0: known to the host, passed on.
+template <int STATS, int GT>
+__global__ void __launch_bounds__(1024)
+k_small_pass(PtrTable g, PtrTable res, int64_t n, SmallScratch ss, double* __restrict__ partials, SelParams p,
+             LeaderArgs la, int32_t leader, int32_t* __restrict__ leader_dev, int32_t* __restrict__ leader_out) {
+  constexpr int T = 1024, U = 2;
+  static_assert(T * U * 4 == kTile, "a chunk is one tile");
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kHistBins];
+  __shared__ uint32_t red_u[T];
+  const int w = blockIdx.y, c = blockIdx.x, nblk = gridDim.x;
+  const int tid = threadIdx.x;
+  const float* __restrict__ gp = g.p[w];
+  float* __restrict__ rp = res.p[w];
+  if (leader >= 0 && c == 0 && w == 0 && tid == 0) {
+    *leader_dev = leader;
+    if (leader_out) *leader_out = leader;
+  }
+  for (int b = tid; b < kHistBins; b += T) lh[b] = 0u;
+  const int64_t q0 = (int64_t)c * (kTile / 4) + tid, q_end = n >> 2;
+  VarAcc va;
+  v4f a[U], b[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {  // (groups behind the vector re-read its last one, unused)
+    const int64_t q = q0 + u * T < q_end ? q0 + u * T : q_end - 1;
+    if (q_end > 0) {
+      a[u] = load4g<false, GT>(gp, 4 * q);
+      b[u] = load4<false>(rp + 4 * q);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (q0 + u * T < q_end) {
+      v4f v;
+      v.x = a[u].x + b[u].x;
+      v.y = a[u].y + b[u].y;
+      v.z = a[u].z + b[u].z;
+      v.w = a[u].w + b[u].w;
+      store4<false>(rp + 4 * (q0 + u * T), v);
+      if (STATS) {
+        va.seed4(STATS == 2 ? a[u] : v);
+        va.add4(STATS == 2 ? a[u] : v);
+      }
+      atomicAdd(&lh[(__float_as_uint(v.x) & kKeyMask) >> 19], 1u);
+      atomicAdd(&lh[(__float_as_uint(v.y) & kKeyMask) >> 19], 1u);
+      atomicAdd(&lh[(__float_as_uint(v.z) & kKeyMask) >> 19], 1u);
+      atomicAdd(&lh[(__float_as_uint(v.w) & kKeyMask) >> 19], 1u);
+    }
+  }
+  if (c == nblk - 1) {  // the n mod 4 last elements
+    const int64_t j = q_end * 4 + tid;
+    if (j < n) {
+      const float gj = load1g<GT>(gp, j);
+      const float v = gj + rp[j];
+      rp[j] = v;
+      if (STATS) {
+        va.seed1(STATS == 2 ? gj : v);
+        va.add1(STATS == 2 ? gj : v);
+      }
+      atomicAdd(&lh[(__float_as_uint(v) & kKeyMask) >> 19], 1u);
+    }
+  }
+  if (STATS) block_moments<T, true>(va, partials, w, nblk, c);
+  flush_suffix_hist<T, true>(lh, red_u, p.S + ((size_t)w * kMaxChunks + (size_t)c) * kHistBins,
+                       ss.hist + ((size_t)w * kSmallReps + (size_t)(c % kSmallReps)) * kHistBins);
+  if (last_block(&ss.ctr[0], gridDim.x * gridDim.y)) pick0_body(p, la, 0, red_u);
+}
+
+// The selection behind k_small_pass: every block writes its chunk's part of the leader's survivor list, its
+// candidates (top digit = threshold digit) a second time, by themselves, and clears its share of the histograms the
+// pass used.  The last block takes the remaining digits from the candidates, a tenth of the list or so, and counts per
+// chunk the list's entries above and at the threshold.  The outputs are left to the many blocks of the next launch
+// (small_kept): one block that also walked the list and wrote them in order took 40 us more on 1 M elements, one in a
+// hundred kept, one that counted over the whole list 10 us more.
+// grid = chunks (of kTile elements), block = 1024.
+__global__ void __launch_bounds__(1024)
+k_small_select(SelParams p, SmallScratch ss) {
+  constexpr int T = 1024, WAVES = T / 64, PER = 8;
+  static_assert(T * PER == kTile, "a chunk is eight elements a thread");
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kHistBins];
+  __shared__ SelState st;
+  __shared__ uint32_t part[T];
+  __shared__ __attribute__((aligned(16))) uint32_t digit2[128];
+  __shared__ uint32_t cnt[2][kSmallMaxChunks];
+  __shared__ uint32_t low_sh[2];
+  __shared__ uint64_t wtot[WAVES];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = blockIdx.x, nchunks = gridDim.x;
+  const SegView sv = seg_view(p, 0);
+  const SelState st0 = *sv.st;  // (of the launch before this one)
+  const bool bad = *p.err != 0u || st0.level != 1u;
+  const uint32_t off = sv.chunk_off[c], coff = ss.cand_off[c];
+  // this thread's eight elements
+  const int64_t n = p.n, j0 = (int64_t)c * kTile + (int64_t)tid * PER;
+  uint32_t raw[PER];
+  if (j0 + PER <= n) {
+    const uint4 a = reinterpret_cast<const uint4*>(sv.x + j0)[0], b = reinterpret_cast<const uint4*>(sv.x + j0)[1];
+    raw[0] = a.x, raw[1] = a.y, raw[2] = a.z, raw[3] = a.w;
+    raw[4] = b.x, raw[5] = b.y, raw[6] = b.z, raw[7] = b.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) raw[e] = j0 + e < n ? __float_as_uint(sv.x[j0 + e]) : 0u;
+  }
+  {
+    uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.hist);
+    const size_t words4 = (size_t)ss.workers * kSmallReps * kHistBins / 4;
+    for (size_t i = (size_t)c * T + tid; i < words4; i += (size_t)nchunks * T) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  uint32_t isA = 0u, isB = 0u, low_max = 0u, inv_max = 0u;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const uint32_t kk = raw[e] & kKeyMask;
+    const bool ok = !bad && j0 + e < n;
+    const bool a = ok && kk > st0.hi, b = ok && kk >= st0.lo && kk <= st0.hi;
+    isA |= a ? 1u << e : 0u;
+    isB |= b ? 1u << e : 0u;
+    const uint32_t low = kk & 0x7ffffu;
+    if (b) {
+      low_max = low > low_max ? low : low_max;
+      inv_max = (low ^ 0x7ffffu) > inv_max ? (low ^ 0x7ffffu) : inv_max;
+    }
+  }
+  const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
+  uint32_t befA = 0u, befB = 0u, totA = 0u, totB = 0u;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const uint64_t pa = __ballot((cA >> b) & 1u), pb = __ballot((cB >> b) & 1u);
+    befA += popc_lt(pa) << b;
+    befB += popc_lt(pb) << b;
+    totA += (uint32_t)__popcll(pa) << b;
+    totB += (uint32_t)__popcll(pb) << b;
+  }
+  if (lane == 0) wtot[wave] = ((uint64_t)totA << 32) | totB;
+  __syncthreads();
+  uint64_t sum = 0ull, all = 0ull;
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) {
+    const uint64_t wt = wtot[i];
+    sum += i < wave ? wt : 0ull;
+    all += wt;
+  }
+  befA += (uint32_t)(sum >> 32);
+  befB += (uint32_t)sum;
+  uint32_t pos = off + befA + befB, cpos = coff + befB;
+  if ((isA | isB) != 0u) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const bool b = (isB >> e) & 1u;
+      if (((isA >> e) & 1u) || b) {
+        if (pos < sv.d.cap) sv.list[pos] = make_uint2((uint32_t)(j0 + e), raw[e]);
+        ++pos;
+      }
+      if (b) {
+        store_through(&ss.cand[cpos], (raw[e] & 0x7ffffu) | ((uint32_t)c << 19));
+        ++cpos;
+      }
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint32_t a = __shfl_xor(low_max, o, 64), b = __shfl_xor(inv_max, o, 64);
+    low_max = a > low_max ? a : low_max;
+    inv_max = b > inv_max ? b : inv_max;
+  }
+  if (lane == 0) store_through(&ss.low_bits[c * WAVES + wave], ((uint64_t)inv_max << 32) | low_max);
+  if (tid == 0) store_through(&ss.sure[c], (uint32_t)(all >> 32));
+  reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (!last_block(&ss.ctr[1], (uint32_t)nchunks)) return;
+
+  // everything that is needed comes in one go: each load is a trip to memory
+  const uint32_t ncand = st0.cand;
+  constexpr int KEEP = 4;  // candidates a thread keeps in registers
+  uint32_t word[KEEP];
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    const uint32_t q = (uint32_t)(i * T + tid);
+    word[i] = 0u;
+    if ((uint32_t)(i * T) < ncand) word[i] = ss.cand[q < ncand ? q : ncand - 1u];
+  }
+  const uint32_t my_sure = tid < nchunks ? ss.sure[tid] : 0u;
+  const uint32_t my_coff = tid < nchunks ? ss.cand_off[tid] : 0u;
+  uint32_t l0 = 0u, l1 = 0u;
+  for (int i = tid; i < nchunks * WAVES; i += T) {
+    const uint64_t lb = ss.low_bits[i];
+    l0 = (uint32_t)lb > l0 ? (uint32_t)lb : l0;
+    l1 = (uint32_t)(lb >> 32) > l1 ? (uint32_t)(lb >> 32) : l1;
+  }
+  if (tid == 0) st = st0;
+  if (tid < 128) digit2[tid] = 0u;
+  if (tid < kSmallMaxChunks) cnt[0][tid] = cnt[1][tid] = 0u;
+  if (tid < 2) low_sh[tid] = 0u;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint32_t o0 = __shfl_xor(l0, o, 64), o1 = __shfl_xor(l1, o, 64);
+    l0 = o0 > l0 ? o0 : l0;
+    l1 = o1 > l1 ? o1 : l1;
+  }
+  __syncthreads();
+  if (lane == 0 && (l0 | l1) != 0u) {
+    atomicMax(&low_sh[0], l0);
+    atomicMax(&low_sh[1], l1);
+  }
+  // for every candidate, in some thread: use(word)
+  auto each = [&](auto use) {
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+      if ((uint32_t)(i * T + tid) < ncand) use(word[i]);
+    for (uint32_t q = (uint32_t)(KEEP * T + tid); q < ncand; q += 4 * T) {  // four loads in flight
+      uint32_t w4[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w4[i] = ss.cand[q + (uint32_t)(i * T) < ncand ? q + (uint32_t)(i * T) : q];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (q + (uint32_t)(i * T) < ncand) use(w4[i]);
+    }
+  };
+  __syncthreads();
+  const bool equal = low_sh[0] == (low_sh[1] ^ 0x7ffffu);
+  if (bad) {
+    if (tid == 0) atomicOr(p.err, kErrSequence);
+    if (tid < 2) ss.ctr[tid] = 0u;
+    return;
+  }
+  if (equal) {  // all candidates are equal: no further digit needed, and each chunk's are known
+    if (tid == 0) {
+      st.lo |= low_sh[0];
+      st.hi = st.lo;
+      st.level = 3u;
+    }
+    if (tid < nchunks) atomicAdd(&cnt[1][tid], (tid + 1 < nchunks ? ss.cand_off[tid + 1] : ncand) - my_coff);
+    __syncthreads();
+  } else {
+    each([&](uint32_t w) { atomicAdd(&hist[(w >> 7) & 0xfffu], 1u); });
+    __syncthreads();
+    block_pick<T>(st, hist, 1, part, p.err);
+    const uint32_t d1 = (st.lo >> 7) & 0xfffu;
+    each([&](uint32_t w) {
+      if (((w >> 7) & 0xfffu) == d1) atomicAdd(&digit2[w & 0x7fu], 1u);
+    });
+    __syncthreads();
+    block_pick<T>(st, digit2, 2, part, p.err);
+    const uint32_t low_t = st.lo & 0x7ffffu;
+    each([&](uint32_t w) {
+      const uint32_t low = w & 0x7ffffu;
+      if (low >= low_t) atomicAdd(&cnt[low > low_t ? 0 : 1][w >> 19], 1u);
+    });
+    __syncthreads();
+  }
+  if (tid < 2) ss.ctr[tid] = 0u;
+  if (st.level != 3u) {
+    if (tid == 0) atomicOr(p.err, kErrSequence);
+    return;
+  }
+  if (tid < nchunks) cnt[0][tid] += my_sure;
+  __syncthreads();
+  if (tid < kSmallMaxChunks) {  // exclusive prefix over the chunks: four waves, each adds the waves before it
+    const uint32_t ca = cnt[0][tid], cb = cnt[1][tid];
+    uint32_t ea = wave_incl_scan(ca) - ca, eb = wave_incl_scan(cb) - cb;
+    for (int i = lane; i < (tid & ~63); i += 64) {
+      uint32_t xa = cnt[0][i], xb = cnt[1][i];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        xa += __shfl_xor(xa, o, 64);
+        xb += __shfl_xor(xb, o, 64);
+      }
+      ea += xa;
+      eb += xb;
+    }
+    ss.before[tid] = make_uint2(ea, eb);
+  }
+  if (tid == 0) *sv.st = st;
+}
+
+// The kept entries of one tile of kSmallTile elements, found again in the list entries of its chunk: calls
+// use(position among the k kept, element, raw bits) for each, in some thread; returns false (in every thread) if
+// the selection failed.  All 256 threads call it.
+template <typename Use>
+__device__ __forceinline__ bool small_kept(const SelParams& p, const SmallScratch& ss, int64_t lo, Use use) {
+  constexpr int T = 256;
+  __shared__ uint32_t wtot[T / 64];
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const SegView sv = seg_view(p, 0);
+  const int c = (int)(lo / kTile);
+  const uint32_t from = sv.chunk_off[c];
+  const uint32_t to = c + 1 < sv.d.geom.nchunks ? sv.chunk_off[c + 1] : sv.st->list_count;
+  const uint2 bef = ss.before[c];
+  const uint32_t klo = sv.st->lo, khi = sv.st->hi, quota = sv.st->need;
+  if (sv.st->level != 3u || *p.err || to > sv.d.cap) return false;
+  uint32_t a0 = bef.x, b0 = bef.y;
+  for (uint32_t q = from; q < to; q += T) {
+    const uint2 ent = sv.list[q + (uint32_t)tid < to ? q + (uint32_t)tid : to - 1u];
+    const uint32_t kk = ent.y & kKeyMask;
+    const bool ok = q + (uint32_t)tid < to;
+    const bool a = ok && kk > khi, b = ok && kk >= klo && kk <= khi;
+    const uint64_t ma = __ballot(a), mb = __ballot(b);
+    if ((tid & 63) == 0) wtot[wave] = ((uint32_t)__popcll(ma) << 16) | (uint32_t)__popcll(mb);
+    __syncthreads();
+    uint32_t ba = a0 + popc_lt(ma), bb = b0 + popc_lt(mb);
+#pragma unroll
+    for (int i = 0; i < T / 64; ++i) {
+      const uint32_t wt = wtot[i];
+      if (i < wave) {
+        ba += wt >> 16;
+        bb += wt & 0xffffu;
+      }
+      a0 += wt >> 16;
+      b0 += wt & 0xffffu;
+    }
+    const int64_t j = (int64_t)ent.x;
+    if ((a || (b && bb < quota)) && j >= lo && j < lo + kSmallTile && j < p.n) {
+      const uint32_t m = ba + (bb < quota ? bb : quota);
+      if (m < sv.d.k) use(m, j, ent.y);
+    }
+    __syncthreads();  // (wtot is free)
+  }
+  return true;
+}
+
+// The rest of a step whose leader was known up front: the outputs of the selection, for every other worker
+// acc = g + residual with the kept positions' values taken and +0.0 left there, the ordered sums, and the dense
+// update (if wanted), a tile of kSmallTile elements a block.  vals: rows to keep the values in, or nullptr.
+template <int GT>
+__global__ void __launch_bounds__(256)
+k_small_rest(SelParams p, SmallScratch ss, PtrTable g, PtrTable res, int w_count, int leader, int64_t k,
+             float* __restrict__ vals, float* __restrict__ sum_out, float* __restrict__ update) {
+  __shared__ __attribute__((aligned(16))) int32_t slot[kSmallTile];   // place among the k kept, or -1
+  __shared__ __attribute__((aligned(16))) float lead[kSmallTile];     // the leader's value there
+  const int tid = threadIdx.x;
+  const int64_t n = p.n, lo = (int64_t)blockIdx.x * kSmallTile;
+  const int64_t j = lo + 4 * tid;  // this thread's group
+  // the first four workers' loads are under way while the tile's kept entries are found
+  const bool whole = j + 4 <= n;
+  v4f a[4], b[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int w = i < w_count ? i : w_count - 1;
+    if (whole) {
+      a[i] = load4g<false, GT>(g.p[w], j);
+      b[i] = load4<false>(res.p[w] + j);
+    }
+  }
+  reinterpret_cast<int4*>(slot)[tid] = make_int4(-1, -1, -1, -1);
+  __syncthreads();
+  float* __restrict__ lead_res = res.p[leader];
+  int32_t* __restrict__ idx_out = p.idx_out;
+  const bool fine = small_kept(p, ss, lo, [&](uint32_t m, int64_t e, uint32_t raw) {
+    slot[e - lo] = (int32_t)m;
+    lead[e - lo] = __uint_as_float(raw);
+    idx_out[m] = (int32_t)e;
+    lead_res[e] = 0.0f;
+  });
+  if (!fine) return;
+  __syncthreads();
+  if (whole) {
+    const int4 s4 = reinterpret_cast<const int4*>(slot)[tid];
+    const int at[4] = {s4.x, s4.y, s4.z, s4.w};
+    const bool any = (s4.x & s4.y & s4.z & s4.w) >= 0;  // the sign bit of -1 in all four: none
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int w0 = 0; w0 < w_count; w0 += 4) {  // four workers' loads in flight, then the ordered adds
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int w = w0 + i;
+        if (w >= w_count) break;
+        float v[4] = {a[i].x + b[i].x, a[i].y + b[i].y, a[i].z + b[i].z, a[i].w + b[i].w};
+        if (any) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (at[e] >= 0) {
+              if (w == leader) v[e] = lead[4 * tid + e];
+              if (vals) vals[(size_t)w * (size_t)k + (size_t)at[e]] = v[e];
+              s[e] = w == 0 ? v[e] : s[e] + v[e];
+              v[e] = 0.0f;
+            }
+          }
+        }
+        if (w != leader) store4<false>(res.p[w] + j, v4f{v[0], v[1], v[2], v[3]});
+      }
+      if (w0 + 4 < w_count) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int w = w0 + 4 + i < w_count ? w0 + 4 + i : w_count - 1;
+          a[i] = load4g<false, GT>(g.p[w], j);
+          b[i] = load4<false>(res.p[w] + j);
+        }
+      }
+    }
+    if (any) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (at[e] >= 0) sum_out[at[e]] = s[e];
+    }
+    if (update) store4<false>(update + j, v4f{s[0], s[1], s[2], s[3]});
+  } else {
+    for (int64_t i = j; i < n; ++i) {  // the vector's last elements
+      const int at = slot[i - lo];
+      float s = 0.0f;
+      for (int w = 0; w < w_count; ++w) {
+        float v = w == leader ? 0.0f : load1g<GT>(g.p[w], i) + res.p[w][i];
+        if (at >= 0) {
+          if (w == leader) v = lead[i - lo];
+          if (vals) vals[(size_t)w * (size_t)k + (size_t)at] = v;
+          s = w == 0 ? v : s + v;
+          v = 0.0f;
+        }
+        if (w != leader) res.p[w][i] = v;
+      }
+      if (at >= 0) sum_out[at] = s;
+      if (update) update[i] = s;
+    }
+  }
+}
+
+// The rest of a step whose pass has run on every worker: the outputs of the selection, vals, ordered sums and +0.0
+// at the kept positions, and the dense update (if wanted), a tile of kSmallTile elements a block.
+__global__ void __launch_bounds__(256)
+k_small_gather(SelParams p, SmallScratch ss, PtrTable tab, int w_count, int64_t k, float* __restrict__ vals,
+               float* __restrict__ sum_out, float* __restrict__ update) {
+  __shared__ __attribute__((aligned(16))) float buf[kSmallTile];
+  const int tid = threadIdx.x;
+  const int64_t n = p.n, lo = (int64_t)blockIdx.x * kSmallTile;
+  reinterpret_cast<float4*>(buf)[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+  __syncthreads();
+  int32_t* __restrict__ idx_out = p.idx_out;
+  const bool fine = small_kept(p, ss, lo, [&](uint32_t m, int64_t e, uint32_t) {
+    idx_out[m] = (int32_t)e;
+    float s = 0.0f;
+    for (int w0 = 0; w0 < w_count; w0 += 8) {  // eight independent loads in flight, then the ordered adds
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (w0 + q < w_count) v[q] = tab.p[w0 + q][e];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (w0 + q < w_count) {
+          if (vals) vals[(size_t)(w0 + q) * (size_t)k + (size_t)m] = v[q];
+          s = (w0 + q == 0) ? v[q] : (s + v[q]);
+          tab.p[w0 + q][e] = 0.0f;
+        }
+      }
+    }
+    sum_out[m] = s;
+    buf[e - lo] = s;
+  });
+  if (!fine || update == nullptr) return;
+  __syncthreads();
+  const int64_t j = lo + 4 * tid;
+  if (j + 4 <= n) {
+    const float4 t4 = reinterpret_cast<const float4*>(buf)[tid];
+    store4<false>(update + j, v4f{t4.x, t4.y, t4.z, t4.w});
+  } else {
+    for (int64_t i = j; i < n; ++i) update[i] = buf[i - lo];
   }
 }
 

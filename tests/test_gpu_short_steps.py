@@ -1,0 +1,95 @@
+"""Steps on short vectors, which run in three launches: against the oracle and against the general launch sequence."""
+
+import numpy as np
+import pytest
+
+from oracle import artopk_oracle as orc
+from tests import gpu_util
+from tests.gpu_util import GpuRunner, assert_step_matches
+
+pytestmark = pytest.mark.gpu
+
+
+def _vector(rng, n, kind, r):
+    x = (rng.standard_normal(n) * 0.01 * (1.0 + 0.3 * r)).astype(np.float32)
+    if kind == "ties":
+        x = np.round(x * 128).astype(np.float32) / 128
+    elif kind == "equal":  # every magnitude the same
+        x = np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32) * np.float32(0.25 * (1 + r))
+    elif kind == "zeros":
+        x[:] = 0.0
+        x[r::max(1, n // 7)] = 1.0 + r
+    elif kind == "one_bin":  # one top digit, many second and third digits: the last block walks a list of n entries
+        x = (1.0 + rng.random(n) * 0.01).astype(np.float32)
+        x[0] += 0.001 * r
+    elif kind == "special":
+        x[rng.integers(0, n, 5)] = np.inf
+        x[rng.integers(0, n, n // 5 + 1)] = np.float32(-1e-45)
+    return x
+
+
+# one element, less than a group, the edges of the last launch's tile and of a chunk, the longest vector of the route
+@pytest.mark.parametrize("n", [1, 3, 1023, 1024, 1025, 8191, 8193, 65537, 300_002, 1 << 20])
+@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "zeros", "one_bin", "special"])
+def test_short_steps_match_the_oracle(n, kind):
+    rng = np.random.default_rng(n)
+    w = 1 + n % 6
+    kmax = min(n, 16384)
+    runner = GpuRunner(w, n, kmax)
+    for mode in (orc.MODE_STAR, orc.MODE_FIXED, orc.MODE_VAR, orc.MODE_VAR_G):
+        if kind == "special" and mode in (orc.MODE_VAR, orc.MODE_VAR_G):
+            continue  # variances of infinities
+        if kind in ("equal", "zeros", "ties") and mode == orc.MODE_VAR_G and w > 1 and n < 64:
+            continue  # equal variances up to rounding
+        for step_no, k in enumerate(sorted({1, (n + 99) // 100, min(kmax, (n + 9) // 10), kmax}), 1):
+            g = [_vector(rng, n, kind, r) for r in range(w)]
+            res = [_vector(rng, n, "normal", r) if step_no % 2 and kind == "normal" else np.zeros(n, np.float32)
+                   for r in range(w)]
+            want = orc.step(g, res, k, mode, step_no=step_no, fixed_leader=w - 1)
+            if mode in (orc.MODE_VAR, orc.MODE_VAR_G) and w > 1 and gpu_util.top_two_gap(want.variances) <= 1e-4:
+                continue
+            runner.load_g(g)
+            runner.load_res(res)
+            got = runner.step(k, mode, step_no, fixed_leader=w - 1, want_vals=step_no % 2 == 1)
+            assert_step_matches(got, want, mode)
+
+
+# the same step on both launch sequences, in turn on one context (the short one must leave its scratch as it found it)
+@pytest.mark.parametrize("n,w,k", [(70_001, 9, 700), (1 << 20, 3, 16384), ((1 << 20) - 3, 17, 1)])
+@pytest.mark.parametrize("g", ["f32", "bf16", "f16"])
+def test_short_steps_and_general_steps_alternate(n, w, k, g):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[g]
+    gs = [(torch.randn(n, generator=gen, device="cuda") * (1.0 + 0.1 * r)).to(dt) for r in range(w)]
+    r0 = [torch.randn(n, generator=gen, device="cuda") for _ in range(w)]
+    ctx = lib.Context(w, n, k)
+
+    def run(short, mode, step):
+        ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, (1 << 20) if short else 0)
+        res = [r.clone() for r in r0]
+        idx = torch.zeros(k, dtype=torch.int32, device="cuda")
+        sm, up = torch.zeros(k, device="cuda"), torch.zeros(n, device="cuda")
+        vals, lead = torch.zeros(w * k, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        var = torch.zeros(w, dtype=torch.float64, device="cuda")
+        more = {"vals_out": vals, "leader_out": lead, "var_out": var}
+        if g == "f32":
+            ctx.artopk_step(gs, res, k, mode, step, idx, sm, up, **more)
+        else:
+            ctx.artopk_step_g16(gs, lib.ARTOPK_G_BF16 if g == "bf16" else lib.ARTOPK_G_F16, res, k, mode, step, idx, sm,
+                                up, **more)
+        ctx.status()
+        if mode not in (lib.ARTOPK_VAR, lib.ARTOPK_VAR_G):
+            var.zero_()
+        return [idx, sm.view(torch.int32), up.view(torch.int32), vals.view(torch.int32), lead] + \
+            [r.view(torch.int32) for r in res], var
+
+    for step, mode in enumerate((lib.ARTOPK_STAR, lib.ARTOPK_VAR, lib.ARTOPK_STAR, lib.ARTOPK_VAR_G), 1):
+        ctx.set_step_counter(step)
+        a, va = run(True, mode, step)
+        b, vb = run(False, mode, step)
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
+        torch.testing.assert_close(va, vb, rtol=1e-12, atol=0.0)  # float64 sums of n terms in another order
