@@ -765,6 +765,17 @@ void launch_mark_spans(artopk_ctx* c, const GuessPlan& gp, int nv, const PtrTabl
     hipLaunchKernelGGL(k_mark_spans<false>, grid, dim3(256), 0, c->stream, x, n, chunk_elems, c->s.h_all, tb);
 }
 
+// The leader's pass of a segmented step: one block per chunk of the layout, which also builds the histograms
+// that enqueue_select would otherwise read the vector for.
+template <int GT>
+void launch_pass_seg(artopk_ctx* c, const Plan& pl, const PtrTable& r, int64_t n, const float* g, float* res) {
+  const SelParams p = make_params(c, pl, r, n, nullptr, nullptr, 0, false);
+  if (c->pass_a_nt)
+    hipLaunchKernelGGL((k_pass_seg<true, GT, 1024>), dim3((unsigned)pl.total_chunks), dim3(1024), 0, c->stream, p, g, res);
+  else
+    hipLaunchKernelGGL((k_pass_seg<false, GT, 1024>), dim3((unsigned)pl.total_chunks), dim3(1024), 0, c->stream, p, g, res);
+}
+
 // Samples the first nvec vectors of (g + residual) into slots 0 .. nvec-1 (cleared beforehand).
 void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const PtrTable& res, int nvec,
                    bool read_only = false) {
@@ -802,7 +813,8 @@ void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const 
 int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n, int32_t* idx_out,
                    bool hist_ready, int slot_by_leader, float* vals_row = nullptr,
                    const LeaderArgs* leader_args = nullptr, bool guessed = false, float* zero_vec = nullptr,
-                   int32_t tile_cap = 0, int32_t first_slot = 0, const GuessPlan* spans = nullptr) {
+                   int32_t tile_cap = 0, int32_t first_slot = 0, const GuessPlan* spans = nullptr,
+                   bool seg_hist_ready = false) {
   hipStream_t st = c->stream;
   const unsigned nseg = (unsigned)pl.nseg;
   SelParams p = make_params(c, pl, tab, n, idx_out, vals_row, (hist_ready || pl.batch) ? slot_by_leader : 0,
@@ -835,7 +847,7 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
     pa.after_mask = 1;
     hipLaunchKernelGGL(k_pick0, dim3(1, nseg), dim3(1024), 0, st, pa, LeaderArgs{});
   } else {
-    if (!hist_ready) hipLaunchKernelGGL(k_hist0<1024>, chunk_grid, dim3(1024), 0, st, p);
+    if (!hist_ready && !seg_hist_ready) hipLaunchKernelGGL(k_hist0<1024>, chunk_grid, dim3(1024), 0, st, p);
     hipLaunchKernelGGL(k_pick0, dim3(1, nseg), dim3(1024), 0, st, p, la);
   }
 
@@ -1814,16 +1826,22 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
     if (gp.on) {
       enqueue_guess(ctx, gp, g1t, r1t, 1);
       launch_pass_mark(ctx, 0, 1, g1t, r1t, n, geom.chunk_elems, gp.tile_cap);
-    } else if (seg_stride) {
-      launch_pass_plain(ctx, 0, 1, g1t, r1t, n);
-    } else {  // (segments build their histograms on the leader's vector afterwards)
-      launch_pass_a(ctx, 0, segmented ? 0 : 1, dim3(geom.nchunks, 1), g1t, r1t, n, geom, segmented ? -1 : 0);
+    } else if (segmented) {
+      if (g_type == ARTOPK_G_BF16)
+        launch_pass_seg<kGBF16>(ctx, *pl, rt, n, g[L], residual[L]);
+      else if (g_type == ARTOPK_G_F16)
+        launch_pass_seg<kGF16>(ctx, *pl, rt, n, g[L], residual[L]);
+      else
+        launch_pass_seg<kGF32>(ctx, *pl, rt, n, g[L], residual[L]);
+      HIP_TRY(ctx, hipGetLastError());
+    } else {
+      launch_pass_a(ctx, 0, 1, dim3(geom.nchunks, 1), g1t, r1t, n, geom, 0);
     }
     prof_mark(ctx, 1);
     // The leader's residual is zeroed inside the selection: its kernels have the kept values in
     // registers (level-1 compaction) or write the kept indices anyway (final list pass).
     if ((rc = enqueue_select(ctx, *pl, rt, n, idx_out, !segmented, 0, vals + (size_t)L * (size_t)k, nullptr, gp.on,
-                             residual[L], gp.tile_cap)))
+                             residual[L], gp.tile_cap, 0, nullptr, segmented)))
       return rc;
     prof_mark(ctx, 2);
     const int rest = (int)w - 1;

@@ -154,3 +154,39 @@ def test_batches_of_whole_vectors(w, n, k):
     ctx.status()
     for r in range(w):
         assert np.array_equal(idx[r].cpu().numpy(), orc.topk_indices(xs[r], k)), r
+
+
+# a segmented step whose leader is known up front forms the leader's error-fed vector and its histograms in one
+# pass over the segments' chunks: every element exactly once, wherever a segment begins
+@pytest.mark.parametrize("start", [0, 1, 2, 3, 8191])
+@pytest.mark.parametrize("g", ["f32", "bf16"])
+def test_segmented_leader_pass(start, g):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    rng = np.random.default_rng(start)
+    sizes = ([start] if start else []) + [1, 2, 3, 4, 5, 6, 7, 8190, 8193, 32771, 1, 270_003, 3]
+    off = [int(o) for o in np.concatenate([[0], np.cumsum(sizes)])]
+    n, w = off[-1], 3
+    ks = [max(1, s // 50) for s in sizes]
+    k = sum(ks)
+    gs, res = [_values(rng, n, "normal") for _ in range(w)], [_values(rng, n, "ties") for _ in range(w)]
+    gd = [torch.from_numpy(x).cuda() for x in gs]
+    if g == "bf16":
+        gd = [x.to(torch.bfloat16) for x in gd]
+        gs = [x.float().cpu().numpy() for x in gd]
+    rd = [torch.from_numpy(x).cuda() for x in res]
+    ctx = lib.Context(w, n, k, max_segments=len(sizes))
+    idx = torch.zeros(k, dtype=torch.int32, device="cuda")
+    sm, up = torch.zeros(k, device="cuda"), torch.full((n,), float("nan"), device="cuda")
+    if g == "f32":
+        ctx.artopk_step(gd, rd, k, lib.ARTOPK_STAR, 2, idx, sm, up, seg_off=off, seg_k=ks)
+    else:
+        ctx.artopk_step_g16(gd, lib.ARTOPK_G_BF16, rd, k, lib.ARTOPK_STAR, 2, idx, sm, up, seg_off=off, seg_k=ks)
+    ctx.status()
+    want = orc.step(gs, res, k, orc.MODE_STAR, step_no=2, seg_off=off, seg_k=ks)
+    assert np.array_equal(idx.cpu().numpy(), want.idx)
+    assert np.array_equal(sm.cpu().numpy().view(np.uint32), want.sum.view(np.uint32))
+    assert np.array_equal(up.cpu().numpy().view(np.uint32), want.update.view(np.uint32))
+    for r in range(w):
+        assert np.array_equal(rd[r].cpu().numpy().view(np.uint32), want.residual[r].view(np.uint32))
