@@ -1012,9 +1012,17 @@ int enqueue_topk_rows(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t n, 
   const bool marks = guessed || gp.on;
   for (int32_t r0 = 0; r0 < w; r0 += per) {
     const int32_t nv = w - r0 < per ? w - r0 : per;
-    // the fused pass counted per chunk of its own layout; otherwise about two thousand chunks over all vectors
+    // The fused pass counted per chunk of its own layout; the two passes of the histogram route do best with about
+    // two thousand chunks over all vectors.  Behind the read-only marking one block copies a chunk's pieces, two
+    // blocks fit a compute unit, and each is mostly latency: one round of 512 blocks up to 2e8 elements, two beyond
+    // (us, one in a hundred kept, 512 / 1024 / 2048 chunks: 1 x 25.6 M 78/85/85, 1 x 138 M 180/183/183, 8 x 25.6 M
+    // 271/266/274, 1 x 400 M 492/477/477; 256 chunks: 76, 183, 271, 492).
     int64_t max_chunks = kMaxChunks;
-    if (!hist_ready && nv > 1) max_chunks = 2 * kMaxChunks / nv > 128 ? 2 * kMaxChunks / nv : 128;
+    if (gp.on)
+      max_chunks = (n * nv <= ((int64_t)3 << 26) ? kMaxChunks / 2 : kMaxChunks) / nv;
+    else if (!hist_ready && nv > 1)
+      max_chunks = 2 * kMaxChunks / nv;
+    if (max_chunks < 64) max_chunks = 64;
     if (max_chunks > kMaxChunks) max_chunks = kMaxChunks;
     Plan pl = flat_plan(c, n, k, -1, marks, !hist_ready && !gp.on, max_chunks);
     pl.nseg = nv;
