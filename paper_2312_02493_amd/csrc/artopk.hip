@@ -1167,6 +1167,7 @@ struct Layout {
   int64_t list_entries = 0, max_tiles = 0, mask_stride = 0, tilebuf_entries = 0;
   int32_t blocks = 0;  // scratch blocks: one per segment, or per vector of a batch
   size_t o_hall = 0, o_mask = 0, o_zero = 0, o_S = 0, o_coff = 0, o_part = 0, o_var = 0, o_leader = 0, o_err = 0, o_counter = 0, o_list = 0, o_vals = 0, o_rows = 0, o_table = 0, o_cmap = 0, o_tstart = 0, o_tbuf = 0, o_tcnt = 0, o_sample = 0, o_small = 0;
+  size_t small_many = 0;   // words of SmallScratch::ctr and ::many
   size_t small_words = 0;  // words of the short vectors' scratch that have to be zero between steps
   size_t total = 0;
 };
@@ -1229,9 +1230,11 @@ Layout scratch_layout(int32_t max_w, int64_t max_n, int64_t max_k, int32_t max_s
   L.o_tbuf = take((size_t)L.tilebuf_entries * sizeof(uint2));
   L.o_tcnt = take((size_t)(max_tiles_pass + 1) * sizeof(uint32_t));
   L.o_sample = take((size_t)16384 * kGuessRun * sizeof(uint32_t));
-  L.small_words = (size_t)max_w * kSmallReps * kHistBins + 16;
+  L.small_words = (size_t)max_w * kSmallReps * kHistBins + kSmallCtr + kManyMid;
   const int64_t small_n = max_n < kSmallMaxNLimit ? max_n : kSmallMaxNLimit;
-  L.o_small = take((L.small_words + (2 * 16 + 2 + 2) * kSmallMaxChunks + (size_t)small_n) * sizeof(uint32_t));
+  L.small_many = kSmallCtr + kManyTail + (size_t)((small_n + kTile - 1) / kTile) * (kTile / kSmallTile) * 128;
+  L.o_small = take(((size_t)max_w * kSmallReps * kHistBins + L.small_many + (2 * 16 + 2 + 2) * kSmallMaxChunks +
+                    (size_t)small_n) * sizeof(uint32_t));
   L.total = off;
   return L;
 }
@@ -1304,7 +1307,8 @@ int artopk_create(artopk_ctx** out, int32_t max_w, int64_t max_n, int64_t max_k,
   uint32_t* small = reinterpret_cast<uint32_t*>(base + L.o_small);
   s.small.hist = small;
   s.small.ctr = small + (size_t)max_w * kSmallReps * kHistBins;
-  s.small.low_bits = reinterpret_cast<uint64_t*>(small + L.small_words);
+  s.small.many = s.small.ctr + kSmallCtr;
+  s.small.low_bits = reinterpret_cast<uint64_t*>(s.small.ctr + L.small_many);
   s.small.before = reinterpret_cast<uint2*>(s.small.low_bits + 16 * kSmallMaxChunks);
   s.small.cand_off = reinterpret_cast<uint32_t*>(s.small.before + kSmallMaxChunks);
   s.small.sure = s.small.cand_off + kSmallMaxChunks;

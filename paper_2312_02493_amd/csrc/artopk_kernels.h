@@ -114,7 +114,8 @@ struct SelState {
   uint32_t use_mask;       // the list is written from the survivor bit mask of the fused pass
   uint32_t need_full;      // the guessed bound did not work out: the top-digit histogram of every key is needed
   uint32_t list_lo;        // with use_mask: the list holds every key >= list_lo (<= lo)
-  uint32_t pad[5];
+  uint32_t many;           // a short vector's selection counted its candidates per tile and wrote no list
+  uint32_t pad[4];
 };
 
 // Bits of the sticky device-side error word.
@@ -3750,10 +3751,39 @@ k_sum_update(const float* __restrict__ vals, int w_count, int64_t n, const int32
 constexpr int kSmallReps = 8;     // copies of a worker's top-digit histogram
 constexpr int kSmallMaxChunks = 256;  // chunks of kTile elements
 constexpr int kSmallTile = 1024;  // elements per block of the last launch: 256 threads x one float4 group
+// More candidates than this are counted by all blocks of k_small_select together: a block alone takes about 0.55 us for
+// a thousand, all together 11 us more than it for none on 9 chunks and 23 more on 128.  Whole steps, us, one block
+// against all: 65537 elements x 2 workers, 8000 candidates 42/42, 12000 46/43, 24000 60/44; 262144, 12000 44/46, 16000
+// 48/46, 24000 54/47; 1 M, 24000 61/68, 32000 66/68, 48000 74/69.  Variance rule, 8 workers: 65537, 12000 53/52; 262144,
+// 16000 59/60, 24000 66/60; 1 M, 32000 109/112, 48000 114/112.
+__device__ __forceinline__ uint32_t small_few(int nchunks) { return 10240u + 240u * (uint32_t)nchunks; }
+constexpr int kSmallHelpSpins = 256;  // looks at the phase word before a waiting block gives up: 100 us or so
+constexpr int kSmallLine = 32;  // words
+// SmallScratch::ctr: blocks done with the first and with the second launch; with many candidates, chunks whose last
+// digits are counted and what is published, 4 times the step's number and kPhaseCount or kPhaseOver; steps of that
+// kind so far (the latter two are not reset).
+constexpr int kCtrPass = 0, kCtrSelect = kSmallLine, kCtrDone = 2 * kSmallLine, kCtrPhase = 3 * kSmallLine,
+              kCtrStep = 4 * kSmallLine, kSmallCtr = 5 * kSmallLine;
+constexpr uint32_t kPhaseNone = 0u, kPhaseCount = 1u, kPhaseOver = 2u;
+
+// SmallScratch::many, words (one pointer: each more of them cost every step's k_small_select a register pair too many):
+constexpr int kSmallMaxTiles = kSmallMaxChunks * (kTile / kSmallTile);
+constexpr int kManyDig1 = 0,                                            // [kSmallReps][kHistBins] second digits of the candidates
+              kManyDig2 = kManyDig1 + kSmallReps * kHistBins,           // [kSmallReps][128] last digits of those that are left then
+              kManyClaim = kManyDig2 + kSmallReps * 128,                // [kSmallMaxChunks] the last step in which somebody took
+                                                                        // the chunk's last digits on
+              kManyMid = kManyClaim + kSmallMaxChunks,                  // the state after the second digit
+              kManyTileCnt = kManyMid + 64,                             // [tiles] uint2: keys above the candidates, candidates
+              kManyTileBefore = kManyTileCnt + 2 * kSmallMaxTiles,      // [tiles] uint2: keys above the threshold, and at it,
+                                                                        // in front of every tile
+              kManyTail = kManyTileBefore + 2 * kSmallMaxTiles;         // [tiles][128] the candidates that are left, by last
+                                                                        // digit: that or a later one
+static_assert(sizeof(SelState) <= 64 * 4 && kManyTileCnt % 4 == 0, "the state fits, rows are aligned");
 
 struct SmallScratch {
   uint32_t* hist;        // [workers][kSmallReps][kHistBins]
-  uint32_t* ctr;         // blocks done with the first and the second launch
+  uint32_t* ctr;         // counters, each in a cache line of its own: kCtrPass ..
+  uint32_t* many;        // kMany.. below (up to kManyMid zero at first)
   // (these are written before they are read in every step)
   uint32_t* cand_off;    // [kSmallMaxChunks] SelParams::cand_off
   uint32_t* sure;        // [kSmallMaxChunks] keys above the threshold digit in every chunk
@@ -3845,7 +3875,275 @@ k_small_pass(PtrTable g, PtrTable res, int64_t n, SmallScratch ss, double* __res
   if (STATS) block_moments<T, true>(va, partials, w, nblk, c);
   flush_suffix_hist<T, true>(lh, red_u, p.S + ((size_t)w * kMaxChunks + (size_t)c) * kHistBins,
                        ss.hist + ((size_t)w * kSmallReps + (size_t)(c % kSmallReps)) * kHistBins);
-  if (last_block(&ss.ctr[0], gridDim.x * gridDim.y)) pick0_body(p, la, 0, red_u);
+  if (last_block(&ss.ctr[kCtrPass], gridDim.x * gridDim.y)) pick0_body(p, la, 0, red_u);
+}
+
+// Eight consecutive elements of x from j0 on (0 behind the vector's end).
+__device__ __forceinline__ void small_load8(const float* __restrict__ x, int64_t n, int64_t j0, uint32_t (&raw)[8]) {
+  if (j0 + 8 <= n) {
+    const uint4 a = reinterpret_cast<const uint4*>(x + j0)[0], b = reinterpret_cast<const uint4*>(x + j0)[1];
+    raw[0] = a.x, raw[1] = a.y, raw[2] = a.z, raw[3] = a.w;
+    raw[4] = b.x, raw[5] = b.y, raw[6] = b.z, raw[7] = b.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) raw[e] = j0 + e < n ? __float_as_uint(x[j0 + e]) : 0u;
+  }
+}
+
+// Clears the histograms that k_small_pass filled, the calling block its share of them.
+__device__ __forceinline__ void small_clear(const SmallScratch& ss) {
+  uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.hist);
+  const size_t words4 = (size_t)ss.workers * kSmallReps * kHistBins / 4;
+  for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < words4; i += (size_t)gridDim.x * 1024)
+    z[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// k_small_select's work where many values share the threshold's top digit (magnitudes within 6 % of each other): the
+// candidates are then most of the vector, and one block walking them took up to 1.2 ms.  With more than small_few of
+// them every block counts its own by their second digit; the last block to finish with that picks
+// the digit and publishes it, and the chunks are then counted by the last digit.  A block that is not the last looks
+// out for the published digit for a while, takes its own chunk on and leaves; the one that published it goes on with
+// the chunks that nobody has taken on, so nothing depends on how many others still run, and whoever finishes the last
+// chunk picks the threshold and clears what this used (a chunk that has been taken on bears the step's number, so a
+// block that comes late touches nothing).  No list is written then: everything is counted per tile of the next
+// launch, which reads the vector again.
+//   Steps that keep one in a hundred, us, ten launches / one block / all blocks: 1 M x 2 between 1 and 1.01 85/371/73,
+// of two values 98/1280/79; 262144 x 2 75/134/51 and 81/364/58; 65537 x 2 74/77/46 and 74/136/53.  Variance rule, 1 M x
+// 8 118/424/120 and 127/1337/128: there the ten launches are level.
+// raw: the thread's eight elements of the block's own chunk; hist: kHistBins words, part: 1024 words, wtot: a word pair per wave, all on chip.
+__device__ __forceinline__ void small_select_many(const SelParams& p, const SmallScratch& ss, const SegView& sv,
+                                                  const SelState& st0, uint32_t (&raw)[8],
+                                                  uint32_t* __restrict__ hist, uint32_t* __restrict__ part,
+                                                  uint64_t* __restrict__ wtot) {
+  constexpr int T = 1024, WAVES = T / 64, PER = 8, TILES = kTile / kSmallTile;
+  static_assert(TILES * 128 == T, "a thread for every tile of a chunk and last digit");
+  __shared__ SelState st;
+  __shared__ __attribute__((aligned(16))) uint32_t digit2[128];
+  __shared__ uint32_t low_sh[2];
+  __shared__ uint32_t turn_sh;
+  uint32_t* const dig1 = ss.many + kManyDig1;
+  uint32_t* const dig2 = ss.many + kManyDig2;
+  uint32_t* const claim = ss.many + kManyClaim;
+  SelState* const mid = reinterpret_cast<SelState*>(ss.many + kManyMid);
+  uint2* const tile_cnt = reinterpret_cast<uint2*>(ss.many + kManyTileCnt);
+  uint2* const tile_before = reinterpret_cast<uint2*>(ss.many + kManyTileBefore);
+  uint32_t* const tail = ss.many + kManyTail;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = blockIdx.x, nchunks = gridDim.x;
+  const int64_t n = p.n, j0 = (int64_t)c * kTile + (int64_t)tid * PER;
+  reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  uint32_t cA = 0u, cB = 0u, low_max = 0u, inv_max = 0u;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const uint32_t kk = raw[e] & kKeyMask, low = kk & 0x7ffffu;
+    const bool ok = j0 + e < n;
+    cA += ok && kk > st0.hi ? 1u : 0u;
+    if (ok && kk >= st0.lo && kk <= st0.hi) {
+      ++cB;
+      low_max = low > low_max ? low : low_max;
+      inv_max = (low ^ 0x7ffffu) > inv_max ? (low ^ 0x7ffffu) : inv_max;
+      atomicAdd(&hist[low >> 7], 1u);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint32_t a = __shfl_xor(low_max, o, 64), b = __shfl_xor(inv_max, o, 64);
+    low_max = a > low_max ? a : low_max;
+    inv_max = b > inv_max ? b : inv_max;
+    cA += __shfl_xor(cA, o, 64);
+    cB += __shfl_xor(cB, o, 64);
+  }
+  if (lane == 0) {
+    wtot[wave] = ((uint64_t)cB << 32) | cA;
+    store_through(&ss.low_bits[c * WAVES + wave], ((uint64_t)inv_max << 32) | low_max);
+  }
+  __syncthreads();
+  if (tid < TILES)  // (a tile is the elements of two waves)
+    store_through(reinterpret_cast<uint64_t*>(tile_cnt) + c * TILES + tid, wtot[2 * tid] + wtot[2 * tid + 1]);
+  uint32_t* __restrict__ d1 = dig1 + (size_t)(c % kSmallReps) * kHistBins;
+#pragma unroll
+  for (int i = 0; i < kHistBins / T; ++i) {
+    const uint32_t v = hist[i * T + tid];
+    if (v) atomicAdd(&d1[i * T + tid], v);
+  }
+
+  // tile_before from every tile's counts, and the final state; all threads call it
+  const int ntiles = nchunks * TILES;  // up to two a thread; those behind the vector count nothing
+  auto finish = [&](auto count) {
+    uint2 c0 = make_uint2(0u, 0u), c1 = make_uint2(0u, 0u);
+    if (2 * tid < ntiles) {
+      c0 = count(2 * tid);
+      c1 = count(2 * tid + 1);
+    }
+    const uint32_t ea = block_prefix_incl<T>(c0.x + c1.x, part) - (c0.x + c1.x);
+    const uint32_t eb = block_prefix_incl<T>(c0.y + c1.y, part) - (c0.y + c1.y);
+    if (2 * tid < ntiles) {
+      tile_before[2 * tid] = make_uint2(ea, eb);
+      tile_before[2 * tid + 1] = make_uint2(ea + c0.x, eb + c0.y);
+    }
+    if (tid == 0) *sv.st = st;
+  };
+
+  const uint32_t step = ss.ctr[kCtrStep] + 1u;
+  // (all that this step's blocks add to these, and read of them, they have before anybody calls this)
+  auto clear = [&]() {
+    uint4* __restrict__ z = reinterpret_cast<uint4*>(dig1);
+    for (int i = tid; i < kSmallReps * kHistBins / 4; i += T) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < kSmallReps * 128) dig2[tid] = 0u;
+    if (tid < 3) ss.ctr[tid * kSmallLine] = 0u;  // (kCtrPass, kCtrSelect, kCtrDone)
+    if (tid == 0) ss.ctr[kCtrStep] = step;
+  };
+  uint32_t phase = kPhaseNone;  // (thread 0's)
+  const bool last = last_block(&ss.ctr[kCtrSelect], (uint32_t)nchunks);
+  if (last) {
+    uint4 q[kSmallReps];
+#pragma unroll
+    for (int r = 0; r < kSmallReps; ++r) q[r] = reinterpret_cast<const uint4*>(dig1 + (size_t)r * kHistBins)[tid];
+    uint32_t l0 = 0u, l1 = 0u;
+    for (int i = tid; i < nchunks * WAVES; i += T) {
+      const uint64_t lb = ss.low_bits[i];
+      l0 = (uint32_t)lb > l0 ? (uint32_t)lb : l0;
+      l1 = (uint32_t)(lb >> 32) > l1 ? (uint32_t)(lb >> 32) : l1;
+    }
+    if (tid == 0) {
+      st = st0;
+      st.many = 1u;
+    }
+    if (tid < 2) low_sh[tid] = 0u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const uint32_t o0 = __shfl_xor(l0, o, 64), o1 = __shfl_xor(l1, o, 64);
+      l0 = o0 > l0 ? o0 : l0;
+      l1 = o1 > l1 ? o1 : l1;
+    }
+    __syncthreads();
+    if (lane == 0) {
+      atomicMax(&low_sh[0], l0);
+      atomicMax(&low_sh[1], l1);
+    }
+    __syncthreads();
+    if (low_sh[0] == (low_sh[1] ^ 0x7ffffu)) {  // all candidates are equal: no further digit needed
+      if (tid == 0) {
+        st.lo |= low_sh[0];
+        st.hi = st.lo;
+        st.level = 3u;
+      }
+      finish([&](int t) { return tile_cnt[t]; });
+      phase = kPhaseOver;
+    } else {  // the second digit from the blocks' counts, then everybody's help with the last
+      uint32_t h[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int r = 0; r < kSmallReps; ++r) h[0] += q[r].x, h[1] += q[r].y, h[2] += q[r].z, h[3] += q[r].w;
+      block_pick_bins<T>(st, h, 1, part, p.err);
+      phase = st.level == 2u ? kPhaseCount : kPhaseOver;
+      if (tid == 0) {
+        const uint32_t* from = reinterpret_cast<const uint32_t*>(&st);
+        for (int i = 0; i < (int)(sizeof(SelState) / 4); ++i) store_through(reinterpret_cast<uint32_t*>(mid) + i, from[i]);
+        if (phase == kPhaseOver) atomicOr(p.err, kErrSequence);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (before the word that says that it is there)
+      }
+    }
+    if (tid == 0) store_through(&ss.ctr[kCtrPhase], 4u * step + phase);
+    if (phase == kPhaseOver) {
+      __syncthreads();  // (every thread has read what clear() clears)
+      clear();
+    }
+  }
+
+  if (tid == 0) {  // (the wait is bounded: without help the block that published the digit does all of it)
+    for (int i = 0; phase == kPhaseNone && i < kSmallHelpSpins; ++i) {
+      const uint32_t word = __hip_atomic_load(&ss.ctr[kCtrPhase], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((word >> 2) == (step & 0x3fffffffu))
+        phase = word & 3u;
+      else
+        __builtin_amdgcn_s_sleep(4);
+    }
+    turn_sh = phase;
+  }
+  __syncthreads();
+  if (turn_sh != kPhaseCount) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const uint32_t lo = mid->lo, hi = mid->hi;
+  int ch = c;
+  while (true) {
+    __syncthreads();  // (turn_sh, low_sh, hist, digit2 and part are free)
+    if (tid == 0)
+      turn_sh = __hip_atomic_exchange(&claim[ch], step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != step ? 1u : 0u;
+    hist[tid] = 0u;  // [TILES][128]
+    if (tid < 128) digit2[tid] = 0u;
+    if (tid == 0) low_sh[0] = (uint32_t)nchunks;
+    if (ch != c) small_load8(sv.x, n, (int64_t)ch * kTile + (int64_t)tid * PER, raw);
+    __syncthreads();
+    if (turn_sh != 0u) {
+      const int64_t e0 = (int64_t)ch * kTile + (int64_t)tid * PER;
+      const int tile = wave / (WAVES / TILES);
+      uint32_t above = 0u;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const uint32_t kk = raw[e] & kKeyMask;
+        const bool ok = e0 + e < n;
+        above += ok && kk > hi ? 1u : 0u;
+        if (ok && kk >= lo && kk <= hi) atomicAdd(&hist[tile * 128 + (int)(kk & 0x7fu)], 1u);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, 64);
+      if (lane == 0) part[wave] = above;
+      __syncthreads();
+      {  // thread = (tile, last digit): two waves a tile
+        const uint32_t v = hist[tid];
+        if (v) atomicAdd(&digit2[tid & 127], v);
+        uint32_t from_here = v;  // this digit or a later one of the wave's
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t x = __shfl_down(from_here, o, 64);
+          if (lane + o < 64) from_here += x;
+        }
+        uint32_t upper = (tid & 64) == 0 ? hist[tid + 64] : 0u;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) upper += __shfl_xor(upper, o, 64);
+        store_through(&tail[(size_t)ch * T + tid], from_here + upper);
+        if ((tid & 127) == 0)
+          store_through(&tile_cnt[ch * TILES + (tid >> 7)].x, part[2 * (tid >> 7)] + part[2 * (tid >> 7) + 1]);
+      }
+      __syncthreads();
+      if (tid < 128) {
+        const uint32_t v = digit2[tid];
+        if (v) atomicAdd(&dig2[(ch % kSmallReps) * 128 + tid], v);
+      }
+      if (last_block(&ss.ctr[kCtrDone], (uint32_t)nchunks)) {  // that was the last chunk: the threshold
+        if (tid == 0) st = *mid;
+        if (tid < 128) {
+          uint32_t v = 0u;
+#pragma unroll
+          for (int r = 0; r < kSmallReps; ++r) v += dig2[r * 128 + tid];
+          digit2[tid] = v;
+        }
+        __syncthreads();
+        block_pick<T>(st, digit2, 2, part, p.err);
+        if (st.level == 3u) {
+          const uint32_t d2 = st.lo & 0x7fu;
+          finish([&](int t) {
+            const uint32_t ge = tail[(size_t)t * 128 + d2];
+            const uint32_t gt = d2 < 127u ? tail[(size_t)t * 128 + d2 + 1] : 0u;
+            return make_uint2(tile_cnt[t].x + gt, ge - gt);
+          });
+        } else if (tid == 0) {
+          atomicOr(p.err, kErrSequence);
+        }
+        clear();
+        return;
+      }
+    }
+    if (!last) return;
+    // a chunk that nobody has taken on yet
+    if (tid < nchunks && __hip_atomic_load(&claim[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != step)
+      atomicMin(&low_sh[0], (uint32_t)tid);
+    __syncthreads();
+    ch = (int)low_sh[0];
+    if (ch >= nchunks) return;  // (the others' blocks finish theirs)
+  }
 }
 
 // The selection behind k_small_pass: every block writes its chunk's part of the leader's survivor list, its
@@ -3876,18 +4174,11 @@ k_small_select(SelParams p, SmallScratch ss) {
   // this thread's eight elements
   const int64_t n = p.n, j0 = (int64_t)c * kTile + (int64_t)tid * PER;
   uint32_t raw[PER];
-  if (j0 + PER <= n) {
-    const uint4 a = reinterpret_cast<const uint4*>(sv.x + j0)[0], b = reinterpret_cast<const uint4*>(sv.x + j0)[1];
-    raw[0] = a.x, raw[1] = a.y, raw[2] = a.z, raw[3] = a.w;
-    raw[4] = b.x, raw[5] = b.y, raw[6] = b.z, raw[7] = b.w;
-  } else {
-#pragma unroll
-    for (int e = 0; e < PER; ++e) raw[e] = j0 + e < n ? __float_as_uint(sv.x[j0 + e]) : 0u;
-  }
-  {
-    uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.hist);
-    const size_t words4 = (size_t)ss.workers * kSmallReps * kHistBins / 4;
-    for (size_t i = (size_t)c * T + tid; i < words4; i += (size_t)nchunks * T) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  small_load8(sv.x, n, j0, raw);
+  small_clear(ss);
+  if (!bad && st0.cand > small_few(nchunks)) {  // the same in every block
+    small_select_many(p, ss, sv, st0, raw, hist, part, wtot);
+    return;
   }
   uint32_t isA = 0u, isB = 0u, low_max = 0u, inv_max = 0u;
 #pragma unroll
@@ -3948,7 +4239,7 @@ k_small_select(SelParams p, SmallScratch ss) {
   if (lane == 0) store_through(&ss.low_bits[c * WAVES + wave], ((uint64_t)inv_max << 32) | low_max);
   if (tid == 0) store_through(&ss.sure[c], (uint32_t)(all >> 32));
   reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
-  if (!last_block(&ss.ctr[1], (uint32_t)nchunks)) return;
+  if (!last_block(&ss.ctr[kCtrSelect], (uint32_t)nchunks)) return;
 
   // everything that is needed comes in one go: each load is a trip to memory
   const uint32_t ncand = st0.cand;
@@ -4001,7 +4292,7 @@ k_small_select(SelParams p, SmallScratch ss) {
   const bool equal = low_sh[0] == (low_sh[1] ^ 0x7ffffu);
   if (bad) {
     if (tid == 0) atomicOr(p.err, kErrSequence);
-    if (tid < 2) ss.ctr[tid] = 0u;
+    if (tid < 2) ss.ctr[tid * kSmallLine] = 0u;  // (kCtrPass, kCtrSelect)
     return;
   }
   if (equal) {  // all candidates are equal: no further digit needed, and each chunk's are known
@@ -4029,7 +4320,7 @@ k_small_select(SelParams p, SmallScratch ss) {
     });
     __syncthreads();
   }
-  if (tid < 2) ss.ctr[tid] = 0u;
+  if (tid < 2) ss.ctr[tid * kSmallLine] = 0u;  // (kCtrPass, kCtrSelect)
   if (st.level != 3u) {
     if (tid == 0) atomicOr(p.err, kErrSequence);
     return;
@@ -4054,22 +4345,70 @@ k_small_select(SelParams p, SmallScratch ss) {
   if (tid == 0) *sv.st = st;
 }
 
-// The kept entries of one tile of kSmallTile elements, found again in the list entries of its chunk: calls
-// use(position among the k kept, element, raw bits) for each, in some thread; returns false (in every thread) if
-// the selection failed.  All 256 threads call it.
+// The kept entries of one tile of kSmallTile elements, found again in the list entries of its chunk (or, with many
+// candidates, in the vector itself): calls use(position among the k kept, element, raw bits) for each, in some thread;
+// returns false (in every thread) if the selection failed.  All 256 threads call it.
 template <typename Use>
 __device__ __forceinline__ bool small_kept(const SelParams& p, const SmallScratch& ss, int64_t lo, Use use) {
   constexpr int T = 256;
   __shared__ uint32_t wtot[T / 64];
   const int tid = threadIdx.x, wave = tid >> 6;
   const SegView sv = seg_view(p, 0);
+  // (every load that does not depend on another is under way before the first branch)
   const int c = (int)(lo / kTile);
   const uint32_t from = sv.chunk_off[c];
   const uint32_t to = c + 1 < sv.d.geom.nchunks ? sv.chunk_off[c + 1] : sv.st->list_count;
-  const uint2 bef = ss.before[c];
-  const uint32_t klo = sv.st->lo, khi = sv.st->hi, quota = sv.st->need;
-  if (sv.st->level != 3u || *p.err || to > sv.d.cap) return false;
-  uint32_t a0 = bef.x, b0 = bef.y;
+  const uint2 bef_chunk = ss.before[c];
+  const uint32_t klo = sv.st->lo, khi = sv.st->hi, quota = sv.st->need, many = sv.st->many;
+  if (sv.st->level != 3u || *p.err) return false;
+  if (__builtin_expect(many != 0u, 0)) {
+    const uint2 bef = reinterpret_cast<const uint2*>(ss.many + kManyTileBefore)[lo / kSmallTile];
+    const int64_t j = lo + 4 * tid;
+    uint32_t raw[4] = {0u, 0u, 0u, 0u};
+    if (j + 4 <= p.n) {
+      const uint4 v = *reinterpret_cast<const uint4*>(sv.x + j);
+      raw[0] = v.x, raw[1] = v.y, raw[2] = v.z, raw[3] = v.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) raw[e] = j + e < p.n ? __float_as_uint(sv.x[j + e]) : 0u;
+    }
+    uint32_t isA = 0u, isB = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t kk = raw[e] & kKeyMask;
+      isA |= j + e < p.n && kk > khi ? 1u << e : 0u;
+      isB |= j + e < p.n && kk >= klo && kk <= khi ? 1u << e : 0u;
+    }
+    const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
+    uint32_t ba = bef.x, bb = bef.y, totA = 0u, totB = 0u;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const uint64_t pa = __ballot((cA >> b) & 1u), pb = __ballot((cB >> b) & 1u);
+      ba += popc_lt(pa) << b;
+      bb += popc_lt(pb) << b;
+      totA += (uint32_t)__popcll(pa) << b;
+      totB += (uint32_t)__popcll(pb) << b;
+    }
+    if ((tid & 63) == 0) wtot[wave] = (totA << 16) | totB;
+    __syncthreads();
+    for (int i = 0; i < wave; ++i) {
+      ba += wtot[i] >> 16;
+      bb += wtot[i] & 0xffffu;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool a = (isA >> e) & 1u, b = (isB >> e) & 1u;
+      if (a || (b && bb < quota)) {
+        const uint32_t m = ba + (bb < quota ? bb : quota);
+        if (m < sv.d.k) use(m, j + e, raw[e]);
+      }
+      ba += a ? 1u : 0u;
+      bb += b ? 1u : 0u;
+    }
+    return true;
+  }
+  if (to > sv.d.cap) return false;
+  uint32_t a0 = bef_chunk.x, b0 = bef_chunk.y;
   for (uint32_t q = from; q < to; q += T) {
     const uint2 ent = sv.list[q + (uint32_t)tid < to ? q + (uint32_t)tid : to - 1u];
     const uint32_t kk = ent.y & kKeyMask;

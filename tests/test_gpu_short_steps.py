@@ -93,3 +93,77 @@ def test_short_steps_and_general_steps_alternate(n, w, k, g):
         for x, y in zip(a, b):
             assert torch.equal(x, y)
         torch.testing.assert_close(va, vb, rtol=1e-12, atol=0.0)  # float64 sums of n terms in another order
+
+
+def _narrow(rng, n, kind, r):
+    """Vectors whose threshold's top digit many values share (up to `few` of them are left to one block of the selection)."""
+    few = 10240 + 240 * ((n + 8191) // 8192)
+    x = (rng.standard_normal(n) * 0.01).astype(np.float32)
+    if kind == "band":  # all of them, most second and last digits
+        return (1.0 + rng.random(n) * 0.06).astype(np.float32)
+    if kind == "two":  # two values: the last digit is the same for half the vector
+        return np.where(rng.random(n) < 0.5, np.float32(1.0), np.float32(-1.03)).astype(np.float32)
+    if kind == "near":  # neighbouring numbers: one second digit, every last digit
+        return (np.uint32(0x3f800000) + rng.integers(0, 128, n).astype(np.uint32)).view(np.float32)
+    if kind == "equal":
+        return np.full(n, np.float32(0.75))
+    m = min(n, few + {"few": 0, "few1": 1}[kind])  # exactly as many as one block takes, and one more
+    x[rng.permutation(n)[:m]] = (1.0 + rng.random(m) * 0.01).astype(np.float32)
+    return x
+
+
+# a step on narrow values before and after an ordinary one on the same context: the selection's blocks share the
+# counting and have to leave the scratch as they found it; 2^21 is the option's largest value
+@pytest.mark.parametrize("n", [16385, 65537, 300_002, (1 << 20) - 3, (1 << 20) + 1, 1 << 21])
+@pytest.mark.parametrize("kind", ["band", "two", "near", "equal", "few", "few1"])
+def test_short_steps_on_narrow_values(n, kind):
+    import paper_2312_02493_amd as lib
+
+    rng = np.random.default_rng(n)
+    w, kmax = 8 if n > 1 << 20 else 2, 16384
+    runner = GpuRunner(w, n, kmax)
+    runner.ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, 1 << 21)
+    step_no = 0
+    for k, mode in ((kmax, orc.MODE_STAR), (min(kmax, n // 100), orc.MODE_VAR), (1, orc.MODE_STAR)):
+        for now in (kind, "ordinary", kind):
+            step_no += 1
+            g = [np.zeros(n, np.float32) for _ in range(w)]
+            if now == "ordinary":
+                res = [_vector(rng, n, "normal", r) for r in range(w)]
+            else:
+                res = [_narrow(rng, n, kind, r) * np.float32(2.0 ** (r % 2)) for r in range(w)]
+            want = orc.step(g, res, k, mode, step_no=step_no)
+            if mode == orc.MODE_VAR and gpu_util.top_two_gap(want.variances) <= 1e-4:
+                continue
+            runner.load_g(g)
+            runner.load_res(res)
+            assert_step_matches(runner.step(k, mode, step_no, want_vals=False), want, mode)
+
+
+# narrow values may not make a short step slower than the general launch sequence is on them (one block alone took
+# four to thirteen times as long; half as long again leaves room for the clock)
+@pytest.mark.parametrize("kind", ["band", "two", "near"])
+def test_short_steps_on_narrow_values_take_no_longer(kind):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    n, w, k = 1 << 20, 2, 10486
+    rng = np.random.default_rng(5)
+    src = [torch.from_numpy(_narrow(rng, n, kind, r)).cuda() for r in range(w)]
+    g = [torch.zeros(n, device="cuda") for _ in range(w)]
+    idx = torch.zeros(k, dtype=torch.int32, device="cuda")
+    sm, up = torch.zeros(k, device="cuda"), torch.zeros(n, device="cuda")
+    best = {}
+    for limit in (0, 1 << 20) * 3:
+        ctx = lib.Context(w, n, k)
+        ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, limit)
+        res = [x.clone() for x in src]
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        for step in range(1, 18):  # (each pass keeps one value in a hundred: the vectors stay narrow)
+            if step == 3:
+                t0.record()
+            ctx.artopk_step(g, res, k, lib.ARTOPK_STAR, step, idx, sm, up)
+        t1.record()
+        ctx.status()
+        best[limit] = min(best.get(limit, 1e9), t0.elapsed_time(t1))
+    assert best[1 << 20] < 1.5 * best[0], best
