@@ -92,6 +92,7 @@ struct Plan {
   int64_t max_tiles = 1;    // largest look-back tile count of a segment
   int64_t total_tiles = 1;
   int64_t max_cap = 1;      // largest list capacity of a segment
+  int64_t k_all = 0;        // entries kept of all segments together
   size_t hist_words = 0;    // words of h_all's memory used for copies of histograms
   bool batch = false;       // nseg whole vectors with one descriptor (SelParams::batch)
   int64_t list_stride = 0;  // list entries per vector of a batch
@@ -367,6 +368,7 @@ Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool
   d.cap = c->s.cap < (uint64_t)n ? c->s.cap : (uint32_t)n;
   d.vec = vec;
   d.hreps = own_hist && d.geom.nchunks > kManyChunks ? kHistReps : 1;
+  pl.k_all = k;
   pl.hist_words = d.hreps > 1 ? (size_t)d.hreps * kHistBins : 0;
   pl.desc.push_back(d);
   pl.max_chunks = d.geom.nchunks;
@@ -420,6 +422,7 @@ int segmented_plan(artopk_ctx* c, int64_t n, int32_t nseg, const int64_t* seg_of
       pl.desc.push_back(d);
     }
     pl.total_tiles = flag_base;
+    pl.k_all = koff;
     if (list_base > c->s.list_entries || flag_base > c->s.max_tiles || chunk_begin > kMaxChunks + c->max_seg)
       return fail(c, ARTOPK_EINVAL, "segment layout exceeds the scratch sized at artopk_create");
     HIP_TRY(c, hipMemcpyAsync(c->s.table_dev, pl.desc.data(), sizeof(SegDesc) * nseg, hipMemcpyHostToDevice,
@@ -470,6 +473,8 @@ SelParams make_params(const artopk_ctx* c, const Plan& pl, const PtrTable& tab, 
   p.zero_vec = nullptr;
   p.err = s.err_dev;
   p.batch = pl.batch ? 1 : 0;
+  const int64_t k_all = pl.batch ? pl.k_all * pl.nseg : pl.k_all;
+  p.k_all = k_all < UINT32_MAX ? (uint32_t)k_all : UINT32_MAX;
   p.list_stride = pl.list_stride;
   p.flag_stride = pl.batch ? pl.max_tiles : 0;
   p.table = pl.use_table ? s.table_dev : nullptr;
@@ -892,25 +897,15 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
     const int64_t b2 = lblocks > cblocks ? lblocks : cblocks;
     hipLaunchKernelGGL(k_level2, dim3((unsigned)b2, nseg), dim3(kCompactThreads), 0, st, p);
   }
-  int64_t k_all = 0;
-  for (const SegDesc& d : pl.desc) k_all += pl.batch ? (int64_t)d.k * pl.nseg : d.k;
-  const bool many = k_all > ((int64_t)1 << 19);
-  const int64_t ltile = kCompactThreads * (many ? 16 : 8);
-  int64_t ltiles = (pl.max_cap + ltile - 1) / ltile;
+  int64_t ltiles = (pl.max_cap + kListTile - 1) / kListTile;
   int fblocks = (int)(ltiles < per_seg ? ltiles : per_seg);
   if (fblocks < 1) fblocks = 1;
   // (the same launch is the level-3 array pass where no list could be written)
   if (!always_fits && fblocks < cblocks) fblocks = cblocks;
-  // entries a lane takes of the list: 8 up to half a million kept, 16 beyond (measured on both sides, see
-  // list_final_body: 255 k entries 11 against 13 us, 1.4 million 26 against 19)
-  if (always_fits && !many)
-    hipLaunchKernelGGL((k_final<true, 8>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
-  else if (always_fits)
-    hipLaunchKernelGGL((k_final<true, 16>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
-  else if (!many)
-    hipLaunchKernelGGL((k_final<false, 8>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
+  if (always_fits)
+    hipLaunchKernelGGL(k_final<true>, dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
   else
-    hipLaunchKernelGGL((k_final<false, 16>), dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
+    hipLaunchKernelGGL(k_final<false>, dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
   HIP_TRY(c, hipGetLastError());
   return ARTOPK_OK;
 }

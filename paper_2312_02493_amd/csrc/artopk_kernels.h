@@ -185,6 +185,7 @@ struct SelParams {
   // Several whole vectors at once: segment s is vector s of the table with `one` for a descriptor, its own
   // list, look-back flags, chunk offsets and output row.
   int32_t batch;
+  uint32_t k_all;          // entries kept of all segments or vectors together
   int64_t list_stride;     // list entries per vector
   int64_t flag_stride;     // look-back tiles per vector
   const SegDesc* table;
@@ -2840,11 +2841,21 @@ __device__ __forceinline__ void compact_body(const SelParams& p, const SegView& 
 constexpr int kListTile = kCompactThreads * 8;  // the smallest tile: 4096 entries
 static_assert(kCompactTile == 4 * kListTile, "four flag words of the list pass per array tile");
 
+// Entries a lane takes of a list: 16 if the list, or all the lists of the launch together (of which at least the kept
+// entries are known), are long.  8 against 16, us: one list of 255 k 10.6/13.8, 512 k 13.8/14.4, 770 k 15.4/15.5, 800 k
+// all equal 13.6/14.6, 1 M 17.8/16.5, 1.5 M all equal 24/16, 3 M all equal 36/27, 14 M 105/90; 8 lists of 25 k 12.2/14,
+// of 40 k 12.7/14.8, of 255 k 29/26; 9 of 154 k 25/20; 54 of 255 k together 15.2/14.4.  (32 entries: 3 M all equal 24,
+// lists that are mostly kept 15 to 25 % slower.)
+constexpr uint32_t kLongList = 3u << 18;
+__device__ __forceinline__ bool long_list(uint32_t entries, uint32_t k_all) {
+  return entries > kLongList || k_all > kLongList;
+}
+
+// stage: kCompactThreads * PER entries on chip.
 template <int PER>
 __device__ __forceinline__ void list_final_body(const SelParams& p, const SegView& sv, const SelState& st,
-                                                uint32_t zero_below, int64_t tile) {
+                                                uint32_t zero_below, int64_t tile, uint2* __restrict__ stage) {
   constexpr int T = kCompactThreads, WAVES = T / 64, TILE = T * PER;
-  __shared__ uint2 stage[TILE];
   __shared__ uint64_t wave_tot[WAVES];
   __shared__ uint64_t tile_excl;
   __shared__ int64_t tile_sh;
@@ -2984,21 +2995,24 @@ k_compact(SelParams p) {
 // or by the level-2 pass) it is the final pass over the list; if not even the level-2
 // survivors fitted one (e.g. an all-equal vector) it is the level-3 pass over the array,
 // which then writes the outputs itself.  ALWAYS_LIST: the list takes the whole vector, so
-// the array passes do not exist.  PER: entries a lane takes of the list.
+// the array passes do not exist.
 // ---------------------------------------------------------------------------
-template <bool ALWAYS_LIST, int PER>
+template <bool ALWAYS_LIST>
 __global__ void __launch_bounds__(kCompactThreads)
 k_final(SelParams p) {
   __shared__ SelState st;
   __shared__ uint32_t pick_part[kCompactThreads];
   __shared__ int64_t first_tile;
+  __shared__ uint2 stage[kCompactThreads * 16];
   const SegView sv = seg_view(p, blockIdx.y);
   const SelState* __restrict__ stp = sv.st;
   const uint32_t zero_below = zeroed_above(stp);
   if (*p.err) return;
   const bool list_known = ALWAYS_LIST || stp->compact_level == 1u;
   // tiles are handed out by a counter, so blocks beyond the number of list tiles are not needed
-  if (list_known && (uint64_t)blockIdx.x * (kCompactThreads * PER) >= (uint64_t)stp->list_count) return;
+  if (list_known && (uint64_t)blockIdx.x * (kCompactThreads * (long_list(stp->list_count, p.k_all) ? 16 : 8)) >=
+                        (uint64_t)stp->list_count)
+    return;
   // (the first tile's number comes while the digits are replayed)
   if (list_known && threadIdx.x == 0) first_tile = (int64_t)atomicAdd(sv.counters + 2, 1u);
   derive_state<kCompactThreads>(sv, st, 3, pick_part, p.err);
@@ -3010,7 +3024,11 @@ k_final(SelParams p) {
     if (threadIdx.x == 0) first_tile = (int64_t)atomicAdd(sv.counters + 2, 1u);
     __syncthreads();
   }
-  list_final_body<PER>(p, sv, st, from_pieces(p, sv) ? (st.hi | 0x7fu) : zero_below, first_tile);
+  const uint32_t below = from_pieces(p, sv) ? (st.hi | 0x7fu) : zero_below;
+  if (long_list(st.list_count, p.k_all))
+    list_final_body<16>(p, sv, st, below, first_tile, stage);
+  else
+    list_final_body<8>(p, sv, st, below, first_tile, stage);
 }
 
 // ---------------------------------------------------------------------------

@@ -79,6 +79,25 @@ def test_final_list_pass_tiles_and_quota(k):
     assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x, k))
 
 
+# few kept of a list that holds the whole vector, as long as the final pass takes with short tiles, and longer
+@pytest.mark.parametrize("n", [3 << 18, (3 << 18) + 1, (3 << 18) + 8192 * 3 + 5, 3_000_001])
+@pytest.mark.parametrize("kind", ["equal", "ends"])
+def test_final_list_pass_on_lists_much_longer_than_k(n, kind):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    x = np.full(n, np.float32(0.5))
+    if kind == "ends":  # the largest ones in the last tile, the ties in the first
+        x[n - 3:] = np.float32(0.5625) - np.float32(2.0 ** -24)
+    xd = torch.from_numpy(x).cuda()
+    ctx = lib.Context(1, n, n // 100)
+    for k in (1, 4097, n // 100):
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        ctx.artopk_select_topk(xd, k, idx)
+        ctx.status()
+        assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x, k)), (n, k)
+
+
 @pytest.mark.parametrize("w,n", [(1, 134_217_728), (1, 134_217_732), (3, 44_739_245), (2, 1023)])
 def test_gain_and_variance_on_both_sides_of_the_cache_limit(w, n):
     """float64 sums in another order: relative difference below n rounding errors of 2^-53, 1e-9 at these sizes."""
