@@ -880,7 +880,10 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
     hipLaunchKernelGGL((k_compact1<kC1Waves, kC1R>), dim3(pl.max_chunks, nseg), dim3(64 * kC1Waves), 0, st, p);
   } else if (guessed && hist_ready) {
     const int64_t b1 = lblocks > pl.max_chunks ? lblocks : pl.max_chunks;
-    hipLaunchKernelGGL(k_level1, dim3((unsigned)b1, nseg), dim3(64 * kC1Waves), 0, st, p);
+    if (spans)  // (half as many chunks as behind a fused pass)
+      hipLaunchKernelGGL(k_level1<8>, dim3((unsigned)b1, nseg), dim3(512), 0, st, p);
+    else
+      hipLaunchKernelGGL(k_level1<kC1Waves>, dim3((unsigned)b1, nseg), dim3(64 * kC1Waves), 0, st, p);
   } else {
     // (8 waves a block: 21.6 against 27.6 us with 4 on 11.7 M elements, 35 against 38 us on 25.6 M in 54 segments)
     hipLaunchKernelGGL((k_compact1<8, kC1R>), chunk_grid, dim3(512), 0, st, p);

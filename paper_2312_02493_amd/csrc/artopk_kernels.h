@@ -1833,20 +1833,26 @@ k_pick_mask(SelParams p, LeaderArgs la) {
 // takes them one per lane, values from the tile's on-chip copy: 141 and 34.5 us.
 // Shapes (138 M select, whole call): 8 waves x 16 elements 303 us, 8 x 8 325, 4 x 16
 // 333, 16 x 16 310, 16 x 8 328.
+//   Tiles in which more than a quarter survives, and survivors that are only counted, go from
+// the registers as before (60 M equal values 229 us, staged 295; one in ten of 11.7 M sorted
+// ones 30 against 40; an eighth or a half for a quarter: the same), so that the stage needs
+// places for a quarter of a tile: 54 instead of 66 KB a block of 8 waves, 35 instead of 58 in
+// k_level1 with 4, whose two jobs share one histogram.
 // ---------------------------------------------------------------------------
 constexpr int kC1Waves = 4, kC1R = 4;  // (flat vectors on the histogram route take 8 waves)
 
+// lh: kHistBins words on chip.
 template <int WAVES, int R>
-__device__ __forceinline__ void compact1_body(const SelParams& p) {
+__device__ __forceinline__ void compact1_body(const SelParams& p, uint32_t* __restrict__ lh) {
   constexpr int T = 64 * WAVES;
   constexpr int E = 4 * R;             // consecutive elements one lane owns in a tile (a power of two)
   constexpr int WSPAN = 64 * E;        // consecutive elements one wave owns in a tile
   constexpr int TILE = WAVES * WSPAN;  // elements per block iteration
+  constexpr int FEW = WSPAN / 4;       // survivors of a wave's tile that are taken one per lane
   static_assert(E <= 32, "one 32-bit mask per lane");
-  __shared__ uint32_t lh[kHistBins];
   __shared__ uint32_t wtot[2][WAVES];
   __shared__ __attribute__((aligned(16))) uint32_t tile_raw[WAVES][WSPAN];  // a wave's tile, group r of lane l at 256 r + 4 l
-  __shared__ uint16_t tile_pos[WAVES][WSPAN];                               // its survivors' places in the wave's tile
+  __shared__ uint16_t tile_pos[WAVES][FEW];                                 // its survivors' places in the wave's tile
 
   int seg, c;
   block_chunk(p, seg, c);
@@ -1956,7 +1962,21 @@ __device__ __forceinline__ void compact1_body(const SelParams& p) {
       }
       buf ^= 1;
     }
-    if (wsum != 0u) {
+    if (wsum > (uint32_t)FEW || !write_out) {  // many, or only to be counted: from the registers
+      uint32_t pos = base + before;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        if ((own >> e) & 1u) {
+          const uint32_t kk = raw[e] & kKeyMask;
+          if (kk <= khi)
+            atomicAdd(&lh[(kk >> 7) & 0xfffu], 1u);
+          else if (zero_out)
+            p.zero_vec[j0 + e] = 0.0f;
+          if (write_out && pos < cap) list[pos] = make_uint2((uint32_t)(j0 + e), raw[e]);
+          ++pos;
+        }
+      }
+    } else if (wsum != 0u) {
       uint32_t* __restrict__ traw = tile_raw[wave];
       uint16_t* __restrict__ tpos = tile_pos[wave];
 #pragma unroll
@@ -1979,7 +1999,7 @@ __device__ __forceinline__ void compact1_body(const SelParams& p) {
         const uint32_t kk = w & kKeyMask;
         const uint32_t j = (uint32_t)(tb + (int64_t)wave * WSPAN) + q;
         // (index, raw bits): the sign travels with the survivor
-        if (write_out && base + i < cap) list[base + i] = make_uint2(j, w);
+        if (base + i < cap) list[base + i] = make_uint2(j, w);
         if (kk <= khi)
           atomicAdd(&lh[(kk >> 7) & 0xfffu], 1u);  // candidate: feeds the next digit
         else if (zero_out)
@@ -3039,9 +3059,8 @@ k_final(SelParams p) {
 // the prologue.
 // ---------------------------------------------------------------------------
 template <int T>
-__device__ __forceinline__ void list_hist_body(const SelParams& p, int digit) {
+__device__ __forceinline__ void list_hist_body(const SelParams& p, int digit, uint32_t* __restrict__ lh) {
   constexpr int PER = 8192 / T;  // entries per thread and round
-  __shared__ uint32_t lh[kHistBins];
   __shared__ SelState st;
   __shared__ uint32_t pick_part[T];
   const SegView sv = seg_view(p, blockIdx.y);
@@ -3114,26 +3133,32 @@ __device__ __forceinline__ void list_hist_body(const SelParams& p, int digit) {
 
 __global__ void __launch_bounds__(256)
 k_list_hist(SelParams p, int digit) {
-  list_hist_body<256>(p, digit);
+  __shared__ uint32_t lh[kHistBins];
+  list_hist_body<256>(p, digit, lh);
 }
 
 template <int WAVES, int R>
 __global__ void __launch_bounds__(64 * WAVES)
 k_compact1(SelParams p) {
-  compact1_body<WAVES, R>(p);
+  __shared__ uint32_t lh[kHistBins];
+  compact1_body<WAVES, R>(p, lh);
 }
 
 // ---------------------------------------------------------------------------
 // k_level1 : the kernel behind the first pick on the guess route.  If the list was
 // written from the mask it counts the second digit over the list's candidates; if the
-// guess did not hold it is the level-1 compaction of the histogram route.
+// guess did not hold it is the level-1 compaction of the histogram route.  8 waves behind the
+// marking of vectors that are only read, whose chunks are twice as long: 400 M values of one
+// top digit 308 us with 8, 312 with 4, 25.6 M 31 against 44.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(64 * kC1Waves)
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES)
 k_level1(SelParams p) {
+  __shared__ uint32_t lh[kHistBins];
   if (seg_view(p, blockIdx.y).st->use_mask != 0u)
-    list_hist_body<64 * kC1Waves>(p, 1);
+    list_hist_body<64 * WAVES>(p, 1, lh);
   else
-    compact1_body<kC1Waves, kC1R>(p);
+    compact1_body<WAVES, kC1R>(p, lh);
 }
 
 // ---------------------------------------------------------------------------
@@ -3148,7 +3173,8 @@ k_level2(SelParams p) {
   const SegView sv = seg_view(p, blockIdx.y);
   if (*p.err) return;
   if (sv.st->compact_level == 1u) {
-    list_hist_body<kCompactThreads>(p, 2);
+    __shared__ uint32_t lh[kHistBins];
+    list_hist_body<kCompactThreads>(p, 2, lh);
   } else {
     __shared__ SelState st;
     __shared__ uint32_t pick_part[kCompactThreads];

@@ -79,6 +79,46 @@ def test_final_list_pass_tiles_and_quota(k):
     assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x, k))
 
 
+# survivors of a wave's tile (1024 elements) around the number that it takes one per lane; the selection alone and in
+# a step, which puts +0.0 at the leader's kept places on the way, with and without a guess that does not hold
+@pytest.mark.parametrize("guess", [1 << 31, 4096])
+def test_tiles_with_few_and_many_survivors(guess):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    counts = [0, 1, 255, 256, 257, 512, 1023, 1024, 256, 1024, 0, 0, 0, 0, 0, 3, 1024, 1024, 1024, 1024, 1024, 1024, 1024, 1024]
+    rng = np.random.default_rng(3)
+    n = 1024 * len(counts) * 4 + 517
+    xs = [(rng.standard_normal(n) * 1e-4).astype(np.float32) for _ in range(2)]
+    total = 0
+    for x in xs:
+        total = 0
+        for t, m in enumerate(counts * 4):
+            at = 1024 * t + rng.permutation(1024)[:m]
+            x[at] = (rng.choice([-1.0, 1.0], m) * (1.0 + 0.2 * rng.random(m))).astype(np.float32)
+            total += m
+    xd = [torch.from_numpy(x).cuda() for x in xs]
+    gd = [torch.zeros(n, device="cuda") for _ in xs]
+    ctx = lib.Context(2, n, n // 2)
+    ctx.set_option(lib.ARTOPK_OPT_GUESS_MIN_N, guess)
+    ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, 0)
+    for k in (17, total // 8, total // 2, total - 5):
+        if k > n // 2:
+            continue
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        sm, up = torch.zeros(k, device="cuda"), torch.zeros(n, device="cuda")
+        ctx.artopk_select_topk(xd[0], k, idx)
+        assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(xs[0], k)), k
+        res = [x.clone() for x in xd]
+        ctx.artopk_step(gd, res, k, lib.ARTOPK_STAR, 2, idx, sm, up)
+        ctx.status()
+        want = orc.step([np.zeros(n, np.float32)] * 2, xs, k, orc.MODE_STAR, step_no=2)
+        assert np.array_equal(idx.cpu().numpy(), want.idx), k
+        assert np.array_equal(sm.cpu().numpy().view(np.uint32), want.sum.view(np.uint32))
+        for r in range(2):
+            assert np.array_equal(res[r].cpu().numpy().view(np.uint32), want.residual[r].view(np.uint32)), (k, r)
+
+
 # few kept of a list that holds the whole vector, as long as the final pass takes with short tiles, and longer
 @pytest.mark.parametrize("n", [3 << 18, (3 << 18) + 1, (3 << 18) + 8192 * 3 + 5, 3_000_001])
 @pytest.mark.parametrize("kind", ["equal", "ends"])
