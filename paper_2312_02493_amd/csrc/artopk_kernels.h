@@ -1834,10 +1834,12 @@ k_pick_mask(SelParams p, LeaderArgs la) {
 // Shapes (138 M select, whole call): 8 waves x 16 elements 303 us, 8 x 8 325, 4 x 16
 // 333, 16 x 16 310, 16 x 8 328.
 //   Tiles in which more than a quarter survives, and survivors that are only counted, go from
-// the registers as before (60 M equal values 229 us, staged 295; one in ten of 11.7 M sorted
-// ones 30 against 40; an eighth or a half for a quarter: the same), so that the stage needs
-// places for a quarter of a tile: 54 instead of 66 KB a block of 8 waves, 35 instead of 58 in
-// k_level1 with 4, whose two jobs share one histogram.
+// the registers as before (60 M equal values 229 us, staged 295; an eighth or a half for a
+// quarter: the same), so that the stage needs places for a quarter of a tile: 54 instead of
+// 66 KB a block of 8 waves, 35 instead of 58 in k_level1 with 4, whose two jobs share one
+// histogram.  Tiles in which all survive need no places and are staged (registers / staged
+// with places / without, us: 3 M of one top digit 29/18/17, of two values 27/23/19; one in ten
+// of 11.7 M sorted ones, all the work in a few blocks, 30/40/34).
 // ---------------------------------------------------------------------------
 constexpr int kC1Waves = 4, kC1R = 4;  // (flat vectors on the histogram route take 8 waves)
 
@@ -1962,7 +1964,8 @@ __device__ __forceinline__ void compact1_body(const SelParams& p, uint32_t* __re
       }
       buf ^= 1;
     }
-    if (wsum > (uint32_t)FEW || !write_out) {  // many, or only to be counted: from the registers
+    const bool full = wsum == (uint32_t)WSPAN;  // every element of the wave's tile
+    if ((wsum > (uint32_t)FEW && !full) || !write_out) {  // many, or only to be counted: from the registers
       uint32_t pos = base + before;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -1985,7 +1988,7 @@ __device__ __forceinline__ void compact1_body(const SelParams& p, uint32_t* __re
             make_uint4(raw[4 * r + 0], raw[4 * r + 1], raw[4 * r + 2], raw[4 * r + 3]);
       // every lane lists its survivors; few lanes have more than one or two
       uint32_t pos = before;
-      for (uint32_t left = own; left != 0u; left &= left - 1u) {
+      for (uint32_t left = full ? 0u : own; left != 0u; left &= left - 1u) {
         tpos[pos] = (uint16_t)(lane * E + (uint32_t)__builtin_ctz(left));
         ++pos;
       }
@@ -1994,7 +1997,7 @@ __device__ __forceinline__ void compact1_body(const SelParams& p, uint32_t* __re
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       // then the wave takes them one per lane: list entries go out side by side
       for (uint32_t i = lane; i < wsum; i += 64u) {
-        const uint32_t q = tpos[i];  // element q of the wave's tile: lane q / E, group (q / 4) mod R
+        const uint32_t q = full ? i : tpos[i];  // element q of the wave's tile: lane q / E, group (q / 4) mod R
         const uint32_t w = traw[((q >> 2) & (uint32_t)(R - 1)) * 256u + (q / E) * 4u + (q & 3u)];
         const uint32_t kk = w & kKeyMask;
         const uint32_t j = (uint32_t)(tb + (int64_t)wave * WSPAN) + q;
