@@ -369,19 +369,24 @@ int artopk_set_profile(artopk_ctx* ctx, int32_t enable);
 int artopk_get_profile(artopk_ctx* ctx, float* ms_out, int32_t count);
 
 /*
- * How the last artopk_step ran its selection (Sec. III-B leaves the Top-k
- * method open; this only reports which of the library's equivalent routes was
- * taken, for tests and tuning).  Synchronises the stream and writes up to
- * `count` host int32 values:
- *   [0] 1 if the step sampled a threshold guess before its fused pass
- *   [1] 1 if the survivor list was then written from the fused pass' bit mask
+ * How the last artopk_step, artopk_select_topk or artopk_topk_workers ran its
+ * selection (Sec. III-B leaves the Top-k method open; this only reports which of
+ * the library's equivalent routes was taken, for tests and tuning).  Synchronises
+ * the stream and writes up to `count` host int32 values:
+ *   [0] 1 if a threshold guess was sampled before the (fused or read-only) pass
+ *   [1] 1 if the survivor list was then written from what that pass marked
  *       (0 with [0] = 1: the guess did not hold and the full route was taken)
  *   [2] entries in the survivor list
  *   [3] 1 if the list was written after the first radix digit (or from the
  *       mask), 0 if that did not fit and the deeper array passes wrote it
  *   [4] workers the dominant streaming kernel covered (W, or W-1 when the
- *       leader is known up front)
- * Flat (one-segment) steps only; segmented steps report [0] = [1] = 0.
+ *       leader is known up front; 1 in a short step with such a leader)
+ *   [5] 1 if the step ran in the short vectors' launch sequence
+ *   [6] 1 if that sequence's selection had so many values to choose among that
+ *       all its blocks counted them (it writes no list then)
+ * Flat (one-segment) selections only; segmented ones report [0] = [1] = 0.  Of
+ * selections on several vectors [1] to [3] are the first vector's of those that
+ * were selected on last.
  */
 int artopk_select_info(artopk_ctx* ctx, int32_t* info_out, int32_t count);
 

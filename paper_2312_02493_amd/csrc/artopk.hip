@@ -121,8 +121,8 @@ struct artopk_ctx {
   bool small_off = false;  // a launch of such a step failed: its scratch may not be zero any more
   void* slab = nullptr;
   Scratch s;
-  // how the last step ran (artopk_select_info)
-  int32_t last_guessed = 0, last_dom_workers = 0;
+  // how the last step or selection ran (artopk_select_info)
+  int32_t last_guessed = 0, last_dom_workers = 0, last_short = 0;
   int g_type = ARTOPK_G_F32;  // element type of the gradients of the step being enqueued
   // descriptors of the last segmented layout uploaded to table_dev
   std::vector<int64_t> cached_off, cached_k;
@@ -1008,6 +1008,7 @@ int enqueue_topk_rows(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t n, 
     }
   }
   const bool marks = guessed || gp.on;
+  c->last_guessed = marks ? 1 : 0;
   for (int32_t r0 = 0; r0 < w; r0 += per) {
     const int32_t nv = w - r0 < per ? w - r0 : per;
     // The fused pass counted per chunk of its own layout; the two passes of the histogram route do best with about
@@ -1424,9 +1425,10 @@ int artopk_select_info(artopk_ctx* ctx, int32_t* info_out, int32_t count) {
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   SelState st{};
   HIP_TRY(ctx, hipMemcpy(&st, ctx->s.zero_base + kSegState, sizeof(st), hipMemcpyDeviceToHost));
-  const int32_t v[5] = {ctx->last_guessed, ctx->last_guessed ? (int32_t)st.use_mask : 0, (int32_t)st.list_count,
-                        (int32_t)st.compact_level, ctx->last_dom_workers};
-  for (int i = 0; i < count && i < 5; ++i) info_out[i] = v[i];
+  const int32_t v[7] = {ctx->last_guessed, ctx->last_guessed ? (int32_t)st.use_mask : 0, (int32_t)st.list_count,
+                        (int32_t)st.compact_level, ctx->last_dom_workers, ctx->last_short,
+                        ctx->last_short ? (int32_t)st.many : 0};
+  for (int i = 0; i < count && i < 7; ++i) info_out[i] = v[i];
   return ARTOPK_OK;
 }
 
@@ -1577,6 +1579,9 @@ int artopk_select_topk(artopk_ctx* ctx, const float* acc, int64_t n, int32_t nse
   const PtrTable tab = make_table(one, 1);
   prof_begin(ctx);
   prof_mark(ctx, 1);
+  ctx->last_guessed = 0;
+  ctx->last_dom_workers = 1;
+  ctx->last_short = 0;
   if (seg_off && nseg > 1) {
     const Plan* pl = nullptr;
     if ((rc = segmented_plan(ctx, n, nseg, seg_off, seg_k, &pl))) return rc;
@@ -1772,6 +1777,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
 
   ctx->last_guessed = 0;
   ctx->last_dom_workers = w;
+  ctx->last_short = 0;
   if (mode == ARTOPK_VAR_TOPK) {
     // Literal Alg. 1: Top-k on every worker, leader = largest squared norm of its own k values,
     // then the leader's indices are the shared ones.
@@ -1814,6 +1820,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
       HIP_TRY(ctx, hipGetLastError());
     }
     if (leader_first) ctx->last_dom_workers = 1;
+    ctx->last_short = 1;
     return small_step(ctx, gt, rt, w, n, k, mode == ARTOPK_VAR ? 1 : mode == ARTOPK_VAR_G ? 2 : 0,
                       leader_first ? leader_host : -1, leader_out, var_out, idx_out, vals_out, sum_out, update_out);
   }

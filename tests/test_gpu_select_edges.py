@@ -187,9 +187,17 @@ def test_selection_marked_in_one_read(n, kind, monkeypatch):
         vals = torch.full((w, k), float("nan"), device="cuda")
         sq = torch.zeros(w, dtype=torch.float64, device="cuda")
         ctx.artopk_topk_workers(xd, k, idx, vals, sq)
+        info = [ctx.select_info()]
         one = torch.full((k,), -1, dtype=torch.int32, device="cuda")
         ctx.artopk_select_topk(xd[w - 1], k, one)
+        info.append(ctx.select_info())
         ctx.status()
+        if not gpu_util.FORCED:  # which route ran: too dense for a bound, a bound that holds, none
+            assert [i["guessed"] for i in info] == [0 if k * 32 > n else 1] * 2, (n, kind, k, info)
+            if k * 32 <= n and (kind in ("normal", "special") or (kind == "clustered" and k <= n // 100)):
+                assert [i["from_mask"] for i in info] == [1, 1], (n, kind, k, info)
+            if kind == "equal":
+                assert [i["from_mask"] for i in info] == [0, 0], (n, kind, k, info)
         for r in range(w):
             want = orc.topk_indices(xs[r], k)
             assert np.array_equal(idx[r].cpu().numpy(), want), (n, kind, k, r)

@@ -52,6 +52,8 @@ def test_short_steps_match_the_oracle(n, kind):
             runner.load_res(res)
             got = runner.step(k, mode, step_no, fixed_leader=w - 1, want_vals=step_no % 2 == 1)
             assert_step_matches(got, want, mode)
+            on_device = mode in (orc.MODE_VAR, orc.MODE_VAR_G) and w < 8
+            assert gpu_util.FORCED or runner.ctx.select_info()["short"] == (n <= (3 << 18 if on_device else 1 << 20))
 
 
 # the same step on both launch sequences, in turn on one context (the short one must leave its scratch as it found it)
@@ -95,9 +97,13 @@ def test_short_steps_and_general_steps_alternate(n, w, k, g):
         torch.testing.assert_close(va, vb, rtol=1e-12, atol=0.0)  # float64 sums of n terms in another order
 
 
+def _few(n):
+    return 10240 + 240 * ((n + 8191) // 8192)
+
+
 def _narrow(rng, n, kind, r):
     """Vectors whose threshold's top digit many values share (up to `few` of them are left to one block of the selection)."""
-    few = 10240 + 240 * ((n + 8191) // 8192)
+    few = _few(n)
     x = (rng.standard_normal(n) * 0.01).astype(np.float32)
     if kind == "band":  # all of them, most second and last digits
         return (1.0 + rng.random(n) * 0.06).astype(np.float32)
@@ -138,6 +144,12 @@ def test_short_steps_on_narrow_values(n, kind):
             runner.load_g(g)
             runner.load_res(res)
             assert_step_matches(runner.step(k, mode, step_no, want_vals=False), want, mode)
+            info = runner.ctx.select_info()
+            assert gpu_util.FORCED or info["short"] == 1
+            if now == "ordinary" or kind == "few":
+                assert gpu_util.FORCED or info["many"] == 0, (k, now)
+            elif kind != "few1" or k <= _few(n):  # (a threshold among the narrow values)
+                assert gpu_util.FORCED or info["many"] == 1, (k, now)
 
 
 # narrow values may not make a short step slower than the general launch sequence is on them (one block alone took
