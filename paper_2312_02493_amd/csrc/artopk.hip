@@ -42,6 +42,7 @@ constexpr int32_t kMaxBatch = 16;  // vectors selected on in one launch set
 // against 79/88, 8 x 4 M 113/117 against 105/117, 1 x 138 M 268/294 against 162/184, 8 x 25.6 M 393/441 against
 // 234/287.  (One in ten kept: 25.6 M 116 against 137, 138 M 390 against 389, so denser than one in 32 never.)
 constexpr int64_t kGuessMinN = (int64_t)1 << 25, kReadGuessMinN = (int64_t)3 << 23;
+constexpr int64_t kTwiceMaxN = (int64_t)5 << 23;  // (see plan_guess_read)
 
 // Flat steps on short vectors run in three launches (small_step) up to ARTOPK_OPT_SHORT_MAX_N elements, or three
 // quarters of that where the leader comes from the data and fewer than eight workers share the cost of it, and up
@@ -743,6 +744,14 @@ GuessPlan plan_guess_read(const artopk_ctx* c, int64_t n, int64_t k, int vectors
   const int64_t nspans = (n + gp.span - 1) / gp.span;
   if (nspans * want * vectors > c->s.tilebuf_entries) return gp;
   gp.tile_cap = (int32_t)want;
+  // A bound that more keys reach than the pieces hold on average (many values equal, or in one top digit, just below
+  // the threshold) has nearly every span marked twice.  From kTwiceMaxN elements on it counts as none: the histogram
+  // route is then the better one (one in a hundred kept, us, marked twice / no bound: one in twenty equal just below,
+  // 1 x 32 M 129/142, 40 M 156/158, 50 M 175/170, 138 M 390/359, 400 M 1002/887, 8 x 4 M 155/140, 4 x 12 M 185/172;
+  // uniform values, 1 x 32 M 112/130, 40 M 127/138, 50 M 143/156, 60 M 172/173, 400 M 834/803, 2 x 20 M 142/145, 4 x 12 M
+  // 160/152).
+  const double held = sample * (double)want / (double)gp.span;
+  if (n * vectors >= kTwiceMaxN && held < (double)gp.m_max) gp.m_max = (uint32_t)held;
   gp.on = true;
   return gp;
 }

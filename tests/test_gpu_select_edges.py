@@ -206,6 +206,25 @@ def test_selection_marked_in_one_read(n, kind, monkeypatch):
         assert np.array_equal(one.cpu().numpy(), orc.topk_indices(xs[w - 1], k))
 
 
+# many values in the threshold's top digit: more than the spans' pieces hold, fewer than the list does.  Long vectors
+# take no bound then (they would be marked twice), short ones are marked again where a piece is too small
+@pytest.mark.parametrize("n,from_mask", [((5 << 23) - 4, 1), (5 << 23, 0), ((5 << 23) + 8195, 0)])
+def test_bound_that_overfills_the_pieces(n, from_mask):
+    import torch
+    import gpu_util
+
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.rand(n, generator=gen, device="cuda")  # one in sixteen in the top digit
+    ctx = gpu_util.make_context(1, n, n // 100)
+    k = n // 100
+    idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+    ctx.artopk_select_topk(x, k, idx)
+    info = ctx.select_info()
+    ctx.status()
+    assert gpu_util.FORCED or (info["guessed"], info["from_mask"]) == (1, from_mask), info
+    assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x.cpu().numpy(), k))
+
+
 # more vectors than a batch holds, and batches whose shares of the list are small (one in eight kept)
 @pytest.mark.parametrize("w,n,k", [(17, 20_001, 2500), (33, 9001, 40), (3, 4_300_000, 600_000), (9, 4_300_001, 43_000)])
 def test_batches_of_whole_vectors(w, n, k):
