@@ -128,7 +128,8 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 1 .. 2^31 (2^31 = never), default 33554432.
  *                                 Selections on vectors as they are take their
  *                                 guess from 25165824 elements on (all vectors
- *                                 of the call together), unless this is changed
+ *                                 of the call together) until this is set, to
+ *                                 whatever value; then from that on, each vector
  *   ARTOPK_OPT_UPDATE_TILES_MIN_N shortest vector whose dense update is
  *                                 streamed tile by tile with the values stored
  *                                 behind the zeros, shorter ones are built

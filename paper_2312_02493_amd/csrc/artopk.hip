@@ -114,6 +114,7 @@ struct artopk_ctx {
   // vectors of at least this many elements get a sampled threshold guess before the fused pass, which
   // then counts and marks only the keys that reach it (the selection no longer re-reads the vector)
   int64_t guess_min_n = kGuessMinN;
+  bool guess_min_n_set = false;  // by artopk_set_option: then it holds for vectors that are only read, too
   // vectors of at least this many elements get their dense update from k_update_tiles
   int64_t update_tiles_min_n = (int64_t)1 << 22;
   int stage_tiles = 1;  // guess route, one marking worker: the fused pass hands the marked elements on per tile
@@ -718,8 +719,7 @@ GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, int marking) {
 // longer list costs little here (nothing has to be given back from it), and pieces wherever they fit.
 GuessPlan plan_guess_read(const artopk_ctx* c, int64_t n, int64_t k, int vectors, int64_t list_cap) {
   GuessPlan gp;
-  const bool by_default = c->guess_min_n == kGuessMinN;  // (the option's own value holds for every vector)
-  if (c->s.mask == nullptr || (by_default ? n * vectors < kReadGuessMinN : n < c->guess_min_n)) return gp;
+  if (c->s.mask == nullptr || (c->guess_min_n_set ? n < c->guess_min_n : n * vectors < kReadGuessMinN)) return gp;
   if (k * 32 > n) return gp;
   int64_t runs = n / (4 * kGuessRun);
   if (runs > 4096) runs = 4096;
@@ -1388,6 +1388,7 @@ int artopk_set_option(artopk_ctx* ctx, int32_t key, int64_t value) {
     case ARTOPK_OPT_GUESS_MIN_N:
       if (value < 1 || value > (1ll << 31)) return fail(ctx, ARTOPK_EINVAL, "ARTOPK_OPT_GUESS_MIN_N outside [1, 2^31]");
       ctx->guess_min_n = value;
+      ctx->guess_min_n_set = true;
       return ARTOPK_OK;
     case ARTOPK_OPT_UPDATE_TILES_MIN_N:
       if (value < 1 || value > (1ll << 31))

@@ -225,6 +225,24 @@ def test_bound_that_overfills_the_pieces(n, from_mask):
     assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x.cpu().numpy(), k))
 
 
+# a length set for the guess holds for selections on vectors as they are, also if it is the default's value
+@pytest.mark.parametrize("value,guessed", [(None, 1), (1 << 25, 0), (25_500_000, 1), (25_500_001, 0)])
+def test_length_from_which_read_only_selections_guess(value, guessed):
+    import torch
+    import paper_2312_02493_amd as lib
+
+    n, k = 25_500_000, 1000
+    x = torch.randn(n, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    ctx = lib.Context(1, n, k)
+    if value is not None:
+        ctx.set_option(lib.ARTOPK_OPT_GUESS_MIN_N, value)
+    idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+    ctx.artopk_select_topk(x, k, idx)
+    assert ctx.select_info()["guessed"] == guessed
+    ctx.status()
+    assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x.cpu().numpy(), k))
+
+
 # more vectors than a batch holds, and batches whose shares of the list are small (one in eight kept)
 @pytest.mark.parametrize("w,n,k", [(17, 20_001, 2500), (33, 9001, 40), (3, 4_300_000, 600_000), (9, 4_300_001, 43_000)])
 def test_batches_of_whole_vectors(w, n, k):
