@@ -11,7 +11,7 @@ if ROOT not in sys.path:
 def pytest_addoption(parser):
     parser.addoption("--artopk-option", action="append", default=[], metavar="NAME=VALUE",
                      help="route switch applied to every context the GPU tests create unless a test sets its own "
-                          "(guess_min_n, update_tiles_min_n, leader_first, nontemporal, stage_tiles); the routes "
+                          "(guess_min_n, update_tiles_min_n, leader_first, nontemporal, stage_tiles, short_max_n); the routes "
                           "give identical results, so the suite may be run on any of them (its checks of which route ran "
                           "are then off)")
 

@@ -13,7 +13,8 @@ OPTIONS = {}
 # Switches forced for the whole session (pytest --artopk-option): a test's checks of WHICH route ran
 # are then off, its comparisons of the results are not.
 FORCED = set()
-_OPTION_KEYS = {"guess_min_n": 0, "update_tiles_min_n": 1, "leader_first": 2, "nontemporal": 3, "stage_tiles": 4}
+_OPTION_KEYS = {"guess_min_n": 0, "update_tiles_min_n": 1, "leader_first": 2, "nontemporal": 3, "stage_tiles": 4,
+                "short_max_n": 5}
 
 
 def make_context(*args, **kwargs):

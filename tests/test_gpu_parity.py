@@ -89,7 +89,9 @@ def _one_step(g, res, k, mode=orc.MODE_FIXED, leader=0, step_no=0):
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 5, 63, 64, 255, 1025, 16384, 16385, 40001])
-def test_tiny_and_ragged_sizes(n):
+@pytest.mark.parametrize("short", [0, 1 << 20])
+def test_tiny_and_ragged_sizes(n, short, monkeypatch):
+    monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", short)  # the general launch sequence, and the short vectors' one
     rng = np.random.default_rng(n)
     g = [rng.standard_normal(n).astype(np.float32) for _ in range(2)]
     res = [rng.standard_normal(n).astype(np.float32) * 0.1 for _ in range(2)]
@@ -499,12 +501,15 @@ def test_bucketed_layout_16mi_elements(rule, monkeypatch):
 
 
 @pytest.mark.parametrize("rule,route", [("var", "histogram"), ("var", "guess"), ("star", "histogram"), ("star", "guess"),
-                                        ("star", "pieces"), ("counter", "histogram"), ("counter", "guess")])
+                                        ("star", "pieces"), ("counter", "histogram"), ("counter", "guess"),
+                                        ("var", "short"), ("star", "short"), ("counter", "short"),
+                                        ("var", "short_narrow"), ("star", "short_narrow"), ("counter", "short_narrow")])
 def test_step_captured_in_a_hip_graph_replays_like_eager_steps(rule, route, monkeypatch):
     """One step recorded into a HIP graph (through torch's capture) and replayed three times,
     with host work and synchronisation between the replays: every replay must be the next step
     of the oracle, residual carried.  The step allocates nothing, clears its scratch with a fill
-    kernel (no memset nodes) and takes every data-dependent decision on the device.  Under the
+    kernel (no memset nodes; the short launch sequence leaves its scratch as it found it, also where
+    all its blocks count narrow values) and takes every data-dependent decision on the device.  Under the
     round-robin rule the recorded leader (step 1 -> worker 1) is the one every replay uses, unless
     the iteration counter lives on the device (rule "counter"): then replay r is step 1 + r with the
     next worker of the round leading.  The dense update is written in its tile-by-tile form on the
@@ -517,6 +522,8 @@ def test_step_captured_in_a_hip_graph_replays_like_eager_steps(rule, route, monk
         monkeypatch.setitem(gpu_util.OPTIONS, "update_tiles_min_n", 1)
         # the leader's fused pass hands the marked elements on tile by tile, or leaves only the mask
         monkeypatch.setitem(gpu_util.OPTIONS, "stage_tiles", 2 if route == "pieces" else 0)
+    else:
+        monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 0 if route == "histogram" else 1 << 20)
     mode_lib = {"var": lib.ARTOPK_VAR, "star": lib.ARTOPK_STAR, "counter": lib.ARTOPK_STAR_COUNTER}[rule]
     mode_orc = orc.MODE_VAR if rule == "var" else orc.MODE_STAR
     n, w = 200_003, 4
@@ -525,6 +532,9 @@ def test_step_captured_in_a_hip_graph_replays_like_eager_steps(rule, route, monk
     dev = torch.device("cuda:0")
     side = torch.cuda.Stream()
     g_np = [wl.gen(1, r) for r in range(w)]
+    if route == "short_narrow":
+        rng = np.random.default_rng(3)
+        g_np = [((1.0 + 0.01 * rng.random(n)) * (1.0 + 0.25 * r)).astype(np.float32) for r in range(w)]
     with torch.cuda.stream(side):
         ctx = gpu_util.make_context(w, n, k, 1, stream=side.cuda_stream)
         g = [torch.from_numpy(a).to(dev) for a in g_np]
@@ -570,12 +580,14 @@ def test_step_captured_in_a_hip_graph_replays_like_eager_steps(rule, route, monk
                 "residual": [r.cpu().numpy() for r in res], "vals": vals.cpu().numpy().reshape(w, k),
             }
             assert_step_matches(got, want, mode_orc)
-            assert gpu_util.FORCED or (ctx.select_info()["guessed"] == (0 if route == "histogram" else 1))
+            info = ctx.select_info()
+            assert gpu_util.FORCED or (info["guessed"], info["short"], info["many"]) == \
+                (int(route in ("guess", "pieces")), int(route in ("short", "short_narrow")), int(route == "short_narrow"))
             want_res = want.residual
             _ = torch.ones(1000, device=dev).sum().item()  # unrelated eager work between the replays
 
 
-@pytest.mark.parametrize("route", ["histogram", "guess", "segments"])
+@pytest.mark.parametrize("route", ["histogram", "guess", "segments", "short"])
 def test_round_robin_leader_from_the_counter_on_the_device(route, monkeypatch):
     """ARTOPK_STAR_COUNTER: the iteration counter of the round-robin rule (Alg. 1, STAR branch) is
     kept by the context on the device, the `step` argument is ignored, and every call moves the
@@ -585,6 +597,8 @@ def test_round_robin_leader_from_the_counter_on_the_device(route, monkeypatch):
 
     if route == "guess":
         monkeypatch.setitem(gpu_util.OPTIONS, "guess_min_n", 4096)
+    elif route == "histogram":
+        monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 0)
     n, w = 150_011, 3
     wl = inp.workload(2, n=n, w=w)
     seg_off = seg_k = None
@@ -607,7 +621,8 @@ def test_round_robin_leader_from_the_counter_on_the_device(route, monkeypatch):
         got = run.step(k, lib.ARTOPK_STAR_COUNTER, 123_456, seg_off=seg_off, seg_k=seg_k)  # step argument unused
         assert_step_matches(got, want, orc.MODE_STAR)
         if route != "segments":
-            assert gpu_util.FORCED or (run.ctx.select_info()["guessed"] == (1 if route == "guess" else 0))
+            info = run.ctx.select_info()
+            assert gpu_util.FORCED or (info["guessed"], info["short"]) == (int(route == "guess"), int(route == "short"))
         res = want.residual
 
 
@@ -763,6 +778,7 @@ def test_dense_update_streamed_tile_by_tile(n, monkeypatch):
     also the stand-alone scatter entry point."""
     import torch
     monkeypatch.setitem(gpu_util.OPTIONS, "update_tiles_min_n", 1)
+    monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 0)  # (whose last launch writes the update itself)
     w = 3
     rng = np.random.default_rng(31)
     kk = min(n, max(n // 200, 12)) if n > 12 else 2   # few enough kept entries for the streamed form when n is not tiny
@@ -801,6 +817,7 @@ def test_ordinary_loads_and_stores_give_the_same_bits(guess, monkeypatch):
     """The streaming passes use non-temporal loads and stores by default; the library's switch to
     ordinary ones must not change a bit, on either selection route and under either kind of leader."""
     monkeypatch.setitem(gpu_util.OPTIONS, "nontemporal", 0)
+    monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 0)  # (which knows ordinary ones only)
     if guess:
         monkeypatch.setitem(gpu_util.OPTIONS, "guess_min_n", 4096)
     w, n = 3, 6 * 32768 + 77
@@ -823,7 +840,7 @@ def test_ordinary_loads_and_stores_give_the_same_bits(guess, monkeypatch):
 
 # ------------------------------------------------------------------ variance against awkward data
 @pytest.mark.parametrize("case", ["outlier_first", "outlier_first_four", "common_offset", "outlier_last"])
-@pytest.mark.parametrize("route", ["stand_alone", "step_histogram", "step_guess"])
+@pytest.mark.parametrize("route", ["stand_alone", "step_histogram", "step_guess", "step_short"])
 def test_variance_is_not_spoilt_by_one_element_or_an_offset(case, route, monkeypatch):
     """The per-worker variance (Sec. III-B leader rule) must stay within 1e-5 of the two-pass
     float64 definition whatever sits at the start of a vector: an element a million standard
@@ -862,8 +879,11 @@ def test_variance_is_not_spoilt_by_one_element_or_an_offset(case, route, monkeyp
         return
     if route == "step_guess":
         monkeypatch.setitem(gpu_util.OPTIONS, "guess_min_n", 4096)
+    elif route == "step_short":
+        monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 1 << 21)
     res = [np.zeros(n, np.float32) for _ in range(w)]
     got, want = _one_step(g, res, k, mode=orc.MODE_VAR)
+    assert gpu_util.FORCED or got["info"]["short"] == int(route == "step_short")
     assert gpu_util.FORCED or (got["info"]["guessed"] == (1 if route == "step_guess" else 0))
     np.testing.assert_allclose(got["var"], ref, rtol=1e-5, atol=0.0)
 
@@ -925,3 +945,10 @@ def test_options_are_validated_and_reported():
         assert e.value.code == -1
     ctx.set_option(lib.ARTOPK_OPT_GUESS_MIN_N, 4096)
     assert ctx.get_option(lib.ARTOPK_OPT_GUESS_MIN_N) == 4096
+    assert ctx.get_option(lib.ARTOPK_OPT_SHORT_MAX_N) == 1 << 20
+    for bad in (-1, (1 << 21) + 1):
+        with pytest.raises(lib.ArTopkError):
+            ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, bad)
+    for value in (0, 1 << 21):
+        ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, value)
+        assert ctx.get_option(lib.ARTOPK_OPT_SHORT_MAX_N) == value

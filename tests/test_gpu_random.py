@@ -87,7 +87,7 @@ def _to_bits16(x32, kind):
 @pytest.mark.parametrize("seed", range(100, 228))
 def test_random_problem_on_random_routes(seed, monkeypatch):
     """The random problems again, each with a random draw of everything that chooses a route or a
-    form of the call: the five route switches, every leader rule (the round-robin counter kept on the
+    form of the call: the six route switches, every leader rule (the round-robin counter kept on the
     device, the raw-gradient variance and the literal rule of Alg. 1 included), gradients stored as
     float32, bfloat16 or float16, with or without vals_out and the dense update.  Three steps with
     the residual carried, bit for bit against the oracle."""
@@ -124,6 +124,7 @@ def _run_on_random_routes(seed, monkeypatch, rng, n, w, kind, k, seg_off, seg_k,
     for name, choices in (("guess_min_n", [1 << 25, 4096, 4096]), ("stage_tiles", [0, 1, 2]), ("leader_first", [0, 1, 1]),
                           ("update_tiles_min_n", [1 << 22, 1]), ("nontemporal", [0, 1])):
         monkeypatch.setitem(gpu_util.OPTIONS, name, int(opt.choice(choices)))
+    monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", int(np.random.default_rng(9000 + seed).choice([0, 1 << 20, 1 << 21])))
     rules = [("star", lib.ARTOPK_STAR, orc.MODE_STAR), ("fixed", lib.ARTOPK_FIXED, orc.MODE_FIXED),
              ("var", lib.ARTOPK_VAR, orc.MODE_VAR), ("var_g", lib.ARTOPK_VAR_G, orc.MODE_VAR_G),
              ("counter", lib.ARTOPK_STAR_COUNTER, orc.MODE_STAR)]

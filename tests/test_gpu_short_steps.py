@@ -29,7 +29,8 @@ def _vector(rng, n, kind, r):
 
 
 # one element, less than a group, the edges of the last launch's tile and of a chunk, the longest vector of the route
-@pytest.mark.parametrize("n", [1, 3, 1023, 1024, 1025, 8191, 8193, 65537, 300_002, 1 << 20])
+# (of the variance rules with fewer than eight workers: 3 << 18)
+@pytest.mark.parametrize("n", [1, 3, 1023, 1024, 1025, 8191, 8193, 65537, 300_002, 3 << 18, (3 << 18) + 1, 1 << 20])
 @pytest.mark.parametrize("kind", ["normal", "ties", "equal", "zeros", "one_bin", "special"])
 def test_short_steps_match_the_oracle(n, kind):
     rng = np.random.default_rng(n)
@@ -70,6 +71,7 @@ def test_short_steps_and_general_steps_alternate(n, w, k, g):
     ctx = lib.Context(w, n, k)
 
     def run(short, mode, step):
+        ctx.set_step_counter(step)
         ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, (1 << 20) if short else 0)
         res = [r.clone() for r in r0]
         idx = torch.zeros(k, dtype=torch.int32, device="cuda")
@@ -88,8 +90,7 @@ def test_short_steps_and_general_steps_alternate(n, w, k, g):
         return [idx, sm.view(torch.int32), up.view(torch.int32), vals.view(torch.int32), lead] + \
             [r.view(torch.int32) for r in res], var
 
-    for step, mode in enumerate((lib.ARTOPK_STAR, lib.ARTOPK_VAR, lib.ARTOPK_STAR, lib.ARTOPK_VAR_G), 1):
-        ctx.set_step_counter(step)
+    for step, mode in enumerate((lib.ARTOPK_STAR, lib.ARTOPK_VAR, lib.ARTOPK_STAR_COUNTER, lib.ARTOPK_VAR_G), 1):
         a, va = run(True, mode, step)
         b, vb = run(False, mode, step)
         for x, y in zip(a, b):
