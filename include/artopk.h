@@ -104,7 +104,9 @@ enum {
  * 8 (max_k + max(max_n / 8, 2^22)) bytes of survivor list plus 8 max_w max_k bytes plus
  * max_n / 8 bytes per worker of survivor bit masks plus 1.5 max_n bytes in which a
  * leader's fused pass stages list entries tile by tile plus, for selections on several vectors
- * at a time, max_n / 341 bytes of scan flags for each of up to 16 workers.  The library reads no environment
+ * at a time, max_n / 341 bytes of scan flags and 64 KiB for each of up to 16 workers plus, for steps on
+ * short vectors, 128 KiB per worker and 4.5 bytes for each of up to 2^21 elements, plus 1.25 MiB
+ * (artopk_scratch_bytes gives the exact size).  The library reads no environment
  * variable and keeps no state outside its contexts (artopk_variance_static's fixed
  * scratch excepted, see there).
  */
@@ -124,7 +126,8 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *   ARTOPK_OPT_GUESS_MIN_N        shortest flat vector that gets the sampled
  *                                 threshold guess before its fused pass (and
  *                                 shortest segmented vector whose fused pass
- *                                 walks the tiles in the same striding order);
+ *                                 walks the tiles in the same striding order,
+ *                                 unless its leader is known up front);
  *                                 1 .. 2^31 (2^31 = never), default 33554432.
  *                                 Selections on vectors as they are take their
  *                                 guess from 25165824 elements on (all vectors
@@ -134,14 +137,16 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 streamed tile by tile with the values stored
  *                                 behind the zeros, shorter ones are built
  *                                 chunk by chunk in on-chip memory; 1 .. 2^31,
- *                                 default 4194304
+ *                                 default 4194304.  (Of a step in the short
+ *                                 vectors' launches the last one writes it)
  *   ARTOPK_OPT_LEADER_FIRST       1 (default): with a leader known up front run
  *                                 its pass and the selection first, then one
  *                                 fused pass over the other workers; 0: the
  *                                 fused pass over all workers first and an
  *                                 entry-by-entry gather, as under the variance rule
  *   ARTOPK_OPT_NONTEMPORAL        1 (default): non-temporal loads and stores in
- *                                 the streaming passes; 0: ordinary ones
+ *                                 the streaming passes; 0: ordinary ones (which
+ *                                 the short vectors' launches always use)
  *   ARTOPK_OPT_STAGE_TILES        on the guess route with a leader known up
  *                                 front, the leader's fused pass can hand the
  *                                 elements that reach the guessed bound on as
@@ -153,9 +158,13 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 the alternative is the histogram route);
  *                                 2: for every selection; 0: never
  *   ARTOPK_OPT_SHORT_MAX_N        longest flat vector whose step runs in three
- *                                 launches (with at most 16384 elements kept;
- *                                 three quarters of it under the variance rules
- *                                 with fewer than eight workers);
+ *                                 launches (four under ARTOPK_STAR_COUNTER), with
+ *                                 at most 16384 elements kept; three quarters of
+ *                                 it where the leader is found on the device (the
+ *                                 variance rules and the counter's) with fewer
+ *                                 than eight workers, never under
+ *                                 ARTOPK_VAR_TOPK, and with a leader known up
+ *                                 front only if ARTOPK_OPT_LEADER_FIRST is 1;
  *                                 0 .. 2^21 (0 = never), default 1048576
  */
 enum {

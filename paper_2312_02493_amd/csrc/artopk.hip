@@ -37,19 +37,23 @@ constexpr int kPassRestThreads = 1024, kPassRestU = 8;
 
 constexpr int32_t kMaxBatch = 16;  // vectors selected on in one launch set
 // Default of ARTOPK_OPT_GUESS_MIN_N, and what stands in its place for vectors that are only read: elements of
-// the vectors selected on together.  Measured (us, one in a thousand / one in a hundred kept; histogram route
-// against read-only marking): 1 x 11.7 M 58/60 against 63/65, 1 x 16.8 M 63/65 against 67/75, 1 x 25.6 M 85/88.5
-// against 79/88, 8 x 4 M 113/117 against 105/117, 1 x 138 M 268/294 against 162/184, 8 x 25.6 M 393/441 against
-// 234/287.  (One in ten kept: 25.6 M 116 against 137, 138 M 390 against 389, so denser than one in 32 never.)
+// the vectors selected on together.  Measured (us, histogram route / read-only marking, one in a thousand, a hundred
+// and 33 kept, heavy tails): 1 x 12 M 60/60 61/64 64/70, 16.8 M 67/63 70/67 71/75, 20 M 79/68 82/70 85/82, 23 M 81/68
+// 86/73 88/84, 25.6 M 90/71 92/77 99/90; 2 x 10 M 86/77 88/81 93/92; 4 x 5 M 82/80 85/86; 8 x 2.5 M 86/84 90/89, 4 M
+// 116/97 119/102; 16 x 1.5 M 98/108.  The line lies where all of them gain.  (One in ten kept: 25.6 M 116 against 137,
+// 138 M 390 against 389, so denser than one in 32 never.)
 constexpr int64_t kGuessMinN = (int64_t)1 << 25, kReadGuessMinN = (int64_t)3 << 23;
 constexpr int64_t kTwiceMaxN = (int64_t)5 << 23;  // (see plan_guess_read)
 
 // Flat steps on short vectors run in three launches (small_step) up to ARTOPK_OPT_SHORT_MAX_N elements, or three
-// quarters of that where the leader comes from the data and fewer than eight workers share the cost of it, and up
-// to 16384 kept (a single block takes the last digits).  Measured, us, ten or eight launches against three, one in
-// a hundred kept: leader known, 2 workers: 65537 elements 58/31, 262144 58/36, 1 M 64/55, 1.6 M 66/70; 16 workers:
-// 58/36, 62/40, 89/73, 107/95.  Variance rule, 2 workers: 49/36, 50/40, 524288 52/46, 1 M 56/61; 8 workers: 53/38,
-// 55/44, 67/56, 88/84, 1.6 M 107/110; 16 workers: 60/43, 73/55, 94/76, 134/117.
+// quarters of that where the leader is found on the device and fewer than eight workers share the cost of that, and
+// up to 16384 kept.  Measured, us, ten or eight launches / three, at most one in a hundred kept, 786432, 1 M, 1.3 M and
+// 1.8 M elements: leader known, 2 workers 59/44 61/49 62/55 65/66, 4 workers 60/44 63/50 65/56 69/71, 8 workers 64/50
+// 68/58 78/63 86/77, 16 workers 80/61 87/70 99/80 119/106; variance rule, 2 workers 52/50 54/55 61/65 66/65, 4 workers
+// 61/56 65/62 74/73 85/85, 6 workers 73/64 76/72 85/83 104/103, 8 workers 77/69 87/82 97/93 117/116, 16 workers 114/94
+// 134/113 153/133 189/197.  More kept, 16384, 32768 and 65536: leader known, 8 workers, 65537 elements 71/38 81/44 -,
+// 524288 63/44 67/45 70/46, 1 M 69/59 69/60 75/60; variance rule, 8 workers, 58/44 61/51 -, 67/59 70/60 72/64, 87/83
+// 89/88 92/90; 2 workers on 1 M 54/57 55/63 58/66.  Both lines lie below the crossing, which differs by rule and workers.
 constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSmallMaxChunks * kTile, kSmallMaxK = 16384;
 
 struct Scratch {
@@ -1023,8 +1027,9 @@ int enqueue_topk_rows(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t n, 
     // The fused pass counted per chunk of its own layout; the two passes of the histogram route do best with about
     // two thousand chunks over all vectors.  Behind the read-only marking one block copies a chunk's pieces, two
     // blocks fit a compute unit, and each is mostly latency: one round of 512 blocks up to 2e8 elements, two beyond
-    // (us, one in a hundred kept, 512 / 1024 / 2048 chunks: 1 x 25.6 M 78/85/85, 1 x 138 M 180/183/183, 8 x 25.6 M
-    // 271/266/274, 1 x 400 M 492/477/477; 256 chunks: 76, 183, 271, 492).
+    // (us, one in a hundred kept, 512 / 1024 / 2048 chunks: 1 x 25.6 M 78/85/85, 60 M 109/115, 138 M 180/183/183, 200 M
+    // 243/247, 230 M 275/275, 270 M 318/317, 330 M 367/369, 400 M 492/477/477; 4 x 40 M 218/219, 60 M 288/296; 8 x 20 M
+    // 219/221, 25.6 M 271/266/274, 30 M 340/346; 256 chunks: 25.6 M 76, 138 M 183, 400 M 492).
     int64_t max_chunks = kMaxChunks;
     if (gp.on)
       max_chunks = (n * nv <= ((int64_t)3 << 26) ? kMaxChunks / 2 : kMaxChunks) / nv;

@@ -3790,7 +3790,7 @@ k_sum_update(const float* __restrict__ vals, int w_count, int64_t n, const int32
 // ---------------------------------------------------------------------------
 // Short vectors: a whole step in three launches (k_small_pass, k_small_select and k_small_rest or
 // k_small_gather).  Ten launches, each a few microseconds of latency, were all that such a step took: 65537
-// elements x 2 workers 52 us, now 31; 1 M x 4 61 us, now 52 (18 and 22 us of them in k_small_select and its
+// elements x 2 workers 52 us, now 31; 1 M x 4 61 us, now 54 (28 us of them in k_small_select and its
 // last block; see small_step's rule for other sizes).  What a single block did in a launch of its own is done by the last block to finish of
 // the launch before it, and nothing has to be cleared first: the scratch of this route (SmallScratch) is
 // zero whenever no step is running, because k_small_select leaves it so.

@@ -44,6 +44,13 @@ def test_scratch_size_query():
              + 1.5 * n)                   # staged list entries
     assert abs(got - model) / model < 0.03, (got, model)
     assert 3.5e9 < got < 4.0e9           # the figure the design notes quote for this size
+    for w, n, k in ((1, 1 << 16, 100), (1, 1 << 20, 10_000), (8, 1 << 20, 10_000), (16, 1 << 18, 2_000),
+                    (64, 1 << 21, 20_000), (8, 11_689_512, 116_896), (8, 1_000_000_000, 1_000_000)):
+        batch = min(w, 16)
+        model = (w * 16.4 * 2**20 + 64 * 2**10 * batch + 8 * min(n, k + max(n // 8, 2**22)) + 8 * w * k + w * n / 8
+                 + 1.5 * n + batch * n / 341 + w * 128 * 2**10 + 4.5 * min(n, 2**21) + 1.25 * 2**20)
+        assert abs(q(w, n, k, 1) - model) / model < 0.015, (w, n, k, q(w, n, k, 1), model)
+    n, w, k = 1_000_000_000, 8, 1_000_000
     assert q(w, n, k, 1) <= q(w + 1, n, k, 1) and q(w, n, k, 1) <= q(w, n, k * 2, 1) and q(w, n, k, 1) <= q(w, n, k, 9)
     assert q(w, 1 << 20, 1024, 1) < q(w, 1 << 24, 1024, 1)
     assert q(1, 1, 1, 1) > 0
