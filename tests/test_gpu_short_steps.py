@@ -180,3 +180,51 @@ def test_short_steps_on_narrow_values_take_no_longer(kind):
         ctx.status()
         best[limit] = min(best.get(limit, 1e9), t0.elapsed_time(t1))
     assert best[1 << 20] < 1.5 * best[0], best
+
+
+# two contexts on streams of their own, beside long kernels of a third: blocks that look out for help or for others may
+# find neither, and every result is the same
+def test_narrow_steps_on_several_streams_beside_other_work():
+    import torch
+    import paper_2312_02493_amd as lib
+
+    n, w, k, steps = 1 << 20, 2, 10486, 6
+    rng = np.random.default_rng(11)
+    src = [torch.from_numpy(_narrow(rng, n, "band", r)).cuda() for r in range(w)]
+    g = [torch.full((n,), 2.0 ** -12, device="cuda") for _ in range(w)]
+    busy = [torch.randn(1 << 27, device="cuda")]
+
+    def start(stream):
+        torch.cuda.synchronize()
+        s = torch.cuda.Stream() if stream else torch.cuda.current_stream()
+        with torch.cuda.stream(s):
+            return {"s": s, "ctx": lib.Context(w, n, k, stream=s.cuda_stream), "res": [x.clone() for x in src],
+                    "idx": torch.zeros(k, dtype=torch.int32, device="cuda"), "sum": torch.zeros(k, device="cuda"),
+                    "up": torch.zeros(n, device="cuda"), "out": []}
+
+    def go(c, step):
+        with torch.cuda.stream(c["s"]):
+            c["ctx"].artopk_step(g, c["res"], k, lib.ARTOPK_STAR, step, c["idx"], c["sum"], c["up"])
+            c["out"].append((c["idx"].clone(), c["sum"].clone()))
+
+    one, two, alone = start(True), start(True), start(False)
+    other = lib.Context(1, 1 << 27, 1, stream=torch.cuda.current_stream().cuda_stream)
+    var = torch.zeros(1, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    for step in range(1, steps + 1):
+        for _ in range(3):
+            other.artopk_variance(busy, var)
+        go(one, step)
+        go(two, step)
+    torch.cuda.synchronize()
+    for step in range(1, steps + 1):
+        go(alone, step)
+    torch.cuda.synchronize()
+    for c in (one, two, alone):
+        assert gpu_util.FORCED or c["ctx"].select_info()["many"] == 1
+        c["ctx"].status()
+    for c in (one, two):
+        for (i, v), (iw, vw) in zip(c["out"], alone["out"]):
+            assert torch.equal(i, iw) and torch.equal(v.view(torch.int32), vw.view(torch.int32))
+        for r, rw in zip(c["res"], alone["res"]):
+            assert torch.equal(r.view(torch.int32), rw.view(torch.int32))
