@@ -137,8 +137,8 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 streamed tile by tile with the values stored
  *                                 behind the zeros, shorter ones are built
  *                                 chunk by chunk in on-chip memory; 1 .. 2^31,
- *                                 default 4194304.  (Of a step in the short
- *                                 vectors' launches the last one writes it)
+ *                                 default 4194304.  (A step in the short
+ *                                 vectors' launch writes it there)
  *   ARTOPK_OPT_LEADER_FIRST       1 (default): with a leader known up front run
  *                                 its pass and the selection first, then one
  *                                 fused pass over the other workers; 0: the
@@ -146,7 +146,7 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 entry-by-entry gather, as under the variance rule
  *   ARTOPK_OPT_NONTEMPORAL        1 (default): non-temporal loads and stores in
  *                                 the streaming passes; 0: ordinary ones (which
- *                                 the short vectors' launches always use)
+ *                                 the short vectors' launch always uses)
  *   ARTOPK_OPT_STAGE_TILES        on the guess route with a leader known up
  *                                 front, the leader's fused pass can hand the
  *                                 elements that reach the guessed bound on as
@@ -157,10 +157,9 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 element in 256 or denser (beyond one in 32
  *                                 the alternative is the histogram route);
  *                                 2: for every selection; 0: never
- *   ARTOPK_OPT_SHORT_MAX_N        longest flat vector whose step runs in three
- *                                 launches (four under ARTOPK_STAR_COUNTER), with
- *                                 at most 16384 elements kept; three quarters of
- *                                 it where the leader is found on the device (the
+ *   ARTOPK_OPT_SHORT_MAX_N        longest flat vector whose step runs in one
+ *                                 launch (two under ARTOPK_STAR_COUNTER); three
+ *                                 quarters of it where the leader is found on the device (the
  *                                 variance rules and the counter's) with fewer
  *                                 than eight workers, never under
  *                                 ARTOPK_VAR_TOPK, and with a leader known up
@@ -391,9 +390,10 @@ int artopk_get_profile(artopk_ctx* ctx, float* ms_out, int32_t count);
  *       mask), 0 if that did not fit and the deeper array passes wrote it
  *   [4] workers the dominant streaming kernel covered (W, or W-1 when the
  *       leader is known up front; 1 in a short step with such a leader)
- *   [5] 1 if the step ran in the short vectors' launch sequence
- *   [6] 1 if that sequence's selection had so many values to choose among that
- *       all its blocks counted them (it writes no list then)
+ *   [5] 1 if the step ran in the short vectors' launch (which writes no list;
+ *       [2] and [3] are what one after the first digit would have held)
+ *   [6] 1 if that launch's threshold shares its top digit with more than 10240
+ *       values and 240 for every 8192 elements
  * Flat (one-segment) selections only; segmented ones report [0] = [1] = 0.  Of
  * selections on several vectors [1] to [3] are the first vector's of those that
  * were selected on last.

@@ -45,16 +45,15 @@ constexpr int32_t kMaxBatch = 16;  // vectors selected on in one launch set
 constexpr int64_t kGuessMinN = (int64_t)1 << 25, kReadGuessMinN = (int64_t)3 << 23;
 constexpr int64_t kTwiceMaxN = (int64_t)5 << 23;  // (see plan_guess_read)
 
-// Flat steps on short vectors run in three launches (small_step) up to ARTOPK_OPT_SHORT_MAX_N elements, or three
-// quarters of that where the leader is found on the device and fewer than eight workers share the cost of that, and
-// up to 16384 kept.  Measured, us, ten or eight launches / three, at most one in a hundred kept, 786432, 1 M, 1.3 M and
-// 1.8 M elements: leader known, 2 workers 59/44 61/49 62/55 65/66, 4 workers 60/44 63/50 65/56 69/71, 8 workers 64/50
-// 68/58 78/63 86/77, 16 workers 80/61 87/70 99/80 119/106; variance rule, 2 workers 52/50 54/55 61/65 66/65, 4 workers
-// 61/56 65/62 74/73 85/85, 6 workers 73/64 76/72 85/83 104/103, 8 workers 77/69 87/82 97/93 117/116, 16 workers 114/94
-// 134/113 153/133 189/197.  More kept, 16384, 32768 and 65536: leader known, 8 workers, 65537 elements 71/38 81/44 -,
-// 524288 63/44 67/45 70/46, 1 M 69/59 69/60 75/60; variance rule, 8 workers, 58/44 61/51 -, 67/59 70/60 72/64, 87/83
-// 89/88 92/90; 2 workers on 1 M 54/57 55/63 58/66.  Both lines lie below the crossing, which differs by rule and workers.
-constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSmallMaxChunks * kTile, kSmallMaxK = 16384;
+// Flat steps on short vectors run in one launch (small_step) up to ARTOPK_OPT_SHORT_MAX_N elements, or three quarters
+// of that where the leader is found on the device and fewer than eight workers share the cost of that.  Measured, us, ten
+// or eight launches / one, one in a hundred kept, 786427, 1 M, 1.3 M and 1.8 M elements: leader known, 2 workers 59/25
+// 59/28 60/28 63/31, 4 workers 61/24 62/26 65/29 69/33, 8 workers 64/29 67/33 76/40 84/47, 16 workers 80/43 87/49 98/60
+// 117/72; variance rule, 2 workers 52/32 53/36 60/39 -, 4 workers 62/38 65/41 73/48 -, 8 workers 77/50 87/53 97/68
+// 117/75, 16 workers 114/77 133/79 152/105 189/113.  All of them lie below the crossing (an option says where the line
+// is, and its default stays).  Any number kept: a tenth, a third and all of 65537 x 2 63/21 71/21 90/23, of 1 M x 8 75/38
+// 90/39 118/40; variance rule, 65537 x 8 53/39 57/41 67/44, 1 M x 8 94/59 103/62 117/59.
+constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSmallMaxChunks * kTile;
 
 struct Scratch {
   // zeroed before every select: one kSegWords block per segment, then the look-back flags
@@ -81,7 +80,8 @@ struct Scratch {
   int64_t tilebuf_entries = 0;
   uint32_t* tile_cnt = nullptr;   // [max_n / kPassTile + 1] entries staged per tile
   uint32_t* sample_keys = nullptr;  // [16384 kGuessRun] keys of one vector's guess sample
-  SmallScratch small{};           // short vectors' steps: zero whenever no step is running
+  SmallScratch small{};           // short vectors' steps
+  size_t small_words = 0;         // of it, zero whenever no step is running
   SegDesc* table_dev = nullptr;   // [max_seg] segment descriptors
   uint32_t* chunk_map = nullptr;  // [kMaxChunks + max_seg] (segment << 16) | chunk, one entry per chunk of the layout
   uint32_t cap = 0;               // list capacity of a flat (one-segment) select
@@ -123,8 +123,7 @@ struct artopk_ctx {
   int64_t update_tiles_min_n = (int64_t)1 << 22;
   int stage_tiles = 1;  // guess route, one marking worker: the fused pass hands the marked elements on per tile
                         // (0 never, 1 for selections of one element in 256 or denser, 2 whenever a piece can hold a tile's share)
-  int64_t small_max_n = kSmallMaxN;  // flat steps of up to about this many elements run in three launches
-  bool small_off = false;  // a launch of such a step failed: its scratch may not be zero any more
+  int64_t small_max_n = kSmallMaxN;  // flat steps of up to about this many elements run in one launch
   void* slab = nullptr;
   Scratch s;
   // how the last step or selection ran (artopk_select_info)
@@ -460,7 +459,6 @@ SelParams make_params(const artopk_ctx* c, const Plan& pl, const PtrTable& tab, 
   p.n = n;
   p.hcopies = s.h_all;
   p.hcopy_stride = kSlotWords;
-  p.cand_off = nullptr;
   p.h_all = hist_from_pass ? s.h_all : nullptr;
   p.mask = nullptr;
   p.mask_stride = s.mask_stride;
@@ -1082,91 +1080,72 @@ int enqueue_topk_workers(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t 
   return ARTOPK_OK;
 }
 
-template <int STATS, int GT>
-void launch_small_pass_g(artopk_ctx* c, dim3 grid, const PtrTable& g, const PtrTable& r, int64_t n, const SelParams& p,
-                         const LeaderArgs& la, int leader, int32_t* leader_out) {
-  hipLaunchKernelGGL((k_small_pass<STATS, GT>), grid, dim3(1024), 0, c->stream, g, r, n, c->s.small, c->s.partials, p, la,
-                     (int32_t)leader, c->s.leader_dev, leader_out);
-}
-
-template <int STATS>
-void launch_small_pass(artopk_ctx* c, dim3 grid, const PtrTable& g, const PtrTable& r, int64_t n, const SelParams& p,
-                       const LeaderArgs& la, int leader, int32_t* leader_out) {
+template <bool STATS, int T>
+void launch_small_t(artopk_ctx* c, const SmallStep& a) {
+  const dim3 grid((unsigned)(a.nchunks * a.groups)), block(T);
   if (c->g_type == ARTOPK_G_BF16)
-    launch_small_pass_g<STATS, kGBF16>(c, grid, g, r, n, p, la, leader, leader_out);
+    hipLaunchKernelGGL((k_small_step<STATS, kGBF16, T>), grid, block, 0, c->stream, a);
   else if (c->g_type == ARTOPK_G_F16)
-    launch_small_pass_g<STATS, kGF16>(c, grid, g, r, n, p, la, leader, leader_out);
+    hipLaunchKernelGGL((k_small_step<STATS, kGF16, T>), grid, block, 0, c->stream, a);
   else
-    launch_small_pass_g<STATS, kGF32>(c, grid, g, r, n, p, la, leader, leader_out);
+    hipLaunchKernelGGL((k_small_step<STATS, kGF32, T>), grid, block, 0, c->stream, a);
 }
 
-// A flat step on a short vector in three launches.  leader >= 0: known up front; else it comes from the
-// statistics (stats 1 or 2) or is in leader_dev already (stats 0).
+template <bool STATS>
+void launch_small(artopk_ctx* c, const SmallStep& a, int threads) {
+  if (threads == 512) return launch_small_t<STATS, 512>(c, a);
+  return launch_small_t<STATS, 1024>(c, a);
+}
+
+// Groups of workers that share out the first part of a short step: as many blocks as there are compute units.  Measured,
+// us, variance rule, 1 / 2 / 4 / 8 / 16 groups: 65537 elements x 4 workers 29/26/23, x 8 39/32/28/25, x 16 61/46/35/31/30,
+// x 64 195/127/84/63/62; 262143 x 8 45/36/32/33, x 16 69/52/44/45/52, x 64 232/152/122/118/128; 500009 x 8 45/42/49/57, x
+// 16 70/65/68/79; 786427 x 8 49/59, x 16 77/94.  With a leader known up front the others' sums are formed while the block
+// waits, unless they are many: 65537 x 8 22/-/23/22, x 16 27/-/28/26/26, x 64 64/-/60/45/47; 100003 x 64 87/-/63/55/56;
+// 200003 x 64 96/-/103/86/87; 262143 x 16 36/-/38/40/45.
+int32_t small_groups(int32_t w, int64_t n, int32_t nchunks, bool known) {
+  if (known && (w <= 16 || n > ((int64_t)1 << 17))) return 1;
+  return std::max<int32_t>(1, std::min<int32_t>(w, kSmallMaxUnits / nchunks));
+}
+
+// A flat step on a short vector in one launch.  leader >= 0: known up front; else it comes from the statistics
+// (stats 1 or 2) or is in leader_dev already (stats 0).
 int small_step(artopk_ctx* ctx, const PtrTable& gt, const PtrTable& rt, int32_t w, int64_t n, int64_t k, int stats,
                int leader, int32_t* leader_out, double* var_out, int32_t* idx_out, float* vals_out, float* sum_out,
                float* update_out) {
   Scratch& s = ctx->s;
-  hipStream_t st = ctx->stream;
-  const bool known = leader >= 0;
-  const int32_t workers = known ? 1 : w;
-  Plan pl = flat_plan(ctx, n, k, known ? leader : -1);
-  pl.desc[0].geom.chunk0 = 0;
-  pl.desc[0].geom.chunk_elems = kTile;
-  pl.desc[0].geom.nchunks = (int32_t)((n + kTile - 1) / kTile);
-  pl.desc[0].hreps = kSmallReps;
-  SmallScratch ss = s.small;
-  ss.workers = workers;
-  SelParams p = make_params(ctx, pl, rt, n, idx_out, nullptr, known ? 0 : 1, false);
-  p.hcopies = ss.hist;
-  p.hcopy_stride = (int64_t)kSmallReps * kHistBins;
-  p.cand_off = ss.cand_off;
-  LeaderArgs la{};
-  if (stats != 0) {
-    la.partials = s.partials;
-    la.w_count = (int)w;
-    la.nblk = pl.desc[0].geom.nchunks;
-    la.n = n;
-    la.var_scratch = s.var_scratch;
-    la.var_out = var_out;
-    la.leader_dev = s.leader_dev;
-    la.leader_out = leader_out;
-  }
-  PtrTable g1 = gt, r1 = rt;
-  if (known) {
-    g1.p[0] = gt.p[leader];
-    r1.p[0] = rt.p[leader];
-  }
-  ctx->small_off = true;  // (until the kernel that leaves the scratch zero is enqueued)
-  const dim3 grid((unsigned)pl.desc[0].geom.nchunks, (unsigned)workers);
+  const int threads = n <= ((int64_t)1 << 20) ? 512 : 1024;
+  SmallStep a{};
+  a.g = gt;
+  a.res = rt;
+  a.n = n;
+  a.k = (uint32_t)k;
+  a.w_count = w;
+  a.leader = leader;
+  a.nchunks = (int32_t)((n + 8 * threads - 1) / (8 * threads));
+  a.reps = a.nchunks <= 128 ? 1 : 2;
+  a.groups = small_groups(w, n, a.nchunks, leader >= 0);
+  a.raw_stats = stats == 2;
+  a.list_cap = s.cap < (uint64_t)n ? s.cap : (uint32_t)n;
+  a.ss = s.small;
+  a.partials = s.partials;
+  a.st = reinterpret_cast<SelState*>(s.zero_base + kSegState);
+  a.err = s.err_dev;
+  a.leader_dev = s.leader_dev;
+  a.leader_out = (leader >= 0 || stats != 0) ? leader_out : nullptr;
+  a.var_out = var_out;
+  a.idx_out = idx_out;
+  a.vals = vals_out;
+  a.sum_out = sum_out;
+  a.update = update_out;
   prof_dom(ctx, false);
   if (stats == 0)
-    launch_small_pass<0>(ctx, grid, g1, r1, n, p, la, leader, leader_out);
-  else if (stats == 1)
-    launch_small_pass<1>(ctx, grid, g1, r1, n, p, la, -1, nullptr);
+    launch_small<false>(ctx, a, threads);
   else
-    launch_small_pass<2>(ctx, grid, g1, r1, n, p, la, -1, nullptr);
+    launch_small<true>(ctx, a, threads);
   HIP_TRY(ctx, hipGetLastError());
   prof_dom(ctx, true);
-  prof_mark(ctx, 1);
-  hipLaunchKernelGGL(k_small_select, dim3((unsigned)pl.desc[0].geom.nchunks), dim3(1024), 0, st, p, ss);
-  HIP_TRY(ctx, hipGetLastError());
-  ctx->small_off = false;
-  prof_mark(ctx, 2);
-  const dim3 tiles((unsigned)((n + kSmallTile - 1) / kSmallTile));
-  if (!known)
-    hipLaunchKernelGGL(k_small_gather, tiles, dim3(256), 0, st, p, ss, rt, (int)w, k, vals_out, sum_out, update_out);
-  else if (ctx->g_type == ARTOPK_G_BF16)
-    hipLaunchKernelGGL(k_small_rest<kGBF16>, tiles, dim3(256), 0, st, p, ss, gt, rt, (int)w, leader, k, vals_out, sum_out,
-                       update_out);
-  else if (ctx->g_type == ARTOPK_G_F16)
-    hipLaunchKernelGGL(k_small_rest<kGF16>, tiles, dim3(256), 0, st, p, ss, gt, rt, (int)w, leader, k, vals_out, sum_out,
-                       update_out);
-  else
-    hipLaunchKernelGGL(k_small_rest<kGF32>, tiles, dim3(256), 0, st, p, ss, gt, rt, (int)w, leader, k, vals_out, sum_out,
-                       update_out);
-  HIP_TRY(ctx, hipGetLastError());
-  prof_mark(ctx, 3);
-  prof_mark(ctx, 4);
+  for (int mark = 1; mark <= 4; ++mark) prof_mark(ctx, mark);
   return ARTOPK_OK;
 }
 
@@ -1174,13 +1153,18 @@ int small_step(artopk_ctx* ctx, const PtrTable& gt, const PtrTable& rt, int32_t 
 
 namespace {
 
+// Zeroes the part of the short steps' scratch that is zero between steps.
+void clear_small(artopk_ctx* c) {
+  hipLaunchKernelGGL(k_fill_zero, dim3(64), dim3(256), 0, c->stream, c->s.small.hist, c->s.small_words, (uint32_t*)nullptr,
+                     (size_t)0, (uint32_t*)nullptr, (size_t)0, 0, (int32_t*)nullptr, (int32_t*)nullptr);
+}
+
 // Where everything lies in the one allocation of a context.
 struct Layout {
   uint32_t cap = 0;
   int64_t list_entries = 0, max_tiles = 0, mask_stride = 0, tilebuf_entries = 0;
   int32_t blocks = 0;  // scratch blocks: one per segment, or per vector of a batch
   size_t o_hall = 0, o_mask = 0, o_zero = 0, o_S = 0, o_coff = 0, o_part = 0, o_var = 0, o_leader = 0, o_err = 0, o_counter = 0, o_list = 0, o_vals = 0, o_rows = 0, o_table = 0, o_cmap = 0, o_tstart = 0, o_tbuf = 0, o_tcnt = 0, o_sample = 0, o_small = 0;
-  size_t small_many = 0;   // words of SmallScratch::ctr and ::many
   size_t small_words = 0;  // words of the short vectors' scratch that have to be zero between steps
   size_t total = 0;
 };
@@ -1243,11 +1227,14 @@ Layout scratch_layout(int32_t max_w, int64_t max_n, int64_t max_k, int32_t max_s
   L.o_tbuf = take((size_t)L.tilebuf_entries * sizeof(uint2));
   L.o_tcnt = take((size_t)(max_tiles_pass + 1) * sizeof(uint32_t));
   L.o_sample = take((size_t)16384 * kGuessRun * sizeof(uint32_t));
-  L.small_words = (size_t)max_w * kSmallReps * kHistBins + kSmallCtr + kManyMid;
+  // (hist, ctr, claim, dig1 and dig2 have to be zero between steps)
+  L.small_words = (size_t)(max_w + 1) * kSmallReps * kHistBins + kSmallCtr + kSmallMaxUnits + 2 * kSmallReps * 128;
   const int64_t small_n = max_n < kSmallMaxNLimit ? max_n : kSmallMaxNLimit;
-  L.small_many = kSmallCtr + kManyTail + (size_t)((small_n + kTile - 1) / kTile) * (kTile / kSmallTile) * 128;
-  L.o_small = take(((size_t)max_w * kSmallReps * kHistBins + L.small_many + (2 * 16 + 2 + 2) * kSmallMaxChunks +
-                    (size_t)small_n) * sizeof(uint32_t));
+  size_t small_bytes = (L.small_words + (size_t)kSmallMaxChunks * 129) * sizeof(uint32_t);
+  // (callers plan with the size that the header states)
+  const size_t stated = (size_t)max_w * ((size_t)128 << 10) + (size_t)(4.5 * (double)small_n) + ((size_t)160 << 10);
+  if (small_bytes < stated) small_bytes = stated;
+  L.o_small = take(small_bytes);
   L.total = off;
   return L;
 }
@@ -1320,20 +1307,19 @@ int artopk_create(artopk_ctx** out, int32_t max_w, int64_t max_n, int64_t max_k,
   uint32_t* small = reinterpret_cast<uint32_t*>(base + L.o_small);
   s.small.hist = small;
   s.small.ctr = small + (size_t)max_w * kSmallReps * kHistBins;
-  s.small.many = s.small.ctr + kSmallCtr;
-  s.small.low_bits = reinterpret_cast<uint64_t*>(s.small.ctr + L.small_many);
-  s.small.before = reinterpret_cast<uint2*>(s.small.low_bits + 16 * kSmallMaxChunks);
-  s.small.cand_off = reinterpret_cast<uint32_t*>(s.small.before + kSmallMaxChunks);
-  s.small.sure = s.small.cand_off + kSmallMaxChunks;
-  s.small.cand = s.small.sure + kSmallMaxChunks;
+  s.small.claim = s.small.ctr + kSmallCtr;
+  s.small.dig1 = s.small.claim + kSmallMaxUnits;
+  s.small.dig2 = s.small.dig1 + (size_t)kSmallReps * kHistBins;
+  s.small.above = s.small.dig2 + 2 * kSmallReps * 128;
+  s.small.rows = s.small.above + kSmallMaxChunks;
+  s.small_words = L.small_words;
 
   // leader, error word and step counter start at zero (stream-ordered before any later call)
   hipLaunchKernelGGL(k_fill_zero, dim3(1), dim3(256), 0, c->stream,
                      reinterpret_cast<uint32_t*>(s.leader_dev), (size_t)1, s.err_dev, (size_t)1,
                      reinterpret_cast<uint32_t*>(s.counter_dev), (size_t)2, 0, (int32_t*)nullptr,
                      (int32_t*)nullptr);
-  hipLaunchKernelGGL(k_fill_zero, dim3(64), dim3(256), 0, c->stream, small, L.small_words, (uint32_t*)nullptr, (size_t)0,
-                     (uint32_t*)nullptr, (size_t)0, 0, (int32_t*)nullptr, (int32_t*)nullptr);
+  clear_small(c);
   if (hipGetLastError() != hipSuccess) {
     (void)hipFree(c->slab);
     delete c;
@@ -1366,6 +1352,9 @@ int artopk_status(artopk_ctx* ctx) {
   HIP_TRY(ctx, hipMemcpy(&err, ctx->s.err_dev, sizeof(err), hipMemcpyDeviceToHost));
   if (err) {
     uint32_t zero = 0;
+    clear_small(ctx);  // (a short step may have ended before its scratch was zero again)
+    HIP_TRY(ctx, hipGetLastError());
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     HIP_TRY(ctx, hipMemcpy(ctx->s.err_dev, &zero, sizeof(zero), hipMemcpyHostToDevice));
     return fail(ctx, ARTOPK_ESTATE, "device error word 0x%x (1 = histogram/count mismatch, 2 = scan wait expired, 4 = kernel sequence, 8 = index out of range)", err);
   }
@@ -1825,7 +1814,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   }
 
   const int64_t short_n = (device_leader && w < 8) ? ctx->small_max_n / 4 * 3 : ctx->small_max_n;
-  if (!segmented && !gp.on && n <= short_n && k <= kSmallMaxK && !ctx->small_off && (leader_first || device_leader)) {
+  if (!segmented && !gp.on && n <= short_n && (leader_first || device_leader)) {
     ctx->lvl1_a = 0;
     ctx->lvl1_b = 1;
     prof_begin(ctx);

@@ -42,7 +42,7 @@
 //   k_gather         vals / ordered sum / residual zeroing at the k indices
 //   k_zero_at        residual zeroing alone
 //   k_update_fill    dense update = zeros + k scattered sums, written once
-//   k_small_pass, k_small_select, k_small_rest / k_small_gather   a whole step on a short vector
+//   k_small_step     a whole step on a short vector
 //   k_update_tiles   the same for long, sparsely kept vectors: zeros streamed tile
 //                    by tile, the sums stored behind them
 //
@@ -114,7 +114,7 @@ struct SelState {
   uint32_t use_mask;       // the list is written from the survivor bit mask of the fused pass
   uint32_t need_full;      // the guessed bound did not work out: the top-digit histogram of every key is needed
   uint32_t list_lo;        // with use_mask: the list holds every key >= list_lo (<= lo)
-  uint32_t many;           // a short vector's selection counted its candidates per tile and wrote no list
+  uint32_t many;           // a short vector's threshold shares its top digit with many others (small_few)
   uint32_t pad[4];
 };
 
@@ -164,7 +164,6 @@ struct SelParams {
   int64_t n;               // length of the vector
   uint32_t* hcopies;       // copies of top-digit histograms that k_hist0 fills (h_all's memory, when no pass fills that)
   int64_t hcopy_stride;    // their words per vector
-  uint32_t* cand_off;      // k_pick0's body leaves the number of candidates in front of every chunk here, or nullptr
   const uint32_t* h_all;   // [workers][kSlotWords] whole-vector histograms from the fused pass, or nullptr
   const uint64_t* mask;    // [workers][mask_stride] survivor bit masks from the fused pass, or nullptr
   int64_t mask_stride;     // 64-bit words per worker
@@ -248,6 +247,12 @@ template <typename V>
 __device__ __forceinline__ void store_through(V* p, V v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Loads of what other blocks of the launch have stored so, or added up.  (An acquire fence and ordinary loads instead
+// invalidate the XCD's cache once for every wave: 16 us a wait with 256 blocks of 512 threads.)
+template <typename V>
+__device__ __forceinline__ V load_through(const V* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -327,7 +332,7 @@ __device__ __forceinline__ double wave_allsum(double v) {
 // Adds up the threads' sums of a block of T threads (all of them call it) and thread 0 writes
 // the block's (n, mean, M2) to partials[w][.][b] (nblk blocks per worker).  Thread 0 must be a
 // thread that saw a value whenever any thread of the block did (it owns the block's first group).
-// THROUGH: for a reader in the same launch (see last_block).
+// THROUGH: for a reader in the same launch.
 template <int T, bool THROUGH = false>
 __device__ __forceinline__ void block_moments(const VarAcc& acc, double* __restrict__ partials, int w, int nblk,
                                               int b) {
@@ -376,21 +381,24 @@ __device__ __forceinline__ void block_moments(const VarAcc& acc, double* __restr
 
 // Variance of worker w from its blocks' partials; the 64 lanes of one wave call it, every lane
 // returns the variance (population: M2 / N).
+// THROUGH: written in the same launch.
+template <bool THROUGH = false>
 __device__ __forceinline__ double wave_variance(const double* __restrict__ partials, int w, int nblk) {
+  auto get = [](const double* q) { return THROUGH ? load_through(q) : *q; };
   const int lane = threadIdx.x & 63;
   const double* __restrict__ pn = partials + (size_t)w * 3 * nblk;
   const double* __restrict__ pm = pn + nblk;
   const double* __restrict__ pq = pm + nblk;
-  const double r = pm[0];
+  const double r = get(pm);
   double n = 0.0, a = 0.0, bq = 0.0;
   int b = lane;
   for (; b + 448 < nblk; b += 512) {  // eight blocks' triples in flight per lane
     double nb[8], mb[8], qb[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      nb[j] = pn[b + 64 * j];
-      mb[j] = pm[b + 64 * j];
-      qb[j] = pq[b + 64 * j];
+      nb[j] = get(pn + b + 64 * j);
+      mb[j] = get(pm + b + 64 * j);
+      qb[j] = get(pq + b + 64 * j);
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -401,10 +409,10 @@ __device__ __forceinline__ double wave_variance(const double* __restrict__ parti
     }
   }
   for (; b < nblk; b += 64) {
-    const double nb = pn[b], d = pm[b] - r;
+    const double nb = get(pn + b), d = get(pm + b) - r, q = get(pq + b);
     n += nb;
     a += nb * d;
-    bq += pq[b] + nb * d * d;
+    bq += q + nb * d * d;
   }
   n = wave_allsum(n);
   a = wave_allsum(a);
@@ -512,8 +520,7 @@ __device__ __forceinline__ uint32_t block_prefix_incl(uint32_t v, uint32_t* wtot
 // Adds the 4096-bin LDS histogram `lh` of a T-thread block to total[0..4096)
 // and writes its suffix sums to dst[0..4096).  `red` is T words of LDS.  All
 // threads of the block must call it after their last histogram update.
-// THROUGH: for a reader in the same launch (see last_block).
-template <int T, bool THROUGH = false>
+template <int T>
 __device__ __forceinline__ void flush_suffix_hist(uint32_t* lh, uint32_t* red, uint32_t* __restrict__ dst,
                                                   uint32_t* __restrict__ total) {
   constexpr int BPT = kHistBins / T;  // consecutive bins per thread (a multiple of 4)
@@ -543,13 +550,7 @@ __device__ __forceinline__ void flush_suffix_hist(uint32_t* lh, uint32_t* red, u
     q.y = v[4 * j + 1] + carry;
     q.z = v[4 * j + 2] + carry;
     q.w = v[4 * j + 3] + carry;
-    if (THROUGH) {
-      uint64_t* d2 = reinterpret_cast<uint64_t*>(dst) + 2 * ((BPT / 4) * t + j);
-      store_through(d2, ((uint64_t)q.y << 32) | q.x);
-      store_through(d2 + 1, ((uint64_t)q.w << 32) | q.z);
-    } else {
-      reinterpret_cast<uint4*>(dst)[(BPT / 4) * t + j] = q;
-    }
+    reinterpret_cast<uint4*>(dst)[(BPT / 4) * t + j] = q;
   }
 }
 
@@ -1751,11 +1752,6 @@ __device__ __forceinline__ void pick0_body(const SelParams& p, const LeaderArgs&
   const uint32_t mine = (t < nchunks) ? sv.S[(size_t)t * kHistBins + b0] : 0u;
   const uint32_t upto = block_prefix_incl<1024>(mine, part);
   if (t < nchunks) sv.chunk_off[t] = upto - mine;
-  if (p.cand_off != nullptr) {
-    const uint32_t above = (t < nchunks && b0 + 1 < kHistBins) ? sv.S[(size_t)t * kHistBins + b0 + 1] : 0u;
-    const uint32_t cand_upto = block_prefix_incl<1024>(mine - above, part);
-    if (t < nchunks) p.cand_off[t] = cand_upto - (mine - above);
-  }
 }
 
 __global__ void __launch_bounds__(1024)
@@ -3788,836 +3784,638 @@ k_sum_update(const float* __restrict__ vals, int w_count, int64_t n, const int32
 }
 
 // ---------------------------------------------------------------------------
-// Short vectors: a whole step in three launches (k_small_pass, k_small_select and k_small_rest or
-// k_small_gather).  Ten launches, each a few microseconds of latency, were all that such a step took: 65537
-// elements x 2 workers 52 us, now 31; 1 M x 4 61 us, now 54 (28 us of them in k_small_select and its
-// last block; see small_step's rule for other sizes).  What a single block did in a launch of its own is done by the last block to finish of
-// the launch before it, and nothing has to be cleared first: the scratch of this route (SmallScratch) is
-// zero whenever no step is running, because k_small_select leaves it so.
+// k_small_step : a whole flat step on a short vector in one launch.  Bound by latency: three launches, each a chain of
+// trips to memory between a start and an end, took 30.6 us on 65537 elements x 2 workers and 55 on 1 M x 4; here the
+// blocks wait for each other in between, which takes a microsecond, and the same steps take 19.9 and 27.5.
+//   A block has one chunk of 8 T elements, of every worker, and takes it from the gradients to the outputs:
+//     acc = g + residual, the counts of the leader's (every worker's, where the leader comes from the data) top digits;
+//     all blocks are through with that: threshold digit (every block picks it for itself), the candidates' second digits;
+//     all are through: second digit of the threshold, the entries it leaves, per chunk, by their last seven bits;
+//     all are through: threshold, how many are kept in front of the chunk, and the outputs of the chunk.
+// So a block reads what it wrote itself, except for counts, which go past the XCD's cache (load_through).  With the
+// leader known up front the other workers' sums are formed while the block waits.  Many workers of few chunks are shared
+// out among further blocks in the first part (small_step's rule); their sums then go past the cache, too.  However many values share the
+// threshold's digits, the work is the same (1 M x 2 between 1 and 1.01, one in a hundred kept: 73 us in three launches).
+//   Nothing depends on how many blocks run at a time: a block that has looked for the others' first counts for a while
+// takes on the chunks that nobody has (a chunk bears the number of the step in which it was taken; a block that comes
+// late finds its own taken and leaves), and from then on every chunk belongs to a block that runs.  Everything that is
+// counted up is zero again when the step ends, or, of two sets in turn, when the next but one begins.
+//   8 T is 4096 up to 2^20 elements and 8192 beyond: at most 256 blocks (us, 2048 / 4096 / 8192: 65537 x 2 21/20/-, 262143
+// x 2 25/21/-; variance rule, the best groups of each, 65537 x 8 27/25/30, 262143 x 8 39/32/35, 500009 x 16 77/65/66, 1 M
+// x 16 -/79/100).  One copy of a histogram up to 128 chunks, two beyond (one / two / four: 524288 x 4 22.8/24.7/25.0, 1 M
+// x 4 28.2/26.6/29.7, 1 M x 8 variance rule 65/54.6/55.6): each more is another 16 KB that every block reads twice, each
+// fewer more additions to one place.
 // ---------------------------------------------------------------------------
-constexpr int kSmallReps = 8;     // copies of a worker's top-digit histogram
-constexpr int kSmallMaxChunks = 256;  // chunks of kTile elements
-constexpr int kSmallTile = 1024;  // elements per block of the last launch: 256 threads x one float4 group
-// More candidates than this are counted by all blocks of k_small_select together: a block alone takes about 0.55 us for
-// a thousand, all together 11 us more than it for none on 9 chunks and 23 more on 128.  Whole steps, us, one block
-// against all: 65537 elements x 2 workers, 8000 candidates 42/42, 12000 46/43, 24000 60/44; 262144, 12000 44/46, 16000
-// 48/46, 24000 54/47; 1 M, 24000 61/68, 32000 66/68, 48000 74/69.  Variance rule, 8 workers: 65537, 12000 53/52; 262144,
-// 16000 59/60, 24000 66/60; 1 M, 32000 109/112, 48000 114/112.
-__device__ __forceinline__ uint32_t small_few(int nchunks) { return 10240u + 240u * (uint32_t)nchunks; }
-constexpr int kSmallHelpSpins = 256;  // looks at the phase word before a waiting block gives up: 100 us or so
-constexpr int kSmallLine = 32;  // words
-// SmallScratch::ctr: blocks done with the first and with the second launch; with many candidates, chunks whose last
-// digits are counted and what is published, 4 times the step's number and kPhaseCount or kPhaseOver; steps of that
-// kind so far (the latter two are not reset).
-constexpr int kCtrPass = 0, kCtrSelect = kSmallLine, kCtrDone = 2 * kSmallLine, kCtrPhase = 3 * kSmallLine,
-              kCtrStep = 4 * kSmallLine, kSmallCtr = 5 * kSmallLine;
-constexpr uint32_t kPhaseNone = 0u, kPhaseCount = 1u, kPhaseOver = 2u;
-
-// SmallScratch::many, words (one pointer: each more of them cost every step's k_small_select a register pair too many):
-constexpr int kSmallMaxTiles = kSmallMaxChunks * (kTile / kSmallTile);
-constexpr int kManyDig1 = 0,                                            // [kSmallReps][kHistBins] second digits of the candidates
-              kManyDig2 = kManyDig1 + kSmallReps * kHistBins,           // [kSmallReps][128] last digits of those that are left then
-              kManyClaim = kManyDig2 + kSmallReps * 128,                // [kSmallMaxChunks] the last step in which somebody took
-                                                                        // the chunk's last digits on
-              kManyMid = kManyClaim + kSmallMaxChunks,                  // the state after the second digit
-              kManyTileCnt = kManyMid + 64,                             // [tiles] uint2: keys above the candidates, candidates
-              kManyTileBefore = kManyTileCnt + 2 * kSmallMaxTiles,      // [tiles] uint2: keys above the threshold, and at it,
-                                                                        // in front of every tile
-              kManyTail = kManyTileBefore + 2 * kSmallMaxTiles;         // [tiles][128] the candidates that are left, by last
-                                                                        // digit: that or a later one
-static_assert(sizeof(SelState) <= 64 * 4 && kManyTileCnt % 4 == 0, "the state fits, rows are aligned");
+constexpr int kSmallReps = 2;         // copies of a histogram, at most
+constexpr int kSmallMaxChunks = 256;  // chunks, at most
+constexpr int kSmallMaxUnits = 256;   // chunks x groups of workers, at most
+constexpr int kSmallLine = 32;        // words between counters
+constexpr int kSmallArrive = 8;       // words a wait counts its blocks on
+constexpr int kSmallHelpSpins = 256;  // looks at the other blocks' counts before looking for chunks that nobody has
+// SmallScratch::ctr, words: the step's number; chunks that other blocks took on, and blocks that came late, of this
+// step; two sets of three waits' counters
+constexpr int kCtrStep = 0, kCtrHelped = kSmallLine, kCtrLate = 2 * kSmallLine, kCtrArrive = 3 * kSmallLine,
+              kCtrSet = 3 * kSmallArrive * kSmallLine, kSmallCtr = kCtrArrive + 2 * kCtrSet;
+// What select_info reports as many candidates.
+__host__ __device__ constexpr uint32_t small_few(int64_t n) { return 10240u + 240u * (uint32_t)((n + kTile - 1) / kTile); }
 
 struct SmallScratch {
-  uint32_t* hist;        // [workers][kSmallReps][kHistBins]
-  uint32_t* ctr;         // counters, each in a cache line of its own: kCtrPass ..
-  uint32_t* many;        // kMany.. below (up to kManyMid zero at first)
-  // (these are written before they are read in every step)
-  uint32_t* cand_off;    // [kSmallMaxChunks] SelParams::cand_off
-  uint32_t* sure;        // [kSmallMaxChunks] keys above the threshold digit in every chunk
-  uint64_t* low_bits;    // [kSmallMaxChunks * 16] every wave's largest low bits of a candidate, and of their complement
-  uint32_t* cand;        // [2^21] the candidates: low 19 bits, chunk << 19
-  uint2* before;         // [kSmallMaxChunks] list entries above the threshold, and at it, in front of every chunk
-  int32_t workers;       // slots of hist in use
+  // zero at first
+  uint32_t* hist;   // [workers][kSmallReps][kHistBins] top digits
+  uint32_t* ctr;    // [kSmallCtr]
+  uint32_t* claim;  // [kSmallMaxUnits] the step in which somebody took the chunk of the group, plus one
+  uint32_t* dig1;   // [kSmallReps][kHistBins] second digits of the candidates
+  uint32_t* dig2;   // [2][kSmallReps][128] last digits of those that are left then
+  // written before they are read in every step
+  uint32_t* above;  // [kSmallMaxChunks] a chunk's keys above those
+  uint32_t* rows;   // [kSmallMaxChunks][128] a chunk's of those: with that last digit or a higher one
 };
 
-// Whether the calling block is the last of `total` to get here; all its threads call it.  What the other blocks
-// wrote before with store_through or atomics is then visible to it.  (Ordinary stores would need a release fence
-// in every block, which writes the XCD's whole cache back: 54 instead of 14 us for k_small_pass on 1 M elements.)
-__device__ __forceinline__ bool last_block(uint32_t* ctr, uint32_t total) {
-  __shared__ int last_sh;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores and atomics have reached memory
-  __syncthreads();
-  if (threadIdx.x == 0)
-    last_sh = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1u ? 1 : 0;
-  __syncthreads();
-  const bool last = last_sh != 0;
-  if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  return last;
-}
+struct SmallStep {
+  PtrTable g, res;
+  int64_t n;
+  uint32_t k;
+  int32_t w_count;
+  int32_t leader;  // -1: from the statistics, or in leader_dev
+  int32_t nchunks, reps;
+  int32_t groups;     // of workers: each has its blocks in the first part (of a known leader: itself, and the others)
+  int32_t raw_stats;  // the statistics are the raw gradient's
+  uint32_t list_cap;  // (what the state reports of the general selection's list)
+  SmallScratch ss;
+  double* partials;
+  SelState* st;
+  uint32_t* err;
+  int32_t* leader_dev;
+  int32_t* leader_out;
+  double* var_out;
+  int32_t* idx_out;
+  float* vals;
+  float* sum_out;
+  float* update;
+};
 
-// acc = g + residual (in place), per-chunk suffix histograms and whole-vector histograms of every worker of the
-// tables, variance partials (STATS as in k_pass_a); the last block takes the leader (la) and the threshold digit.
-// grid = (chunks of kTile elements, workers), block = 1024.  leader >= 0: known to the host, passed on.
-template <int STATS, int GT>
-__global__ void __launch_bounds__(1024)
-k_small_pass(PtrTable g, PtrTable res, int64_t n, SmallScratch ss, double* __restrict__ partials, SelParams p,
-             LeaderArgs la, int32_t leader, int32_t* __restrict__ leader_dev, int32_t* __restrict__ leader_out) {
-  constexpr int T = 1024, U = 2;
-  static_assert(T * U * 4 == kTile, "a chunk is one tile");
-  __shared__ __attribute__((aligned(16))) uint32_t lh[kHistBins];
-  __shared__ uint32_t red_u[T];
-  const int w = blockIdx.y, c = blockIdx.x, nblk = gridDim.x;
-  const int tid = threadIdx.x;
-  const float* __restrict__ gp = g.p[w];
-  float* __restrict__ rp = res.p[w];
-  if (leader >= 0 && c == 0 && w == 0 && tid == 0) {
-    *leader_dev = leader;
-    if (leader_out) *leader_out = leader;
-  }
-  for (int b = tid; b < kHistBins; b += T) lh[b] = 0u;
-  const int64_t q0 = (int64_t)c * (kTile / 4) + tid, q_end = n >> 2;
-  VarAcc va;
-  v4f a[U], b[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {  // (groups behind the vector re-read its last one, unused)
-    const int64_t q = q0 + u * T < q_end ? q0 + u * T : q_end - 1;
-    if (q_end > 0) {
-      a[u] = load4g<false, GT>(gp, 4 * q);
-      b[u] = load4<false>(rp + 4 * q);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (q0 + u * T < q_end) {
-      v4f v;
-      v.x = a[u].x + b[u].x;
-      v.y = a[u].y + b[u].y;
-      v.z = a[u].z + b[u].z;
-      v.w = a[u].w + b[u].w;
-      store4<false>(rp + 4 * (q0 + u * T), v);
-      if (STATS) {
-        va.seed4(STATS == 2 ? a[u] : v);
-        va.add4(STATS == 2 ? a[u] : v);
-      }
-      atomicAdd(&lh[(__float_as_uint(v.x) & kKeyMask) >> 19], 1u);
-      atomicAdd(&lh[(__float_as_uint(v.y) & kKeyMask) >> 19], 1u);
-      atomicAdd(&lh[(__float_as_uint(v.z) & kKeyMask) >> 19], 1u);
-      atomicAdd(&lh[(__float_as_uint(v.w) & kKeyMask) >> 19], 1u);
-    }
-  }
-  if (c == nblk - 1) {  // the n mod 4 last elements
-    const int64_t j = q_end * 4 + tid;
-    if (j < n) {
-      const float gj = load1g<GT>(gp, j);
-      const float v = gj + rp[j];
-      rp[j] = v;
-      if (STATS) {
-        va.seed1(STATS == 2 ? gj : v);
-        va.add1(STATS == 2 ? gj : v);
-      }
-      atomicAdd(&lh[(__float_as_uint(v) & kKeyMask) >> 19], 1u);
-    }
-  }
-  if (STATS) block_moments<T, true>(va, partials, w, nblk, c);
-  flush_suffix_hist<T, true>(lh, red_u, p.S + ((size_t)w * kMaxChunks + (size_t)c) * kHistBins,
-                       ss.hist + ((size_t)w * kSmallReps + (size_t)(c % kSmallReps)) * kHistBins);
-  if (last_block(&ss.ctr[kCtrPass], gridDim.x * gridDim.y)) pick0_body(p, la, 0, red_u);
-}
-
-// Eight consecutive elements of x from j0 on (0 behind the vector's end).
-__device__ __forceinline__ void small_load8(const float* __restrict__ x, int64_t n, int64_t j0, uint32_t (&raw)[8]) {
+// The elements [j0, j0 + 8) of g and of r (those behind the vector unspecified).
+template <int GT>
+__device__ __forceinline__ void small_fetch(const float* __restrict__ g, const float* __restrict__ r, int64_t n,
+                                            int64_t j0, v4f (&a)[2], v4f (&b)[2]) {
   if (j0 + 8 <= n) {
-    const uint4 a = reinterpret_cast<const uint4*>(x + j0)[0], b = reinterpret_cast<const uint4*>(x + j0)[1];
-    raw[0] = a.x, raw[1] = a.y, raw[2] = a.z, raw[3] = a.w;
-    raw[4] = b.x, raw[5] = b.y, raw[6] = b.z, raw[7] = b.w;
-  } else {
+    a[0] = load4g<false, GT>(g, j0);
+    a[1] = load4g<false, GT>(g, j0 + 4);
+    b[0] = load4<false>(r + j0);
+    b[1] = load4<false>(r + j0 + 4);
+  } else if (j0 < n) {  // one thread of the vector's (behind its end the last element again, unused)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) raw[e] = j0 + e < n ? __float_as_uint(x[j0 + e]) : 0u;
-  }
-}
-
-// Clears the histograms that k_small_pass filled, the calling block its share of them.
-__device__ __forceinline__ void small_clear(const SmallScratch& ss) {
-  uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.hist);
-  const size_t words4 = (size_t)ss.workers * kSmallReps * kHistBins / 4;
-  for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < words4; i += (size_t)gridDim.x * 1024)
-    z[i] = make_uint4(0u, 0u, 0u, 0u);
-}
-
-// k_small_select's work where many values share the threshold's top digit (magnitudes within 6 % of each other): the
-// candidates are then most of the vector, and one block walking them took up to 1.2 ms.  With more than small_few of
-// them every block counts its own by their second digit; the last block to finish with that picks
-// the digit and publishes it, and the chunks are then counted by the last digit.  A block that is not the last looks
-// out for the published digit for a while, takes its own chunk on and leaves; the one that published it goes on with
-// the chunks that nobody has taken on, so nothing depends on how many others still run, and whoever finishes the last
-// chunk picks the threshold and clears what this used (a chunk that has been taken on bears the step's number, so a
-// block that comes late touches nothing).  No list is written then: everything is counted per tile of the next
-// launch, which reads the vector again.
-//   Steps that keep one in a hundred, us, ten launches / one block / all blocks: 1 M x 2 between 1 and 1.01 85/371/73,
-// of two values 98/1280/79; 262144 x 2 75/134/51 and 81/364/58; 65537 x 2 74/77/46 and 74/136/53.  Variance rule, 1 M x
-// 8 118/424/120 and 127/1337/128: there the ten launches are level.
-// raw: the thread's eight elements of the block's own chunk; hist: kHistBins words, part: 1024 words, wtot: a word pair per wave, all on chip.
-__device__ __forceinline__ void small_select_many(const SelParams& p, const SmallScratch& ss, const SegView& sv,
-                                                  const SelState& st0, uint32_t (&raw)[8],
-                                                  uint32_t* __restrict__ hist, uint32_t* __restrict__ part,
-                                                  uint64_t* __restrict__ wtot) {
-  constexpr int T = 1024, WAVES = T / 64, PER = 8, TILES = kTile / kSmallTile;
-  static_assert(TILES * 128 == T, "a thread for every tile of a chunk and last digit");
-  __shared__ SelState st;
-  __shared__ __attribute__((aligned(16))) uint32_t digit2[128];
-  __shared__ uint32_t low_sh[2];
-  __shared__ uint32_t turn_sh;
-  uint32_t* const dig1 = ss.many + kManyDig1;
-  uint32_t* const dig2 = ss.many + kManyDig2;
-  uint32_t* const claim = ss.many + kManyClaim;
-  SelState* const mid = reinterpret_cast<SelState*>(ss.many + kManyMid);
-  uint2* const tile_cnt = reinterpret_cast<uint2*>(ss.many + kManyTileCnt);
-  uint2* const tile_before = reinterpret_cast<uint2*>(ss.many + kManyTileBefore);
-  uint32_t* const tail = ss.many + kManyTail;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = blockIdx.x, nchunks = gridDim.x;
-  const int64_t n = p.n, j0 = (int64_t)c * kTile + (int64_t)tid * PER;
-  reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
-  __syncthreads();
-  uint32_t cA = 0u, cB = 0u, low_max = 0u, inv_max = 0u;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const uint32_t kk = raw[e] & kKeyMask, low = kk & 0x7ffffu;
-    const bool ok = j0 + e < n;
-    cA += ok && kk > st0.hi ? 1u : 0u;
-    if (ok && kk >= st0.lo && kk <= st0.hi) {
-      ++cB;
-      low_max = low > low_max ? low : low_max;
-      inv_max = (low ^ 0x7ffffu) > inv_max ? (low ^ 0x7ffffu) : inv_max;
-      atomicAdd(&hist[low >> 7], 1u);
+    for (int e = 0; e < 8; ++e) {
+      const int64_t j = j0 + e < n ? j0 + e : n - 1;
+      a[e >> 2][e & 3] = load1g<GT>(g, j);
+      b[e >> 2][e & 3] = r[j];
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t a = __shfl_xor(low_max, o, 64), b = __shfl_xor(inv_max, o, 64);
-    low_max = a > low_max ? a : low_max;
-    inv_max = b > inv_max ? b : inv_max;
-    cA += __shfl_xor(cA, o, 64);
-    cB += __shfl_xor(cB, o, 64);
-  }
-  if (lane == 0) {
-    wtot[wave] = ((uint64_t)cB << 32) | cA;
-    store_through(&ss.low_bits[c * WAVES + wave], ((uint64_t)inv_max << 32) | low_max);
-  }
+}
+
+// Adds the occupied bins of the block's histogram to dst and clears it.
+template <int T>
+__device__ __forceinline__ void small_flush(uint32_t* __restrict__ lh, uint32_t* __restrict__ dst) {
   __syncthreads();
-  if (tid < TILES)  // (a tile is the elements of two waves)
-    store_through(reinterpret_cast<uint64_t*>(tile_cnt) + c * TILES + tid, wtot[2 * tid] + wtot[2 * tid + 1]);
-  uint32_t* __restrict__ d1 = dig1 + (size_t)(c % kSmallReps) * kHistBins;
 #pragma unroll
   for (int i = 0; i < kHistBins / T; ++i) {
-    const uint32_t v = hist[i * T + tid];
-    if (v) atomicAdd(&d1[i * T + tid], v);
-  }
-
-  // tile_before from every tile's counts, and the final state; all threads call it
-  const int ntiles = nchunks * TILES;  // up to two a thread; those behind the vector count nothing
-  auto finish = [&](auto count) {
-    uint2 c0 = make_uint2(0u, 0u), c1 = make_uint2(0u, 0u);
-    if (2 * tid < ntiles) {
-      c0 = count(2 * tid);
-      c1 = count(2 * tid + 1);
+    const uint32_t v = lh[i * T + threadIdx.x];
+    if (v) {
+      atomicAdd(&dst[i * T + threadIdx.x], v);
+      lh[i * T + threadIdx.x] = 0u;
     }
-    const uint32_t ea = block_prefix_incl<T>(c0.x + c1.x, part) - (c0.x + c1.x);
-    const uint32_t eb = block_prefix_incl<T>(c0.y + c1.y, part) - (c0.y + c1.y);
-    if (2 * tid < ntiles) {
-      tile_before[2 * tid] = make_uint2(ea, eb);
-      tile_before[2 * tid + 1] = make_uint2(ea + c0.x, eb + c0.y);
-    }
-    if (tid == 0) *sv.st = st;
-  };
-
-  const uint32_t step = ss.ctr[kCtrStep] + 1u;
-  // (all that this step's blocks add to these, and read of them, they have before anybody calls this)
-  auto clear = [&]() {
-    uint4* __restrict__ z = reinterpret_cast<uint4*>(dig1);
-    for (int i = tid; i < kSmallReps * kHistBins / 4; i += T) z[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (tid < kSmallReps * 128) dig2[tid] = 0u;
-    if (tid < 3) ss.ctr[tid * kSmallLine] = 0u;  // (kCtrPass, kCtrSelect, kCtrDone)
-    if (tid == 0) ss.ctr[kCtrStep] = step;
-  };
-  uint32_t phase = kPhaseNone;  // (thread 0's)
-  const bool last = last_block(&ss.ctr[kCtrSelect], (uint32_t)nchunks);
-  if (last) {
-    uint4 q[kSmallReps];
-#pragma unroll
-    for (int r = 0; r < kSmallReps; ++r) q[r] = reinterpret_cast<const uint4*>(dig1 + (size_t)r * kHistBins)[tid];
-    uint32_t l0 = 0u, l1 = 0u;
-    for (int i = tid; i < nchunks * WAVES; i += T) {
-      const uint64_t lb = ss.low_bits[i];
-      l0 = (uint32_t)lb > l0 ? (uint32_t)lb : l0;
-      l1 = (uint32_t)(lb >> 32) > l1 ? (uint32_t)(lb >> 32) : l1;
-    }
-    if (tid == 0) {
-      st = st0;
-      st.many = 1u;
-    }
-    if (tid < 2) low_sh[tid] = 0u;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const uint32_t o0 = __shfl_xor(l0, o, 64), o1 = __shfl_xor(l1, o, 64);
-      l0 = o0 > l0 ? o0 : l0;
-      l1 = o1 > l1 ? o1 : l1;
-    }
-    __syncthreads();
-    if (lane == 0) {
-      atomicMax(&low_sh[0], l0);
-      atomicMax(&low_sh[1], l1);
-    }
-    __syncthreads();
-    if (low_sh[0] == (low_sh[1] ^ 0x7ffffu)) {  // all candidates are equal: no further digit needed
-      if (tid == 0) {
-        st.lo |= low_sh[0];
-        st.hi = st.lo;
-        st.level = 3u;
-      }
-      finish([&](int t) { return tile_cnt[t]; });
-      phase = kPhaseOver;
-    } else {  // the second digit from the blocks' counts, then everybody's help with the last
-      uint32_t h[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int r = 0; r < kSmallReps; ++r) h[0] += q[r].x, h[1] += q[r].y, h[2] += q[r].z, h[3] += q[r].w;
-      block_pick_bins<T>(st, h, 1, part, p.err);
-      phase = st.level == 2u ? kPhaseCount : kPhaseOver;
-      if (tid == 0) {
-        const uint32_t* from = reinterpret_cast<const uint32_t*>(&st);
-        for (int i = 0; i < (int)(sizeof(SelState) / 4); ++i) store_through(reinterpret_cast<uint32_t*>(mid) + i, from[i]);
-        if (phase == kPhaseOver) atomicOr(p.err, kErrSequence);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (before the word that says that it is there)
-      }
-    }
-    if (tid == 0) store_through(&ss.ctr[kCtrPhase], 4u * step + phase);
-    if (phase == kPhaseOver) {
-      __syncthreads();  // (every thread has read what clear() clears)
-      clear();
-    }
-  }
-
-  if (tid == 0) {  // (the wait is bounded: without help the block that published the digit does all of it)
-    for (int i = 0; phase == kPhaseNone && i < kSmallHelpSpins; ++i) {
-      const uint32_t word = __hip_atomic_load(&ss.ctr[kCtrPhase], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((word >> 2) == (step & 0x3fffffffu))
-        phase = word & 3u;
-      else
-        __builtin_amdgcn_s_sleep(4);
-    }
-    turn_sh = phase;
   }
   __syncthreads();
-  if (turn_sh != kPhaseCount) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  const uint32_t lo = mid->lo, hi = mid->hi;
-  int ch = c;
-  while (true) {
-    __syncthreads();  // (turn_sh, low_sh, hist, digit2 and part are free)
-    if (tid == 0)
-      turn_sh = __hip_atomic_exchange(&claim[ch], step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != step ? 1u : 0u;
-    hist[tid] = 0u;  // [TILES][128]
-    if (tid < 128) digit2[tid] = 0u;
-    if (tid == 0) low_sh[0] = (uint32_t)nchunks;
-    if (ch != c) small_load8(sv.x, n, (int64_t)ch * kTile + (int64_t)tid * PER, raw);
-    __syncthreads();
-    if (turn_sh != 0u) {
-      const int64_t e0 = (int64_t)ch * kTile + (int64_t)tid * PER;
-      const int tile = wave / (WAVES / TILES);
-      uint32_t above = 0u;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const uint32_t kk = raw[e] & kKeyMask;
-        const bool ok = e0 + e < n;
-        above += ok && kk > hi ? 1u : 0u;
-        if (ok && kk >= lo && kk <= hi) atomicAdd(&hist[tile * 128 + (int)(kk & 0x7fu)], 1u);
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, 64);
-      if (lane == 0) part[wave] = above;
-      __syncthreads();
-      {  // thread = (tile, last digit): two waves a tile
-        const uint32_t v = hist[tid];
-        if (v) atomicAdd(&digit2[tid & 127], v);
-        uint32_t from_here = v;  // this digit or a later one of the wave's
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t x = __shfl_down(from_here, o, 64);
-          if (lane + o < 64) from_here += x;
-        }
-        uint32_t upper = (tid & 64) == 0 ? hist[tid + 64] : 0u;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) upper += __shfl_xor(upper, o, 64);
-        store_through(&tail[(size_t)ch * T + tid], from_here + upper);
-        if ((tid & 127) == 0)
-          store_through(&tile_cnt[ch * TILES + (tid >> 7)].x, part[2 * (tid >> 7)] + part[2 * (tid >> 7) + 1]);
-      }
-      __syncthreads();
-      if (tid < 128) {
-        const uint32_t v = digit2[tid];
-        if (v) atomicAdd(&dig2[(ch % kSmallReps) * 128 + tid], v);
-      }
-      if (last_block(&ss.ctr[kCtrDone], (uint32_t)nchunks)) {  // that was the last chunk: the threshold
-        if (tid == 0) st = *mid;
-        if (tid < 128) {
-          uint32_t v = 0u;
-#pragma unroll
-          for (int r = 0; r < kSmallReps; ++r) v += dig2[r * 128 + tid];
-          digit2[tid] = v;
-        }
-        __syncthreads();
-        block_pick<T>(st, digit2, 2, part, p.err);
-        if (st.level == 3u) {
-          const uint32_t d2 = st.lo & 0x7fu;
-          finish([&](int t) {
-            const uint32_t ge = tail[(size_t)t * 128 + d2];
-            const uint32_t gt = d2 < 127u ? tail[(size_t)t * 128 + d2 + 1] : 0u;
-            return make_uint2(tile_cnt[t].x + gt, ge - gt);
-          });
-        } else if (tid == 0) {
-          atomicOr(p.err, kErrSequence);
-        }
-        clear();
-        return;
-      }
-    }
-    if (!last) return;
-    // a chunk that nobody has taken on yet
-    if (tid < nchunks && __hip_atomic_load(&claim[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != step)
-      atomicMin(&low_sh[0], (uint32_t)tid);
-    __syncthreads();
-    ch = (int)low_sh[0];
-    if (ch >= nchunks) return;  // (the others' blocks finish theirs)
-  }
 }
 
-// The selection behind k_small_pass: every block writes its chunk's part of the leader's survivor list, its
-// candidates (top digit = threshold digit) a second time, by themselves, and clears its share of the histograms the
-// pass used.  The last block takes the remaining digits from the candidates, a tenth of the list or so, and counts per
-// chunk the list's entries above and at the threshold.  The outputs are left to the many blocks of the next launch
-// (small_kept): one block that also walked the list and wrote them in order took 40 us more on 1 M elements, one in a
-// hundred kept, one that counted over the whole list 10 us more.
-// grid = chunks (of kTile elements), block = 1024.
-__global__ void __launch_bounds__(1024)
-k_small_select(SelParams p, SmallScratch ss) {
-  constexpr int T = 1024, WAVES = T / 64, PER = 8;
-  static_assert(T * PER == kTile, "a chunk is eight elements a thread");
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kHistBins];
+template <bool STATS, int GT, int T>
+__global__ void __launch_bounds__(T)
+k_small_step(SmallStep a) {
+  constexpr int M = T == 1024 ? 2 : 4;
+  constexpr int C = 8 * T, WAVES = T / 64, BPT = kHistBins / T;
+  constexpr int POOL = C > kHistBins ? C : kHistBins;
+  __shared__ __attribute__((aligned(16))) uint32_t pool[POOL];  // the block's histogram; at last its part of the update
+  __shared__ uint16_t place[C];  // the chunk's kept elements, in order
   __shared__ SelState st;
-  __shared__ uint32_t part[T];
-  __shared__ __attribute__((aligned(16))) uint32_t digit2[128];
-  __shared__ uint32_t cnt[2][kSmallMaxChunks];
-  __shared__ uint32_t low_sh[2];
+  __shared__ uint32_t part[WAVES];
   __shared__ uint64_t wtot[WAVES];
+  __shared__ double var_sh[STATS ? kMaxW : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t tail[128];
+  __shared__ uint16_t owned[kSmallMaxChunks];
+  __shared__ int verdict;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = blockIdx.x, nchunks = gridDim.x;
-  const SegView sv = seg_view(p, 0);
-  const SelState st0 = *sv.st;  // (of the launch before this one)
-  const bool bad = *p.err != 0u || st0.level != 1u;
-  const uint32_t off = sv.chunk_off[c], coff = ss.cand_off[c];
-  // this thread's eight elements
-  const int64_t n = p.n, j0 = (int64_t)c * kTile + (int64_t)tid * PER;
-  uint32_t raw[PER];
-  small_load8(sv.x, n, j0, raw);
-  small_clear(ss);
-  if (!bad && st0.cand > small_few(nchunks)) {  // the same in every block
-    small_select_many(p, ss, sv, st0, raw, hist, part, wtot);
-    return;
-  }
-  uint32_t isA = 0u, isB = 0u, low_max = 0u, inv_max = 0u;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const uint32_t kk = raw[e] & kKeyMask;
-    const bool ok = !bad && j0 + e < n;
-    const bool a = ok && kk > st0.hi, b = ok && kk >= st0.lo && kk <= st0.hi;
-    isA |= a ? 1u << e : 0u;
-    isB |= b ? 1u << e : 0u;
-    const uint32_t low = kk & 0x7ffffu;
-    if (b) {
-      low_max = low > low_max ? low : low_max;
-      inv_max = (low ^ 0x7ffffu) > inv_max ? (low ^ 0x7ffffu) : inv_max;
-    }
-  }
-  const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
-  uint32_t befA = 0u, befB = 0u, totA = 0u, totB = 0u;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const uint64_t pa = __ballot((cA >> b) & 1u), pb = __ballot((cB >> b) & 1u);
-    befA += popc_lt(pa) << b;
-    befB += popc_lt(pb) << b;
-    totA += (uint32_t)__popcll(pa) << b;
-    totB += (uint32_t)__popcll(pb) << b;
-  }
-  if (lane == 0) wtot[wave] = ((uint64_t)totA << 32) | totB;
-  __syncthreads();
-  uint64_t sum = 0ull, all = 0ull;
-#pragma unroll
-  for (int i = 0; i < WAVES; ++i) {
-    const uint64_t wt = wtot[i];
-    sum += i < wave ? wt : 0ull;
-    all += wt;
-  }
-  befA += (uint32_t)(sum >> 32);
-  befB += (uint32_t)sum;
-  uint32_t pos = off + befA + befB, cpos = coff + befB;
-  if ((isA | isB) != 0u) {
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const bool b = (isB >> e) & 1u;
-      if (((isA >> e) & 1u) || b) {
-        if (pos < sv.d.cap) sv.list[pos] = make_uint2((uint32_t)(j0 + e), raw[e]);
-        ++pos;
-      }
-      if (b) {
-        store_through(&ss.cand[cpos], (raw[e] & 0x7ffffu) | ((uint32_t)c << 19));
-        ++cpos;
-      }
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t a = __shfl_xor(low_max, o, 64), b = __shfl_xor(inv_max, o, 64);
-    low_max = a > low_max ? a : low_max;
-    inv_max = b > inv_max ? b : inv_max;
-  }
-  if (lane == 0) store_through(&ss.low_bits[c * WAVES + wave], ((uint64_t)inv_max << 32) | low_max);
-  if (tid == 0) store_through(&ss.sure[c], (uint32_t)(all >> 32));
-  reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
-  if (!last_block(&ss.ctr[kCtrSelect], (uint32_t)nchunks)) return;
+  const int64_t n = a.n;
+  const int nchunks = a.nchunks, w_count = a.w_count, groups = a.groups, nunits = nchunks * groups, u0 = blockIdx.x;
+  const SmallScratch& ss = a.ss;
+  const bool known = a.leader >= 0;
 
-  // everything that is needed comes in one go: each load is a trip to memory
-  const uint32_t ncand = st0.cand;
-  constexpr int KEEP = 4;  // candidates a thread keeps in registers
-  uint32_t word[KEEP];
-#pragma unroll
-  for (int i = 0; i < KEEP; ++i) {
-    const uint32_t q = (uint32_t)(i * T + tid);
-    word[i] = 0u;
-    if ((uint32_t)(i * T) < ncand) word[i] = ss.cand[q < ncand ? q : ncand - 1u];
+  // the first worker's loads are on their way while the chunk is taken
+  v4f g8[2], r8[2];
+  // the workers of a unit's group: a known leader alone in group 0 (as long as there are others), else shares of them all
+  const int rest = w_count - 1;
+  auto first_of = [&](int grp) __attribute__((always_inline)) {
+    return known ? rest * (grp - 1) / (groups > 1 ? groups - 1 : 1) : w_count * grp / groups;
+  };
+  auto worker = [&](int i) __attribute__((always_inline)) { return known && i >= a.leader ? i + 1 : i; };
+  auto fetch = [&](int w, int c) __attribute__((always_inline)) {
+    small_fetch<GT>(a.g.p[w], a.res.p[w], n, (int64_t)c * C + 8 * tid, g8, r8);
+  };
+  auto fetch_first = [&](int unit) __attribute__((always_inline)) {
+    const int grp = unit / nchunks;
+    fetch(known && grp == 0 ? a.leader : worker(first_of(grp)), unit % nchunks);
+  };
+  fetch_first(u0);
+  const uint32_t step = ss.ctr[kCtrStep];
+  if (*a.err != 0u) return;  // (set before this launch: the same in every block)
+  if (tid == 0) {
+    const uint32_t was = __hip_atomic_exchange(&ss.claim[u0], step + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    verdict = was == step + 1u ? -1 : 0;
+    owned[0] = (uint16_t)u0;
   }
-  const uint32_t my_sure = tid < nchunks ? ss.sure[tid] : 0u;
-  const uint32_t my_coff = tid < nchunks ? ss.cand_off[tid] : 0u;
-  uint32_t l0 = 0u, l1 = 0u;
-  for (int i = tid; i < nchunks * WAVES; i += T) {
-    const uint64_t lb = ss.low_bits[i];
-    l0 = (uint32_t)lb > l0 ? (uint32_t)lb : l0;
-    l1 = (uint32_t)(lb >> 32) > l1 ? (uint32_t)(lb >> 32) : l1;
-  }
-  if (tid == 0) st = st0;
-  if (tid < 128) digit2[tid] = 0u;
-  if (tid < kSmallMaxChunks) cnt[0][tid] = cnt[1][tid] = 0u;
-  if (tid < 2) low_sh[tid] = 0u;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t o0 = __shfl_xor(l0, o, 64), o1 = __shfl_xor(l1, o, 64);
-    l0 = o0 > l0 ? o0 : l0;
-    l1 = o1 > l1 ? o1 : l1;
-  }
+  for (int b = tid; b < kHistBins; b += T) pool[b] = 0u;
+  if (tid < 128) tail[tid] = 0u;
   __syncthreads();
-  if (lane == 0 && (l0 | l1) != 0u) {
-    atomicMax(&low_sh[0], l0);
-    atomicMax(&low_sh[1], l1);
-  }
-  // for every candidate, in some thread: use(word)
-  auto each = [&](auto use) {
-#pragma unroll
-    for (int i = 0; i < KEEP; ++i)
-      if ((uint32_t)(i * T + tid) < ncand) use(word[i]);
-    for (uint32_t q = (uint32_t)(KEEP * T + tid); q < ncand; q += 4 * T) {  // four loads in flight
-      uint32_t w4[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) w4[i] = ss.cand[q + (uint32_t)(i * T) < ncand ? q + (uint32_t)(i * T) : q];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (q + (uint32_t)(i * T) < ncand) use(w4[i]);
+  // The step's number goes up once every block has read it: at once where every block took its own chunk, else when
+  // as many blocks as chunks were taken on by others have come late, and this (the last to leave, then) is through.
+  auto leave = [&](uint32_t helped) __attribute__((always_inline)) {
+    if (tid != 0) return;
+    bool last = true;
+    if (helped != 0u) {
+      const uint32_t late = __hip_atomic_fetch_add(&ss.ctr[kCtrLate], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = late == load_through(&ss.ctr[kCtrHelped]);
+    }
+    if (last) {
+      store_through(&ss.ctr[kCtrStep], step + 1u);
+      if (helped != 0u) {
+        store_through(&ss.ctr[kCtrHelped], 0u);
+        store_through(&ss.ctr[kCtrLate], 0u);
+      }
     }
   };
-  __syncthreads();
-  const bool equal = low_sh[0] == (low_sh[1] ^ 0x7ffffu);
-  if (bad) {
-    if (tid == 0) atomicOr(p.err, kErrSequence);
-    if (tid < 2) ss.ctr[tid * kSmallLine] = 0u;  // (kCtrPass, kCtrSelect)
-    return;
-  }
-  if (equal) {  // all candidates are equal: no further digit needed, and each chunk's are known
-    if (tid == 0) {
-      st.lo |= low_sh[0];
-      st.hi = st.lo;
-      st.level = 3u;
-    }
-    if (tid < nchunks) atomicAdd(&cnt[1][tid], (tid + 1 < nchunks ? ss.cand_off[tid + 1] : ncand) - my_coff);
-    __syncthreads();
-  } else {
-    each([&](uint32_t w) { atomicAdd(&hist[(w >> 7) & 0xfffu], 1u); });
-    __syncthreads();
-    block_pick<T>(st, hist, 1, part, p.err);
-    const uint32_t d1 = (st.lo >> 7) & 0xfffu;
-    each([&](uint32_t w) {
-      if (((w >> 7) & 0xfffu) == d1) atomicAdd(&digit2[w & 0x7fu], 1u);
-    });
-    __syncthreads();
-    block_pick<T>(st, digit2, 2, part, p.err);
-    const uint32_t low_t = st.lo & 0x7ffffu;
-    each([&](uint32_t w) {
-      const uint32_t low = w & 0x7ffffu;
-      if (low >= low_t) atomicAdd(&cnt[low > low_t ? 0 : 1][w >> 19], 1u);
-    });
-    __syncthreads();
-  }
-  if (tid < 2) ss.ctr[tid * kSmallLine] = 0u;  // (kCtrPass, kCtrSelect)
-  if (st.level != 3u) {
-    if (tid == 0) atomicOr(p.err, kErrSequence);
-    return;
-  }
-  if (tid < nchunks) cnt[0][tid] += my_sure;
-  __syncthreads();
-  if (tid < kSmallMaxChunks) {  // exclusive prefix over the chunks: four waves, each adds the waves before it
-    const uint32_t ca = cnt[0][tid], cb = cnt[1][tid];
-    uint32_t ea = wave_incl_scan(ca) - ca, eb = wave_incl_scan(cb) - cb;
-    for (int i = lane; i < (tid & ~63); i += 64) {
-      uint32_t xa = cnt[0][i], xb = cnt[1][i];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        xa += __shfl_xor(xa, o, 64);
-        xb += __shfl_xor(xb, o, 64);
-      }
-      ea += xa;
-      eb += xb;
-    }
-    ss.before[tid] = make_uint2(ea, eb);
-  }
-  if (tid == 0) *sv.st = st;
-}
+  if (verdict < 0) return leave(1u);
+  int n_owned = u0 < nchunks ? 1 : 0;  // chunks that this block takes to the outputs: of the first group
 
-// The kept entries of one tile of kSmallTile elements, found again in the list entries of its chunk (or, with many
-// candidates, in the vector itself): calls use(position among the k kept, element, raw bits) for each, in some thread;
-// returns false (in every thread) if the selection failed.  All 256 threads call it.
-template <typename Use>
-__device__ __forceinline__ bool small_kept(const SelParams& p, const SmallScratch& ss, int64_t lo, Use use) {
-  constexpr int T = 256;
-  __shared__ uint32_t wtot[T / 64];
-  const int tid = threadIdx.x, wave = tid >> 6;
-  const SegView sv = seg_view(p, 0);
-  // (every load that does not depend on another is under way before the first branch)
-  const int c = (int)(lo / kTile);
-  const uint32_t from = sv.chunk_off[c];
-  const uint32_t to = c + 1 < sv.d.geom.nchunks ? sv.chunk_off[c + 1] : sv.st->list_count;
-  const uint2 bef_chunk = ss.before[c];
-  const uint32_t klo = sv.st->lo, khi = sv.st->hi, quota = sv.st->need, many = sv.st->many;
-  if (sv.st->level != 3u || *p.err) return false;
-  if (__builtin_expect(many != 0u, 0)) {
-    const uint2 bef = reinterpret_cast<const uint2*>(ss.many + kManyTileBefore)[lo / kSmallTile];
-    const int64_t j = lo + 4 * tid;
-    uint32_t raw[4] = {0u, 0u, 0u, 0u};
-    if (j + 4 <= p.n) {
-      const uint4 v = *reinterpret_cast<const uint4*>(sv.x + j);
-      raw[0] = v.x, raw[1] = v.y, raw[2] = v.z, raw[3] = v.w;
+  uint32_t* const arrive0 = ss.ctr + kCtrArrive + (step & 1u) * kCtrSet;
+  uint32_t* const dig2 = ss.dig2 + (step & 1u) * kSmallReps * 128;
+  // what this block has stored through and added is there, for chunk c
+  auto arrive = [&](int b, int c) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+      __hip_atomic_fetch_add(&arrive0[(b * kSmallArrive + c % kSmallArrive) * kSmallLine], 1u, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto arrived = [&](int b) __attribute__((always_inline)) {  // a wave's: whether all chunks have
+    uint32_t v = 0u;
+    if (lane < kSmallArrive)
+      v = load_through(&arrive0[(b * kSmallArrive + lane) * kSmallLine]);
+    v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 2, 64);
+    v += __shfl_xor(v, 4, 64);
+    return __builtin_amdgcn_readfirstlane(v) == (uint32_t)(b == 0 ? nunits : nchunks);
+  };
+  // waits for all chunks, at most `spins` looks; false (in every thread) if they are not there
+  auto wait = [&](int b, int spins) __attribute__((always_inline)) {
+    if (wave == 0) {
+      bool ok = arrived(b);
+      for (int i = 0; !ok && i < spins; ++i) ok = arrived(b);
+      if (lane == 0) verdict = ok ? 1 : 0;
+    }
+    __syncthreads();
+    const bool ok = verdict != 0;
+    __syncthreads();  // (verdict is free)
+    return ok;
+  };
+
+  uint32_t raw[8];  // the leader's elements of chunk `cur`
+  int cur = -1;
+  // acc = g + residual of worker w's chunk c, from what small_fetch has loaded; counts the top digits in `pool`
+  auto sum_up = [&](int w, int c, const v4f (&ga)[2], const v4f (&ra)[2], VarAcc* va, bool count) __attribute__((always_inline)) {
+    const int64_t j0 = (int64_t)c * C + 8 * tid;
+    const bool full = j0 + 8 <= n;
+    float* __restrict__ rp = a.res.p[w];
+    v4f v[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      v[u].x = ga[u].x + ra[u].x;
+      v[u].y = ga[u].y + ra[u].y;
+      v[u].z = ga[u].z + ra[u].z;
+      v[u].w = ga[u].w + ra[u].w;
+    }
+    if (full) {
+      if (groups > 1) {  // (another block gathers from them)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          store_through(reinterpret_cast<uint64_t*>(rp + j0) + u,
+                        ((uint64_t)__float_as_uint(v[u >> 1][2 * (u & 1) + 1]) << 32) | __float_as_uint(v[u >> 1][2 * (u & 1)]));
+      } else {
+        store4<false>(rp + j0, v[0]);
+        store4<false>(rp + j0 + 4, v[1]);
+      }
+      if (STATS) {
+        va->seed4(a.raw_stats ? ga[0] : v[0]);
+        va->add4(a.raw_stats ? ga[0] : v[0]);
+        va->add4(a.raw_stats ? ga[1] : v[1]);
+      }
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) raw[e] = j + e < p.n ? __float_as_uint(sv.x[j + e]) : 0u;
+      for (int e = 0; e < 8; ++e) {
+        if (j0 + e < n) {
+          store_through(rp + j0 + e, v[e >> 2][e & 3]);
+          if (STATS) {
+            va->seed1(a.raw_stats ? ga[e >> 2][e & 3] : v[e >> 2][e & 3]);
+            va->add1(a.raw_stats ? ga[e >> 2][e & 3] : v[e >> 2][e & 3]);
+          }
+        }
+      }
     }
+    if (count) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t bits = __float_as_uint(v[e >> 2][e & 3]);
+        raw[e] = bits;
+        if (full || j0 + e < n) atomicAdd(&pool[(bits & kKeyMask) >> 19], 1u);
+      }
+    }
+  };
+  // the first part of a chunk, its first worker's elements loaded already
+  auto begin = [&](int unit) __attribute__((always_inline)) {
+    const int c = unit % nchunks, grp = unit / nchunks;
+    if (known && grp == 0) {
+      sum_up(a.leader, c, g8, r8, nullptr, true);
+      cur = c;
+      small_flush<T>(pool, ss.hist + (size_t)(c % a.reps) * kHistBins);
+    } else {
+      const int end = first_of(grp + 1);
+      for (int i = first_of(grp); i < end; ++i) {
+        const int w = worker(i);
+        const v4f ga[2] = {g8[0], g8[1]}, ra[2] = {r8[0], r8[1]};
+        if (i + 1 < end) fetch(worker(i + 1), c);
+        VarAcc va;
+        sum_up(w, c, ga, ra, &va, !known);
+        if (known) continue;
+        if (STATS) block_moments<T, true>(va, a.partials, w, nchunks, c);
+        small_flush<T>(pool, ss.hist + ((size_t)w * kSmallReps + (size_t)(c % a.reps)) * kHistBins);
+      }
+    }
+    arrive(0, unit);
+  };
+  // the sums of the workers other than a known leader, up to the upto-th of them
+  int others = known && groups == 1 ? 0 : rest;
+  auto more = [&](int upto) __attribute__((always_inline)) {
+    while (others < upto) {
+      const int m = upto - others < M ? upto - others : M;  // as many workers' loads in flight
+      for (int i = 0; i < n_owned; ++i) {
+        const int c = owned[i];
+        const int64_t j0 = (int64_t)c * C + 8 * tid;
+        v4f ga[M][2], ra[M][2];
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+          if (q < m) {
+            const int w = worker(others + q);
+            small_fetch<GT>(a.g.p[w], a.res.p[w], n, j0, ga[q], ra[q]);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+          if (q < m) sum_up(worker(others + q), c, ga[q], ra[q], nullptr, false);
+      }
+      others += m;
+    }
+  };
+
+  begin(u0);
+  if (n_owned == 0) return;
+  more((rest + 2) / 3);
+  for (int look = u0 + 1; !wait(0, kSmallHelpSpins);) {
+    // a chunk that nobody has taken: its block does not run yet, and may not before this one is done
+    if (tid == 0) {
+      verdict = -1;
+      for (int i = 0; i < nunits && verdict < 0; ++i, ++look) {
+        const int c = look % nunits;
+        if (load_through(&ss.claim[c]) == step + 1u) continue;
+        // (counted before it is taken: a late block never finds fewer of them than have come late)
+        __hip_atomic_fetch_add(&ss.ctr[kCtrHelped], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if (__hip_atomic_exchange(&ss.claim[c], step + 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != step + 1u)
+          verdict = c;
+        else
+          __hip_atomic_fetch_sub(&ss.ctr[kCtrHelped], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (verdict >= 0 && verdict < nchunks) owned[n_owned] = (uint16_t)verdict;
+    }
+    __syncthreads();
+    const int c = verdict;
+    __syncthreads();
+    if (c < 0) {  // all are taken, by blocks that run
+      if (wait(0, kSpinLimit)) break;
+      if (tid == 0) atomicOr(a.err, kErrWait);
+      return;
+    }
+    fetch_first(c);
+    begin(c);
+    if (known && groups == 1) {  // (its share of what the other chunks have had of the other workers)
+      for (int o = 0; o < others; ++o) {
+        fetch(worker(o), c);
+        sum_up(worker(o), c, g8, r8, nullptr, false);
+      }
+    }
+    n_owned += c < nchunks ? 1 : 0;
+  }
+
+  // the leader
+  int lead = a.leader;
+  if (!known) {
+    if (STATS) {
+      for (int w = wave; w < w_count; w += WAVES) {
+        const double v = wave_variance<true>(a.partials, w, nchunks);
+        if (lane == 0) var_sh[w] = v;
+      }
+      __syncthreads();
+      lead = 0;
+      for (int w = 1; w < w_count; ++w)
+        if (var_sh[w] > var_sh[lead]) lead = w;
+      lead = __builtin_amdgcn_readfirstlane(lead);
+    } else {
+      lead = *a.leader_dev;
+    }
+  }
+  const bool first = owned[0] == 0;  // chunk 0's block reports (or whoever took it, below)
+  bool reports = first;
+  for (int i = 1; i < n_owned; ++i) reports = reports || owned[i] == 0;
+  if (reports) {
+    if (STATS && !known && a.var_out && tid < w_count) a.var_out[tid] = var_sh[tid];
+    if (tid == 0 && (known || STATS)) {
+      *a.leader_dev = lead;
+      if (a.leader_out) *a.leader_out = lead;
+    }
+    // the set of the next step (of the one before last: nobody is at it)
+    uint32_t* const next = ss.ctr + kCtrArrive + ((step + 1u) & 1u) * kCtrSet;
+    if (tid < 3 * kSmallArrive) next[tid * kSmallLine] = 0u;
+    for (int i = tid; i < kSmallReps * 128; i += T) ss.dig2[((step + 1u) & 1u) * kSmallReps * 128 + i] = 0u;
+  }
+  const float* lx = a.res.p[lead];
+
+  // picks digit `digit` of the threshold from `reps` copies of its histogram
+  auto pick = [&](const uint32_t* __restrict__ hist, auto digit_tag) __attribute__((always_inline)) {
+    constexpr int digit = decltype(digit_tag)::value, pairs = (int)(digit_mask(digit) + 1u) / 2;
+    // neighbouring lanes read neighbouring bins, all of a copy's loads together; `pool` hands them to the bins' owners
+    constexpr int J = pairs > T ? pairs / T : 1;
+    uint64_t sum[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) sum[j] = 0ull;
+    for (int r = 0; r < a.reps; ++r) {
+      const uint64_t* __restrict__ from = reinterpret_cast<const uint64_t*>(hist) + (size_t)r * pairs;
+      uint64_t q[J];
+#pragma unroll
+      for (int j = 0; j < J; ++j) q[j] = pairs >= T || tid < pairs ? load_through(from + j * T + tid) : 0ull;
+#pragma unroll
+      for (int j = 0; j < J; ++j) sum[j] += q[j];
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (pairs >= T || tid < pairs) reinterpret_cast<uint64_t*>(pool)[j * T + tid] = sum[j];
+    __syncthreads();
+    uint32_t h[BPT];
+#pragma unroll
+    for (int j = 0; j < BPT / 4; ++j) {
+      uint4* const mine = reinterpret_cast<uint4*>(pool) + (BPT / 4) * tid + j;
+      const uint4 q = *mine;
+      h[4 * j + 0] = q.x;
+      h[4 * j + 1] = q.y;
+      h[4 * j + 2] = q.z;
+      h[4 * j + 3] = q.w;
+      *mine = make_uint4(0u, 0u, 0u, 0u);
+    }
+    block_pick_bins<T>(st, h, digit, part, a.err);
+  };
+  // the leader's elements of chunk c in `raw`
+  auto take = [&](int c) __attribute__((always_inline)) {
+    if (c == cur) return;
+    cur = c;
+    const int64_t j0 = (int64_t)c * C + 8 * tid;
+    if (groups > 1) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint64_t x = j0 + 2 * e + 2 <= n ? load_through(reinterpret_cast<const uint64_t*>(lx + j0) + e) : 0ull;
+        raw[2 * e] = (uint32_t)x;
+        raw[2 * e + 1] = (uint32_t)(x >> 32);
+      }
+      if (j0 < n && n - j0 < 8 && (n & 1)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (j0 + e == n - 1) raw[e] = load_through(reinterpret_cast<const uint32_t*>(lx) + n - 1);
+      }
+    } else if (j0 + 8 <= n) {
+      const uint4 x = reinterpret_cast<const uint4*>(lx + j0)[0], y = reinterpret_cast<const uint4*>(lx + j0)[1];
+      raw[0] = x.x, raw[1] = x.y, raw[2] = x.z, raw[3] = x.w;
+      raw[4] = y.x, raw[5] = y.y, raw[6] = y.z, raw[7] = y.w;
+    } else if (j0 < n) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) raw[e] = __float_as_uint(lx[j0 + e < n ? j0 + e : n - 1]);
+    }
+  };
+  if (!known) {
+    cur = -1;
+    take(owned[0]);
+  }
+  if (tid == 0) {
+    st = SelState{};
+    st.hi = kKeyMask;
+    st.need = a.k;
+  }
+  pick(ss.hist + (known ? 0 : (size_t)lead * kSmallReps * kHistBins), std::integral_constant<int, 0>{});
+  const uint32_t cand0 = st.cand, list0 = st.n_gt + st.cand;  // (reported)
+
+  for (int i = 0; i < n_owned; ++i) {
+    const int c = owned[i];
+    take(c);
+    const int64_t left = n - ((int64_t)c * C + 8 * tid);
+    const uint32_t lo = st.lo, hi = st.hi;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t kk = raw[e] & kKeyMask;
+      if (e < left && kk >= lo && kk <= hi) atomicAdd(&pool[(kk >> 7) & 0xfffu], 1u);
+    }
+    small_flush<T>(pool, ss.dig1 + (size_t)(c % a.reps) * kHistBins);
+    arrive(1, c);
+  }
+  more((2 * rest + 2) / 3);
+  if (!wait(1, kSpinLimit)) {
+    if (tid == 0) atomicOr(a.err, kErrWait);
+    return;
+  }
+  pick(ss.dig1, std::integral_constant<int, 1>{});
+
+  for (int i = 0; i < n_owned; ++i) {
+    const int c = owned[i];
+    take(c);
+    const int64_t left = n - ((int64_t)c * C + 8 * tid);
+    const uint32_t lo = st.lo, hi = st.hi;
+    uint32_t up = 0u;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t kk = raw[e] & kKeyMask;
+      up += e < left && kk > hi ? 1u : 0u;
+      if (e < left && kk >= lo && kk <= hi) atomicAdd(&tail[kk & 0x7fu], 1u);
+    }
+    uint32_t all = 0u;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) all += (uint32_t)__popcll(__ballot((up >> b) & 1u)) << b;
+    if (lane == 0) part[wave] = all;
+    __syncthreads();
+    if (wave == 0) {  // lane's digits 2 lane and 2 lane + 1
+      const uint32_t t0 = tail[2 * lane], t1 = tail[2 * lane + 1];
+      uint32_t* __restrict__ d2 = dig2 + (size_t)(c % a.reps) * 128;
+      if (t0) atomicAdd(&d2[2 * lane], t0);
+      if (t1) atomicAdd(&d2[2 * lane + 1], t1);
+      uint32_t s = t0 + t1;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = __shfl_down(s, off, 64);
+        if (lane + off < 64) s += x;
+      }
+      store_through(reinterpret_cast<uint64_t*>(ss.rows + (size_t)c * 128) + lane, ((uint64_t)(s - t0) << 32) | s);
+      tail[2 * lane] = tail[2 * lane + 1] = 0u;
+      if (lane == 0) {
+        uint32_t sum = 0u;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) sum += part[v];
+        store_through(&ss.above[c], sum);
+      }
+    }
+    arrive(2, c);
+  }
+  // every block has read the top digits' histograms; each clears its share
+  {
+    uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.hist);
+    const int words4 = (known ? 1 : w_count) * kSmallReps * (kHistBins / 4);
+    for (int i = 0; i < n_owned; ++i)
+      for (int q = (int)owned[i] * T + tid; q < words4; q += nchunks * T) z[q] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  more(rest);
+  uint32_t helped = 0u;  // (of the block that reports, thread 0; all chunks have been taken when it looks)
+  if (reports && tid == 0) helped = load_through(&ss.ctr[kCtrHelped]);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the block gathers from its workers' sums)
+  if (!wait(2, kSpinLimit)) {
+    if (tid == 0) atomicOr(a.err, kErrWait);
+    return;
+  }
+  pick(dig2, std::integral_constant<int, 2>{});
+  if (reports && tid == 0) {
+    SelState out = st;
+    out.many = cand0 > small_few(n) ? 1u : 0u;
+    out.compact_level = list0 <= a.list_cap ? 1u : 0u;
+    out.list_count = out.compact_level ? list0 : 0u;
+    *a.st = out;
+    if (st.level != 3u) atomicOr(a.err, kErrSequence);
+  }
+  {
+    uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.dig1);
+    for (int i = 0; i < n_owned; ++i)
+      for (int q = (int)owned[i] * T + tid; q < kSmallReps * (kHistBins / 4); q += nchunks * T)
+        z[q] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if (reports) leave(helped);
+  if (st.level != 3u) return;
+
+  const uint32_t klo = st.lo, khi = st.hi, quota = st.need, digit = klo & 0x7fu;
+  float* const buf = reinterpret_cast<float*>(pool);
+  for (int i = 0; i < n_owned; ++i) {
+    const int c = owned[i];
+    // kept in front of the chunk: keys above the threshold, and at it
+    uint64_t before = 0ull;
+    if (tid < c) {
+      const uint32_t* __restrict__ row = ss.rows + (size_t)tid * 128 + digit;
+      const uint32_t at = load_through(row), over = digit < 127u ? load_through(row + 1) : 0u;
+      before = ((uint64_t)(load_through(&ss.above[tid]) + over) << 32) | (at - over);
+    }
+    take(c);
+    const int64_t left = n - ((int64_t)c * C + 8 * tid);
     uint32_t isA = 0u, isB = 0u;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < 8; ++e) {
       const uint32_t kk = raw[e] & kKeyMask;
-      isA |= j + e < p.n && kk > khi ? 1u << e : 0u;
-      isB |= j + e < p.n && kk >= klo && kk <= khi ? 1u << e : 0u;
+      isA |= e < left && kk > khi ? 1u << e : 0u;
+      isB |= e < left && kk >= klo && kk <= khi ? 1u << e : 0u;
     }
     const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
-    uint32_t ba = bef.x, bb = bef.y, totA = 0u, totB = 0u;
+    uint32_t bA = 0u, bB = 0u, totA = 0u, totB = 0u;
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
+    for (int b = 0; b < 4; ++b) {
       const uint64_t pa = __ballot((cA >> b) & 1u), pb = __ballot((cB >> b) & 1u);
-      ba += popc_lt(pa) << b;
-      bb += popc_lt(pb) << b;
+      bA += popc_lt(pa) << b;
+      bB += popc_lt(pb) << b;
       totA += (uint32_t)__popcll(pa) << b;
       totB += (uint32_t)__popcll(pb) << b;
     }
-    if ((tid & 63) == 0) wtot[wave] = (totA << 16) | totB;
+    before = wave_allsum_u64(before);
+    __syncthreads();  // (wtot, var_sh's and the last chunk's uses of `pool` are over)
+    if (lane == 0) {
+      wtot[wave] = ((uint64_t)totA << 32) | totB;
+      reinterpret_cast<uint64_t*>(tail)[wave] = before;
+    }
+    for (int b = tid; b < C / 4; b += T) reinterpret_cast<uint4*>(pool)[b] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    for (int i = 0; i < wave; ++i) {
-      ba += wtot[i] >> 16;
-      bb += wtot[i] & 0xffffu;
-    }
+    uint64_t front = 0ull, mine = 0ull, chunk = 0ull;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool a = (isA >> e) & 1u, b = (isB >> e) & 1u;
-      if (a || (b && bb < quota)) {
-        const uint32_t m = ba + (bb < quota ? bb : quota);
-        if (m < sv.d.k) use(m, j + e, raw[e]);
-      }
-      ba += a ? 1u : 0u;
-      bb += b ? 1u : 0u;
+    for (int v = 0; v < WAVES; ++v) {
+      front += reinterpret_cast<const uint64_t*>(tail)[v];
+      mine += v < wave ? wtot[v] : 0ull;
+      chunk += wtot[v];
     }
-    return true;
-  }
-  if (to > sv.d.cap) return false;
-  uint32_t a0 = bef_chunk.x, b0 = bef_chunk.y;
-  for (uint32_t q = from; q < to; q += T) {
-    const uint2 ent = sv.list[q + (uint32_t)tid < to ? q + (uint32_t)tid : to - 1u];
-    const uint32_t kk = ent.y & kKeyMask;
-    const bool ok = q + (uint32_t)tid < to;
-    const bool a = ok && kk > khi, b = ok && kk >= klo && kk <= khi;
-    const uint64_t ma = __ballot(a), mb = __ballot(b);
-    if ((tid & 63) == 0) wtot[wave] = ((uint32_t)__popcll(ma) << 16) | (uint32_t)__popcll(mb);
+    auto kept = [&](uint64_t ab) __attribute__((always_inline)) {
+      const uint32_t b = (uint32_t)ab;
+      return (uint32_t)(ab >> 32) + (b < quota ? b : quota);
+    };
+    const uint32_t m0 = kept(front), m1 = kept(front + chunk);
+    bA += (uint32_t)((front + mine) >> 32);
+    bB += (uint32_t)(front + mine);
+    if ((isA | isB) != 0u) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool is_a = (isA >> e) & 1u, is_b = (isB >> e) & 1u;
+        if (is_a || (is_b && bB < quota)) place[bA + (bB < quota ? bB : quota) - m0] = (uint16_t)(8 * tid + e);
+        bA += is_a ? 1u : 0u;
+        bB += is_b ? 1u : 0u;
+      }
+    }
     __syncthreads();
-    uint32_t ba = a0 + popc_lt(ma), bb = b0 + popc_lt(mb);
+    for (uint32_t q = (uint32_t)tid; q < m1 - m0; q += T) {
+      const uint32_t at = place[q], m = m0 + q;
+      const int64_t j = (int64_t)c * C + at;
+      if (m >= a.k) break;
+      float s = 0.0f;
+      for (int w0 = 0; w0 < w_count; w0 += 8) {  // eight independent loads in flight, then the ordered adds
+        float v[8];
 #pragma unroll
-    for (int i = 0; i < T / 64; ++i) {
-      const uint32_t wt = wtot[i];
-      if (i < wave) {
-        ba += wt >> 16;
-        bb += wt & 0xffffu;
-      }
-      a0 += wt >> 16;
-      b0 += wt & 0xffffu;
-    }
-    const int64_t j = (int64_t)ent.x;
-    if ((a || (b && bb < quota)) && j >= lo && j < lo + kSmallTile && j < p.n) {
-      const uint32_t m = ba + (bb < quota ? bb : quota);
-      if (m < sv.d.k) use(m, j, ent.y);
-    }
-    __syncthreads();  // (wtot is free)
-  }
-  return true;
-}
-
-// The rest of a step whose leader was known up front: the outputs of the selection, for every other worker
-// acc = g + residual with the kept positions' values taken and +0.0 left there, the ordered sums, and the dense
-// update (if wanted), a tile of kSmallTile elements a block.  vals: rows to keep the values in, or nullptr.
-template <int GT>
-__global__ void __launch_bounds__(256)
-k_small_rest(SelParams p, SmallScratch ss, PtrTable g, PtrTable res, int w_count, int leader, int64_t k,
-             float* __restrict__ vals, float* __restrict__ sum_out, float* __restrict__ update) {
-  __shared__ __attribute__((aligned(16))) int32_t slot[kSmallTile];   // place among the k kept, or -1
-  __shared__ __attribute__((aligned(16))) float lead[kSmallTile];     // the leader's value there
-  const int tid = threadIdx.x;
-  const int64_t n = p.n, lo = (int64_t)blockIdx.x * kSmallTile;
-  const int64_t j = lo + 4 * tid;  // this thread's group
-  // the first four workers' loads are under way while the tile's kept entries are found
-  const bool whole = j + 4 <= n;
-  v4f a[4], b[4];
+        for (int u = 0; u < 8; ++u)
+          if (w0 + u < w_count) v[u] = groups > 1 ? load_through(a.res.p[w0 + u] + j) : a.res.p[w0 + u][j];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int w = i < w_count ? i : w_count - 1;
-    if (whole) {
-      a[i] = load4g<false, GT>(g.p[w], j);
-      b[i] = load4<false>(res.p[w] + j);
-    }
-  }
-  reinterpret_cast<int4*>(slot)[tid] = make_int4(-1, -1, -1, -1);
-  __syncthreads();
-  float* __restrict__ lead_res = res.p[leader];
-  int32_t* __restrict__ idx_out = p.idx_out;
-  const bool fine = small_kept(p, ss, lo, [&](uint32_t m, int64_t e, uint32_t raw) {
-    slot[e - lo] = (int32_t)m;
-    lead[e - lo] = __uint_as_float(raw);
-    idx_out[m] = (int32_t)e;
-    lead_res[e] = 0.0f;
-  });
-  if (!fine) return;
-  __syncthreads();
-  if (whole) {
-    const int4 s4 = reinterpret_cast<const int4*>(slot)[tid];
-    const int at[4] = {s4.x, s4.y, s4.z, s4.w};
-    const bool any = (s4.x & s4.y & s4.z & s4.w) >= 0;  // the sign bit of -1 in all four: none
-    float s[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int w0 = 0; w0 < w_count; w0 += 4) {  // four workers' loads in flight, then the ordered adds
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int w = w0 + i;
-        if (w >= w_count) break;
-        float v[4] = {a[i].x + b[i].x, a[i].y + b[i].y, a[i].z + b[i].z, a[i].w + b[i].w};
-        if (any) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (at[e] >= 0) {
-              if (w == leader) v[e] = lead[4 * tid + e];
-              if (vals) vals[(size_t)w * (size_t)k + (size_t)at[e]] = v[e];
-              s[e] = w == 0 ? v[e] : s[e] + v[e];
-              v[e] = 0.0f;
-            }
+        for (int u = 0; u < 8; ++u) {
+          if (w0 + u < w_count) {
+            if (a.vals) a.vals[(size_t)(w0 + u) * (size_t)a.k + (size_t)m] = v[u];
+            s = w0 + u == 0 ? v[u] : s + v[u];
+            a.res.p[w0 + u][j] = 0.0f;
           }
         }
-        if (w != leader) store4<false>(res.p[w] + j, v4f{v[0], v[1], v[2], v[3]});
       }
-      if (w0 + 4 < w_count) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int w = w0 + 4 + i < w_count ? w0 + 4 + i : w_count - 1;
-          a[i] = load4g<false, GT>(g.p[w], j);
-          b[i] = load4<false>(res.p[w] + j);
-        }
-      }
+      a.idx_out[m] = (int32_t)j;
+      a.sum_out[m] = s;
+      buf[at] = s;
     }
-    if (any) {
+    if (a.update == nullptr) continue;
+    __syncthreads();
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (at[e] >= 0) sum_out[at[e]] = s[e];
-    }
-    if (update) store4<false>(update + j, v4f{s[0], s[1], s[2], s[3]});
-  } else {
-    for (int64_t i = j; i < n; ++i) {  // the vector's last elements
-      const int at = slot[i - lo];
-      float s = 0.0f;
-      for (int w = 0; w < w_count; ++w) {
-        float v = w == leader ? 0.0f : load1g<GT>(g.p[w], i) + res.p[w][i];
-        if (at >= 0) {
-          if (w == leader) v = lead[i - lo];
-          if (vals) vals[(size_t)w * (size_t)k + (size_t)at] = v;
-          s = w == 0 ? v : s + v;
-          v = 0.0f;
-        }
-        if (w != leader) res.p[w][i] = v;
-      }
-      if (at >= 0) sum_out[at] = s;
-      if (update) update[i] = s;
-    }
-  }
-}
-
-// The rest of a step whose pass has run on every worker: the outputs of the selection, vals, ordered sums and +0.0
-// at the kept positions, and the dense update (if wanted), a tile of kSmallTile elements a block.
-__global__ void __launch_bounds__(256)
-k_small_gather(SelParams p, SmallScratch ss, PtrTable tab, int w_count, int64_t k, float* __restrict__ vals,
-               float* __restrict__ sum_out, float* __restrict__ update) {
-  __shared__ __attribute__((aligned(16))) float buf[kSmallTile];
-  const int tid = threadIdx.x;
-  const int64_t n = p.n, lo = (int64_t)blockIdx.x * kSmallTile;
-  reinterpret_cast<float4*>(buf)[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-  __syncthreads();
-  int32_t* __restrict__ idx_out = p.idx_out;
-  const bool fine = small_kept(p, ss, lo, [&](uint32_t m, int64_t e, uint32_t) {
-    idx_out[m] = (int32_t)e;
-    float s = 0.0f;
-    for (int w0 = 0; w0 < w_count; w0 += 8) {  // eight independent loads in flight, then the ordered adds
-      float v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (w0 + q < w_count) v[q] = tab.p[w0 + q][e];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        if (w0 + q < w_count) {
-          if (vals) vals[(size_t)(w0 + q) * (size_t)k + (size_t)m] = v[q];
-          s = (w0 + q == 0) ? v[q] : (s + v[q]);
-          tab.p[w0 + q][e] = 0.0f;
-        }
+    for (int u = 0; u < 2; ++u) {
+      const int at = 4 * (u * T + tid);
+      const int64_t j = (int64_t)c * C + at;
+      if (j + 4 <= n) {
+        store4<false>(a.update + j, reinterpret_cast<const v4f*>(pool)[u * T + tid]);
+      } else {
+        for (int e = 0; j + e < n; ++e) a.update[j + e] = buf[at + e];
       }
     }
-    sum_out[m] = s;
-    buf[e - lo] = s;
-  });
-  if (!fine || update == nullptr) return;
-  __syncthreads();
-  const int64_t j = lo + 4 * tid;
-  if (j + 4 <= n) {
-    const float4 t4 = reinterpret_cast<const float4*>(buf)[tid];
-    store4<false>(update + j, v4f{t4.x, t4.y, t4.z, t4.w});
-  } else {
-    for (int64_t i = j; i < n; ++i) update[i] = buf[i - lo];
   }
 }
 

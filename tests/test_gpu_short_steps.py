@@ -1,4 +1,4 @@
-"""Steps on short vectors, which run in three launches: against the oracle and against the general launch sequence."""
+"""Steps on short vectors, which run in one launch: against the oracle and against the general launch sequence."""
 
 import numpy as np
 import pytest
@@ -55,6 +55,28 @@ def test_short_steps_match_the_oracle(n, kind):
             assert_step_matches(got, want, mode)
             on_device = mode in (orc.MODE_VAR, orc.MODE_VAR_G) and w < 8
             assert gpu_util.FORCED or runner.ctx.select_info()["short"] == (n <= (3 << 18 if on_device else 1 << 20))
+
+
+# chunks of 2048, 4096 and 8192 elements (up to 2^18, 2^20 and 2^21): one, whole ones, an element more or less, the
+# last one short; one worker, more than are loaded at a time, and the most
+@pytest.mark.parametrize("n", [2047, 4097, 65536, (1 << 18) - 3, 1 << 18, (1 << 18) + 1, (1 << 20) + 8191])
+@pytest.mark.parametrize("w", [1, 6, 64])
+def test_short_steps_at_the_edges_of_chunks(n, w):
+    import paper_2312_02493_amd as lib
+
+    rng = np.random.default_rng(n + w)
+    k = max(1, min(n // 10, 16384))
+    runner = GpuRunner(w, n, k)
+    runner.ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, 1 << 21)
+    res = [np.zeros(n, np.float32) for _ in range(w)]
+    runner.load_res(res)
+    for step_no, mode in enumerate((orc.MODE_STAR, orc.MODE_VAR, orc.MODE_STAR), 1):
+        g = [_vector(rng, n, "ties" if step_no == 2 else "normal", r) for r in range(w)]
+        want = orc.step(g, res, k, mode, step_no=step_no)
+        runner.load_g(g)
+        assert_step_matches(runner.step(k, mode, step_no, want_vals=step_no == 1), want, mode)
+        assert gpu_util.FORCED or runner.ctx.select_info()["short"] == 1
+        res = want.residual
 
 
 # the same step on both launch sequences, in turn on one context (the short one must leave its scratch as it found it)
