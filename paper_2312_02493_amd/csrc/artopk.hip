@@ -821,6 +821,22 @@ void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const 
                        gp.m_hi);
 }
 
+// Elements a wave of k_tail takes where it is the better way to select, else 0.
+int64_t tail_range(const Plan& pl, int64_t n, int source) {
+  if (pl.use_table || pl.nseg > kTailRanges) return 0;
+  const int64_t waves = (int64_t)(kTailRanges / pl.nseg) * kTailWaves;
+  const int64_t elems = ((n + waves - 1) / waves + kTailRow - 1) / kTailRow * kTailRow;
+  // Survivors a wave is expected to have: the candidates below the threshold, or the guess' margin and the rest of its
+  // bin, come to less than half of k.
+  if (1.5 * (double)pl.desc[0].k / (double)waves > (double)kTailKeep) return 0;
+  // (Denser ones, 138 M and one in 33: the list kernels read their entries from memory a few times less.)
+  // With nothing there yet, two passes over the vector and short chunks stand up better to runs of large values, unless a
+  // wave can keep all its elements (us, list kernels / this, normal values and a run: 8 x 2 M 100/66 98/123, 1 x 11.7 M
+  // 61/58 66/92, 1 x 3 M 46/45 47/47, 16 x 1.2 M 98/72 94/117).
+  if (source == kTailNone && (pl.nseg < 2 || elems > kTailKeep)) return 0;
+  return elems;
+}
+
 // Top-k of every segment of the plan on the vector tab.p[*leader_dev]; the
 // scratch must have been cleared.  If hist_ready the per-chunk suffix
 // histograms are already in S (flat plans only: pass A built them, in slot
@@ -840,6 +856,18 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   p.zero_vec = zero_vec;
   LeaderArgs la{};
   if (leader_args) la = *leader_args;
+  const int source = spans ? kTailSpans : hist_ready ? kTailHist : kTailNone;
+  const int64_t tail_elems = guessed && !spans ? 0 : tail_range(pl, n, source);
+  if (tail_elems > 0) {
+    if (spans) {
+      p.tiles = span_buf(c, *spans, n);
+      p.use_mcount = 1;
+    }
+    const unsigned ranges = (unsigned)((n + kTailWaves * tail_elems - 1) / (kTailWaves * tail_elems));
+    hipLaunchKernelGGL(k_tail, dim3(ranges, nseg), dim3(64 * kTailWaves), 0, st, p, la, source, tail_elems);
+    HIP_TRY(c, hipGetLastError());
+    return ARTOPK_OK;
+  }
   // the per-chunk kernels: one block per chunk of a segmented layout, else a (chunks, segments) grid
   const dim3 chunk_grid = p.chunk_map ? dim3((unsigned)pl.total_chunks, 1) : dim3(pl.max_chunks, nseg);
 

@@ -391,28 +391,24 @@ __device__ __forceinline__ double wave_variance(const double* __restrict__ parti
   const double* __restrict__ pq = pm + nblk;
   const double r = get(pm);
   double n = 0.0, a = 0.0, bq = 0.0;
-  int b = lane;
-  for (; b + 448 < nblk; b += 512) {  // eight blocks' triples in flight per lane
+  for (int b = lane; b < nblk; b += 512) {  // eight blocks' triples in flight per lane (absent ones add nothing)
     double nb[8], mb[8], qb[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      nb[j] = get(pn + b + 64 * j);
-      mb[j] = get(pm + b + 64 * j);
-      qb[j] = get(pq + b + 64 * j);
+      const int at = b + 64 * j < nblk ? b + 64 * j : lane;
+      nb[j] = get(pn + at);
+      mb[j] = get(pm + at);
+      qb[j] = get(pq + at);
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const double d = mb[j] - r;
-      n += nb[j];
-      a += nb[j] * d;
-      bq += qb[j] + nb[j] * d * d;
+      if (b + 64 * j < nblk) {
+        const double d = mb[j] - r;
+        n += nb[j];
+        a += nb[j] * d;
+        bq += qb[j] + nb[j] * d * d;
+      }
     }
-  }
-  for (; b < nblk; b += 64) {
-    const double nb = get(pn + b), d = get(pm + b) - r, q = get(pq + b);
-    n += nb;
-    a += nb * d;
-    bq += q + nb * d * d;
   }
   n = wave_allsum(n);
   a = wave_allsum(a);
@@ -1637,12 +1633,12 @@ struct LeaderArgs {
 };
 
 // Finishes the per-worker variances from the fused pass' partials and takes the first
-// worker of largest variance (same arithmetic as k_leader).  All 1024 threads of the
+// worker of largest variance (same arithmetic as k_leader).  All threads of the
 // block call it; returns the leader in thread 0 only.
 __device__ int block_take_leader(const LeaderArgs& la) {
   const int t = threadIdx.x;
   const int wave = t >> 6, lane = t & 63;
-  for (int w = wave; w < la.w_count; w += 16) {
+  for (int w = wave; w < la.w_count; w += (int)blockDim.x / 64) {
     const double v = wave_variance(la.partials, w, la.nblk);
     if (lane == 0) {
       la.var_scratch[w] = v;
@@ -3182,6 +3178,602 @@ k_level2(SelParams p) {
   }
 }
 
+
+// ---------------------------------------------------------------------------
+// k_tail : a flat selection from the top digits on (or several at a time, one per blockIdx.y), in one launch instead of
+// four behind a pass that counted the top digits (pick, compaction, list digits, final pass), six behind the read-only
+// marking or five behind nothing.  Those are bound by latency, 5 us for a launch and a trip to memory or two in each; here
+// the blocks wait for each other in between (a microsecond), and a block's survivors (keys that reach the threshold's
+// top digit, or the guessed bound) stay on chip, an eighth with each wave, in order.  Before and after, us: select 138 M, one
+// in a hundred kept 181 / 171, with values in runs 402 / 183, in 54 layers of different scale 237 / 198, all equal 1910 /
+// 1080; 8 selections on 25.6 M 269 / 244; steps 11.7 M x 8 327 / 322, all equal 618 / 547, 25.6 M x 8 in 16 bits 451 / 445.
+//   kTailSpans: the pieces of k_mark_spans, if their bound holds (k_pick_mask's rule) and a wave can keep its share of
+// them.  How many there are in front of every chunk is known, so each wave has as many as any other, however they are
+// spread.  kTailHist: the top digits' counts of a fused pass; kTailNone (and a bound that does not hold): nothing, the
+// blocks count them first.  Each wave then has as many elements as any other; survivors that do not fit go to its part
+// of the list's memory, and if they do not fit there either the wave reads its elements again each time.
+//   The blocks count the threshold's next digit over their survivors, wait, pick it each for itself, and so on; the last
+// count also says how many kept entries lie in front of each range, and every wave then writes its own.  A block that has
+// waited for the first counts for a while takes on ranges that nobody has and collects them anew each time (see
+// k_small_step: nothing depends on how many blocks run at a time).
+// wave_elems: a wave's elements, a multiple of kTailRow.  grid = (ranges, vectors), block = 64 kTailWaves.
+// The counts lie in the segment's scratch block (cleared before), rows and above in S's memory.
+// ---------------------------------------------------------------------------
+constexpr int kTailSpans = 0, kTailHist = 1, kTailNone = 2;
+constexpr int kTailRanges = 256;   // blocks of a launch, at most: one per compute unit
+constexpr int kTailWaves = 8;      // (16 a block: 87 registers of each thread spilled, and everything took 35 us longer)
+constexpr int kTailKeep = 2000;    // survivors a wave keeps on chip
+constexpr int kTailRow = 256;
+constexpr int kTailWaits = 4, kTailArrive = 8;
+// in the words of kSegHist2 behind the last digit's 128 counts: whether somebody has taken a range, the waits' counters
+constexpr int kTailClaim = 128, kTailCount = 512;
+static_assert(kTailClaim + kTailRanges <= kTailCount && kTailCount + kTailWaits * kTailArrive * 32 <= kHistBins, "they fit");
+constexpr int kTailHelpSpins = 256;
+
+// Adds 1 to hist[bin] for every active lane; lanes with the first one's bin (all, where values are equal) in one addition.
+__device__ __forceinline__ void wave_count(uint32_t* hist, uint32_t bin) {
+  const uint32_t one = __builtin_amdgcn_readfirstlane(bin);
+  const uint64_t same = __ballot(bin == one);
+  if (bin != one)
+    atomicAdd(&hist[bin], 1u);
+  else if (popc_lt(same) == 0u)
+    atomicAdd(&hist[one], (uint32_t)__popcll(same));
+}
+
+// Threads' loop over the elements of x[lo, hi) whose key reaches `bound`, the 64 lanes of a wave together: use(element,
+// raw bits), in no order.
+template <typename Use>
+__device__ __forceinline__ void wave_each(const float* __restrict__ x, int64_t lo, int64_t hi, uint32_t bound, Use use) {
+  const int lane = (int)lane_id();
+  for (int64_t base = lo; base < hi; base += kSpanStep) {
+    uint4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t j = base + 4 * (lane + 64 * u);
+      v[u] = make_uint4(0u, 0u, 0u, 0u);
+      if (base + 256 * u + 256 <= hi) {  // (the same in every lane)
+        v[u] = *reinterpret_cast<const uint4*>(x + j);
+      } else if (j + 4 <= hi) {
+        v[u] = *reinterpret_cast<const uint4*>(x + j);
+      } else {
+        if (j + 0 < hi) v[u].x = __float_as_uint(x[j + 0]);
+        if (j + 1 < hi) v[u].y = __float_as_uint(x[j + 1]);
+        if (j + 2 < hi) v[u].z = __float_as_uint(x[j + 2]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t j = base + 4 * (lane + 64 * u);
+      const uint32_t raw[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (j + e < hi && (raw[e] & kKeyMask) >= bound) use(j + e, raw[e]);
+    }
+  }
+}
+
+// The elements of x[lo, hi) whose key reaches `bound`, in order, the first cap of them: put(number, element, raw bits);
+// returns their number, or more than cap.  The 64 lanes of a wave call it; lo is a multiple of 4.  (wave_span with the bound as a key.)
+template <typename Put>
+__device__ __forceinline__ uint32_t wave_collect(const float* __restrict__ x, int64_t lo, int64_t hi, uint32_t bound,
+                                                 SpanQueue& qu, uint32_t cap, Put put) {
+  const uint32_t lane = lane_id();
+  uint32_t count = 0u, head = 0u, queued = 0u;
+  auto take = [&](uint32_t m) __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint32_t p = (head + lane) & 127u;
+    const uint4 v = qu.val[p];
+    const uint32_t g = qu.group[p];
+    const uint32_t raw[4] = {v.x, v.y, v.z, v.w};
+    uint32_t own = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) own |= (raw[e] & kKeyMask) >= bound && (int64_t)4 * g + e < hi ? 1u << e : 0u;
+    if (lane >= m) own = 0u;
+    const uint32_t c = (uint32_t)__popc(own);
+    uint32_t before = 0u, total = 0u;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const uint64_t plane = __ballot((c >> b) & 1u);
+      before += popc_lt(plane) << b;
+      total += (uint32_t)__popcll(plane) << b;
+    }
+    uint32_t pos = count + before;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if ((own >> e) & 1u) {
+        if (pos < cap) put(pos, (int64_t)4 * g + e, raw[e]);
+        ++pos;
+      }
+    }
+    count += total;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  for (int64_t base = lo; base < hi; base += kSpanStep) {
+    const uint32_t g0 = (uint32_t)(base >> 2) + lane;
+    uint4 v[8];
+    if (base + kSpanStep <= hi) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint4*>(x + 4 * (int64_t)(g0 + 64u * u));
+    } else {  // the wave's last rows, the vector's end: absent elements as 0, which only a bound of 0 takes (take() looks again)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t j = 4 * (int64_t)(g0 + 64u * u);
+        v[u] = make_uint4(0u, 0u, 0u, 0u);
+        if (base + 256 * u + 256 <= hi) {  // (the same in every lane)
+          v[u] = *reinterpret_cast<const uint4*>(x + j);
+        } else if (j + 4 <= hi) {
+          v[u] = *reinterpret_cast<const uint4*>(x + j);
+        } else {
+          if (j + 0 < hi) v[u].x = __float_as_uint(x[j + 0]);
+          if (j + 1 < hi) v[u].y = __float_as_uint(x[j + 1]);
+          if (j + 2 < hi) v[u].z = __float_as_uint(x[j + 2]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t a = v[u].x & kKeyMask, b = v[u].y & kKeyMask, c = v[u].z & kKeyMask, d = v[u].w & kKeyMask;
+      const uint32_t ab = a > b ? a : b, cd = c > d ? c : d;
+      const bool hit = (ab > cd ? ab : cd) >= bound;
+      const uint64_t hits = __ballot(hit);
+      if (hits != 0ull) {
+        if (hit) {
+          const uint32_t p = (head + queued + popc_lt(hits)) & 127u;
+          qu.val[p] = v[u];
+          qu.group[p] = g0 + 64u * u;
+        }
+        queued += (uint32_t)__popcll(hits);
+        if (queued >= 64u) {
+          take(64u);
+          head += 64u;
+          queued -= 64u;
+        }
+      }
+    }
+    if (count > cap) return count;  // (no use in going on)
+  }
+  if (queued != 0u) take(queued);
+  return count;
+}
+
+__global__ void __launch_bounds__(64 * kTailWaves)
+k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
+  constexpr int WAVES = kTailWaves, T = 64 * WAVES, BPT = kHistBins / T;
+  __shared__ uint2 list[WAVES][kTailKeep];  // (element, raw bits)
+  __shared__ union {
+    __attribute__((aligned(16))) uint32_t hist[kHistBins];
+    SpanQueue qu[WAVES];
+  } pool;
+  __shared__ __attribute__((aligned(16))) uint32_t tail[128];
+  __shared__ SelState st, st1;
+  __shared__ uint32_t part[WAVES];
+  __shared__ uint64_t wtot[WAVES], wfront[WAVES];
+  __shared__ uint16_t owned[kTailRanges];
+  __shared__ int verdict;
+  __shared__ uint32_t chunk_at[kMaxChunks + 1];  // entries in front of every chunk of the marking (kTailSpans)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nranges = gridDim.x, vec = blockIdx.y, c0 = blockIdx.x;
+  if (*p.err != 0u) return;  // (set before this launch: the same in every block)
+  if (tid == 0) verdict = -1;
+  if (la.partials != nullptr) {  // (every block finds, and writes, the same)
+    const int best = block_take_leader(la);
+    if (tid == 0) verdict = best;
+  }
+  __syncthreads();
+  const SegView sv = seg_view(p, vec, verdict);
+  const float* x = sv.x;
+  const int64_t n = p.n;
+  const uint32_t k = sv.d.k;
+  uint32_t* const claim = sv.hist2 + kTailClaim;
+  uint32_t* const count = sv.hist2 + kTailCount;
+  // rows and above of all the launch's ranges
+  uint32_t* const rows = p.S + (size_t)vec * nranges * 128;
+  uint32_t* const above = p.S + (size_t)kTailRanges * 128 + (size_t)vec * nranges;
+  __syncthreads();  // (verdict has been read)
+  if (tid == 0) {
+    verdict = __hip_atomic_exchange(&claim[c0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ? 1 : 0;
+    owned[0] = (uint16_t)c0;
+    st = SelState{};
+    st.hi = kKeyMask;
+    st.need = k;
+  }
+  if (tid < 128) tail[tid] = 0u;
+  __syncthreads();
+  if (verdict != 0) return;
+  int n_owned = 1;
+
+  auto arrive = [&](int b, int c) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+      __hip_atomic_fetch_add(&count[(b * kTailArrive + c % kTailArrive) * 32], 1u, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto arrived = [&](int b) __attribute__((always_inline)) {
+    uint32_t v = lane < kTailArrive ? load_through(&count[(b * kTailArrive + lane) * 32]) : 0u;
+    v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 2, 64);
+    v += __shfl_xor(v, 4, 64);
+    return __builtin_amdgcn_readfirstlane(v) == (uint32_t)nranges;
+  };
+  auto wait = [&](int b, int spins) __attribute__((always_inline)) {
+    if (wave == 0) {
+      bool ok = arrived(b);
+      for (int i = 0; !ok && i < spins; ++i) ok = arrived(b);
+      if (lane == 0) verdict = ok ? 1 : 0;
+    }
+    __syncthreads();
+    const bool ok = verdict != 0;
+    __syncthreads();
+    return ok;
+  };
+  // this wave's elements of range c
+  auto lo_of = [&](int c) __attribute__((always_inline)) { return ((int64_t)c * WAVES + wave) * wave_elems; };
+  auto hi_of = [&](int c) __attribute__((always_inline)) {
+    const int64_t hi = lo_of(c) + wave_elems;
+    return hi < n ? hi : n;
+  };
+  auto clear_hist = [&]() __attribute__((always_inline)) {
+    __syncthreads();
+    for (int i = tid; i < kHistBins / 4; i += T) reinterpret_cast<uint4*>(pool.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+  };
+  auto pick = [&](const uint32_t* hist, int digit) __attribute__((always_inline)) {
+    const int bins = (int)digit_mask(digit) + 1;
+    uint32_t h[BPT];
+#pragma unroll
+    for (int j = 0; j < BPT / 2; ++j) {
+      const uint64_t q = BPT * tid < bins ? load_through(reinterpret_cast<const uint64_t*>(hist) + BPT / 2 * tid + j) : 0ull;
+      h[2 * j] = (uint32_t)q;
+      h[2 * j + 1] = (uint32_t)(q >> 32);
+    }
+    block_pick_bins<T>(st, h, digit, part, p.err);
+  };
+
+  // what the list of the first range, and every reading of the others, holds: keys that reach this
+  uint32_t bound = 0u, total = 0u;
+  bool spans = false, listed = false;
+  uint32_t mine = 0u;  // the wave's entries in `list`
+  if (source == kTailSpans) {  // (k_pick_mask's rule)
+    bound = sv.ctrl[1];
+    constexpr int PER = kMaxChunks / T;
+    uint32_t m[PER], sum = 0u;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      m[j] = PER * tid + j < sv.d.geom.nchunks ? sv.mcount[PER * tid + j] : 0u;
+      sum += m[j];
+    }
+    uint32_t upto = block_prefix_incl<T>(sum, part, &total) - sum;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {  // (chunks that are not there: `total`)
+      chunk_at[PER * tid + j] = upto;
+      upto += m[j];
+    }
+    if (tid == 0) chunk_at[kMaxChunks] = total;
+    uint64_t limit = (uint64_t)k + ((uint64_t)n >> 3);
+    if (limit > sv.d.cap) limit = sv.d.cap;
+    spans = bound != kNoGuess && total >= k && total <= limit && total <= (uint32_t)(nranges * WAVES * kTailKeep);
+    if (!spans) bound = 0u;
+  }
+  const uint32_t share = spans ? (total + (uint32_t)(nranges * WAVES) - 1u) / (uint32_t)(nranges * WAVES) : 0u;
+  // what a wave does not keep on chip goes to its part of the survivor list's memory
+  const uint32_t room = sv.d.cap / (uint32_t)(nranges * WAVES);
+  auto more_of = [&](int c) __attribute__((always_inline)) { return sv.list + (size_t)(c * WAVES + wave) * room; };
+  int cur = -1;  // the range whose survivors `list` holds, if they fit
+  // The survivors of range c, from the pieces or from the vector; all threads call it.
+  auto collect = [&](int c) __attribute__((always_inline)) {
+    cur = c;
+    mine = 0u;
+    __syncthreads();  // (`pool` is free)
+    if (spans) {
+      // entries [e0, e1) of all, in order: this wave's
+      const uint64_t from = (uint64_t)((uint32_t)c * WAVES + (uint32_t)wave) * share;
+      const uint32_t e0 = from < total ? (uint32_t)from : total, e1 = total - e0 < share ? total : e0 + share;
+      if (e0 < e1) {
+        int ch = 0;  // the chunk of entry e0: the last with no more entries in front of it
+#pragma unroll
+        for (int w = kMaxChunks / 2; w > 0; w >>= 1) ch += chunk_at[ch + w] <= e0 ? w : 0;
+        const int64_t span = p.tiles.span, nspans = (n + span - 1) / span;
+        uint32_t at = chunk_at[ch];  // entries in front of span s0
+        for (int64_t s0 = (int64_t)ch * sv.d.geom.chunk_elems / span; s0 < nspans && at < e1; s0 += 64) {
+          const uint32_t cnt = s0 + lane < nspans ? sv.tcnt[s0 + lane] : 0u;
+          const uint32_t incl = wave_incl_scan(cnt);
+          const uint64_t some = __ballot(at + incl > e0 && at + incl - cnt < e1 && cnt != 0u);
+          for (uint64_t left = some; left != 0ull;) {  // four spans' loads in flight
+            uint2 ent[4];
+            uint32_t put[4], cn[4];
+            const uint2* piece[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int s = left != 0ull ? __builtin_ctzll(left) : 0;
+              cn[q] = left != 0ull ? __shfl(cnt, s, 64) : 0u;
+              put[q] = at + __shfl(incl, s, 64) - __shfl(cnt, s, 64);  // the number of its first entry
+              piece[q] = sv.tbuf + (size_t)(s0 + s) * (size_t)sv.tcap;
+              left &= left - 1ull;
+              if (cn[q] > (uint32_t)sv.tcap) {  // more than its piece holds: from the vector
+                const int64_t x0 = (s0 + s) * span, x1 = x0 + span < n ? x0 + span : n;
+                (void)wave_collect(x, x0, x1, bound, pool.qu[wave], kQuotaInf,
+                                   [&](uint32_t m, int64_t j, uint32_t raw) __attribute__((always_inline)) {
+                                     const uint32_t e = put[q] + m;
+                                     if (e >= e0 && e < e1) list[wave][e - e0] = make_uint2((uint32_t)j, raw);
+                                   });
+                cn[q] = 0u;
+              }
+              ent[q] = piece[q][(uint32_t)lane < cn[q] ? lane : 0];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              for (uint32_t m = (uint32_t)lane; m < cn[q]; m += 64u) {
+                const uint32_t e = put[q] + m;
+                if (m >= 64u) ent[q] = piece[q][m];
+                if (e >= e0 && e < e1) list[wave][e - e0] = ent[q];
+              }
+            }
+          }
+          at += __shfl(incl, 63, 64);
+        }
+        mine = e1 - e0;
+      }
+    } else {
+      mine = wave_collect(x, lo_of(c), hi_of(c), bound, pool.qu[wave], (uint32_t)kTailKeep + room,
+                          [&](uint32_t m, int64_t j, uint32_t raw) __attribute__((always_inline)) {
+                            if (m < (uint32_t)kTailKeep)
+                              list[wave][m] = make_uint2((uint32_t)j, raw);
+                            else
+                              more_of(c)[m - kTailKeep] = make_uint2((uint32_t)j, raw);
+                          });
+    }
+    __syncthreads();
+    listed = mine <= (uint32_t)kTailKeep + room;
+  };
+  auto entry = [&](int c, uint32_t i) __attribute__((always_inline)) {
+    return i < (uint32_t)kTailKeep ? list[wave][i] : more_of(c)[i - kTailKeep];
+  };
+  // use(element, raw bits) for every survivor of range c, in some thread
+  auto each = [&](int c, auto use) __attribute__((always_inline)) {
+    if (listed && c == cur) {
+      for (uint32_t i = (uint32_t)lane; i < mine; i += 64u) {
+        const uint2 ent = entry(c, i);
+        use((int64_t)ent.x, ent.y);
+      }
+    } else {
+      wave_each(x, lo_of(c), hi_of(c), bound, use);
+    }
+  };
+  // counts digit `digit` of range c's candidates and adds that to dst
+  auto digits = [&](int c, int digit, uint32_t* dst) __attribute__((always_inline)) {
+    clear_hist();
+    const uint32_t lo = st.lo, hi = st.hi;
+    const int sh = digit_shift(digit);
+    each(c, [&](int64_t, uint32_t raw) __attribute__((always_inline)) {
+      const uint32_t kk = raw & kKeyMask;
+      if (kk >= lo && kk <= hi) wave_count(pool.hist, (kk >> sh) & 0xfffu);
+    });
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      const uint32_t v = pool.hist[i * T + tid];
+      if (v) atomicAdd(&dst[i * T + tid], v);
+    }
+  };
+  auto report_state = [&]() __attribute__((always_inline)) {  // what select_info reports: the state behind the top digit
+    st1 = st;
+    st1.compact_level = spans || fits_list(st, sv.d.cap) ? 1u : 0u;
+    st1.list_count = spans ? total : st1.compact_level ? st.n_gt + st.cand : 0u;
+    st1.use_mask = spans ? 1u : 0u;
+    st1.list_lo = spans ? bound : 0u;
+    st1.need_full = source == kTailSpans && !spans ? 1u : 0u;
+  };
+  auto give_up = [&]() __attribute__((always_inline)) {
+    if (tid == 0) atomicOr(p.err, kErrWait);
+  };
+
+  int stage = 0;
+  if (!spans && source == kTailHist) {  // the top digits' counts are there
+    uint32_t h[BPT];
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) h[j] = 0u;
+    for (int r0 = 0; r0 < sv.htop_reps; r0 += 8) {
+      uint4 q[8][BPT / 4];
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int j = 0; j < BPT / 4; ++j)
+          q[r][j] = reinterpret_cast<const uint4*>(sv.htop + (size_t)(r0 + r < sv.htop_reps ? r0 + r : r0) * kHistBins)
+              [BPT / 4 * tid + j];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (r0 + r < sv.htop_reps) {
+#pragma unroll
+          for (int j = 0; j < BPT / 4; ++j) {
+            h[4 * j + 0] += q[r][j].x;
+            h[4 * j + 1] += q[r][j].y;
+            h[4 * j + 2] += q[r][j].z;
+            h[4 * j + 3] += q[r][j].w;
+          }
+        }
+      }
+    }
+    block_pick_bins<T>(st, h, 0, part, p.err);
+    bound = st.lo;
+    stage = 1;
+  }
+  // 0: the top digits of the survivors, or of everything where no bound is known yet; 1: the second digits of the
+  // candidates; 2: the last ones; 3: the outputs
+  for (int first = stage;; ++stage) {
+    const uint32_t klo = st.lo, khi = st.hi, quota = st.need, digit = klo & 0x7fu;
+    const int b = stage - first;
+    uint32_t* const dst = stage == 0 ? sv.hseg : stage == 1 ? sv.hist1 : sv.hist2;
+    for (int done = 0, look = c0 + 1;;) {
+      for (; done < n_owned; ++done) {
+        const int c = owned[done];
+        if (c != cur && (spans || stage > 0)) collect(c);
+        if (stage < 2) {
+          digits(c, stage, dst);
+          arrive(b, c);
+          continue;
+        }
+        if (stage == 2) {
+          uint32_t up = 0u;
+          each(c, [&](int64_t, uint32_t raw) __attribute__((always_inline)) {
+            const uint32_t kk = raw & kKeyMask;
+            up += kk > khi ? 1u : 0u;
+            if (kk >= klo && kk <= khi) wave_count(tail, kk & 0x7fu);
+          });
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) up += __shfl_xor(up, o, 64);
+          if (lane == 0) part[wave] = up;
+          __syncthreads();
+          if (wave == 0) {  // lane's digits 2 lane and 2 lane + 1
+            const uint32_t t0 = tail[2 * lane], t1 = tail[2 * lane + 1];
+            if (t0) atomicAdd(&sv.hist2[2 * lane], t0);
+            if (t1) atomicAdd(&sv.hist2[2 * lane + 1], t1);
+            uint32_t s = t0 + t1;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+              const uint32_t y = __shfl_down(s, off, 64);
+              if (lane + off < 64) s += y;
+            }
+            store_through(reinterpret_cast<uint64_t*>(rows + (size_t)c * 128) + lane, ((uint64_t)(s - t0) << 32) | s);
+            tail[2 * lane] = tail[2 * lane + 1] = 0u;
+            if (lane == 0) {
+              uint32_t sum = 0u;
+#pragma unroll
+              for (int w = 0; w < WAVES; ++w) sum += part[w];
+              store_through(&above[c], sum);
+            }
+          }
+          arrive(b, c);
+          continue;
+        }
+        // kept in front of the range: keys above the threshold, and at it
+        uint64_t before = 0ull;
+        if (tid < c) {
+          const uint32_t* row = rows + (size_t)tid * 128 + digit;
+          const uint32_t at = load_through(row), more = digit < 127u ? load_through(row + 1) : 0u;
+          before = ((uint64_t)(load_through(&above[tid]) + more) << 32) | (at - more);
+        }
+        before = wave_allsum_u64(before);
+        // the wave's own
+        uint32_t nA = 0u, nB = 0u;
+        each(c, [&](int64_t, uint32_t raw) __attribute__((always_inline)) {
+          const uint32_t kk = raw & kKeyMask;
+          nA += kk > khi ? 1u : 0u;
+          nB += kk >= klo && kk <= khi ? 1u : 0u;
+        });
+        const uint64_t own = wave_allsum_u64(((uint64_t)nA << 32) | nB);
+        __syncthreads();  // (wtot and wfront are free)
+        if (lane == 0) {
+          wtot[wave] = own;
+          wfront[wave] = before;
+        }
+        __syncthreads();
+        uint64_t front = 0ull;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) front += wfront[w] + (w < wave ? wtot[w] : 0ull);
+        uint32_t runA = (uint32_t)(front >> 32), runB = (uint32_t)front;
+        auto keep = [&](uint32_t a, uint32_t b, int64_t j, uint32_t raw) __attribute__((always_inline)) {
+          const uint32_t m = a + (b < quota ? b : quota);
+          if (m >= k) return;
+          sv.idx_out[m] = (int32_t)j;
+          if (sv.vals_row) sv.vals_row[m] = __uint_as_float(raw);
+          if (p.zero_vec) p.zero_vec[j] = 0.0f;
+        };
+        if (listed) {
+          for (uint32_t q = 0u; q < mine; q += 64u) {
+            const bool ok = q + (uint32_t)lane < mine;
+            const uint2 ent = entry(c, ok ? q + (uint32_t)lane : mine - 1u);
+            const uint32_t kk = ent.y & kKeyMask;
+            const bool is_a = ok && kk > khi, is_b = ok && kk >= klo && kk <= khi;
+            const uint64_t ma = __ballot(is_a), mb = __ballot(is_b);
+            const uint32_t a = runA + popc_lt(ma), b = runB + popc_lt(mb);
+            if (is_a || (is_b && b < quota)) keep(a, b, (int64_t)ent.x, ent.y);
+            runA += (uint32_t)__popcll(ma);
+            runB += (uint32_t)__popcll(mb);
+          }
+        } else {
+          const int64_t hi_e = hi_of(c);
+          for (int64_t base = lo_of(c); base < hi_e; base += 256) {
+            const int64_t j = base + 4 * lane;
+            uint32_t raw[4] = {0u, 0u, 0u, 0u};
+            if (j + 4 <= hi_e) {
+              const uint4 v = *reinterpret_cast<const uint4*>(x + j);
+              raw[0] = v.x, raw[1] = v.y, raw[2] = v.z, raw[3] = v.w;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 3; ++e)
+                if (j + e < hi_e) raw[e] = __float_as_uint(x[j + e]);
+            }
+            uint32_t isA = 0u, isB = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const uint32_t kk = raw[e] & kKeyMask;
+              isA |= j + e < hi_e && kk > khi ? 1u << e : 0u;
+              isB |= j + e < hi_e && kk >= klo && kk <= khi ? 1u << e : 0u;
+            }
+            if (__ballot((isA | isB) != 0u) == 0ull) continue;
+            const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
+            uint32_t a = runA, b = runB;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+              const uint64_t pa = __ballot((cA >> q) & 1u), pb = __ballot((cB >> q) & 1u);
+              a += popc_lt(pa) << q;
+              b += popc_lt(pb) << q;
+              runA += (uint32_t)__popcll(pa) << q;
+              runB += (uint32_t)__popcll(pb) << q;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const bool is_a = (isA >> e) & 1u, is_b = (isB >> e) & 1u;
+              if (is_a || (is_b && b < quota)) keep(a, b, j + e, raw[e]);
+              a += is_a ? 1u : 0u;
+              b += is_b ? 1u : 0u;
+            }
+          }
+        }
+      }
+      if (stage == 3) return;
+      if (wait(b, b == 0 ? kTailHelpSpins : kSpinLimit)) break;
+      if (b > 0) return give_up();
+      // a range that nobody has taken: its block does not run yet, and may not before this one is done
+      if (tid == 0) {
+        verdict = -1;
+        for (int i = 0; i < nranges && verdict < 0; ++i, ++look) {
+          const int c = look % nranges;
+          if (load_through(&claim[c]) == 0u &&
+              __hip_atomic_exchange(&claim[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+            verdict = c;
+        }
+        if (verdict >= 0) owned[n_owned] = (uint16_t)verdict;
+      }
+      __syncthreads();
+      const bool taken = verdict >= 0;
+      __syncthreads();
+      if (taken) {
+        ++n_owned;
+      } else {  // all belong to blocks that run
+        if (!wait(b, kSpinLimit)) return give_up();
+        break;
+      }
+    }
+    if (stage == 1 && tid == 0) report_state();
+    pick(dst, stage);
+    if (stage == 0 && !spans) bound = st.lo;
+    if (stage == 2) {
+      bool reports = false;
+      for (int i = 0; i < n_owned; ++i) reports = reports || owned[i] == 0;
+      if (reports && tid == 0) {
+        *sv.st = st1;
+        if (st.level != 3u) atomicOr(p.err, kErrSequence);
+      }
+      if (st.level != 3u) return;
+    }
+  }
+}
 
 // ---------------------------------------------------------------------------
 // k_tile_starts : tile_start[t] = number of kept indices below t * kPassTile, for

@@ -294,3 +294,34 @@ def test_segmented_leader_pass(start, g):
     assert np.array_equal(up.cpu().numpy().view(np.uint32), want.update.view(np.uint32))
     for r in range(w):
         assert np.array_equal(rd[r].cpu().numpy().view(np.uint32), want.residual[r].view(np.uint32))
+
+
+# steps on the histogram route: a wave's elements are rows of 256 (one row each, an element more, many); survivors of the
+# top digit that a wave keeps on chip, that go to the list's memory, and that do not fit there either
+@pytest.mark.parametrize("n", [(1 << 19), (1 << 19) + 1, 9_000_001])
+@pytest.mark.parametrize("kind", ["normal", "special", "run", "half", "equal"])
+def test_steps_whose_survivors_outgrow_a_wave(n, kind, monkeypatch):
+    from tests import gpu_util
+    from tests.gpu_util import GpuRunner, assert_step_matches
+
+    monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 0)
+    rng = np.random.default_rng(n)
+    w, kmax = 2, n // 4
+    g = [_values(rng, n, kind) for _ in range(w)]
+    if kind == "run":
+        for r, x in enumerate(g):
+            x[n // 3:n // 3 + n // 40] += np.float32(50.0)
+    elif kind == "half":
+        for x in g:
+            x[: n // 2] = (1.0 + 0.03 * rng.random(n // 2)).astype(np.float32)
+            rng.shuffle(x)
+    elif kind == "equal":
+        g = [np.full(n, np.float32(0.5 - r)) for r in range(w)]
+    runner = GpuRunner(w, n, kmax)
+    for step_no, k in enumerate((1, n // 100, kmax), 1):
+        res = [np.zeros(n, np.float32) for _ in range(w)]
+        want = orc.step(g, res, k, orc.MODE_STAR, step_no=step_no)
+        runner.load_g(g)
+        runner.load_res(res)
+        assert_step_matches(runner.step(k, orc.MODE_STAR, step_no, want_vals=True), want, orc.MODE_STAR)
+        runner.ctx.status()
