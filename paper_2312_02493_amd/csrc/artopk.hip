@@ -512,31 +512,31 @@ int enqueue_clear(artopk_ctx* c, const Plan& pl, int hist_slots, int32_t leader 
 // Launches the fused pass over grid.y workers with the wanted options.
 template <int STATS, int HIST, int GT>
 void launch_pass_a_g(artopk_ctx* c, dim3 grid, const PtrTable& g, const PtrTable& r, int64_t n, const ChunkGeom& geom,
-                     int hist_worker) {
+                     int hist_worker, bool by_tile) {
   Scratch& s = c->s;
   if (c->pass_a_nt)
     hipLaunchKernelGGL((k_pass_a<STATS, HIST, true, GT, kPassAThreads, kPassAU>), grid, dim3(kPassAThreads), 0,
-                       c->stream, g, r, n, geom, hist_worker, s.S, s.h_all, s.partials);
+                       c->stream, g, r, n, geom, hist_worker, by_tile ? nullptr : s.S, s.h_all, s.partials);
   else
     hipLaunchKernelGGL((k_pass_a<STATS, HIST, false, GT, kPassAThreads, kPassAU>), grid, dim3(kPassAThreads), 0,
-                       c->stream, g, r, n, geom, hist_worker, s.S, s.h_all, s.partials);
+                       c->stream, g, r, n, geom, hist_worker, by_tile ? nullptr : s.S, s.h_all, s.partials);
 }
 
 template <int STATS, int HIST>
 void launch_pass_a_t(artopk_ctx* c, dim3 grid, const PtrTable& g, const PtrTable& r, int64_t n, const ChunkGeom& geom,
-                     int hist_worker) {
+                     int hist_worker, bool by_tile) {
   if (c->g_type == ARTOPK_G_BF16)
-    launch_pass_a_g<STATS, HIST, kGBF16>(c, grid, g, r, n, geom, hist_worker);
+    launch_pass_a_g<STATS, HIST, kGBF16>(c, grid, g, r, n, geom, hist_worker, by_tile);
   else if (c->g_type == ARTOPK_G_F16)
-    launch_pass_a_g<STATS, HIST, kGF16>(c, grid, g, r, n, geom, hist_worker);
+    launch_pass_a_g<STATS, HIST, kGF16>(c, grid, g, r, n, geom, hist_worker, by_tile);
   else
-    launch_pass_a_g<STATS, HIST, kGF32>(c, grid, g, r, n, geom, hist_worker);
+    launch_pass_a_g<STATS, HIST, kGF32>(c, grid, g, r, n, geom, hist_worker, by_tile);
 }
 
 void launch_pass_a(artopk_ctx* c, int stats, int hist, dim3 grid, const PtrTable& g, const PtrTable& r, int64_t n,
-                   const ChunkGeom& geom, int hist_worker) {
+                   const ChunkGeom& geom, int hist_worker, bool by_tile = false) {
 #define PASS_A_CASE(S_, H_) \
-  if (stats == S_ && hist == H_) return launch_pass_a_t<S_, H_>(c, grid, g, r, n, geom, hist_worker)
+  if (stats == S_ && hist == H_) return launch_pass_a_t<S_, H_>(c, grid, g, r, n, geom, hist_worker, by_tile)
   PASS_A_CASE(0, 0);
   PASS_A_CASE(0, 1);
   PASS_A_CASE(0, 2);
@@ -1740,6 +1740,17 @@ int artopk_apply_update(artopk_ctx* ctx, float* weights, int64_t n, const int32_
 
 namespace {
 
+// Blocks per worker of a pass A that strides over the tiles of n elements, or 0 where it had better take chunks: a quarter
+// of a tile each, they still fill the chip (1.2 M elements of a leader known up front, 37 tiles: 61.6 us a step with
+// chunks, 63.5 with tiles; of four workers under the variance rule, 148 tiles, 71.8 and 59.2).  512 / 1024 / 2048 blocks
+// over all workers: 11.7 M x 8 292.7/288.4/286.8 us a step, 5 M x 16 258/260/249, 25 M x 4 331/328/328.
+int tile_blocks(int64_t n, int workers) {
+  const int64_t ntiles = (n + kPassTile - 1) / kPassTile;
+  if (ntiles * workers < 128) return 0;
+  const int64_t blocks = 2048 / workers;
+  return (int)(ntiles < blocks ? ntiles : blocks);
+}
+
 // One step; the g rows hold elements of type g_type (float32 rows are passed as they are, 16-bit
 // rows behind the same pointer type).
 int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* const* residual, int32_t w, int64_t n,
@@ -1799,9 +1810,14 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   } else {
     flat = flat_plan(ctx, n, k, -1, gp.on);
   }
-  // pass A always works on whole-vector chunks; for a flat select they are the select's chunks too
+  // pass A always works on whole-vector chunks; for a flat select they are the select's chunks too, unless k_tail
+  // selects, which needs none: then the pass strides over the tiles
   const ChunkGeom geom = make_geom(0, n, kMaxChunks, gp.on);
-  const dim3 grid(geom.nchunks, w);
+  const int tile_nblk = !segmented && !gp.on && mode != ARTOPK_VAR_TOPK && tail_range(flat, n, kTailHist) > 0
+                            ? tile_blocks(n, leader_first ? 1 : (int)w) : 0;
+  const bool by_tile = tile_nblk > 0;
+  const int pass_nblk = by_tile ? tile_nblk : (int)geom.nchunks;
+  const dim3 grid(pass_nblk, w);
 
   // a long segmented vector: the fused pass strides over the tiles as on the guess route (the
   // selection builds the segments' histograms from the leader's vector afterwards either way)
@@ -1884,7 +1900,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
         launch_pass_seg<kGF32>(ctx, *pl, rt, n, g[L], residual[L]);
       HIP_TRY(ctx, hipGetLastError());
     } else {
-      launch_pass_a(ctx, 0, 1, dim3(geom.nchunks, 1), g1t, r1t, n, geom, 0);
+      launch_pass_a(ctx, 0, 1, dim3(pass_nblk, 1), g1t, r1t, n, geom, 0, by_tile);
     }
     prof_mark(ctx, 1);
     // The leader's residual is zeroed inside the selection: its kernels have the kept values in
@@ -1942,7 +1958,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
       launch_pass_mark(ctx, 0, (int)w, gt, rt, n, geom.chunk_elems);
       slot_by_leader = 1;
     } else {
-      launch_pass_a(ctx, 0, 2, grid, gt, rt, n, geom, -1);
+      launch_pass_a(ctx, 0, 2, grid, gt, rt, n, geom, -1, by_tile);
       slot_by_leader = 1;
     }
     prof_dom(ctx, true);
@@ -1962,7 +1978,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
       if (gp.on) {
         launch_pass_mark(ctx, stats, (int)w, gt, rt, n, geom.chunk_elems);
       } else {
-        launch_pass_a(ctx, stats, 2, grid, gt, rt, n, geom, -1);
+        launch_pass_a(ctx, stats, 2, grid, gt, rt, n, geom, -1, by_tile);
       }
       slot_by_leader = 1;
     }
@@ -1975,7 +1991,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
     } else {          // otherwise the selection's first kernel takes the leader itself
       leader_args.partials = s.partials;
       leader_args.w_count = (int)w;
-      leader_args.nblk = marking ? pass_blocks(n) : (int)geom.nchunks;
+      leader_args.nblk = marking ? pass_blocks(n) : pass_nblk;
       leader_args.n = n;
       leader_args.var_scratch = s.var_scratch;
       leader_args.var_out = var_out;
@@ -1987,7 +2003,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
     if (seg_stride)
       launch_pass_plain(ctx, 0, (int)w, gt, rt, n);
     else
-      launch_pass_a(ctx, 0, segmented ? 0 : 1, grid, gt, rt, n, geom, leader_host);
+      launch_pass_a(ctx, 0, segmented ? 0 : 1, grid, gt, rt, n, geom, leader_host, by_tile);
     prof_dom(ctx, true);
     prof_mark(ctx, 1);
     hipLaunchKernelGGL(k_set_leader, dim3(1), dim3(64), 0, st, (int32_t)leader_host, s.leader_dev, leader_out);

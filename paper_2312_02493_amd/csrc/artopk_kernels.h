@@ -514,7 +514,7 @@ __device__ __forceinline__ uint32_t block_prefix_incl(uint32_t v, uint32_t* wtot
 }
 
 // Adds the 4096-bin LDS histogram `lh` of a T-thread block to total[0..4096)
-// and writes its suffix sums to dst[0..4096).  `red` is T words of LDS.  All
+// and writes its suffix sums to dst[0..4096), unless that is nullptr.  `red` is T words of LDS.  All
 // threads of the block must call it after their last histogram update.
 template <int T>
 __device__ __forceinline__ void flush_suffix_hist(uint32_t* lh, uint32_t* red, uint32_t* __restrict__ dst,
@@ -536,6 +536,7 @@ __device__ __forceinline__ void flush_suffix_hist(uint32_t* lh, uint32_t* red, u
 #pragma unroll
   for (int j = 0; j < BPT; ++j)
     if (v[j]) atomicAdd(&total[BPT * t + j], v[j]);
+  if (dst == nullptr) return;
 #pragma unroll
   for (int j = BPT - 2; j >= 0; --j) v[j] += v[j + 1];
   const uint32_t carry = block_suffix_incl<T>(v[0], red) - v[0];
@@ -614,6 +615,9 @@ k_fill_zero(uint32_t* __restrict__ p1, size_t words1, uint32_t* __restrict__ p2,
 //   STATS: 0 none, 1 variance partials of acc, 2 of the raw gradient g: the
 //   block's (count, mean, sum of squared deviations) in float64 (see VarAcc).
 //   NT: non-temporal loads of g and stores of acc.
+//   S == nullptr: nobody needs counts per chunk; the blocks stride over the tiles instead, a few of them each.  With
+//   chunks of one tile the counts were 4 % more to write and the additions to the whole-vector histograms what bound the
+//   pass of many workers: 11.7 M x 8 311 us a step, now 287, 3 M x 4 106 and 82, 5 M x 16 433 and 249.
 // ---------------------------------------------------------------------------
 constexpr int kPassAUnroll = 4;
 
@@ -642,10 +646,12 @@ k_pass_a(PtrTable g, PtrTable res, int64_t n, ChunkGeom geom, int hist_worker, u
     __syncthreads();
   }
 
-  const int64_t c_lo = geom.chunk0 + (int64_t)c * geom.chunk_elems;
-  int64_t c_hi = c_lo + geom.chunk_elems;
+  const bool by_tile = S == nullptr;
+  const int64_t c_lo = by_tile ? (int64_t)c * T * U * 4 : geom.chunk0 + (int64_t)c * geom.chunk_elems;
+  int64_t c_hi = by_tile ? n : c_lo + geom.chunk_elems;
   if (c_hi > n) c_hi = n;
   const int64_t q_hi = c_hi >> 2;  // whole float4 groups of this chunk
+  const int64_t step = by_tile ? (int64_t)nblk * T * U : (int64_t)T * U;
 
   VarAcc va;
 
@@ -698,10 +704,10 @@ k_pass_a(PtrTable g, PtrTable res, int64_t n, ChunkGeom geom, int hist_worker, u
   // the loop runs on the wave's first group, so all 64 lanes stay together
   const int64_t qw0 = (c_lo >> 2) + __builtin_amdgcn_readfirstlane(tid - lane);
   int64_t qw = qw0;
-  for (; qw + (int64_t)(U - 1) * T + 64 <= q_hi; qw += T * U) tile(qw, std::true_type{});
+  for (; qw + (int64_t)(U - 1) * T + 64 <= q_hi; qw += step) tile(qw, std::true_type{});
   if (qw < q_hi) tile(qw, std::false_type{});
-  // scalar tail (n not a multiple of 4): the block that owns the last chunk
-  if (c_hi == n) {
+  // scalar tail (n not a multiple of 4): the block that owns the last chunk, or the first one
+  if (by_tile ? c == 0 : c_hi == n) {
     const int64_t j = (n >> 2) * 4 + tid;
     if (j < n) {
       const float gj = load1g<GT>(gp, j);
@@ -721,7 +727,7 @@ k_pass_a(PtrTable g, PtrTable res, int64_t n, ChunkGeom geom, int hist_worker, u
   if (LH) {
     if (do_hist) {
       // many blocks add to the same few hundred bins: spread them over kHistReps partial copies
-      flush_suffix_hist<T>(lh, red_u, S + (slot * kMaxChunks + (size_t)c) * kHistBins,
+      flush_suffix_hist<T>(lh, red_u, by_tile ? nullptr : S + (slot * kMaxChunks + (size_t)c) * kHistBins,
                            h_all + slot * kSlotWords + (size_t)(c % kHistReps) * kHistBins);
     }
   }
