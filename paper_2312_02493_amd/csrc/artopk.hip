@@ -834,6 +834,11 @@ int64_t tail_range(const Plan& pl, int64_t n, int source) {
   // wave can keep all its elements (us, list kernels / this, normal values and a run: 8 x 2 M 100/66 98/123, 1 x 11.7 M
   // 61/58 66/92, 1 x 3 M 46/45 47/47, 16 x 1.2 M 98/72 94/117).
   if (source == kTailNone && (pl.nseg < 2 || elems > kTailKeep)) return 0;
+  // Behind a pass' counts a few waves have most of the work if the large values lie together, and more of it the longer
+  // the vector (variance rule, pass and selection, one in a hundred kept, list kernels / this, normal values, layers of 54
+  // scales, a run: 6 M x 2 125/89 120/94 133/134, 11.7 M x 2 132/123 134/137 162/199, x 8 315/288 298/290 320/341, 18 M x 4
+  // 267/251 260/257 294/337, 25.6 M x 4 358/334 340/356 370/444).
+  if (source == kTailHist && elems > 6144) return 0;
   return elems;
 }
 
@@ -857,7 +862,8 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   LeaderArgs la{};
   if (leader_args) la = *leader_args;
   const int source = spans ? kTailSpans : hist_ready ? kTailHist : kTailNone;
-  const int64_t tail_elems = guessed && !spans ? 0 : tail_range(pl, n, source);
+  // (the leader's own selection in front of the other workers' pass gains 2 % of a step, and loses a third on a run)
+  const int64_t tail_elems = (guessed && !spans) || zero_vec ? 0 : tail_range(pl, n, source);
   if (tail_elems > 0) {
     if (spans) {
       p.tiles = span_buf(c, *spans, n);
@@ -1741,9 +1747,9 @@ int artopk_apply_update(artopk_ctx* ctx, float* weights, int64_t n, const int32_
 namespace {
 
 // Blocks per worker of a pass A that strides over the tiles of n elements, or 0 where it had better take chunks: a quarter
-// of a tile each, they still fill the chip (1.2 M elements of a leader known up front, 37 tiles: 61.6 us a step with
-// chunks, 63.5 with tiles; of four workers under the variance rule, 148 tiles, 71.8 and 59.2).  512 / 1024 / 2048 blocks
-// over all workers: 11.7 M x 8 292.7/288.4/286.8 us a step, 5 M x 16 258/260/249, 25 M x 4 331/328/328.
+// of a tile each, they still fill the chip (1.2 M elements of one worker, 37 tiles: 61.6 us a step with chunks, 63.5 with
+// tiles; of four workers, 148 tiles, 71.8 and 59.2).  512 / 1024 / 2048 blocks
+// over all workers: 11.7 M x 8 292.7/288.4/286.8 us a step, 5 M x 16 258/260/249.
 int tile_blocks(int64_t n, int workers) {
   const int64_t ntiles = (n + kPassTile - 1) / kPassTile;
   if (ntiles * workers < 128) return 0;
@@ -1813,8 +1819,8 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   // pass A always works on whole-vector chunks; for a flat select they are the select's chunks too, unless k_tail
   // selects, which needs none: then the pass strides over the tiles
   const ChunkGeom geom = make_geom(0, n, kMaxChunks, gp.on);
-  const int tile_nblk = !segmented && !gp.on && mode != ARTOPK_VAR_TOPK && tail_range(flat, n, kTailHist) > 0
-                            ? tile_blocks(n, leader_first ? 1 : (int)w) : 0;
+  const int tile_nblk = !segmented && !gp.on && !leader_first && mode != ARTOPK_VAR_TOPK && tail_range(flat, n, kTailHist) > 0
+                            ? tile_blocks(n, (int)w) : 0;
   const bool by_tile = tile_nblk > 0;
   const int pass_nblk = by_tile ? tile_nblk : (int)geom.nchunks;
   const dim3 grid(pass_nblk, w);

@@ -3192,7 +3192,7 @@ k_level2(SelParams p) {
 // the blocks wait for each other in between (a microsecond), and a block's survivors (keys that reach the threshold's
 // top digit, or the guessed bound) stay on chip, an eighth with each wave, in order.  Before and after, us: select 138 M, one
 // in a hundred kept 181 / 171, with values in runs 402 / 183, in 54 layers of different scale 237 / 198, all equal 1910 /
-// 1080; 8 selections on 25.6 M 269 / 244; steps 11.7 M x 8 327 / 322, all equal 618 / 547, 25.6 M x 8 in 16 bits 451 / 445.
+// 1080; 8 selections on 25.6 M 269 / 244; steps 11.7 M x 8 327 / 322, all equal 618 / 547.
 //   kTailSpans: the pieces of k_mark_spans, if their bound holds (k_pick_mask's rule) and a wave can keep its share of
 // them.  How many there are in front of every chunk is known, so each wave has as many as any other, however they are
 // spread.  kTailHist: the top digits' counts of a fused pass; kTailNone (and a bound that does not hold): nothing, the
@@ -3542,9 +3542,13 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
   // use(element, raw bits) for every survivor of range c, in some thread
   auto each = [&](int c, auto use) __attribute__((always_inline)) {
     if (listed && c == cur) {
-      for (uint32_t i = (uint32_t)lane; i < mine; i += 64u) {
-        const uint2 ent = entry(c, i);
-        use((int64_t)ent.x, ent.y);
+      for (uint32_t i = (uint32_t)lane; i < mine; i += 256u) {  // four entries in flight
+        uint2 ent[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ent[q] = entry(c, i + 64u * q < mine ? i + 64u * q : i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (i + 64u * q < mine) use((int64_t)ent[q].x, ent[q].y);
       }
     } else {
       wave_each(x, lo_of(c), hi_of(c), bound, use);
@@ -3687,57 +3691,73 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
           if (m >= k) return;
           sv.idx_out[m] = (int32_t)j;
           if (sv.vals_row) sv.vals_row[m] = __uint_as_float(raw);
-          if (p.zero_vec) p.zero_vec[j] = 0.0f;
         };
         if (listed) {
-          for (uint32_t q = 0u; q < mine; q += 64u) {
-            const bool ok = q + (uint32_t)lane < mine;
-            const uint2 ent = entry(c, ok ? q + (uint32_t)lane : mine - 1u);
-            const uint32_t kk = ent.y & kKeyMask;
-            const bool is_a = ok && kk > khi, is_b = ok && kk >= klo && kk <= khi;
-            const uint64_t ma = __ballot(is_a), mb = __ballot(is_b);
-            const uint32_t a = runA + popc_lt(ma), b = runB + popc_lt(mb);
-            if (is_a || (is_b && b < quota)) keep(a, b, (int64_t)ent.x, ent.y);
-            runA += (uint32_t)__popcll(ma);
-            runB += (uint32_t)__popcll(mb);
+          for (uint32_t q0 = 0u; q0 < mine; q0 += 256u) {
+            uint2 four[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const uint32_t q = q0 + 64u * u + (uint32_t)lane;
+              four[u] = entry(c, q < mine ? q : mine - 1u);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const bool ok = q0 + 64u * u + (uint32_t)lane < mine;
+              const uint2 ent = four[u];
+              const uint32_t kk = ent.y & kKeyMask;
+              const bool is_a = ok && kk > khi, is_b = ok && kk >= klo && kk <= khi;
+              const uint64_t ma = __ballot(is_a), mb = __ballot(is_b);
+              const uint32_t a = runA + popc_lt(ma), b = runB + popc_lt(mb);
+              if (is_a || (is_b && b < quota)) keep(a, b, (int64_t)ent.x, ent.y);
+              runA += (uint32_t)__popcll(ma);
+              runB += (uint32_t)__popcll(mb);
+            }
           }
         } else {
           const int64_t hi_e = hi_of(c);
-          for (int64_t base = lo_of(c); base < hi_e; base += 256) {
-            const int64_t j = base + 4 * lane;
-            uint32_t raw[4] = {0u, 0u, 0u, 0u};
-            if (j + 4 <= hi_e) {
-              const uint4 v = *reinterpret_cast<const uint4*>(x + j);
-              raw[0] = v.x, raw[1] = v.y, raw[2] = v.z, raw[3] = v.w;
-            } else {
+          for (int64_t base = lo_of(c); base < hi_e; base += kSpanStep) {
+            uint4 rows8[8];  // eight rows in flight
 #pragma unroll
-              for (int e = 0; e < 3; ++e)
-                if (j + e < hi_e) raw[e] = __float_as_uint(x[j + e]);
-            }
-            uint32_t isA = 0u, isB = 0u;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const uint32_t kk = raw[e] & kKeyMask;
-              isA |= j + e < hi_e && kk > khi ? 1u << e : 0u;
-              isB |= j + e < hi_e && kk >= klo && kk <= khi ? 1u << e : 0u;
-            }
-            if (__ballot((isA | isB) != 0u) == 0ull) continue;
-            const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
-            uint32_t a = runA, b = runB;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-              const uint64_t pa = __ballot((cA >> q) & 1u), pb = __ballot((cB >> q) & 1u);
-              a += popc_lt(pa) << q;
-              b += popc_lt(pb) << q;
-              runA += (uint32_t)__popcll(pa) << q;
-              runB += (uint32_t)__popcll(pb) << q;
+            for (int u = 0; u < 8; ++u) {
+              const int64_t j = base + 4 * (lane + 64 * u);
+              rows8[u] = make_uint4(0u, 0u, 0u, 0u);
+              if (j + 4 <= hi_e) {
+                rows8[u] = *reinterpret_cast<const uint4*>(x + j);
+              } else {
+                if (j + 0 < hi_e) rows8[u].x = __float_as_uint(x[j + 0]);
+                if (j + 1 < hi_e) rows8[u].y = __float_as_uint(x[j + 1]);
+                if (j + 2 < hi_e) rows8[u].z = __float_as_uint(x[j + 2]);
+              }
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const bool is_a = (isA >> e) & 1u, is_b = (isB >> e) & 1u;
-              if (is_a || (is_b && b < quota)) keep(a, b, j + e, raw[e]);
-              a += is_a ? 1u : 0u;
-              b += is_b ? 1u : 0u;
+            for (int u = 0; u < 8; ++u) {
+              const int64_t j = base + 4 * (lane + 64 * u);
+              const uint32_t raw[4] = {rows8[u].x, rows8[u].y, rows8[u].z, rows8[u].w};
+              uint32_t isA = 0u, isB = 0u;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const uint32_t kk = raw[e] & kKeyMask;
+                isA |= j + e < hi_e && kk > khi ? 1u << e : 0u;
+                isB |= j + e < hi_e && kk >= klo && kk <= khi ? 1u << e : 0u;
+              }
+              if (__ballot((isA | isB) != 0u) == 0ull) continue;
+              const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
+              uint32_t a = runA, b = runB;
+#pragma unroll
+              for (int q = 0; q < 3; ++q) {
+                const uint64_t pa = __ballot((cA >> q) & 1u), pb = __ballot((cB >> q) & 1u);
+                a += popc_lt(pa) << q;
+                b += popc_lt(pb) << q;
+                runA += (uint32_t)__popcll(pa) << q;
+                runB += (uint32_t)__popcll(pb) << q;
+              }
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const bool is_a = (isA >> e) & 1u, is_b = (isB >> e) & 1u;
+                if (is_a || (is_b && b < quota)) keep(a, b, j + e, raw[e]);
+                a += is_a ? 1u : 0u;
+                b += is_b ? 1u : 0u;
+              }
             }
           }
         }
