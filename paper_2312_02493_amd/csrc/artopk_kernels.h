@@ -3193,11 +3193,12 @@ k_level2(SelParams p) {
 // top digit, or the guessed bound) stay on chip, an eighth with each wave, in order.  Before and after, us: select 138 M, one
 // in a hundred kept 181 / 171, with values in runs 402 / 183, in 54 layers of different scale 237 / 198, all equal 1910 /
 // 1080; 8 selections on 25.6 M 269 / 244; steps 11.7 M x 8 327 / 322, all equal 618 / 547.
-//   kTailSpans: the pieces of k_mark_spans, if their bound holds (k_pick_mask's rule) and a wave can keep its share of
-// them.  How many there are in front of every chunk is known, so each wave has as many as any other, however they are
-// spread.  kTailHist: the top digits' counts of a fused pass; kTailNone (and a bound that does not hold): nothing, the
-// blocks count them first.  Each wave then has as many elements as any other; survivors that do not fit go to its part
-// of the list's memory, and if they do not fit there either the wave reads its elements again each time.
+//   kTailSpans: the pieces of k_mark_spans, if their bound holds (k_pick_mask's rule).  How many there are in front of
+// every chunk is known, so each wave has as many as any other, however they are spread.  kTailHist: the top digits' counts
+// of a fused pass; kTailNone (and a bound that does not hold): nothing, the blocks count them first.  Each wave then has as
+// many elements as any other.  What a wave does not keep on chip goes to its part of the list's memory (of the pieces it
+// always fits; with a limit of 2000 entries a wave instead, 60 M x 4 and one in a hundred kept had read the vectors again:
+// 642 us, by the list kernels 318, now 285); survivors that do not fit there either are read from the vector again each time.
 //   The blocks count the threshold's next digit over their survivors, wait, pick it each for itself, and so on; the last
 // count also says how many kept entries lie in front of each range, and every wave then writes its own.  A block that has
 // waited for the first counts for a while takes on ranges that nobody has and collects them anew each time (see
@@ -3462,13 +3463,20 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
     if (tid == 0) chunk_at[kMaxChunks] = total;
     uint64_t limit = (uint64_t)k + ((uint64_t)n >> 3);
     if (limit > sv.d.cap) limit = sv.d.cap;
-    spans = bound != kNoGuess && total >= k && total <= limit && total <= (uint32_t)(nranges * WAVES * kTailKeep);
+    spans = bound != kNoGuess && total >= k && total <= limit;
     if (!spans) bound = 0u;
   }
   const uint32_t share = spans ? (total + (uint32_t)(nranges * WAVES) - 1u) / (uint32_t)(nranges * WAVES) : 0u;
   // what a wave does not keep on chip goes to its part of the survivor list's memory
   const uint32_t room = sv.d.cap / (uint32_t)(nranges * WAVES);
+  // (a share of the pieces' entries, of which there are no more than the list takes, always fits)
   auto more_of = [&](int c) __attribute__((always_inline)) { return sv.list + (size_t)(c * WAVES + wave) * room; };
+  auto put = [&](int c, uint32_t m, uint2 v) __attribute__((always_inline)) {
+    if (m < (uint32_t)kTailKeep)
+      list[wave][m] = v;
+    else
+      more_of(c)[m - kTailKeep] = v;
+  };
   int cur = -1;  // the range whose survivors `list` holds, if they fit
   // The survivors of range c, from the pieces or from the vector; all threads call it.
   auto collect = [&](int c) __attribute__((always_inline)) {
@@ -3491,21 +3499,21 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
           const uint64_t some = __ballot(at + incl > e0 && at + incl - cnt < e1 && cnt != 0u);
           for (uint64_t left = some; left != 0ull;) {  // four spans' loads in flight
             uint2 ent[4];
-            uint32_t put[4], cn[4];
+            uint32_t first[4], cn[4];
             const uint2* piece[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               const int s = left != 0ull ? __builtin_ctzll(left) : 0;
               cn[q] = left != 0ull ? __shfl(cnt, s, 64) : 0u;
-              put[q] = at + __shfl(incl, s, 64) - __shfl(cnt, s, 64);  // the number of its first entry
+              first[q] = at + __shfl(incl, s, 64) - __shfl(cnt, s, 64);  // the number of its first entry
               piece[q] = sv.tbuf + (size_t)(s0 + s) * (size_t)sv.tcap;
               left &= left - 1ull;
               if (cn[q] > (uint32_t)sv.tcap) {  // more than its piece holds: from the vector
                 const int64_t x0 = (s0 + s) * span, x1 = x0 + span < n ? x0 + span : n;
                 (void)wave_collect(x, x0, x1, bound, pool.qu[wave], kQuotaInf,
                                    [&](uint32_t m, int64_t j, uint32_t raw) __attribute__((always_inline)) {
-                                     const uint32_t e = put[q] + m;
-                                     if (e >= e0 && e < e1) list[wave][e - e0] = make_uint2((uint32_t)j, raw);
+                                     const uint32_t e = first[q] + m;
+                                     if (e >= e0 && e < e1) put(c, e - e0, make_uint2((uint32_t)j, raw));
                                    });
                 cn[q] = 0u;
               }
@@ -3514,9 +3522,9 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               for (uint32_t m = (uint32_t)lane; m < cn[q]; m += 64u) {
-                const uint32_t e = put[q] + m;
+                const uint32_t e = first[q] + m;
                 if (m >= 64u) ent[q] = piece[q][m];
-                if (e >= e0 && e < e1) list[wave][e - e0] = ent[q];
+                if (e >= e0 && e < e1) put(c, e - e0, ent[q]);
               }
             }
           }
@@ -3527,10 +3535,7 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
     } else {
       mine = wave_collect(x, lo_of(c), hi_of(c), bound, pool.qu[wave], (uint32_t)kTailKeep + room,
                           [&](uint32_t m, int64_t j, uint32_t raw) __attribute__((always_inline)) {
-                            if (m < (uint32_t)kTailKeep)
-                              list[wave][m] = make_uint2((uint32_t)j, raw);
-                            else
-                              more_of(c)[m - kTailKeep] = make_uint2((uint32_t)j, raw);
+                            put(c, m, make_uint2((uint32_t)j, raw));
                           });
     }
     __syncthreads();

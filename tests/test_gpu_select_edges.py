@@ -225,6 +225,36 @@ def test_bound_that_overfills_the_pieces(n, from_mask):
     assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x.cpu().numpy(), k))
 
 
+# a bound that holds, with more entries than the waves of the one-launch selection keep on chip (4.1 M on one vector, an
+# eighth of that on each of eight): the pieces' entries are shared out all the same, and the vectors are not read again
+@pytest.mark.parametrize("n,w", [(40_000_003, 1), (4_400_001, 8)])
+def test_bound_that_more_reach_than_stay_on_chip(n, w):
+    import torch
+    import gpu_util
+
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    xs = [torch.randn(n, generator=gen, device="cuda") * 1e-3 for _ in range(w)]
+    k = n // 100
+    for x in xs:  # ties at the threshold, among them larger ones
+        x[torch.rand(n, generator=gen, device="cuda") < 0.1145] = -0.5
+        x[torch.randint(0, n, (k // 2,), generator=gen, device="cuda")] = 0.75
+    ctx = gpu_util.make_context(w, n, k)
+    idx = torch.full((w, k), -1, dtype=torch.int32, device="cuda")
+    vals = torch.zeros(w, k, device="cuda")
+    if w == 1:
+        ctx.artopk_select_topk(xs[0], k, idx[0])
+    else:
+        ctx.artopk_topk_workers(xs, k, idx, vals)
+    info = ctx.select_info()
+    ctx.status()
+    assert gpu_util.FORCED or ((info["guessed"], info["from_mask"]) == (1, 1) and info["list_count"] > 4_096_000 // w), info
+    for r in range(w):
+        want = orc.topk_indices(xs[r].cpu().numpy(), k)
+        assert np.array_equal(idx[r].cpu().numpy(), want), r
+        if w > 1:
+            assert torch.equal(vals[r].view(torch.int32), xs[r][idx[r].long()].view(torch.int32))
+
+
 # a length set for the guess holds for selections on vectors as they are, also if it is the default's value
 @pytest.mark.parametrize("value,guessed", [(None, 1), (1 << 25, 0), (25_500_000, 1), (25_500_001, 0)])
 def test_length_from_which_read_only_selections_guess(value, guessed):
