@@ -394,6 +394,8 @@ int artopk_get_profile(artopk_ctx* ctx, float* ms_out, int32_t count);
  *       [2] and [3] are what one after the first digit would have held)
  *   [6] 1 if that launch's threshold shares its top digit with more than 10240
  *       values and 240 for every 8192 elements
+ *   [7] 1 if everything behind the top digits' counts of a pass, or behind the
+ *       read-only marking, ran in one launch
  * Flat (one-segment) selections only; segmented ones report [0] = [1] = 0.  Of
  * selections on several vectors [1] to [3] are the first vector's of those that
  * were selected on last.

@@ -127,7 +127,7 @@ struct artopk_ctx {
   void* slab = nullptr;
   Scratch s;
   // how the last step or selection ran (artopk_select_info)
-  int32_t last_guessed = 0, last_dom_workers = 0, last_short = 0;
+  int32_t last_guessed = 0, last_dom_workers = 0, last_short = 0, last_one_launch = 0;
   int g_type = ARTOPK_G_F32;  // element type of the gradients of the step being enqueued
   // descriptors of the last segmented layout uploaded to table_dev
   std::vector<int64_t> cached_off, cached_k;
@@ -821,25 +821,33 @@ void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const 
                        gp.m_hi);
 }
 
-// Elements a wave of k_tail takes where it is the better way to select, else 0.
-int64_t tail_range(const Plan& pl, int64_t n, int source) {
-  if (pl.use_table || pl.nseg > kTailRanges) return 0;
+// How k_tail takes a selection: ranges (blocks) a vector, and rows of 256 elements in each of a wave's pieces (log2).
+struct TailPlan {
+  int32_t ranges = 0;  // 0: the list kernels are the better way
+  int32_t row_log2 = 0;
+};
+
+TailPlan tail_plan(const Plan& pl, int64_t n, int source) {
+  TailPlan t;
+  if (pl.use_table || pl.nseg > kTailRanges) return t;
   const int64_t waves = (int64_t)(kTailRanges / pl.nseg) * kTailWaves;
   const int64_t elems = ((n + waves - 1) / waves + kTailRow - 1) / kTailRow * kTailRow;
   // Survivors a wave is expected to have: the candidates below the threshold, or the guess' margin and the rest of its
   // bin, come to less than half of k.
-  if (1.5 * (double)pl.desc[0].k / (double)waves > (double)kTailKeep) return 0;
+  if (1.5 * (double)pl.desc[0].k / (double)waves > (double)kTailKeep) return t;
   // (Denser ones, 138 M and one in 33: the list kernels read their entries from memory a few times less.)
   // With nothing there yet, two passes over the vector and short chunks stand up better to runs of large values, unless a
   // wave can keep all its elements (us, list kernels / this, normal values and a run: 8 x 2 M 100/66 98/123, 1 x 11.7 M
   // 61/58 66/92, 1 x 3 M 46/45 47/47, 16 x 1.2 M 98/72 94/117).
-  if (source == kTailNone && (pl.nseg < 2 || elems > kTailKeep)) return 0;
-  // Behind a pass' counts a few waves have most of the work if the large values lie together, and more of it the longer
-  // the vector (variance rule, pass and selection, one in a hundred kept, list kernels / this, normal values, layers of 54
-  // scales, a run: 6 M x 2 125/89 120/94 133/134, 11.7 M x 2 132/123 134/137 162/199, x 8 315/288 298/290 320/341, 18 M x 4
-  // 267/251 260/257 294/337, 25.6 M x 4 358/334 340/356 370/444).
-  if (source == kTailHist && elems > 6144) return 0;
-  return elems;
+  if (source == kTailNone && (pl.nseg < 2 || elems > kTailKeep)) return t;
+  // Behind a pass' counts the list kernels are measured against it up to 12.5 M elements (see k_tail; in one piece a wave,
+  // longer vectors lost on layers and runs, 25.6 M x 4, list kernels / that: 358/334 normal values, 340/356, 370/444).
+  if (source == kTailHist && elems > 6144) return t;
+  // Up to 16 pieces a wave, and more where fewer blocks share a vector: every block reads what the others keep of theirs.
+  const int32_t most = std::min(kTailPieces, 4096 / (kTailRanges / pl.nseg));
+  while (((int64_t)kTailRow << t.row_log2) * most < elems) ++t.row_log2;
+  t.ranges = (int32_t)std::min<int64_t>(kTailRanges / pl.nseg, (n + kTailWaves * kTailRow - 1) / (kTailWaves * kTailRow));
+  return t;
 }
 
 // Top-k of every segment of the plan on the vector tab.p[*leader_dev]; the
@@ -863,14 +871,20 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   if (leader_args) la = *leader_args;
   const int source = spans ? kTailSpans : hist_ready ? kTailHist : kTailNone;
   // (the leader's own selection in front of the other workers' pass gains 2 % of a step, and loses a third on a run)
-  const int64_t tail_elems = (guessed && !spans) || zero_vec ? 0 : tail_range(pl, n, source);
-  if (tail_elems > 0) {
+  const TailPlan tp = (guessed && !spans) || zero_vec ? TailPlan{} : tail_plan(pl, n, source);
+  c->last_one_launch = tp.ranges > 0 ? 1 : 0;
+  if (tp.ranges > 0) {
     if (spans) {
       p.tiles = span_buf(c, *spans, n);
       p.use_mcount = 1;
     }
-    const unsigned ranges = (unsigned)((n + kTailWaves * tail_elems - 1) / (kTailWaves * tail_elems));
-    hipLaunchKernelGGL(k_tail, dim3(ranges, nseg), dim3(64 * kTailWaves), 0, st, p, la, source, tail_elems);
+    const dim3 grid((unsigned)tp.ranges, nseg), block(64 * kTailWaves);
+    if (source == kTailSpans)
+      hipLaunchKernelGGL(k_tail<kTailSpans>, grid, block, 0, st, p, la, tp.row_log2);
+    else if (source == kTailHist)
+      hipLaunchKernelGGL(k_tail<kTailHist>, grid, block, 0, st, p, la, tp.row_log2);
+    else
+      hipLaunchKernelGGL(k_tail<kTailNone>, grid, block, 0, st, p, la, tp.row_log2);
     HIP_TRY(c, hipGetLastError());
     return ARTOPK_OK;
   }
@@ -1463,10 +1477,10 @@ int artopk_select_info(artopk_ctx* ctx, int32_t* info_out, int32_t count) {
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   SelState st{};
   HIP_TRY(ctx, hipMemcpy(&st, ctx->s.zero_base + kSegState, sizeof(st), hipMemcpyDeviceToHost));
-  const int32_t v[7] = {ctx->last_guessed, ctx->last_guessed ? (int32_t)st.use_mask : 0, (int32_t)st.list_count,
+  const int32_t v[8] = {ctx->last_guessed, ctx->last_guessed ? (int32_t)st.use_mask : 0, (int32_t)st.list_count,
                         (int32_t)st.compact_level, ctx->last_dom_workers, ctx->last_short,
-                        ctx->last_short ? (int32_t)st.many : 0};
-  for (int i = 0; i < count && i < 7; ++i) info_out[i] = v[i];
+                        ctx->last_short ? (int32_t)st.many : 0, ctx->last_one_launch};
+  for (int i = 0; i < count && i < 8; ++i) info_out[i] = v[i];
   return ARTOPK_OK;
 }
 
@@ -1819,7 +1833,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   // pass A always works on whole-vector chunks; for a flat select they are the select's chunks too, unless k_tail
   // selects, which needs none: then the pass strides over the tiles
   const ChunkGeom geom = make_geom(0, n, kMaxChunks, gp.on);
-  const int tile_nblk = !segmented && !gp.on && !leader_first && mode != ARTOPK_VAR_TOPK && tail_range(flat, n, kTailHist) > 0
+  const int tile_nblk = !segmented && !gp.on && !leader_first && mode != ARTOPK_VAR_TOPK && tail_plan(flat, n, kTailHist).ranges > 0
                             ? tile_blocks(n, (int)w) : 0;
   const bool by_tile = tile_nblk > 0;
   const int pass_nblk = by_tile ? tile_nblk : (int)geom.nchunks;
@@ -1875,6 +1889,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
     }
     if (leader_first) ctx->last_dom_workers = 1;
     ctx->last_short = 1;
+    ctx->last_one_launch = 0;
     return small_step(ctx, gt, rt, w, n, k, mode == ARTOPK_VAR ? 1 : mode == ARTOPK_VAR_G ? 2 : 0,
                       leader_first ? leader_host : -1, leader_out, var_out, idx_out, vals_out, sum_out, update_out);
   }

@@ -3190,31 +3190,43 @@ k_level2(SelParams p) {
 // four behind a pass that counted the top digits (pick, compaction, list digits, final pass), six behind the read-only
 // marking or five behind nothing.  Those are bound by latency, 5 us for a launch and a trip to memory or two in each; here
 // the blocks wait for each other in between (a microsecond), and a block's survivors (keys that reach the threshold's
-// top digit, or the guessed bound) stay on chip, an eighth with each wave, in order.  Before and after, us: select 138 M, one
-// in a hundred kept 181 / 171, with values in runs 402 / 183, in 54 layers of different scale 237 / 198, all equal 1910 /
-// 1080; 8 selections on 25.6 M 269 / 244; steps 11.7 M x 8 327 / 322, all equal 618 / 547.
+// top digit, or the guessed bound) stay on chip, an eighth with each wave, in order.  List kernels / this, us: select 138 M,
+// one in a hundred kept 181 / 170, with values in runs 402 / 174, all equal 1914 / 1209; 8 selections on 25.6 M 278 / 248;
+// variance rule, pass and selection, 11.7 M x 8 312 / 281, all equal 658 / 576.
 //   kTailSpans: the pieces of k_mark_spans, if their bound holds (k_pick_mask's rule).  How many there are in front of
 // every chunk is known, so each wave has as many as any other, however they are spread.  kTailHist: the top digits' counts
 // of a fused pass; kTailNone (and a bound that does not hold): nothing, the blocks count them first.  Each wave then has as
-// many elements as any other.  What a wave does not keep on chip goes to its part of the list's memory (of the pieces it
-// always fits; with a limit of 2000 entries a wave instead, 60 M x 4 and one in a hundred kept had read the vectors again:
-// 642 us, by the list kernels 318, now 285); survivors that do not fit there either are read from the vector again each time.
-//   The blocks count the threshold's next digit over their survivors, wait, pick it each for itself, and so on; the last
-// count also says how many kept entries lie in front of each range, and every wave then writes its own.  A block that has
-// waited for the first counts for a while takes on ranges that nobody has and collects them anew each time (see
+// many elements as any other, in up to 16 pieces (64 where several vectors share the blocks) spread over the vector, so
+// that large values that lie together are those of many waves.  In one piece, a few waves had most of the work (variance
+// rule, 11.7 M x 2, one in a hundred, list kernels / one piece / now: normal values 131/122/124, layers of 54 scales
+// 132/133/124, a run 163/195/152, sorted 222/251/203; x 8 312/284/281, 298/281/271, 311/331/286, 528/532/478).
+//   What a wave does not keep on chip goes to its part of the list's memory (of the pieces it always fits; with a limit of
+// 2000 entries a wave instead, 60 M x 4 and one in a hundred kept had read the vectors again: 642 us, by the list kernels
+// 318, now 287); survivors that do not fit there either are read from the vector again each time.
+//   The blocks count the threshold's next digit over their survivors, wait, pick it each for itself, and so on.  Where no
+// more than 512 candidates are left for the last digit (without many ties: 13 of 11.7 M normal values), each block hands
+// on its own, and how many entries lie above them in each of its pieces; else it counts their digits, waits, and counts
+// then what is kept.  Either way every wave knows what is kept in front of each of its pieces and writes its own.  A block
+// that has waited for the first counts for a while takes on ranges that nobody has and collects them anew each time (see
 // k_small_step: nothing depends on how many blocks run at a time).
-// wave_elems: a wave's elements, a multiple of kTailRow.  grid = (ranges, vectors), block = 64 kTailWaves.
-// The counts lie in the segment's scratch block (cleared before), rows and above in S's memory.
+//   The length of the code matters: it is read in by a launch of 40 us.  With rows and entries taken by instructions of
+// their own eight and four at a time, 108 KB, the same took 15 us longer behind a pass than in 29 KB.
+// row_log2: rows of 256 elements in a piece.  grid = (ranges, vectors), block = 64 kTailWaves.  The counts lie in the
+// segment's scratch block (cleared before), what the blocks hand on in S's memory.
 // ---------------------------------------------------------------------------
 constexpr int kTailSpans = 0, kTailHist = 1, kTailNone = 2;
 constexpr int kTailRanges = 256;   // blocks of a launch, at most: one per compute unit
 constexpr int kTailWaves = 8;      // (16 a block: 87 registers of each thread spilled, and everything took 35 us longer)
 constexpr int kTailKeep = 2000;    // survivors a wave keeps on chip
 constexpr int kTailRow = 256;
+constexpr int kTailPieces = 64;  // pieces of a wave's elements, at most
+constexpr int kTailFew = 64 * kTailWaves;  // candidates that are handed on one by one, a few of each range in places of its own
+constexpr int kTailSlots = 4;
 constexpr int kTailWaits = 4, kTailArrive = 8;
 // in the words of kSegHist2 behind the last digit's 128 counts: whether somebody has taken a range, the waits' counters
 constexpr int kTailClaim = 128, kTailCount = 512;
-static_assert(kTailClaim + kTailRanges <= kTailCount && kTailCount + kTailWaits * kTailArrive * 32 <= kHistBins, "they fit");
+constexpr int kTailFewAt = kTailWaits * kTailArrive * 32;  // (behind kTailCount: candidates handed on so far)
+static_assert(kTailClaim + kTailRanges <= kTailCount && kTailCount + kTailFewAt < kHistBins, "they fit");
 constexpr int kTailHelpSpins = 256;
 
 // Adds 1 to hist[bin] for every active lane; lanes with the first one's bin (all, where values are equal) in one addition.
@@ -3227,43 +3239,63 @@ __device__ __forceinline__ void wave_count(uint32_t* hist, uint32_t bin) {
     atomicAdd(&hist[one], (uint32_t)__popcll(same));
 }
 
-// Threads' loop over the elements of x[lo, hi) whose key reaches `bound`, the 64 lanes of a wave together: use(element,
-// raw bits), in no order.
-template <typename Use>
-__device__ __forceinline__ void wave_each(const float* __restrict__ x, int64_t lo, int64_t hi, uint32_t bound, Use use) {
-  const int lane = (int)lane_id();
-  for (int64_t base = lo; base < hi; base += kSpanStep) {
+// A wave's walk over rows of 256 elements of x, four a lane, eight of them in flight: at(r) is the first element of row r,
+// a multiple of 4, n or more where there is no such row.  row(its number, the lane's first element, words) for every row in
+// order, with what lies behind n unspecified, until enough() is true after eight of them.  OWN: each of the eight is taken
+// by instructions of its own, which pays for vectors of many rows (all equal, 138 M: 1209 us, else 1309); else by the same
+// ones.  x16: 16 bytes to read where n has not even those.  The 64 lanes of a wave call it.
+typedef uint32_t RowWords __attribute__((ext_vector_type(32)));
+
+template <bool OWN, typename At, typename Row, typename Enough>
+__device__ __forceinline__ void wave_walk(const float* __restrict__ x, uint32_t n, const void* x16, int nrows, At at,
+                                          Row row, Enough enough) {
+  const uint32_t lane = lane_id();
+  const uint32_t last = n & ~3u;  // the group that n cuts, if it does
+  uint4 cut = make_uint4(0u, 0u, 0u, 0u);
+  if (last + 0 < n) cut.x = __float_as_uint(x[last + 0]);
+  if (last + 1 < n) cut.y = __float_as_uint(x[last + 1]);
+  if (last + 2 < n) cut.z = __float_as_uint(x[last + 2]);
+  const float* const from = n >= 4u ? x : static_cast<const float*>(x16);
+  const uint32_t most = n >= 4u ? last - 4u : 0u;
+  for (int r0 = 0; r0 < nrows && !enough(); r0 += 8) {
     uint4 v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int64_t j = base + 4 * (lane + 64 * u);
-      v[u] = make_uint4(0u, 0u, 0u, 0u);
-      if (base + 256 * u + 256 <= hi) {  // (the same in every lane)
-        v[u] = *reinterpret_cast<const uint4*>(x + j);
-      } else if (j + 4 <= hi) {
-        v[u] = *reinterpret_cast<const uint4*>(x + j);
-      } else {
-        if (j + 0 < hi) v[u].x = __float_as_uint(x[j + 0]);
-        if (j + 1 < hi) v[u].y = __float_as_uint(x[j + 1]);
-        if (j + 2 < hi) v[u].z = __float_as_uint(x[j + 2]);
-      }
+      const uint32_t j = at(r0 + u) + 4u * lane;
+      v[u] = *reinterpret_cast<const uint4*>(from + (j < most ? j : most));
     }
+    if (OWN) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t j = at(r0 + u) + 4u * lane;
+        if (j == last) v[u] = cut;
+        if (r0 + u < nrows) row(r0 + u, j, v[u]);
+      }
+      continue;
+    }
+    RowWords w;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int64_t j = base + 4 * (lane + 64 * u);
-      const uint32_t raw[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (j + e < hi && (raw[e] & kKeyMask) >= bound) use(j + e, raw[e]);
+      w[4 * u + 0] = v[u].x;
+      w[4 * u + 1] = v[u].y;
+      w[4 * u + 2] = v[u].z;
+      w[4 * u + 3] = v[u].w;
+    }
+#pragma unroll 1
+    for (int u = 0; u < 8 && r0 + u < nrows; ++u) {
+      const uint32_t j = at(r0 + u) + 4u * lane;
+      uint4 t = make_uint4(w[4 * u], w[4 * u + 1], w[4 * u + 2], w[4 * u + 3]);
+      if (j == last) t = cut;
+      row(r0 + u, j, t);
     }
   }
 }
 
-// The elements of x[lo, hi) whose key reaches `bound`, in order, the first cap of them: put(number, element, raw bits);
-// returns their number, or more than cap.  The 64 lanes of a wave call it; lo is a multiple of 4.  (wave_span with the bound as a key.)
-template <typename Put>
-__device__ __forceinline__ uint32_t wave_collect(const float* __restrict__ x, int64_t lo, int64_t hi, uint32_t bound,
-                                                 SpanQueue& qu, uint32_t cap, Put put) {
+// The elements of a wave's rows (see wave_walk) whose key reaches `bound`, in order, the first cap of them: put(number,
+// element, raw bits); returns their number, or more than cap.
+template <bool OWN, typename At, typename Put>
+__device__ __forceinline__ uint32_t wave_collect(const float* __restrict__ x, uint32_t n, const void* x16, int nrows, At at,
+                                                 uint32_t bound, SpanQueue& qu, uint32_t cap, Put put) {
   const uint32_t lane = lane_id();
   uint32_t count = 0u, head = 0u, queued = 0u;
   auto take = [&](uint32_t m) __attribute__((always_inline)) {
@@ -3276,7 +3308,7 @@ __device__ __forceinline__ uint32_t wave_collect(const float* __restrict__ x, in
     const uint32_t raw[4] = {v.x, v.y, v.z, v.w};
     uint32_t own = 0u;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) own |= (raw[e] & kKeyMask) >= bound && (int64_t)4 * g + e < hi ? 1u << e : 0u;
+    for (int e = 0; e < 4; ++e) own |= (raw[e] & kKeyMask) >= bound && 4u * g + e < n ? 1u << e : 0u;
     if (lane >= m) own = 0u;
     const uint32_t c = (uint32_t)__popc(own);
     uint32_t before = 0u, total = 0u;
@@ -3290,7 +3322,7 @@ __device__ __forceinline__ uint32_t wave_collect(const float* __restrict__ x, in
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if ((own >> e) & 1u) {
-        if (pos < cap) put(pos, (int64_t)4 * g + e, raw[e]);
+        if (pos < cap) put(pos, 4u * g + e, raw[e]);
         ++pos;
       }
     }
@@ -3298,89 +3330,106 @@ __device__ __forceinline__ uint32_t wave_collect(const float* __restrict__ x, in
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
-  for (int64_t base = lo; base < hi; base += kSpanStep) {
-    const uint32_t g0 = (uint32_t)(base >> 2) + lane;
-    uint4 v[8];
-    if (base + kSpanStep <= hi) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint4*>(x + 4 * (int64_t)(g0 + 64u * u));
-    } else {  // the wave's last rows, the vector's end: absent elements as 0, which only a bound of 0 takes (take() looks again)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int64_t j = 4 * (int64_t)(g0 + 64u * u);
-        v[u] = make_uint4(0u, 0u, 0u, 0u);
-        if (base + 256 * u + 256 <= hi) {  // (the same in every lane)
-          v[u] = *reinterpret_cast<const uint4*>(x + j);
-        } else if (j + 4 <= hi) {
-          v[u] = *reinterpret_cast<const uint4*>(x + j);
-        } else {
-          if (j + 0 < hi) v[u].x = __float_as_uint(x[j + 0]);
-          if (j + 1 < hi) v[u].y = __float_as_uint(x[j + 1]);
-          if (j + 2 < hi) v[u].z = __float_as_uint(x[j + 2]);
-        }
-      }
+  wave_walk<OWN>(x, n, x16, nrows, at, [&](int, uint32_t j, uint4 raw) __attribute__((always_inline)) {
+    // (take() looks which of a group's elements there are)
+    const uint32_t a = raw.x & kKeyMask, b = raw.y & kKeyMask, c = raw.z & kKeyMask, d = raw.w & kKeyMask;
+    const uint32_t ab = a > b ? a : b, cd = c > d ? c : d;
+    const bool hit = (ab > cd ? ab : cd) >= bound && j < n;
+    const uint64_t hits = __ballot(hit);
+    if (hits == 0ull) return;
+    if (hit) {
+      const uint32_t p = (head + queued + popc_lt(hits)) & 127u;
+      qu.val[p] = raw;
+      qu.group[p] = j >> 2;
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const uint32_t a = v[u].x & kKeyMask, b = v[u].y & kKeyMask, c = v[u].z & kKeyMask, d = v[u].w & kKeyMask;
-      const uint32_t ab = a > b ? a : b, cd = c > d ? c : d;
-      const bool hit = (ab > cd ? ab : cd) >= bound;
-      const uint64_t hits = __ballot(hit);
-      if (hits != 0ull) {
-        if (hit) {
-          const uint32_t p = (head + queued + popc_lt(hits)) & 127u;
-          qu.val[p] = v[u];
-          qu.group[p] = g0 + 64u * u;
-        }
-        queued += (uint32_t)__popcll(hits);
-        if (queued >= 64u) {
-          take(64u);
-          head += 64u;
-          queued -= 64u;
-        }
-      }
+    queued += (uint32_t)__popcll(hits);
+    if (queued >= 64u) {
+      take(64u);
+      head += 64u;
+      queued -= 64u;
     }
-    if (count > cap) return count;  // (no use in going on)
-  }
+  }, [&]() __attribute__((always_inline)) { return count > cap; });  // (no use in going on)
   if (queued != 0u) take(queued);
   return count;
 }
 
-__global__ void __launch_bounds__(64 * kTailWaves)
-k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
-  constexpr int WAVES = kTailWaves, T = 64 * WAVES, BPT = kHistBins / T;
-  __shared__ uint2 list[WAVES][kTailKeep];  // (element, raw bits)
-  __shared__ union {
+struct TailShared {
+  uint2 list[kTailWaves][kTailKeep];  // (element, raw bits)
+  union {
     __attribute__((aligned(16))) uint32_t hist[kHistBins];
-    SpanQueue qu[WAVES];
+    SpanQueue qu[kTailWaves];
+    struct {  // kept entries: (above the threshold, at it)
+      uint2 own[kTailWaves][kTailPieces];    // of a wave's piece
+      uint2 front[kTailWaves][kTailPieces];  // in front of it, less those of the wave's pieces before
+      uint64_t all[kTailPieces];             // of all blocks' pieces of that number: above << 32 | at
+      uint64_t before[kTailPieces];          // of those, the blocks in front of this one's
+      uint2 few[kTailFew];                   // candidates: (place, last digit)
+    } kept;
   } pool;
-  __shared__ __attribute__((aligned(16))) uint32_t tail[128];
-  __shared__ SelState st, st1;
-  __shared__ uint32_t part[WAVES];
-  __shared__ uint64_t wtot[WAVES], wfront[WAVES];
-  __shared__ uint16_t owned[kTailRanges];
-  __shared__ int verdict;
-  __shared__ uint32_t chunk_at[kMaxChunks + 1];  // entries in front of every chunk of the marking (kTailSpans)
+  uint32_t tail[128];
+  SelState st, st1;
+  uint32_t part[kTailWaves];
+  uint16_t owned[kTailRanges];
+  int verdict;
+  uint32_t few_n, few_at;
+  uint2 few_all[kTailFew];         // all blocks' candidates, where there are few
+  uint32_t chunk_at[kMaxChunks + 1];  // entries in front of every chunk of the marking (kTailSpans)
+};
+
+// What comes from on-chip memory and is the same in every lane, taken as such: addresses and loops stay scalar.
+template <typename V>
+__device__ __forceinline__ V same(V v) {
+  return (V)__builtin_amdgcn_readfirstlane((int)v);
+}
+template <typename V>
+__device__ __forceinline__ V* same_ptr(V* q) {
+  const uint64_t v = (uint64_t)q;
+  return (V*)(((uint64_t)same((uint32_t)(v >> 32)) << 32) | same((uint32_t)v));
+}
+
+// k_tail's work.  full: behind a marking whose bound does not hold.  bound, total: kTailSpans' bound and the number of
+// entries that reach it.
+template <int source, bool full>
+__device__ __forceinline__ void tail_select(const SelParams& p, const SegView& sv, TailShared& sh, int row_log2,
+                                            uint32_t bound, uint32_t total) {
+  constexpr int WAVES = kTailWaves, T = 64 * WAVES, BPT = kHistBins / T;
+  constexpr bool spans = source == kTailSpans;
+  auto& list = sh.list;
+  auto& pool = sh.pool;
+  auto& tail = sh.tail;
+  auto& st = sh.st;
+  auto& st1 = sh.st1;
+  auto& part = sh.part;
+  auto& owned = sh.owned;
+  auto& verdict = sh.verdict;
+  auto& few_n = sh.few_n;
+  auto& few_at = sh.few_at;
+  auto& few_all = sh.few_all;
+  auto& chunk_at = sh.chunk_at;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nranges = gridDim.x, vec = blockIdx.y, c0 = blockIdx.x;
-  if (*p.err != 0u) return;  // (set before this launch: the same in every block)
-  if (tid == 0) verdict = -1;
-  if (la.partials != nullptr) {  // (every block finds, and writes, the same)
-    const int best = block_take_leader(la);
-    if (tid == 0) verdict = best;
-  }
-  __syncthreads();
-  const SegView sv = seg_view(p, vec, verdict);
   const float* x = sv.x;
-  const int64_t n = p.n;
+  const uint32_t n = (uint32_t)p.n;
   const uint32_t k = sv.d.k;
   uint32_t* const claim = sv.hist2 + kTailClaim;
   uint32_t* const count = sv.hist2 + kTailCount;
-  // rows and above of all the launch's ranges
-  uint32_t* const rows = p.S + (size_t)vec * nranges * 128;
-  uint32_t* const above = p.S + (size_t)kTailRanges * 128 + (size_t)vec * nranges;
-  __syncthreads();  // (verdict has been read)
+  // the wave's pieces of range c: `pieces` of them, 256 << row_log2 elements each, `stride` elements apart
+  const uint32_t stride = ((uint32_t)nranges * WAVES) << (8 + row_log2);
+  const int pieces = (int)((n + stride - 1u) / stride), nrows = pieces << row_log2;
+  auto rows_of = [&](int c) __attribute__((always_inline)) {
+    const uint32_t first = (uint32_t)(c * WAVES + wave) << (8 + row_log2);
+    return [=](int r) __attribute__((always_inline)) {
+      return (uint32_t)(r >> row_log2) * stride + first + ((uint32_t)(r & ((1 << row_log2) - 1)) << 8);
+    };
+  };
+  // kept entries of every range's pieces: [piece][range], above << 32 | at
+  uint64_t* const kept_of = reinterpret_cast<uint64_t*>(p.S) + (size_t)vec * kTailPieces * nranges;
+  // candidates of every range where there are few: kTailSlots each, and what is more of any: last digit << 32 | place, which
+  // is (piece x ranges + range) x waves + wave
+  uint64_t* const slots_of = reinterpret_cast<uint64_t*>(p.S) + (size_t)kTailPieces * kTailRanges +
+                             (size_t)vec * (kTailRanges * kTailSlots + kTailFew);
+  uint64_t* const few_of = slots_of + kTailRanges * kTailSlots;
   if (tid == 0) {
     verdict = __hip_atomic_exchange(&claim[c0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ? 1 : 0;
     owned[0] = (uint16_t)c0;
@@ -3414,58 +3463,12 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
       if (lane == 0) verdict = ok ? 1 : 0;
     }
     __syncthreads();
-    const bool ok = verdict != 0;
+    const bool ok = same(verdict) != 0;
     __syncthreads();
     return ok;
   };
-  // this wave's elements of range c
-  auto lo_of = [&](int c) __attribute__((always_inline)) { return ((int64_t)c * WAVES + wave) * wave_elems; };
-  auto hi_of = [&](int c) __attribute__((always_inline)) {
-    const int64_t hi = lo_of(c) + wave_elems;
-    return hi < n ? hi : n;
-  };
-  auto clear_hist = [&]() __attribute__((always_inline)) {
-    __syncthreads();
-    for (int i = tid; i < kHistBins / 4; i += T) reinterpret_cast<uint4*>(pool.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-  };
-  auto pick = [&](const uint32_t* hist, int digit) __attribute__((always_inline)) {
-    const int bins = (int)digit_mask(digit) + 1;
-    uint32_t h[BPT];
-#pragma unroll
-    for (int j = 0; j < BPT / 2; ++j) {
-      const uint64_t q = BPT * tid < bins ? load_through(reinterpret_cast<const uint64_t*>(hist) + BPT / 2 * tid + j) : 0ull;
-      h[2 * j] = (uint32_t)q;
-      h[2 * j + 1] = (uint32_t)(q >> 32);
-    }
-    block_pick_bins<T>(st, h, digit, part, p.err);
-  };
-
-  // what the list of the first range, and every reading of the others, holds: keys that reach this
-  uint32_t bound = 0u, total = 0u;
-  bool spans = false, listed = false;
+  bool listed = false;
   uint32_t mine = 0u;  // the wave's entries in `list`
-  if (source == kTailSpans) {  // (k_pick_mask's rule)
-    bound = sv.ctrl[1];
-    constexpr int PER = kMaxChunks / T;
-    uint32_t m[PER], sum = 0u;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      m[j] = PER * tid + j < sv.d.geom.nchunks ? sv.mcount[PER * tid + j] : 0u;
-      sum += m[j];
-    }
-    uint32_t upto = block_prefix_incl<T>(sum, part, &total) - sum;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {  // (chunks that are not there: `total`)
-      chunk_at[PER * tid + j] = upto;
-      upto += m[j];
-    }
-    if (tid == 0) chunk_at[kMaxChunks] = total;
-    uint64_t limit = (uint64_t)k + ((uint64_t)n >> 3);
-    if (limit > sv.d.cap) limit = sv.d.cap;
-    spans = bound != kNoGuess && total >= k && total <= limit;
-    if (!spans) bound = 0u;
-  }
   const uint32_t share = spans ? (total + (uint32_t)(nranges * WAVES) - 1u) / (uint32_t)(nranges * WAVES) : 0u;
   // what a wave does not keep on chip goes to its part of the survivor list's memory
   const uint32_t room = sv.d.cap / (uint32_t)(nranges * WAVES);
@@ -3483,96 +3486,101 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
     cur = c;
     mine = 0u;
     __syncthreads();  // (`pool` is free)
+    // entries [e0, e1) of all, in order: this wave's (from the vector: what it has room for)
+    const uint64_t from = (uint64_t)((uint32_t)c * WAVES + (uint32_t)wave) * share;
+    const uint32_t e0 = from < total ? (uint32_t)from : total;
+    const uint32_t e1 = !spans ? (uint32_t)kTailKeep + room : total - e0 < share ? total : e0 + share;
+    int ch = 0;  // the chunk of entry e0: the last with no more entries in front of it
     if (spans) {
-      // entries [e0, e1) of all, in order: this wave's
-      const uint64_t from = (uint64_t)((uint32_t)c * WAVES + (uint32_t)wave) * share;
-      const uint32_t e0 = from < total ? (uint32_t)from : total, e1 = total - e0 < share ? total : e0 + share;
-      if (e0 < e1) {
-        int ch = 0;  // the chunk of entry e0: the last with no more entries in front of it
 #pragma unroll
-        for (int w = kMaxChunks / 2; w > 0; w >>= 1) ch += chunk_at[ch + w] <= e0 ? w : 0;
-        const int64_t span = p.tiles.span, nspans = (n + span - 1) / span;
-        uint32_t at = chunk_at[ch];  // entries in front of span s0
-        for (int64_t s0 = (int64_t)ch * sv.d.geom.chunk_elems / span; s0 < nspans && at < e1; s0 += 64) {
-          const uint32_t cnt = s0 + lane < nspans ? sv.tcnt[s0 + lane] : 0u;
-          const uint32_t incl = wave_incl_scan(cnt);
-          const uint64_t some = __ballot(at + incl > e0 && at + incl - cnt < e1 && cnt != 0u);
-          for (uint64_t left = some; left != 0ull;) {  // four spans' loads in flight
-            uint2 ent[4];
-            uint32_t first[4], cn[4];
-            const uint2* piece[4];
+      for (int w = kMaxChunks / 2; w > 0; w >>= 1) ch += same(chunk_at[ch + w]) <= e0 ? w : 0;
+    }
+    const uint32_t span = (uint32_t)p.tiles.span, nspans = spans ? (n + span - 1u) / span : 1u;
+    uint32_t at = spans ? same(chunk_at[ch]) : 0u;  // entries in front of span s0
+    for (uint32_t s0 = spans ? (uint32_t)(ch * same((int)sv.d.geom.chunk_elems)) / span : 0u; s0 < nspans && at < e1; s0 += 64u) {
+      uint32_t cnt = 0u, incl = 0u;
+      uint64_t read = 1ull;  // what has to be taken from the vector: the wave's rows, or spans with more than their pieces hold
+      if (spans) {
+        cnt = s0 + (uint32_t)lane < nspans ? sv.tcnt[s0 + (uint32_t)lane] : 0u;
+        incl = wave_incl_scan(cnt);
+        const uint64_t some = __ballot(at + incl > e0 && at + incl - cnt < e1 && cnt != 0u);
+        read = some & __ballot(cnt > (uint32_t)sv.tcap);
+        for (uint64_t left = some & ~read; left != 0ull;) {  // four spans' loads in flight
+          uint2 ent[4];
+          uint32_t first[4], cn[4], span_of[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int s = left != 0ull ? __builtin_ctzll(left) : 0;
-              cn[q] = left != 0ull ? __shfl(cnt, s, 64) : 0u;
-              first[q] = at + __shfl(incl, s, 64) - __shfl(cnt, s, 64);  // the number of its first entry
-              piece[q] = sv.tbuf + (size_t)(s0 + s) * (size_t)sv.tcap;
-              left &= left - 1ull;
-              if (cn[q] > (uint32_t)sv.tcap) {  // more than its piece holds: from the vector
-                const int64_t x0 = (s0 + s) * span, x1 = x0 + span < n ? x0 + span : n;
-                (void)wave_collect(x, x0, x1, bound, pool.qu[wave], kQuotaInf,
-                                   [&](uint32_t m, int64_t j, uint32_t raw) __attribute__((always_inline)) {
-                                     const uint32_t e = first[q] + m;
-                                     if (e >= e0 && e < e1) put(c, e - e0, make_uint2((uint32_t)j, raw));
-                                   });
-                cn[q] = 0u;
-              }
-              ent[q] = piece[q][(uint32_t)lane < cn[q] ? lane : 0];
-            }
+          for (int q = 0; q < 4; ++q) {
+            const int s = left != 0ull ? __builtin_ctzll(left) : 0;
+            cn[q] = left != 0ull ? (uint32_t)__builtin_amdgcn_readlane((int)cnt, s) : 0u;
+            first[q] = at + (uint32_t)__builtin_amdgcn_readlane((int)(incl - cnt), s);  // the number of its first entry
+            span_of[q] = s0 + (uint32_t)s;
+            left &= left - 1ull;
+            ent[q] = sv.tbuf[(size_t)span_of[q] * (size_t)sv.tcap + ((uint32_t)lane < cn[q] ? lane : 0)];
+          }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              for (uint32_t m = (uint32_t)lane; m < cn[q]; m += 64u) {
-                const uint32_t e = first[q] + m;
-                if (m >= 64u) ent[q] = piece[q][m];
-                if (e >= e0 && e < e1) put(c, e - e0, ent[q]);
-              }
+          for (int q = 0; q < 4; ++q) {
+            for (uint32_t m0 = 0u; m0 < cn[q]; m0 += 64u) {
+              const uint32_t m = m0 + (uint32_t)lane, e = first[q] + m;
+              if (m0 != 0u && m < cn[q]) ent[q] = sv.tbuf[(size_t)span_of[q] * (size_t)sv.tcap + m];
+              if (m < cn[q] && e >= e0 && e < e1) put(c, e - e0, ent[q]);
             }
           }
-          at += __shfl(incl, 63, 64);
         }
-        mine = e1 - e0;
       }
-    } else {
-      mine = wave_collect(x, lo_of(c), hi_of(c), bound, pool.qu[wave], (uint32_t)kTailKeep + room,
-                          [&](uint32_t m, int64_t j, uint32_t raw) __attribute__((always_inline)) {
-                            put(c, m, make_uint2((uint32_t)j, raw));
-                          });
+      for (; read != 0ull; read &= read - 1ull) {
+        const int s = __builtin_ctzll(read);
+        const uint32_t first = at + (uint32_t)__builtin_amdgcn_readlane((int)(incl - cnt), s);
+        const uint32_t x0 = (s0 + (uint32_t)s) * span, x1 = spans && n - x0 > span ? x0 + span : n;
+        const auto own = rows_of(c);
+        const uint32_t found = wave_collect<spans || full>(
+            x, x1, p.zero_base, spans ? (int)((x1 - x0 + 255u) / 256u) : nrows,
+            [&](int r) __attribute__((always_inline)) { return spans ? x0 + 256u * (uint32_t)r : own(r); },
+            bound, pool.qu[wave], spans ? e1 - first : e1, [&](uint32_t m, uint32_t j, uint32_t raw) __attribute__((always_inline)) {
+              const uint32_t e = first + m;
+              if (e >= e0 && e < e1) put(c, e - e0, make_uint2(j, raw));
+            });
+        if (!spans) mine = found;
+      }
+      at += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
+    if (spans) mine = e0 < e1 ? e1 - e0 : 0u;
     __syncthreads();
+    mine = same(mine);
     listed = mine <= (uint32_t)kTailKeep + room;
   };
   auto entry = [&](int c, uint32_t i) __attribute__((always_inline)) {
     return i < (uint32_t)kTailKeep ? list[wave][i] : more_of(c)[i - kTailKeep];
   };
-  // use(element, raw bits) for every survivor of range c, in some thread
+  // use(element, raw bits) for every survivor of range c, and others below the bound, in some thread
   auto each = [&](int c, auto use) __attribute__((always_inline)) {
-    if (listed && c == cur) {
-      for (uint32_t i = (uint32_t)lane; i < mine; i += 256u) {  // four entries in flight
+    if (spans || (listed && c == cur)) {
+      for (uint32_t q0 = 0u; q0 < mine; q0 += 256u) {  // four entries in flight
         uint2 ent[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ent[q] = entry(c, i + 64u * q < mine ? i + 64u * q : i);
+        for (uint32_t q = 0u; q < 4u; ++q) {
+          const uint32_t i = q0 + 64u * q + (uint32_t)lane;
+          ent[q] = entry(c, i < mine ? i : mine - 1u);
+        }
+        if (spans) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (i + 64u * q < mine) use((int64_t)ent[q].x, ent[q].y);
+          for (uint32_t q = 0u; q < 4u; ++q)
+            if (q0 + 64u * q + (uint32_t)lane < mine) use(ent[q].x, ent[q].y);
+          continue;
+        }
+#pragma unroll 1
+        for (uint32_t m = q0; m < mine && m < q0 + 256u; m += 64u) {
+          if (m + (uint32_t)lane < mine) use(ent[0].x, ent[0].y);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) ent[q] = ent[q + 1];
+        }
       }
     } else {
-      wave_each(x, lo_of(c), hi_of(c), bound, use);
-    }
-  };
-  // counts digit `digit` of range c's candidates and adds that to dst
-  auto digits = [&](int c, int digit, uint32_t* dst) __attribute__((always_inline)) {
-    clear_hist();
-    const uint32_t lo = st.lo, hi = st.hi;
-    const int sh = digit_shift(digit);
-    each(c, [&](int64_t, uint32_t raw) __attribute__((always_inline)) {
-      const uint32_t kk = raw & kKeyMask;
-      if (kk >= lo && kk <= hi) wave_count(pool.hist, (kk >> sh) & 0xfffu);
-    });
-    __syncthreads();
+      wave_walk<full>(x, n, p.zero_base, nrows, rows_of(c), [&](int, uint32_t j, uint4 v) __attribute__((always_inline)) {
+        const uint32_t raw[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int i = 0; i < BPT; ++i) {
-      const uint32_t v = pool.hist[i * T + tid];
-      if (v) atomicAdd(&dst[i * T + tid], v);
+        for (uint32_t e = 0u; e < 4u; ++e)
+          if (j + e < n) use(j + e, raw[e]);
+      }, []() { return false; });
     }
   };
   auto report_state = [&]() __attribute__((always_inline)) {  // what select_info reports: the state behind the top digit
@@ -3581,123 +3589,208 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
     st1.list_count = spans ? total : st1.compact_level ? st.n_gt + st.cand : 0u;
     st1.use_mask = spans ? 1u : 0u;
     st1.list_lo = spans ? bound : 0u;
-    st1.need_full = source == kTailSpans && !spans ? 1u : 0u;
+    st1.need_full = full ? 1u : 0u;
   };
+  // the piece that element j of a wave's belongs to (exact: fewer than 2^20 steps of 2048 << row_log2 elements)
+  const float per_piece = 1.0f / (float)nranges;
+  auto piece_of = [&](uint32_t j) __attribute__((always_inline)) {
+    static_assert(WAVES == 8, "a block's pieces of one number: 2048 << row_log2 elements");
+    return spans ? 0u : (uint32_t)(((float)(j >> (11 + row_log2)) + 0.5f) * per_piece);
+  };
+  const int kept_pieces = spans ? 1 : pieces;
   auto give_up = [&]() __attribute__((always_inline)) {
     if (tid == 0) atomicOr(p.err, kErrWait);
+    __builtin_amdgcn_wave_barrier();  // (the lanes meet here, not where the ways out of the loops do: those stay scalar)
   };
 
-  int stage = 0;
-  if (!spans && source == kTailHist) {  // the top digits' counts are there
-    uint32_t h[BPT];
-#pragma unroll
-    for (int j = 0; j < BPT; ++j) h[j] = 0u;
-    for (int r0 = 0; r0 < sv.htop_reps; r0 += 8) {
-      uint4 q[8][BPT / 4];
-#pragma unroll
-      for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int j = 0; j < BPT / 4; ++j)
-          q[r][j] = reinterpret_cast<const uint4*>(sv.htop + (size_t)(r0 + r < sv.htop_reps ? r0 + r : r0) * kHistBins)
-              [BPT / 4 * tid + j];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        if (r0 + r < sv.htop_reps) {
-#pragma unroll
-          for (int j = 0; j < BPT / 4; ++j) {
-            h[4 * j + 0] += q[r][j].x;
-            h[4 * j + 1] += q[r][j].y;
-            h[4 * j + 2] += q[r][j].z;
-            h[4 * j + 3] += q[r][j].w;
-          }
-        }
-      }
-    }
-    block_pick_bins<T>(st, h, 0, part, p.err);
-    bound = st.lo;
-    stage = 1;
-  }
+  constexpr bool counted = source == kTailHist;  // the top digits' counts are there
+  bool few = false;
+  uint32_t cand = 0u;      // candidates of the last digit
+  uint64_t ahead[kTailRanges / 64];  // kept_of of the wave's first piece, on its way while the threshold is picked
   // 0: the top digits of the survivors, or of everything where no bound is known yet; 1: the second digits of the
-  // candidates; 2: the last ones; 3: the outputs
-  for (int first = stage;; ++stage) {
-    const uint32_t klo = st.lo, khi = st.hi, quota = st.need, digit = klo & 0x7fu;
-    const int b = stage - first;
+  // candidates; 2: the last ones; 3: how many are kept of every piece; 4: the outputs
+  for (int stage = 0;; ++stage) {
+    const uint32_t klo = same(st.lo), khi = same(st.hi), quota = same(st.need);
     uint32_t* const dst = stage == 0 ? sv.hseg : stage == 1 ? sv.hist1 : sv.hist2;
-    for (int done = 0, look = c0 + 1;;) {
+    const bool digits = stage < 2 || (stage == 2 && !few);
+    const int sh_bits = digit_shift(stage), bins = (int)digit_mask(stage) + 1;
+    for (int done = 0, look = c0 + 1; stage > 0 || !counted;) {
       for (; done < n_owned; ++done) {
-        const int c = owned[done];
+        const int c = same((int)owned[done]);
         if (c != cur && (spans || stage > 0)) collect(c);
-        if (stage < 2) {
-          digits(c, stage, dst);
-          arrive(b, c);
+        const bool again = stage == 4 && n_owned > 1;  // (the last range's counts are there else)
+        if (stage < 4 || again) {
+          // the digits of the candidates, or the entries of the wave's pieces that reach klo (with a few candidates at
+          // stage 2 also these themselves)
+          __syncthreads();
+          if (digits) {
+            for (int i = tid; i < kHistBins / 4; i += T) reinterpret_cast<uint4*>(pool.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+          } else {
+            if (lane < kept_pieces) pool.kept.own[wave][lane] = make_uint2(0u, 0u);
+            if (tid == 0) few_n = 0u;
+          }
+          __syncthreads();
+          auto digit = [&](uint32_t kk) __attribute__((always_inline)) {
+            if (kk >= klo && kk <= khi) wave_count(pool.hist, (kk >> sh_bits) & (uint32_t)(bins - 1));
+          };
+          auto hand_on = [&](uint32_t q, uint32_t kk) __attribute__((always_inline)) {
+            const uint32_t i = atomicAdd(&few_n, 1u);
+            if (i < (uint32_t)kTailFew)
+              pool.kept.few[i] = make_uint2((q * (uint32_t)nranges + (uint32_t)c) * WAVES + (uint32_t)wave, kk & 0x7fu);
+          };
+          uint32_t upA = 0u, atB = 0u;
+          if (spans && digits) {
+            each(c, [&](uint32_t, uint32_t raw) __attribute__((always_inline)) { digit(raw & kKeyMask); });
+          } else if (spans) {
+            each(c, [&](uint32_t, uint32_t raw) __attribute__((always_inline)) {
+              const uint32_t kk = raw & kKeyMask;
+              if (kk > khi) {
+                ++upA;
+              } else if (kk >= klo) {
+                ++atB;
+                if (stage == 2) hand_on(0u, kk);
+              }
+            });
+          } else {
+            each(c, [&](uint32_t j, uint32_t raw) __attribute__((always_inline)) {
+              const uint32_t kk = raw & kKeyMask;
+              if (digits) return digit(kk);
+              if (kk < klo) return;
+              const uint32_t q = piece_of(j);
+              if (stage == 2 && kk <= khi) hand_on(q, kk);
+              for (bool left = true; left;) {  // (in order: the 64 lanes hold one piece's, or a few pieces')
+                const uint32_t one = __builtin_amdgcn_readfirstlane(q);
+                const uint64_t with = __ballot(q == one), up = __ballot(q == one && kk > khi);
+                if (q == one) {
+                  if (popc_lt(with) == 0u) {
+                    const uint32_t a = (uint32_t)__popcll(up);
+                    atomicAdd(&pool.kept.own[wave][one].x, a);
+                    atomicAdd(&pool.kept.own[wave][one].y, (uint32_t)__popcll(with) - a);
+                  }
+                  left = false;
+                }
+              }
+            });
+          }
+          if (spans && !digits) {
+            const uint64_t both = wave_allsum_u64(((uint64_t)upA << 32) | atB);
+            if (lane == 0) pool.kept.own[wave][0] = make_uint2((uint32_t)(both >> 32), (uint32_t)both);
+          }
+          __syncthreads();
+        }
+        if (digits) {
+          for (int i = tid; i < bins; i += T) {
+            const uint32_t v = pool.hist[i];
+            if (v) atomicAdd(&dst[i], v);
+          }
+          arrive(stage, c);
           continue;
         }
         if (stage == 2) {
-          uint32_t up = 0u;
-          each(c, [&](int64_t, uint32_t raw) __attribute__((always_inline)) {
-            const uint32_t kk = raw & kKeyMask;
-            up += kk > khi ? 1u : 0u;
-            if (kk >= klo && kk <= khi) wave_count(tail, kk & 0x7fu);
-          });
-#pragma unroll
-          for (int o = 32; o > 0; o >>= 1) up += __shfl_xor(up, o, 64);
-          if (lane == 0) part[wave] = up;
-          __syncthreads();
-          if (wave == 0) {  // lane's digits 2 lane and 2 lane + 1
-            const uint32_t t0 = tail[2 * lane], t1 = tail[2 * lane + 1];
-            if (t0) atomicAdd(&sv.hist2[2 * lane], t0);
-            if (t1) atomicAdd(&sv.hist2[2 * lane + 1], t1);
-            uint32_t s = t0 + t1;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-              const uint32_t y = __shfl_down(s, off, 64);
-              if (lane + off < 64) s += y;
-            }
-            store_through(reinterpret_cast<uint64_t*>(rows + (size_t)c * 128) + lane, ((uint64_t)(s - t0) << 32) | s);
-            tail[2 * lane] = tail[2 * lane + 1] = 0u;
-            if (lane == 0) {
-              uint32_t sum = 0u;
-#pragma unroll
-              for (int w = 0; w < WAVES; ++w) sum += part[w];
-              store_through(&above[c], sum);
+          const uint32_t mine_few = same(few_n < (uint32_t)kTailFew ? few_n : (uint32_t)kTailFew);
+          if (tid < kTailSlots) {
+            const uint2 f = pool.kept.few[tid];
+            store_through(&slots_of[c * kTailSlots + tid], (uint32_t)tid < mine_few ? ((uint64_t)f.y << 32) | f.x : ~(uint64_t)0);
+          }
+          if (mine_few > (uint32_t)kTailSlots) {
+            const uint32_t more = mine_few - (uint32_t)kTailSlots;
+            if (tid == 0)
+              few_at = __hip_atomic_fetch_add(&count[kTailFewAt], more, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            if ((uint32_t)tid < more && few_at + (uint32_t)tid < (uint32_t)kTailFew) {
+              const uint2 f = pool.kept.few[kTailSlots + tid];
+              store_through(&few_of[few_at + (uint32_t)tid], ((uint64_t)f.y << 32) | f.x);
             }
           }
-          arrive(b, c);
+        }
+        if (stage < 4) {
+          if (tid < kept_pieces) {
+            uint64_t sum = 0ull;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) sum += ((uint64_t)pool.kept.own[w][tid].x << 32) | pool.kept.own[w][tid].y;
+            store_through(&kept_of[(size_t)tid * nranges + c], sum);
+          }
+          arrive(stage, c);
           continue;
         }
-        // kept in front of the range: keys above the threshold, and at it
-        uint64_t before = 0ull;
-        if (tid < c) {
-          const uint32_t* row = rows + (size_t)tid * 128 + digit;
-          const uint32_t at = load_through(row), more = digit < 127u ? load_through(row + 1) : 0u;
-          before = ((uint64_t)(load_through(&above[tid]) + more) << 32) | (at - more);
-        }
-        before = wave_allsum_u64(before);
-        // the wave's own
-        uint32_t nA = 0u, nB = 0u;
-        each(c, [&](int64_t, uint32_t raw) __attribute__((always_inline)) {
-          const uint32_t kk = raw & kKeyMask;
-          nA += kk > khi ? 1u : 0u;
-          nB += kk >= klo && kk <= khi ? 1u : 0u;
-        });
-        const uint64_t own = wave_allsum_u64(((uint64_t)nA << 32) | nB);
-        __syncthreads();  // (wtot and wfront are free)
-        if (lane == 0) {
-          wtot[wave] = own;
-          wfront[wave] = before;
+        // kept in front of every piece of the wave's
+        for (int q = wave, turn = 0; q < kept_pieces; q += WAVES, ++turn) {
+          uint64_t all = 0ull, before = 0ull;
+#pragma unroll
+          for (int i = 0; i < kTailRanges / 64; ++i) {
+            const int r = lane + 64 * i;
+            uint64_t v = 0ull;
+            if (turn == 0)
+              v = ahead[i];
+            else if (r < nranges)
+              v = load_through(&kept_of[(size_t)q * nranges + r]);
+            if (few) v &= ~0xffffffffull;
+            all += v;
+            before += r < c ? v : 0ull;
+          }
+          all = wave_allsum_u64(all);
+          before = wave_allsum_u64(before);
+          if (lane == 0) {
+            pool.kept.all[q] = all;
+            pool.kept.before[q] = before;
+          }
         }
         __syncthreads();
-        uint64_t front = 0ull;
+        if (few) {  // (candidates above the threshold, or at it)
+          if (!again) {
+            if (lane < kept_pieces) pool.kept.own[wave][lane].y = 0u;
+            __syncthreads();
+          }
+          const uint2 f = few_all[tid];
+          if ((uint32_t)tid < cand && f.y >= (klo & 0x7fu)) {
+            const uint32_t at = f.x / WAVES, q = (at / (uint32_t)nranges) & (uint32_t)(kTailPieces - 1);
+            const uint32_t range = at - q * (uint32_t)nranges;
+            const bool up = f.y > (klo & 0x7fu);
+            const uint64_t v = up ? 1ull << 32 : 1ull;
+            atomicAdd(reinterpret_cast<unsigned long long*>(&pool.kept.all[q]), v);
+            if (range < (uint32_t)c) atomicAdd(reinterpret_cast<unsigned long long*>(&pool.kept.before[q]), v);
+            if (range == (uint32_t)c && !again) {
+              uint2* const own = &pool.kept.own[f.x % WAVES][q];
+              atomicAdd(up ? &own->x : &own->y, 1u);
+            }
+          }
+          __syncthreads();
+        }
+        {
+          const bool real = lane < kept_pieces;
+          uint64_t mine_q = 0ull, front = real ? pool.kept.before[lane] : 0ull;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) front += wfront[w] + (w < wave ? wtot[w] : 0ull);
-        uint32_t runA = (uint32_t)(front >> 32), runB = (uint32_t)front;
-        auto keep = [&](uint32_t a, uint32_t b, int64_t j, uint32_t raw) __attribute__((always_inline)) {
+          for (int w = 0; w < WAVES; ++w) {
+            const uint2 o = real ? pool.kept.own[w][lane] : make_uint2(0u, 0u);
+            const uint64_t v = ((uint64_t)o.x << 32) | o.y;
+            front += w < wave ? v : 0ull;
+            mine_q = w == wave ? v : mine_q;
+          }
+          uint64_t all = real ? pool.kept.all[lane] : 0ull, own = mine_q;
+          const uint64_t all0 = all;
+#pragma unroll
+          for (int off = 1; off < 64; off <<= 1) {
+            const uint64_t ya = __shfl_up(all, off, 64), yo = __shfl_up(own, off, 64);
+            if (lane >= off) {
+              all += ya;
+              own += yo;
+            }
+          }
+          front += all - all0;
+          own -= mine_q;
+          if (real)
+            pool.kept.front[wave][lane] =
+                make_uint2((uint32_t)(front >> 32) - (uint32_t)(own >> 32), (uint32_t)front - (uint32_t)own);
+        }
+        __syncthreads();
+        uint32_t runA = 0u, runB = 0u;
+        auto keep = [&](uint32_t a, uint32_t b, uint32_t j, uint32_t raw) __attribute__((always_inline)) {
           const uint32_t m = a + (b < quota ? b : quota);
           if (m >= k) return;
           sv.idx_out[m] = (int32_t)j;
           if (sv.vals_row) sv.vals_row[m] = __uint_as_float(raw);
         };
-        if (listed) {
+        if (spans || listed) {
           for (uint32_t q0 = 0u; q0 < mine; q0 += 256u) {
             uint2 four[4];
 #pragma unroll
@@ -3705,49 +3798,38 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
               const uint32_t q = q0 + 64u * u + (uint32_t)lane;
               four[u] = entry(c, q < mine ? q : mine - 1u);
             }
+#pragma unroll 1
+            for (uint32_t m = q0; m < mine && m < q0 + 256u; m += 64u) {
+              const bool ok = m + (uint32_t)lane < mine;
+              const uint2 ent = four[0];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const bool ok = q0 + 64u * u + (uint32_t)lane < mine;
-              const uint2 ent = four[u];
+              for (int u = 0; u < 3; ++u) four[u] = four[u + 1];
               const uint32_t kk = ent.y & kKeyMask;
               const bool is_a = ok && kk > khi, is_b = ok && kk >= klo && kk <= khi;
               const uint64_t ma = __ballot(is_a), mb = __ballot(is_b);
-              const uint32_t a = runA + popc_lt(ma), b = runB + popc_lt(mb);
-              if (is_a || (is_b && b < quota)) keep(a, b, (int64_t)ent.x, ent.y);
+              if (is_a || is_b) {
+                const uint2 front = pool.kept.front[wave][piece_of(ent.x)];
+                const uint32_t a = front.x + runA + popc_lt(ma), b = front.y + runB + popc_lt(mb);
+                if (is_a || b < quota) keep(a, b, ent.x, ent.y);
+              }
               runA += (uint32_t)__popcll(ma);
               runB += (uint32_t)__popcll(mb);
             }
           }
         } else {
-          const int64_t hi_e = hi_of(c);
-          for (int64_t base = lo_of(c); base < hi_e; base += kSpanStep) {
-            uint4 rows8[8];  // eight rows in flight
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const int64_t j = base + 4 * (lane + 64 * u);
-              rows8[u] = make_uint4(0u, 0u, 0u, 0u);
-              if (j + 4 <= hi_e) {
-                rows8[u] = *reinterpret_cast<const uint4*>(x + j);
-              } else {
-                if (j + 0 < hi_e) rows8[u].x = __float_as_uint(x[j + 0]);
-                if (j + 1 < hi_e) rows8[u].y = __float_as_uint(x[j + 1]);
-                if (j + 2 < hi_e) rows8[u].z = __float_as_uint(x[j + 2]);
-              }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const int64_t j = base + 4 * (lane + 64 * u);
-              const uint32_t raw[4] = {rows8[u].x, rows8[u].y, rows8[u].z, rows8[u].w};
+          wave_walk<full>(x, n, p.zero_base, nrows, rows_of(c), [&](int r, uint32_t j, uint4 v) __attribute__((always_inline)) {
+              const uint32_t raw[4] = {v.x, v.y, v.z, v.w};
               uint32_t isA = 0u, isB = 0u;
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
                 const uint32_t kk = raw[e] & kKeyMask;
-                isA |= j + e < hi_e && kk > khi ? 1u << e : 0u;
-                isB |= j + e < hi_e && kk >= klo && kk <= khi ? 1u << e : 0u;
+                isA |= j + e < n && kk > khi ? 1u << e : 0u;
+                isB |= j + e < n && kk >= klo && kk <= khi ? 1u << e : 0u;
               }
-              if (__ballot((isA | isB) != 0u) == 0ull) continue;
+              if (__ballot((isA | isB) != 0u) == 0ull) return;
               const uint32_t cA = (uint32_t)__popc(isA), cB = (uint32_t)__popc(isB);
-              uint32_t a = runA, b = runB;
+              const uint2 front = pool.kept.front[wave][r >> row_log2];
+              uint32_t a = front.x + runA, b = front.y + runB;
 #pragma unroll
               for (int q = 0; q < 3; ++q) {
                 const uint64_t pa = __ballot((cA >> q) & 1u), pb = __ballot((cB >> q) & 1u);
@@ -3763,13 +3845,13 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
                 a += is_a ? 1u : 0u;
                 b += is_b ? 1u : 0u;
               }
-            }
-          }
+          }, []() { return false; });
         }
       }
-      if (stage == 3) return;
-      if (wait(b, b == 0 ? kTailHelpSpins : kSpinLimit)) break;
-      if (b > 0) return give_up();
+      if (stage == 4) return;
+      const bool first = stage == (counted ? 1 : 0);
+      if (wait(stage, first ? kTailHelpSpins : kSpinLimit)) break;
+      if (!first) return give_up();
       // a range that nobody has taken: its block does not run yet, and may not before this one is done
       if (tid == 0) {
         verdict = -1;
@@ -3782,18 +3864,86 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
         if (verdict >= 0) owned[n_owned] = (uint16_t)verdict;
       }
       __syncthreads();
-      const bool taken = verdict >= 0;
+      const bool taken = same(verdict) >= 0;
       __syncthreads();
       if (taken) {
         ++n_owned;
       } else {  // all belong to blocks that run
-        if (!wait(b, kSpinLimit)) return give_up();
+        if (!wait(stage, kSpinLimit)) return give_up();
         break;
       }
     }
+    if (!digits) {
+#pragma unroll
+      for (int i = 0; i < kTailRanges / 64; ++i)
+        ahead[i] = wave < kept_pieces && lane + 64 * i < nranges
+                       ? load_through(&kept_of[(size_t)wave * nranges + lane + 64 * i]) : 0ull;
+    }
+    if (stage == 3) continue;
     if (stage == 1 && tid == 0) report_state();
-    pick(dst, stage);
-    if (stage == 0 && !spans) bound = st.lo;
+    uint32_t h[BPT];
+    if (stage == 0 && counted) {
+#pragma unroll
+      for (int j = 0; j < BPT; ++j) h[j] = 0u;
+      for (int r0 = 0; r0 < sv.htop_reps; r0 += 8) {
+        uint4 q[8][BPT / 4];
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+          for (int j = 0; j < BPT / 4; ++j)
+            q[r][j] = reinterpret_cast<const uint4*>(sv.htop + (size_t)(r0 + r < sv.htop_reps ? r0 + r : r0) * kHistBins)
+                [BPT / 4 * tid + j];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          if (r0 + r < sv.htop_reps) {
+#pragma unroll
+            for (int j = 0; j < BPT / 4; ++j) {
+              h[4 * j + 0] += q[r][j].x;
+              h[4 * j + 1] += q[r][j].y;
+              h[4 * j + 2] += q[r][j].z;
+              h[4 * j + 3] += q[r][j].w;
+            }
+          }
+        }
+      }
+    } else if (stage == 2 && few) {
+      constexpr int PER = kTailRanges * kTailSlots / T;
+      uint64_t f[PER];
+#pragma unroll
+      for (int i = 0; i < PER; ++i) f[i] = i * T + tid < nranges * kTailSlots ? load_through(&slots_of[i * T + tid]) : ~(uint64_t)0;
+      if (tid == 0) few_n = 0u;
+      __syncthreads();
+      auto add = [&](uint64_t v) __attribute__((always_inline)) {
+        const uint32_t i = atomicAdd(&few_n, 1u);
+        if (i < (uint32_t)kTailFew) few_all[i] = make_uint2((uint32_t)v, (uint32_t)(v >> 32) & 0x7fu);
+        atomicAdd(&tail[(uint32_t)(v >> 32) & 0x7fu], 1u);
+      };
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (f[i] != ~(uint64_t)0) add(f[i]);
+      __syncthreads();
+      const uint32_t there = same(few_n);
+      if (there < cand) {  // some range has more than its places take
+        __syncthreads();
+        if ((uint32_t)tid < cand - there) add(load_through(&few_of[tid]));
+        __syncthreads();
+      }
+#pragma unroll
+      for (int j = 0; j < BPT; ++j) h[j] = BPT * tid < 128 ? tail[(BPT * tid + j) & 127] : 0u;
+    } else {
+#pragma unroll
+      for (int j = 0; j < BPT / 2; ++j) {
+        const uint64_t q = BPT * tid < bins ? load_through(reinterpret_cast<const uint64_t*>(dst) + BPT / 2 * tid + j) : 0ull;
+        h[2 * j] = (uint32_t)q;
+        h[2 * j + 1] = (uint32_t)(q >> 32);
+      }
+    }
+    block_pick_bins<T>(st, h, stage, part, p.err);
+    if (stage == 1) {
+      cand = same(st.cand);
+      few = cand <= (uint32_t)kTailFew;
+    }
+    if (stage == 0 && !spans) bound = same(st.lo);
     if (stage == 2) {
       bool reports = false;
       for (int i = 0; i < n_owned; ++i) reports = reports || owned[i] == 0;
@@ -3801,9 +3951,64 @@ k_tail(SelParams p, LeaderArgs la, int source, int64_t wave_elems) {
         *sv.st = st1;
         if (st.level != 3u) atomicOr(p.err, kErrSequence);
       }
-      if (st.level != 3u) return;
+      if (same(st.level) != 3u) return;
+      if (few) ++stage;  // (how many are kept in front of every piece is known)
     }
   }
+}
+
+template <int source>
+__global__ void __launch_bounds__(64 * kTailWaves)
+k_tail(SelParams p, LeaderArgs la, int row_log2) {
+  __shared__ TailShared sh;
+  constexpr int T = 64 * kTailWaves;
+  const int tid = threadIdx.x;
+  // (set before this launch, or by a block of it that has given up: then the others do too, if they wait for this one)
+  if (*p.err != 0u) return;
+  if (tid == 0) sh.verdict = -1;
+  if (source == kTailHist && la.partials != nullptr) {  // (every block finds, and writes, the same)
+    const int best = block_take_leader(la);
+    if (tid == 0) sh.verdict = best;
+  }
+  __syncthreads();
+  SegView sv = seg_view(p, blockIdx.y, same(sh.verdict));
+  sv.x = same_ptr(sv.x);
+  sv.hist1 = same_ptr(sv.hist1);
+  sv.hist2 = same_ptr(sv.hist2);
+  sv.hseg = same_ptr(sv.hseg);
+  sv.htop = same_ptr(sv.htop);
+  sv.tbuf = same_ptr(sv.tbuf);
+  sv.tcnt = same_ptr(sv.tcnt);
+  sv.list = same_ptr(sv.list);
+  sv.idx_out = same_ptr(sv.idx_out);
+  sv.vals_row = same_ptr(sv.vals_row);
+  sv.d.k = same(sv.d.k);
+  sv.d.cap = same(sv.d.cap);
+  __syncthreads();  // (verdict has been read)
+  if (source == kTailSpans) {
+    constexpr int PER = kMaxChunks / T;
+    uint32_t m[PER], sum = 0u, total;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      m[j] = PER * tid + j < sv.d.geom.nchunks ? sv.mcount[PER * tid + j] : 0u;
+      sum += m[j];
+    }
+    uint32_t upto = block_prefix_incl<T>(sum, sh.part, &total) - sum;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {  // (chunks that are not there: `total`)
+      sh.chunk_at[PER * tid + j] = upto;
+      upto += m[j];
+    }
+    total = same(total);
+    if (tid == 0) sh.chunk_at[kMaxChunks] = total;
+    const uint32_t bound = same(sv.ctrl[1]);
+    uint64_t limit = (uint64_t)sv.d.k + ((uint64_t)p.n >> 3);  // (k_pick_mask's rule)
+    if (limit > sv.d.cap) limit = sv.d.cap;
+    if (bound != kNoGuess && total >= sv.d.k && total <= limit)
+      return tail_select<kTailSpans, false>(p, sv, sh, row_log2, bound, total);
+    return tail_select<kTailNone, true>(p, sv, sh, row_log2, 0u, 0u);
+  }
+  tail_select<source, false>(p, sv, sh, row_log2, 0u, 0u);
 }
 
 // ---------------------------------------------------------------------------

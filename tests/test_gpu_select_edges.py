@@ -326,17 +326,19 @@ def test_segmented_leader_pass(start, g):
         assert np.array_equal(rd[r].cpu().numpy().view(np.uint32), want.residual[r].view(np.uint32))
 
 
-# steps on the histogram route: a wave's elements are rows of 256 (one row each, an element more, many); survivors of the
-# top digit that a wave keeps on chip, that go to the list's memory, and that do not fit there either
-@pytest.mark.parametrize("n", [(1 << 19), (1 << 19) + 1, 9_000_001])
-@pytest.mark.parametrize("kind", ["normal", "special", "run", "half", "equal"])
-def test_steps_whose_survivors_outgrow_a_wave(n, kind, monkeypatch):
+# the one-launch selection behind a pass: a wave's elements are rows of 256 (one row each, an element more, many);
+# survivors of the top digit that a wave keeps on chip, that go to the list's memory, and, where few may be kept, that do
+# not fit there either; more and fewer than 512 candidates for the last digit
+@pytest.mark.parametrize("n,kmax", [(1 << 19, 1 << 17), ((1 << 19) + 1, 1 << 17), (9_000_001, 2_250_000), (9_000_001, 90_000)])
+@pytest.mark.parametrize("kind", ["normal", "special", "run", "half", "equal", "sorted"])
+def test_steps_whose_survivors_outgrow_a_wave(n, kmax, kind, monkeypatch):
     from tests import gpu_util
     from tests.gpu_util import GpuRunner, assert_step_matches
 
     monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 0)
+    monkeypatch.setitem(gpu_util.OPTIONS, "leader_first", 0)  # (a selection in front of the other workers' pass is not it)
     rng = np.random.default_rng(n)
-    w, kmax = 2, n // 4
+    w = 2
     g = [_values(rng, n, kind) for _ in range(w)]
     if kind == "run":
         for r, x in enumerate(g):
@@ -347,11 +349,71 @@ def test_steps_whose_survivors_outgrow_a_wave(n, kind, monkeypatch):
             rng.shuffle(x)
     elif kind == "equal":
         g = [np.full(n, np.float32(0.5 - r)) for r in range(w)]
+    elif kind == "sorted":
+        g = [np.sort(np.abs(x)) for x in g]
     runner = GpuRunner(w, n, kmax)
-    for step_no, k in enumerate((1, n // 100, kmax), 1):
+    for step_no, k in enumerate(sorted({1, n // 100, kmax}), 1):
         res = [np.zeros(n, np.float32) for _ in range(w)]
         want = orc.step(g, res, k, orc.MODE_STAR, step_no=step_no)
         runner.load_g(g)
         runner.load_res(res)
         assert_step_matches(runner.step(k, orc.MODE_STAR, step_no, want_vals=True), want, orc.MODE_STAR)
+        assert gpu_util.FORCED or runner.ctx.select_info()["one_launch"] == 1
         runner.ctx.status()
+
+
+# large values that lie together may not cost the one-launch selection behind a pass much more than others do: a run of
+# them made a step a quarter longer with the list kernels (163 and 131 us), by 0.6 with a wave's elements in one piece, by
+# a quarter in many (0.4 leaves room for the clock)
+def test_steps_on_a_run_of_large_values_take_little_longer():
+    import torch
+    import paper_2312_02493_amd as lib
+
+    n, w = 11_689_512, 2
+    k = n // 100
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    src = {"normal": [torch.randn(n, generator=gen, device="cuda") for _ in range(w)]}
+    src["run"] = [x.clone() for x in src["normal"]]
+    for x in src["run"]:
+        x[n // 2:n // 2 + n // 100] += 50.0
+    g = [torch.zeros(n, device="cuda") for _ in range(w)]
+    idx = torch.zeros(k, dtype=torch.int32, device="cuda")
+    sm, up = torch.zeros(k, device="cuda"), torch.zeros(n, device="cuda")
+    ctx = lib.Context(w, n, k)
+    best = {}
+    for kind in ("normal", "run") * 8:
+        res = [x.clone() for x in src[kind]]
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        t0.record()
+        ctx.artopk_step(g, res, k, lib.ARTOPK_VAR, 1, idx, sm, up)
+        t1.record()
+        assert ctx.select_info()["one_launch"] == 1
+        ctx.status()
+        best[kind] = min(best.get(kind, 1e9), t0.elapsed_time(t1))
+    assert best["run"] < 1.4 * best["normal"], best
+
+
+# a sampled bound that comes to nothing on a vector that is only read: the blocks count everything and read the vector
+# again, a wave's survivors on chip, in the list's memory or in neither
+@pytest.mark.parametrize("kind", ["equal", "two", "run"])
+def test_bound_that_comes_to_nothing(kind):
+    import torch
+    import gpu_util
+
+    n, k = 42_000_003, 4200
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n, generator=gen, device="cuda")
+    if kind == "equal":
+        x.fill_(-0.5)
+    elif kind == "two":
+        x = torch.where(x > 0, 1.0, -1.03)
+    else:  # more in one top digit than the pieces would hold
+        x[n // 3:n // 3 + n // 10] = 40.0 + torch.rand(n // 10, generator=gen, device="cuda")
+    ctx = gpu_util.make_context(1, n, k)
+    idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+    ctx.artopk_select_topk(x, k, idx)
+    info = ctx.select_info()
+    ctx.status()
+    assert gpu_util.FORCED or (info["guessed"], info["from_mask"], info["one_launch"]) == (1, 0, 1), info
+    assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x.cpu().numpy(), k))
