@@ -9,6 +9,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB_PATH = os.path.join(HERE, "libartopk.so")
+# the same with blocks that start late and waits that expire when a test says so (tests/test_gpu_held_blocks.py)
+HELD_PATH = os.path.join(HERE, "libartopk_held.so")
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -23,17 +25,22 @@ HIPCC_FLAGS = [
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     src = os.path.join(HERE, "csrc", "artopk.hip")
-    cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
-           src, "-o", LIB_PATH + ".tmp"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    proc = subprocess.run(cmd, capture_output=True, text=True)
-    if proc.returncode != 0:
-        sys.stderr.write(proc.stdout + proc.stderr)
-        raise RuntimeError("hipcc failed building libartopk.so")
-    if verbose and proc.stderr.strip():
-        sys.stderr.write(proc.stderr)
-    os.replace(LIB_PATH + ".tmp", LIB_PATH)
+    runs = []
+    for path, flags in ((LIB_PATH, []), (HELD_PATH, ["-DARTOPK_HELD_BLOCKS"])):
+        cmd = [hipcc, *HIPCC_FLAGS, *flags, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
+               src, "-o", path + ".tmp"]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        runs.append((path, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)))
+    for path, proc in runs:
+        out, err = proc.communicate()
+        if proc.returncode != 0:
+            sys.stderr.write(out + err)
+            raise RuntimeError(f"hipcc failed building {os.path.basename(path)}")
+        if verbose and err.strip():
+            sys.stderr.write(err)
+    for path, _ in runs:
+        os.replace(path + ".tmp", path)
     build_abi_client(hipcc, verbose)
     return LIB_PATH
 

@@ -2070,3 +2070,15 @@ int artopk_step_g16(artopk_ctx* ctx, const void* const* g, int32_t g_type, float
 }
 
 }  // extern "C"
+
+#ifdef ARTOPK_HELD_BLOCKS
+// For tests of how blocks take on others' work: sets HeldBlocks and says how many units were taken on since the last call.
+extern "C" int artopk_held_blocks(uint32_t ticks, uint32_t looks, uint32_t* helped_out) {
+  HeldBlocks h{};
+  if (hipDeviceSynchronize() != hipSuccess || hipMemcpyFromSymbol(&h, HIP_SYMBOL(held_blocks), sizeof(h)) != hipSuccess)
+    return ARTOPK_EHIP;
+  *helped_out = h.helped;
+  h = HeldBlocks{ticks, looks, 0u};
+  return hipMemcpyToSymbol(HIP_SYMBOL(held_blocks), &h, sizeof(h)) == hipSuccess ? ARTOPK_OK : ARTOPK_EHIP;
+}
+#endif

@@ -3186,6 +3186,138 @@ k_level2(SelParams p) {
 
 
 // ---------------------------------------------------------------------------
+// Blocks of one launch that wait for each other (k_tail, k_small_step).  The launch's work is cut into units, one for each
+// block, and a wait is for all units to be through with a part of it.  Nothing depends on how many blocks run at a time: a
+// block takes its unit with its first instructions (meet_take), and one that comes late finds it taken and leaves; before
+// the first wait a block that has looked kHelpLooks times takes on units that nobody has, one after the other
+// (meet_help), until all are taken.  Every unit then belongs to a block that runs, and those wait for no other.
+//   What blocks hand on goes through store_through, load_through and atomics, which are served behind the XCDs' own caches.
+// meet_arrive waits until this wave's have been (s_waitcnt vmcnt(0)), then for the block's other waves, and only then counts
+// the unit; loads behind meet_wait are issued after it has seen the count.  The orders that the language knows (a release
+// in front of the count, an acquire behind the look) would do the same and besides write back and invalidate the whole
+// cache once for every wave: 72 us instead of 28 on a step of 1 M x 4.
+//   Beside a stream of copies, whose blocks leave no compute unit empty for long, many blocks start late.  List kernels / 256
+// looks before every unit and one lane searching for it / 64 before the first and all lanes searching, us: select 25.6 M
+// 157/345/130, 138 M 325/607/283, step 11.7 M x 8 559/646/508, 3 M x 2 variance rule 145/264/115 (beside variances of 268 M
+// values 282/260/228, 578/343/342, 676/628/624, 198/254/229; beside matrix products 5 to 10 % less than the list kernels).
+// 16 looks take on units whose blocks are about to start: 1 M x 4 beside steps of 134 M x 2 100, else 53.
+// ---------------------------------------------------------------------------
+constexpr int kMeetWords = 8;   // words that the units of a wait are counted on,
+constexpr int kMeetLine = 32;   // so many words apart
+constexpr int kMeetWait = kMeetWords * kMeetLine;
+constexpr int kHelpLooks = 64;
+
+struct Meeting {
+  uint32_t* claim;  // [units] `mark`: somebody has taken the unit
+  uint32_t* count;  // [waits][kMeetWait] units that are through, zero at first
+  uint32_t mark;
+  int units;
+};
+
+#ifdef ARTOPK_HELD_BLOCKS
+// A build for tests: two blocks in three start late, and waits expire after a number of looks that the test sets.
+struct HeldBlocks {
+  uint32_t ticks;   // of 10 ns
+  uint32_t looks;   // instead of kSpinLimit
+  uint32_t helped;  // units taken on for others so far
+};
+__device__ HeldBlocks held_blocks;
+__device__ __forceinline__ void meet_start() {
+  if ((blockIdx.x + blockIdx.y) % 3u != 0u) {
+    const uint64_t from = wall_clock64();
+    for (int i = 0; i < (1 << 16) && wall_clock64() - from < held_blocks.ticks; ++i) __builtin_amdgcn_s_sleep(2);
+  }
+}
+__device__ __forceinline__ int meet_limit() { return (int)held_blocks.looks; }
+__device__ __forceinline__ void meet_helped() { atomicAdd(&held_blocks.helped, 1u); }
+#else
+__device__ __forceinline__ void meet_start() {}
+__device__ __forceinline__ int meet_limit() { return kSpinLimit; }
+__device__ __forceinline__ void meet_helped() {}
+#endif
+
+// What comes from on-chip memory and is the same in every lane, taken as such: addresses and loops stay scalar.
+template <typename V>
+__device__ __forceinline__ V same(V v) {
+  return (V)__builtin_amdgcn_readfirstlane((int)v);
+}
+template <typename V>
+__device__ __forceinline__ V* same_ptr(V* q) {
+  const uint64_t v = (uint64_t)q;
+  return (V*)(((uint64_t)same((uint32_t)(v >> 32)) << 32) | same((uint32_t)v));
+}
+
+// Whether unit u was still to be had; one lane calls it.
+__device__ __forceinline__ bool meet_take(const Meeting& m, int u) {
+  return __hip_atomic_exchange(&m.claim[u], m.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != m.mark;
+}
+
+// Unit u is through with the part in front of wait b; all threads of the block call it.
+__device__ __forceinline__ void meet_arrive(const Meeting& m, int b, int u) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_fetch_add(&m.count[b * kMeetWait + u % kMeetWords * kMeetLine], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits for `total` units, at most for 1 + looks looks; whether they are there.  If they are not in the end (meet_limit, a
+// second or so), the block sets the error word and leaves: blocks that come later leave at once, those that wait for its
+// units or theirs when their looks are used up, and artopk_status reports it and clears what the launch leaves behind.  All
+// threads of the block call it; sh is a word of on-chip memory, free before and after.
+__device__ __forceinline__ bool meet_wait(const Meeting& m, int b, int total, int looks, int& sh) {
+  if (same(threadIdx.x >> 6) == 0u) {
+    const uint32_t lane = lane_id();
+    bool ok = false;
+    for (int i = 0; !ok && i <= looks; ++i) {
+      uint32_t v = lane < (uint32_t)kMeetWords ? load_through(&m.count[b * kMeetWait + lane * kMeetLine]) : 0u;
+      v += __shfl_xor(v, 1, 64);
+      v += __shfl_xor(v, 2, 64);
+      v += __shfl_xor(v, 4, 64);
+      ok = same(v) == (uint32_t)total;
+    }
+    if (lane == 0u) sh = ok ? 1 : 0;
+  }
+  __syncthreads();
+  const bool ok = same(sh) != 0;
+  __syncthreads();
+  return ok;
+}
+
+// A unit that nobody had taken and that this block has now, searched for from `look` on, or -1.  helped (or nullptr) counts
+// them, before each is taken: a late block that finds its own taken finds it counted.  All threads of the block call it.
+__device__ __forceinline__ int meet_help(const Meeting& m, int look, uint32_t* helped, int& sh) {
+  if (same(threadIdx.x >> 6) == 0u) {
+    const int lane = (int)lane_id();
+    int got = -1;
+    for (int i = 0; i < m.units && got < 0; i += 64) {
+      const int u = (look + i + lane) % m.units;
+      uint64_t open = __ballot(i + lane < m.units && load_through(&m.claim[u]) != m.mark);
+      for (; open != 0ull && got < 0; open &= open - 1ull) {
+        const int c = (look + i + __builtin_ctzll(open)) % m.units;
+        int ok = 0;
+        if (lane == 0) {
+          if (helped) {
+            __hip_atomic_fetch_add(helped, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          }
+          ok = meet_take(m, c) ? 1 : 0;
+          if (ok)
+            meet_helped();
+          else if (helped)
+            __hip_atomic_fetch_sub(helped, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (same(ok) != 0) got = c;
+      }
+    }
+    if (lane == 0) sh = got;
+  }
+  __syncthreads();
+  const int got = same(sh);
+  __syncthreads();
+  return got;
+}
+
+// ---------------------------------------------------------------------------
 // k_tail : a flat selection from the top digits on (or several at a time, one per blockIdx.y), in one launch instead of
 // four behind a pass that counted the top digits (pick, compaction, list digits, final pass), six behind the read-only
 // marking or five behind nothing.  Those are bound by latency, 5 us for a launch and a trip to memory or two in each; here
@@ -3222,12 +3354,11 @@ constexpr int kTailRow = 256;
 constexpr int kTailPieces = 64;  // pieces of a wave's elements, at most
 constexpr int kTailFew = 64 * kTailWaves;  // candidates that are handed on one by one, a few of each range in places of its own
 constexpr int kTailSlots = 4;
-constexpr int kTailWaits = 4, kTailArrive = 8;
+constexpr int kTailWaits = 4;
 // in the words of kSegHist2 behind the last digit's 128 counts: whether somebody has taken a range, the waits' counters
 constexpr int kTailClaim = 128, kTailCount = 512;
-constexpr int kTailFewAt = kTailWaits * kTailArrive * 32;  // (behind kTailCount: candidates handed on so far)
+constexpr int kTailFewAt = kTailWaits * kMeetWait;  // (behind kTailCount: candidates handed on so far)
 static_assert(kTailClaim + kTailRanges <= kTailCount && kTailCount + kTailFewAt < kHistBins, "they fit");
-constexpr int kTailHelpSpins = 256;
 
 // Adds 1 to hist[bin] for every active lane; lanes with the first one's bin (all, where values are equal) in one addition.
 __device__ __forceinline__ void wave_count(uint32_t* hist, uint32_t bin) {
@@ -3376,17 +3507,6 @@ struct TailShared {
   uint32_t chunk_at[kMaxChunks + 1];  // entries in front of every chunk of the marking (kTailSpans)
 };
 
-// What comes from on-chip memory and is the same in every lane, taken as such: addresses and loops stay scalar.
-template <typename V>
-__device__ __forceinline__ V same(V v) {
-  return (V)__builtin_amdgcn_readfirstlane((int)v);
-}
-template <typename V>
-__device__ __forceinline__ V* same_ptr(V* q) {
-  const uint64_t v = (uint64_t)q;
-  return (V*)(((uint64_t)same((uint32_t)(v >> 32)) << 32) | same((uint32_t)v));
-}
-
 // k_tail's work.  full: behind a marking whose bound does not hold.  bound, total: kTailSpans' bound and the number of
 // entries that reach it.
 template <int source, bool full>
@@ -3412,8 +3532,8 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
   const float* x = sv.x;
   const uint32_t n = (uint32_t)p.n;
   const uint32_t k = sv.d.k;
-  uint32_t* const claim = sv.hist2 + kTailClaim;
   uint32_t* const count = sv.hist2 + kTailCount;
+  const Meeting meet{sv.hist2 + kTailClaim, count, 1u, nranges};
   // the wave's pieces of range c: `pieces` of them, 256 << row_log2 elements each, `stride` elements apart
   const uint32_t stride = ((uint32_t)nranges * WAVES) << (8 + row_log2);
   const int pieces = (int)((n + stride - 1u) / stride), nrows = pieces << row_log2;
@@ -3431,7 +3551,7 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
                              (size_t)vec * (kTailRanges * kTailSlots + kTailFew);
   uint64_t* const few_of = slots_of + kTailRanges * kTailSlots;
   if (tid == 0) {
-    verdict = __hip_atomic_exchange(&claim[c0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ? 1 : 0;
+    verdict = meet_take(meet, c0) ? 0 : 1;
     owned[0] = (uint16_t)c0;
     st = SelState{};
     st.hi = kKeyMask;
@@ -3442,31 +3562,6 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
   if (verdict != 0) return;
   int n_owned = 1;
 
-  auto arrive = [&](int b, int c) __attribute__((always_inline)) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0)
-      __hip_atomic_fetch_add(&count[(b * kTailArrive + c % kTailArrive) * 32], 1u, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-  };
-  auto arrived = [&](int b) __attribute__((always_inline)) {
-    uint32_t v = lane < kTailArrive ? load_through(&count[(b * kTailArrive + lane) * 32]) : 0u;
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    return __builtin_amdgcn_readfirstlane(v) == (uint32_t)nranges;
-  };
-  auto wait = [&](int b, int spins) __attribute__((always_inline)) {
-    if (wave == 0) {
-      bool ok = arrived(b);
-      for (int i = 0; !ok && i < spins; ++i) ok = arrived(b);
-      if (lane == 0) verdict = ok ? 1 : 0;
-    }
-    __syncthreads();
-    const bool ok = same(verdict) != 0;
-    __syncthreads();
-    return ok;
-  };
   bool listed = false;
   uint32_t mine = 0u;  // the wave's entries in `list`
   const uint32_t share = spans ? (total + (uint32_t)(nranges * WAVES) - 1u) / (uint32_t)(nranges * WAVES) : 0u;
@@ -3683,7 +3778,7 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
             const uint32_t v = pool.hist[i];
             if (v) atomicAdd(&dst[i], v);
           }
-          arrive(stage, c);
+          meet_arrive(meet, stage, c);
           continue;
         }
         if (stage == 2) {
@@ -3710,7 +3805,7 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
             for (int w = 0; w < WAVES; ++w) sum += ((uint64_t)pool.kept.own[w][tid].x << 32) | pool.kept.own[w][tid].y;
             store_through(&kept_of[(size_t)tid * nranges + c], sum);
           }
-          arrive(stage, c);
+          meet_arrive(meet, stage, c);
           continue;
         }
         // kept in front of every piece of the wave's
@@ -3850,28 +3945,14 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
       }
       if (stage == 4) return;
       const bool first = stage == (counted ? 1 : 0);
-      if (wait(stage, first ? kTailHelpSpins : kSpinLimit)) break;
-      if (!first) return give_up();
-      // a range that nobody has taken: its block does not run yet, and may not before this one is done
-      if (tid == 0) {
-        verdict = -1;
-        for (int i = 0; i < nranges && verdict < 0; ++i, ++look) {
-          const int c = look % nranges;
-          if (load_through(&claim[c]) == 0u &&
-              __hip_atomic_exchange(&claim[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-            verdict = c;
-        }
-        if (verdict >= 0) owned[n_owned] = (uint16_t)verdict;
-      }
+      if (meet_wait(meet, stage, nranges, first && look >= 0 ? (n_owned == 1 ? kHelpLooks : 0) : meet_limit(), verdict)) break;
+      if (!first || look < 0) return give_up();
+      look = meet_help(meet, look, nullptr, verdict);  // (-1: all are taken)
+      if (look < 0) continue;
+      if (tid == 0) owned[n_owned] = (uint16_t)look;
       __syncthreads();
-      const bool taken = same(verdict) >= 0;
-      __syncthreads();
-      if (taken) {
-        ++n_owned;
-      } else {  // all belong to blocks that run
-        if (!wait(stage, kSpinLimit)) return give_up();
-        break;
-      }
+      ++n_owned;
+      ++look;
     }
     if (!digits) {
 #pragma unroll
@@ -3961,9 +4042,10 @@ template <int source>
 __global__ void __launch_bounds__(64 * kTailWaves)
 k_tail(SelParams p, LeaderArgs la, int row_log2) {
   __shared__ TailShared sh;
+  meet_start();
   constexpr int T = 64 * kTailWaves;
   const int tid = threadIdx.x;
-  // (set before this launch, or by a block of it that has given up: then the others do too, if they wait for this one)
+  // (from before this launch, or set by a block of it that has given up: see meet_wait)
   if (*p.err != 0u) return;
   if (tid == 0) sh.verdict = -1;
   if (source == kTailHist && la.partials != nullptr) {  // (every block finds, and writes, the same)
@@ -4638,12 +4720,10 @@ constexpr int kSmallReps = 2;         // copies of a histogram, at most
 constexpr int kSmallMaxChunks = 256;  // chunks, at most
 constexpr int kSmallMaxUnits = 256;   // chunks x groups of workers, at most
 constexpr int kSmallLine = 32;        // words between counters
-constexpr int kSmallArrive = 8;       // words a wait counts its blocks on
-constexpr int kSmallHelpSpins = 256;  // looks at the other blocks' counts before looking for chunks that nobody has
 // SmallScratch::ctr, words: the step's number; chunks that other blocks took on, and blocks that came late, of this
 // step; two sets of three waits' counters
 constexpr int kCtrStep = 0, kCtrHelped = kSmallLine, kCtrLate = 2 * kSmallLine, kCtrArrive = 3 * kSmallLine,
-              kCtrSet = 3 * kSmallArrive * kSmallLine, kSmallCtr = kCtrArrive + 2 * kCtrSet;
+              kCtrSet = 3 * kMeetWait, kSmallCtr = kCtrArrive + 2 * kCtrSet;
 // What select_info reports as many candidates.
 __host__ __device__ constexpr uint32_t small_few(int64_t n) { return 10240u + 240u * (uint32_t)((n + kTile - 1) / kTile); }
 
@@ -4738,6 +4818,7 @@ k_small_step(SmallStep a) {
   const SmallScratch& ss = a.ss;
   const bool known = a.leader >= 0;
 
+  meet_start();
   // the first worker's loads are on their way while the chunk is taken
   v4f g8[2], r8[2];
   // the workers of a unit's group: a known leader alone in group 0 (as long as there are others), else shares of them all
@@ -4755,10 +4836,10 @@ k_small_step(SmallStep a) {
   };
   fetch_first(u0);
   const uint32_t step = ss.ctr[kCtrStep];
-  if (*a.err != 0u) return;  // (set before this launch: the same in every block)
+  if (*a.err != 0u) return;  // (from before this launch, or set by a block of it that has given up: see meet_wait)
+  const Meeting meet{ss.claim, ss.ctr + kCtrArrive + (step & 1u) * kCtrSet, step + 1u, nunits};
   if (tid == 0) {
-    const uint32_t was = __hip_atomic_exchange(&ss.claim[u0], step + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    verdict = was == step + 1u ? -1 : 0;
+    verdict = meet_take(meet, u0) ? 0 : -1;
     owned[0] = (uint16_t)u0;
   }
   for (int b = tid; b < kHistBins; b += T) pool[b] = 0u;
@@ -4784,37 +4865,7 @@ k_small_step(SmallStep a) {
   if (verdict < 0) return leave(1u);
   int n_owned = u0 < nchunks ? 1 : 0;  // chunks that this block takes to the outputs: of the first group
 
-  uint32_t* const arrive0 = ss.ctr + kCtrArrive + (step & 1u) * kCtrSet;
   uint32_t* const dig2 = ss.dig2 + (step & 1u) * kSmallReps * 128;
-  // what this block has stored through and added is there, for chunk c
-  auto arrive = [&](int b, int c) __attribute__((always_inline)) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0)
-      __hip_atomic_fetch_add(&arrive0[(b * kSmallArrive + c % kSmallArrive) * kSmallLine], 1u, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-  };
-  auto arrived = [&](int b) __attribute__((always_inline)) {  // a wave's: whether all chunks have
-    uint32_t v = 0u;
-    if (lane < kSmallArrive)
-      v = load_through(&arrive0[(b * kSmallArrive + lane) * kSmallLine]);
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    return __builtin_amdgcn_readfirstlane(v) == (uint32_t)(b == 0 ? nunits : nchunks);
-  };
-  // waits for all chunks, at most `spins` looks; false (in every thread) if they are not there
-  auto wait = [&](int b, int spins) __attribute__((always_inline)) {
-    if (wave == 0) {
-      bool ok = arrived(b);
-      for (int i = 0; !ok && i < spins; ++i) ok = arrived(b);
-      if (lane == 0) verdict = ok ? 1 : 0;
-    }
-    __syncthreads();
-    const bool ok = verdict != 0;
-    __syncthreads();  // (verdict is free)
-    return ok;
-  };
 
   uint32_t raw[8];  // the leader's elements of chunk `cur`
   int cur = -1;
@@ -4887,7 +4938,7 @@ k_small_step(SmallStep a) {
         small_flush<T>(pool, ss.hist + ((size_t)w * kSmallReps + (size_t)(c % a.reps)) * kHistBins);
       }
     }
-    arrive(0, unit);
+    meet_arrive(meet, 0, unit);
   };
   // the sums of the workers other than a known leader, up to the upto-th of them
   int others = known && groups == 1 ? 0 : rest;
@@ -4916,30 +4967,16 @@ k_small_step(SmallStep a) {
   begin(u0);
   if (n_owned == 0) return;
   more((rest + 2) / 3);
-  for (int look = u0 + 1; !wait(0, kSmallHelpSpins);) {
-    // a chunk that nobody has taken: its block does not run yet, and may not before this one is done
-    if (tid == 0) {
-      verdict = -1;
-      for (int i = 0; i < nunits && verdict < 0; ++i, ++look) {
-        const int c = look % nunits;
-        if (load_through(&ss.claim[c]) == step + 1u) continue;
-        // (counted before it is taken: a late block never finds fewer of them than have come late)
-        __hip_atomic_fetch_add(&ss.ctr[kCtrHelped], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (__hip_atomic_exchange(&ss.claim[c], step + 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != step + 1u)
-          verdict = c;
-        else
-          __hip_atomic_fetch_sub(&ss.ctr[kCtrHelped], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if (verdict >= 0 && verdict < nchunks) owned[n_owned] = (uint16_t)verdict;
-    }
-    __syncthreads();
-    const int c = verdict;
-    __syncthreads();
+  for (int look = u0 + 1, looks = kHelpLooks; !meet_wait(meet, 0, nunits, looks, verdict); looks = 0) {
+    const int c = meet_help(meet, look, &ss.ctr[kCtrHelped], verdict);
     if (c < 0) {  // all are taken, by blocks that run
-      if (wait(0, kSpinLimit)) break;
+      if (meet_wait(meet, 0, nunits, meet_limit(), verdict)) break;
       if (tid == 0) atomicOr(a.err, kErrWait);
       return;
     }
+    look = c + 1;
+    if (tid == 0 && c < nchunks) owned[n_owned] = (uint16_t)c;
+    __syncthreads();
     fetch_first(c);
     begin(c);
     if (known && groups == 1) {  // (its share of what the other chunks have had of the other workers)
@@ -4979,7 +5016,7 @@ k_small_step(SmallStep a) {
     }
     // the set of the next step (of the one before last: nobody is at it)
     uint32_t* const next = ss.ctr + kCtrArrive + ((step + 1u) & 1u) * kCtrSet;
-    if (tid < 3 * kSmallArrive) next[tid * kSmallLine] = 0u;
+    if (tid < 3 * kMeetWords) next[tid * kMeetLine] = 0u;
     for (int i = tid; i < kSmallReps * 128; i += T) ss.dig2[((step + 1u) & 1u) * kSmallReps * 128 + i] = 0u;
   }
   const float* lx = a.res.p[lead];
@@ -5066,10 +5103,10 @@ k_small_step(SmallStep a) {
       if (e < left && kk >= lo && kk <= hi) atomicAdd(&pool[(kk >> 7) & 0xfffu], 1u);
     }
     small_flush<T>(pool, ss.dig1 + (size_t)(c % a.reps) * kHistBins);
-    arrive(1, c);
+    meet_arrive(meet, 1, c);
   }
   more((2 * rest + 2) / 3);
-  if (!wait(1, kSpinLimit)) {
+  if (!meet_wait(meet, 1, nchunks, meet_limit(), verdict)) {
     if (tid == 0) atomicOr(a.err, kErrWait);
     return;
   }
@@ -5112,7 +5149,7 @@ k_small_step(SmallStep a) {
         store_through(&ss.above[c], sum);
       }
     }
-    arrive(2, c);
+    meet_arrive(meet, 2, c);
   }
   // every block has read the top digits' histograms; each clears its share
   {
@@ -5125,7 +5162,7 @@ k_small_step(SmallStep a) {
   uint32_t helped = 0u;  // (of the block that reports, thread 0; all chunks have been taken when it looks)
   if (reports && tid == 0) helped = load_through(&ss.ctr[kCtrHelped]);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the block gathers from its workers' sums)
-  if (!wait(2, kSpinLimit)) {
+  if (!meet_wait(meet, 2, nchunks, meet_limit(), verdict)) {
     if (tid == 0) atomicOr(a.err, kErrWait);
     return;
   }
