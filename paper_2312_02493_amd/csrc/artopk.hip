@@ -100,6 +100,7 @@ struct Plan {
   int64_t k_all = 0;        // entries kept of all segments together
   size_t hist_words = 0;    // words of h_all's memory used for copies of histograms
   bool batch = false;       // nseg whole vectors with one descriptor (SelParams::batch)
+  bool lists = false;       // select with the list kernels
   int64_t list_stride = 0;  // list entries per vector of a batch
   int32_t total_chunks = 0; // chunks of all segments together (entries of the device chunk map), 0: no map
 };
@@ -829,7 +830,7 @@ struct TailPlan {
 
 TailPlan tail_plan(const Plan& pl, int64_t n, int source) {
   TailPlan t;
-  if (pl.use_table || pl.nseg > kTailRanges) return t;
+  if (pl.use_table || pl.nseg > kTailRanges || pl.lists) return t;
   const int64_t waves = (int64_t)(kTailRanges / pl.nseg) * kTailWaves;
   const int64_t elems = ((n + waves - 1) / waves + kTailRow - 1) / kTailRow * kTailRow;
   // Survivors a wave is expected to have: the candidates below the threshold, or the guess' margin and the rest of its
@@ -1833,6 +1834,9 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   // pass A always works on whole-vector chunks; for a flat select they are the select's chunks too, unless k_tail
   // selects, which needs none: then the pass strides over the tiles
   const ChunkGeom geom = make_geom(0, n, kMaxChunks, gp.on);
+  // (sparse selections of few tiles: list kernels / k_tail, us, 1 M x 2, one in a thousand and in a hundred 50.8/51.8
+  // 53.8/53.7, 1.3 M 57.6/61.0 61.5/61.5, 1.8 M 61.2/63.8 66.2/64.8; without statistics 1.3 M 53.5/56.5 59.1/57.2)
+  flat.lists = device_leader && tile_blocks(n, (int)w) == 0 && 256 * k < n;
   const int tile_nblk = !segmented && !gp.on && !leader_first && mode != ARTOPK_VAR_TOPK && tail_plan(flat, n, kTailHist).ranges > 0
                             ? tile_blocks(n, (int)w) : 0;
   const bool by_tile = tile_nblk > 0;

@@ -362,6 +362,24 @@ def test_steps_whose_survivors_outgrow_a_wave(n, kmax, kind, monkeypatch):
         runner.ctx.status()
 
 
+# sparse selections of few tiles take the list kernels: either side of the line, results and route
+@pytest.mark.parametrize("n,w,k,one", [(1_300_000, 2, 5078, 0), (1_300_000, 2, 5079, 1), (1_300_000, 4, 100, 1), (2_096_128, 2, 100, 1),
+                                       (2_064_384, 2, 100, 0)])
+def test_steps_of_few_tiles(n, w, k, one):
+    from tests import gpu_util
+    from tests.gpu_util import GpuRunner, assert_step_matches
+
+    rng = np.random.default_rng(n + k)
+    g = [_values(rng, n, "normal") * np.float32(1 + r) for r in range(w)]
+    res = [np.zeros(n, np.float32) for _ in range(w)]
+    runner = GpuRunner(w, n, k)
+    want = orc.step(g, res, k, orc.MODE_VAR, step_no=1)
+    runner.load_g(g)
+    runner.load_res(res)
+    assert_step_matches(runner.step(k, orc.MODE_VAR, 1), want, orc.MODE_VAR)
+    assert gpu_util.FORCED or runner.ctx.select_info()["one_launch"] == one
+
+
 # large values that lie together may not cost the one-launch selection behind a pass much more than others do: a run of
 # them made a step a quarter longer with the list kernels (163 and 131 us), by 0.6 with a wave's elements in one piece, by
 # a quarter in many (0.4 leaves room for the clock)
