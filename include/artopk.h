@@ -164,7 +164,11 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 than eight workers, never under
  *                                 ARTOPK_VAR_TOPK, and with a leader known up
  *                                 front only if ARTOPK_OPT_LEADER_FIRST is 1;
- *                                 0 .. 2^21 (0 = never), default 1048576
+ *                                 0 .. 2^21 (0 = never), default 1048576.  Until
+ *                                 it is set, whatever the value, steps under the
+ *                                 variance rules on 524288 .. 786432 elements of
+ *                                 more than 24 workers run so only up to 22
+ *                                 million values of all of them
  */
 enum {
   ARTOPK_OPT_GUESS_MIN_N = 0,

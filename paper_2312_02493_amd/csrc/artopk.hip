@@ -54,6 +54,12 @@ constexpr int64_t kTwiceMaxN = (int64_t)5 << 23;  // (see plan_guess_read)
 // is, and its default stays).  Any number kept: a tenth, a third and all of 65537 x 2 63/21 71/21 90/23, of 1 M x 8 75/38
 // 90/39 118/40; variance rule, 65537 x 8 53/39 57/41 67/44, 1 M x 8 94/59 103/62 117/59.
 constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSmallMaxChunks * kTile;
+// Where the leader comes from statistics, a block takes its chunk of one worker after the other, and beyond this many values
+// of more than 24 workers the general launches are ahead on vectors whose chunks do not fill the chip, unless the option
+// was set.  One launch / eight, us, one in a hundred and in ten kept: 524288 x 48 144/148 167/145, x 64 185/182 215/180,
+// 700001 x 32 134/127 170/147, x 48 190/170 244/196, 786427 x 32 137/126 176/145, x 64 255/215 332/252; outside 700001 x 24
+// 107/108 133/128, 400009 x 64 159/175 190/168, and with all the chip 1 M x 32 128/142 182/168.
+constexpr int64_t kSmallMaxValues = 22000000, kSmallManyMinN = (int64_t)1 << 19, kSmallManyMaxN = (int64_t)3 << 18;
 
 struct Scratch {
   // zeroed before every select: one kSegWords block per segment, then the look-back flags
@@ -125,6 +131,7 @@ struct artopk_ctx {
   int stage_tiles = 1;  // guess route, one marking worker: the fused pass hands the marked elements on per tile
                         // (0 never, 1 for selections of one element in 256 or denser, 2 whenever a piece can hold a tile's share)
   int64_t small_max_n = kSmallMaxN;  // flat steps of up to about this many elements run in one launch
+  bool small_max_n_set = false;      // by artopk_set_option: then however many workers there are
   void* slab = nullptr;
   Scratch s;
   // how the last step or selection ran (artopk_select_info)
@@ -1151,9 +1158,10 @@ void launch_small(artopk_ctx* c, const SmallStep& a, int threads) {
 // x 64 195/127/84/63/62; 262143 x 8 45/36/32/33, x 16 69/52/44/45/52, x 64 232/152/122/118/128; 500009 x 8 45/42/49/57, x
 // 16 70/65/68/79; 786427 x 8 49/59, x 16 77/94.  With a leader known up front the others' sums are formed while the block
 // waits, unless they are many: 65537 x 8 22/-/23/22, x 16 27/-/28/26/26, x 64 64/-/60/45/47; 100003 x 64 87/-/63/55/56;
-// 200003 x 64 96/-/103/86/87; 262143 x 16 36/-/38/40/45.
+// 262143 x 16 36/-/38/40/45; 150001 x 64 one group and as many as there are units for 86/68, x 48 67/62, x 40 54/52, x
+// 24 37/37, 200003 x 33 57/61, x 48 83/81.
 int32_t small_groups(int32_t w, int64_t n, int32_t nchunks, bool known) {
-  if (known && (w <= 16 || n > ((int64_t)1 << 17))) return 1;
+  if (known && (w <= 16 || n > (w <= 40 ? (int64_t)128 << 10 : (int64_t)160 << 10))) return 1;
   return std::max<int32_t>(1, std::min<int32_t>(w, kSmallMaxUnits / nchunks));
 }
 
@@ -1453,6 +1461,7 @@ int artopk_set_option(artopk_ctx* ctx, int32_t key, int64_t value) {
     case ARTOPK_OPT_SHORT_MAX_N:
       if (value < 0 || value > kSmallMaxNLimit) return fail(ctx, ARTOPK_EINVAL, "ARTOPK_OPT_SHORT_MAX_N outside [0, 2^21]");
       ctx->small_max_n = value;
+      ctx->small_max_n_set = true;
       return ARTOPK_OK;
     default:
       return fail(ctx, ARTOPK_EINVAL, "unknown option %d", key);
@@ -1882,7 +1891,9 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   }
 
   const int64_t short_n = (device_leader && w < 8) ? ctx->small_max_n / 4 * 3 : ctx->small_max_n;
-  if (!segmented && !gp.on && n <= short_n && (leader_first || device_leader)) {
+  const bool too_many = device_leader && mode != ARTOPK_STAR_COUNTER && !ctx->small_max_n_set && w > 24 &&
+                        n >= kSmallManyMinN && n <= kSmallManyMaxN && (int64_t)w * n > kSmallMaxValues;
+  if (!segmented && !gp.on && n <= short_n && !too_many && (leader_first || device_leader)) {
     ctx->lvl1_a = 0;
     ctx->lvl1_b = 1;
     prof_begin(ctx);

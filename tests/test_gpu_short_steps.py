@@ -79,6 +79,30 @@ def test_short_steps_at_the_edges_of_chunks(n, w):
         res = want.residual
 
 
+# where the general launches are ahead of the one (many workers' values under a variance rule, until the option is set),
+# and either side of the line from which on a known leader's fellow workers are shared out among further blocks
+@pytest.mark.parametrize("n,w,mode,setting,short", [(524_288, 42, orc.MODE_VAR, None, 0), (524_288, 41, orc.MODE_VAR, None, 1),
+                                                    (524_288, 42, orc.MODE_VAR, 1 << 20, 1), (524_287, 48, orc.MODE_VAR, None, 1),
+                                                    (786_432, 28, orc.MODE_VAR_G, None, 0), (786_433, 28, orc.MODE_VAR, None, 1),
+                                                    (163_840, 41, orc.MODE_STAR, None, 1), (163_841, 41, orc.MODE_STAR, None, 1),
+                                                    (163_840, 40, orc.MODE_STAR, None, 1)])
+def test_short_steps_of_many_workers(n, w, mode, setting, short):
+    import paper_2312_02493_amd as lib
+
+    rng = np.random.default_rng(n + w)
+    k = n // 100
+    runner = GpuRunner(w, n, k)
+    if setting is not None:
+        runner.ctx.set_option(lib.ARTOPK_OPT_SHORT_MAX_N, setting)
+    g = [_vector(rng, n, "normal", r) for r in range(w)]
+    res = [np.zeros(n, np.float32) for _ in range(w)]
+    want = orc.step(g, res, k, mode, step_no=1)
+    runner.load_g(g)
+    runner.load_res(res)
+    assert_step_matches(runner.step(k, mode, 1, want_vals=False), want, mode)
+    assert gpu_util.FORCED or runner.ctx.select_info()["short"] == short
+
+
 # the same step on both launch sequences, in turn on one context (the short one must leave its scratch as it found it)
 @pytest.mark.parametrize("n,w,k", [(70_001, 9, 700), (1 << 20, 3, 16384), ((1 << 20) - 3, 17, 1)])
 @pytest.mark.parametrize("g", ["f32", "bf16", "f16"])
