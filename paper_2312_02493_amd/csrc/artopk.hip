@@ -1936,7 +1936,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
         launch_pass_seg<kGF32>(ctx, *pl, rt, n, g[L], residual[L]);
       HIP_TRY(ctx, hipGetLastError());
     } else {
-      launch_pass_a(ctx, 0, 1, dim3(pass_nblk, 1), g1t, r1t, n, geom, 0, by_tile);
+      launch_pass_a(ctx, 0, 1, dim3(geom.nchunks, 1), g1t, r1t, n, geom, 0);
     }
     prof_mark(ctx, 1);
     // The leader's residual is zeroed inside the selection: its kernels have the kept values in
