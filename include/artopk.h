@@ -104,9 +104,9 @@ enum {
  * 8 (max_k + max(max_n / 8, 2^22)) bytes of survivor list plus 8 max_w max_k bytes plus
  * max_n / 8 bytes per worker of survivor bit masks plus 1.5 max_n bytes in which a
  * leader's fused pass stages list entries tile by tile plus, for selections on several vectors
- * at a time, max_n / 341 bytes of scan flags and 64 KiB for each of up to 16 workers plus, for steps on
- * short vectors, 128 KiB per worker and 4.5 bytes for each of up to 2^21 elements, plus 1.25 MiB
- * (artopk_scratch_bytes gives the exact size).  The library reads no environment
+ * at a time, max_n / 341 bytes of scan flags and 64 KiB for each of up to 16 workers plus, set aside for steps on
+ * short vectors (which use 32 KiB per worker and 170 KiB of it), 128 KiB per worker and 4.5 bytes for each of up to
+ * 2^21 elements, plus 1.25 MiB (artopk_scratch_bytes gives the exact size).  The library reads no environment
  * variable and keeps no state outside its contexts (artopk_variance_static's fixed
  * scratch excepted, see there).
  */

@@ -50,8 +50,9 @@ constexpr int64_t kTwiceMaxN = (int64_t)5 << 23;  // (see plan_guess_read)
 // or eight launches / one, one in a hundred kept, 786427, 1 M, 1.3 M and 1.8 M elements: leader known, 2 workers 59/25
 // 59/28 60/28 63/31, 4 workers 61/24 62/26 65/29 69/33, 8 workers 64/29 67/33 76/40 84/47, 16 workers 80/43 87/49 98/60
 // 117/72; variance rule, 2 workers 52/32 53/36 60/39 -, 4 workers 62/38 65/41 73/48 -, 8 workers 77/50 87/53 97/68
-// 117/75, 16 workers 114/77 133/79 152/105 189/113.  All of them lie below the crossing (an option says where the line
-// is, and its default stays).  Any number kept: a tenth, a third and all of 65537 x 2 63/21 71/21 90/23, of 1 M x 8 75/38
+// 117/75, 16 workers 114/77 133/79 152/105 189/113.  So both lines lie below the crossing, which is beyond 1.8 M for all of
+// these: they are those of the option's documented default, where the short vectors' launches used to cross, and a caller
+// who sets the option has the launch up to 2^21.  Any number kept: a tenth, a third and all of 65537 x 2 63/21 71/21 90/23, of 1 M x 8 75/38
 // 90/39 118/40; variance rule, 65537 x 8 53/39 57/41 67/44, 1 M x 8 94/59 103/62 117/59.
 constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSmallMaxChunks * kTile;
 // Where the leader comes from statistics, a block takes its chunk of one worker after the other, and beyond this many values
@@ -1771,9 +1772,11 @@ int artopk_apply_update(artopk_ctx* ctx, float* weights, int64_t n, const int32_
 namespace {
 
 // Blocks per worker of a pass A that strides over the tiles of n elements, or 0 where it had better take chunks: a quarter
-// of a tile each, they still fill the chip (1.2 M elements of one worker, 37 tiles: 61.6 us a step with chunks, 63.5 with
-// tiles; of four workers, 148 tiles, 71.8 and 59.2).  512 / 1024 / 2048 blocks
-// over all workers: 11.7 M x 8 292.7/288.4/286.8 us a step, 5 M x 16 258/260/249.
+// of a tile each, they still fill the chip (variance rule, us a step, one in a hundred and in ten kept, chunks / tiles,
+// normal values and sorted ones, whose digits all are a tile's: 37 tiles of all workers, 1.2 M x 1, 51/52 57/64, 68/88
+// 68/88; 68, 1.1 M x 2, 59/55 66/65, 81/89 80/89; 128, 1 M x 4, 64/57 71/67, 83/90 83/90; 160, 1.3 M x 4, 72/59 81/71, 96/91
+// 95/90; 232, 1.9 M x 4, 84/65 95/79, 111/94 109/93).  512 / 1024 / 2048 blocks over all workers: 11.7 M x 8
+// 292.7/288.4/286.8 us a step, 5 M x 16 258/260/249.
 int tile_blocks(int64_t n, int workers) {
   const int64_t ntiles = (n + kPassTile - 1) / kPassTile;
   if (ntiles * workers < 128) return 0;

@@ -114,7 +114,7 @@ struct SelState {
   uint32_t use_mask;       // the list is written from the survivor bit mask of the fused pass
   uint32_t need_full;      // the guessed bound did not work out: the top-digit histogram of every key is needed
   uint32_t list_lo;        // with use_mask: the list holds every key >= list_lo (<= lo)
-  uint32_t many;           // a short vector's threshold shares its top digit with many others (small_few)
+  uint32_t many;           // a short vector's threshold shares its top digit with many others (small_few); for select_info
   uint32_t pad[4];
 };
 
@@ -4724,7 +4724,7 @@ constexpr int kSmallLine = 32;        // words between counters
 // step; two sets of three waits' counters
 constexpr int kCtrStep = 0, kCtrHelped = kSmallLine, kCtrLate = 2 * kSmallLine, kCtrArrive = 3 * kSmallLine,
               kCtrSet = 3 * kMeetWait, kSmallCtr = kCtrArrive + 2 * kCtrSet;
-// What select_info reports as many candidates.
+// What select_info reports as many candidates (no route depends on it).
 __host__ __device__ constexpr uint32_t small_few(int64_t n) { return 10240u + 240u * (uint32_t)((n + kTile - 1) / kTile); }
 
 struct SmallScratch {

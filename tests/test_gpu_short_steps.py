@@ -19,7 +19,7 @@ def _vector(rng, n, kind, r):
     elif kind == "zeros":
         x[:] = 0.0
         x[r::max(1, n // 7)] = 1.0 + r
-    elif kind == "one_bin":  # one top digit, many second and third digits: the last block walks a list of n entries
+    elif kind == "one_bin":  # one top digit, many second and third digits
         x = (1.0 + rng.random(n) * 0.01).astype(np.float32)
         x[0] += 0.001 * r
     elif kind == "special":
@@ -28,7 +28,7 @@ def _vector(rng, n, kind, r):
     return x
 
 
-# one element, less than a group, the edges of the last launch's tile and of a chunk, the longest vector of the route
+# one element, less than a group, the edges of a wave's share and of a chunk, the longest vector of the route
 # (of the variance rules with fewer than eight workers: 3 << 18)
 @pytest.mark.parametrize("n", [1, 3, 1023, 1024, 1025, 8191, 8193, 65537, 300_002, 3 << 18, (3 << 18) + 1, 1 << 20])
 @pytest.mark.parametrize("kind", ["normal", "ties", "equal", "zeros", "one_bin", "special"])
@@ -57,9 +57,10 @@ def test_short_steps_match_the_oracle(n, kind):
             assert gpu_util.FORCED or runner.ctx.select_info()["short"] == (n <= (3 << 18 if on_device else 1 << 20))
 
 
-# chunks of 2048, 4096 and 8192 elements (up to 2^18, 2^20 and 2^21): one, whole ones, an element more or less, the
-# last one short; one worker, more than are loaded at a time, and the most
-@pytest.mark.parametrize("n", [2047, 4097, 65536, (1 << 18) - 3, 1 << 18, (1 << 18) + 1, (1 << 20) + 8191])
+# chunks of 4096 elements (up to 2^20) and 8192 (up to 2^21): one, whole ones, an element more or less, the last one
+# short; one worker, more than are loaded at a time, and the most
+@pytest.mark.parametrize("n", [2047, 4095, 4096, 4097, 65536, (1 << 18) - 3, 1 << 18, (1 << 18) + 1, (1 << 20) - 1, (1 << 20) + 1,
+                               (1 << 20) + 8191, (1 << 20) + 8192, (1 << 20) + 8193])
 @pytest.mark.parametrize("w", [1, 6, 64])
 def test_short_steps_at_the_edges_of_chunks(n, w):
     import paper_2312_02493_amd as lib
@@ -149,7 +150,7 @@ def _few(n):
 
 
 def _narrow(rng, n, kind, r):
-    """Vectors whose threshold's top digit many values share (up to `few` of them are left to one block of the selection)."""
+    """Vectors whose threshold's top digit many values share (select_info tells whether more than `few`)."""
     few = _few(n)
     x = (rng.standard_normal(n) * 0.01).astype(np.float32)
     if kind == "band":  # all of them, most second and last digits
@@ -160,13 +161,13 @@ def _narrow(rng, n, kind, r):
         return (np.uint32(0x3f800000) + rng.integers(0, 128, n).astype(np.uint32)).view(np.float32)
     if kind == "equal":
         return np.full(n, np.float32(0.75))
-    m = min(n, few + {"few": 0, "few1": 1}[kind])  # exactly as many as one block takes, and one more
+    m = min(n, few + {"few": 0, "few1": 1}[kind])  # exactly as many as select_info takes for few, and one more
     x[rng.permutation(n)[:m]] = (1.0 + rng.random(m) * 0.01).astype(np.float32)
     return x
 
 
-# a step on narrow values before and after an ordinary one on the same context: the selection's blocks share the
-# counting and have to leave the scratch as they found it; 2^21 is the option's largest value
+# a step on narrow values before and after an ordinary one on the same context: the blocks have to leave
+# the scratch as they found it; 2^21 is the option's largest value
 @pytest.mark.parametrize("n", [16385, 65537, 300_002, (1 << 20) - 3, (1 << 20) + 1, 1 << 21])
 @pytest.mark.parametrize("kind", ["band", "two", "near", "equal", "few", "few1"])
 def test_short_steps_on_narrow_values(n, kind):
