@@ -3592,7 +3592,7 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
     }
     const uint32_t span = (uint32_t)p.tiles.span, nspans = spans ? (n + span - 1u) / span : 1u;
     uint32_t at = spans ? same(chunk_at[ch]) : 0u;  // entries in front of span s0
-    for (uint32_t s0 = spans ? (uint32_t)(ch * same((int)sv.d.geom.chunk_elems)) / span : 0u; s0 < nspans && at < e1; s0 += 64u) {
+    for (uint32_t s0 = spans ? (uint32_t)ch * same((uint32_t)sv.d.geom.chunk_elems) / span : 0u; s0 < nspans && at < e1; s0 += 64u) {
       uint32_t cnt = 0u, incl = 0u;
       uint64_t read = 1ull;  // what has to be taken from the vector: the wave's rows, or spans with more than their pieces hold
       if (spans) {
