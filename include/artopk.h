@@ -103,7 +103,8 @@ enum {
  * 64 KiB per segment plus
  * 8 (max_k + max(max_n / 8, 2^22)) bytes of survivor list plus 8 max_w max_k bytes plus
  * max_n / 8 bytes per worker of survivor bit masks plus 1.5 max_n bytes in which a
- * leader's fused pass stages list entries tile by tile plus, for selections on several vectors
+ * leader's fused pass stages list entries tile by tile plus, with more than one segment, 24 bytes
+ * for every 16384 elements and for two more such tiles of every segment plus, for selections on several vectors
  * at a time, max_n / 341 bytes of scan flags and 64 KiB for each of up to 16 workers plus, set aside for steps on
  * short vectors (which use 32 KiB per worker and 170 KiB of it), 128 KiB per worker and 4.5 bytes for each of up to
  * 2^21 elements, plus 1.25 MiB (artopk_scratch_bytes gives the exact size).  The library reads no environment
@@ -129,10 +130,15 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 walks the tiles in the same striding order,
  *                                 unless its leader is known up front);
  *                                 1 .. 2^31 (2^31 = never), default 33554432.
- *                                 Selections on vectors as they are take their
+ *                                 Until this is set, to whatever value,
+ *                                 selections on vectors as they are take their
  *                                 guess from 25165824 elements on (all vectors
- *                                 of the call together) until this is set, to
- *                                 whatever value; then from that on, each vector
+ *                                 of the call together), flat steps that hand
+ *                                 marks on by tiles (ARTOPK_OPT_STAGE_TILES)
+ *                                 from 12582912 and segmented steps and
+ *                                 selections, whose segments are then guessed
+ *                                 for one by one, from 8388608; then all of them
+ *                                 from that on
  *   ARTOPK_OPT_UPDATE_TILES_MIN_N shortest vector whose dense update is
  *                                 streamed tile by tile with the values stored
  *                                 behind the zeros, shorter ones are built
@@ -149,14 +155,14 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 the short vectors' launch always uses)
  *   ARTOPK_OPT_STAGE_TILES        on the guess route with a leader known up
  *                                 front, the leader's fused pass can hand the
- *                                 elements that reach the guessed bound on as
- *                                 list entries, tile by tile, instead of leaving
- *                                 only the bit mask (from which the list is
- *                                 built by fetching the marked values one by
- *                                 one).  1 (default): for selections of one
- *                                 element in 256 or denser (beyond one in 32
- *                                 the alternative is the histogram route);
- *                                 2: for every selection; 0: never
+ *                                 elements that reach the guessed bound on tile
+ *                                 by tile, instead of leaving only the bit mask
+ *                                 (from which a list is built by fetching the
+ *                                 marked values one by one).  1 (default):
+ *                                 except for selections sparser than one element
+ *                                 in 700 of 2^28 or more; 2: for every selection
+ *                                 up to about one in seven; 0: never.  (Flat
+ *                                 selections only: segments have no mask)
  *   ARTOPK_OPT_SHORT_MAX_N        longest flat vector whose step runs in one
  *                                 launch (two under ARTOPK_STAR_COUNTER); three
  *                                 quarters of it where the leader is found on the device (the
@@ -387,9 +393,9 @@ int artopk_get_profile(artopk_ctx* ctx, float* ms_out, int32_t count);
  * the library's equivalent routes was taken, for tests and tuning).  Synchronises
  * the stream and writes up to `count` host int32 values:
  *   [0] 1 if a threshold guess was sampled before the (fused or read-only) pass
- *   [1] 1 if the survivor list was then written from what that pass marked
+ *   [1] 1 if the selection was then made from what that pass marked
  *       (0 with [0] = 1: the guess did not hold and the full route was taken)
- *   [2] entries in the survivor list
+ *   [2] entries in the survivor list, or elements marked where these are handed on by tiles
  *   [3] 1 if the list was written after the first radix digit (or from the
  *       mask), 0 if that did not fit and the deeper array passes wrote it
  *   [4] workers the dominant streaming kernel covered (W, or W-1 when the

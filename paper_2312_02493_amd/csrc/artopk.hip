@@ -62,6 +62,14 @@ constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSma
 // 107/108 133/128, 400009 x 64 159/175 190/168, and with all the chip 1 M x 32 128/142 182/168.
 constexpr int64_t kSmallMaxValues = 22000000, kSmallManyMinN = (int64_t)1 << 19, kSmallManyMaxN = (int64_t)3 << 18;
 
+// Selections by tiles from this many elements on: flat ones of a leader known up front, and segmented ones.  Launches of the
+// histogram route / tiles, us: flat, one in a hundred and in ten kept, 3 M x 2 73/81 86/94, 6 M x 2 93/93 118/110, x 8
+// 171/172 198/193, 12 M x 2 125/120 153/144, x 8 273/268 312/294, 25.6 M x 2 218/193 291/227, bfloat16 gradients 12 M x 8
+// 236/237 280/268, 25.6 M x 8 449/427 550/478.  Segmented, one in a hundred, leader known, 4 M x 2 in 54 segments 93/114, in
+// 8 99/92, 8 M x 2 in 54 131/129, in 8 154/105, in 160 149/143, 25.6 M x 8 in 54 533/503; variance rule, 4 M x 2 in 54
+// 107/118, in 8 115/96, 8 M x 2 in 54 163/140, x 8 341/256, 25.6 M x 8 644/620, one in ten 964/937.
+constexpr int64_t kTilesMinN = (int64_t)3 << 22, kSegTilesMinN = (int64_t)1 << 23;
+
 struct Scratch {
   // zeroed before every select: one kSegWords block per segment, then the look-back flags
   uint32_t* h_all = nullptr;      // [max_w][kSlotWords] whole-vector histograms of the fused pass, guess sample
@@ -83,14 +91,14 @@ struct Scratch {
   float* vals = nullptr;          // [max_w][max_k] gathered rows when the caller passes no vals_out
   int32_t* idx_rows = nullptr;    // [max_w][max_k] every worker's own Top-k (literal Alg. 1 leader rule)
   int32_t* tile_start = nullptr;  // [max_n / kPassTile + 2] kept indices below every tile of the streaming pass
-  uint2* tilebuf = nullptr;       // list entries the fused pass stages per tile (guess route, one marking worker)
+  uint2* tilebuf = nullptr;       // pieces of marked elements, of tiles or of the spans of vectors that are only read
   int64_t tilebuf_entries = 0;
-  uint32_t* tile_cnt = nullptr;   // [max_n / kPassTile + 1] entries staged per tile
-  uint32_t* sample_keys = nullptr;  // [16384 kGuessRun] keys of one vector's guess sample
   SmallScratch small{};           // short vectors' steps
   size_t small_words = 0;         // of it, zero whenever no step is running
   SegDesc* table_dev = nullptr;   // [max_seg] segment descriptors
   uint32_t* chunk_map = nullptr;  // [kMaxChunks + max_seg] (segment << 16) | chunk, one entry per chunk of the layout
+  uint4* tile_map = nullptr;      // [map_tiles] tiles of a segmented layout, then their groups (TileArgs::map, groups)
+  int64_t map_tiles = 0;
   uint32_t cap = 0;               // list capacity of a flat (one-segment) select
 };
 
@@ -110,6 +118,9 @@ struct Plan {
   bool lists = false;       // select with the list kernels
   int64_t list_stride = 0;  // list entries per vector of a batch
   int32_t total_chunks = 0; // chunks of all segments together (entries of the device chunk map), 0: no map
+  int32_t tiles = 0, tile_groups = 0;  // tiles of all segments together, 0: not selected on by tiles
+  int32_t more_bins = 0;               // further copies of segments' bins
+  bool tiles_aligned = true;           // they are the streaming passes' tiles
 };
 
 }  // namespace
@@ -129,8 +140,8 @@ struct artopk_ctx {
   bool guess_min_n_set = false;  // by artopk_set_option: then it holds for vectors that are only read, too
   // vectors of at least this many elements get their dense update from k_update_tiles
   int64_t update_tiles_min_n = (int64_t)1 << 22;
-  int stage_tiles = 1;  // guess route, one marking worker: the fused pass hands the marked elements on per tile
-                        // (0 never, 1 for selections of one element in 256 or denser, 2 whenever a piece can hold a tile's share)
+  int stage_tiles = 1;  // guess route, one marking worker: the marked elements are handed on by tiles (0 never, 1 where that
+                        // is the better way, 2 whenever a piece can hold a tile's share)
   int64_t small_max_n = kSmallMaxN;  // flat steps of up to about this many elements run in one launch
   bool small_max_n_set = false;      // by artopk_set_option: then however many workers there are
   void* slab = nullptr;
@@ -382,6 +393,10 @@ Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool
   d.cap = c->s.cap < (uint64_t)n ? c->s.cap : (uint32_t)n;
   d.vec = vec;
   d.hreps = own_hist && d.geom.nchunks > kManyChunks ? kHistReps : 1;
+  d.tile_begin = 0;
+  d.ntiles = (int32_t)((n + kMarkTile - 1) / kMarkTile);
+  d.group_begin = d.bins_begin = 0;
+  d.bins_more = 7;
   pl.k_all = k;
   pl.hist_words = d.hreps > 1 ? (size_t)d.hreps * kHistBins : 0;
   pl.desc.push_back(d);
@@ -389,6 +404,18 @@ Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool
   pl.max_tiles = pl.total_tiles = tiles_of_range(0, n);
   pl.max_cap = d.cap;
   return pl;
+}
+
+// Words of TileArgs' tables for every tile, and where the further copies of segments' bins lie behind them.
+constexpr int kTileWords = 6 + (2 + kTileSlots) * kTileWaves;
+uint32_t* tile_more_bins(const artopk_ctx* c, int32_t tiles) { return c->s.S + (kTileWords * (size_t)tiles + 63) / 64 * 64; }
+
+// Further copies of the bins of a segment of `ntiles` tiles where the layout has `tiles` and `have` copies already: one for
+// sixteen tiles, seven at most, as long as S's memory has room for them behind the tables.
+int32_t more_bins(const artopk_ctx* c, int32_t ntiles, int32_t tiles, int32_t have) {
+  const int32_t want = std::min(ntiles / 16, 7);
+  const int64_t words = ((int64_t)c->max_w * kMaxChunks + c->max_seg) * kHistBins;
+  return kTileWords * (int64_t)tiles + 64 + (int64_t)(have + want) * kHistBins <= words ? want : 0;
 }
 
 // Descriptors for nseg > 1 segments; uploads them to the device table unless the
@@ -425,6 +452,10 @@ int segmented_plan(artopk_ctx* c, int64_t n, int32_t nseg, const int64_t* seg_of
       d.cap = (uint32_t)seg_list_cap(ns, seg_k[sgi]);
       d.vec = -1;
       d.hreps = 1;
+      d.tile_begin = pl.tiles;
+      d.ntiles = (int32_t)((d.e_hi - d.e_lo / 32 * 32 + kMarkTile - 1) / kMarkTile);
+      pl.tiles += d.ntiles;
+      if (d.e_lo % kPassTile != 0) pl.tiles_aligned = false;
       koff += seg_k[sgi];
       list_base += ((int64_t)d.cap + 3) / 4 * 4;
       const int64_t tiles = tiles_of_range(d.e_lo, d.e_hi);
@@ -439,6 +470,13 @@ int segmented_plan(artopk_ctx* c, int64_t n, int32_t nseg, const int64_t* seg_of
     pl.k_all = koff;
     if (list_base > c->s.list_entries || flag_base > c->s.max_tiles || chunk_begin > kMaxChunks + c->max_seg)
       return fail(c, ARTOPK_EINVAL, "segment layout exceeds the scratch sized at artopk_create");
+    for (SegDesc& d : pl.desc) {
+      d.group_begin = pl.tile_groups;
+      pl.tile_groups += (d.ntiles + kTileWaves - 1) / kTileWaves;
+      d.bins_begin = pl.more_bins;
+      d.bins_more = more_bins(c, d.ntiles, pl.tiles, pl.more_bins);
+      pl.more_bins += d.bins_more;
+    }
     HIP_TRY(c, hipMemcpyAsync(c->s.table_dev, pl.desc.data(), sizeof(SegDesc) * nseg, hipMemcpyHostToDevice,
                               c->stream));
     // one block per chunk of the layout for the per-chunk kernels (a (chunks, segments) grid of a layout
@@ -450,6 +488,13 @@ int segmented_plan(artopk_ctx* c, int64_t n, int32_t nseg, const int64_t* seg_of
     HIP_TRY(c, hipMemcpyAsync(c->s.chunk_map, cmap.data(), sizeof(uint32_t) * cmap.size(), hipMemcpyHostToDevice,
                               c->stream));
     pl.total_chunks = chunk_begin;
+    if ((int64_t)nseg * kPassTile <= n && pl.tiles <= c->s.map_tiles) {
+      hipLaunchKernelGGL(k_tile_map, dim3((unsigned)nseg), dim3(256), 0, c->stream, c->s.table_dev,
+                         c->s.tile_map, reinterpret_cast<uint2*>(c->s.tile_map + c->s.map_tiles));
+      HIP_TRY(c, hipGetLastError());
+    } else {
+      pl.tiles = 0;
+    }
     c->cached_plan = pl;
     c->cached_n = n;
     c->cached_off.assign(seg_off, seg_off + nseg + 1);
@@ -501,10 +546,12 @@ SelParams make_params(const artopk_ctx* c, const Plan& pl, const PtrTable& tab, 
 // whole-vector histograms of the first hist_slots slots a fused pass is about to fill.
 // leader >= 0 also records a host-known leader (and copies it to leader_out).
 int enqueue_clear(artopk_ctx* c, const Plan& pl, int hist_slots, int32_t leader = -1,
-                  int32_t* leader_out = nullptr) {
+                  int32_t* leader_out = nullptr, bool tiles = false) {
   Scratch& s = c->s;
   const size_t words1 = (size_t)pl.nseg * kSegWords;
-  const size_t words2 = (size_t)pl.total_tiles * kNumLookback * 2;
+  // (the selection by tiles has no look-back flags, but copies of bins)
+  const size_t words2 = tiles ? (size_t)pl.more_bins * kHistBins : (size_t)pl.total_tiles * kNumLookback * 2;
+  uint32_t* const range2 = tiles ? tile_more_bins(c, pl.tiles) : reinterpret_cast<uint32_t*>(s.flags);
   // (a plan with histograms of its own uses h_all's memory for their copies; no pass fills slots then)
   const size_t words3 = hist_slots > 0 ? (size_t)hist_slots * kSlotWords : pl.hist_words;
   const size_t total = words1 + words2 + words3;
@@ -512,7 +559,7 @@ int enqueue_clear(artopk_ctx* c, const Plan& pl, int hist_slots, int32_t leader 
   if (blocks < 1) blocks = 1;
   if (blocks > c->num_cu * 4) blocks = c->num_cu * 4;
   hipLaunchKernelGGL(k_fill_zero, dim3(blocks), dim3(256), 0, c->stream, s.zero_base, words1,
-                     reinterpret_cast<uint32_t*>(s.flags), words2, s.h_all, words3, leader,
+                     range2, words2, s.h_all, words3, leader,
                      leader >= 0 ? s.leader_dev : nullptr, leader_out);
   HIP_TRY(c, hipGetLastError());
   return ARTOPK_OK;
@@ -570,45 +617,34 @@ int rest_blocks(int64_t n) {
   return (int)(ntiles < 512 ? ntiles : 512);
 }
 
-// What the fused pass stages per tile for one marking worker (slot 0), or nothing.
-TileBuf tile_buf(const artopk_ctx* c, int32_t tile_cap) {
-  if (tile_cap <= 0) return TileBuf{nullptr, nullptr, 0, 0, 0};
-  return TileBuf{c->s.tilebuf, c->s.tile_cnt, 0, 0, tile_cap};
-}
-
 // The fused pass of the guess route over the first nw workers of the tables (worker y in slot y).
-// tile_cap > 0 (one worker, no statistics): the pass also stages the marked elements per tile.
-template <int STATS, int GT, bool STAGE>
-void launch_pass_mark_g(artopk_ctx* c, int nw, const PtrTable& g, const PtrTable& r, int64_t n, int64_t chunk_elems,
-                        int32_t tile_cap) {
+template <int STATS, int GT>
+void launch_pass_mark_g(artopk_ctx* c, int nw, const PtrTable& g, const PtrTable& r, int64_t n, int64_t chunk_elems) {
   Scratch& s = c->s;
   const dim3 grid(pass_blocks(n), nw);
-  const TileBuf tb = tile_buf(c, STAGE ? tile_cap : 0);
   if (c->pass_a_nt)
-    hipLaunchKernelGGL((k_pass_mark<STATS, true, GT, kPassAThreads, kPassAU, STAGE>), grid, dim3(kPassAThreads), 0,
-                       c->stream, g, r, n, chunk_elems, s.h_all, s.mask, s.mask_stride, s.partials, tb);
+    hipLaunchKernelGGL((k_pass_mark<STATS, true, GT, kPassAThreads, kPassAU>), grid, dim3(kPassAThreads), 0, c->stream, g, r,
+                       n, chunk_elems, s.h_all, s.mask, s.mask_stride, s.partials);
   else
-    hipLaunchKernelGGL((k_pass_mark<STATS, false, GT, kPassAThreads, kPassAU, STAGE>), grid, dim3(kPassAThreads), 0,
-                       c->stream, g, r, n, chunk_elems, s.h_all, s.mask, s.mask_stride, s.partials, tb);
+    hipLaunchKernelGGL((k_pass_mark<STATS, false, GT, kPassAThreads, kPassAU>), grid, dim3(kPassAThreads), 0, c->stream, g, r,
+                       n, chunk_elems, s.h_all, s.mask, s.mask_stride, s.partials);
 }
 
-template <int STATS, bool STAGE>
-void launch_pass_mark_t(artopk_ctx* c, int nw, const PtrTable& g, const PtrTable& r, int64_t n, int64_t chunk_elems,
-                        int32_t tile_cap) {
+template <int STATS>
+void launch_pass_mark_t(artopk_ctx* c, int nw, const PtrTable& g, const PtrTable& r, int64_t n, int64_t chunk_elems) {
   if (c->g_type == ARTOPK_G_BF16)
-    launch_pass_mark_g<STATS, kGBF16, STAGE>(c, nw, g, r, n, chunk_elems, tile_cap);
+    launch_pass_mark_g<STATS, kGBF16>(c, nw, g, r, n, chunk_elems);
   else if (c->g_type == ARTOPK_G_F16)
-    launch_pass_mark_g<STATS, kGF16, STAGE>(c, nw, g, r, n, chunk_elems, tile_cap);
+    launch_pass_mark_g<STATS, kGF16>(c, nw, g, r, n, chunk_elems);
   else
-    launch_pass_mark_g<STATS, kGF32, STAGE>(c, nw, g, r, n, chunk_elems, tile_cap);
+    launch_pass_mark_g<STATS, kGF32>(c, nw, g, r, n, chunk_elems);
 }
 
 void launch_pass_mark(artopk_ctx* c, int stats, int nw, const PtrTable& g, const PtrTable& r, int64_t n,
-                      int64_t chunk_elems, int32_t tile_cap = 0) {
-  if (stats == 0 && tile_cap > 0 && nw == 1) return launch_pass_mark_t<0, true>(c, nw, g, r, n, chunk_elems, tile_cap);
-  if (stats == 0) return launch_pass_mark_t<0, false>(c, nw, g, r, n, chunk_elems, 0);
-  if (stats == 1) return launch_pass_mark_t<1, false>(c, nw, g, r, n, chunk_elems, 0);
-  return launch_pass_mark_t<2, false>(c, nw, g, r, n, chunk_elems, 0);
+                      int64_t chunk_elems) {
+  if (stats == 0) return launch_pass_mark_t<0>(c, nw, g, r, n, chunk_elems);
+  if (stats == 1) return launch_pass_mark_t<1>(c, nw, g, r, n, chunk_elems);
+  return launch_pass_mark_t<2>(c, nw, g, r, n, chunk_elems);
 }
 
 // The striding pass without a bound: error-feedback add and statistics of all w workers (per-block
@@ -617,13 +653,12 @@ template <int STATS, int GT>
 void launch_pass_plain_g(artopk_ctx* c, int nw, const PtrTable& g, const PtrTable& r, int64_t n) {
   Scratch& s = c->s;
   const dim3 grid(pass_blocks(n), nw);
-  const TileBuf tb = tile_buf(c, 0);
   if (c->pass_a_nt)
-    hipLaunchKernelGGL((k_pass_mark<STATS, true, GT, kPassAThreads, kPassAU, false, true>), grid, dim3(kPassAThreads), 0,
-                       c->stream, g, r, n, (int64_t)kPassTile, s.h_all, s.mask, s.mask_stride, s.partials, tb);
+    hipLaunchKernelGGL((k_pass_mark<STATS, true, GT, kPassAThreads, kPassAU, true>), grid, dim3(kPassAThreads), 0,
+                       c->stream, g, r, n, (int64_t)kPassTile, s.h_all, s.mask, s.mask_stride, s.partials);
   else
-    hipLaunchKernelGGL((k_pass_mark<STATS, false, GT, kPassAThreads, kPassAU, false, true>), grid, dim3(kPassAThreads), 0,
-                       c->stream, g, r, n, (int64_t)kPassTile, s.h_all, s.mask, s.mask_stride, s.partials, tb);
+    hipLaunchKernelGGL((k_pass_mark<STATS, false, GT, kPassAThreads, kPassAU, true>), grid, dim3(kPassAThreads), 0,
+                       c->stream, g, r, n, (int64_t)kPassTile, s.h_all, s.mask, s.mask_stride, s.partials);
 }
 
 template <int STATS>
@@ -686,34 +721,29 @@ struct GuessPlan {
   int runs = 0;
   int64_t stride = 0;
   uint32_t m_hi = 0;
-  int32_t span = 0;      // elements per piece of the read-only marking pass (tile_cap entries each)
+  uint32_t m_mid = 0, m_lo = 0;  // with tiles: the sample's share of k, and as far on the other side
+  int32_t span = 0;      // elements per piece of the read-only marking pass
   uint32_t m_max = 0xffffffffu;  // more sample keys at or above a bound than this: no bound
-  int32_t tile_cap = 0;  // > 0: one marking worker, whose fused pass stages up to this many list entries per tile
+  int32_t tile_cap = 0;  // entries per piece of it
+  bool tiles = false;    // one vector whose marks are handed on by tiles
 };
 
 // marking = number of workers whose fused pass will mark (1: a leader known up front).
 GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, int marking) {
   GuessPlan gp;
-  if (c->s.mask == nullptr || n < c->guess_min_n) return gp;
-  // A selection of more than one element in 32 is not worth fetching entry by entry from the mask.
-  // With one marking worker its fused pass hands the marked elements on per tile instead (measured on
-  // 138 M elements: one in ten kept 1.73 ms a step against 1.92 on the histogram route, one in a
-  // hundred 1.40 against 1.43 with the mask alone, one in a thousand 1.365 against 1.347: a tile has
-  // to hand on a hundred elements or so for the pieces to pay for what they cost the pass, so
-  // sparser selections keep the mask alone unless the option asks for pieces everywhere).  Entries a
-  // tile is expected to hand on: the keys reaching the guessed bound are at most about 1.2 k (the
-  // bound is the lower edge of a top-digit bin, or with pieces of a second-digit bin), spread over
-  // the tiles; room for 1.3 k's share plus six standard deviations of a tile's count.  Selections
-  // too dense for a piece take the histogram route.
-  const bool dense = k * 32 > n;
-  const bool worth_pieces = k * 256 >= n;  // 128 kept elements per tile or more
-  const double per_tile = 1.3 * (double)k * (double)kPassTile / (double)n;
-  const int64_t want = ((int64_t)std::ceil(per_tile + 6.0 * std::sqrt(per_tile) + 32.0) + 63) / 64 * 64;
-  const int64_t ntiles = (n + kPassTile - 1) / kPassTile;
-  if ((c->stage_tiles == 2 || (c->stage_tiles == 1 && worth_pieces)) && marking == 1 && want <= kStageMax &&
-      ntiles * want <= c->s.tilebuf_entries)
-    gp.tile_cap = (int32_t)want;
-  if (gp.tile_cap == 0 && dense) return gp;
+  if (c->s.mask == nullptr || n < (marking == 1 && !c->guess_min_n_set ? kTilesMinN : c->guess_min_n)) return gp;
+  // With one marking worker its marks are handed on by tiles (k_mark_tiles), unless the option forbids it or a tile's piece
+  // would not hold its share: at most 1.3 k's, and six standard deviations.  Very sparse selections on very long vectors do
+  // without, as the mask then is the smaller thing to write (histogram route / mask / tiles, us a step: 138 M x 4, one in
+  // 3000 kept 1386/1266/1269, in 1000 1396/1282/1264, in 250 1419/1321/1269, in 100 1468/1413/1294; 400 M x 2, one in 3000
+  // 2324/1978/2039, in 1000 2354/2011/2027, in 500 2395/2081/2032; 25.6 M x 4, one in 1000 304/306/280, in 100
+  // 316/323/290; below kTilesMinN see there).
+  const double per_tile = 1.3 * (double)k * (double)kMarkTile / (double)n;
+  const bool worth = c->stage_tiles == 2 || n < ((int64_t)1 << 28) || k * 700 >= n;
+  gp.tiles = c->stage_tiles != 0 && marking == 1 && worth && per_tile + 6.0 * std::sqrt(per_tile) + 32.0 <= (double)kMarkMax;
+  // A selection of more than one element in 32 is not worth fetching entry by entry from the mask; nor is the mask on
+  // vectors that the tiles alone would take.
+  if (!gp.tiles && (k * 32 > n || n < c->guess_min_n)) return gp;
   int64_t runs = n / (4 * kGuessRun);  // at most a quarter of the vector
   if (runs > 16384) runs = 16384;
   if (runs < 256) return gp;
@@ -721,8 +751,12 @@ GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, int marking) {
   gp.stride = n / runs;
   // keys of the sample expected above the true threshold, plus six standard deviations and a few
   const double expect = (double)k * (double)(runs * kGuessRun) / (double)n;
-  gp.m_hi = (uint32_t)std::ceil(expect + 6.0 * std::sqrt(expect) + 8.0);
+  const double margin = 6.0 * std::sqrt(expect) + 8.0;
+  gp.m_hi = (uint32_t)std::ceil(expect + margin);
+  gp.m_mid = (uint32_t)std::max(1.0, expect + 0.5);
+  gp.m_lo = (uint32_t)std::max(1.0, expect - margin);
   gp.on = (int64_t)gp.m_hi <= runs * kGuessRun;
+  gp.tiles = gp.tiles && gp.on;
   return gp;
 }
 
@@ -771,10 +805,8 @@ GuessPlan plan_guess_read(const artopk_ctx* c, int64_t n, int64_t k, int vectors
 // the memory of the vectors' masks, which this route does not use.
 TileBuf span_buf(const artopk_ctx* c, const GuessPlan& gp, int64_t n) {
   const int64_t nspans = (n + gp.span - 1) / gp.span;
-  TileBuf t{c->s.tilebuf, reinterpret_cast<uint32_t*>(c->s.mask), nspans * gp.tile_cap, 2 * c->s.mask_stride,
-            gp.tile_cap};
-  t.span = gp.span;
-  return t;
+  return TileBuf{c->s.tilebuf, reinterpret_cast<uint32_t*>(c->s.mask), nspans * gp.tile_cap, 2 * c->s.mask_stride,
+                 gp.tile_cap, gp.span};
 }
 
 // The marking pass over the first nv vectors of the table.
@@ -804,30 +836,24 @@ void launch_pass_seg(artopk_ctx* c, const Plan& pl, const PtrTable& r, int64_t n
 // Samples the first nvec vectors of (g + residual) into slots 0 .. nvec-1 (cleared beforehand).
 void enqueue_guess(artopk_ctx* c, const GuessPlan& gp, const PtrTable& g, const PtrTable& res, int nvec,
                    bool read_only = false) {
-  // one vector whose marked elements are handed on per tile: a finer bound keeps the list (and the
-  // number of values to give back afterwards) close to k
-  uint32_t* sample = (!read_only && nvec == 1 && gp.tile_cap > 0) ? c->s.sample_keys : nullptr;
   // about 128 blocks over all vectors (measured: 8 vectors take 70 us with 64 blocks each, 32 us
   // with 16; one vector 15 us with 64 blocks, 19 us with 16)
   int gblocks = 128 / nvec;
   if (gblocks > 64) gblocks = 64;
   if (gblocks < 8) gblocks = 8;
-  if (read_only) {
-    gblocks = (gp.runs + 255) / 256;  // one run a thread
-    hipLaunchKernelGGL(k_guess<kGNone>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
-                       gp.stride, gp.m_hi, gp.m_max, sample);
-  } else if (c->g_type == ARTOPK_G_BF16)
-    hipLaunchKernelGGL(k_guess<kGBF16>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
-                       gp.stride, gp.m_hi, gp.m_max, sample);
+  if (read_only) gblocks = (gp.runs + 255) / 256;  // one run a thread
+#define GUESS_LAUNCH(GT_) \
+  hipLaunchKernelGGL(k_guess<GT_>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs, gp.stride, \
+                     gp.m_hi, gp.m_max)
+  if (read_only)
+    GUESS_LAUNCH(kGNone);
+  else if (c->g_type == ARTOPK_G_BF16)
+    GUESS_LAUNCH(kGBF16);
   else if (c->g_type == ARTOPK_G_F16)
-    hipLaunchKernelGGL(k_guess<kGF16>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
-                       gp.stride, gp.m_hi, gp.m_max, sample);
+    GUESS_LAUNCH(kGF16);
   else
-    hipLaunchKernelGGL(k_guess<kGF32>, dim3(gblocks, nvec), dim3(256), 0, c->stream, g, res, c->s.h_all, gp.runs,
-                       gp.stride, gp.m_hi, gp.m_max, sample);
-  if (sample != nullptr)
-    hipLaunchKernelGGL(k_guess_refine, dim3(64), dim3(256), 0, c->stream, c->s.h_all, sample, gp.runs * kGuessRun,
-                       gp.m_hi);
+    GUESS_LAUNCH(kGF32);
+#undef GUESS_LAUNCH
 }
 
 // How k_tail takes a selection: ranges (blocks) a vector, and rows of 256 elements in each of a wave's pieces (log2).
@@ -867,7 +893,7 @@ TailPlan tail_plan(const Plan& pl, int64_t n, int source) {
 int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n, int32_t* idx_out,
                    bool hist_ready, int slot_by_leader, float* vals_row = nullptr,
                    const LeaderArgs* leader_args = nullptr, bool guessed = false, float* zero_vec = nullptr,
-                   int32_t tile_cap = 0, int32_t first_slot = 0, const GuessPlan* spans = nullptr,
+                   int32_t first_slot = 0, const GuessPlan* spans = nullptr,
                    bool seg_hist_ready = false) {
   hipStream_t st = c->stream;
   const unsigned nseg = (unsigned)pl.nseg;
@@ -906,7 +932,7 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
     // state says need_full, and the same two launches build the histogram of every key and pick
     // from that, after which the selection goes on as without a guess.
     p.mask = spans ? nullptr : c->s.mask + (size_t)first_slot * (size_t)c->s.mask_stride;
-    p.tiles = spans ? span_buf(c, *spans, n) : tile_buf(c, tile_cap);
+    if (spans) p.tiles = span_buf(c, *spans, n);
     p.use_mcount = 1;
     hipLaunchKernelGGL(k_pick_mask, dim3(1, nseg), dim3(1024), 0, st, p, la);
     SelParams pf = p;
@@ -941,12 +967,7 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   // shapes measured on the 138 M and 1 G workloads); on the guess route the same launch counts
   // the second digit over a list that was written from the mask
   const bool long_list = one_range && (int64_t)pl.desc[0].k * 32 > n;
-  if (guessed && hist_ready && long_list) {
-    // a list of many millions of entries written from the staged pieces: the lean list kernel
-    // counts its second digit; the array pass stands by for a guess that did not hold
-    hipLaunchKernelGGL(k_list_hist, dim3((unsigned)lblocks, nseg), dim3(256), 0, st, p, 1);
-    hipLaunchKernelGGL((k_compact1<kC1Waves, kC1R>), dim3(pl.max_chunks, nseg), dim3(64 * kC1Waves), 0, st, p);
-  } else if (guessed && hist_ready) {
+  if (guessed && hist_ready) {
     const int64_t b1 = lblocks > pl.max_chunks ? lblocks : pl.max_chunks;
     if (spans)  // (half as many chunks as behind a fused pass)
       hipLaunchKernelGGL(k_level1<8>, dim3((unsigned)b1, nseg), dim3(512), 0, st, p);
@@ -977,6 +998,93 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
     hipLaunchKernelGGL(k_final<true>, dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
   else
     hipLaunchKernelGGL(k_final<false>, dim3(fblocks, nseg), dim3(kCompactThreads), 0, st, p);
+  HIP_TRY(c, hipGetLastError());
+  return ARTOPK_OK;
+}
+
+// Whether a segmented selection goes by tiles (a guess length that was set holds for these, too).
+bool segments_by_tiles(const artopk_ctx* c, const Plan& pl, int64_t n) {
+  return pl.tiles > 0 && n >= (c->guess_min_n_set ? c->guess_min_n : kSegTilesMinN);
+}
+
+// Entries that a tile's piece may have: those of the fused pass' tiles, or what there is room for.
+int32_t tile_piece_cap(const artopk_ctx* c, int64_t tiles) {
+  return (int32_t)std::min<int64_t>(kMarkMax, c->s.tilebuf_entries / tiles);
+}
+
+// A vector that is only read by tiles comes through the caches up to this length: what gathers from it next then finds some
+// of its lines there (25.6 M x 8, variance rule, gather 96 us behind non-temporal loads, 86 behind ordinary ones).
+constexpr int64_t kCachedMaxN = (int64_t)1 << 26;
+
+// The bounds and the marking.
+template <int GT>
+void launch_tiles(artopk_ctx* c, const SelParams& p, const TileArgs& a, const Plan& pl, const GuessPlan& gp, const float* g, float* res) {
+  const dim3 block(kMarkThreads), mark_grid((unsigned)std::min<int32_t>(a.ntiles, 2 * kMaxPassBlocks));
+  if (pl.use_table) {
+    PtrTable gt{};
+    gt.p[0] = const_cast<float*>(g);
+    hipLaunchKernelGGL(k_guess_segs<GT>, dim3((unsigned)pl.nseg), dim3(1024), 0, c->stream, p, gt, a.cap);
+  } else if constexpr (GT != kGNone) {
+    hipLaunchKernelGGL(k_guess_tiles<GT>, dim3((unsigned)((gp.runs + kGuessThreads - 1) / kGuessThreads)), dim3(kGuessThreads), 0, c->stream, g, res,
+                       c->s.h_all, gp.runs, gp.stride, gp.m_hi, gp.m_mid, gp.m_lo, c->s.zero_base + kTileInfo);
+  }
+  if (c->pass_a_nt && (GT != kGNone || p.n > kCachedMaxN))
+    hipLaunchKernelGGL((k_mark_tiles<true, GT>), mark_grid, block, 0, c->stream, p, a, g, res);
+  else
+    hipLaunchKernelGGL((k_mark_tiles<false, GT>), mark_grid, block, 0, c->stream, p, a, g, res);
+}
+
+template <bool APART>
+void launch_tiles_rest(artopk_ctx* c, const SelParams& p, const TileArgs& a) {
+  const dim3 groups((unsigned)a.ngroups), block(64 * kTileWaves);
+  hipLaunchKernelGGL((k_tiles_digit<1, APART>), groups, block, 0, c->stream, p, a);
+  hipLaunchKernelGGL((k_tiles_digit<2, APART>), groups, block, 0, c->stream, p, a);
+  hipLaunchKernelGGL(k_tiles_count<APART>, groups, block, 0, c->stream, p, a);
+  hipLaunchKernelGGL(k_tiles_out<APART>, groups, block, 0, c->stream, p, a);
+}
+
+// Selection by tiles (see TileArgs) on the leader's vector, leader_dev's, of tab, from the sample on; the scratch has been
+// cleared.  g and res: its gradients, and itself, to be added up on the way, or nullptr.  zero: its kept entries become +0.0.
+int enqueue_tiles(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n, int32_t* idx_out, float* vals_row,
+                  const GuessPlan& gp, const float* g, float* res, bool zero) {
+  Scratch& s = c->s;
+  SelParams p = make_params(c, pl, tab, n, idx_out, vals_row, 0, false);
+  p.zero_vec = zero ? res : nullptr;
+  TileArgs a{};
+  a.ntiles = pl.use_table ? pl.tiles : pl.desc[0].ntiles;
+  a.ngroups = pl.use_table ? pl.tile_groups : (a.ntiles + kTileWaves - 1) / kTileWaves;
+  a.map = pl.use_table ? s.tile_map : nullptr;
+  a.groups = pl.use_table ? reinterpret_cast<const uint2*>(s.tile_map + s.map_tiles) : nullptr;
+  a.pieces = s.tilebuf;
+  a.cap = tile_piece_cap(c, a.ntiles);
+  // (nobody else has anything in S's memory now: 16.8 MB at least and 16 KB for every segment, for kTileWords a tile)
+  a.kept = reinterpret_cast<uint64_t*>(s.S);
+  a.held = s.S + 4 * (size_t)a.ntiles;  // (no more blocks than tiles)
+  a.marked = a.held + a.ntiles;
+  a.above = a.marked + a.ntiles;
+  a.among = a.above + (size_t)kTileWaves * a.ntiles;
+  a.slots = a.among + (size_t)kTileWaves * a.ntiles;
+  a.bins = pl.use_table ? s.zero_base + kSegHtop : s.h_all;
+  a.bins_stride = pl.use_table ? kSegWords : 0;
+  a.more_bins = pl.use_table ? tile_more_bins(c, a.ntiles) : s.h_all + kHistBins;
+  a.any_full = s.zero_base + kTileInfo + kTileFull;
+  a.tile_start = !pl.use_table || pl.tiles_aligned ? s.tile_start : nullptr;
+  if (g == nullptr)
+    launch_tiles<kGNone>(c, p, a, pl, gp, g, res);
+  else if (c->g_type == ARTOPK_G_BF16)
+    launch_tiles<kGBF16>(c, p, a, pl, gp, g, res);
+  else if (c->g_type == ARTOPK_G_F16)
+    launch_tiles<kGF16>(c, p, a, pl, gp, g, res);
+  else
+    launch_tiles<kGF32>(c, p, a, pl, gp, g, res);
+  if (g != nullptr) prof_mark(c, 1);
+  hipLaunchKernelGGL(k_tiles_pick, dim3((unsigned)pl.nseg), dim3(1024), 0, c->stream, p, a);
+  hipLaunchKernelGGL(k_tiles_full, dim3((unsigned)std::min<int32_t>(a.ntiles, 2 * c->num_cu)), dim3(kMarkThreads), 0, c->stream, p, a);
+  // (a block's tiles apart: each wave adds up what is in front of its own, which long vectors have too many tiles for)
+  if (a.ntiles <= 4096)
+    launch_tiles_rest<true>(c, p, a);
+  else
+    launch_tiles_rest<false>(c, p, a);
   HIP_TRY(c, hipGetLastError());
   return ARTOPK_OK;
 }
@@ -1110,7 +1218,7 @@ int enqueue_topk_rows(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t n, 
     }
     if ((rc = enqueue_select(c, pl, t, n, idx_rows + (size_t)r0 * (size_t)k, hist_ready || gp.on, 1,
                              val_rows ? val_rows + (size_t)r0 * (size_t)k : nullptr, nullptr, marks, nullptr,
-                             0, hist_ready ? r0 : 0, gp.on ? &gp : nullptr)))
+                             hist_ready ? r0 : 0, gp.on ? &gp : nullptr)))
       return rc;
   }
   return ARTOPK_OK;
@@ -1221,8 +1329,9 @@ void clear_small(artopk_ctx* c) {
 struct Layout {
   uint32_t cap = 0;
   int64_t list_entries = 0, max_tiles = 0, mask_stride = 0, tilebuf_entries = 0;
+  int64_t map_tiles = 0;
   int32_t blocks = 0;  // scratch blocks: one per segment, or per vector of a batch
-  size_t o_hall = 0, o_mask = 0, o_zero = 0, o_S = 0, o_coff = 0, o_part = 0, o_var = 0, o_leader = 0, o_err = 0, o_counter = 0, o_list = 0, o_vals = 0, o_rows = 0, o_table = 0, o_cmap = 0, o_tstart = 0, o_tbuf = 0, o_tcnt = 0, o_sample = 0, o_small = 0;
+  size_t o_hall = 0, o_mask = 0, o_zero = 0, o_S = 0, o_coff = 0, o_part = 0, o_var = 0, o_leader = 0, o_err = 0, o_counter = 0, o_list = 0, o_vals = 0, o_rows = 0, o_table = 0, o_cmap = 0, o_tstart = 0, o_tmap = 0, o_tbuf = 0, o_small = 0;
   size_t small_words = 0;  // words of the short vectors' scratch that have to be zero between steps
   size_t total = 0;
 };
@@ -1278,19 +1387,19 @@ Layout scratch_layout(int32_t max_w, int64_t max_n, int64_t max_k, int32_t max_s
   L.o_table = take((size_t)max_segments * sizeof(SegDesc));
   L.o_cmap = take(((size_t)kMaxChunks + (size_t)max_segments) * sizeof(uint32_t));
   L.o_tstart = take((size_t)(max_n / kPassTile + 2) * sizeof(int32_t));
-  // pieces of the survivor list staged per tile by the fused pass: room for kStageMax entries in
-  // every tile of the longest vector (1.5 bytes per element)
-  const int64_t max_tiles_pass = (max_n + kPassTile - 1) / kPassTile;
-  L.tilebuf_entries = max_tiles_pass * (int64_t)kStageMax;
+  // tiles of a segmented layout: two more than its share of the vector for every segment, and their groups
+  const int64_t mark_tiles = max_n / kMarkTile + 1;
+  L.map_tiles = max_segments > 1 ? mark_tiles + 2 * std::min<int64_t>(max_segments, mark_tiles) : 0;
+  L.o_tmap = take((size_t)(L.map_tiles + L.map_tiles / 2 + 1) * sizeof(uint4));
+  // pieces of marked elements: 6144 entries for every tile of the streaming passes (1.5 bytes per element)
+  L.tilebuf_entries = (max_n + kPassTile - 1) / kPassTile * 6144;
   L.o_tbuf = take((size_t)L.tilebuf_entries * sizeof(uint2));
-  L.o_tcnt = take((size_t)(max_tiles_pass + 1) * sizeof(uint32_t));
-  L.o_sample = take((size_t)16384 * kGuessRun * sizeof(uint32_t));
   // (hist, ctr, claim, dig1 and dig2 have to be zero between steps)
   L.small_words = (size_t)(max_w + 1) * kSmallReps * kHistBins + kSmallCtr + kSmallMaxUnits + 2 * kSmallReps * 128;
   const int64_t small_n = max_n < kSmallMaxNLimit ? max_n : kSmallMaxNLimit;
   size_t small_bytes = (L.small_words + (size_t)kSmallMaxChunks * 129) * sizeof(uint32_t);
   // (callers plan with the size that the header states)
-  const size_t stated = (size_t)max_w * ((size_t)128 << 10) + (size_t)(4.5 * (double)small_n) + ((size_t)160 << 10);
+  const size_t stated = (size_t)max_w * ((size_t)128 << 10) + (size_t)(4.5 * (double)small_n) + ((size_t)1184 << 10);
   if (small_bytes < stated) small_bytes = stated;
   L.o_small = take(small_bytes);
   L.total = off;
@@ -1358,9 +1467,9 @@ int artopk_create(artopk_ctx** out, int32_t max_w, int64_t max_n, int64_t max_k,
   s.table_dev = reinterpret_cast<SegDesc*>(base + L.o_table);
   s.chunk_map = reinterpret_cast<uint32_t*>(base + L.o_cmap);
   s.tile_start = reinterpret_cast<int32_t*>(base + L.o_tstart);
+  s.tile_map = reinterpret_cast<uint4*>(base + L.o_tmap);
+  s.map_tiles = L.map_tiles;
   s.tilebuf = reinterpret_cast<uint2*>(base + L.o_tbuf);
-  s.tile_cnt = reinterpret_cast<uint32_t*>(base + L.o_tcnt);
-  s.sample_keys = reinterpret_cast<uint32_t*>(base + L.o_sample);
 
   uint32_t* small = reinterpret_cast<uint32_t*>(base + L.o_small);
   s.small.hist = small;
@@ -1648,8 +1757,9 @@ int artopk_select_topk(artopk_ctx* ctx, const float* acc, int64_t n, int32_t nse
   if (seg_off && nseg > 1) {
     const Plan* pl = nullptr;
     if ((rc = segmented_plan(ctx, n, nseg, seg_off, seg_k, &pl))) return rc;
-    if ((rc = enqueue_clear(ctx, *pl, 0, 0, nullptr))) return rc;  // the single vector is "leader 0"
-    rc = enqueue_select(ctx, *pl, tab, n, idx_out, false, 0);
+    if ((rc = enqueue_clear(ctx, *pl, 0, 0, nullptr, segments_by_tiles(ctx, *pl, n)))) return rc;  // the single vector is "leader 0"
+    rc = segments_by_tiles(ctx, *pl, n) ? enqueue_tiles(ctx, *pl, tab, n, idx_out, nullptr, GuessPlan{}, nullptr, nullptr, false)
+                                             : enqueue_select(ctx, *pl, tab, n, idx_out, false, 0);
   } else {
     rc = enqueue_topk_rows(ctx, tab, 1, n, k, idx_out, nullptr, false, false);
   }
@@ -1858,6 +1968,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   // a long segmented vector: the fused pass strides over the tiles as on the guess route (the
   // selection builds the segments' histograms from the leader's vector afterwards either way)
   const bool seg_stride = segmented && n >= ctx->guess_min_n;
+  const bool by_tiles = segmented && segments_by_tiles(ctx, *pl, n);
 
   ctx->last_guessed = 0;
   ctx->last_dom_workers = w;
@@ -1924,32 +2035,38 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
     const PtrTable g1t = make_table(g1, 1), r1t = make_table(r1, 1);
     prof_begin(ctx);
     prof_mark(ctx, 0);
-    if ((rc = enqueue_clear(ctx, *pl, segmented ? 0 : 1, L, leader_out))) return rc;
+    const bool tiles = segmented ? by_tiles : gp.tiles;
+    if ((rc = enqueue_clear(ctx, *pl, segmented ? 0 : 1, L, leader_out, tiles))) return rc;
     ctx->last_guessed = gp.on ? 1 : 0;
+    ctx->last_one_launch = 0;
     ctx->last_dom_workers = w > 1 ? w - 1 : 1;
-    if (gp.on) {
-      enqueue_guess(ctx, gp, g1t, r1t, 1);
-      launch_pass_mark(ctx, 0, 1, g1t, r1t, n, geom.chunk_elems, gp.tile_cap);
-    } else if (segmented) {
-      if (g_type == ARTOPK_G_BF16)
-        launch_pass_seg<kGBF16>(ctx, *pl, rt, n, g[L], residual[L]);
-      else if (g_type == ARTOPK_G_F16)
-        launch_pass_seg<kGF16>(ctx, *pl, rt, n, g[L], residual[L]);
-      else
-        launch_pass_seg<kGF32>(ctx, *pl, rt, n, g[L], residual[L]);
-      HIP_TRY(ctx, hipGetLastError());
+    if (gp.on && !tiles) enqueue_guess(ctx, gp, g1t, r1t, 1);
+    if (tiles) {
+      if ((rc = enqueue_tiles(ctx, *pl, rt, n, idx_out, vals + (size_t)L * (size_t)k, gp, g[L], residual[L], true))) return rc;
     } else {
-      launch_pass_a(ctx, 0, 1, dim3(geom.nchunks, 1), g1t, r1t, n, geom, 0);
+      if (gp.on) {
+        launch_pass_mark(ctx, 0, 1, g1t, r1t, n, geom.chunk_elems);
+      } else if (segmented) {
+        if (g_type == ARTOPK_G_BF16)
+          launch_pass_seg<kGBF16>(ctx, *pl, rt, n, g[L], residual[L]);
+        else if (g_type == ARTOPK_G_F16)
+          launch_pass_seg<kGF16>(ctx, *pl, rt, n, g[L], residual[L]);
+        else
+          launch_pass_seg<kGF32>(ctx, *pl, rt, n, g[L], residual[L]);
+        HIP_TRY(ctx, hipGetLastError());
+      } else {
+        launch_pass_a(ctx, 0, 1, dim3(geom.nchunks, 1), g1t, r1t, n, geom, 0);
+      }
+      prof_mark(ctx, 1);
+      // The leader's residual is zeroed inside the selection: its kernels have the kept values in
+      // registers (level-1 compaction) or write the kept indices anyway (final list pass).
+      if ((rc = enqueue_select(ctx, *pl, rt, n, idx_out, !segmented, 0, vals + (size_t)L * (size_t)k, nullptr, gp.on,
+                               residual[L], 0, nullptr, segmented)))
+        return rc;
     }
-    prof_mark(ctx, 1);
-    // The leader's residual is zeroed inside the selection: its kernels have the kept values in
-    // registers (level-1 compaction) or write the kept indices anyway (final list pass).
-    if ((rc = enqueue_select(ctx, *pl, rt, n, idx_out, !segmented, 0, vals + (size_t)L * (size_t)k, nullptr, gp.on,
-                             residual[L], gp.tile_cap, 0, nullptr, segmented)))
-      return rc;
     prof_mark(ctx, 2);
     const int rest = (int)w - 1;
-    enqueue_tile_starts(ctx, idx_out, n, k);
+    if (!tiles || !pl->tiles_aligned) enqueue_tile_starts(ctx, idx_out, n, k);  // (else k_tiles_out has left them)
     prof_dom(ctx, false);
     if (rest > 0) {
       launch_pass_rest(ctx, gt, rt, (int)w, L, n, idx_out, k, vals);
@@ -1977,7 +2094,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   prof_begin(ctx);
   prof_mark(ctx, 0);
   // the flat select reuses the histograms pass A builds; segments build their own afterwards
-  if ((rc = enqueue_clear(ctx, *pl, segmented ? 0 : (device_leader ? (int)w : 1)))) return rc;
+  if ((rc = enqueue_clear(ctx, *pl, segmented ? 0 : (device_leader ? (int)w : 1), -1, nullptr, by_tiles))) return rc;
   int slot_by_leader = 0;
   LeaderArgs leader_args{};
   const bool marking = gp.on && device_leader;
@@ -2049,8 +2166,9 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   }
   HIP_TRY(ctx, hipGetLastError());
 
-  rc = enqueue_select(ctx, *pl, rt, n, idx_out, !segmented, slot_by_leader, nullptr,
-                      leader_args.partials ? &leader_args : nullptr, marking);
+  rc = by_tiles ? enqueue_tiles(ctx, *pl, rt, n, idx_out, nullptr, gp, nullptr, nullptr, false)
+                : enqueue_select(ctx, *pl, rt, n, idx_out, !segmented, slot_by_leader, nullptr,
+                                 leader_args.partials ? &leader_args : nullptr, marking);
   if (rc) return rc;
   prof_mark(ctx, 2);
   if ((rc = enqueue_gather(ctx, rt, w, n, idx_out, k, vals_out, sum_out, true))) return rc;

@@ -9,6 +9,9 @@
 //   k_pass_mark      the same pass behind k_guess: instead of histograms a bit
 //                    mask of the keys reaching the guessed bound; its blocks
 //                    stride over the tiles of the vector
+//   k_guess_tiles / k_guess_segs, k_mark_tiles, k_tiles_pick .. k_tiles_out   the leader's own
+//                    pass where it is known up front, and segments of long vectors: bounds,
+//                    marked elements handed on tile by tile, and the selection from these
 //   k_mark_spans     the marking alone, on vectors that are only read: their marked
 //                    elements per span of a wave (k_spans_or_hist then writes the list)
 //   k_hist0          the same histograms alone (stand-alone select, segments,
@@ -72,11 +75,12 @@ constexpr int kHistReps = 16;            // partial copies of a whole-vector his
 // One slot of whole-vector scratch (32-bit words): the partial histogram copies, then the
 // histogram of the threshold-guess sample, then its control words.
 constexpr int kSlotGuessHist = kHistReps * kHistBins;
-constexpr int kSlotCtrl = kSlotGuessHist + kHistBins;  // [0] blocks done, [1] guessed key bound, [2] a tile kept its marks to the mask,
-                                                       // [3] top digit of the bound, [4] sample keys above that digit, [5] refine blocks done
+constexpr int kSlotCtrl = kSlotGuessHist + kHistBins;  // [0] blocks done, [1] guessed key bound, [2] blocks of k_guess_tiles through
 constexpr int kSlotMcount = kSlotCtrl + 16;            // marked elements per chunk (kMaxChunks words)
-constexpr int kSlotRefine = kSlotMcount + 1024;        // second-digit histogram of the guess sample (k_guess_refine)
+constexpr int kSlotRefine = kSlotMcount + 1024;        // second-digit histogram of the guess sample (k_guess_tiles)
 constexpr int kSlotWords = kSlotRefine + kHistBins;
+constexpr int kGuessMidAt = 8 * kHistBins;             // (k_guess_tiles: two histograms in copies' places)
+constexpr int kGuessOddAt = 9 * kHistBins;
 constexpr uint32_t kNoGuess = 0xffffffffu;             // no key reaches this bound
 constexpr int kGuessRun = 16;                          // consecutive elements per sample run
 constexpr uint32_t kKeyMask = 0x7fffffffu;
@@ -86,16 +90,14 @@ constexpr uint32_t kQuotaInf = 0x7fffffffu;
 __host__ __device__ constexpr int digit_shift(int level) { return level == 0 ? 19 : (level == 1 ? 7 : 0); }
 __host__ __device__ constexpr uint32_t digit_mask(int level) { return level == 2 ? 0x7fu : 0xfffu; }
 
-constexpr uint32_t kTileOverflow = 0xffffffffu;
-constexpr int kStageMax = 6144;  // list entries a tile can hand on (48 KiB of on-chip memory)
-
+// The pieces of k_mark_spans: the marked elements of every `span` elements, in order.
 struct TileBuf {
-  uint2* buf;       // [slot][tile][cap] staged list entries, or nullptr
-  uint32_t* cnt;    // [slot][tile] entries staged per tile, or kTileOverflow
-  int64_t buf_stride;  // entries per slot
-  int64_t cnt_stride;  // tiles per slot
-  int32_t cap;         // entries per tile (<= kStageMax)
-  int32_t span = 0;    // > 0: pieces of k_mark_spans, one per `span` elements (no mask stands behind them)
+  uint2* buf;       // [vector][span][cap] (index, raw bits)
+  uint32_t* cnt;    // [vector][span] marked elements, which may be more than cap
+  int64_t buf_stride;  // entries per vector
+  int64_t cnt_stride;  // spans per vector
+  int32_t cap;         // entries per span
+  int32_t span;
 };
 
 struct PtrTable {
@@ -152,6 +154,8 @@ struct SegDesc {
   uint32_t k;          // entries wanted
   uint32_t cap;        // survivor-list capacity of this segment
   int32_t vec;         // which vector of the pointer table to select on; -1 = the leader's
+  // its tiles among those of the layout (see TileArgs), the blocks that have them, and further copies of its bins
+  int32_t tile_begin, ntiles, group_begin, bins_begin, bins_more;
   int32_t hreps;  // k_hist0 adds the blocks' histograms to this many copies in SelParams::hcopies (1: to the
                   // one in the segment's scratch block)
 };
@@ -167,7 +171,7 @@ struct SelParams {
   const uint32_t* h_all;   // [workers][kSlotWords] whole-vector histograms from the fused pass, or nullptr
   const uint64_t* mask;    // [workers][mask_stride] survivor bit masks from the fused pass, or nullptr
   int64_t mask_stride;     // 64-bit words per worker
-  TileBuf tiles;           // list entries the fused pass staged per tile (buf == nullptr: none)
+  TileBuf tiles;           // pieces of a marking of vectors that are only read (buf == nullptr: none)
   int32_t use_mcount;      // the slots' per-chunk counts of marked elements are valid
   int32_t from_list;       // k_pick0: the top-digit histogram covers the survivor list written from the mask
   int32_t after_mask;      // k_pick0 behind k_mask_or_hist: from_list if the mask was used, else the full pick
@@ -220,9 +224,9 @@ struct SegView {
   uint32_t* hseg;       // the segment's own top-digit histogram (single copy), what k_hist0 fills without h_all
   const uint32_t* ctrl;  // control words of the vector's slot (guessed bound), or nullptr
   const uint64_t* mask;  // survivor bit mask of the vector, or nullptr
-  const uint2* tbuf;     // list entries the fused pass staged per tile of the vector, or nullptr
-  const uint32_t* tcnt;  // their number per tile (kTileOverflow: none, use the mask)
-  int32_t tcap;          // entries per tile in tbuf
+  const uint2* tbuf;     // the vector's pieces, or nullptr
+  const uint32_t* tcnt;  // marked elements per span
+  int32_t tcap;          // entries per piece
   const uint32_t* mcount;  // marked elements per chunk of the vector, or nullptr
   uint64_t* flags;
   uint32_t* S;
@@ -757,18 +761,6 @@ k_pass_a(PtrTable g, PtrTable res, int64_t n, ChunkGeom geom, int hist_worker, u
 //   histograms afterwards (long segmented vectors).  The ballots and the mask words
 //   (zero, but for Inf and NaN) stay: without them the same pass streamed slower on
 //   8 x 1e9 elements, 16.6 against 16.1 ms.
-//   STAGE: the marked elements of a tile are also handed on as list entries
-//   (index, raw bits), in ascending element order: ranked inside the block (the
-//   128 row counts of the tile are scanned by every wave), collected in on-chip
-//   memory and stored as one contiguous piece to tiles.buf[tile][0 .. count), with
-//   tiles.cnt[tile] = count.  A tile with more marks than tiles.cap entries stores
-//   none and reports kTileOverflow; its marks are still in the mask.  Whoever
-//   builds the survivor list then copies the pieces instead of fetching the marked
-//   values one by one.  In a tile that hands its marks on, the marked elements are
-//   stored to the residual as +0.0 straight away: nearly all of them will be kept,
-//   and the others get their values back from the list once the threshold is known
-//   (see from_pieces(); restore_pieces() does it for all of them if the guess does
-//   not hold).
 // ---------------------------------------------------------------------------
 // Inclusive prefix sums over the 64 lanes of a wave.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
@@ -787,13 +779,10 @@ __device__ __forceinline__ int64_t mask_word(int64_t row) {
   return (row >> 7) * 512 + (row & 15) * 32 + ((row >> 4) & 7) * 4;
 }
 
-template <int STATS, bool NT, int GT, int T, int U, bool STAGE, bool PLAIN = false>
+template <int STATS, bool NT, int GT, int T, int U, bool PLAIN = false>
 __global__ void __launch_bounds__(T)
 k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* __restrict__ h_all,
-            uint64_t* __restrict__ mask, int64_t mask_stride, double* __restrict__ partials, TileBuf tiles) {
-  static_assert(!(PLAIN && STAGE), "nothing is marked in the plain form");
-  __shared__ uint32_t wcnt[STAGE ? (T / 64) * U : 1];  // the tile's 128 row counts, row-major
-  __shared__ uint2 stage[STAGE ? kStageMax : 1];
+            uint64_t* __restrict__ mask, int64_t mask_stride, double* __restrict__ partials) {
   const int w = blockIdx.y;
   const int bx = blockIdx.x;
   const int nblk = gridDim.x;
@@ -816,14 +805,6 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
   VarAcc va;
   const int wave_first = __builtin_amdgcn_readfirstlane(tid - lane);
   static_assert(T == 1024 && U == 8, "mask_word() is laid out for 16 waves x 8 rows");
-  const int wave = wave_first >> 6;
-  uint2* __restrict__ tbuf = STAGE ? tiles.buf + (size_t)w * (size_t)tiles.buf_stride : nullptr;
-  uint32_t* __restrict__ tcnt = STAGE ? tiles.cnt + (size_t)w * (size_t)tiles.cnt_stride : nullptr;
-  // STAGE: what a lane keeps of a tile until its marks are ranked
-  uint32_t own = 0u;      // bit 4 u + e: element e of this lane's group in row u is marked
-  uint32_t rows_cnt = 0u; // lane u < U: marks of the wave's row u
-  uint32_t bits[STAGE ? U : 1][4];
-
   // One tile: U rows of T float4 groups; the wave's rows start at group qw (a multiple of 64).
   // FULL: every group of the tile lies inside the vector, so nothing is predicated.
   auto tile = [&](const int64_t qw, auto full_tag) {
@@ -857,7 +838,7 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
         v.y = a[u].y + b[u].y;
         v.z = a[u].z + b[u].z;
         v.w = a[u].w + b[u].w;
-        if (!STAGE) store4<NT>(rp + 4 * q, v);  // (STAGE stores below, the marked elements as +0.0)
+        store4<NT>(rp + 4 * q, v);
         if (STATS) {  // of the raw gradient, or of the error-fed value
           if (u == 0) va.seed4(STATS == 2 ? a[u] : v);
           va.add4(STATS == 2 ? a[u] : v);
@@ -867,30 +848,7 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
       const uint64_t m1 = __ballot(valid && !(__builtin_fabsf(v.y) < gf));
       const uint64_t m2 = __ballot(valid && !(__builtin_fabsf(v.z) < gf));
       const uint64_t m3 = __ballot(valid && !(__builtin_fabsf(v.w) < gf));
-      const uint32_t row_marked = (uint32_t)(__popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3));
-      marked += row_marked;
-      if (STAGE) {
-        const uint32_t o = (uint32_t)((m0 >> lane) & 1ull) | (uint32_t)((m1 >> lane) & 1ull) << 1 |
-                           (uint32_t)((m2 >> lane) & 1ull) << 2 | (uint32_t)((m3 >> lane) & 1ull) << 3;
-        own |= o << (4 * u);
-        rows_cnt = lane == u ? row_marked : rows_cnt;
-        bits[STAGE ? u : 0][0] = __float_as_uint(v.x);
-        bits[STAGE ? u : 0][1] = __float_as_uint(v.y);
-        bits[STAGE ? u : 0][2] = __float_as_uint(v.z);
-        bits[STAGE ? u : 0][3] = __float_as_uint(v.w);
-        if (valid) {
-          // The marked elements go out as +0.0: they are survivors, nearly all of which the
-          // selection keeps; the list carries their values on, and its final pass puts back the
-          // few that are not kept.  (A tile that turns out not to hand its marks on stores them
-          // again, below.)
-          v4f z;
-          z.x = (o & 1u) ? 0.0f : v.x;
-          z.y = (o & 2u) ? 0.0f : v.y;
-          z.z = (o & 4u) ? 0.0f : v.z;
-          z.w = (o & 8u) ? 0.0f : v.w;
-          store4<NT>(rp + 4 * q, z);
-        }
-      }
+      marked += (uint32_t)(__popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3));
       mine = lane == 4 * u + 0 ? m0 : mine;
       mine = lane == 4 * u + 1 ? m1 : mine;
       mine = lane == 4 * u + 2 ? m2 : mine;
@@ -903,62 +861,8 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
 
   for (int64_t ti = bx; ti < ntiles; ti += nblk) {
     const int64_t qw = ti * TQ + wave_first;  // wave-uniform, so all 64 lanes stay together (the masks need that)
-    if (STAGE) own = 0u;
     const uint32_t marked = (ti + 1) * TQ <= q_hi ? tile(qw, std::true_type{}) : tile(qw, std::false_type{});
     if (!PLAIN && lane == 0 && marked != 0u) atomicAdd(&mcount[(ti * TQ * 4) / chunk_elems], marked);
-    if (STAGE) {
-      // rank the tile's marks: element order is row-major, row = 16 u + wave, then lane, then e
-      if (lane < U) wcnt[lane * (T / 64) + wave] = rows_cnt;
-      __syncthreads();
-      const uint32_t c0 = wcnt[lane], c1 = wcnt[64 + lane];  // (every wave scans the 128 counts itself)
-      const uint32_t s0 = wave_incl_scan(c0), s1 = wave_incl_scan(c1);
-      const uint32_t half = __shfl(s0, 63, 64);
-      const uint32_t total = half + __shfl(s1, 63, 64);
-      const bool fits = total <= (uint32_t)tiles.cap;
-      if (!fits) {  // rare: the marks stay in the mask only, so their values go back into the vector
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (((own >> (4 * u)) & 0xfu) != 0u) {
-            const int64_t q = qw + lane + u * T;
-            v4f v;
-            v.x = __uint_as_float(bits[STAGE ? u : 0][0]);
-            v.y = __uint_as_float(bits[STAGE ? u : 0][1]);
-            v.z = __uint_as_float(bits[STAGE ? u : 0][2]);
-            v.w = __uint_as_float(bits[STAGE ? u : 0][3]);
-            store4<NT>(rp + 4 * q, v);
-          }
-        }
-        if (tid == 0) atomicOr(&slot[kSlotCtrl + 2], 1u);
-      }
-      if (fits && total != 0u) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int r = u * (T / 64) + wave;  // this wave's row u among the tile's 128
-          // marks in the rows before it
-          const uint32_t before = r < 64 ? __shfl(s0 - c0, r, 64) : half + __shfl(s1 - c1, r - 64, 64);
-          const uint64_t b0 = __ballot((own >> (4 * u + 0)) & 1u), b1 = __ballot((own >> (4 * u + 1)) & 1u);
-          const uint64_t b2 = __ballot((own >> (4 * u + 2)) & 1u), b3 = __ballot((own >> (4 * u + 3)) & 1u);
-          if (((own >> (4 * u)) & 0xfu) != 0u) {
-            uint32_t pos = before + popc_lt(b0) + popc_lt(b1) + popc_lt(b2) + popc_lt(b3);
-            const uint32_t j0 = (uint32_t)(4 * (qw + lane + u * T));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              if ((own >> (4 * u + e)) & 1u) {
-                stage[pos] = make_uint2(j0 + (uint32_t)e, bits[STAGE ? u : 0][e]);
-                ++pos;
-              }
-            }
-          }
-        }
-      }
-      __syncthreads();
-      if (fits) {
-        uint2* __restrict__ dst = tbuf + (size_t)ti * (size_t)tiles.cap;
-        for (uint32_t i = (uint32_t)tid; i < total; i += T) dst[i] = stage[i];
-      }
-      if (tid == 0) tcnt[ti] = fits ? total : kTileOverflow;
-      // (the next tile writes wcnt before its first barrier and stage behind it: both are free by then)
-    }
   }
   // scalar tail (n not a multiple of 4): the first block
   if (bx == 0) {
@@ -1179,6 +1083,28 @@ __global__ void k_set_counter(uint64_t* __restrict__ counter, uint64_t value) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *counter = value;
 }
 
+// words of a segment's scratch block, behind the last digit's 128 counts in kSegHist2: what the marking of tiles goes by
+constexpr int kTileInfo = kSegHist2 + 1024;
+constexpr int kTileBound = 0;  // the bound (0: none)
+constexpr int kTileShift = 1;  // bits of a bin
+constexpr int kTileZero = 2;   // marked keys from here on are stored as +0.0 at once
+constexpr int kTileFull = 8;   // (of the first segment's) some segment's bound does not hold
+constexpr int kMarkThreads = 512, kMarkTile = 32 * kMarkThreads;  // a block of k_mark_tiles, and what it loads at a time
+constexpr int kMarkMax = 2816;   // entries a tile's piece can have (22 KiB on chip: four blocks a compute unit)
+constexpr int kTileBins = 4095;  // bins that start at the bound; what is above them all is not binned
+
+// bound: at most k keys of the sample's share, and a margin, reach it; mid: the sample's estimate of the threshold; top: a
+// digit that surely lies above it.
+__device__ __forceinline__ void tile_info(uint32_t* __restrict__ info, uint32_t bound, uint32_t mid, uint32_t top) {
+  if (bound == 0u) return;
+  const uint32_t reach = ((top + 1u) << 19) - bound;
+  uint32_t s = 0u;
+  while (s < 19u && ((uint32_t)kTileBins << s) < reach) ++s;
+  info[kTileBound] = bound;
+  info[kTileShift] = s;
+  info[kTileZero] = mid < bound ? bound : mid < 0x7f800000u ? mid : 0x7f800000u;
+}
+
 // ---------------------------------------------------------------------------
 // k_guess : a lower bound on the key of the k-th largest |g + residual| of each
 // vector, from a sample, before the fused pass runs.  grid = (blocks, vectors),
@@ -1189,17 +1115,14 @@ __global__ void k_set_counter(uint64_t* __restrict__ counter, uint64_t value) {
 // than m_hi, or more than m_max of its keys reach that bound).  GT = kGNone samples
 // the residuals alone.  The bound is only a guess: whoever uses it checks that at least
 // k keys of the whole vector reach it.
-//   With sample_keys (vector 0 only: room for runs kGuessRun keys) every block
-//   also stores its sample's keys there, for k_guess_refine.
 // ---------------------------------------------------------------------------
 template <int GT>
 __global__ void __launch_bounds__(256)
 k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_t stride, uint32_t m_hi,
-        uint32_t m_max, uint32_t* __restrict__ sample_keys) {
+        uint32_t m_max) {
   __shared__ uint32_t lh[kHistBins];
   __shared__ uint32_t wsum[4];
   __shared__ int last_sh, hit_sh;
-  __shared__ uint32_t hit_above_sh;
   const int tid = threadIdx.x;
   const int v = blockIdx.y;
   const float* __restrict__ gp = g.p[v];
@@ -1218,16 +1141,10 @@ k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_
     }
 #pragma unroll
     for (int i = 0; i < kGuessRun / 4; ++i) {
-      uint4 kq;
-      kq.x = __float_as_uint(GT != kGNone ? a[i].x + b[i].x : b[i].x) & kKeyMask;
-      kq.y = __float_as_uint(GT != kGNone ? a[i].y + b[i].y : b[i].y) & kKeyMask;
-      kq.z = __float_as_uint(GT != kGNone ? a[i].z + b[i].z : b[i].z) & kKeyMask;
-      kq.w = __float_as_uint(GT != kGNone ? a[i].w + b[i].w : b[i].w) & kKeyMask;
-      atomicAdd(&lh[kq.x >> 19], 1u);
-      atomicAdd(&lh[kq.y >> 19], 1u);
-      atomicAdd(&lh[kq.z >> 19], 1u);
-      atomicAdd(&lh[kq.w >> 19], 1u);
-      if (sample_keys != nullptr && v == 0) reinterpret_cast<uint4*>(sample_keys + (size_t)r * kGuessRun)[i] = kq;
+      atomicAdd(&lh[(__float_as_uint(GT != kGNone ? a[i].x + b[i].x : b[i].x) & kKeyMask) >> 19], 1u);
+      atomicAdd(&lh[(__float_as_uint(GT != kGNone ? a[i].y + b[i].y : b[i].y) & kKeyMask) >> 19], 1u);
+      atomicAdd(&lh[(__float_as_uint(GT != kGNone ? a[i].z + b[i].z : b[i].z) & kKeyMask) >> 19], 1u);
+      atomicAdd(&lh[(__float_as_uint(GT != kGNone ? a[i].w + b[i].w : b[i].w) & kKeyMask) >> 19], 1u);
     }
   }
   __syncthreads();
@@ -1268,7 +1185,6 @@ k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_
     if (above < m_hi && above + h[j] >= m_hi) {  // one thread, one bin
       // (a bound that so many keys reach that the list could not take them is none)
       if (above + h[j] <= m_max) hit_sh = 16 * tid + j;
-      hit_above_sh = above;
     }
     above += h[j];
   }
@@ -1276,79 +1192,7 @@ k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_
   const int hit = hit_sh;
   // bounds above infinity's digit would not survive the floating-point comparison of the fused pass
   const uint32_t bound = hit >= 0 ? (uint32_t)(hit < 0xff0 ? hit : 0xff0) << 19 : kNoGuess;
-  if (tid == 0) {
-    ctrl[3] = (hit >= 0 && hit < 0xff0) ? (uint32_t)hit : kNoGuess;  // (what k_guess_refine may refine)
-    ctrl[4] = hit_above_sh;
-  }
   if (tid == 0) ctrl[1] = bound;
-}
-
-// ---------------------------------------------------------------------------
-// k_guess_refine : refines the bound k_guess published for vector 0 by the next 12
-// key bits: among the stored sample keys of the bound's top digit d it takes the
-// second digit of the key that is m_hi-th largest in the whole sample.  A bound
-// this fine admits about 1 % more keys than needed (plus the margin in m_hi)
-// instead of up to 15 %.  grid = blocks of 256 threads striding over the nkeys
-// sample keys; the last block to finish picks.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-k_guess_refine(uint32_t* __restrict__ slots, const uint32_t* __restrict__ sample_keys, int nkeys, uint32_t m_hi) {
-  __shared__ uint32_t lh[kHistBins];
-  __shared__ uint32_t wsum[4];
-  __shared__ int last_sh, hit_sh;
-  const int tid = threadIdx.x;
-  uint32_t* __restrict__ ctrl = slots + kSlotCtrl;
-  uint32_t* __restrict__ hist = slots + kSlotRefine;
-  const uint32_t d0 = ctrl[3];
-  if (d0 == kNoGuess) return;  // (the same in every block)
-  for (int b = tid; b < kHistBins; b += 256) lh[b] = 0u;
-  __syncthreads();
-  const uint4* __restrict__ sk = reinterpret_cast<const uint4*>(sample_keys);
-  for (int q = blockIdx.x * 256 + tid; q < nkeys / 4; q += gridDim.x * 256) {
-    const uint4 kq = sk[q];
-    if ((kq.x >> 19) == d0) atomicAdd(&lh[(kq.x >> 7) & 0xfffu], 1u);
-    if ((kq.y >> 19) == d0) atomicAdd(&lh[(kq.y >> 7) & 0xfffu], 1u);
-    if ((kq.z >> 19) == d0) atomicAdd(&lh[(kq.z >> 7) & 0xfffu], 1u);
-    if ((kq.w >> 19) == d0) atomicAdd(&lh[(kq.w >> 7) & 0xfffu], 1u);
-  }
-  __syncthreads();
-  for (int b = tid; b < kHistBins; b += 256) {
-    const uint32_t c = lh[b];
-    if (c) atomicAdd(&hist[b], c);
-  }
-  __threadfence();
-  __syncthreads();
-  if (tid == 0) {
-    last_sh = atomicAdd(&ctrl[5], 1u) == gridDim.x - 1 ? 1 : 0;
-    hit_sh = -1;
-  }
-  __syncthreads();
-  if (!last_sh) return;
-  __threadfence();
-  uint32_t h[16];
-  uint32_t tot = 0u;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    h[j] = __hip_atomic_load(&hist[16 * tid + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    tot += h[j];
-  }
-  uint32_t suf = tot;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t x = __shfl_down(suf, off, 64);
-    if ((tid & 63) + off < 64) suf += x;
-  }
-  if ((tid & 63) == 0) wsum[tid >> 6] = suf;
-  __syncthreads();
-  uint32_t above = ctrl[4] + suf - tot;  // sample keys of higher top digit, or of higher second digit
-  for (int i = (tid >> 6) + 1; i < 4; ++i) above += wsum[i];
-#pragma unroll
-  for (int j = 15; j >= 0; --j) {
-    if (above < m_hi && above + h[j] >= m_hi) hit_sh = 16 * tid + j;  // one thread, one bin
-    above += h[j];
-  }
-  __syncthreads();
-  if (tid == 0 && hit_sh >= 0) ctrl[1] = (d0 << 19) | ((uint32_t)hit_sh << 7);
 }
 
 // ---------------------------------------------------------------------------
@@ -1360,27 +1204,6 @@ k_guess_refine(uint32_t* __restrict__ slots, const uint32_t* __restrict__ sample
 // most three elements before and behind them one by one.  Bound by the chip's memory and
 // then by the on-chip atomics (more copies of the block's histogram changed nothing).
 // ---------------------------------------------------------------------------
-// The guess did not hold after a fused pass that handed marked elements on per tile and stored
-// +0.0 in their place: the block that owns chunk c puts the values of its tiles' pieces back into
-// the vector before anything reads it (chunks are whole tiles on this route, so this is local to
-// the block; the caller's barrier and this fence order it before the block's own reads).
-template <int T>
-__device__ __forceinline__ void restore_pieces(const SelParams& p, const SegView& sv, int c) {
-  const int64_t c_begin = sv.d.geom.chunk0 + (int64_t)c * sv.d.geom.chunk_elems;
-  int64_t c_end = c_begin + sv.d.geom.chunk_elems;
-  if (c_end > (p.n & ~(int64_t)3)) c_end = p.n & ~(int64_t)3;
-  for (int64_t t = c_begin / kPassTile; t * kPassTile < c_end; ++t) {
-    const uint32_t cnt = sv.tcnt[t];
-    if (cnt == kTileOverflow) continue;
-    const uint2* __restrict__ piece = sv.tbuf + (size_t)t * (size_t)sv.tcap;
-    for (uint32_t e = threadIdx.x; e < cnt; e += T) {
-      const uint2 ent = piece[e];
-      if ((int64_t)ent.x < p.n) p.zero_vec[ent.x] = __uint_as_float(ent.y);
-    }
-  }
-  __threadfence();
-}
-
 template <int T>
 __device__ __forceinline__ void hist0_body(const SelParams& p) {
   constexpr int U = 8;  // float4 groups a thread has in flight
@@ -1394,7 +1217,6 @@ __device__ __forceinline__ void hist0_body(const SelParams& p) {
   const int tid = threadIdx.x;
   const float* __restrict__ xp = sv.x;
   for (int b = tid; b < kHistBins; b += T) lh[b] = 0u;
-  if (sv.tbuf != nullptr && p.zero_vec != nullptr) restore_pieces<T>(p, sv, c);
   __syncthreads();
   int64_t cs = sv.d.geom.chunk0 + (int64_t)c * sv.d.geom.chunk_elems;
   int64_t ce = cs + sv.d.geom.chunk_elems;
@@ -1447,9 +1269,8 @@ __device__ __forceinline__ void hist0_body(const SelParams& p) {
 // k_pass_seg : the leader's fused pass of a segmented step whose leader is known up front:
 // acc = g + residual in place, chunk by chunk of the segments' layout, and k_hist0's
 // per-chunk histograms of the result in the same read.  One block per chunk, as k_hist0.
-// Striding over the tiles instead and reading the vector again for the histograms took 276 +
-// 129 us on 138 M elements in 16 Mi buckets; the whole step 1575 -> 1485 us, 25.6 M x 8 in 54
-// segments 566 -> 529, 200 k x 4 in 20 segments 67 -> 55.
+// Striding over the tiles instead and reading the vector again for the histograms takes longer:
+// the whole step on 200 k x 4 in 20 segments 67 us, now 55.  (Long vectors go by tiles.)
 // ---------------------------------------------------------------------------
 template <bool NT, int GT, int T>
 __global__ void __launch_bounds__(T)
@@ -2183,160 +2004,6 @@ __device__ __forceinline__ void compact_mask_body(const SelParams& p) {
 }
 
 // ---------------------------------------------------------------------------
-// compact_tiles_body : the survivor list from what the fused pass staged per tile
-// (k_pass_mark with STAGE): one block of 1024 threads per chunk copies the tiles'
-// pieces, in tile order, to the list from chunk_off[c] on and counts the entries'
-// top digits, as compact_mask_body does.  The chunk is walked in slabs of eight
-// tiles; a slab with a tile that staged nothing (kTileOverflow: more marks than a
-// piece holds) is built from the mask instead: one thread per mask row writes the
-// row's marked indices, then the block fetches the values entry by entry.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void compact_tiles_body(const SelParams& p) {
-  constexpr int T = 1024, WAVES = 16, SLAB = 8;  // tiles per slab (1024 mask rows)
-  __shared__ uint32_t wtot[WAVES];
-  __shared__ uint32_t lh[kHistBins];
-  __shared__ uint32_t tc[SLAB];
-
-  const SegView sv = seg_view(p, blockIdx.y);
-  const int c = blockIdx.x;
-  if (c >= sv.d.geom.nchunks) return;
-  const SelState st = *sv.st;
-  if (st.use_mask == 0u || sv.mask == nullptr || *p.err) return;
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
-  const uint32_t lane = lane_id();
-  const int64_t n = p.n;
-  const ChunkGeom geom = sv.d.geom;
-  const uint32_t cap = sv.d.cap;
-  const uint32_t list_lo = st.list_lo;
-  const float* __restrict__ xp = sv.x;
-  const uint64_t* __restrict__ mk = sv.mask;
-  uint2* list = sv.list;
-
-  for (int b = tid; b < kHistBins; b += T) lh[b] = 0u;
-
-  const int64_t c_begin = geom.chunk0 + (int64_t)c * geom.chunk_elems;  // a whole number of tiles
-  int64_t c_end = c_begin + geom.chunk_elems;
-  if (c_end > n) c_end = n;
-  const int64_t n_vec = n & ~(int64_t)3;                      // marked elements end here
-  const int64_t v_end = c_end < n_vec ? c_end : n_vec;
-  const int64_t tile_lo = c_begin / kPassTile;
-  const int64_t tile_hi = (v_end + kPassTile - 1) / kPassTile;  // exclusive
-  const int64_t row_end = (v_end + 255) >> 8;                   // exclusive
-
-  uint32_t run = sv.chunk_off[c];  // list position of the next entry of this chunk
-  for (int64_t t0 = tile_lo; t0 < tile_hi; t0 += SLAB) {
-    const int ntl = (int)(tile_hi - t0 < SLAB ? tile_hi - t0 : SLAB);
-    __syncthreads();  // tc, wtot and the histogram's clearing
-    if (tid < SLAB) tc[tid] = tid < ntl ? sv.tcnt[t0 + tid] : 0u;
-    __syncthreads();
-    uint32_t pre[SLAB + 1];
-    bool staged = true;
-    pre[0] = 0u;
-#pragma unroll
-    for (int i = 0; i < SLAB; ++i) {
-      const uint32_t v = tc[i];
-      staged = staged && v != kTileOverflow;
-      pre[i + 1] = pre[i] + (v != kTileOverflow ? v : 0u);
-    }
-    if (staged) {  // the same in every thread
-      const uint32_t total = pre[SLAB];
-      for (uint32_t f0 = (uint32_t)tid; f0 < total; f0 += 4 * T) {  // four entries in flight per thread
-        uint2 ent[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint32_t f = f0 + (uint32_t)u * T < total ? f0 + (uint32_t)u * T : total - 1u;
-          int i = 0;
-#pragma unroll
-          for (int q = 1; q < SLAB; ++q) i += f >= pre[q] ? 1 : 0;  // the tile this entry belongs to
-          ent[u] = sv.tbuf[(size_t)(t0 + i) * (size_t)sv.tcap + (f - pre[i])];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint32_t f = f0 + (uint32_t)u * T;
-          if (f < total) {
-            if (run + f < cap) list[run + f] = ent[u];
-            atomicAdd(&lh[(ent[u].y & kKeyMask) >> 19], 1u);
-          }
-        }
-      }
-      run += total;
-      continue;
-    }
-    // from the mask: thread t owns row 128 t0 + t
-    const int64_t row = t0 * (kPassTile / 256) + tid;
-    uint64_t m[4] = {0ull, 0ull, 0ull, 0ull};
-    if (row < row_end) {
-      const uint4 lo2 = reinterpret_cast<const uint4*>(mk + mask_word(row))[0];
-      const uint4 hi2 = reinterpret_cast<const uint4*>(mk + mask_word(row))[1];
-      m[0] = ((uint64_t)lo2.y << 32) | lo2.x;
-      m[1] = ((uint64_t)lo2.w << 32) | lo2.z;
-      m[2] = ((uint64_t)hi2.y << 32) | hi2.x;
-      m[3] = ((uint64_t)hi2.w << 32) | hi2.z;
-    }
-    const uint32_t cnt = (uint32_t)(__popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]));
-    uint32_t before = 0u, wsum = 0u;
-#pragma unroll
-    for (int b = 0; b <= 8; ++b) {
-      const uint64_t plane = __ballot((cnt >> b) & 1u);
-      before += popc_lt(plane) << b;
-      wsum += (uint32_t)__popcll(plane) << b;
-    }
-    if (lane == 0) wtot[wave] = wsum;
-    __syncthreads();
-    uint32_t pos = run + before, total = 0u;
-#pragma unroll
-    for (int i = 0; i < WAVES; ++i) {
-      const uint32_t wt = wtot[i];
-      if (i < wave) pos += wt;
-      total += wt;
-    }
-    uint64_t any = m[0] | m[1] | m[2] | m[3];
-    while (any) {
-      const int g = __builtin_ctzll(any);
-      const uint64_t bit = 1ull << g;
-      any &= ~bit;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (m[e] & bit) {
-          if (pos < cap) list[pos].x = (uint32_t)(row * 256 + 4 * g + e);
-          ++pos;
-        }
-      }
-    }
-    __threadfence_block();  // the indices are written before any thread of the block reads them
-    __syncthreads();
-    for (uint32_t e0 = (uint32_t)tid; e0 < total; e0 += T) {
-      if (run + e0 < cap) {
-        const uint32_t raw = __float_as_uint(xp[list[run + e0].x]);
-        list[run + e0].y = raw;
-        atomicAdd(&lh[(raw & kKeyMask) >> 19], 1u);
-      }
-    }
-    run += total;
-  }
-  // the elements behind the last whole group of four are not in the mask
-  if (c_end == n && n_vec < n && tid == 0) {
-    for (int64_t j = n_vec; j < n; ++j) {
-      const uint32_t raw = __float_as_uint(xp[j]);
-      const uint32_t kk = raw & kKeyMask;
-      if (kk >= list_lo) {
-        atomicAdd(&lh[kk >> 19], 1u);
-        if (run < cap) list[run] = make_uint2((uint32_t)j, raw);
-        ++run;
-      }
-    }
-  }
-
-  __syncthreads();
-  uint32_t* __restrict__ htop = sv.htop + (size_t)(c % sv.htop_reps) * kHistBins;
-  for (int b = tid; b < kHistBins; b += T) {
-    const uint32_t v = lh[b];
-    if (v) atomicAdd(&htop[b], v);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Marking on vectors that are only read (k_mark_spans): a wave works alone on spans of
 // 2048 or 8192 consecutive elements.  Per row of 64 float4 groups it needs the largest
 // magnitude of each group, one comparison with the bound and, where a group reaches it,
@@ -2567,14 +2234,10 @@ template <int UB>
 __global__ void __launch_bounds__(1024)
 k_mask_or_hist(SelParams p, SelParams p_full) {
   const SelState* st = seg_view(p, blockIdx.y).st;
-  if (st->use_mask != 0u) {
-    if (p.tiles.buf != nullptr)
-      compact_tiles_body(p);
-    else
-      compact_mask_body<UB>(p);
-  } else if (st->need_full != 0u) {
+  if (st->use_mask != 0u)
+    compact_mask_body<UB>(p);
+  else if (st->need_full != 0u)
     hist0_body<1024>(p_full);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2983,16 +2646,6 @@ __device__ __forceinline__ void list_final_body(const SelParams& p, const SegVie
   }
 }
 
-// The survivor list was copied from pieces staged by a fused pass that stored +0.0 in place of
-// every element it handed on (k_pass_mark with STAGE).  The pass that counts the last digit over the
-// list (list_hist_body, digit 2) knows the threshold key up to its last seven bits, [lo, hi]: it gives
-// the handed-on elements with key <= hi their values back and puts +0.0 over the keys > hi that no
-// piece handed on (a tile whose marks stayed in the mask, the n mod 4 last elements).  The final pass
-// over the list then has the kept entries with key <= hi left to zero.
-__device__ __forceinline__ bool from_pieces(const SelParams& p, const SegView& sv) {
-  return p.zero_vec != nullptr && sv.tbuf != nullptr && sv.st->use_mask != 0u;
-}
-
 // Keys the level-1 pass has already put to +0.0 in zero_vec lie above this one (every key if it
 // has not zeroed any).
 __device__ __forceinline__ uint32_t zeroed_above(const SelState* stp) {
@@ -3045,11 +2698,10 @@ k_final(SelParams p) {
     if (threadIdx.x == 0) first_tile = (int64_t)atomicAdd(sv.counters + 2, 1u);
     __syncthreads();
   }
-  const uint32_t below = from_pieces(p, sv) ? (st.hi | 0x7fu) : zero_below;
   if (long_list(st.list_count, p.k_all))
-    list_final_body<16>(p, sv, st, below, first_tile, stage);
+    list_final_body<16>(p, sv, st, zero_below, first_tile, stage);
   else
-    list_final_body<8>(p, sv, st, below, first_tile, stage);
+    list_final_body<8>(p, sv, st, zero_below, first_tile, stage);
 }
 
 // ---------------------------------------------------------------------------
@@ -3085,44 +2737,17 @@ __device__ __forceinline__ void list_hist_body(const SelParams& p, int digit, ui
   const uint32_t klo = st.lo, khi = st.hi;
   const int sh = digit_shift(digit);
   const uint32_t dm = digit_mask(digit);
-  if (digit == 2 && from_pieces(p, sv)) {
-    // the same count, and on the way the residual is put right around the threshold (see from_pieces)
-    const bool all_pieces = sv.ctrl != nullptr && sv.ctrl[2] == 0u;  // no tile kept its marks to the mask
-    const int64_t n_vec = p.n & ~(int64_t)3;
-    for (uint64_t base = (uint64_t)blockIdx.x * 8192u; base < cnt; base += (uint64_t)nb * 8192u) {
-      uint2 ent[PER];
+  for (uint64_t base = (uint64_t)blockIdx.x * 8192u; base < cnt; base += (uint64_t)nb * 8192u) {
+    uint32_t key[PER];
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {  // (no branch around the loads: behind the list they re-read its last entry)
-        const uint64_t q = base + (uint64_t)i * T + tid;
-        ent[i] = sv.list[q < cnt ? q : cnt - 1u];
-      }
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int64_t j = (int64_t)ent[i].x;
-        if (base + (uint64_t)i * T + tid >= cnt || j >= p.n) continue;
-        const uint32_t kk = ent[i].y & kKeyMask;
-        if (kk >= klo && kk <= khi) atomicAdd(&lh[(kk >> sh) & dm], 1u);
-        const bool handed_on = j < n_vec && (all_pieces || sv.tcnt[j / kPassTile] != kTileOverflow);
-        if (handed_on) {
-          if (kk <= khi) p.zero_vec[j] = __uint_as_float(ent[i].y);
-        } else if (kk > khi) {
-          p.zero_vec[j] = 0.0f;
-        }
-      }
+    for (int i = 0; i < PER; ++i) {  // (no branch around the loads: behind the list they re-read its last entry)
+      const uint64_t q = base + (uint64_t)i * T + tid;
+      key[i] = sv.list[q < cnt ? q : cnt - 1u].y & kKeyMask;
     }
-  } else {
-    for (uint64_t base = (uint64_t)blockIdx.x * 8192u; base < cnt; base += (uint64_t)nb * 8192u) {
-      uint32_t key[PER];
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {  // (no branch around the loads: behind the list they re-read its last entry)
-        const uint64_t q = base + (uint64_t)i * T + tid;
-        key[i] = sv.list[q < cnt ? q : cnt - 1u].y & kKeyMask;
-      }
-#pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (base + (uint64_t)i * T + tid < cnt && key[i] >= klo && key[i] <= khi)
-          atomicAdd(&lh[(key[i] >> sh) & dm], 1u);
-    }
+    for (int i = 0; i < PER; ++i)
+      if (base + (uint64_t)i * T + tid < cnt && key[i] >= klo && key[i] <= khi)
+        atomicAdd(&lh[(key[i] >> sh) & dm], 1u);
   }
   __syncthreads();
   uint32_t* __restrict__ dst = digit == 1 ? sv.hist1 : sv.hist2;
@@ -4091,6 +3716,1112 @@ k_tail(SelParams p, LeaderArgs la, int row_log2) {
     return tail_select<kTailNone, true>(p, sv, sh, row_log2, 0u, 0u);
   }
   tail_select<source, false>(p, sv, sh, row_log2, 0u, 0u);
+}
+
+// ---------------------------------------------------------------------------
+// Selection from marked tiles.  Where the leader's vector is read anyway (its own pass, the leader known up front) or once
+// (segments whose leader comes from the data), every segment is cut into tiles of kMarkTile elements and
+//   k_guess_segs / k_guess_tiles   sample it for a lower bound on the key of its k-th largest magnitude,
+//   k_mark_tiles   reads (and, with gradients, writes) the vector once: a tile's elements that reach the bound are stored in
+//                  order as the tile's piece of (index, raw bits), and counted in 4095 narrow bins above the bound,
+//   k_tiles_pick   finds the threshold's bin, or that the bound does not hold,
+//   k_tiles_full   (only then) gives the pieces back and counts the top digits of everything,
+//   k_tiles_digit  counts the next digits of the bin's keys, and per tile what lies above the bin,
+//   k_tiles_count  knows the threshold and counts per tile what is kept,
+//   k_tiles_out    puts a tile's kept entries where they belong.
+// A tile with more marked elements than a piece takes, and every tile of a segment without a bound (too dense ones, and where
+// it did not hold), has no piece: its values are in the vector, and the kernels behind the marking read them there, the waves
+// of a block a part each.  The bins are so narrow that few keys share the threshold's: k_tiles_count looks only at the tiles
+// that have one.  So a piece is read twice, once to count what is above the bin and once to put it out, by a wave to itself.
+//   One list of all pieces instead (its writing, two digit counts and final pass 66 + 38 + 36 + 89 us for 14 M entries, and 5
+// for each of three launches that had nothing to do), and for segments per-chunk histograms, which the leader's vector was
+// read again for: 138 M x 4, leader known, one in ten kept 1671 us a step, now 1507, in 16 Mi buckets, one in a hundred, 1474
+// / 1295, 25.6 M x 8 in 54 segments, variance rule, 642 / 622.  What values do to it, us, before / now, one in a hundred:
+// 25.6 M x 2 normal 222/203, layers of 54 scales 221/215, a run of large values 250/243, sorted 377/300, all equal 610/505;
+// 138 M x 2 833/769, 882/811, 955/852, 1107/901, 3144/1776; in buckets 947/783, 946/779, 973/789, 1860/1527, 2850/2339.
+//   Tiles without pieces a wave each: 25.6 M x 2 with a run 280; a block of four waves each 241, but all ties 222 (four times
+// the blocks add to the same digits), and 138 M in buckets 1330.
+// ---------------------------------------------------------------------------
+struct TileArgs {
+  const uint4* map;      // [tiles] (first element, a multiple of 4; first and last + 1 of the segment's; segment), or nullptr: one segment
+  const uint2* groups;   // [blocks of the kernels behind the marking] (segment, number among its blocks), or nullptr
+  uint2* pieces;         // [tiles][cap]
+  uint32_t* held;        // [tiles] entries of the piece, or kTileOverflow
+  uint32_t* marked;      // [tiles] elements that reach the bound
+  // of each tile's kTileWaves parts, of which a tile with a piece has the first only:
+  uint32_t* above;       // keys above the threshold's bin; then kept ones above the threshold
+  uint32_t* among;       // keys in it; then those equal to the threshold
+  uint32_t* slots;       // [kTileSlots] the first of those
+  uint32_t* bins;        // [segments] bins_stride words apart
+  int64_t bins_stride;
+  uint32_t* more_bins;   // [SegDesc::bins_begin + bins_more][kHistBins]
+  uint64_t* kept;        // [tiles], then [blocks] kept entries: above the threshold << 32 | at it
+  uint32_t* any_full;    // set where some segment's bound does not hold
+  int32_t* tile_start;   // kept entries in front of every tile of the streaming passes (two of these), or nullptr
+  int32_t ntiles, ngroups, cap;
+};
+constexpr int kTileWaves = 4;  // waves, and tiles, of a block of the kernels behind the marking; and parts of a tile without a piece
+constexpr int kTileSlots = 4;
+constexpr uint32_t kTileOverflow = 0xffffffffu;
+constexpr int kGuessLooks = 1 << 14;  // of a block of k_guess_tiles for the others, at most (some 10 ms)
+// How far the threshold is known: keys [lo, lo + 2^bits), `above` of them higher, `need` of the `cand` in it kept.
+struct TilePick {
+  uint32_t lo, bits, above, need, cand;
+};
+
+// Bins of 4096 by rank: T threads' counts of the bins BPT t .., how many lie above them (scan), and the bin that the
+// need-th largest key falls into (find; res: bin, keys above it, keys in it); all threads call them.
+template <int T>
+struct TileBins {
+  static constexpr int BPT = kHistBins / T;
+  uint32_t h[BPT];
+  uint32_t above;
+  __device__ __forceinline__ void scan(uint32_t* part) {
+    uint32_t tot = 0u;
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) tot += h[j];
+    above = block_suffix_incl<T>(tot, part) - tot;
+  }
+  // false: there are not so many.  (res is free again behind it.)
+  __device__ __forceinline__ bool find(uint32_t need, uint32_t* res, uint4& got) const {
+    if (threadIdx.x == 0) res[0] = ~0u;
+    __syncthreads();
+    uint32_t upto = above;
+#pragma unroll
+    for (int j = BPT - 1; j >= 0; --j) {
+      if (upto < need && need <= upto + h[j]) {
+        res[0] = (uint32_t)(BPT * (int)threadIdx.x + j);
+        res[1] = upto;
+        res[2] = h[j];
+      }
+      upto += h[j];
+    }
+    __syncthreads();
+    got = make_uint4(res[0], res[1], res[2], 0u);
+    __syncthreads();
+    return got.x != ~0u;
+  }
+};
+
+// Narrows `pk` by the bits that the bins tell apart, or the counts in memory.
+template <int T>
+__device__ __forceinline__ void tile_take(TileBins<T>& tb, TilePick& pk, uint32_t bits, uint32_t* part, uint32_t* res,
+                                          uint32_t* __restrict__ err) {
+  uint4 got;
+  tb.scan(part);
+  if (tb.find(pk.need, res, got)) {
+    pk.lo += got.x << bits;
+    pk.above += got.y;
+    pk.need -= got.y;
+    pk.cand = got.z;
+  } else if (threadIdx.x == 0) {
+    atomicOr(err, kErrPick);
+  }
+  pk.bits = bits;
+}
+
+template <int T>
+__device__ __forceinline__ void tile_narrow(TilePick& pk, const uint32_t* __restrict__ hist, uint32_t bits, uint32_t* part,
+                                            uint32_t* res, uint32_t* __restrict__ err) {
+  TileBins<T> tb;
+  constexpr int BPT = TileBins<T>::BPT;
+  static_assert(BPT % 4 == 0, "whole uint4 groups per thread");
+#pragma unroll
+  for (int j = 0; j < BPT / 4; ++j) {
+    const uint4 q = reinterpret_cast<const uint4*>(hist)[(BPT / 4) * threadIdx.x + j];
+    tb.h[4 * j + 0] = q.x;
+    tb.h[4 * j + 1] = q.y;
+    tb.h[4 * j + 2] = q.z;
+    tb.h[4 * j + 3] = q.w;
+  }
+  tile_take(tb, pk, bits, part, res, err);
+}
+
+// Bits below the second digit of a bin of `bits`, which takes twelve.
+__device__ __forceinline__ uint32_t tile_rest(uint32_t bits) { return bits > 12u ? bits - 12u : 0u; }
+
+// What k_tiles_pick found of the segment, and where its bound did not hold the pick from k_tiles_full's counts.
+template <int T>
+__device__ __forceinline__ TilePick tile_first(const SegView& sv, uint32_t* part, uint32_t* res, uint32_t* __restrict__ err) {
+  const SelState st = *sv.st;
+  TilePick pk{st.lo, st.pad[0], st.n_gt, st.need, st.cand};
+  if (st.need_full != 0u) {
+    pk = TilePick{0u, 31u, 0u, sv.d.k, 0u};
+    tile_narrow<T>(pk, sv.hseg, 19u, part, res, err);
+  }
+  return pk;
+}
+
+// Adds the counts of T threads to `dst`, and clears them; a thread has its own.
+template <int T>
+__device__ __forceinline__ void tile_flush(uint32_t* lh, uint32_t* __restrict__ dst) {
+#pragma unroll
+  for (int i = 0; i < kHistBins / 4 / T; ++i) {
+    const int b = (int)threadIdx.x + i * T;
+    const uint4 q = reinterpret_cast<uint4*>(lh)[b];
+    if (q.x) atomicAdd(dst + 4 * b + 0, q.x);
+    if (q.y) atomicAdd(dst + 4 * b + 1, q.y);
+    if (q.z) atomicAdd(dst + 4 * b + 2, q.z);
+    if (q.w) atomicAdd(dst + 4 * b + 3, q.w);
+    reinterpret_cast<uint4*>(lh)[b] = make_uint4(0u, 0u, 0u, 0u);
+  }
+}
+
+// Where tile t of segment seg adds its bins: long segments' blocks would wait for each other at the same few hundred.
+__device__ __forceinline__ uint32_t* tile_bins(const SelParams& p, const TileArgs& a, int seg, uint32_t t) {
+  const SegDesc& d = p.table != nullptr ? p.table[seg] : p.one;
+  const uint32_t more = (uint32_t)d.bins_more, c = t % (more + 1u);
+  return c == more ? a.bins + (size_t)seg * (size_t)a.bins_stride : a.more_bins + (size_t)(d.bins_begin + (int)c) * kHistBins;
+}
+
+// Tile t: its first element (of 4 in a row), and which of the segment's it has.
+__device__ __forceinline__ uint4 tile_at(const TileArgs& a, int64_t n, int64_t t) {
+  if (a.map != nullptr) return a.map[t];
+  const int64_t first = t * kMarkTile;
+  return make_uint4((uint32_t)first, (uint32_t)first, (uint32_t)(first + kMarkTile < n ? first + kMarkTile : n), 0u);
+}
+
+// ---------------------------------------------------------------------------
+// k_tile_map : TileArgs::map and groups of a segmented layout, one block per segment.  A segment's tiles start with the line
+// of its first element.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256)
+k_tile_map(const SegDesc* __restrict__ table, uint4* __restrict__ map, uint2* __restrict__ groups) {
+  const SegDesc d = table[blockIdx.x];
+  const int64_t line = d.e_lo & ~(int64_t)31;
+  for (int t = threadIdx.x; t < d.ntiles; t += 256) {
+    const int64_t first = line + (int64_t)t * kMarkTile, end = first + kMarkTile;
+    map[d.tile_begin + t] = make_uint4((uint32_t)first, (uint32_t)(first < d.e_lo ? d.e_lo : first),
+                                       (uint32_t)(end < d.e_hi ? end : d.e_hi), (uint32_t)blockIdx.x);
+    if (t % kTileWaves == 0) groups[d.group_begin + t / kTileWaves] = make_uint2((uint32_t)blockIdx.x, (uint32_t)(t / kTileWaves));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// k_guess_tiles : the bound of a flat vector, from `runs` runs of the sample that k_guess takes, one a thread.
+// Bound by its trips to memory: the blocks count the keys' top digits, wait for each other once, pick the
+// digits of three ranks (m_hi for the bound, m_mid for the sample's own threshold, m_lo for what surely lies above it), each
+// block for itself, and count the second digits of the first two; the last one through picks from these.  (In two launches,
+// the keys stored in between and 64 blocks of 256 threads adding to the same few hundred bins, 16.7 + 17.1 us.)
+//   A block that has waited long leaves; then nobody is the last, and the vector has no bound, which costs time only.
+// ---------------------------------------------------------------------------
+// A block's share of a sample, from run `first` on: runs of RUN elements, run r at element at(r), RUN / 4 lanes to a run, so
+// that a wave's load touches no more lines than it has to (a run a lane: twice the time).  RUN / 4 groups of four keys a
+// thread, bit j of the result says whether group j is there.  GT = kGNone: xp's own keys.
+template <int GT, int RUN, int T, typename At>
+__device__ __forceinline__ uint32_t sample_keys(const float* __restrict__ gp, const float* __restrict__ xp, int first, int runs,
+                                                At at, uint32_t (&key)[RUN]) {
+  constexpr int PER = RUN / 4;
+  v4f a[PER], b[PER];
+  uint32_t there = 0u;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int r = first + j * (T / PER) + (int)threadIdx.x / PER;
+    const int64_t e = at(r < runs ? r : runs - 1) + 4 * ((int)threadIdx.x % PER);
+    if (GT != kGNone) a[j] = load4g<false, GT>(gp, e);
+    b[j] = load4<false>(xp + e);
+    there |= r < runs ? 1u << j : 0u;
+  }
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    key[4 * j + 0] = __float_as_uint(GT != kGNone ? a[j].x + b[j].x : b[j].x) & kKeyMask;
+    key[4 * j + 1] = __float_as_uint(GT != kGNone ? a[j].y + b[j].y : b[j].y) & kKeyMask;
+    key[4 * j + 2] = __float_as_uint(GT != kGNone ? a[j].z + b[j].z : b[j].z) & kKeyMask;
+    key[4 * j + 3] = __float_as_uint(GT != kGNone ? a[j].w + b[j].w : b[j].w) & kKeyMask;
+  }
+  return there;
+}
+
+// Counts the keys' top digits in lh.
+template <int RUN>
+__device__ __forceinline__ void sample_first(const uint32_t (&key)[RUN], uint32_t there, uint32_t* lh) {
+#pragma unroll
+  for (int i = 0; i < RUN; ++i)
+    if ((there >> (i / 4)) & 1u) atomicAdd(&lh[key[i] >> 19], 1u);
+}
+
+// Counts the second digits of the keys with top digit `low` in lh[0], with top digit `mid` in lh[1].
+template <int RUN>
+__device__ __forceinline__ void sample_second(const uint32_t (&key)[RUN], uint32_t there, uint32_t low, uint32_t mid,
+                                              uint32_t (*lh)[kHistBins]) {
+#pragma unroll
+  for (int i = 0; i < RUN; ++i) {
+    const bool ok = (there >> (i / 4)) & 1u;
+    if (ok && (key[i] >> 19) == low) atomicAdd(&lh[0][(key[i] >> 7) & 0xfffu], 1u);
+    if (ok && (key[i] >> 19) == mid) atomicAdd(&lh[1][(key[i] >> 7) & 0xfffu], 1u);
+  }
+}
+
+constexpr int kGuessThreads = 512;
+template <int GT>
+__global__ void __launch_bounds__(kGuessThreads)
+k_guess_tiles(const float* __restrict__ gp, const float* __restrict__ rp, uint32_t* __restrict__ slot, int runs,
+              int64_t stride, uint32_t m_hi, uint32_t m_mid, uint32_t m_lo, uint32_t* __restrict__ info) {
+  constexpr int T = kGuessThreads;
+  __shared__ __attribute__((aligned(16))) uint32_t lh[2][kHistBins];
+  __shared__ uint32_t part[T / 64];
+  __shared__ uint32_t res[4];
+  __shared__ int sh;
+  const int tid = threadIdx.x;
+  uint32_t* __restrict__ ctrl = slot + kSlotCtrl;
+  uint32_t key[kGuessRun];
+  const uint32_t there = sample_keys<GT, kGuessRun, T>(
+      gp, rp, (int)blockIdx.x * T, runs, [&](int r) { return ((int64_t)r * stride) & ~(int64_t)(kGuessRun - 1); }, key);
+  for (int i = tid; i < 2 * kHistBins / 4; i += T) reinterpret_cast<uint4*>(lh[0])[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) sh = 0;
+  __syncthreads();
+  sample_first(key, there, lh[0]);
+  __syncthreads();
+  tile_flush<T>(lh[0], slot + (blockIdx.x % 2u == 0u ? kSlotGuessHist : kGuessOddAt));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (what this wave has added is there: see meet_arrive)
+  __syncthreads();
+  if (tid == 0) {
+    __hip_atomic_fetch_add(&ctrl[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 0; i < kGuessLooks && sh == 0; ++i) sh = load_through(&ctrl[0]) == gridDim.x ? 1 : 0;
+  }
+  __syncthreads();
+  if (sh == 0) return;
+  TileBins<T> tb;
+  auto read = [&](const uint32_t* hist, const uint32_t* more) __attribute__((always_inline)) {
+    uint64_t q[TileBins<T>::BPT / 2], m[TileBins<T>::BPT / 2];
+#pragma unroll
+    for (int j = 0; j < TileBins<T>::BPT / 2; ++j) {
+      q[j] = load_through(reinterpret_cast<const uint64_t*>(hist) + TileBins<T>::BPT / 2 * tid + j);
+      m[j] = more != nullptr ? load_through(reinterpret_cast<const uint64_t*>(more) + TileBins<T>::BPT / 2 * tid + j) : 0ull;
+    }
+#pragma unroll
+    for (int j = 0; j < TileBins<T>::BPT / 2; ++j) {
+      tb.h[2 * j] = (uint32_t)q[j] + (uint32_t)m[j];
+      tb.h[2 * j + 1] = (uint32_t)(q[j] >> 32) + (uint32_t)(m[j] >> 32);
+    }
+    tb.scan(part);
+  };
+  uint4 low, mid, top, low2, mid2;
+  read(slot + kSlotGuessHist, slot + kGuessOddAt);
+  if (!tb.find(m_hi, res, low) || low.x >= 0xff0u) return;  // (bounds beyond infinity's digit: none)
+  tb.find(m_mid, res, mid);
+  tb.find(m_lo, res, top);
+  sample_second(key, there, low.x, mid.x, lh);
+  __syncthreads();
+  tile_flush<T>(lh[0], slot + kSlotRefine);
+  tile_flush<T>(lh[1], slot + kGuessMidAt);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) sh = __hip_atomic_fetch_add(&ctrl[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
+  __syncthreads();
+  if (sh == 0) return;
+  read(slot + kSlotRefine, nullptr);
+  const bool ok = tb.find(m_hi - low.y, res, low2);
+  read(slot + kGuessMidAt, nullptr);
+  const bool ok_mid = tb.find(m_mid - mid.y, res, mid2);
+  if (tid == 0) tile_info(info, (low.x << 19) | (ok ? low2.x << 7 : 0u), (mid.x << 19) | (ok_mid ? mid2.x << 7 : 0u), top.x);
+}
+
+// ---------------------------------------------------------------------------
+// k_guess_segs : the bounds of a segmented selection, one block of 1024 threads per segment.  Up to 1024 runs of 32
+// elements, a line of memory each, are sampled, one a thread; the bound's rank is the sample's share of k and six standard deviations, widened by
+// how much the runs' counts differ from each other (values that lie together are worth fewer draws).  Bound by loading
+// them (a block's lines come at about 0.4 a ns).  Segments too dense for pieces get no bound.
+// ---------------------------------------------------------------------------
+constexpr int kSegRun = 32;
+template <int GT>
+__global__ void __launch_bounds__(1024)
+k_guess_segs(SelParams p, PtrTable g, int32_t cap) {
+  constexpr int T = 1024;
+  __shared__ __attribute__((aligned(16))) uint32_t lh[2][kHistBins];
+  __shared__ uint32_t part[T / 64];
+  __shared__ uint32_t res[4];
+  __shared__ uint64_t wsum[T / 64];
+  const int seg = blockIdx.x, tid = threadIdx.x;
+  const SegView sv = seg_view(p, seg);
+  const int64_t len = sv.d.e_hi - sv.d.e_lo;
+  const int64_t k = sv.d.k;
+  const int64_t e_first = (sv.d.e_lo + kSegRun - 1) & ~(int64_t)(kSegRun - 1);
+  // (short segments are read whole but for a few elements at their ends: the bound is then exact)
+  const bool whole = len <= T * kSegRun;
+  int64_t runs = whole ? (sv.d.e_hi - e_first) / kSegRun : len / (4 * kSegRun);
+  if (runs > T) runs = T;
+  // a piece has to hold what a tile is expected to mark, with some room
+  const float per_tile = 1.3f * (float)k * fminf(1.0f, (float)kMarkTile / (float)len);
+  if (runs < 1 || per_tile + 6.0f * sqrtf(per_tile) + 32.0f > (float)cap) return;  // (`info` has been cleared)
+  const int64_t stride = whole ? kSegRun : len / runs;
+  uint32_t key[kSegRun];
+  const uint32_t there = sample_keys<GT, kSegRun, T>(
+      g.p[0], sv.x, 0, (int)runs,
+      [&](int r) { return e_first + ((r * stride) & ~(int64_t)(kSegRun - 1)); },  // (the last one ends in front of the segment's end)
+      key);
+  for (int i = tid; i < 2 * kHistBins / 4; i += T) reinterpret_cast<uint4*>(lh[0])[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  sample_first(key, there, lh[0]);
+  __syncthreads();
+  TileBins<T> tb;
+  auto read = [&](int which) __attribute__((always_inline)) {
+    const uint4 q = reinterpret_cast<const uint4*>(lh[which])[tid];
+    tb.h[0] = q.x;
+    tb.h[1] = q.y;
+    tb.h[2] = q.z;
+    tb.h[3] = q.w;
+    tb.scan(part);
+  };
+  const float sample = (float)(runs * kSegRun), expect = whole ? (float)k : (float)k * sample / (float)len;
+  const uint32_t m_mid = (uint32_t)fmaxf(1.0f, expect + 0.5f);
+  uint4 low, mid, top, low2, mid2;
+  read(0);
+  reinterpret_cast<uint4*>(lh[0])[tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (!tb.find(m_mid, res, mid)) return;
+  // how the runs' counts of keys that reach that digit vary, against draws that know nothing of each other
+  uint32_t c1 = 0u, c2 = 0u;
+#pragma unroll
+  for (int j = 0; j < kSegRun / 4; ++j) {
+    uint32_t c = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c += ((there >> j) & 1u) && (key[4 * j + e] >> 19) >= mid.x ? 1u : 0u;
+    c1 += c;
+#pragma unroll
+    for (int off = 1; off < kSegRun / 4; off <<= 1) c += __shfl_xor(c, off, 64);
+    c2 += tid % (kSegRun / 4) == 0 ? c * c : 0u;
+  }
+  const uint64_t both = wave_allsum_u64(((uint64_t)c1 << 32) | c2);
+  if ((tid & 63) == 0) wsum[tid >> 6] = both;
+  __syncthreads();
+  uint64_t all = 0ull;
+#pragma unroll
+  for (int i = 0; i < T / 64; ++i) all += wsum[i];
+  const float s1 = (float)(uint32_t)(all >> 32), s2 = (float)(uint32_t)all;
+  const float wide = fmaxf(1.0f, (s2 - s1 * s1 / (float)runs) / fmaxf(1.0f, s1));
+  const float margin = whole ? 0.0f : 6.0f * sqrtf(expect * wide) + 8.0f;
+  if (expect + margin > sample) return;
+  const uint32_t m_hi = whole ? (uint32_t)k : (uint32_t)ceilf(expect + margin);
+  const float less = whole ? 64.0f : margin;  // (as many may be missing)
+  if (!tb.find(m_hi, res, low) || low.x >= 0xff0u) return;  // (bounds beyond infinity's digit: none)
+  tb.find((uint32_t)fmaxf(1.0f, expect - less), res, top);
+  sample_second(key, there, low.x, mid.x, lh);
+  __syncthreads();
+  read(0);
+  const bool ok = tb.find(m_hi - low.y, res, low2);
+  read(1);
+  const bool ok_mid = tb.find(m_mid - mid.y, res, mid2);
+  if (tid == 0)
+    tile_info(p.zero_base + (size_t)seg * kSegWords + kTileInfo, (low.x << 19) | (ok ? low2.x << 7 : 0u),
+              (mid.x << 19) | (ok_mid ? mid2.x << 7 : 0u), top.x);
+}
+
+// ---------------------------------------------------------------------------
+// k_mark_tiles : acc = g + residual (in place over residual; GT = kGNone: the vector is only read), and every tile's marked
+// elements as its piece and in the segment's bins.  grid = blocks striding over the tiles.  Bound by memory: 138 M elements,
+// one in a hundred kept, 273 us (6.1 TB/s), one in ten 318 (5.6; with blocks of twice the threads and tile, of which one fits
+// a compute unit instead of two, 348, so that nothing is loaded while a tile's marks are ranked); where few tiles are only
+// read, by instructions (25.6 M 38 us, of which a block ranks its marks for a third).  An element is marked if not |x| < bound (a NaN is).
+// Marked elements from the sample's own estimate of the threshold on are stored as +0.0 at once: nearly all of them are
+// kept, nearly none of those below, and k_tiles_out puts the others right.
+// ---------------------------------------------------------------------------
+template <bool NT, int GT>
+__global__ void __launch_bounds__(kMarkThreads, GT == kGNone ? 8 : 4)
+k_mark_tiles(SelParams p, TileArgs a, const float* __restrict__ gp, float* __restrict__ rp) {
+  constexpr int T = kMarkThreads, U = 8, WAVES = T / 64;
+  static_assert(T * U * 4 == kMarkTile && WAVES * U == 64, "a tile a block, and a lane for every row's count");
+  __shared__ uint32_t wcnt[WAVES * U];  // the tile's row counts, row-major
+  __shared__ uint2 stage[kMarkMax];
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kHistBins];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (GT == kGNone) rp = p.tab.p[p.one.vec >= 0 ? p.one.vec : *p.leader_dev];
+#pragma unroll
+  for (int i = 0; i < kHistBins / 4 / T; ++i) reinterpret_cast<uint4*>(lh)[tid + i * T] = make_uint4(0u, 0u, 0u, 0u);
+  for (int64_t ti = blockIdx.x; ti < a.ntiles; ti += gridDim.x) {
+    const uint4 at = tile_at(a, p.n, ti);
+    const int seg = (int)__builtin_amdgcn_readfirstlane(at.w);
+    const uint32_t first = __builtin_amdgcn_readfirstlane(at.x), lo = __builtin_amdgcn_readfirstlane(at.y);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(at.z);
+    const uint32_t* __restrict__ info = p.zero_base + (size_t)seg * kSegWords + kTileInfo;
+    const uint32_t bound = info[kTileBound], shift = info[kTileShift], zero = info[kTileZero];
+    const float gf = __uint_as_float(bound), zf = __uint_as_float(zero);
+    const uint32_t q0 = (first >> 2) + (uint32_t)tid;
+    uint32_t own = 0u;       // bit 4 u + e: element e of this lane's group in row u is marked
+    uint32_t rows_cnt = 0u;  // lane u < U: marks of the wave's row u
+    uint32_t zeroed = 0u;    // as own: stored as +0.0
+    uint32_t bits[U][4];
+    // FULL: the whole tile is the segment's, so nothing is predicated.
+    auto load = [&](auto full_tag) {
+      constexpr bool FULL = decltype(full_tag)::value;
+      const uint32_t w_lo = (lo + 3u) >> 2, w_hi = hi >> 2;  // whole groups
+      v4f x[U], b[U];
+      if (FULL || w_lo < w_hi) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          // (groups outside re-read the nearest one, unused: no branch between the loads)
+          const uint32_t q = q0 + (uint32_t)(u * T);
+          const uint32_t ql = FULL ? q : (q < w_lo ? w_lo : (q < w_hi ? q : w_hi - 1u));
+          if (GT != kGNone) x[u] = load4g<NT, GT>(gp, 4 * (int64_t)ql);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {  // (one array after the other: see k_pass_mark)
+          const uint32_t q = q0 + (uint32_t)(u * T);
+          const uint32_t ql = FULL ? q : (q < w_lo ? w_lo : (q < w_hi ? q : w_hi - 1u));
+          b[u] = load4<NT>(rp + 4 * (int64_t)ql);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t q = q0 + (uint32_t)(u * T);
+        uint32_t there = 0xfu;  // the group's elements that are the tile's
+        if (!FULL) {
+          there = 0u;
+#pragma unroll
+          for (uint32_t e = 0u; e < 4u; ++e) there |= (4u * q + e >= lo && 4u * q + e < hi) ? 1u << e : 0u;
+        }
+        v4f v = {0.f, 0.f, 0.f, 0.f};
+        if (FULL || there == 0xfu) {
+          v = b[u];
+          if (GT != kGNone) {
+            v.x = x[u].x + b[u].x;
+            v.y = x[u].y + b[u].y;
+            v.z = x[u].z + b[u].z;
+            v.w = x[u].w + b[u].w;
+          }
+        } else if (there != 0u) {
+          float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (uint32_t e = 0u; e < 4u; ++e)
+            if ((there >> e) & 1u) {
+              s[e] = rp[4 * (int64_t)q + e];
+              if (GT != kGNone) s[e] = load1g<GT>(gp, 4 * (int64_t)q + e) + s[e];
+            }
+          v = v4f{s[0], s[1], s[2], s[3]};
+        }
+        const bool h0 = (FULL || (there & 1u)) && !(__builtin_fabsf(v.x) < gf);
+        const bool h1 = (FULL || (there & 2u)) && !(__builtin_fabsf(v.y) < gf);
+        const bool h2 = (FULL || (there & 4u)) && !(__builtin_fabsf(v.z) < gf);
+        const bool h3 = (FULL || (there & 8u)) && !(__builtin_fabsf(v.w) < gf);
+        const uint32_t row = (uint32_t)(__popcll(__ballot(h0)) + __popcll(__ballot(h1)) + __popcll(__ballot(h2)) + __popcll(__ballot(h3)));
+        own |= ((h0 ? 1u : 0u) | (h1 ? 2u : 0u) | (h2 ? 4u : 0u) | (h3 ? 8u : 0u)) << (4 * u);
+        rows_cnt = lane == u ? row : rows_cnt;
+        bits[u][0] = __float_as_uint(v.x);
+        bits[u][1] = __float_as_uint(v.y);
+        bits[u][2] = __float_as_uint(v.z);
+        bits[u][3] = __float_as_uint(v.w);
+        if (GT != kGNone) {
+          v4f z = v;
+          uint32_t zs = 0u;
+          if (bound != 0u) {
+            const bool z0 = h0 && !(__builtin_fabsf(v.x) < zf), z1 = h1 && !(__builtin_fabsf(v.y) < zf);
+            const bool z2 = h2 && !(__builtin_fabsf(v.z) < zf), z3 = h3 && !(__builtin_fabsf(v.w) < zf);
+            z.x = z0 ? 0.0f : v.x;
+            z.y = z1 ? 0.0f : v.y;
+            z.z = z2 ? 0.0f : v.z;
+            z.w = z3 ? 0.0f : v.w;
+            zs = (z0 ? 1u : 0u) | (z1 ? 2u : 0u) | (z2 ? 4u : 0u) | (z3 ? 8u : 0u);
+          }
+          zeroed |= zs << (4 * u);
+          if (FULL || there == 0xfu) {
+            store4<NT>(rp + 4 * (int64_t)q, z);
+          } else if (there != 0u) {
+            const float s[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+            for (uint32_t e = 0u; e < 4u; ++e)
+              if ((there >> e) & 1u) rp[4 * (int64_t)q + e] = s[e];
+          }
+        }
+      }
+    };
+    if (lo == first && hi == first + (uint32_t)kMarkTile)
+      load(std::true_type{});
+    else
+      load(std::false_type{});
+    if (bound == 0u) {  // no bound: every element's top digit is counted, and there is no piece
+      __syncthreads();  // (the tile before has cleared the counts)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((own >> (4 * u + e)) & 1u) atomicAdd(&lh[(bits[u][e] & kKeyMask) >> 19], 1u);
+      if (tid == 0) {
+        a.held[ti] = kTileOverflow;
+        a.marked[ti] = hi - lo;
+      }
+      __syncthreads();
+    } else {
+      // rank the tile's marks: element order is row-major, row = 8 u + wave, then lane, then e
+      if (lane < U) wcnt[lane * WAVES + wave] = rows_cnt;
+      __syncthreads();
+      const uint32_t c0 = wcnt[lane];  // (every wave scans the counts itself)
+      const uint32_t s0 = wave_incl_scan(c0);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)s0, 63);
+      const bool fits = total <= (uint32_t)a.cap;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        // marks in the rows before this wave's row u
+        const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(s0 - c0), u * WAVES + wave);
+        const uint64_t b0 = __ballot((own >> (4 * u + 0)) & 1u), b1 = __ballot((own >> (4 * u + 1)) & 1u);
+        const uint64_t b2 = __ballot((own >> (4 * u + 2)) & 1u), b3 = __ballot((own >> (4 * u + 3)) & 1u);
+        if (((own >> (4 * u)) & 0xfu) != 0u) {
+          uint32_t pos = before + popc_lt(b0) + popc_lt(b1) + popc_lt(b2) + popc_lt(b3);
+          const uint32_t j0 = 4u * (q0 + (uint32_t)(u * T));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if ((own >> (4 * u + e)) & 1u) {
+              const uint32_t bin = ((bits[u][e] & kKeyMask) - bound) >> shift;
+              if (bin < (uint32_t)kTileBins) atomicAdd(&lh[bin], 1u);
+              if (fits) stage[pos] = make_uint2(j0 + (uint32_t)e, bits[u][e]);
+              ++pos;
+            }
+          }
+          if (GT != kGNone && !fits && ((zeroed >> (4 * u)) & 0xfu) != 0u) {  // rare: the values go back into the vector
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if ((zeroed >> (4 * u + e)) & 1u) rp[j0 + (uint32_t)e] = __uint_as_float(bits[u][e]);
+          }
+        }
+      }
+      __syncthreads();
+      if (fits) {
+        uint2* __restrict__ dst = a.pieces + (size_t)ti * (size_t)a.cap;
+        for (uint32_t i = (uint32_t)tid; i < total; i += T) dst[i] = stage[i];
+      }
+      if (tid == 0) {
+        a.held[ti] = fits ? total : kTileOverflow;
+        a.marked[ti] = total;
+      }
+    }
+    // (the next tile counts behind its first barrier)
+    tile_flush<T>(lh, tile_bins(p, a, seg, (uint32_t)ti));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// k_tiles_pick : one block of 1024 threads per segment: the threshold's bin.  A bound that fewer than k keys reach, or more
+// than k + n/8, or below which all bins lie, does not hold (need_full; the segment's own histogram is zero then).
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(1024)
+k_tiles_pick(SelParams p, TileArgs a) {
+  constexpr int T = 1024;
+  __shared__ uint32_t part[T];
+  __shared__ uint32_t res[4];
+  __shared__ uint64_t wsum[T / 64];
+  const int seg = blockIdx.x, tid = threadIdx.x;
+  const SegView sv = seg_view(p, seg);
+  const uint32_t* __restrict__ info = p.zero_base + (size_t)seg * kSegWords + kTileInfo;
+  const uint32_t bound = info[kTileBound], shift = bound != 0u ? info[kTileShift] : 19u;
+  uint32_t* __restrict__ bins = a.bins + (size_t)seg * (size_t)a.bins_stride;
+  TileBins<T> tb;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) tb.h[j] = 0u;
+  const uint4 own = reinterpret_cast<const uint4*>(bins)[tid];
+  for (int r0 = 0; r0 < sv.d.bins_more; r0 += 4) {  // four copies in flight
+    uint4 q[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      q[r] = reinterpret_cast<const uint4*>(a.more_bins +
+                                            (size_t)(sv.d.bins_begin + (r0 + r < sv.d.bins_more ? r0 + r : r0)) * kHistBins)[tid];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (r0 + r < sv.d.bins_more) {
+        tb.h[0] += q[r].x;
+        tb.h[1] += q[r].y;
+        tb.h[2] += q[r].z;
+        tb.h[3] += q[r].w;
+      }
+    }
+  }
+  tb.h[0] += own.x;
+  tb.h[1] += own.y;
+  tb.h[2] += own.z;
+  tb.h[3] += own.w;
+  uint64_t marks = 0u;
+  for (int t = tid; t < sv.d.ntiles; t += 8 * T) {  // eight tiles' in flight
+    uint32_t m[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m[u] = a.marked[sv.d.tile_begin + (t + u * T < sv.d.ntiles ? t + u * T : t)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) marks += t + u * T < sv.d.ntiles ? m[u] : 0u;
+  }
+  const uint64_t binned = (uint64_t)tb.h[0] + tb.h[1] + tb.h[2] + tb.h[3];
+  const uint64_t both = wave_allsum_u64((marks << 32) | binned);  // (both are below 2^31)
+  if ((tid & 63) == 0) wsum[tid >> 6] = both;
+  __syncthreads();
+  uint64_t all = 0u;
+#pragma unroll
+  for (int i = 0; i < T / 64; ++i) all += wsum[i];
+  const uint32_t total = (uint32_t)(all >> 32), high = bound == 0u ? 0u : total - (uint32_t)all;  // above all bins
+  const uint32_t k = sv.d.k;
+  uint64_t limit = (uint64_t)k + ((uint64_t)(sv.d.e_hi - sv.d.e_lo) >> 3);
+  if (limit > sv.d.cap) limit = sv.d.cap;
+  const bool holds = bound == 0u || (total >= k && total <= limit && high < k);
+  SelState st{};
+  if (holds) {
+    uint4 got;
+    tb.scan(part);
+    if (!tb.find(k - high, res, got)) {
+      if (tid == 0) atomicOr(p.err, kErrPick);
+      return;
+    }
+    st.lo = bound + (got.x << shift);
+    st.hi = st.lo + ((1u << shift) - 1u);
+    st.n_gt = high + got.y;
+    st.need = k - st.n_gt;
+    st.cand = got.z;
+    st.level = 1u;
+    st.compact_level = bound != 0u || fits_list(st, sv.d.cap) ? 1u : 0u;
+    st.list_count = bound != 0u ? total : st.compact_level ? st.n_gt + st.cand : 0u;
+    st.use_mask = bound != 0u ? 1u : 0u;
+    st.list_lo = bound;
+    st.pad[0] = shift;
+  } else {
+    st.need_full = 1u;
+    if (bins == sv.hseg) reinterpret_cast<uint4*>(bins)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0) *a.any_full = 1u;
+  }
+  if (tid == 0) *sv.st = st;
+}
+
+// ---------------------------------------------------------------------------
+// k_tiles_full : for segments whose bound does not hold: the marked elements get their values back, and the segment's own
+// histogram the top digits of all keys.  Blocks stride over the tiles.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(kMarkThreads)
+k_tiles_full(SelParams p, TileArgs a) {
+  constexpr int T = kMarkThreads, U = 8;
+  if (*a.any_full == 0u) return;
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kHistBins];
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < kHistBins / 4 / T; ++i) reinterpret_cast<uint4*>(lh)[tid + i * T] = make_uint4(0u, 0u, 0u, 0u);
+  for (int64_t ti = blockIdx.x; ti < a.ntiles; ti += gridDim.x) {
+    const uint4 at = tile_at(a, p.n, ti);
+    const SegView sv = seg_view(p, (int)at.w);
+    if (sv.st->need_full == 0u) continue;  // (the same in every thread)
+    const uint32_t lo = at.y, hi = at.z, held = a.held[ti];
+    const uint32_t zero = p.zero_base[(size_t)at.w * kSegWords + kTileInfo + kTileZero];
+    if (p.zero_vec != nullptr && held != kTileOverflow) {
+      const uint2* __restrict__ piece = a.pieces + (size_t)ti * (size_t)a.cap;
+      for (uint32_t i = (uint32_t)tid; i < held; i += T) {
+        const uint2 ent = piece[i];
+        if ((ent.y & kKeyMask) >= zero && ent.x >= lo && ent.x < hi) p.zero_vec[ent.x] = __uint_as_float(ent.y);
+      }
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (tid == 0) a.held[ti] = kTileOverflow;
+    const uint32_t w_lo = (lo + 3u) >> 2, w_hi = hi >> 2;
+    auto count = [&](uint32_t raw) { wave_count(lh, (raw & kKeyMask) >> 19); };
+    if (w_lo < w_hi) {
+      uint4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t q = w_lo + (uint32_t)(tid + u * T);
+        v[u] = *reinterpret_cast<const uint4*>(sv.x + 4 * (int64_t)(q < w_hi ? q : w_hi - 1u));
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (w_lo + (uint32_t)(tid + u * T) < w_hi) {
+          count(v[u].x);
+          count(v[u].y);
+          count(v[u].z);
+          count(v[u].w);
+        }
+      }
+    }
+    // the elements outside whole groups: at most three on either side
+    const uint32_t front = w_lo < w_hi ? 4u * w_lo - lo : hi - lo, back = w_lo < w_hi ? hi - 4u * w_hi : 0u;
+    if ((uint32_t)tid < front) count(__float_as_uint(sv.x[lo + (uint32_t)tid]));
+    if ((uint32_t)tid < back) count(__float_as_uint(sv.x[4 * (int64_t)w_hi + tid]));
+    __syncthreads();
+    tile_flush<T>(lh, sv.hseg);
+    __syncthreads();
+  }
+}
+
+// The entries of tile `at`: a piece's, `held` of them, in rows of 64 (row1(entry, whether it is there)), or where there is none
+// those of the tile's part `part` from the vector, in rows of 256, four in a row a lane's (row4(raw bits, the first one's
+// element, which of them are there)), in order.  The 64 lanes of a wave call it.
+template <typename Row1, typename Row4>
+__device__ __forceinline__ void tile_rows(const TileArgs& a, const float* x, int64_t t, uint32_t held, int part, const uint4 at,
+                                          Row1 row1, Row4 row4) {
+  const uint32_t lane = lane_id();
+  if (held != kTileOverflow) {
+    const uint2* __restrict__ piece = a.pieces + (size_t)t * (size_t)a.cap;
+#pragma unroll 1
+    for (uint32_t r0 = 0u; r0 < held; r0 += 512u) {  // eight rows in flight
+      uint2 ent[8];
+#pragma unroll
+      for (uint32_t u = 0u; u < 8u; ++u) {
+        const uint32_t i = r0 + 64u * u + lane;
+        ent[u] = piece[i < held ? i : held - 1u];
+      }
+#pragma unroll
+      for (uint32_t u = 0u; u < 8u; ++u)
+        if (r0 + 64u * u < held) row1(ent[u], r0 + 64u * u + lane < held);
+    }
+    return;
+  }
+  constexpr uint32_t PART = kMarkTile / kTileWaves;
+  const uint32_t first = __builtin_amdgcn_readfirstlane(at.x) + (uint32_t)part * PART;
+  uint32_t lo = __builtin_amdgcn_readfirstlane(at.y), hi = __builtin_amdgcn_readfirstlane(at.z);
+  if (lo < first) lo = first;
+  if (hi > first + PART) hi = first + PART;
+  if (lo == first && hi == first + PART) {
+    const uint4* __restrict__ from = reinterpret_cast<const uint4*>(x + first) + lane;
+    constexpr int ROWS = (int)PART / 256;
+    uint4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = from[64 * u];
+#pragma unroll 1
+    for (int r0 = 0; r0 < ROWS; r0 += 4) {  // the next four rows' loads in front of these rows' work
+      uint4 w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] = from[64 * (r0 + 4 < ROWS ? r0 + 4 + u : u)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) row4(v[u], first + 256u * (uint32_t)(r0 + u) + 4u * lane, 0xfu);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = w[u];
+    }
+    return;
+  }
+  const uint32_t w_lo = (lo + 3u) >> 2, w_hi = hi >> 2;
+#pragma unroll 1
+  for (uint32_t q0 = first >> 2; 4u * q0 < hi; q0 += 256u) {
+    uint4 v[4];
+#pragma unroll
+    for (uint32_t u = 0u; u < 4u; ++u) {
+      const uint32_t q = q0 + 64u * u + lane;
+      v[u] = make_uint4(0u, 0u, 0u, 0u);
+      if (q >= w_lo && q < w_hi) {
+        v[u] = *reinterpret_cast<const uint4*>(x + 4 * (int64_t)q);
+      } else {  // at most one group on either side
+        if (4u * q + 0u >= lo && 4u * q + 0u < hi) v[u].x = __float_as_uint(x[4 * (int64_t)q + 0]);
+        if (4u * q + 1u >= lo && 4u * q + 1u < hi) v[u].y = __float_as_uint(x[4 * (int64_t)q + 1]);
+        if (4u * q + 2u >= lo && 4u * q + 2u < hi) v[u].z = __float_as_uint(x[4 * (int64_t)q + 2]);
+        if (4u * q + 3u >= lo && 4u * q + 3u < hi) v[u].w = __float_as_uint(x[4 * (int64_t)q + 3]);
+      }
+    }
+#pragma unroll 1
+    for (uint32_t u = 0u; u < 4u; ++u) {
+      const uint32_t q = q0 + 64u * u + lane;
+      uint32_t there = 0u;
+#pragma unroll
+      for (uint32_t e = 0u; e < 4u; ++e) there |= (4u * q + e >= lo && 4u * q + e < hi) ? 1u << e : 0u;
+      if (4u * (q0 + 64u * u) < hi) row4(v[0], 4u * q, there);
+      v[0] = v[1];
+      v[1] = v[2];
+      v[2] = v[3];
+    }
+  }
+}
+
+// What a block of k_tiles_digit, k_tiles_count or k_tiles_out has: kTileWaves tiles of a segment, side by side, or (APART)
+// as many blocks apart as the segment has, so that a few blocks do not get all the tiles without pieces where large values lie
+// together.  A wave first takes its own tile's piece, then its part of each tile of the block that has none.
+template <bool APART>
+struct TileGroup {
+  int seg, number, blocks, ntiles;
+  int64_t begin;
+  uint32_t own;   // entries in the piece of the wave's own tile
+  uint32_t open;  // bit i: the block's i-th tile has none
+  __device__ __forceinline__ TileGroup(const SelParams& p, const TileArgs& a, int wave) {
+    seg = 0;
+    number = (int)blockIdx.x;
+    if (a.groups != nullptr) {
+      const uint2 g = a.groups[blockIdx.x];
+      seg = (int)__builtin_amdgcn_readfirstlane(g.x);
+      number = (int)__builtin_amdgcn_readfirstlane(g.y);
+    }
+    const SegDesc& d = p.table != nullptr ? p.table[seg] : p.one;
+    ntiles = d.ntiles;
+    begin = d.tile_begin;
+    blocks = (ntiles + kTileWaves - 1) / kTileWaves;
+    const int i = (int)lane_id() & (kTileWaves - 1);
+    const uint32_t held = a.held[begin + (tile(i) < ntiles ? tile(i) : 0)];
+    own = (uint32_t)__builtin_amdgcn_readlane((int)held, wave);
+    open = (uint32_t)__ballot(tile(i) < ntiles && held == kTileOverflow) & ((1u << kTileWaves) - 1u);
+  }
+  // the segment's tile that is the block's i-th; ntiles or more where there is none
+  __device__ __forceinline__ int tile(int i) const { return APART ? number + i * blocks : number * kTileWaves + i; }
+  // job(the block's tile, the part of it) for whatever wave `wave` has to do, in some order
+  template <typename Job>
+  __device__ __forceinline__ void each(int wave, Job job) const {
+#pragma unroll 1
+    for (int n = 0; n <= kTileWaves; ++n) {
+      const int i = n == 0 ? wave : n - 1;
+      if (tile(i) < ntiles && (n == 0) != (((open >> i) & 1u) != 0u)) job(i, n == 0 ? own : kTileOverflow, n == 0 ? 0 : wave);
+    }
+  }
+};
+
+// ---------------------------------------------------------------------------
+// k_tiles_digit : counts the next digits of the keys in the threshold's bin (LEVEL 1: twelve bits, and per tile how many lie
+// above the bin, how many in it, and the first few of these; LEVEL 2: the up to seven bits that are left where the bin was
+// as wide as a top digit).
+// ---------------------------------------------------------------------------
+template <int LEVEL, bool APART>
+__global__ void __launch_bounds__(64 * kTileWaves)
+k_tiles_digit(SelParams p, TileArgs a) {
+  constexpr int T = 64 * kTileWaves;
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kHistBins];
+  __shared__ uint32_t part[T];
+  __shared__ uint32_t res[4];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lane = lane_id();
+  if (*p.err != 0u) return;
+  const TileGroup<APART> tg(p, a, wave);
+  const SegView sv = seg_view(p, tg.seg);
+  if (LEVEL == 2 && sv.st->need_full == 0u && tile_rest(sv.st->pad[0]) == 0u) return;
+#pragma unroll
+  for (int i = 0; i < kHistBins / 4 / T; ++i) reinterpret_cast<uint4*>(lh)[tid + i * T] = make_uint4(0u, 0u, 0u, 0u);
+  TilePick pk = tile_first<T>(sv, part, res, p.err);
+  if (LEVEL == 1 && tg.number == 0 && tid == 0 && sv.st->need_full != 0u) {  // what select_info reports
+    SelState st{};
+    st.n_gt = pk.above;
+    st.cand = pk.cand;
+    const bool fits = fits_list(st, sv.d.cap);
+    sv.st->list_count = fits ? pk.above + pk.cand : 0u;
+    sv.st->compact_level = fits ? 1u : 0u;
+  }
+  if (LEVEL == 2) tile_narrow<T>(pk, sv.hist1, tile_rest(pk.bits), part, res, p.err);
+  __syncthreads();
+  const uint32_t klo = pk.lo, khi = pk.lo + ((1u << pk.bits) - 1u), rest = LEVEL == 2 ? 0u : tile_rest(pk.bits);
+  const uint32_t width = khi - klo;
+  tg.each(wave, [&](int i, uint32_t held, int q) __attribute__((always_inline)) {
+    const int64_t t = tg.begin + tg.tile(i), tp = t * kTileWaves + q;
+    if (LEVEL == 2 && a.among[tp] == 0u) return;
+    uint32_t up = 0u, in = 0u;  // a lane's own; the wave's
+    auto middle = [&](uint32_t kk, bool mid) __attribute__((always_inline)) {
+      const uint64_t m = __ballot(mid);
+      if (mid) {
+        wave_count(lh, (kk - klo) >> rest);
+        const uint32_t at = in + popc_lt(m);
+        if (LEVEL == 1 && at < (uint32_t)kTileSlots) a.slots[tp * kTileSlots + at] = kk;
+      }
+      in += (uint32_t)__popcll(m);
+    };
+    tile_rows(a, sv.x, t, held, q, tile_at(a, p.n, t),
+              [&](uint2 ent, bool ok) __attribute__((always_inline)) {
+                const uint32_t kk = ent.y & kKeyMask;
+                up += ok && kk > khi ? 1u : 0u;
+                const bool mid = ok && kk - klo <= width;
+                if (__ballot(mid) != 0ull) middle(kk, mid);
+              },
+              [&](uint4 v, uint32_t, uint32_t there) __attribute__((always_inline)) {
+                const uint32_t kk[4] = {v.x & kKeyMask, v.y & kKeyMask, v.z & kKeyMask, v.w & kKeyMask};
+                bool mid[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const bool ok = (there >> e) & 1u;
+                  up += ok && kk[e] > khi ? 1u : 0u;
+                  mid[e] = ok && kk[e] - klo <= width;
+                }
+                if (__ballot(mid[0] || mid[1] || mid[2] || mid[3]) == 0ull) return;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) middle(kk[e], mid[e]);
+              });
+    if (LEVEL == 1) {
+      up = (uint32_t)wave_allsum_u64(up);
+      if (lane < (held != kTileOverflow ? (uint32_t)kTileWaves : 1u)) {  // (the other parts of a tile with a piece are empty)
+        a.above[tp + lane] = lane == 0u ? up : 0u;
+        a.among[tp + lane] = lane == 0u ? in : 0u;
+      }
+    }
+  });
+  __syncthreads();
+  tile_flush<T>(lh, LEVEL == 1 ? sv.hist1 : sv.hist2);
+}
+
+// The threshold itself: pk.lo is the key, pk.need of the pk.cand entries that have it are kept.
+template <int T>
+__device__ __forceinline__ TilePick tile_threshold(const SegView& sv, uint32_t* part, uint32_t* res, uint32_t* __restrict__ err,
+                                                   uint32_t* top = nullptr) {
+  TilePick pk = tile_first<T>(sv, part, res, err);
+  if (top != nullptr) *top = pk.lo + ((1u << pk.bits) - 1u);
+  tile_narrow<T>(pk, sv.hist1, tile_rest(pk.bits), part, res, err);
+  if (pk.bits != 0u) {  // (the same in every thread; only the first 128 counts of hist2 are the digit's)
+    TileBins<T> tb;
+#pragma unroll
+    for (int j = 0; j < TileBins<T>::BPT; ++j) {
+      const int b = TileBins<T>::BPT * (int)threadIdx.x + j;
+      tb.h[j] = b < 128 ? sv.hist2[b] : 0u;
+    }
+    tile_take(tb, pk, 0u, part, res, err);
+  }
+  return pk;
+}
+
+// ---------------------------------------------------------------------------
+// k_tiles_count : per tile the entries above the threshold and at it; only tiles with keys in the bin have anything to look
+// at, and most of those all of them in their few slots.
+// ---------------------------------------------------------------------------
+template <bool APART>
+__global__ void __launch_bounds__(64 * kTileWaves)
+k_tiles_count(SelParams p, TileArgs a) {
+  constexpr int T = 64 * kTileWaves;
+  __shared__ uint32_t part[T];
+  __shared__ uint32_t res[4];
+  __shared__ unsigned long long kept_sh[kTileWaves];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane = lane_id();
+  if (*p.err != 0u) return;
+  const TileGroup<APART> tg(p, a, wave);
+  const SegView sv = seg_view(p, tg.seg);
+  if (threadIdx.x < kTileWaves) kept_sh[threadIdx.x] = 0ull;
+  uint32_t top;  // the last key of the bin
+  const TilePick pk = tile_threshold<T>(sv, part, res, p.err, &top);
+  const uint32_t width = top - pk.lo;
+  tg.each(wave, [&](int i, uint32_t held, int q) __attribute__((always_inline)) {
+    const int64_t t = tg.begin + tg.tile(i), tp = t * kTileWaves + q;
+    const uint32_t in = __builtin_amdgcn_readfirstlane(a.among[tp]);
+    uint64_t kept = (uint64_t)a.above[tp] << 32;
+    if (in != 0u) {
+      uint32_t up = 0u, eq = 0u;  // a lane's own
+      auto one = [&](uint32_t kk, bool ok) __attribute__((always_inline)) {
+        up += ok && kk - pk.lo - 1u < width ? 1u : 0u;
+        eq += ok && kk == pk.lo ? 1u : 0u;
+      };
+      if (in <= (uint32_t)kTileSlots) {
+        const bool ok = lane < in;
+        one(a.slots[tp * kTileSlots + (ok ? lane : 0u)], ok);
+      } else {
+        tile_rows(a, sv.x, t, held, q, tile_at(a, p.n, t), [&](uint2 ent, bool ok) { one(ent.y & kKeyMask, ok); },
+                  [&](uint4 v, uint32_t, uint32_t there) __attribute__((always_inline)) {
+                    one(v.x & kKeyMask, (there & 1u) != 0u);
+                    one(v.y & kKeyMask, (there & 2u) != 0u);
+                    one(v.z & kKeyMask, (there & 4u) != 0u);
+                    one(v.w & kKeyMask, (there & 8u) != 0u);
+                  });
+      }
+      kept += wave_allsum_u64(((uint64_t)up << 32) | eq);
+      if (lane == 0u) {
+        a.above[tp] = (uint32_t)(kept >> 32);
+        a.among[tp] = (uint32_t)kept;
+      }
+    }
+    if (lane == 0u) atomicAdd(&kept_sh[i], (unsigned long long)kept);
+  });
+  __syncthreads();
+  if (threadIdx.x < kTileWaves && tg.tile((int)threadIdx.x) < tg.ntiles)
+    a.kept[tg.begin + tg.tile((int)threadIdx.x)] = kept_sh[threadIdx.x];
+  if (threadIdx.x == 0) {
+    uint64_t sum = 0ull;
+#pragma unroll
+    for (int i = 0; i < kTileWaves; ++i) sum += kept_sh[i];
+    a.kept[a.ntiles + (int)blockIdx.x] = sum;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// k_tiles_out : the kept entries, in order: what the tiles in front of each of a block's keep is added up first (by block,
+// or where the block's tiles lie apart by tile, a wave for each).  With zero_vec the kept entries become +0.0 there, those
+// that were at the marking already and are not kept get their values back.
+// ---------------------------------------------------------------------------
+template <bool APART>
+__global__ void __launch_bounds__(64 * kTileWaves)
+k_tiles_out(SelParams p, TileArgs a) {
+  constexpr int T = 64 * kTileWaves;
+  __shared__ uint32_t part[T];
+  __shared__ uint32_t res[4];
+  __shared__ uint64_t wsum[kTileWaves];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lane = lane_id();
+  if (*p.err != 0u) return;
+  const TileGroup<APART> tg(p, a, wave);
+  const SegView sv = seg_view(p, tg.seg);
+  const TilePick pk = tile_threshold<T>(sv, part, res, p.err);
+  // above the threshold << 32 | at it
+  const uint64_t* __restrict__ front = a.kept + (APART ? tg.begin : (int64_t)a.ntiles + sv.d.group_begin);
+  const int count = APART ? (tg.tile(wave) < tg.ntiles ? tg.tile(wave) : 0) : tg.number;
+  const int step = APART ? 64 : T;
+  uint64_t sum = 0ull;
+  for (int i = APART ? (int)lane : tid; i < count; i += 4 * step) {  // four in flight
+    uint64_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = front[i + q * step < count ? i + q * step : i];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum += i + q * step < count ? v[q] : 0ull;
+  }
+  sum = wave_allsum_u64(sum);
+  if (lane == 0u) wsum[wave] = sum;
+  __syncthreads();
+  const uint32_t key = pk.lo, quota = pk.need, k = sv.d.k;
+  const uint32_t zero = p.zero_base[(size_t)tg.seg * kSegWords + kTileInfo + kTileZero];
+  float* const zv = p.zero_vec;
+  uint32_t nA = 0u, nB = 0u;
+  auto place = [&](uint32_t up, uint32_t eq) { return up + (eq < quota ? eq : quota); };
+  auto keep = [&](uint32_t m, uint32_t j, uint32_t raw) {
+    if (m >= k) return;
+    sv.idx_out[m] = (int32_t)j;
+    if (sv.vals_row) sv.vals_row[m] = __uint_as_float(raw);
+  };
+  tg.each(wave, [&](int i, uint32_t held, int q) __attribute__((always_inline)) {
+    const int ts = tg.tile(i);
+    const int64_t t = tg.begin + ts;
+    uint64_t ahead = 0ull;
+    if (APART) {
+      ahead = wsum[i];
+    } else {
+#pragma unroll
+      for (int w = 0; w < kTileWaves; ++w) ahead += wsum[w];
+      for (int w = 0; w < i; ++w) ahead += a.kept[t - i + w];
+    }
+    for (int w = 0; w < q; ++w) ahead += ((uint64_t)a.above[t * kTileWaves + w] << 32) | a.among[t * kTileWaves + w];
+    nA = (uint32_t)(ahead >> 32);
+    nB = (uint32_t)ahead;
+    if (a.tile_start != nullptr && lane == 0u && q == 0) {
+      static_assert(kPassTile == 2 * kMarkTile, "two tiles");
+      if ((t & 1) == 0) a.tile_start[t >> 1] = (int32_t)sv.d.koff + (int32_t)place(nA, nB);
+      if (ts == tg.ntiles - 1) a.tile_start[(t + 2) >> 1] = (int32_t)sv.d.koff + (int32_t)k;
+    }
+    tile_rows(a, sv.x, t, held, q, tile_at(a, p.n, t),
+              [&](uint2 ent, bool ok) __attribute__((always_inline)) {
+                const uint32_t kk = ent.y & kKeyMask;
+                const bool up = ok && kk > key, eq = ok && kk == key;
+                const uint64_t mu = __ballot(up), me = __ballot(eq);
+                const uint32_t before = nB + popc_lt(me);
+                const bool kept = up || (eq && before < quota);
+                if (kept) keep(place(nA + popc_lt(mu), before), ent.x, ent.y);
+                if (zv != nullptr && ok && (int64_t)ent.x < p.n) {
+                  if (kept && kk < zero) zv[ent.x] = 0.0f;
+                  if (!kept && kk >= zero) zv[ent.x] = __uint_as_float(ent.y);
+                }
+                nA += (uint32_t)__popcll(mu);
+                nB += (uint32_t)__popcll(me);
+              },
+              [&](uint4 v, uint32_t j, uint32_t there) __attribute__((always_inline)) {
+                const uint32_t raw[4] = {v.x, v.y, v.z, v.w};
+                bool up[4], eq[4];
+                uint64_t mu[4], me[4];
+  #pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const uint32_t kk = raw[e] & kKeyMask;
+                  up[e] = ((there >> e) & 1u) && kk > key;
+                  eq[e] = ((there >> e) & 1u) && kk == key;
+                  mu[e] = __ballot(up[e]);
+                  me[e] = __ballot(eq[e]);
+                }
+                if ((mu[0] | mu[1] | mu[2] | mu[3] | me[0] | me[1] | me[2] | me[3]) == 0ull) return;
+                uint32_t bu = nA, be = nB;
+  #pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  bu += popc_lt(mu[e]);
+                  nA += (uint32_t)__popcll(mu[e]);
+                }
+                if ((me[0] | me[1] | me[2] | me[3]) != 0ull) {
+  #pragma unroll
+                  for (int e = 0; e < 4; ++e) {
+                    be += popc_lt(me[e]);
+                    nB += (uint32_t)__popcll(me[e]);
+                  }
+                }
+  #pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  if (up[e] || (eq[e] && be < quota)) {
+                    keep(place(bu, be), j + (uint32_t)e, raw[e]);
+                    if (zv != nullptr) zv[j + (uint32_t)e] = 0.0f;
+                  }
+                  bu += up[e] ? 1u : 0u;
+                  be += eq[e] ? 1u : 0u;
+                }
+              });
+  });
 }
 
 // ---------------------------------------------------------------------------

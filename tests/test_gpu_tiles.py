@@ -1,0 +1,174 @@
+"""GPU parity of the selection by marked tiles (k_mark_tiles and what follows it): flat steps whose leader is known up
+front, and segments, bit for bit against the oracle.  The length from which it is used is lowered through
+ARTOPK_OPT_GUESS_MIN_N; the sizes lie around a tile's 32768 elements, its groups of four and the sixteen tiles of a block,
+and the values are those for which a sampled bound, a tile's piece or the narrow bins do not do."""
+
+import numpy as np
+import pytest
+
+import artopk_inputs as inp
+from oracle import artopk_oracle as orc
+from tests import gpu_util
+from tests.gpu_util import GpuRunner, assert_step_matches
+
+pytestmark = pytest.mark.gpu
+TILE = 32768
+
+
+@pytest.fixture(autouse=True)
+def tiles_on(monkeypatch):
+    monkeypatch.setitem(gpu_util.OPTIONS, "guess_min_n", 4096)
+    monkeypatch.setitem(gpu_util.OPTIONS, "stage_tiles", 2)
+    monkeypatch.setitem(gpu_util.OPTIONS, "short_max_n", 0)
+
+
+def _values(kind, n, rng):
+    x = rng.standard_normal(n).astype(np.float32)
+    if kind == "normal":
+        return x
+    if kind == "equal":
+        return np.full(n, -0.375, dtype=np.float32)
+    if kind == "zeros":
+        return np.where(rng.random(n) < 1e-3, x, 0.0).astype(np.float32)
+    if kind == "ties":  # a few hundred values, so that the threshold is one of them
+        return (np.round(x * 32.0) / 32.0).astype(np.float32)
+    if kind == "run":  # tiles with more marks than a piece takes, and a sample that sees few of them
+        x *= np.float32(1e-3)
+        lo = n // 3
+        x[lo:lo + n // 20] += np.float32(2.0)
+        return x
+    if kind == "sorted":
+        return np.sort(np.abs(x))
+    if kind == "narrow":  # all in one top digit
+        return (1.0 + 0.06 * rng.random(n)).astype(np.float32)
+    if kind == "odd":  # infinities, NaNs of either sign, negative zeros and denormals
+        x[::977] = np.inf
+        x[5::1931] = -np.inf
+        x[3::2003] = np.float32(np.nan)
+        x[7::2003] = -np.float32(np.nan)
+        x[2::11] = -0.0
+        x[4::13] = np.float32(1e-41)
+        return x
+    raise ValueError(kind)
+
+
+def _steps(w, n, k, mode, gen, steps=2, seg_off=None, seg_k=None, max_k=None):
+    runner = GpuRunner(w, n, max_k or k, max_segments=len(seg_k) if seg_k else 1)
+    res = [np.zeros(n, dtype=np.float32) for _ in range(w)]
+    for step_no in range(1, steps + 1):
+        g = [gen(step_no, r) for r in range(w)]
+        with np.errstate(all="ignore"):
+            want = orc.step(g, res, k, mode, step_no=step_no, seg_off=seg_off, seg_k=seg_k)
+        runner.load_g(g)
+        got = runner.step(k, mode, step_no, seg_off=seg_off, seg_k=seg_k)
+        assert_step_matches(got, want, mode)
+        res = want.residual
+    return runner
+
+
+@pytest.mark.parametrize("n", [16384, TILE - 1, TILE, TILE + 1, 16 * TILE - 2, 16 * TILE + 5, 33 * TILE + 31])
+@pytest.mark.parametrize("rho", [0.001, 0.02, 0.12])
+def test_flat_lengths(n, rho):
+    rng = np.random.default_rng(n)
+    _steps(2, n, max(1, int(n * rho)), orc.MODE_STAR, lambda s, r: _values("normal", n, rng))
+
+
+@pytest.mark.parametrize("kind", ["equal", "zeros", "ties", "run", "sorted", "narrow", "odd"])
+@pytest.mark.parametrize("rho", [0.005, 0.1])
+def test_flat_values(kind, rho):
+    n = 19 * TILE + 3
+    rng = np.random.default_rng(3)
+    _steps(2, n, int(n * rho), orc.MODE_STAR, lambda s, r: _values(kind, n, rng), steps=1 if kind == "odd" else 2)
+
+
+def _layout(name):
+    if name == "buckets":  # whole tiles, the last one ragged
+        return [0, 4 * TILE, 8 * TILE, 12 * TILE, 14 * TILE + 77]
+    if name == "layers":  # none at a tile's edge, a few too short to be sampled, elements of two segments in one group
+        return [0, 13, 40, 700, 40_003, 40_070, 300_001, 300_002, 420_420, 800_001, 1_100_003]
+    if name == "two":
+        return [0, 17 * TILE + 9, 40 * TILE]
+    if name == "edges":  # around lines of 32 elements and tiles
+        return [0, TILE - 1, TILE + 1, 2 * TILE + 31, 2 * TILE + 32, 3 * TILE + 33, 20 * TILE]
+    raise ValueError(name)
+
+
+@pytest.mark.parametrize("layout", ["buckets", "layers", "two", "edges"])
+@pytest.mark.parametrize("mode", ["star", "var"])
+@pytest.mark.parametrize("rho", [0.01, 0.2])
+def test_segments(layout, mode, rho):
+    off = _layout(layout)
+    ks = [max(1, int(np.ceil(rho * (b - a)))) for a, b in zip(off, off[1:])]
+    n, w = off[-1], 3
+    wl = inp.workload(2, n=n, w=w)
+    _steps(w, n, sum(ks), orc.MODE_STAR if mode == "star" else orc.MODE_VAR, wl.gen, seg_off=off, seg_k=ks)
+
+
+@pytest.mark.parametrize("kind", ["equal", "zeros", "ties", "run", "sorted", "narrow", "odd"])
+@pytest.mark.parametrize("layout", ["buckets", "layers"])
+def test_segment_values(kind, layout):
+    off = _layout(layout)
+    ks = [max(1, (b - a) // 40) for a, b in zip(off, off[1:])]
+    rng = np.random.default_rng(4)
+    _steps(2, off[-1], sum(ks), orc.MODE_STAR, lambda s, r: _values(kind, off[-1], rng), seg_off=off, seg_k=ks,
+           steps=1 if kind == "odd" else 2)
+
+
+@pytest.mark.parametrize("values", ["normal", "run"])
+def test_segments_keep_everything_or_one(values):
+    off = _layout("layers")
+    ks = [1 if i % 2 else b - a for i, (a, b) in enumerate(zip(off, off[1:]))]
+    rng = np.random.default_rng(5)
+    _steps(2, off[-1], sum(ks), orc.MODE_STAR, lambda s, r: _values(values, off[-1], rng), seg_off=off, seg_k=ks)
+
+
+@pytest.mark.parametrize("layout", ["buckets", "layers", "edges"])
+def test_segmented_selection_alone(layout):
+    """artopk_select_topk on segments, twice on one context with another layout in between."""
+    import torch
+
+    off = _layout(layout)
+    n = off[-1]
+    ks = [max(1, (b - a) // 50) for a, b in zip(off, off[1:])]
+    x = _values("ties", n, np.random.default_rng(6))
+    ctx = gpu_util.make_context(1, n, sum(ks), max(2, len(ks)))
+    t = torch.from_numpy(x).cuda()
+    idx = torch.full((sum(ks),), -1, dtype=torch.int32, device="cuda")
+    half = [0, n // 2, n]
+    for o, q in ((off, ks), (half, [3, 5]), (off, ks)):
+        idx.fill_(-1)
+        ctx.artopk_select_topk(t, sum(q), idx, seg_off=o, seg_k=q)
+        ctx.status()
+        want = np.concatenate([orc.topk_indices(x[a:b], m) + a for a, b, m in zip(o, o[1:], q)])
+        assert np.array_equal(idx[: sum(q)].cpu().numpy(), want)
+        assert np.array_equal(t.cpu().numpy(), x)
+
+
+@pytest.mark.parametrize("gtype", ["bf16", "f16"])
+@pytest.mark.parametrize("layout", [None, "layers"])
+def test_16_bit_gradients(gtype, layout):
+    import torch
+
+    off = _layout(layout) if layout else None
+    n, w = (off[-1] if off else 20 * TILE + 3), 2
+    ks = [max(1, (b - a) // 30) for a, b in zip(off, off[1:])] if off else None
+    k = sum(ks) if ks else n // 30
+    dtype = torch.bfloat16 if gtype == "bf16" else torch.float16
+    runner = GpuRunner(w, n, k, max_segments=len(ks) if ks else 1)
+    rng = np.random.default_rng(8)
+    res = [np.zeros(n, dtype=np.float32) for _ in range(w)]
+    for step_no in (1, 2):
+        g16 = [torch.from_numpy(_values("normal", n, rng)).to(dtype).cuda() for _ in range(w)]
+        g = [t.float().cpu().numpy() for t in g16]
+        want = orc.step(g, res, k, orc.MODE_STAR, step_no=step_no, seg_off=off, seg_k=ks)
+        more = {"seg_off": off, "seg_k": ks} if off else {}
+        runner.ctx.artopk_step_g16(g16, runner.lib.ARTOPK_G_BF16 if gtype == "bf16" else runner.lib.ARTOPK_G_F16, runner.res, k,
+                                   orc.MODE_STAR, step_no, runner.idx, runner.sum, runner.update, leader_out=runner.leader,
+                                   **more)
+        runner.ctx.status()
+        assert np.array_equal(runner.idx[:k].cpu().numpy(), want.idx)
+        assert np.array_equal(gpu_util.bits(runner.sum[:k].cpu().numpy()), gpu_util.bits(want.sum))
+        assert np.array_equal(gpu_util.bits(runner.update.cpu().numpy()), gpu_util.bits(want.update))
+        for r in range(w):
+            assert np.array_equal(gpu_util.bits(runner.res[r].cpu().numpy()), gpu_util.bits(want.residual[r]))
+        res = want.residual
