@@ -76,11 +76,13 @@ constexpr int kHistReps = 16;            // partial copies of a whole-vector his
 // histogram of the threshold-guess sample, then its control words.
 constexpr int kSlotGuessHist = kHistReps * kHistBins;
 constexpr int kSlotCtrl = kSlotGuessHist + kHistBins;  // [0] blocks done, [1] guessed key bound, [2] blocks of k_guess_tiles through
-constexpr int kSlotMcount = kSlotCtrl + 16;            // marked elements per chunk (kMaxChunks words)
-constexpr int kSlotRefine = kSlotMcount + 1024;        // second-digit histogram of the guess sample (k_guess_tiles)
-constexpr int kSlotWords = kSlotRefine + kHistBins;
-constexpr int kGuessMidAt = 8 * kHistBins;             // (k_guess_tiles: two histograms in copies' places)
+constexpr int kSlotMcount = kSlotCtrl + 16;            // marked elements per chunk, kMcountLine words apart
+constexpr int kMcountLine = 16;  // (neighbouring chunks are marked at the same time, and additions to one line of memory wait
+                                 // for each other: 138 M elements read only, one in 800 marked, 104 us side by side, 90 so)
+constexpr int kSlotWords = kSlotMcount + 1024 * kMcountLine;
+constexpr int kGuessMidAt = 8 * kHistBins;             // (k_guess_tiles: three histograms in copies' places)
 constexpr int kGuessOddAt = 9 * kHistBins;
+constexpr int kGuessLowAt = 10 * kHistBins;
 constexpr uint32_t kNoGuess = 0xffffffffu;             // no key reaches this bound
 constexpr int kGuessRun = 16;                          // consecutive elements per sample run
 constexpr uint32_t kKeyMask = 0x7fffffffu;
@@ -227,7 +229,7 @@ struct SegView {
   const uint2* tbuf;     // the vector's pieces, or nullptr
   const uint32_t* tcnt;  // marked elements per span
   int32_t tcap;          // entries per piece
-  const uint32_t* mcount;  // marked elements per chunk of the vector, or nullptr
+  const uint32_t* mcount;  // marked elements per chunk of the vector, kMcountLine words apart, or nullptr
   uint64_t* flags;
   uint32_t* S;
   uint32_t* chunk_off;
@@ -276,7 +278,7 @@ __device__ __forceinline__ uint64_t wave_allsum_u64(uint64_t v) {
 
 constexpr int kTile = 8192;       // chunk granularity (a quarter of a tile of the fused pass)
 constexpr int kMaxChunks = 1024;  // chunks per vector range
-static_assert(kSlotRefine == kSlotMcount + kMaxChunks, "one count per chunk");
+static_assert(kSlotWords == kSlotMcount + kMaxChunks * kMcountLine, "one count per chunk");
 constexpr int kPassTile = 32768;      // elements per block iteration of the streaming passes (1024 threads x 8 float4)
 constexpr int kMaxPassBlocks = 4096;  // blocks per worker of a streaming pass that strides over tiles
 
@@ -862,7 +864,7 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
   for (int64_t ti = bx; ti < ntiles; ti += nblk) {
     const int64_t qw = ti * TQ + wave_first;  // wave-uniform, so all 64 lanes stay together (the masks need that)
     const uint32_t marked = (ti + 1) * TQ <= q_hi ? tile(qw, std::true_type{}) : tile(qw, std::false_type{});
-    if (!PLAIN && lane == 0 && marked != 0u) atomicAdd(&mcount[(ti * TQ * 4) / chunk_elems], marked);
+    if (!PLAIN && lane == 0 && marked != 0u) atomicAdd(&mcount[(ti * TQ * 4) / chunk_elems * kMcountLine], marked);
   }
   // scalar tail (n not a multiple of 4): the first block
   if (bx == 0) {
@@ -875,7 +877,7 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
         va.seed1(STATS == 2 ? gj : v);
         va.add1(STATS == 2 ? gj : v);
       }
-      if (!PLAIN && !(__builtin_fabsf(v) < gf)) atomicAdd(&mcount[(n - 1) / chunk_elems], 1u);
+      if (!PLAIN && !(__builtin_fabsf(v) < gf)) atomicAdd(&mcount[(n - 1) / chunk_elems * kMcountLine], 1u);
     }
   }
 
@@ -1152,15 +1154,15 @@ k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_
     const uint32_t c = lh[b];
     if (c) atomicAdd(&ghist[b], c);
   }
-  __threadfence();
+  // (what this wave has added is there: see meet_arrive; a fence would write back and invalidate the cache for every wave)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {
-    last_sh = atomicAdd(&ctrl[0], 1u) == gridDim.x - 1 ? 1 : 0;
+    last_sh = __hip_atomic_fetch_add(&ctrl[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
     hit_sh = -1;
   }
   __syncthreads();
   if (!last_sh) return;
-  __threadfence();
   // the last block: suffix sums over the sample histogram, 16 consecutive bins per thread
   uint32_t h[16];
   uint32_t tot = 0u;
@@ -1607,7 +1609,7 @@ k_pick_mask(SelParams p, LeaderArgs la) {
   const uint32_t k = sv.d.k;
   const int nchunks = sv.d.geom.nchunks;
   const uint32_t gkey = sv.ctrl[1];
-  const uint32_t mine = (t < nchunks) ? sv.mcount[t] : 0u;
+  const uint32_t mine = (t < nchunks) ? sv.mcount[t * kMcountLine] : 0u;
   uint32_t total;
   const uint32_t upto = block_prefix_incl<1024>(mine, part, &total);
   // accepted if the bound holds at least k keys and not more than the list takes; a list far
@@ -2130,7 +2132,7 @@ k_mark_spans(PtrTable x, int64_t n, int64_t chunk_elems, uint32_t* __restrict__ 
                                      buf + (size_t)sp * (size_t)tiles.cap, (uint32_t)tiles.cap, nullptr);
     if (lane_id() == 0) {
       cnt[sp] = c;
-      if (c != 0u) atomicAdd(&slot[kSlotMcount + (sp * tiles.span) / chunk_elems], c);
+      if (c != 0u) atomicAdd(&slot[kSlotMcount + (sp * tiles.span) / chunk_elems * kMcountLine], c);
     }
   }
 }
@@ -3697,7 +3699,7 @@ k_tail(SelParams p, LeaderArgs la, int row_log2) {
     uint32_t m[PER], sum = 0u, total;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      m[j] = PER * tid + j < sv.d.geom.nchunks ? sv.mcount[PER * tid + j] : 0u;
+      m[j] = PER * tid + j < sv.d.geom.nchunks ? sv.mcount[(PER * tid + j) * kMcountLine] : 0u;
       sum += m[j];
     }
     uint32_t upto = block_prefix_incl<T>(sum, sh.part, &total) - sum;
@@ -4003,14 +4005,14 @@ k_guess_tiles(const float* __restrict__ gp, const float* __restrict__ rp, uint32
   tb.find(m_lo, res, top);
   sample_second(key, there, low.x, mid.x, lh);
   __syncthreads();
-  tile_flush<T>(lh[0], slot + kSlotRefine);
+  tile_flush<T>(lh[0], slot + kGuessLowAt);
   tile_flush<T>(lh[1], slot + kGuessMidAt);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) sh = __hip_atomic_fetch_add(&ctrl[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
   __syncthreads();
   if (sh == 0) return;
-  read(slot + kSlotRefine, nullptr);
+  read(slot + kGuessLowAt, nullptr);
   const bool ok = tb.find(m_hi - low.y, res, low2);
   read(slot + kGuessMidAt, nullptr);
   const bool ok_mid = tb.find(m_mid - mid.y, res, mid2);
