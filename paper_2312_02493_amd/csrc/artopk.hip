@@ -324,14 +324,15 @@ int stats_blocks(int num_cu, int32_t w, int64_t n) {
   return (int)nblk;
 }
 
+// Beyond twice the last-level cache (256 MiB) reads of w vectors of n elements are non-temporal (see k_stats).
+bool beyond_cache(int32_t w, int64_t n) { return (int64_t)w * n * 4 > ((int64_t)1 << 29); }
+
 // Launches the statistics of w vectors of n elements (k_stats; rows 16-byte aligned).
-template <bool SHIFT>
 void launch_stats(hipStream_t st, const PtrTable& x, int nblk, int32_t w, int64_t n, double* partials) {
-  // beyond twice the last-level cache (256 MiB) the loads are non-temporal (see the kernel)
-  if ((int64_t)w * n * 4 > ((int64_t)1 << 29))
-    hipLaunchKernelGGL((k_stats<SHIFT, true, true>), dim3(nblk, w), dim3(256), 0, st, x, n, partials);
+  if (beyond_cache(w, n))
+    hipLaunchKernelGGL(k_stats<true>, dim3(nblk, w), dim3(256), 0, st, x, n, partials);
   else
-    hipLaunchKernelGGL((k_stats<SHIFT, true, false>), dim3(nblk, w), dim3(256), 0, st, x, n, partials);
+    hipLaunchKernelGGL(k_stats<false>, dim3(nblk, w), dim3(256), 0, st, x, n, partials);
 }
 
 // A stage boundary (level 2 only).
@@ -1238,7 +1239,8 @@ int enqueue_topk_workers(artopk_ctx* c, const PtrTable& tab, int32_t w, int64_t 
   int nblk = (int)((k + 256 * 16 - 1) / (256 * 16));
   if (nblk < 1) nblk = 1;
   if (nblk > kMaxChunks) nblk = kMaxChunks;
-  hipLaunchKernelGGL((k_stats<false, false, false>), dim3(nblk, w), dim3(256), 0, c->stream, vtab, k, s.partials);
+  hipLaunchKernelGGL(k_squares<false>, dim3(nblk, w), dim3(256), 0, c->stream, vtab, (int64_t)0, 0, vtab, k, nblk, s.partials,
+                     s.partials);
   hipLaunchKernelGGL(k_sqnorm, dim3(1), dim3(1024), 0, c->stream, s.partials, nblk, (int)w, s.var_scratch,
                      sqnorm_out, s.leader_dev, argmax_out);
   HIP_TRY(c, hipGetLastError());
@@ -1655,7 +1657,7 @@ int artopk_variance(artopk_ctx* ctx, const float* const* x, int32_t w, int64_t n
   const PtrTable tab = make_table(x, w);
   const int nblk = stats_blocks(ctx->num_cu, w, n);
   Scratch& s = ctx->s;
-  launch_stats<true>(ctx->stream, tab, nblk, w, n, s.partials);
+  launch_stats(ctx->stream, tab, nblk, w, n, s.partials);
   hipLaunchKernelGGL(k_leader, dim3(1), dim3(1024), 0, ctx->stream, s.partials, (int)w, nblk, n, s.var_scratch,
                      var_out, s.leader_dev, argmax_out);
   HIP_TRY(ctx, hipGetLastError());
@@ -1726,7 +1728,7 @@ int artopk_variance_static(const float* const* x, int32_t w, int64_t n, double* 
   double* var_scratch = sd->ptr + kStaticPartials;
   int32_t* leader_word = reinterpret_cast<int32_t*>(sd->ptr + kStaticPartials + kMaxW);
   // every word of the scratch that is read is written first by these two launches: nothing to clear
-  launch_stats<true>(st, tab, nblk, w, n, partials);
+  launch_stats(st, tab, nblk, w, n, partials);
   hipLaunchKernelGGL(k_leader, dim3(1), dim3(1024), 0, st, partials, (int)w, nblk, n, var_scratch, var_out,
                      leader_word, argmax_out);
   const hipError_t e = hipGetLastError();
@@ -1850,10 +1852,15 @@ int artopk_compression_gain(artopk_ctx* ctx, const float* const* residual, int32
   if (nblk_vals > kMaxChunks / 2) nblk_vals = kMaxChunks / 2;
   // the two partial arrays share the variance scratch: residual partials first
   double* part_res = s.partials;
-  double* part_vals = s.partials + (size_t)ctx->max_w * (kMaxChunks / 2) * 2;
+  double* part_vals = s.partials + (size_t)ctx->max_w * (kMaxChunks / 2);
   const int nblk_res_c = nblk_res > kMaxChunks / 2 ? kMaxChunks / 2 : nblk_res;
-  launch_stats<false>(ctx->stream, rtab, nblk_res_c, w, n, part_res);
-  hipLaunchKernelGGL((k_stats<false, false, false>), dim3(nblk_vals, w), dim3(256), 0, ctx->stream, vtab, k, part_vals);
+  const dim3 grid((unsigned)(nblk_vals + nblk_res_c), (unsigned)w);
+  if (beyond_cache(w, n))
+    hipLaunchKernelGGL(k_squares<true>, grid, dim3(256), 0, ctx->stream, rtab, n, nblk_res_c, vtab, k, nblk_vals, part_res,
+                       part_vals);
+  else
+    hipLaunchKernelGGL(k_squares<false>, grid, dim3(256), 0, ctx->stream, rtab, n, nblk_res_c, vtab, k, nblk_vals, part_res,
+                       part_vals);
   hipLaunchKernelGGL(k_gain, dim3(1), dim3(1024), 0, ctx->stream, part_vals, nblk_vals, part_res, nblk_res_c, (int)w,
                      gain_out);
   HIP_TRY(ctx, hipGetLastError());

@@ -885,10 +885,8 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
 }
 
 // ---------------------------------------------------------------------------
-// k_stats : statistics of read-only vectors in float64.  grid = (nblk, W).
-//   SHIFT (variance): the block's (count, mean, sum of squared deviations), see VarAcc.
-//   !SHIFT (sum of squares): the block's sum of x and of x^2 to partials[w][b][0..1].
-// VEC reads float4 groups (rows must be 16-byte aligned).
+// k_stats : the variances' part of read-only vectors in float64, grid = (nblk, W): the block's (count, mean, sum of
+// squared deviations), see VarAcc.  Rows must be 16-byte aligned.
 //   NT: non-temporal loads, for vectors that together are larger than twice the last-level
 // cache: what earlier kernels left there (written and half-written lines) slowed ordinary
 // loads to 4.4 TB/s on 2 x 138 M elements behind a residual rewrite, non-temporal ones
@@ -896,77 +894,114 @@ k_pass_mark(PtrTable g, PtrTable res, int64_t n, int64_t chunk_elems, uint32_t* 
 // partly lie in the cache ordinary loads are the better ones (1 x 60 M behind a rewrite:
 // 54 against 92 us, 8 x 11.7 M 86 against 99, 1 x 138 M the same).
 // ---------------------------------------------------------------------------
-template <bool SHIFT, bool VEC, bool NT>
+template <bool NT>
 __global__ void __launch_bounds__(256)
 k_stats(PtrTable x, int64_t n, double* __restrict__ partials) {
-  __shared__ double red[3 * 4];
   const int w = blockIdx.y, bx = blockIdx.x, nblk = gridDim.x, tid = threadIdx.x;
   const float* __restrict__ xp = x.p[w];
-  const int64_t n4 = VEC ? (n >> 2) : 0;
-  VarAcc va;                 // SHIFT
-  double s = 0.0, ss = 0.0;  // !SHIFT
-  if (VEC) {
-    const int64_t tile = 256 * kPassAUnroll;
-    const int64_t ntile = (n4 + tile - 1) / tile;
-    for (int64_t t = bx; t < ntile; t += nblk) {
-      const int64_t q0 = t * tile + tid;
-      v4f a[kPassAUnroll];
+  const int64_t n4 = n >> 2;
+  VarAcc va;
+  const int64_t tile = 256 * kPassAUnroll;
+  const int64_t ntile = (n4 + tile - 1) / tile;
+  for (int64_t t = bx; t < ntile; t += nblk) {
+    const int64_t q0 = t * tile + tid;
+    v4f a[kPassAUnroll];
 #pragma unroll
-      for (int u = 0; u < kPassAUnroll; ++u) {
-        const int64_t q = q0 + u * 256;
-        if (q < n4) a[u] = load4<NT>(xp + 4 * q);
-      }
+    for (int u = 0; u < kPassAUnroll; ++u) {
+      const int64_t q = q0 + u * 256;
+      if (q < n4) a[u] = load4<NT>(xp + 4 * q);
+    }
 #pragma unroll
-      for (int u = 0; u < kPassAUnroll; ++u) {
-        const int64_t q = q0 + u * 256;
-        if (q < n4) {
-          if (SHIFT) {
-            if (u == 0) va.seed4(a[u]);
-            va.add4(a[u]);
-          } else {
-            const double d0 = (double)a[u].x, d1 = (double)a[u].y, d2 = (double)a[u].z, d3 = (double)a[u].w;
-            s += (d0 + d1) + (d2 + d3);
-            ss = fma(d0, d0, ss);
-            ss = fma(d1, d1, ss);
-            ss = fma(d2, d2, ss);
-            ss = fma(d3, d3, ss);
-          }
-        }
+    for (int u = 0; u < kPassAUnroll; ++u) {
+      const int64_t q = q0 + u * 256;
+      if (q < n4) {
+        if (u == 0) va.seed4(a[u]);
+        va.add4(a[u]);
       }
     }
   }
-  // elements not covered by whole float4 groups (all of them when the row is not 16-byte aligned)
+  // elements not covered by whole float4 groups
   for (int64_t j = n4 * 4 + (int64_t)bx * 256 + tid; j < n; j += (int64_t)nblk * 256) {
-    if (SHIFT) {
-      va.seed1(xp[j]);
-      va.add1(xp[j]);
-    } else {
-      const double d = (double)xp[j];
-      s += d;
-      ss = fma(d, d, ss);
-    }
+    va.seed1(xp[j]);
+    va.add1(xp[j]);
   }
-  if (SHIFT) {
-    block_moments<256>(va, partials, w, nblk, bx);
-  } else {
-    s = wave_sum(s);
-    ss = wave_sum(ss);
-    if ((tid & 63) == 0) {
-      red[tid >> 6] = s;
-      red[4 + (tid >> 6)] = ss;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      partials[((size_t)w * nblk + bx) * 2 + 0] = (red[0] + red[1]) + (red[2] + red[3]);
-      partials[((size_t)w * nblk + bx) * 2 + 1] = (red[4] + red[5]) + (red[6] + red[7]);
-    }
-  }
+  block_moments<256>(va, partials, w, nblk, bx);
 }
 
 // ---------------------------------------------------------------------------
-// k_gain : one block.  gain_w = V_w / (V_w + R_w) with V_w, R_w the sums of
-// squares (second partial of every block) of worker w's gathered values and of
-// its residual after the step; the two have disjoint support, so V_w + R_w is
+// k_squares : sums of squares in float64 of w short rows of k values (of any alignment), which nfew blocks a row take, and
+// in the blocks behind them of w vectors of n elements (16-byte aligned), which nblk take; part_few[w][nfew] and
+// part_vec[w][nblk].  NT as in k_stats.  In one launch the rows are summed beside the vectors, and eight values a thread
+// are on their way at a time: 2 x 138 M and 2 x 1.4 M 198 + 9 us in two, now 199; eight rows of 256 thousand 6.9 us one
+// value after the other, now 4.8.  The long vectors are bound by memory (5.6 TB/s behind the residual rewrite).
+// ---------------------------------------------------------------------------
+template <bool NT>
+__global__ void __launch_bounds__(256)
+k_squares(PtrTable x, int64_t n, int nblk, PtrTable few, int64_t k, int nfew, double* __restrict__ part_vec,
+          double* __restrict__ part_few) {
+  __shared__ double red[4];
+  const int w = blockIdx.y, tid = threadIdx.x;
+  const bool rows = (int)blockIdx.x < nfew;
+  const int bx = rows ? (int)blockIdx.x : (int)blockIdx.x - nfew, blocks = rows ? nfew : nblk;
+  const float* __restrict__ xp = rows ? few.p[w] : x.p[w];
+  const int64_t len = rows ? k : n;
+  const int64_t n4 = rows ? 0 : n >> 2;
+  double ss = 0.0;
+  auto add = [&](float v) {
+    const double d = (double)v;
+    ss = fma(d, d, ss);
+  };
+  const int64_t tile = 256 * kPassAUnroll;
+  const int64_t ntile = (n4 + tile - 1) / tile;
+  for (int64_t t = bx; t < ntile; t += blocks) {
+    const int64_t q0 = t * tile + tid;
+    v4f a[kPassAUnroll];
+#pragma unroll
+    for (int u = 0; u < kPassAUnroll; ++u) {
+      const int64_t q = q0 + u * 256;
+      if (q < n4) a[u] = load4<NT>(xp + 4 * q);
+    }
+#pragma unroll
+    for (int u = 0; u < kPassAUnroll; ++u) {
+      if (q0 + u * 256 < n4) {
+        add(a[u].x);
+        add(a[u].y);
+        add(a[u].z);
+        add(a[u].w);
+      }
+    }
+  }
+  const int64_t step = (int64_t)blocks * 256;
+  for (int64_t j = n4 * 4 + (int64_t)bx * 256 + tid; j < len; j += 8 * step) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = xp[j + u * step < len ? j + u * step : j];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (j + u * step < len) add(v[u]);
+  }
+  ss = wave_sum(ss);
+  if ((tid & 63) == 0) red[tid >> 6] = ss;
+  __syncthreads();
+  if (tid == 0) (rows ? part_few : part_vec)[(size_t)w * blocks + bx] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Sum of `count` partial sums; the 64 lanes of a wave call it, lane 0 has the result.
+__device__ __forceinline__ double wave_total(const double* __restrict__ part, int count) {
+  double v = 0.0;
+  for (int b = threadIdx.x & 63; b < count; b += 512) {  // eight in flight
+    double q[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) q[u] = part[b + 64 * u < count ? b + 64 * u : b];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += b + 64 * u < count ? q[u] : 0.0;
+  }
+  return wave_sum(v);
+}
+
+// ---------------------------------------------------------------------------
+// k_gain : one block.  gain_w = V_w / (V_w + R_w) with V_w, R_w the sums of squares of worker w's
+// gathered values and of its residual after the step; the two have disjoint support, so V_w + R_w is
 // the squared norm of the error-fed gradient.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(1024)
@@ -974,27 +1009,22 @@ k_gain(const double* __restrict__ part_vals, int nblk_vals, const double* __rest
        int w_count, double* __restrict__ gain_out) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int w = wave; w < w_count; w += 16) {
-    double v = 0.0, r = 0.0;
-    for (int b = lane; b < nblk_vals; b += 64) v += part_vals[((size_t)w * nblk_vals + b) * 2 + 1];
-    for (int b = lane; b < nblk_res; b += 64) r += part_res[((size_t)w * nblk_res + b) * 2 + 1];
-    v = wave_sum(v);
-    r = wave_sum(r);
+    const double v = wave_total(part_vals + (size_t)w * nblk_vals, nblk_vals);
+    const double r = wave_total(part_res + (size_t)w * nblk_res, nblk_res);
     if (lane == 0) gain_out[w] = (v + r > 0.0) ? v / (v + r) : 0.0;
   }
 }
 
 // ---------------------------------------------------------------------------
-// k_sqnorm : one block.  out[w] = sum of the second partials (sums of squares)
-// of vector w; argmax = first w with the largest value (also stored as leader).
+// k_sqnorm : one block.  out[w] = sum of the partial sums of squares of vector w;
+// argmax = first w with the largest value (also stored as leader).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(1024)
 k_sqnorm(const double* __restrict__ part, int nblk, int w_count, double* __restrict__ scratch,
          double* __restrict__ out, int32_t* __restrict__ leader_dev, int32_t* __restrict__ argmax_out) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int w = wave; w < w_count; w += 16) {
-    double v = 0.0;
-    for (int b = lane; b < nblk; b += 64) v += part[((size_t)w * nblk + b) * 2 + 1];
-    v = wave_sum(v);
+    const double v = wave_total(part + (size_t)w * nblk, nblk);
     if (lane == 0) {
       scratch[w] = v;
       if (out) out[w] = v;
@@ -5071,10 +5101,14 @@ k_gather(PtrTable tab, int w_count, int64_t n, const int32_t* __restrict__ idx, 
   if (sum) sum[m] = s;
 }
 
+// ---------------------------------------------------------------------------
+// k_zero_at : +0.0 at the kept indices of every worker, from the last ones on: a gather that went before has left the lines
+// of those in the last-level cache (2 x 2.8 M of 138 M, the whole exchange 440 us forwards, 435 backwards).
+// ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 k_zero_at(PtrTable tab, int w_count, int64_t n, const int32_t* __restrict__ idx, int64_t k,
           uint32_t* __restrict__ err) {
-  const int64_t m = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t m = (int64_t)(gridDim.x - 1u - blockIdx.x) * 256 + threadIdx.x;
   if (m >= k) return;
   const int64_t i = (int64_t)idx[m];
   if (i < 0 || i >= n) {

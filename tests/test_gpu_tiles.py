@@ -1,6 +1,6 @@
 """GPU parity of the selection by marked tiles (k_mark_tiles and what follows it): flat steps whose leader is known up
 front, and segments, bit for bit against the oracle.  The length from which it is used is lowered through
-ARTOPK_OPT_GUESS_MIN_N; the sizes lie around a tile's 32768 elements, its groups of four and the sixteen tiles of a block,
+ARTOPK_OPT_GUESS_MIN_N; the sizes lie around a tile's 16384 elements, pairs and groups of tiles and a float4 group,
 and the values are those for which a sampled bound, a tile's piece or the narrow bins do not do."""
 
 import numpy as np
