@@ -266,14 +266,36 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;  // valid in lane 0
 }
 
+// What the lanes that CTRL names hold, in the rows (of 16 lanes) that ROWS names; 0 where there is no such lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t from_lanes(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t from_lanes(uint64_t v) {
+  return ((uint64_t)from_lanes<CTRL, ROWS>((uint32_t)(v >> 32)) << 32) | from_lanes<CTRL, ROWS>((uint32_t)v);
+}
+
+// Inclusive prefix sums over the 64 lanes of a wave, all of which call it: 1, 2, 4 and 8 lanes down inside each row, then
+// each odd row takes the last lane of the row before it, and the upper half the last lane of the lower.  Lanes read each
+// other's registers; by way of on-chip memory (shuffles) each of the six steps waits for
+// it: a step on 65537 x 2 took 18.4 us so, now 17.3, 1 M x 4 27.9 and 27.3, a selection of 138 M 163.9 and 162.4.
+template <typename V>
+__device__ __forceinline__ V wave_incl_scan(V v) {
+  v += from_lanes<0x111, 0xf>(v);
+  v += from_lanes<0x112, 0xf>(v);
+  v += from_lanes<0x114, 0xf>(v);
+  v += from_lanes<0x118, 0xf>(v);
+  v += from_lanes<0x142, 0xa>(v);
+  v += from_lanes<0x143, 0xc>(v);
+  return v;
+}
+// What the last lane holds.
+__device__ __forceinline__ uint32_t wave_last(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+
 __device__ __forceinline__ uint64_t wave_allsum_u64(uint64_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    uint32_t lo = __shfl_xor((uint32_t)v, off, 64);
-    uint32_t hi = __shfl_xor((uint32_t)(v >> 32), off, 64);
-    v += ((uint64_t)hi << 32) | lo;
-  }
-  return v;  // the total, in every lane
+  v = wave_incl_scan(v);
+  return ((uint64_t)wave_last((uint32_t)(v >> 32)) << 32) | wave_last((uint32_t)v);  // the total, in every lane
 }
 
 constexpr int kTile = 8192;       // chunk granularity (a quarter of a tile of the fused pass)
@@ -469,20 +491,15 @@ __device__ __forceinline__ float load1g(const float* base, int64_t e) {
   return widen16<GT>(reinterpret_cast<const unsigned short*>(base)[e]);
 }
 
-// Block-wide inclusive scans of one word per thread: a shuffle scan inside each
+// Block-wide inclusive scans of one word per thread: a scan inside each
 // wave, then the wave totals through `wtot` (T/64 words of shared memory that no
 // thread still reads on entry).  Two barriers; `wtot` is free again on return.
 // The exclusive value is the result minus the thread's own word.
 template <int T>
 __device__ __forceinline__ uint32_t block_suffix_incl(uint32_t v, uint32_t* wtot, uint32_t* total = nullptr) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t s = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t x = __shfl_down(s, off, 64);
-    if (lane + off < 64) s += x;
-  }
-  if (lane == 0) wtot[wave] = s;
+  const uint32_t incl = wave_incl_scan(v), all = wave_last(incl), s = all - incl + v;
+  if (lane == 0) wtot[wave] = all;
   __syncthreads();
   uint32_t add = 0u, tot = 0u;
 #pragma unroll
@@ -499,12 +516,7 @@ __device__ __forceinline__ uint32_t block_suffix_incl(uint32_t v, uint32_t* wtot
 template <int T>
 __device__ __forceinline__ uint32_t block_prefix_incl(uint32_t v, uint32_t* wtot, uint32_t* total = nullptr) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t s = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t x = __shfl_up(s, off, 64);
-    if (lane >= off) s += x;
-  }
+  const uint32_t s = wave_incl_scan(v);
   if (lane == 63) wtot[wave] = s;
   __syncthreads();
   uint32_t add = 0u, tot = 0u;
@@ -764,17 +776,6 @@ k_pass_a(PtrTable g, PtrTable res, int64_t n, ChunkGeom geom, int hist_worker, u
 //   (zero, but for Inf and NaN) stay: without them the same pass streamed slower on
 //   8 x 1e9 elements, 16.6 against 16.1 ms.
 // ---------------------------------------------------------------------------
-// Inclusive prefix sums over the 64 lanes of a wave.
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t x = __shfl_up(v, off, 64);
-    if (lane >= off) v += x;
-  }
-  return v;
-}
-
 // First of the four mask words of row `row` (256 elements) of a vector: tiles of 128 rows, inside a
 // tile row r belongs to wave r mod 16 as its (r / 16)-th row.
 __device__ __forceinline__ int64_t mask_word(int64_t row) {
@@ -1202,12 +1203,8 @@ k_guess(PtrTable g, PtrTable res, uint32_t* __restrict__ slots, int runs, int64_
     tot += h[j];
   }
   // inclusive suffix sum of tot over the 64 lanes, then over the 4 waves
-  uint32_t suf = tot;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t x = __shfl_down(suf, off, 64);
-    if ((tid & 63) + off < 64) suf += x;
-  }
+  const uint32_t incl = wave_incl_scan(tot);
+  const uint32_t suf = wave_last(incl) - incl + tot;
   if ((tid & 63) == 0) wsum[tid >> 6] = suf;
   __syncthreads();
   uint32_t above = suf - tot;  // bins of higher threads in this wave
@@ -2199,7 +2196,7 @@ __device__ __forceinline__ void compact_spans_body(const SelParams& p) {
     const int ns = (int)(s_hi - s0 < 64 ? s_hi - s0 : 64);
     const uint32_t mine = lane < ns ? sv.tcnt[s0 + lane] : 0u;  // (every wave scans the counts itself)
     const uint32_t incl = wave_incl_scan(mine);
-    const uint32_t total = __shfl(incl, 63, 64);
+    const uint32_t total = wave_last(incl);
     const uint64_t over = __ballot(mine > piece);
     __syncthreads();  // pre is free, and the histogram cleared
     if (wave == 0) {
@@ -3520,14 +3517,8 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
           }
           uint64_t all = real ? pool.kept.all[lane] : 0ull, own = mine_q;
           const uint64_t all0 = all;
-#pragma unroll
-          for (int off = 1; off < 64; off <<= 1) {
-            const uint64_t ya = __shfl_up(all, off, 64), yo = __shfl_up(own, off, 64);
-            if (lane >= off) {
-              all += ya;
-              own += yo;
-            }
-          }
+          all = wave_incl_scan(all);
+          own = wave_incl_scan(own);
           front += all - all0;
           own -= mine_q;
           if (real)
@@ -5463,7 +5454,7 @@ k_sum_update(const float* __restrict__ vals, int w_count, int64_t n, const int32
 // ---------------------------------------------------------------------------
 // k_small_step : a whole flat step on a short vector in one launch.  Bound by latency: three launches, each a chain of
 // trips to memory between a start and an end, took 30.6 us on 65537 elements x 2 workers and 55 on 1 M x 4; here the
-// blocks wait for each other in between, which takes a microsecond, and the same steps take 19.9 and 27.5.
+// blocks wait for each other in between, which takes a microsecond, and the same steps take 17.3 and 27.3.
 //   A block has one chunk of 8 T elements, of every worker, and takes it from the gradients to the outputs:
 //     acc = g + residual, the counts of the leader's (every worker's, where the leader comes from the data) top digits;
 //     all blocks are through with that: threshold digit (every block picks it for itself), the candidates' second digits;
@@ -5491,6 +5482,8 @@ constexpr int kSmallLine = 32;        // words between counters
 // step; two sets of three waits' counters
 constexpr int kCtrStep = 0, kCtrHelped = kSmallLine, kCtrLate = 2 * kSmallLine, kCtrArrive = 3 * kSmallLine,
               kCtrSet = 3 * kMeetWait, kSmallCtr = kCtrArrive + 2 * kCtrSet;
+// Few candidates: so many of the vector's, in so many chunks at most (a lane each), are handed on themselves.
+constexpr int kSmallFew = 2048, kSmallFewChunks = 64, kSmallRows = kSmallMaxChunks * 128;
 // What select_info reports as many candidates (no route depends on it).
 __host__ __device__ constexpr uint32_t small_few(int64_t n) { return 10240u + 240u * (uint32_t)((n + kTile - 1) / kTile); }
 
@@ -5503,7 +5496,7 @@ struct SmallScratch {
   uint32_t* dig2;   // [2][kSmallReps][128] last digits of those that are left then
   // written before they are read in every step
   uint32_t* above;  // [kSmallMaxChunks] a chunk's keys above those
-  uint32_t* rows;   // [kSmallMaxChunks][128] a chunk's of those: with that last digit or a higher one
+  uint32_t* rows;   // [kSmallMaxChunks][128] a chunk's of those: with that last digit or a higher one; or its candidates
 };
 
 struct SmallStep {
@@ -5577,6 +5570,7 @@ k_small_step(SmallStep a) {
   __shared__ double var_sh[STATS ? kMaxW : 1];
   __shared__ __attribute__((aligned(16))) uint32_t tail[128];
   __shared__ uint16_t owned[kSmallMaxChunks];
+  __shared__ uint32_t few[kSmallFew];
   __shared__ int verdict;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -5788,7 +5782,23 @@ k_small_step(SmallStep a) {
   }
   const float* lx = a.res.p[lead];
 
-  // picks digit `digit` of the threshold from `reps` copies of its histogram
+  // picks digit `digit` of the threshold from the counts in `pool`
+  auto pick_here = [&](int digit) __attribute__((always_inline)) {
+    __syncthreads();
+    uint32_t h[BPT];
+#pragma unroll
+    for (int j = 0; j < BPT / 4; ++j) {
+      uint4* const mine = reinterpret_cast<uint4*>(pool) + (BPT / 4) * tid + j;
+      const uint4 q = *mine;
+      h[4 * j + 0] = q.x;
+      h[4 * j + 1] = q.y;
+      h[4 * j + 2] = q.z;
+      h[4 * j + 3] = q.w;
+      *mine = make_uint4(0u, 0u, 0u, 0u);
+    }
+    block_pick_bins<T>(st, h, digit, part, a.err);
+  };
+  // the same from `reps` copies of its histogram
   auto pick = [&](const uint32_t* __restrict__ hist, auto digit_tag) __attribute__((always_inline)) {
     constexpr int digit = decltype(digit_tag)::value, pairs = (int)(digit_mask(digit) + 1u) / 2;
     // neighbouring lanes read neighbouring bins, all of a copy's loads together; `pool` hands them to the bins' owners
@@ -5807,19 +5817,7 @@ k_small_step(SmallStep a) {
 #pragma unroll
     for (int j = 0; j < J; ++j)
       if (pairs >= T || tid < pairs) reinterpret_cast<uint64_t*>(pool)[j * T + tid] = sum[j];
-    __syncthreads();
-    uint32_t h[BPT];
-#pragma unroll
-    for (int j = 0; j < BPT / 4; ++j) {
-      uint4* const mine = reinterpret_cast<uint4*>(pool) + (BPT / 4) * tid + j;
-      const uint4 q = *mine;
-      h[4 * j + 0] = q.x;
-      h[4 * j + 1] = q.y;
-      h[4 * j + 2] = q.z;
-      h[4 * j + 3] = q.w;
-      *mine = make_uint4(0u, 0u, 0u, 0u);
-    }
-    block_pick_bins<T>(st, h, digit, part, a.err);
+    pick_here(digit);
   };
   // the leader's elements of chunk c in `raw`
   auto take = [&](int c) __attribute__((always_inline)) {
@@ -5859,81 +5857,191 @@ k_small_step(SmallStep a) {
   pick(ss.hist + (known ? 0 : (size_t)lead * kSmallReps * kHistBins), std::integral_constant<int, 0>{});
   const uint32_t cand0 = st.cand, list0 = st.n_gt + st.cand;  // (reported)
 
-  for (int i = 0; i < n_owned; ++i) {
-    const int c = owned[i];
-    take(c);
-    const int64_t left = n - ((int64_t)c * C + 8 * tid);
-    const uint32_t lo = st.lo, hi = st.hi;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t kk = raw[e] & kKeyMask;
-      if (e < left && kk >= lo && kk <= hi) atomicAdd(&pool[(kk >> 7) & 0xfffu], 1u);
-    }
-    small_flush<T>(pool, ss.dig1 + (size_t)(c % a.reps) * kHistBins);
-    meet_arrive(meet, 1, c);
-  }
-  more((2 * rest + 2) / 3);
-  if (!meet_wait(meet, 1, nchunks, meet_limit(), verdict)) {
-    if (tid == 0) atomicOr(a.err, kErrWait);
-    return;
-  }
-  pick(ss.dig1, std::integral_constant<int, 1>{});
-
-  for (int i = 0; i < n_owned; ++i) {
-    const int c = owned[i];
-    take(c);
-    const int64_t left = n - ((int64_t)c * C + 8 * tid);
-    const uint32_t lo = st.lo, hi = st.hi;
-    uint32_t up = 0u;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t kk = raw[e] & kKeyMask;
-      up += e < left && kk > hi ? 1u : 0u;
-      if (e < left && kk >= lo && kk <= hi) atomicAdd(&tail[kk & 0x7fu], 1u);
-    }
-    uint32_t all = 0u;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) all += (uint32_t)__popcll(__ballot((up >> b) & 1u)) << b;
-    if (lane == 0) part[wave] = all;
-    __syncthreads();
-    if (wave == 0) {  // lane's digits 2 lane and 2 lane + 1
-      const uint32_t t0 = tail[2 * lane], t1 = tail[2 * lane + 1];
-      uint32_t* __restrict__ d2 = dig2 + (size_t)(c % a.reps) * 128;
-      if (t0) atomicAdd(&d2[2 * lane], t0);
-      if (t1) atomicAdd(&d2[2 * lane + 1], t1);
-      uint32_t s = t0 + t1;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t x = __shfl_down(s, off, 64);
-        if (lane + off < 64) s += x;
-      }
-      store_through(reinterpret_cast<uint64_t*>(ss.rows + (size_t)c * 128) + lane, ((uint64_t)(s - t0) << 32) | s);
-      tail[2 * lane] = tail[2 * lane + 1] = 0u;
-      if (lane == 0) {
-        uint32_t sum = 0u;
-#pragma unroll
-        for (int v = 0; v < WAVES; ++v) sum += part[v];
-        store_through(&ss.above[c], sum);
-      }
-    }
-    meet_arrive(meet, 2, c);
-  }
   // every block has read the top digits' histograms; each clears its share
-  {
+  auto clear_top = [&]() __attribute__((always_inline)) {
     uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.hist);
     const int words4 = (known ? 1 : w_count) * kSmallReps * (kHistBins / 4);
     for (int i = 0; i < n_owned; ++i)
       for (int q = (int)owned[i] * T + tid; q < words4; q += nchunks * T) z[q] = make_uint4(0u, 0u, 0u, 0u);
-  }
-  more(rest);
+  };
   uint32_t helped = 0u;  // (of the block that reports, thread 0; all chunks have been taken when it looks)
-  if (reports && tid == 0) helped = load_through(&ss.ctr[kCtrHelped]);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the block gathers from its workers' sums)
-  if (!meet_wait(meet, 2, nchunks, meet_limit(), verdict)) {
-    if (tid == 0) atomicOr(a.err, kErrWait);
-    return;
+  auto last_wait = [&](int wait) __attribute__((always_inline)) {
+    more(rest);
+    if (reports && tid == 0) helped = load_through(&ss.ctr[kCtrHelped]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the block gathers from its workers' sums)
+    const bool ok = meet_wait(meet, wait, nchunks, meet_limit(), verdict);
+    if (!ok && tid == 0) atomicOr(a.err, kErrWait);
+    return ok;
+  };
+  // Few candidates, all known when the top digits are: each chunk hands on its own instead of their digits' counts, and every
+  // block picks both digits from them: one wait less, and no 16 KB to read (65537 x 2, one in a hundred, 570 candidates in
+  // 17 chunks: 19.4 us with counts, 18.4 so with both digits counted on chip, 17.3 with the last from up to 64 keys in
+  // registers and scans by lanes).  The line is where a chunk's share of `rows` takes all of them, whosever they are.
+  const int row_words = kSmallRows / nchunks;
+  const bool by_keys = nchunks <= kSmallFewChunks && cand0 < (uint32_t)row_words && cand0 <= (uint32_t)kSmallFew;
+  uint32_t few_at = 0u, few_over = 0u;  // of chunk `lane`: its first candidate in `few`, and how many keys lie above them
+  if (by_keys) {
+    for (int i = 0; i < n_owned; ++i) {
+      const int c = owned[i];
+      take(c);
+      const int64_t left = n - ((int64_t)c * C + 8 * tid);
+      const uint32_t lo = st.lo, hi = st.hi;
+      uint32_t is = 0u, up = 0u;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t kk = raw[e] & kKeyMask;
+        up += e < left && kk > hi ? 1u : 0u;
+        is |= e < left && kk >= lo && kk <= hi ? 1u << e : 0u;
+      }
+      const uint32_t cnt = (uint32_t)__popc(is);
+      uint32_t at = 1u, tot = 0u;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const uint64_t pc = __ballot((cnt >> b) & 1u), pu = __ballot((up >> b) & 1u);
+        at += popc_lt(pc) << b;
+        tot += ((uint32_t)__popcll(pc) << b) + ((uint32_t)__popcll(pu) << (b + 16));
+      }
+      if (lane == 0) part[wave] = tot;
+      __syncthreads();
+      uint32_t sum = 0u;
+#pragma unroll
+      for (int v = 0; v < WAVES; ++v) {
+        at += v < wave ? part[v] & 0xffffu : 0u;
+        sum += part[v];
+      }
+      uint32_t* __restrict__ row = ss.rows + (size_t)c * row_words;
+      if (tid == 0) store_through(row, sum);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if ((is >> e) & 1u) store_through(row + at++, raw[e] & kKeyMask);
+      meet_arrive(meet, 1, c);
+    }
+    if (!last_wait(1)) return;
+    // (a row's first 64 candidates are on their way before it is known how many there are)
+    constexpr int R = kSmallFewChunks / WAVES;
+    const uint32_t head = lane < nchunks ? load_through(ss.rows + lane * row_words) : 0u;
+    uint32_t q[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int c = wave + r * WAVES;
+      q[r] = c < nchunks ? load_through(ss.rows + c * row_words + 1 + lane) : 0u;
+    }
+    const uint32_t have = (head & 0xffffu) < (uint32_t)row_words ? head & 0xffffu : 0u;
+    few_over = head >> 16;
+    few_at = wave_incl_scan(have) - have;
+    auto put = [&](uint32_t at, uint32_t kk) __attribute__((always_inline)) {
+      if (at < (uint32_t)kSmallFew) few[at] = kk;
+      atomicAdd(&pool[(kk >> 7) & 0xfffu], 1u);
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int c = wave + r * WAVES;
+      if (c < nchunks) {
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)have, c);
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)few_at, c);
+        if ((uint32_t)lane < cnt) put(at + lane, q[r]);
+        for (uint32_t e = 64u + lane; e < cnt; e += 64u) put(at + e, load_through(ss.rows + c * row_words + 1 + e));
+      }
+    }
+    pick_here(1);
+    clear_top();
+    const uint32_t lo = st.lo, hi = st.hi, left = st.cand, need = st.need;
+    if (left <= 64u) {  // (nearly always: a lane takes one and counts those above and beside it)
+      for (uint32_t e = (uint32_t)tid; e < cand0; e += T) {
+        const uint32_t kk = few[e];
+        if (kk >= lo && kk <= hi) {
+          const uint32_t at = atomicAdd(&tail[64], 1u);
+          if (at < 64u) tail[at] = kk;
+        }
+      }
+      __syncthreads();
+      if (wave == 0) {
+        const bool real = (uint32_t)lane < left;
+        const uint32_t mine = real ? tail[lane] : 0u;
+        uint32_t over = 0u, same_key = 0u;
+        for (int i = 0; i < (int)same(left); ++i) {
+          const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
+          over += x > mine ? 1u : 0u;
+          same_key += x == mine ? 1u : 0u;
+        }
+        const uint64_t hit = __ballot(real && over < need && need <= over + same_key);
+        if (lane == 0 && hit == 0ull) atomicOr(a.err, kErrPick);
+        if (hit != 0ull && lane == __builtin_ctzll(hit)) {
+          st.lo = st.hi = mine;
+          st.n_gt += over;
+          st.need = need - over;
+          st.cand = same_key;
+          st.level = 3u;
+        }
+      }
+      __syncthreads();
+    } else {
+      for (uint32_t e = (uint32_t)tid; e < cand0; e += T) {
+        const uint32_t kk = few[e];
+        if (kk >= lo && kk <= hi) atomicAdd(&pool[kk & 0x7fu], 1u);
+      }
+      pick_here(2);
+    }
+  } else {
+    for (int i = 0; i < n_owned; ++i) {
+      const int c = owned[i];
+      take(c);
+      const int64_t left = n - ((int64_t)c * C + 8 * tid);
+      const uint32_t lo = st.lo, hi = st.hi;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t kk = raw[e] & kKeyMask;
+        if (e < left && kk >= lo && kk <= hi) atomicAdd(&pool[(kk >> 7) & 0xfffu], 1u);
+      }
+      small_flush<T>(pool, ss.dig1 + (size_t)(c % a.reps) * kHistBins);
+      meet_arrive(meet, 1, c);
+    }
+    more((2 * rest + 2) / 3);
+    if (!meet_wait(meet, 1, nchunks, meet_limit(), verdict)) {
+      if (tid == 0) atomicOr(a.err, kErrWait);
+      return;
+    }
+    pick(ss.dig1, std::integral_constant<int, 1>{});
+
+    for (int i = 0; i < n_owned; ++i) {
+      const int c = owned[i];
+      take(c);
+      const int64_t left = n - ((int64_t)c * C + 8 * tid);
+      const uint32_t lo = st.lo, hi = st.hi;
+      uint32_t up = 0u;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t kk = raw[e] & kKeyMask;
+        up += e < left && kk > hi ? 1u : 0u;
+        if (e < left && kk >= lo && kk <= hi) atomicAdd(&tail[kk & 0x7fu], 1u);
+      }
+      uint32_t all = 0u;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) all += (uint32_t)__popcll(__ballot((up >> b) & 1u)) << b;
+      if (lane == 0) part[wave] = all;
+      __syncthreads();
+      if (wave == 0) {  // lane's digits 2 lane and 2 lane + 1
+        const uint32_t t0 = tail[2 * lane], t1 = tail[2 * lane + 1];
+        uint32_t* __restrict__ d2 = dig2 + (size_t)(c % a.reps) * 128;
+        if (t0) atomicAdd(&d2[2 * lane], t0);
+        if (t1) atomicAdd(&d2[2 * lane + 1], t1);
+        const uint32_t incl = wave_incl_scan(t0 + t1);
+        const uint32_t s = wave_last(incl) - incl + t0 + t1;
+        store_through(reinterpret_cast<uint64_t*>(ss.rows + (size_t)c * 128) + lane, ((uint64_t)(s - t0) << 32) | s);
+        tail[2 * lane] = tail[2 * lane + 1] = 0u;
+        if (lane == 0) {
+          uint32_t sum = 0u;
+#pragma unroll
+          for (int v = 0; v < WAVES; ++v) sum += part[v];
+          store_through(&ss.above[c], sum);
+        }
+      }
+      meet_arrive(meet, 2, c);
+    }
+    clear_top();
+    if (!last_wait(2)) return;
+    pick(dig2, std::integral_constant<int, 2>{});
   }
-  pick(dig2, std::integral_constant<int, 2>{});
   if (reports && tid == 0) {
     SelState out = st;
     out.many = cand0 > small_few(n) ? 1u : 0u;
@@ -5942,7 +6050,7 @@ k_small_step(SmallStep a) {
     *a.st = out;
     if (st.level != 3u) atomicOr(a.err, kErrSequence);
   }
-  {
+  if (!by_keys) {
     uint4* __restrict__ z = reinterpret_cast<uint4*>(ss.dig1);
     for (int i = 0; i < n_owned; ++i)
       for (int q = (int)owned[i] * T + tid; q < kSmallReps * (kHistBins / 4); q += nchunks * T)
@@ -5957,7 +6065,12 @@ k_small_step(SmallStep a) {
     const int c = owned[i];
     // kept in front of the chunk: keys above the threshold, and at it
     uint64_t before = 0ull;
-    if (tid < c) {
+    if (by_keys) {
+      if (tid < c) before = (uint64_t)few_over << 32;  // (fewer chunks than a wave has lanes)
+      const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)few_at, same(c));
+      for (uint32_t e = (uint32_t)tid; e < upto && e < (uint32_t)kSmallFew; e += T)
+        before += few[e] > khi ? 1ull << 32 : few[e] >= klo ? 1ull : 0ull;
+    } else if (tid < c) {
       const uint32_t* __restrict__ row = ss.rows + (size_t)tid * 128 + digit;
       const uint32_t at = load_through(row), over = digit < 127u ? load_through(row + 1) : 0u;
       before = ((uint64_t)(load_through(&ss.above[tid]) + over) << 32) | (at - over);

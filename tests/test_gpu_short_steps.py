@@ -275,3 +275,37 @@ def test_narrow_steps_on_several_streams_beside_other_work():
             assert torch.equal(i, iw) and torch.equal(v.view(torch.int32), vw.view(torch.int32))
         for r, rw in zip(c["res"], alone["res"]):
             assert torch.equal(r.view(torch.int32), rw.view(torch.int32))
+
+
+# As many values share the threshold's top digit as a chunk's share of the memory for them just takes, or one more; one,
+# sixteen and sixty-four chunks, and a chunk too many.
+@pytest.mark.parametrize("n,room", [(4001, 2048), (65_536, 2047), (1 << 18, 511), ((1 << 18) + 1, 500)])
+@pytest.mark.parametrize("kind", ["spread", "one_chunk", "equal", "last_digit"])
+def test_short_steps_with_few_candidates(n, room, kind):
+    rng = np.random.default_rng(n + len(kind))
+    w, top = 3, 7
+    runner = GpuRunner(w, n, top + room + 1)
+    for step_no, m in enumerate([room - 1, room, room + 1, 65, 64, 1]):
+        for mode in (orc.MODE_STAR, orc.MODE_VAR):
+            def vector(r):
+                x = (rng.standard_normal(n) * 0.01).astype(np.float32)
+                at = rng.permutation(n if kind != "one_chunk" else min(n, 4096))[:m + top]
+                v = 1.0 + rng.random(m + top) * 0.06
+                if kind == "equal":
+                    v[:] = 1.03
+                elif kind == "last_digit":
+                    v = 1.03125 + rng.integers(0, 128, m + top) * 2.0 ** -23
+                v[m:] = 2.0 + rng.random(top)
+                x[at] = (v * rng.choice([-1.0, 1.0], m + top)).astype(np.float32)
+                if r == 1:
+                    x[at[m:]] *= 3.0  # the variance rule's leader
+                return x
+
+            g, res = [vector(r) for r in range(w)], [np.zeros(n, np.float32) for _ in range(w)]
+            k = top + max(1, (m * (1 + step_no % 3)) // 3)
+            want = orc.step(g, res, k, mode, step_no=step_no)
+            assert mode == orc.MODE_STAR or gpu_util.top_two_gap(want.variances) > 1e-4
+            runner.load_g(g)
+            runner.load_res(res)
+            assert_step_matches(runner.step(k, mode, step_no), want, mode)
+            assert gpu_util.FORCED or runner.ctx.select_info()["short"] == 1
