@@ -19,6 +19,7 @@
 //   k_pass_seg       g + residual and those histograms in one pass, for the leader of a
 //                    segmented step that is known up front
 //   k_stats          variance partials alone (stand-alone variance)
+//   k_squares        sums of squares of vectors and of their kept values
 //   k_leader         finishes the variances and takes the first argmax
 //   k_pick0          (flat VAR: finishes the variances, takes the leader;) finds the
 //                    threshold digit and every chunk's list offset
@@ -2977,7 +2978,8 @@ __device__ __forceinline__ int meet_help(const Meeting& m, int look, uint32_t* h
 // marking or five behind nothing.  Those are bound by latency, 5 us for a launch and a trip to memory or two in each; here
 // the blocks wait for each other in between (a microsecond), and a block's survivors (keys that reach the threshold's
 // top digit, or the guessed bound) stay on chip, an eighth with each wave, in order.  List kernels / this, us: select 138 M,
-// one in a hundred kept 181 / 170, with values in runs 402 / 174, all equal 1914 / 1209; 8 selections on 25.6 M 278 / 248;
+// one in a hundred kept 181 / 170 (now 160), with values in runs 402 / 174, all equal 1914 / 1209; 8 selections on 25.6 M
+// 278 / 248 (now 219 with their norms);
 // variance rule, pass and selection, 11.7 M x 8 312 / 281, all equal 658 / 576.
 //   kTailSpans: the pieces of k_mark_spans, if their bound holds (k_pick_mask's rule).  How many there are in front of
 // every chunk is known, so each wave has as many as any other, however they are spread.  kTailHist: the top digits' counts
@@ -3254,26 +3256,33 @@ __device__ __forceinline__ void tail_select(const SelParams& p, const SegView& s
         incl = wave_incl_scan(cnt);
         const uint64_t some = __ballot(at + incl > e0 && at + incl - cnt < e1 && cnt != 0u);
         read = some & __ballot(cnt > (uint32_t)sv.tcap);
-        for (uint64_t left = some & ~read; left != 0ull;) {  // four spans' loads in flight
-          uint2 ent[4];
-          uint32_t first[4], cn[4], span_of[4];
+        // eight rows of 64 entries in flight, whosever piece they are of (the first 64 of four pieces at a time, and each
+        // further row of theirs behind the one before: 8 selections of 25.6 M, 123 entries a piece, 10.5 us here, now 7.8)
+        uint64_t left = some & ~read;
+        const uint2* piece = sv.tbuf;
+        uint32_t first = 0u, m0 = 0u, m1 = 0u;  // of the piece: the number of its first entry; its entries [m0, m1) are to come
+        while (left != 0ull || m0 < m1) {
+          uint2 ent[8];
+          uint32_t number[8], there[8];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int s = left != 0ull ? __builtin_ctzll(left) : 0;
-            cn[q] = left != 0ull ? (uint32_t)__builtin_amdgcn_readlane((int)cnt, s) : 0u;
-            first[q] = at + (uint32_t)__builtin_amdgcn_readlane((int)(incl - cnt), s);  // the number of its first entry
-            span_of[q] = s0 + (uint32_t)s;
-            left &= left - 1ull;
-            ent[q] = sv.tbuf[(size_t)span_of[q] * (size_t)sv.tcap + ((uint32_t)lane < cn[q] ? lane : 0)];
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            for (uint32_t m0 = 0u; m0 < cn[q]; m0 += 64u) {
-              const uint32_t m = m0 + (uint32_t)lane, e = first[q] + m;
-              if (m0 != 0u && m < cn[q]) ent[q] = sv.tbuf[(size_t)span_of[q] * (size_t)sv.tcap + m];
-              if (m < cn[q] && e >= e0 && e < e1) put(c, e - e0, ent[q]);
+          for (int q = 0; q < 8; ++q) {
+            if (m0 >= m1 && left != 0ull) {
+              const int s = __builtin_ctzll(left);
+              left &= left - 1ull;
+              m1 = (uint32_t)__builtin_amdgcn_readlane((int)cnt, s);
+              first = at + (uint32_t)__builtin_amdgcn_readlane((int)(incl - cnt), s);
+              piece = sv.tbuf + (size_t)(s0 + (uint32_t)s) * (size_t)sv.tcap;
+              m0 = e0 > first ? e0 - first : 0u;
+              if (m1 > e1 - first) m1 = e1 - first;
             }
+            number[q] = first + m0 - e0;
+            there[q] = m0 < m1 ? m1 - m0 : 0u;
+            ent[q] = piece[(uint32_t)lane < there[q] ? m0 + (uint32_t)lane : 0u];
+            m0 += 64u;
           }
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            if ((uint32_t)lane < there[q]) put(c, number[q] + (uint32_t)lane, ent[q]);
         }
       }
       for (; read != 0ull; read &= read - 1ull) {
