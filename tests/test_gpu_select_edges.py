@@ -435,3 +435,34 @@ def test_bound_that_comes_to_nothing(kind):
     ctx.status()
     assert gpu_util.FORCED or (info["guessed"], info["from_mask"], info["one_launch"]) == (1, 0, 1), info
     assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x.cpu().numpy(), k))
+
+
+# pieces of none, one, a row (64), a row and one, eight rows and one entry, and more, next to each other, so that a wave's
+# share begins and ends inside pieces and rows
+@pytest.mark.parametrize("n", [700_003, 9_000_001])
+@pytest.mark.parametrize("k_of", [33, 100, 400])
+def test_selection_from_pieces_of_every_size(n, k_of, monkeypatch):
+    import torch
+    from tests import gpu_util
+
+    monkeypatch.setitem(gpu_util.OPTIONS, "guess_min_n", 4096)
+    span = 2048 if n < 1 << 23 else 8192  # elements a piece is of
+    rng = np.random.default_rng(n + k_of)
+    mean = span // k_of
+    sizes = [s for s in (0, 1, 2, 63, 64, 65, 128, 129, 511, 512, 513) if s <= 3 * mean] + [mean]
+    x = (rng.random(n) * 0.5).astype(np.float32)
+    k = 0
+    for s0 in range(0, n, span):
+        m = min(int(rng.choice(sizes)), min(span, n - s0))
+        at = s0 + rng.permutation(min(span, n - s0))[:m]
+        x[at] = ((1.0 + rng.random(m)) * rng.choice([-1.0, 1.0], m)).astype(np.float32)
+        k += m
+    xd = torch.from_numpy(x).cuda()
+    ctx = gpu_util.make_context(1, n, k)
+    for keep in (k, k - k // 3):
+        idx = torch.full((keep,), -1, dtype=torch.int32, device="cuda")
+        ctx.artopk_select_topk(xd, keep, idx)
+        info = ctx.select_info()
+        ctx.status()
+        assert gpu_util.FORCED or info["guessed"] == 1, info
+        assert np.array_equal(idx.cpu().numpy(), orc.topk_indices(x, keep))
