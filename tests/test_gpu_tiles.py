@@ -41,6 +41,8 @@ def _values(kind, n, rng):
         return np.sort(np.abs(x))
     if kind == "narrow":  # all in one top digit
         return (1.0 + 0.06 * rng.random(n)).astype(np.float32)
+    if kind == "steps":  # a few hundred neighbouring values, a few thousand times each: bins of a few keys
+        return (1.0 + rng.integers(0, 300, n) * 2.0 ** -23).astype(np.float32)
     if kind == "odd":  # infinities, NaNs of either sign, negative zeros and denormals
         x[::977] = np.inf
         x[5::1931] = -np.inf
@@ -73,7 +75,7 @@ def test_flat_lengths(n, rho):
     _steps(2, n, max(1, int(n * rho)), orc.MODE_STAR, lambda s, r: _values("normal", n, rng))
 
 
-@pytest.mark.parametrize("kind", ["equal", "zeros", "ties", "run", "sorted", "narrow", "odd"])
+@pytest.mark.parametrize("kind", ["equal", "zeros", "ties", "run", "sorted", "narrow", "steps", "odd"])
 @pytest.mark.parametrize("rho", [0.005, 0.1])
 def test_flat_values(kind, rho):
     n = 19 * TILE + 3
@@ -104,7 +106,7 @@ def test_segments(layout, mode, rho):
     _steps(w, n, sum(ks), orc.MODE_STAR if mode == "star" else orc.MODE_VAR, wl.gen, seg_off=off, seg_k=ks)
 
 
-@pytest.mark.parametrize("kind", ["equal", "zeros", "ties", "run", "sorted", "narrow", "odd"])
+@pytest.mark.parametrize("kind", ["equal", "zeros", "ties", "run", "sorted", "narrow", "steps", "odd"])
 @pytest.mark.parametrize("layout", ["buckets", "layers"])
 def test_segment_values(kind, layout):
     off = _layout(layout)
