@@ -729,11 +729,13 @@ struct GuessPlan {
   bool tiles = false;    // one vector whose marks are handed on by tiles
 };
 
-// marking = number of workers whose fused pass will mark (1: a leader known up front).
-GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, int marking) {
+// known: the leader is known up front, and its pass alone will mark.  (Not so with a single worker whose leader comes from the
+// data or the counter: such a step takes the mask, and with it the mask's lines: 25.6 M x 1, one in a hundred / in ten kept,
+// histogram route 167/227 us, mask 181/286; 13 M x 1 104/135 and 119/172.)
+GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, bool known) {
   GuessPlan gp;
-  if (c->s.mask == nullptr || n < (marking == 1 && !c->guess_min_n_set ? kTilesMinN : c->guess_min_n)) return gp;
-  // With one marking worker its marks are handed on by tiles (k_mark_tiles), unless the option forbids it or a tile's piece
+  if (c->s.mask == nullptr || n < (known && !c->guess_min_n_set ? kTilesMinN : c->guess_min_n)) return gp;
+  // A leader known up front hands its marks on by tiles (k_mark_tiles), unless the option forbids it or a tile's piece
   // would not hold its share: at most 1.3 k's, and six standard deviations.  Very sparse selections on very long vectors do
   // without, as the mask then is the smaller thing to write (histogram route / mask / tiles, us a step: 138 M x 4, one in
   // 3000 kept 1386/1266/1269, in 1000 1396/1282/1264, in 250 1419/1321/1269, in 100 1468/1413/1294; 400 M x 2, one in 3000
@@ -741,7 +743,7 @@ GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, int marking) {
   // 316/323/290; below kTilesMinN see there).
   const double per_tile = 1.3 * (double)k * (double)kMarkTile / (double)n;
   const bool worth = c->stage_tiles == 2 || n < ((int64_t)1 << 28) || k * 700 >= n;
-  gp.tiles = c->stage_tiles != 0 && marking == 1 && worth && per_tile + 6.0 * std::sqrt(per_tile) + 32.0 <= (double)kMarkMax;
+  gp.tiles = c->stage_tiles != 0 && known && worth && per_tile + 6.0 * std::sqrt(per_tile) + 32.0 <= (double)kMarkMax;
   // A selection of more than one element in 32 is not worth fetching entry by entry from the mask; nor is the mask on
   // vectors that the tiles alone would take.
   if (!gp.tiles && (k * 32 > n || n < c->guess_min_n)) return gp;
@@ -1952,7 +1954,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   // a flat selection on a long vector samples a threshold guess first; its chunks are then whole
   // tiles of the fused pass, which strides over the tiles and counts per chunk
   const bool leader_first = (mode == ARTOPK_STAR || mode == ARTOPK_FIXED) && ctx->leader_first;
-  const GuessPlan gp = segmented ? GuessPlan{} : plan_guess(ctx, n, k, leader_first ? 1 : (int)w);
+  const GuessPlan gp = segmented ? GuessPlan{} : plan_guess(ctx, n, k, leader_first);
   Plan flat;
   const Plan* pl = &flat;
   if (segmented) {

@@ -229,6 +229,45 @@ def test_guess_kept_elements_clustered_in_two_tiles(guess_on, mode):
     _run_steps(runner, gen, w, n, k, orc.MODE_STAR if mode == "star" else orc.MODE_VAR, 2, expect_mask=None)
 
 
+_LATE_LEADER = [("var", 1), ("var_g", 1), ("var_topk", 1), ("counter", 1), ("var", 2)]
+
+
+@pytest.mark.parametrize("mode,w", _LATE_LEADER)
+@pytest.mark.parametrize("stage", [1, 2])
+def test_guess_leader_from_the_data_keeps_to_the_masks_lines(monkeypatch, mode, w, stage):
+    """A leader that is not known up front has its marks in the mask, however few workers there are: no guess for a
+    selection of more than one element in 32, nor, by default, below 2^25 elements."""
+    import paper_2312_02493_amd as lib
+    import torch
+
+    mode = {"var": lib.ARTOPK_VAR, "var_g": lib.ARTOPK_VAR_G, "var_topk": lib.ARTOPK_VAR_TOPK,
+            "counter": lib.ARTOPK_STAR_COUNTER}[mode]
+    monkeypatch.setitem(gpu_util.OPTIONS, "stage_tiles", stage)
+    rng = np.random.default_rng(41)
+    for n, k, guess_min_n, guessed in ((600_003, 60_000, 4096, 0), (600_003, 6_000, 4096, 1), (12_600_001, 126_000, None, 0)):
+        ctx = gpu_util.make_context(w, n, k)
+        if guess_min_n:
+            ctx.set_option(lib.ARTOPK_OPT_GUESS_MIN_N, guess_min_n)
+        g = [(rng.standard_normal(n, dtype=np.float32) * (r + 1)).astype(np.float32) for r in range(w)]
+        gd = [torch.from_numpy(x).cuda() for x in g]
+        res = [torch.zeros(n, device="cuda") for _ in range(w)]
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        total, update, leader = torch.zeros(k, device="cuda"), torch.zeros(n, device="cuda"), torch.full((1,), -1, dtype=torch.int32, device="cuda")
+        ctx.artopk_step(gd, res, k, mode, 1, idx, total, update, leader_out=leader)
+        ctx.status()
+        assert gpu_util.FORCED or ctx.select_info()["guessed"] == guessed, (n, k)
+        lead = 0 if mode == lib.ARTOPK_STAR_COUNTER else w - 1
+        assert int(leader.item()) == lead
+        want = orc.topk_indices(g[lead], k)
+        assert np.array_equal(idx.cpu().numpy(), want)
+        acc = sum((g[r][want] for r in range(1, w)), g[0][want])
+        assert np.array_equal(gpu_util.bits(total.cpu().numpy()), gpu_util.bits(acc))
+        for r in range(w):
+            left = g[r].copy()
+            left[want] = 0.0
+            assert np.array_equal(gpu_util.bits(res[r].cpu().numpy()), gpu_util.bits(left))
+
+
 @pytest.mark.parametrize("n", [16_384, 32_768, 32_769, 3 * 32_768 + 2, 9 * 32_768 - 1, 17 * 32_768 + 131])
 def test_guess_pieces_ragged_lengths(guess_on, n):
     """Vector lengths around the tile and slab borders of the staged pieces (a slab is eight tiles)."""
