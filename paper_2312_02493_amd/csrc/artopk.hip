@@ -1051,6 +1051,7 @@ void launch_tiles_rest(artopk_ctx* c, const SelParams& p, const TileArgs& a) {
 int enqueue_tiles(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n, int32_t* idx_out, float* vals_row,
                   const GuessPlan& gp, const float* g, float* res, bool zero) {
   Scratch& s = c->s;
+  c->last_one_launch = 0;
   SelParams p = make_params(c, pl, tab, n, idx_out, vals_row, 0, false);
   p.zero_vec = zero ? res : nullptr;
   TileArgs a{};
@@ -2047,7 +2048,6 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
     const bool tiles = segmented ? by_tiles : gp.tiles;
     if ((rc = enqueue_clear(ctx, *pl, segmented ? 0 : 1, L, leader_out, tiles))) return rc;
     ctx->last_guessed = gp.on ? 1 : 0;
-    ctx->last_one_launch = 0;
     ctx->last_dom_workers = w > 1 ? w - 1 : 1;
     if (gp.on && !tiles) enqueue_guess(ctx, gp, g1t, r1t, 1);
     if (tiles) {

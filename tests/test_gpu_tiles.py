@@ -146,6 +146,28 @@ def test_segmented_selection_alone(layout):
         assert np.array_equal(t.cpu().numpy(), x)
 
 
+def test_what_select_info_says_behind_a_selection_in_one_launch():
+    """A segmented selection takes many launches, whatever the call before it took."""
+    import torch
+
+    off, ks = _layout("two"), [3000, 5000]
+    n = off[-1]
+    ctx = gpu_util.make_context(2, n, sum(ks), 2)
+    x = torch.from_numpy(_values("normal", n, np.random.default_rng(7))).cuda()
+    g, res = [x, 2 * x], [torch.zeros(n, device="cuda") for _ in range(2)]
+    idx, total = torch.zeros(sum(ks), dtype=torch.int32, device="cuda"), torch.zeros(sum(ks), device="cuda")
+    update = torch.zeros(n, device="cuda")
+    for call in ("select", "var", "star"):
+        ctx.artopk_select_topk(x, 4000, idx)
+        assert gpu_util.FORCED or ctx.select_info()["one_launch"] == 1
+        if call == "select":
+            ctx.artopk_select_topk(x, sum(ks), idx, seg_off=off, seg_k=ks)
+        else:
+            ctx.artopk_step(g, res, sum(ks), orc.MODE_VAR if call == "var" else orc.MODE_STAR, 1, idx, total, update, seg_off=off,
+                            seg_k=ks)
+        assert gpu_util.FORCED or ctx.select_info()["one_launch"] == 0, call
+
+
 @pytest.mark.parametrize("gtype", ["bf16", "f16"])
 @pytest.mark.parametrize("layout", [None, "layers"])
 def test_16_bit_gradients(gtype, layout):
