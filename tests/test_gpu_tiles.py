@@ -168,6 +168,66 @@ def test_what_select_info_says_behind_a_selection_in_one_launch():
         assert gpu_util.FORCED or ctx.select_info()["one_launch"] == 0, call
 
 
+def _kernels_of(call):
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.key for e in prof.key_averages()]
+
+
+def test_the_map_of_a_layouts_tiles_is_made_when_it_is_first_wanted():
+    """Not for layouts that do not go by tiles, once for one that does, and for a layout that the context knows already when
+    the length is lowered behind its back, also in a recorded call, whose replays leave eager calls as they were."""
+    import torch
+
+    off = _layout("layers")
+    n, ks = off[-1], [max(1, (b - a) // 50) for a, b in zip(off, off[1:])]
+    k, half = sum(ks), [0, n // 2, n]
+    x = _values("ties", n, np.random.default_rng(6))
+    want = np.concatenate([orc.topk_indices(x[a:b], m) + a for a, b, m in zip(off, off[1:], ks)])
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        t = torch.from_numpy(x).cuda()
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+
+        def select(ctx, o=off, q=ks):
+            idx.fill_(-1)
+            ctx.artopk_select_topk(t, sum(q), idx, seg_off=o, seg_k=q)
+
+        def check(ctx):
+            ctx.status()
+            assert np.array_equal(idx.cpu().numpy(), want)
+
+        for recorded in (False, True):
+            ctx = gpu_util.make_context(1, n, k, len(ks), stream=side.cuda_stream)
+            ctx.set_option(0, n + 1)
+            names = _kernels_of(lambda: select(ctx))
+            assert any("k_final" in s for s in names), names  # (they are seen)
+            assert not any("k_tile" in s for s in names), names
+            check(ctx)
+            ctx.set_option(0, 4096)
+            if recorded:
+                side.synchronize()
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=side):
+                    ctx.artopk_select_topk(t, k, idx, seg_off=off, seg_k=ks)
+            for i in range(3):
+                if recorded:
+                    idx.fill_(-1)
+                    graph.replay()
+                    check(ctx)
+                names = _kernels_of(lambda: select(ctx))
+                assert any("k_mark_tiles" in s for s in names) and any("k_tile_map" in s for s in names) == (i == 0), names
+                check(ctx)
+            select(ctx, half, [3, 5])
+            select(ctx)
+            check(ctx)
+
+
 @pytest.mark.parametrize("gtype", ["bf16", "f16"])
 @pytest.mark.parametrize("layout", [None, "layers"])
 def test_16_bit_gradients(gtype, layout):
