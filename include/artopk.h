@@ -406,7 +406,10 @@ int artopk_get_profile(artopk_ctx* ctx, float* ms_out, int32_t count);
  *       values and 240 for every 8192 elements
  *   [7] 1 if everything behind the top digits' counts of a pass, or behind the
  *       read-only marking, ran in one launch
- * Flat (one-segment) selections only; segmented ones report [0] = [1] = 0.  Of
+ *   [8] 1 if the selection was made from marked tiles (ARTOPK_OPT_STAGE_TILES)
+ *   [9] with [8]: segments (of a flat selection: 1) whose bound held, so that
+ *       their tiles' pieces were used
+ * [0] to [7] of flat (one-segment) selections only; segmented ones report [0] = [1] = 0.  Of
  * selections on several vectors [1] to [3] are the first vector's of those that
  * were selected on last.
  */

@@ -177,11 +177,11 @@ class Context:
         return int(out.value)
 
     def select_info(self) -> dict:
-        buf = (C.c_int32 * 8)()
-        self._check(self._lib.artopk_select_info(self._h, buf, 8))
+        buf = (C.c_int32 * 10)()
+        self._check(self._lib.artopk_select_info(self._h, buf, 10))
         return {"guessed": int(buf[0]), "from_mask": int(buf[1]), "list_count": int(buf[2]),
                 "list_level": int(buf[3]), "dominant_workers": int(buf[4]), "short": int(buf[5]), "many": int(buf[6]),
-                "one_launch": int(buf[7])}
+                "one_launch": int(buf[7]), "tiles": int(buf[8]), "tile_bounds": int(buf[9])}
 
     def get_profile(self) -> dict:
         buf = (C.c_float * len(PROF_NAMES))()

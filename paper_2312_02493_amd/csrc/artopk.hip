@@ -148,6 +148,7 @@ struct artopk_ctx {
   Scratch s;
   // how the last step or selection ran (artopk_select_info)
   int32_t last_guessed = 0, last_dom_workers = 0, last_short = 0, last_one_launch = 0;
+  int32_t last_tiles = 0;  // segments selected on by tiles (1: a flat vector), or 0
   int g_type = ARTOPK_G_F32;  // element type of the gradients of the step being enqueued
   // descriptors of the last segmented layout uploaded to table_dev
   std::vector<int64_t> cached_off, cached_k;
@@ -923,6 +924,7 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   // (the leader's own selection in front of the other workers' pass gains 2 % of a step, and loses a third on a run)
   const TailPlan tp = (guessed && !spans) || zero_vec ? TailPlan{} : tail_plan(pl, n, source);
   c->last_one_launch = tp.ranges > 0 ? 1 : 0;
+  c->last_tiles = 0;
   if (tp.ranges > 0) {
     if (spans) {
       p.tiles = span_buf(c, *spans, n);
@@ -1059,6 +1061,7 @@ int enqueue_tiles(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n,
                   const GuessPlan& gp, const float* g, float* res, bool zero) {
   Scratch& s = c->s;
   c->last_one_launch = 0;
+  c->last_tiles = pl.nseg;
   SelParams p = make_params(c, pl, tab, n, idx_out, vals_row, 0, false);
   p.zero_vec = zero ? res : nullptr;
   TileArgs a{};
@@ -1609,10 +1612,18 @@ int artopk_select_info(artopk_ctx* ctx, int32_t* info_out, int32_t count) {
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   SelState st{};
   HIP_TRY(ctx, hipMemcpy(&st, ctx->s.zero_base + kSegState, sizeof(st), hipMemcpyDeviceToHost));
-  const int32_t v[8] = {ctx->last_guessed, ctx->last_guessed ? (int32_t)st.use_mask : 0, (int32_t)st.list_count,
-                        (int32_t)st.compact_level, ctx->last_dom_workers, ctx->last_short,
-                        ctx->last_short ? (int32_t)st.many : 0, ctx->last_one_launch};
-  for (int i = 0; i < count && i < 8; ++i) info_out[i] = v[i];
+  int32_t bounds = 0;
+  for (int32_t seg = 0; count > 9 && seg < ctx->last_tiles; seg += 64) {
+    SelState of[64];
+    const int32_t some = std::min(ctx->last_tiles - seg, 64);
+    HIP_TRY(ctx, hipMemcpy2D(of, sizeof(SelState), ctx->s.zero_base + (size_t)seg * kSegWords + kSegState,
+                             kSegWords * sizeof(uint32_t), sizeof(SelState), (size_t)some, hipMemcpyDeviceToHost));
+    for (int32_t i = 0; i < some; ++i) bounds += of[i].use_mask != 0u ? 1 : 0;
+  }
+  const int32_t v[10] = {ctx->last_guessed, ctx->last_guessed ? (int32_t)st.use_mask : 0, (int32_t)st.list_count,
+                         (int32_t)st.compact_level, ctx->last_dom_workers, ctx->last_short,
+                         ctx->last_short ? (int32_t)st.many : 0, ctx->last_one_launch, ctx->last_tiles > 0 ? 1 : 0, bounds};
+  for (int i = 0; i < count && i < 10; ++i) info_out[i] = v[i];
   return ARTOPK_OK;
 }
 
@@ -1990,6 +2001,7 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   ctx->last_guessed = 0;
   ctx->last_dom_workers = w;
   ctx->last_short = 0;
+  ctx->last_tiles = 0;
   if (mode == ARTOPK_VAR_TOPK) {
     // Literal Alg. 1: Top-k on every worker, leader = largest squared norm of its own k values,
     // then the leader's indices are the shared ones.
