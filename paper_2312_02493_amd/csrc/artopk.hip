@@ -1019,11 +1019,6 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   return ARTOPK_OK;
 }
 
-// Entries that a tile's piece may have: those of the fused pass' tiles, or what there is room for.
-int32_t tile_piece_cap(const artopk_ctx* c, int64_t tiles) {
-  return (int32_t)std::min<int64_t>(kMarkMax, c->s.tilebuf_entries / tiles);
-}
-
 // A vector that is only read by tiles comes through the caches up to this length: what gathers from it next then finds some
 // of its lines there (25.6 M x 8, variance rule, gather 96 us behind non-temporal loads, 86 behind ordinary ones).
 constexpr int64_t kCachedMaxN = (int64_t)1 << 26;
@@ -1035,7 +1030,7 @@ void launch_tiles(artopk_ctx* c, const SelParams& p, const TileArgs& a, const Pl
   if (pl.use_table) {
     PtrTable gt{};
     gt.p[0] = const_cast<float*>(g);
-    hipLaunchKernelGGL(k_guess_segs<GT>, dim3((unsigned)pl.nseg), dim3(1024), 0, c->stream, p, gt, a.cap);
+    hipLaunchKernelGGL(k_guess_segs<GT>, dim3((unsigned)pl.nseg), dim3(1024), 0, c->stream, p, gt);
   } else if constexpr (GT != kGNone) {
     hipLaunchKernelGGL(k_guess_tiles<GT>, dim3((unsigned)((gp.runs + kGuessThreads - 1) / kGuessThreads)), dim3(kGuessThreads), 0, c->stream, g, res,
                        c->s.h_all, gp.runs, gp.stride, gp.m_hi, gp.m_mid, gp.m_lo, c->s.zero_base + kTileInfo);
@@ -1070,7 +1065,6 @@ int enqueue_tiles(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n,
   a.map = pl.use_table ? s.tile_map : nullptr;
   a.groups = pl.use_table ? reinterpret_cast<const uint2*>(s.tile_map + s.map_tiles) : nullptr;
   a.pieces = s.tilebuf;
-  a.cap = tile_piece_cap(c, a.ntiles);
   // (nobody else has anything in S's memory now: 16.8 MB at least and 16 KB for every segment, for kTileWords a tile)
   a.kept = reinterpret_cast<uint64_t*>(s.S);
   a.held = s.S + 4 * (size_t)a.ntiles;  // (no more blocks than tiles)
@@ -1408,6 +1402,7 @@ Layout scratch_layout(int32_t max_w, int64_t max_n, int64_t max_k, int32_t max_s
   L.o_tmap = take((size_t)(L.map_tiles + L.map_tiles / 2 + 1) * sizeof(uint4));
   // pieces of marked elements: 6144 entries for every tile of the streaming passes (1.5 bytes per element)
   L.tilebuf_entries = (max_n + kPassTile - 1) / kPassTile * 6144;
+  static_assert(piece_at(kPassTile) == 6144, "pieces lie as their elements do");
   L.o_tbuf = take((size_t)L.tilebuf_entries * sizeof(uint2));
   // (hist, ctr, claim, dig1 and dig2 have to be zero between steps)
   L.small_words = (size_t)(max_w + 1) * kSmallReps * kHistBins + kSmallCtr + kSmallMaxUnits + 2 * kSmallReps * 128;

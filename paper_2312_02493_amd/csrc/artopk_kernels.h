@@ -3777,7 +3777,7 @@ k_tail(SelParams p, LeaderArgs la, int row_log2) {
 struct TileArgs {
   const uint4* map;      // [tiles] (first element, a multiple of 4; first and last + 1 of the segment's; segment), or nullptr: one segment
   const uint2* groups;   // [blocks of the kernels behind the marking] (segment, number among its blocks), or nullptr
-  uint2* pieces;         // [tiles][cap]
+  uint2* pieces;         // each tile's from piece_at of its first own element on
   uint32_t* held;        // [tiles] entries of the piece, or kTileOverflow
   uint32_t* marked;      // [tiles] elements that reach the bound
   // of each tile's kTileWaves parts, of which a tile with a piece has the first only:
@@ -3790,8 +3790,19 @@ struct TileArgs {
   uint64_t* kept;        // [tiles], then [blocks] kept entries: above the threshold << 32 | at it
   uint32_t* any_full;    // set where some segment's bound does not hold
   int32_t* tile_start;   // kept entries in front of every tile of the streaming passes (two of these), or nullptr
-  int32_t ntiles, ngroups, cap;
+  int32_t ntiles, ngroups;
 };
+// Where the piece of a tile whose own elements begin with `lo` lies, and how many entries the piece of [lo, hi) can have:
+// three for sixteen elements, so that pieces lie as the tiles do, whole tiles have room for more than kMarkMax, and however
+// many short segments there are takes nothing from the others (an equal share for each tile, 8.4 M elements in 250 segments
+// from 500 to 200,000 long, one in ten kept: no share was large enough, 181 us to select, list kernels 93).
+constexpr int kPieceOf = 16, kPieceEntries = 3;
+__host__ __device__ constexpr int64_t piece_at(int64_t lo) { return lo * kPieceEntries / kPieceOf; }
+__host__ __device__ constexpr uint32_t piece_room(uint32_t lo, uint32_t hi) {
+  const int64_t room = piece_at(hi) - piece_at(lo);
+  return room < (int64_t)kMarkMax ? (uint32_t)room : (uint32_t)kMarkMax;
+}
+static_assert(piece_at(kMarkTile) >= kMarkMax, "a whole tile's marks are bounded by what fits on chip");
 constexpr int kTileWaves = 4;  // waves, and tiles, of a block of the kernels behind the marking; and parts of a tile without a piece
 constexpr int kTileSlots = 4;
 constexpr uint32_t kTileOverflow = 0xffffffffu;
@@ -4078,7 +4089,7 @@ k_guess_tiles(const float* __restrict__ gp, const float* __restrict__ rp, uint32
 constexpr int kSegRun = 32;
 template <int GT>
 __global__ void __launch_bounds__(1024)
-k_guess_segs(SelParams p, PtrTable g, int32_t cap) {
+k_guess_segs(SelParams p, PtrTable g) {
   constexpr int T = 1024;
   __shared__ __attribute__((aligned(16))) uint32_t lh[2][kHistBins];
   __shared__ uint32_t part[T / 64];
@@ -4093,9 +4104,14 @@ k_guess_segs(SelParams p, PtrTable g, int32_t cap) {
   const bool whole = len <= T * kSegRun;
   int64_t runs = whole ? (sv.d.e_hi - e_first) / kSegRun : len / (4 * kSegRun);
   if (runs > T) runs = T;
-  // a piece has to hold what a tile is expected to mark, with some room
-  const float per_tile = 1.3f * (float)k * fminf(1.0f, (float)kMarkTile / (float)len);
-  if (runs < 1 || per_tile + 6.0f * sqrtf(per_tile) + 32.0f > (float)cap) return;  // (`info` has been cleared)
+  const float sample = (float)(runs * kSegRun), expect = whole ? (float)k : (float)k * sample / (float)len;
+  const float chance = whole ? 0.0f : 6.0f * sqrtf(expect) + 8.0f;  // of draws that know nothing of each other
+  // A piece has to hold what a tile is expected to mark, and six standard deviations where it shares them with others: up to
+  // about one in seven kept.
+  const float per_tile = runs < 1 ? 0.0f : (expect + chance) / (whole ? (float)len : sample) * fminf((float)kMarkTile, (float)len);
+  const uint32_t tile_end = (uint32_t)(sv.d.ntiles > 1 ? sv.d.e_lo + kMarkTile : sv.d.e_hi);
+  if (runs < 1 || per_tile + (sv.d.ntiles > 1 ? 6.0f * sqrtf(per_tile) : 0.0f) > (float)piece_room((uint32_t)sv.d.e_lo, tile_end))
+    return;  // (`info` has been cleared)
   const int64_t stride = whole ? kSegRun : len / runs;
   uint32_t key[kSegRun];
   const uint32_t there = sample_keys<GT, kSegRun, T>(
@@ -4115,7 +4131,6 @@ k_guess_segs(SelParams p, PtrTable g, int32_t cap) {
     tb.h[3] = q.w;
     tb.scan(part);
   };
-  const float sample = (float)(runs * kSegRun), expect = whole ? (float)k : (float)k * sample / (float)len;
   const uint32_t m_mid = (uint32_t)fmaxf(1.0f, expect + 0.5f);
   uint4 low, mid, top, low2, mid2;
   read(0);
@@ -4300,7 +4315,7 @@ k_mark_tiles(SelParams p, TileArgs a, const float* __restrict__ gp, float* __res
       const uint32_t c0 = wcnt[lane];  // (every wave scans the counts itself)
       const uint32_t s0 = wave_incl_scan(c0);
       const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)s0, 63);
-      const bool fits = total <= (uint32_t)a.cap;
+      const bool fits = total <= piece_room(lo, hi);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         // marks in the rows before this wave's row u
@@ -4328,7 +4343,7 @@ k_mark_tiles(SelParams p, TileArgs a, const float* __restrict__ gp, float* __res
       }
       __syncthreads();
       if (fits) {
-        uint2* __restrict__ dst = a.pieces + (size_t)ti * (size_t)a.cap;
+        uint2* __restrict__ dst = a.pieces + piece_at(lo);
         for (uint32_t i = (uint32_t)tid; i < total; i += T) dst[i] = stage[i];
       }
       if (tid == 0) {
@@ -4446,7 +4461,7 @@ k_tiles_full(SelParams p, TileArgs a) {
     const uint32_t lo = at.y, hi = at.z, held = a.held[ti];
     const uint32_t zero = p.zero_base[(size_t)at.w * kSegWords + kTileInfo + kTileZero];
     if (p.zero_vec != nullptr && held != kTileOverflow) {
-      const uint2* __restrict__ piece = a.pieces + (size_t)ti * (size_t)a.cap;
+      const uint2* __restrict__ piece = a.pieces + piece_at(lo);
       for (uint32_t i = (uint32_t)tid; i < held; i += T) {
         const uint2 ent = piece[i];
         if ((ent.y & kKeyMask) >= zero && ent.x >= lo && ent.x < hi) p.zero_vec[ent.x] = __uint_as_float(ent.y);
@@ -4484,15 +4499,14 @@ k_tiles_full(SelParams p, TileArgs a) {
   }
 }
 
-// The entries of tile `at`: a piece's, `held` of them, in rows of 64 (row1(entry, whether it is there)), or where there is none
+// The entries of tile `at`: `piece`'s, `held` of them, in rows of 64 (row1(entry, whether it is there)), or where there is none
 // those of the tile's part `part` from the vector, in rows of 256, four in a row a lane's (row4(raw bits, the first one's
 // element, which of them are there)), in order.  The 64 lanes of a wave call it.
 template <typename Row1, typename Row4>
-__device__ __forceinline__ void tile_rows(const TileArgs& a, const float* x, int64_t t, uint32_t held, int part, const uint4 at,
+__device__ __forceinline__ void tile_rows(const uint2* __restrict__ piece, const float* x, uint32_t held, int part, const uint4 at,
                                           Row1 row1, Row4 row4) {
   const uint32_t lane = lane_id();
   if (held != kTileOverflow) {
-    const uint2* __restrict__ piece = a.pieces + (size_t)t * (size_t)a.cap;
 #pragma unroll 1
     for (uint32_t r0 = 0u; r0 < held; r0 += 512u) {  // eight rows in flight
       uint2 ent[8];
@@ -4568,7 +4582,8 @@ template <bool APART>
 struct TileGroup {
   int seg, number, blocks, ntiles;
   int64_t begin;
-  uint32_t own;   // entries in the piece of the wave's own tile
+  const uint2* piece;  // of the wave's own tile
+  uint32_t own;   // its entries
   uint32_t open;  // bit i: the block's i-th tile has none
   __device__ __forceinline__ TileGroup(const SelParams& p, const TileArgs& a, int wave) {
     seg = 0;
@@ -4583,7 +4598,9 @@ struct TileGroup {
     begin = d.tile_begin;
     blocks = (ntiles + kTileWaves - 1) / kTileWaves;
     const int i = (int)lane_id() & (kTileWaves - 1);
-    const uint32_t held = a.held[begin + (tile(i) < ntiles ? tile(i) : 0)];
+    const int64_t t = begin + (tile(i) < ntiles ? tile(i) : 0);
+    const uint32_t held = a.held[t], lo = tile_at(a, p.n, t).y;
+    piece = a.pieces + piece_at((uint32_t)__builtin_amdgcn_readlane((int)lo, wave));
     own = (uint32_t)__builtin_amdgcn_readlane((int)held, wave);
     open = (uint32_t)__ballot(tile(i) < ntiles && held == kTileOverflow) & ((1u << kTileWaves) - 1u);
   }
@@ -4648,7 +4665,7 @@ k_tiles_digit(SelParams p, TileArgs a) {
       }
       in += (uint32_t)__popcll(m);
     };
-    tile_rows(a, sv.x, t, held, q, tile_at(a, p.n, t),
+    tile_rows(tg.piece, sv.x, held, q, tile_at(a, p.n, t),
               [&](uint2 ent, bool ok) __attribute__((always_inline)) {
                 const uint32_t kk = ent.y & kKeyMask;
                 up += ok && kk > khi ? 1u : 0u;
@@ -4733,7 +4750,7 @@ k_tiles_count(SelParams p, TileArgs a) {
         const bool ok = lane < in;
         one(a.slots[tp * kTileSlots + (ok ? lane : 0u)], ok);
       } else {
-        tile_rows(a, sv.x, t, held, q, tile_at(a, p.n, t), [&](uint2 ent, bool ok) { one(ent.y & kKeyMask, ok); },
+        tile_rows(tg.piece, sv.x, held, q, tile_at(a, p.n, t), [&](uint2 ent, bool ok) { one(ent.y & kKeyMask, ok); },
                   [&](uint4 v, uint32_t, uint32_t there) __attribute__((always_inline)) {
                     one(v.x & kKeyMask, (there & 1u) != 0u);
                     one(v.y & kKeyMask, (there & 2u) != 0u);
@@ -4823,7 +4840,7 @@ k_tiles_out(SelParams p, TileArgs a) {
       if ((t & 1) == 0) a.tile_start[t >> 1] = (int32_t)sv.d.koff + (int32_t)place(nA, nB);
       if (ts == tg.ntiles - 1) a.tile_start[(t + 2) >> 1] = (int32_t)sv.d.koff + (int32_t)k;
     }
-    tile_rows(a, sv.x, t, held, q, tile_at(a, p.n, t),
+    tile_rows(tg.piece, sv.x, held, q, tile_at(a, p.n, t),
               [&](uint2 ent, bool ok) __attribute__((always_inline)) {
                 const uint32_t kk = ent.y & kKeyMask;
                 const bool up = ok && kk > key, eq = ok && kk == key;
