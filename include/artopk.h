@@ -137,8 +137,10 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 marks on by tiles (ARTOPK_OPT_STAGE_TILES)
  *                                 from 12582912 and segmented steps and
  *                                 selections, whose segments are then guessed
- *                                 for one by one, from 8388608; then all of them
- *                                 from that on
+ *                                 for one by one, from 8388608 to 25165824, the
+ *                                 more segments the later, and not where a part
+ *                                 of them is too dense for it (above about one
+ *                                 in seven); then all of them from that on
  *   ARTOPK_OPT_UPDATE_TILES_MIN_N shortest vector whose dense update is
  *                                 streamed tile by tile with the values stored
  *                                 behind the zeros, shorter ones are built

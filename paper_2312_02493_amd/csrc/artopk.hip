@@ -62,13 +62,28 @@ constexpr int64_t kSmallMaxN = (int64_t)1 << 20, kSmallMaxNLimit = (int64_t)kSma
 // 107/108 133/128, 400009 x 64 159/175 190/168, and with all the chip 1 M x 32 128/142 182/168.
 constexpr int64_t kSmallMaxValues = 22000000, kSmallManyMinN = (int64_t)1 << 19, kSmallManyMaxN = (int64_t)3 << 18;
 
-// Selections by tiles from this many elements on: flat ones of a leader known up front, and segmented ones.  Launches of the
-// histogram route / tiles, us: flat, one in a hundred and in ten kept, 3 M x 2 73/81 86/94, 6 M x 2 93/93 118/110, x 8
+// Selections by tiles from this many elements on: flat ones of a leader known up front.  Launches of the histogram route /
+// tiles, us, one in a hundred and in ten kept, 3 M x 2 73/81 86/94, 6 M x 2 93/93 118/110, x 8
 // 171/172 198/193, 12 M x 2 125/120 153/144, x 8 273/268 312/294, 25.6 M x 2 218/193 291/227, bfloat16 gradients 12 M x 8
-// 236/237 280/268, 25.6 M x 8 449/427 550/478.  Segmented, one in a hundred, leader known, 4 M x 2 in 54 segments 93/114, in
-// 8 99/92, 8 M x 2 in 54 131/129, in 8 154/105, in 160 149/143, 25.6 M x 8 in 54 533/503; variance rule, 4 M x 2 in 54
-// 107/118, in 8 115/96, 8 M x 2 in 54 163/140, x 8 341/256, 25.6 M x 8 644/620, one in ten 964/937.
-constexpr int64_t kTilesMinN = (int64_t)3 << 22, kSegTilesMinN = (int64_t)1 << 23;
+// 236/237 280/268, 25.6 M x 8 449/427 550/478.
+constexpr int64_t kTilesMinN = (int64_t)3 << 22;
+
+// Segmented selections by tiles (segments_by_tiles).  List kernels / tiles, us, a selection, one in a hundred kept; s: in as
+// many equal segments, u: of sizes spread over a factor of 40,000.
+//   Every segment costs a sample, a pick and tiles that are not whole, the list kernels more the longer the longest one is:
+// 8.4 M u2 69/61, u8 69/60, s3 59/65, u20 63/64, u54 64/76, u250 76/96; 10 M s3 69/63, u20 64/65, u54 67/69; 12.6 M s3 71/64,
+// u20 70/67, u54 68/82, u250 90/100; 16 M u54 81/72, u100 85/90, u160 108/95, u250 95/105; 20 M u54 90/89, u250 101/106; 25.6 M
+// u54 110/80, u700 154/147.
+//   A segment without pieces is read by each of the kernels behind the marking, the parts of a block's four tiles one after
+// the other, and then the more the longer it is.  One such segment among four, of 512 / 2048 / 16384 / 32768 elements, 16 M
+// 72/74 72/82 72/88 73/108, 25.6 M 105/84 106/92 106/97 107/118; one in five kept of an eighth / a quarter / all of the
+// elements, else one in a hundred, 25.6 M s8 111/171 117/178 143/202, 138 M 364/336 376/382 507/755; three in ten / four in
+// ten kept, 25.6 M s8 174/210 200/202, 60 M s8 327/343 379/329, 138 M 704/783 826/773.  But the list kernels are slow where
+// one segment is much longer than the others, or there are very many: three in ten, 25.6 M u54 276/203, s770 221/204, 138 M
+// u54 1260/787, u1000 1173/760, s4000 1129/903.
+constexpr int64_t kSegTilesMinN = (int64_t)1 << 23, kSegTilesSomeN = (int64_t)10 << 20, kSegTilesAllN = (int64_t)14 << 20;
+constexpr int64_t kSegTilesBareN = (int64_t)3 << 23, kSegTilesFewBareN = (int64_t)3 << 25, kShortBare = 1024;
+constexpr int32_t kSegTilesEach = 24, kSegTilesFew = 6, kSegTilesMany = 512;
 
 struct Scratch {
   // zeroed before every select: one kSegWords block per segment, then the look-back flags
@@ -121,6 +136,9 @@ struct Plan {
   int32_t tiles = 0, tile_groups = 0;  // tiles of all segments together, 0: not selected on by tiles
   int32_t more_bins = 0;               // further copies of segments' bins
   bool tiles_aligned = true;           // they are the streaming passes' tiles
+  int64_t longest = 0;   // elements of the longest segment,
+  int64_t bare = 0;      // of those of more than a tile whose tiles will have no pieces,
+  bool some_bare = false;  // and whether there are such of more than kShortBare
 };
 
 }  // namespace
@@ -423,7 +441,14 @@ int32_t more_bins(const artopk_ctx* c, int32_t ntiles, int32_t tiles, int32_t ha
 
 // Whether a segmented selection goes by tiles (a guess length that was set holds for these, too).
 bool segments_by_tiles(const artopk_ctx* c, const Plan& pl, int64_t n) {
-  return pl.tiles > 0 && n >= (c->guess_min_n_set ? c->guess_min_n : kSegTilesMinN);
+  if (pl.tiles == 0) return false;
+  if (c->guess_min_n_set) return n >= c->guess_min_n;
+  if (n < kSegTilesBareN)
+    return !pl.some_bare && ((n >= kSegTilesMinN && pl.longest * 2 > n) ||
+                             (n >= kSegTilesSomeN && pl.tiles >= kSegTilesEach * (int64_t)pl.nseg) ||
+                             (n >= kSegTilesAllN && pl.tiles >= kSegTilesFew * (int64_t)pl.nseg));
+  return pl.bare == 0 || pl.longest * pl.nseg > 4 * n || pl.nseg >= kSegTilesMany || pl.k_all * 5 > 2 * n ||
+         (n >= kSegTilesFewBareN && pl.bare * 5 <= n);
 }
 
 // Descriptors for nseg > 1 segments; uploads them to the device table unless the
@@ -465,6 +490,11 @@ int segmented_plan(artopk_ctx* c, int64_t n, int32_t nseg, const int64_t* seg_of
       d.tile_begin = pl.tiles;
       d.ntiles = (int32_t)((d.e_hi - d.e_lo / 32 * 32 + kMarkTile - 1) / kMarkTile);
       pl.tiles += d.ntiles;
+      pl.longest = std::max(pl.longest, ns);
+      if (ns > kShortBare && !SegSample(d.e_lo, d.e_hi, seg_k[sgi]).has_pieces(d.e_lo, d.e_hi, d.ntiles)) {
+        pl.some_bare = true;
+        if (ns > kMarkTile) pl.bare += ns;
+      }
       if (d.e_lo % kPassTile != 0) pl.tiles_aligned = false;
       koff += seg_k[sgi];
       list_base += ((int64_t)d.cap + 3) / 4 * 4;

@@ -4086,11 +4086,38 @@ k_guess_tiles(const float* __restrict__ gp, const float* __restrict__ rp, uint32
 // how much the runs' counts differ from each other (values that lie together are worth fewer draws).  Bound by loading
 // them (a block's lines come at about 0.4 a ns).  Segments too dense for pieces get no bound.
 // ---------------------------------------------------------------------------
-constexpr int kSegRun = 32;
+constexpr int kSegRun = 32, kSegRuns = 1024;
+// What is sampled of the segment [lo, hi): its lines from `first` on, `runs` of them, all of a short one's (but for a few
+// elements at its ends: the bound is then exact).
+struct SegSample {
+  int64_t first, runs;
+  bool whole;
+  float expect, chance;  // of its k largest in the sample, and six standard deviations of draws that know nothing of each other
+  __host__ __device__ SegSample(int64_t lo, int64_t hi, int64_t k) {
+    const int64_t len = hi - lo;
+    first = (lo + kSegRun - 1) / kSegRun * kSegRun;
+    whole = len <= kSegRuns * kSegRun;
+    runs = whole ? (hi - first) / kSegRun : len / (4 * kSegRun);
+    if (runs > kSegRuns) runs = kSegRuns;
+    expect = whole ? (float)k : (float)k * elements() / (float)len;
+    chance = whole ? 0.0f : 6.0f * sqrtf(expect) + 8.0f;
+  }
+  __host__ __device__ float elements() const { return (float)(runs * kSegRun); }
+  // Whether a piece holds what a tile is expected to mark, and six standard deviations where it shares the marks with other
+  // tiles: up to about one in seven kept.
+  __host__ __device__ bool has_pieces(int64_t lo, int64_t hi, int ntiles) const {
+    if (runs < 1) return false;
+    const float len = (float)(hi - lo), tile = len < (float)kMarkTile ? len : (float)kMarkTile;
+    const float marks = (expect + chance) / (whole ? len : elements()) * tile;
+    return marks + (ntiles > 1 ? 6.0f * sqrtf(marks) : 0.0f) <=
+           (float)piece_room((uint32_t)lo, (uint32_t)(ntiles > 1 ? lo + kMarkTile : hi));
+  }
+};
+
 template <int GT>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(kSegRuns)
 k_guess_segs(SelParams p, PtrTable g) {
-  constexpr int T = 1024;
+  constexpr int T = kSegRuns;
   __shared__ __attribute__((aligned(16))) uint32_t lh[2][kHistBins];
   __shared__ uint32_t part[T / 64];
   __shared__ uint32_t res[4];
@@ -4099,19 +4126,11 @@ k_guess_segs(SelParams p, PtrTable g) {
   const SegView sv = seg_view(p, seg);
   const int64_t len = sv.d.e_hi - sv.d.e_lo;
   const int64_t k = sv.d.k;
-  const int64_t e_first = (sv.d.e_lo + kSegRun - 1) & ~(int64_t)(kSegRun - 1);
-  // (short segments are read whole but for a few elements at their ends: the bound is then exact)
-  const bool whole = len <= T * kSegRun;
-  int64_t runs = whole ? (sv.d.e_hi - e_first) / kSegRun : len / (4 * kSegRun);
-  if (runs > T) runs = T;
-  const float sample = (float)(runs * kSegRun), expect = whole ? (float)k : (float)k * sample / (float)len;
-  const float chance = whole ? 0.0f : 6.0f * sqrtf(expect) + 8.0f;  // of draws that know nothing of each other
-  // A piece has to hold what a tile is expected to mark, and six standard deviations where it shares them with others: up to
-  // about one in seven kept.
-  const float per_tile = runs < 1 ? 0.0f : (expect + chance) / (whole ? (float)len : sample) * fminf((float)kMarkTile, (float)len);
-  const uint32_t tile_end = (uint32_t)(sv.d.ntiles > 1 ? sv.d.e_lo + kMarkTile : sv.d.e_hi);
-  if (runs < 1 || per_tile + (sv.d.ntiles > 1 ? 6.0f * sqrtf(per_tile) : 0.0f) > (float)piece_room((uint32_t)sv.d.e_lo, tile_end))
-    return;  // (`info` has been cleared)
+  const SegSample of(sv.d.e_lo, sv.d.e_hi, k);
+  if (!of.has_pieces(sv.d.e_lo, sv.d.e_hi, sv.d.ntiles)) return;  // (`info` has been cleared)
+  const bool whole = of.whole;
+  const int64_t runs = of.runs, e_first = of.first;
+  const float sample = of.elements(), expect = of.expect;
   const int64_t stride = whole ? kSegRun : len / runs;
   uint32_t key[kSegRun];
   const uint32_t there = sample_keys<GT, kSegRun, T>(

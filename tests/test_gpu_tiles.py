@@ -161,6 +161,64 @@ def test_segmented_selection_alone(layout):
         assert np.array_equal(t.cpu().numpy(), x)
 
 
+def _parts(n, m):
+    return [n * i // m for i in range(m + 1)]
+
+
+# lengths and layouts on either side of the lines from which segments go by tiles, (offsets, one in so many kept of each): few
+# and many segments, one as long as all others together, and segments too dense for pieces: short ones, a part of the
+# elements, all of them, and all but one of very different sizes
+M = 1_000_000
+_DEFAULTS = {
+    "8.4m-two": ([0, 8_399_000, 8_400_000], None, 1),
+    "8.4m-three": (_parts(8_400_000, 3), None, 0),
+    "8.4m-half": ([0, 4_300_000, 6_000_000, 8_400_000], None, 1),
+    "8.3m-half": ([0, 8_000_000, 8_300_000], None, 0),
+    "11m-twenty": (_parts(11 * M, 20), None, 1),
+    "11m-fifty": (_parts(11 * M, 50), None, 0),
+    "16m-hundred": (_parts(16 * M, 100), None, 1),
+    "16m-many": (_parts(16 * M, 250), None, 0),
+    "16m-some-dense": (_parts(16 * M, 16), lambda i: 5 if i == 3 else 100, 0),
+    "16m-short-dense": ([0, 500, 1000, 16 * M], lambda i: 4 if i < 2 else 100, 1),
+    "16m-tile-dense": ([0, 2000, 16 * M], lambda i: 4 if i < 1 else 100, 0),
+    "26m-tile-dense": ([0, 16_000, 26 * M], lambda i: 4 if i < 1 else 100, 1),
+    "26m-tiles-dense": ([0, 26 * M, 26 * M + 33_000], lambda i: 4 if i > 0 else 100, 0),
+    "16m-one-in-eight": (_parts(16 * M, 8), lambda i: 8, 1),
+    "26m-some-dense": (_parts(26 * M, 8), lambda i: 5 if i == 3 else 100, 0),
+    "26m-all-dense": (_parts(26 * M, 8), lambda i: 5, 0),
+    "26m-half-kept": (_parts(26 * M, 8), lambda i: 2, 1),
+    "26m-uneven": ([0, 20 * M] + [20 * M + 200_000 * (i + 1) for i in range(30)], lambda i: 5, 1),
+    "26m-many": (_parts(26 * M, 520), lambda i: 5, 1),
+    "101m-some-dense": (_parts(101 * M, 8), lambda i: 5 if i == 3 else 100, 1),
+    "101m-more-dense": (_parts(101 * M, 8), lambda i: 5 if i % 2 else 100, 0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(_DEFAULTS))
+def test_which_segments_go_by_tiles(name):
+    """Without switches set; the results are those of the other route."""
+    import paper_2312_02493_amd as lib
+    import torch
+
+    off, one_in, tiles = _DEFAULTS[name]
+    ks = [-(-(b - a) // (one_in(i) if one_in else 100)) for i, (a, b) in enumerate(zip(off, off[1:]))]
+    n, k = off[-1], sum(ks)
+    x = torch.randn(n, generator=torch.Generator(device="cuda").manual_seed(9), device="cuda")
+    got = []
+    for guess_min_n in (None, 1 << 31 if tiles else 4096):
+        ctx = lib.Context(1, n, k, len(ks))
+        if guess_min_n:
+            ctx.set_option(lib.ARTOPK_OPT_GUESS_MIN_N, guess_min_n)
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        ctx.artopk_select_topk(x, k, idx, seg_off=off, seg_k=ks)
+        ctx.status()
+        got.append((ctx.select_info()["tiles"], idx))
+    assert (got[0][0], got[1][0]) == (tiles, 1 - tiles)
+    assert torch.equal(got[0][1], got[1][1])
+    a, b = off[-2], off[-1]
+    assert np.array_equal(got[0][1][k - ks[-1]:].cpu().numpy(), orc.topk_indices(x[a:b].cpu().numpy(), ks[-1]) + a)
+
+
 def test_what_select_info_says_behind_a_selection_in_one_launch():
     """A segmented selection takes many launches, whatever the call before it took."""
     import torch
