@@ -778,29 +778,32 @@ struct GuessPlan {
 GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, bool known) {
   GuessPlan gp;
   if (c->s.mask == nullptr || n < (known && !c->guess_min_n_set ? kTilesMinN : c->guess_min_n)) return gp;
+  int64_t runs = n / (4 * kGuessRun);  // at most a quarter of the vector
+  if (runs > 16384) runs = 16384;
+  if (runs < 256) return gp;
+  const double sample = (double)(runs * kGuessRun);
+  // keys of the sample expected above the true threshold, plus six standard deviations and a few
+  const double expect = (double)k * sample / (double)n;
+  const double margin = 6.0 * std::sqrt(expect) + 8.0;
+  gp.runs = (int)runs;
+  gp.stride = n / runs;
+  gp.m_hi = (uint32_t)std::ceil(expect + margin);
+  gp.m_mid = (uint32_t)std::max(1.0, expect + 0.5);
+  gp.m_lo = (uint32_t)std::max(1.0, expect - margin);
   // A leader known up front hands its marks on by tiles (k_mark_tiles), unless the option forbids it or a tile's piece
-  // would not hold its share: at most 1.3 k's, and six standard deviations.  Very sparse selections on very long vectors do
+  // would not hold its share of what reaches the bound, and six standard deviations: up to one in seven kept (histogram
+  // route / tiles, us a step, one in eight 12.6 M x 2 167/162, 25.6 M x 2 270/239, 138 M x 2 1358/948, x 4 1980/1585, one in
+  // seven 171/166, 280/250, 1425/1027, 2051/1654).  Very sparse selections on very long vectors do
   // without, as the mask then is the smaller thing to write (histogram route / mask / tiles, us a step: 138 M x 4, one in
   // 3000 kept 1386/1266/1269, in 1000 1396/1282/1264, in 250 1419/1321/1269, in 100 1468/1413/1294; 400 M x 2, one in 3000
   // 2324/1978/2039, in 1000 2354/2011/2027, in 500 2395/2081/2032; 25.6 M x 4, one in 1000 304/306/280, in 100
   // 316/323/290; below kTilesMinN see there).
-  const double per_tile = 1.3 * (double)k * (double)kMarkTile / (double)n;
+  const double per_tile = (double)gp.m_hi / sample * (double)kMarkTile;
   const bool worth = c->stage_tiles == 2 || n < ((int64_t)1 << 28) || k * 700 >= n;
-  gp.tiles = c->stage_tiles != 0 && known && worth && per_tile + 6.0 * std::sqrt(per_tile) + 32.0 <= (double)kMarkMax;
+  gp.tiles = c->stage_tiles != 0 && known && worth && per_tile + 6.0 * std::sqrt(per_tile) <= (double)kMarkMax;
   // A selection of more than one element in 32 is not worth fetching entry by entry from the mask; nor is the mask on
   // vectors that the tiles alone would take.
   if (!gp.tiles && (k * 32 > n || n < c->guess_min_n)) return gp;
-  int64_t runs = n / (4 * kGuessRun);  // at most a quarter of the vector
-  if (runs > 16384) runs = 16384;
-  if (runs < 256) return gp;
-  gp.runs = (int)runs;
-  gp.stride = n / runs;
-  // keys of the sample expected above the true threshold, plus six standard deviations and a few
-  const double expect = (double)k * (double)(runs * kGuessRun) / (double)n;
-  const double margin = 6.0 * std::sqrt(expect) + 8.0;
-  gp.m_hi = (uint32_t)std::ceil(expect + margin);
-  gp.m_mid = (uint32_t)std::max(1.0, expect + 0.5);
-  gp.m_lo = (uint32_t)std::max(1.0, expect - margin);
   gp.on = (int64_t)gp.m_hi <= runs * kGuessRun;
   gp.tiles = gp.tiles && gp.on;
   return gp;

@@ -81,7 +81,18 @@ def _steps(w, n, k, mode, gen, steps=2, seg_off=None, seg_k=None, max_k=None, bo
 @pytest.mark.parametrize("rho", [0.001, 0.02, 0.12])
 def test_flat_lengths(n, rho):
     rng = np.random.default_rng(n)
-    _steps(2, n, max(1, int(n * rho)), orc.MODE_STAR, lambda s, r: _values("normal", n, rng), bounds=1 if rho < 0.12 else "other")
+    # (one tile's sample is too small to say that one in eight fits a piece)
+    bounds = "other" if (n, rho) == (16384, 0.12) else 1
+    _steps(2, n, max(1, int(n * rho)), orc.MODE_STAR, lambda s, r: _values("normal", n, rng), bounds=bounds)
+
+
+@pytest.mark.parametrize("one_in,tiles", [(8, 1), (7, 1), (6.5, 0)])
+def test_flat_density(one_in, tiles):
+    """Up to one in seven kept a piece holds a tile's share."""
+    n = 33 * TILE + 31
+    rng = np.random.default_rng(11)
+    runner = _steps(2, n, int(n / one_in), orc.MODE_STAR, lambda s, r: _values("normal", n, rng), bounds=1 if tiles else "other")
+    assert gpu_util.FORCED or runner.ctx.select_info()["tiles"] == tiles
 
 
 @pytest.mark.parametrize("kind", ["equal", "zeros", "ties", "run", "sorted", "narrow", "steps", "odd"])
