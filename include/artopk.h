@@ -162,7 +162,7 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 (from which a list is built by fetching the
  *                                 marked values one by one).  1 (default):
  *                                 except for selections sparser than one element
- *                                 in 700 of 2^28 or more; 2: for every selection
+ *                                 in 500 of 5 2^25 or more; 2: for every selection
  *                                 up to about one in seven; 0: never.  (Flat
  *                                 selections only: segments have no mask)
  *   ARTOPK_OPT_SHORT_MAX_N        longest flat vector whose step runs in one

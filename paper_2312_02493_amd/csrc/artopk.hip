@@ -793,13 +793,14 @@ GuessPlan plan_guess(const artopk_ctx* c, int64_t n, int64_t k, bool known) {
   // A leader known up front hands its marks on by tiles (k_mark_tiles), unless the option forbids it or a tile's piece
   // would not hold its share of what reaches the bound, and six standard deviations: up to one in seven kept (histogram
   // route / tiles, us a step, one in eight 12.6 M x 2 167/162, 25.6 M x 2 270/239, 138 M x 2 1358/948, x 4 1980/1585, one in
-  // seven 171/166, 280/250, 1425/1027, 2051/1654).  Very sparse selections on very long vectors do
-  // without, as the mask then is the smaller thing to write (histogram route / mask / tiles, us a step: 138 M x 4, one in
-  // 3000 kept 1386/1266/1269, in 1000 1396/1282/1264, in 250 1419/1321/1269, in 100 1468/1413/1294; 400 M x 2, one in 3000
-  // 2324/1978/2039, in 1000 2354/2011/2027, in 500 2395/2081/2032; 25.6 M x 4, one in 1000 304/306/280, in 100
-  // 316/323/290; below kTilesMinN see there).
+  // seven 171/166, 280/250, 1425/1027, 2051/1654).  Very sparse selections on very long vectors do without, as the mask then is
+  // the smaller thing to write (histogram route / mask / tiles, us a step: 138 M x 4, one in 3000 kept 1386/1266/1269, in
+  // 1000 1396/1282/1264, in 250 1419/1321/1269, in 100 1468/1413/1294; mask / tiles, x 2, one in 3000, 1000, 700, 500 and 250,
+  // 180 M 923/934 934/937 939/944 949/947 991/948, 220 M 1117/1144 1140/1144 1148/1150 1152/1156 1216/1159, 268 M 1362/1387
+  // 1355/1389 1368/1399 1379/1400 1464/1403, 300 M 1518/1557 1530/1554 1536/1553 1553/1562 1657/1571; 25.6 M x 4, one in 1000
+  // 306/280, in 100 323/290; below kTilesMinN see there).
   const double per_tile = (double)gp.m_hi / sample * (double)kMarkTile;
-  const bool worth = c->stage_tiles == 2 || n < ((int64_t)1 << 28) || k * 700 >= n;
+  const bool worth = c->stage_tiles == 2 || n < ((int64_t)5 << 25) || k * 500 >= n;
   gp.tiles = c->stage_tiles != 0 && known && worth && per_tile + 6.0 * std::sqrt(per_tile) <= (double)kMarkMax;
   // A selection of more than one element in 32 is not worth fetching entry by entry from the mask; nor is the mask on
   // vectors that the tiles alone would take.

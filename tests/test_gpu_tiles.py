@@ -105,6 +105,29 @@ def test_flat_values(kind, rho):
     _steps(2, n, int(n * rho), orc.MODE_STAR, lambda s, r: _values(kind, n, rng), steps=1 if kind == "odd" else 2, bounds=bounds)
 
 
+@pytest.mark.parametrize("n,one_in,tiles", [(167_700_000, 3000, 1), (167_900_000, 3000, 0), (167_900_000, 499, 1)])
+def test_long_sparse_steps_leave_the_mask_instead(n, one_in, tiles):
+    """Without switches set; the result is the other route's."""
+    import paper_2312_02493_amd as lib
+    import torch
+
+    k = n // one_in
+    g = torch.randn(n, generator=torch.Generator(device="cuda").manual_seed(10), device="cuda")
+    got = []
+    for stage_tiles in (1, 2 - 2 * tiles):
+        ctx = lib.Context(1, n, k)
+        ctx.set_option(lib.ARTOPK_OPT_STAGE_TILES, stage_tiles)
+        res, idx, total = torch.zeros(n, device="cuda"), torch.full((k,), -1, dtype=torch.int32, device="cuda"), torch.zeros(k, device="cuda")
+        ctx.artopk_step([g], [res], k, orc.MODE_STAR, 1, idx, total, None)
+        ctx.status()
+        info = ctx.select_info()
+        assert (info["guessed"], info["from_mask"]) == (1, 1)
+        got.append((info["tiles"], idx, total, res))
+    assert (got[0][0], got[1][0]) == (tiles, 1 - tiles)
+    assert all(torch.equal(a, b) for a, b in zip(got[0][1:], got[1][1:]))
+    assert torch.equal(got[0][2], g[got[0][1].long()]) and int((got[0][3] == 0).sum()) >= k
+
+
 def _layout(name):
     if name == "buckets":  # whole tiles, the last one ragged
         return [0, 4 * TILE, 8 * TILE, 12 * TILE, 14 * TILE + 77]
