@@ -1053,8 +1053,10 @@ int enqueue_select(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n
   return ARTOPK_OK;
 }
 
-// A vector that is only read by tiles comes through the caches up to this length: what gathers from it next then finds some
-// of its lines there (25.6 M x 8, variance rule, gather 96 us behind non-temporal loads, 86 behind ordinary ones).
+// A vector that is only read by tiles comes through the caches up to this length: the next selection on it may find it there
+// (ordinary / non-temporal loads, us, one in a hundred, 54 segments: 25.6 M 81/81, 40 M 92/96, 60 M 107/112, 67 M 117/120,
+// 80 M 134/130, 100 M 156/150, 138 M 198/187).  A step is the same either way (variance rule, x 8, 25.6 M 602/597, 60 M
+// 1302/1292, 67 M 1436/1430, 80 M 1704/1702).
 constexpr int64_t kCachedMaxN = (int64_t)1 << 26;
 
 // The bounds and the marking.
