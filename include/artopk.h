@@ -163,8 +163,10 @@ int64_t artopk_scratch_bytes(int32_t max_w, int64_t max_n, int64_t max_k, int32_
  *                                 marked values one by one).  1 (default):
  *                                 except for selections sparser than one element
  *                                 in 500 of 5 2^25 or more; 2: for every selection
- *                                 up to about one in seven; 0: never.  (Flat
- *                                 selections only: segments have no mask)
+ *                                 up to about one in seven; 0: never.  Long
+ *                                 segmented selections (ARTOPK_OPT_GUESS_MIN_N)
+ *                                 hand them on so, too, under 1 and 2, and
+ *                                 under 0 are made from histograms
  *   ARTOPK_OPT_SHORT_MAX_N        longest flat vector whose step runs in one
  *                                 launch (two under ARTOPK_STAR_COUNTER); three
  *                                 quarters of it where the leader is found on the device (the

@@ -158,8 +158,8 @@ struct artopk_ctx {
   bool guess_min_n_set = false;  // by artopk_set_option: then it holds for vectors that are only read, too
   // vectors of at least this many elements get their dense update from k_update_tiles
   int64_t update_tiles_min_n = (int64_t)1 << 22;
-  int stage_tiles = 1;  // guess route, one marking worker: the marked elements are handed on by tiles (0 never, 1 where that
-                        // is the better way, 2 whenever a piece can hold a tile's share)
+  int stage_tiles = 1;  // marked elements are handed on by tiles: 0 never, 1 where that is the better way, 2 (flat vectors)
+                        // whenever a piece can hold a tile's share
   int64_t small_max_n = kSmallMaxN;  // flat steps of up to about this many elements run in one launch
   bool small_max_n_set = false;      // by artopk_set_option: then however many workers there are
   void* slab = nullptr;
@@ -439,9 +439,9 @@ int32_t more_bins(const artopk_ctx* c, int32_t ntiles, int32_t tiles, int32_t ha
   return kTileWords * (int64_t)tiles + 64 + (int64_t)(have + want) * kHistBins <= words ? want : 0;
 }
 
-// Whether a segmented selection goes by tiles (a guess length that was set holds for these, too).
+// Whether a segmented selection goes by tiles (switches that were set hold for these, too).
 bool segments_by_tiles(const artopk_ctx* c, const Plan& pl, int64_t n) {
-  if (pl.tiles == 0) return false;
+  if (pl.tiles == 0 || c->stage_tiles == 0) return false;
   if (c->guess_min_n_set) return n >= c->guess_min_n;
   if (n < kSegTilesBareN)
     return !pl.some_bare && ((n >= kSegTilesMinN && pl.longest * 2 > n) ||

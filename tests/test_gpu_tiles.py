@@ -253,6 +253,33 @@ def test_which_segments_go_by_tiles(name):
     assert np.array_equal(got[0][1][k - ks[-1]:].cpu().numpy(), orc.topk_indices(x[a:b].cpu().numpy(), ks[-1]) + a)
 
 
+@pytest.mark.parametrize("stage_tiles", [0, 1, 2])
+def test_the_switch_holds_for_segments(stage_tiles):
+    import paper_2312_02493_amd as lib
+    import torch
+
+    off = _layout("layers")
+    n, ks = off[-1], [max(1, (b - a) // 50) for a, b in zip(off, off[1:])]
+    k = sum(ks)
+    ctx = gpu_util.make_context(2, n, k, len(ks))
+    ctx.set_option(lib.ARTOPK_OPT_STAGE_TILES, stage_tiles)
+    x = _values("normal", n, np.random.default_rng(12))
+    t = torch.from_numpy(x).cuda()
+    idx, total = torch.zeros(k, dtype=torch.int32, device="cuda"), torch.zeros(k, device="cuda")
+    want = np.concatenate([orc.topk_indices(x[a:b], m) + a for a, b, m in zip(off, off[1:], ks)])
+    for call in ("select", "var", "star"):
+        idx.fill_(-1)
+        if call == "select":
+            ctx.artopk_select_topk(t, k, idx, seg_off=off, seg_k=ks)
+        else:
+            res = [torch.zeros(n, device="cuda") for _ in range(2)]
+            ctx.artopk_step([0.5 * t, t], res, k, orc.MODE_VAR if call == "var" else orc.MODE_STAR, 1, idx, total, None,
+                            seg_off=off, seg_k=ks)
+        ctx.status()
+        assert ctx.select_info()["tiles"] == (1 if stage_tiles else 0), call
+        assert np.array_equal(idx.cpu().numpy(), want)
+
+
 def test_what_select_info_says_behind_a_selection_in_one_launch():
     """A segmented selection takes many launches, whatever the call before it took."""
     import torch
