@@ -1124,8 +1124,7 @@ int enqueue_tiles(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n,
   if (g != nullptr) prof_mark(c, 1);
   hipLaunchKernelGGL(k_tiles_pick, dim3((unsigned)pl.nseg), dim3(1024), 0, c->stream, p, a);
   hipLaunchKernelGGL(k_tiles_full, dim3((unsigned)std::min<int32_t>(a.ntiles, 2 * c->num_cu)), dim3(kMarkThreads), 0, c->stream, p, a);
-  // (a block's tiles apart: each wave adds up what is in front of its own, which long vectors have too many tiles for)
-  if (a.ntiles <= 4096)
+  if (a.ntiles <= kTilesApart)
     launch_tiles_rest<true>(c, p, a);
   else
     launch_tiles_rest<false>(c, p, a);

@@ -3803,6 +3803,13 @@ __host__ __device__ constexpr uint32_t piece_room(uint32_t lo, uint32_t hi) {
   return room < (int64_t)kMarkMax ? (uint32_t)room : (uint32_t)kMarkMax;
 }
 static_assert(piece_at(kMarkTile) >= kMarkMax, "a whole tile's marks are bounded by what fits on chip");
+// Up to so many tiles a block's lie apart (few in the build for tests, so that both forms run on short vectors): each wave then
+// adds up what is in front of its own, which long vectors have too many tiles for.
+#ifdef ARTOPK_HELD_BLOCKS
+constexpr int kTilesApart = 16;
+#else
+constexpr int kTilesApart = 4096;
+#endif
 constexpr int kTileWaves = 4;  // waves, and tiles, of a block of the kernels behind the marking; and parts of a tile without a piece
 constexpr int kTileSlots = 4;
 constexpr uint32_t kTileOverflow = 0xffffffffu;
@@ -4026,6 +4033,7 @@ k_guess_tiles(const float* __restrict__ gp, const float* __restrict__ rp, uint32
   __shared__ uint32_t res[4];
   __shared__ int sh;
   const int tid = threadIdx.x;
+  meet_start();
   uint32_t* __restrict__ ctrl = slot + kSlotCtrl;
   uint32_t key[kGuessRun];
   const uint32_t there = sample_keys<GT, kGuessRun, T>(
@@ -4040,7 +4048,8 @@ k_guess_tiles(const float* __restrict__ gp, const float* __restrict__ rp, uint32
   __syncthreads();
   if (tid == 0) {
     __hip_atomic_fetch_add(&ctrl[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int i = 0; i < kGuessLooks && sh == 0; ++i) sh = load_through(&ctrl[0]) == gridDim.x ? 1 : 0;
+    const int looks = meet_limit() < kGuessLooks ? meet_limit() : kGuessLooks;
+    for (int i = 0; i < looks && sh == 0; ++i) sh = load_through(&ctrl[0]) == gridDim.x ? 1 : 0;
   }
   __syncthreads();
   if (sh == 0) return;

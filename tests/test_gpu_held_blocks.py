@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import artopk_oracle as orc
+from tests import gpu_util, test_gpu_tiles
 from tests.gpu_util import GpuRunner, assert_step_matches, bits
 
 pytestmark = pytest.mark.gpu
@@ -117,6 +118,68 @@ def test_selections_of_whole_vectors(held, kind, guess, from_mask):
             want = orc.topk_indices(xs[r], k)
             assert np.array_equal(idx[r].cpu().numpy(), want)
             assert np.array_equal(bits(vals[r].cpu().numpy()), bits(xs[r][want]))
+
+
+@pytest.fixture
+def tiles_on(held, monkeypatch):
+    for name, value in (("guess_min_n", 4096), ("stage_tiles", 2), ("short_max_n", 0)):
+        monkeypatch.setitem(gpu_util.OPTIONS, name, value)
+    return held
+
+
+# the sample of a selection by tiles waits for its blocks once: late ones, none that waits at all, and one look each, so that
+# most leave and the last ones still pick (nobody is the last one through, then); a vector without a bound is an ordinary one
+@pytest.mark.parametrize("ticks,looks,bound", [(LATE, LOOKS, 1), (0, -1, 0), (LATE, -1, 0), (LATE, 1, 0)])
+@pytest.mark.parametrize("kind", ["normal", "ties"])
+def test_sample_of_marked_tiles(tiles_on, ticks, looks, bound, kind):
+    rng = np.random.default_rng(looks & 7)
+    n, w = 1_100_003, 2
+    k = n // 60
+    runner = GpuRunner(w, n, k)
+    res = [np.zeros(n, np.float32) for _ in range(w)]
+    runner.load_res(res)
+    for step_no in (1, 2, 3):
+        g = [_values(rng, n, kind, r) for r in range(w)]
+        want = orc.step(g, res, k, orc.MODE_STAR, step_no=step_no)
+        runner.load_g(g)
+        tiles_on(ticks if step_no != 2 else 0, looks if step_no != 2 else LOOKS)
+        assert_step_matches(runner.step(k, orc.MODE_STAR, step_no), want, orc.MODE_STAR)
+        info = runner.ctx.select_info()
+        assert (info["tiles"], info["from_mask"]) == (1, bound if step_no != 2 else 1), (step_no, info)
+        res = want.residual
+
+
+# the form for many tiles, a block's side by side (here from 17 on): flat and in segments, whose blocks' counts begin behind
+# other segments', with tiles that have no piece, bounds that do not hold and none
+# (under the variance rule flat selections do not go by tiles, and who leads has to be beyond doubt)
+_BESIDE = [(layout, kind, mode) for layout in (None, "buckets", "layers", "two", "edges")
+           for kind in ("normal", "equal", "zeros", "ties", "run", "sorted", "steps", "odd") for mode in ("star", "var")
+           if mode == "star" or (layout is not None and kind not in ("equal", "odd"))]
+
+
+@pytest.mark.parametrize("layout,kind,mode", _BESIDE)
+def test_tiles_side_by_side(tiles_on, layout, kind, mode):
+    tiles_on(0, LOOKS)
+    off = test_gpu_tiles._layout(layout) if layout else None
+    n = off[-1] if off else 21 * 32768 + 3
+    ks = [max(1, (b - a) // 40) for a, b in zip(off, off[1:])] if off else None
+    rng = np.random.default_rng(14)
+    scale = (1.0, 1.5) if mode == "var" else (1.0, 1.0)
+    test_gpu_tiles._steps(2, n, sum(ks) if ks else n // 40, orc.MODE_STAR if mode == "star" else orc.MODE_VAR,
+                          lambda s, r: test_gpu_tiles._values(kind, n, rng) * np.float32(scale[r]), steps=1 if kind == "odd" else 2,
+                          seg_off=off, seg_k=ks)
+
+
+@pytest.mark.parametrize("dense", [20, 5, 2])
+def test_tiles_side_by_side_of_dense_segments(tiles_on, dense):
+    tiles_on(0, LOOKS)
+    off = test_gpu_tiles._layout("layers")
+    n, ks = off[-1], [-(-(b - a) // (dense if i % 2 else 50)) for i, (a, b) in enumerate(zip(off, off[1:]))]
+    rng = np.random.default_rng(15)
+    runner = test_gpu_tiles._steps(2, n, sum(ks), orc.MODE_STAR, lambda s, r: _values(rng, n, "normal", r), seg_off=off, seg_k=ks)
+    runner.load_res([np.zeros(n, np.float32)] * 2)
+    names = test_gpu_tiles._kernels_of(lambda: runner.step(sum(ks), orc.MODE_STAR, 1, seg_off=off, seg_k=ks))
+    assert any("k_tiles_out<false>" in s for s in names), names
 
 
 # beside a stream of copies most blocks start late: with a long wait before each unit that the others take on, a
