@@ -427,8 +427,14 @@ Plan flat_plan(const artopk_ctx* c, int64_t n, int64_t k, int32_t vec = -1, bool
   return pl;
 }
 
-// Words of TileArgs' tables for every tile, and where the further copies of segments' bins lie behind them.
-constexpr int kTileWords = 6 + (2 + kTileSlots) * kTileWaves;
+// TileArgs' tables, one behind the other: where each begins, in words for every tile (kept has two of 64 bits: a tile's, and
+// there are no more blocks than tiles), and where the further copies of segments' bins lie behind them all.
+constexpr int kTileHeldAt = 4, kTileMarkedAt = kTileHeldAt + 1, kTileAboveAt = kTileMarkedAt + 1;
+constexpr int kTileAmongAt = kTileAboveAt + kTileWaves, kTileSlotsAt = kTileAmongAt + kTileWaves;
+constexpr int kTileWords = kTileSlotsAt + kTileSlots * kTileWaves;
+static_assert((((int64_t)1 << 31) / kMarkTile + 2) * kTileWords < (int64_t)kMaxChunks * kHistBins,
+              "one worker's S has room for them (that of each segment takes its two tiles more)");
+static_assert(2 * kTileWords < kHistBins, "see there");
 uint32_t* tile_more_bins(const artopk_ctx* c, int32_t tiles) { return c->s.S + (kTileWords * (size_t)tiles + 63) / 64 * 64; }
 
 // Further copies of the bins of a segment of `ntiles` tiles where the layout has `tiles` and `have` copies already: one for
@@ -1101,13 +1107,13 @@ int enqueue_tiles(artopk_ctx* c, const Plan& pl, const PtrTable& tab, int64_t n,
   a.map = pl.use_table ? s.tile_map : nullptr;
   a.groups = pl.use_table ? reinterpret_cast<const uint2*>(s.tile_map + s.map_tiles) : nullptr;
   a.pieces = s.tilebuf;
-  // (nobody else has anything in S's memory now: 16.8 MB at least and 16 KB for every segment, for kTileWords a tile)
+  // (nobody else has anything in S's memory now)
   a.kept = reinterpret_cast<uint64_t*>(s.S);
-  a.held = s.S + 4 * (size_t)a.ntiles;  // (no more blocks than tiles)
-  a.marked = a.held + a.ntiles;
-  a.above = a.marked + a.ntiles;
-  a.among = a.above + (size_t)kTileWaves * a.ntiles;
-  a.slots = a.among + (size_t)kTileWaves * a.ntiles;
+  a.held = s.S + kTileHeldAt * (size_t)a.ntiles;
+  a.marked = s.S + kTileMarkedAt * (size_t)a.ntiles;
+  a.above = s.S + kTileAboveAt * (size_t)a.ntiles;
+  a.among = s.S + kTileAmongAt * (size_t)a.ntiles;
+  a.slots = s.S + kTileSlotsAt * (size_t)a.ntiles;
   a.bins = pl.use_table ? s.zero_base + kSegHtop : s.h_all;
   a.bins_stride = pl.use_table ? kSegWords : 0;
   a.more_bins = pl.use_table ? tile_more_bins(c, a.ntiles) : s.h_all + kHistBins;
@@ -2023,8 +2029,8 @@ int step_impl(artopk_ctx* ctx, const float* const* g, int32_t g_type, float* con
   const int pass_nblk = by_tile ? tile_nblk : (int)geom.nchunks;
   const dim3 grid(pass_nblk, w);
 
-  // a long segmented vector: the fused pass strides over the tiles as on the guess route (the
-  // selection builds the segments' histograms from the leader's vector afterwards either way)
+  // a long segmented vector whose leader is found on the device: the fused pass strides over the tiles as on the guess
+  // route (the selection reads the leader's vector again either way, by tiles or for its segments' histograms)
   const bool seg_stride = segmented && n >= ctx->guess_min_n;
   const bool by_tiles = segmented && segments_by_tiles(ctx, *pl, n);
 
