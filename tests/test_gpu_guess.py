@@ -25,8 +25,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.fixture(params=["pieces", "mask_only"])
 def guess_on(monkeypatch, request):
-    """The guess route on short vectors, in both of its forms for a leader known up front: the
-    fused pass hands the marked elements on tile by tile (the default), or leaves only the mask."""
+    """The guess route on short vectors, in both of its forms for a leader known up front: its
+    marks are handed on tile by tile (the default), or the fused pass leaves only the mask."""
     monkeypatch.setitem(gpu_util.OPTIONS, "guess_min_n", 4096)
     monkeypatch.setitem(gpu_util.OPTIONS, "stage_tiles", 2 if request.param == "pieces" else 0)
 
@@ -270,7 +270,8 @@ def test_guess_leader_from_the_data_keeps_to_the_masks_lines(monkeypatch, mode, 
 
 @pytest.mark.parametrize("n", [16_384, 32_768, 32_769, 3 * 32_768 + 2, 9 * 32_768 - 1, 17 * 32_768 + 131])
 def test_guess_pieces_ragged_lengths(guess_on, n):
-    """Vector lengths around the tile and slab borders of the staged pieces (a slab is eight tiles)."""
+    """Vector lengths around the borders of the fused pass' tiles, which are two of the pieces', and
+    of the mask's slabs of 1024 rows (eight of them)."""
     w = 2
     wl = inp.workload(1, n=n, w=w)
     k = max(1, n // 200)
@@ -303,8 +304,8 @@ def test_guess_pieces_dense_keep(guess_on, rho):
 
 @pytest.mark.parametrize("where", ["one_tile_overflows", "every_eighth_tile_overflows", "all_in_last_tile"])
 def test_guess_pieces_tiles_with_more_marks_than_a_piece_holds(guess_on, where):
-    """Tiles whose marks exceed the piece size report an overflow and their slab is built from the
-    mask, next to slabs built from pieces."""
+    """Tiles whose marks exceed the piece size have none: waves read parts of them from the vector,
+    next to tiles read from their pieces."""
     n, w, k = 37 * 32768 + 77, 2, 6_000
     rng = np.random.default_rng(31)
 
