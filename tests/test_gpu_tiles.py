@@ -310,7 +310,10 @@ def _kernels_of(call):
     with profile(activities=[ProfilerActivity.CUDA]) as prof:
         call()
         torch.cuda.synchronize()
-    return [e.key for e in prof.key_averages()]
+    names = [e.key for e in prof.key_averages()]
+    if not names:
+        pytest.skip("no kernel trace here")
+    return names
 
 
 def test_the_map_of_a_layouts_tiles_is_made_when_it_is_first_wanted():
